@@ -4,11 +4,13 @@
 // the per-channel parameter, which is block-uniform in the row kernels and so lives
 // in scalar registers.  The reduction reads the tensor once.
 //
-// Two launch shapes per operator:
-//   rows : one workgroup per (row = outer*channels index, segment of inner);
-//          128-bit loads/stores; parameters fetched once per workgroup.
-//   flat : one element per lane with the channel recovered by division; used
-//          for short or unaligned rows (e.g. channel-last tensors).
+// Three launch shapes per operator, all with 128-bit accesses:
+//   rows     : one workgroup per (row = outer*channels index, segment of inner); the channel's
+//              parameters are fetched once per workgroup.  Aligned rows of 512 elements or more.
+//   periodic : short or ragged rows (channel-last tensors among them) whose pattern of channels comes
+//              back within the tensor: a lane keeps the same four channels' parameters over many vectors.
+//   flat     : the rest (the pattern comes back fewer than four times): four consecutive elements per
+//              vector, their channels found with one multiply-high division.
 #include "hago_device.h"
 #include "launch.h"
 
@@ -245,44 +247,11 @@ __global__ __launch_bounds__(kThreads) void simquant_batched_rows_kernel(
   }
 }
 
-__global__ __launch_bounds__(kThreads) void simquant_batched_flat_kernel(
-    const float* __restrict__ x, float* __restrict__ y, int64_t total, int64_t inner,
-    int64_t channels, int32_t nbatch, int32_t nparam, const float* __restrict__ scale,
-    const int32_t* __restrict__ zp, int per_channel, CandidateClips clips) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += stride) {
-    const int64_t c = per_channel ? (i / inner) % channels : 0;
-    const float v = x[i];
-    for (int b = 0; b < nbatch; ++b)
-      y[(int64_t)b * total + i] = simquant_one(v, scale[(int64_t)b * nparam + c],
-                                               (float)zp[(int64_t)b * nparam + c], clips.lo[b],
-                                               clips.hi[b]);
-  }
-}
-
-template <bool WRAP = false>
-__global__ __launch_bounds__(kThreads) void simquant_flat_kernel(
-    const float* __restrict__ x, float* __restrict__ y, int64_t total, int64_t inner,
-    int64_t channels, const float* __restrict__ scale, const int32_t* __restrict__ zp,
-    int per_channel, float lo, float hi, int wrap_bits = 0, int wrap_signed = 0) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += stride) {
-    const int64_t c = per_channel ? (i / inner) % channels : 0;
-    if constexpr (WRAP) y[i] = simquant_wrap_of(rintf(x[i] / scale[c]), scale[c], (float)zp[c], lo, hi, wrap_bits, wrap_signed);
-    else y[i] = simquant_one(x[i], scale[c], (float)zp[c], lo, hi);
-  }
-}
-
 // AWAY: the launch's tie rule is halves away from zero (the general form); else the plain one.
 template <bool AWAY>
 __device__ __forceinline__ int32_t requant_pick(int32_t acc, int32_t mult, int32_t sh, const RequantScalars& rs) {
   if constexpr (AWAY) return requant_half_away(acc, mult, sh, rs);
   else return requant_one(acc, mult, sh, rs);
-}
-
-template <typename AccT>
-__device__ __forceinline__ int32_t load_acc(const AccT* p, int64_t i) {
-  return (int32_t)p[i];
 }
 
 // rows: 4 accumulators -> 4 output bytes per step, 128-bit loads for int32; U steps per lane
@@ -322,42 +291,6 @@ __global__ __launch_bounds__(kThreads) void requant_rows_kernel(
         }
       }
     }
-  }
-}
-
-// channel-last (inner == 1) with channels % 4 == 0: 4 consecutive channels.
-template <typename AccT, bool AWAY>
-__global__ __launch_bounds__(kThreads) void requant_lastaxis_kernel(
-    const AccT* __restrict__ acc, uint32_t* __restrict__ out, int64_t total_vec,
-    int32_t channels_vec, const int4* __restrict__ mult, const int4* __restrict__ shift,
-    RequantScalars rs) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x; v < total_vec; v += stride) {
-    const int32_t cv = (int32_t)(v % channels_vec);
-    const int4 m = mult[cv];
-    const int4 sh = shift[cv];
-    int32_t a0, a1, a2, a3;
-    if constexpr (sizeof(AccT) == 4) {
-      const int4 q = reinterpret_cast<const int4*>(acc)[v];
-      a0 = q.x; a1 = q.y; a2 = q.z; a3 = q.w;
-    } else {
-      const short4 q = reinterpret_cast<const short4*>(acc)[v];
-      a0 = q.x; a1 = q.y; a2 = q.z; a3 = q.w;
-    }
-    out[v] = pack4(requant_pick<AWAY>(a0, m.x, sh.x, rs), requant_pick<AWAY>(a1, m.y, sh.y, rs),
-                   requant_pick<AWAY>(a2, m.z, sh.z, rs), requant_pick<AWAY>(a3, m.w, sh.w, rs));
-  }
-}
-
-template <typename AccT, bool AWAY>
-__global__ __launch_bounds__(kThreads) void requant_flat_kernel(
-    const AccT* __restrict__ acc, uint8_t* __restrict__ out, int64_t total, int64_t inner,
-    int64_t channels, const int32_t* __restrict__ mult, const int32_t* __restrict__ shift,
-    int per_channel, RequantScalars rs) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += stride) {
-    const int64_t c = per_channel ? (i / inner) % channels : 0;
-    out[i] = (uint8_t)requant_pick<AWAY>(load_acc(acc, i), rq_mult(mult, c), rq_shift(mult, shift, c), rs);
   }
 }
 
@@ -476,22 +409,406 @@ __global__ __launch_bounds__(kThreads) void quant_rows_kernel(
   }
 }
 
-template <typename Q, int OP>
-__global__ __launch_bounds__(kThreads) void quant_flat_kernel(
-    const void* __restrict__ in, void* __restrict__ out, float* __restrict__ out2, int64_t total, int64_t inner,
-    int64_t channels, const float* __restrict__ scale, const int32_t* __restrict__ zp,
-    int per_channel, float lo, float hi) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < total; i += stride) {
-    const int64_t c = per_channel ? (i / inner) % channels : 0;
+// ---- short, ragged and channel-last rows.  An operator of this section names how four consecutive
+// elements are loaded, what a channel's parameters are and how they are applied; the two kernels below
+// find the channels.  The vectors carry the element type's alignment only, so a tensor that starts
+// anywhere takes the same code (global accesses of gfx950 may be unaligned).
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t v4i32_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef int16_t v4i16_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+
+template <typename T> struct AnyVec;  // four T as one access of T's alignment
+template <> struct AnyVec<float> { typedef v4f_any T; };
+template <> struct AnyVec<int32_t> { typedef v4i32_any T; };
+template <> struct AnyVec<int16_t> { typedef v4i16_any T; };
+template <> struct AnyVec<int8_t> { typedef u32_any T; };
+template <> struct AnyVec<uint8_t> { typedef u32_any T; };
+
+template <typename T>
+__device__ __forceinline__ auto load4(const T* p, int64_t i) {
+  return __builtin_nontemporal_load(reinterpret_cast<const typename AnyVec<T>::T*>(p + i));
+}
+template <typename T, typename V>
+__device__ __forceinline__ void store4(T* p, int64_t i, V v) {
+  __builtin_nontemporal_store((typename AnyVec<T>::T)v, reinterpret_cast<typename AnyVec<T>::T*>(p + i));
+}
+
+// s, z and (RC) the reciprocal of s for fast_quotient4; without it the division is taken at once.
+struct ScaleZero {
+  float s, zf, rc;
+};
+
+template <bool RC>
+__device__ __forceinline__ ScaleZero scale_zero(const float* scale, const int32_t* zp, int64_t c) {
+  const float s = scale[c];
+  return ScaleZero{s, (float)zp[c], RC ? quotient_reciprocal(s) : 0.0f};
+}
+
+// The four rounded quotients; returns whether all are known to be finite.
+template <bool RC>
+__device__ __forceinline__ bool quotients4(v4f x, const ScaleZero (&p)[4], v4f& n) {
+  if constexpr (RC) {
+    bool ok = true;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float qt = x[e] * p[e].rc;
+      n[e] = rintf(qt);
+      ok = ok && (fabsf(qt - n[e]) < __builtin_fmaf(fabsf(qt), -0x1p-21f, 0.5f));  // as in fast_quotient4
+    }
+    if (__builtin_expect(ok, 1)) return true;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) n[e] = rintf(x[e] / p[e].s);
+  return false;
+}
+
+template <bool WRAP, bool RC>
+struct SimquantOp {
+  typedef v4f Vec;
+  typedef ScaleZero Par;
+  const float* x;
+  float* y;
+  const float* scale;
+  const int32_t* zp;
+  float lo, hi;
+  int wrap_bits, wrap_signed;
+  __device__ Par par(int64_t c) const { return scale_zero<RC>(scale, zp, c); }
+  __device__ Vec load(int64_t i) const { return load4(x, i); }
+  __device__ float of(float u, const Par& p) const {
+    if constexpr (WRAP) return simquant_wrap_of(u, p.s, p.zf, lo, hi, wrap_bits, wrap_signed);
+    else return simquant_of(u, p.s, p.zf, lo, hi);
+  }
+  __device__ void four(int64_t i, Vec v, const Par (&p)[4]) const {
+    v4f n;
+    quotients4<RC>(v, p, n);
+    store4(y, i, v4f{of(n.x, p[0]), of(n.y, p[1]), of(n.z, p[2]), of(n.w, p[3])});
+  }
+  __device__ void one(int64_t i, const Par& p) const { y[i] = of(rintf(x[i] / p.s), p); }
+};
+
+// OP as in quant_rows_kernel.
+template <typename Q, int OP, bool RC>
+struct QuantOp {
+  typedef typename std::conditional<OP == 1, typename QVec<Q>::T, v4f>::type Vec;
+  typedef ScaleZero Par;
+  const void* in;
+  void* out;
+  float* out2;
+  const float* scale;
+  const int32_t* zp;
+  float lo, hi;
+  __device__ Par par(int64_t c) const { return scale_zero<RC && OP != 1>(scale, zp, c); }
+  __device__ Vec load(int64_t i) const {
+    if constexpr (OP == 1) return load4(static_cast<const Q*>(in), i);
+    else return load4(static_cast<const float*>(in), i);
+  }
+  __device__ void four(int64_t i, Vec v, const Par (&p)[4]) const {
     if constexpr (OP == 1) {
-      static_cast<float*>(out)[i] = dequantize_one((int32_t)static_cast<const Q*>(in)[i], scale[c], (float)zp[c]);
+      int32_t q[4];
+      unpack_codes<Q>(v, q);
+      store4(static_cast<float*>(out), i, v4f{dequantize_one(q[0], p[0].s, p[0].zf), dequantize_one(q[1], p[1].s, p[1].zf),
+                                              dequantize_one(q[2], p[2].s, p[2].zf), dequantize_one(q[3], p[3].s, p[3].zf)});
     } else {
-      const float x = static_cast<const float*>(in)[i];
-      static_cast<Q*>(out)[i] = (Q)quantize_one(x, scale[c], (float)zp[c], lo, hi);
-      if constexpr (OP == 2) out2[i] = simquant_one(x, scale[c], (float)zp[c], lo, hi);
+      v4f n;
+      quotients4<RC>(v, p, n);
+      store4(static_cast<Q*>(out), i, pack_codes<Q>(quantize_of(n.x, p[0].zf, lo, hi), quantize_of(n.y, p[1].zf, lo, hi),
+                                                    quantize_of(n.z, p[2].zf, lo, hi), quantize_of(n.w, p[3].zf, lo, hi)));
+      if constexpr (OP == 2)
+        store4(out2, i, v4f{simquant_of(n.x, p[0].s, p[0].zf, lo, hi), simquant_of(n.y, p[1].s, p[1].zf, lo, hi),
+                            simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)});
     }
   }
+  __device__ void one(int64_t i, const Par& p) const {
+    if constexpr (OP == 1) {
+      static_cast<float*>(out)[i] = dequantize_one((int32_t)static_cast<const Q*>(in)[i], p.s, p.zf);
+    } else {
+      const float u = rintf(static_cast<const float*>(in)[i] / p.s);
+      static_cast<Q*>(out)[i] = (Q)quantize_of(u, p.zf, lo, hi);
+      if constexpr (OP == 2) out2[i] = simquant_of(u, p.s, p.zf, lo, hi);
+    }
+  }
+};
+
+template <typename AccT, bool AWAY>
+struct RequantOp {
+  typedef typename std::conditional<sizeof(AccT) == 4, v4i32, v4i16>::type Vec;
+  struct Par {
+    int32_t m, sh;
+  };
+  const AccT* acc;
+  void* out;
+  const int32_t* mult;
+  const int32_t* shift;
+  RequantScalars rs;
+  __device__ Par par(int64_t c) const { return Par{rq_mult(mult, c), rq_shift(mult, shift, c)}; }
+  __device__ Vec load(int64_t i) const { return load4(acc, i); }
+  __device__ int32_t of(int32_t a, const Par& p) const { return requant_pick<AWAY>(a, p.m, p.sh, rs); }
+  __device__ void four(int64_t i, Vec v, const Par (&p)[4]) const {
+    store4(static_cast<uint8_t*>(out), i, pack4(of(v.x, p[0]), of(v.y, p[1]), of(v.z, p[2]), of(v.w, p[3])));
+  }
+  __device__ void one(int64_t i, const Par& p) const { static_cast<uint8_t*>(out)[i] = (uint8_t)of(acc[i], p); }
+};
+
+// The channel of flat element i = (o * channels + c) * inner + k, and k.
+struct ChannelDiv {
+  int64_t inner, channels;
+  uint32_t inv_inner, inv_channels;
+  int32_t narrow;  // the whole tensor has fewer than 2^32 elements
+};
+
+inline ChannelDiv channel_div(int64_t total, int64_t channels, int64_t inner) {
+  return ChannelDiv{inner, channels, reciprocal32(inner), reciprocal32(channels), total < (1ll << 32) ? 1 : 0};
+}
+
+__device__ __forceinline__ int64_t channel_at(const ChannelDiv& d, int64_t i, int64_t& k) {
+  if (d.narrow) {
+    uint32_t r, c;
+    const uint32_t q = div32((uint32_t)i, (uint32_t)d.inner, d.inv_inner, r);
+    div32(q, (uint32_t)d.channels, d.inv_channels, c);
+    k = r;
+    return c;
+  }
+  const int64_t q = i / d.inner;
+  k = i - q * d.inner;
+  return q % d.channels;
+}
+
+// Channels of four consecutive elements from i on.
+__device__ __forceinline__ void channels4(const ChannelDiv& d, int64_t i, int64_t (&c)[4]) {
+  int64_t k;
+  c[0] = channel_at(d, i, k);
+#pragma unroll
+  for (int e = 1; e < 4; ++e) {
+    c[e] = c[e - 1];
+    if (++k == d.inner) {
+      k = 0;
+      if (++c[e] == d.channels) c[e] = 0;
+    }
+  }
+}
+
+// The channels of consecutive vectors come back every lv vectors (channels * inner elements, taken two
+// or four times where that is not a multiple of four).  `span` is a multiple of lv of about a workgroup's
+// width where lv is small, lv itself where it is large; vector j of every span has the same four channels.  A
+// workgroup owns the vectors [seg * seg_len, ...) of `rows` consecutive spans: the lane's parameters
+// stay in registers, what is left per element is the operator itself.
+struct SpanArgs {
+  int64_t total;  // elements
+  int64_t spans;
+  int32_t span, nseg, seg_len, rows;
+};
+
+template <class Op, int U>
+__global__ __launch_bounds__(kThreads) void periodic_kernel(Op op, SpanArgs g, ChannelDiv d) {
+  const int t = threadIdx.x;
+  const int32_t rg = (int32_t)(blockIdx.x / (uint32_t)g.nseg);
+  const int32_t j = (int32_t)(blockIdx.x - (uint32_t)rg * (uint32_t)g.nseg) * g.seg_len + t;
+  const int64_t nvec = g.total >> 2;
+  if (blockIdx.x == 0 && t < (int)(g.total & 3)) {  // the last, incomplete vector
+    int64_t k;
+    const int64_t i = 4 * nvec + t;
+    op.one(i, op.par(channel_at(d, i, k)));
+  }
+  if (t >= g.seg_len || j >= g.span) return;
+  int64_t c[4];
+  channels4(d, 4ll * j, c);
+  const typename Op::Par p[4] = {op.par(c[0]), op.par(c[1]), op.par(c[2]), op.par(c[3])};
+  int64_t v = (int64_t)rg * g.rows * g.span + j;
+  const int64_t end = v + (int64_t)g.rows * g.span < nvec ? v + (int64_t)g.rows * g.span : nvec;
+  for (; v < end; v += (int64_t)U * g.span) {
+    typename Op::Vec a[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v + (int64_t)u * g.span < end) a[u] = op.load(4 * (v + (int64_t)u * g.span));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v + (int64_t)u * g.span < end) op.four(4 * (v + (int64_t)u * g.span), a[u], p);
+  }
+}
+
+// MULTI: inner < 4, every element of a vector may have its own channel; else at most two.
+template <class Op, int U, bool MULTI>
+__global__ __launch_bounds__(kThreads) void flat_kernel(Op op, int64_t total, ChannelDiv d) {
+  const int64_t nvec = total >> 2;
+  const int64_t v0 = (int64_t)blockIdx.x * (kThreads * U) + threadIdx.x;
+  if (v0 < (total & 3)) {  // the last, incomplete vector (v0 < 4: threads of the first workgroup)
+    int64_t k;
+    const int64_t i = 4 * nvec + v0;
+    op.one(i, op.par(channel_at(d, i, k)));
+  }
+  typename Op::Vec a[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (v0 + u * kThreads < nvec) a[u] = op.load(4 * (v0 + u * kThreads));
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t v = v0 + u * kThreads;
+    if (v >= nvec) break;
+    if constexpr (MULTI) {
+      int64_t c[4];
+      channels4(d, 4 * v, c);
+      const typename Op::Par p[4] = {op.par(c[0]), op.par(c[1]), op.par(c[2]), op.par(c[3])};
+      op.four(4 * v, a[u], p);
+    } else {
+      int64_t k;
+      const int64_t c0 = channel_at(d, 4 * v, k);
+      const int64_t left = d.inner - k;  // elements before the next channel
+      const int64_t c1 = left < 4 ? (c0 + 1 == d.channels ? 0 : c0 + 1) : c0;
+      const typename Op::Par p0 = op.par(c0), p1 = op.par(c1);
+      const typename Op::Par p[4] = {p0, left > 1 ? p0 : p1, left > 2 ? p0 : p1, left > 3 ? p0 : p1};
+      op.four(4 * v, a[u], p);
+    }
+  }
+}
+
+// Vectors after which the channels of a vector come back.
+inline int64_t channel_period(int64_t channels, int64_t inner) {
+  const int64_t p = channels * inner;
+  return p % 4 == 0 ? p / 4 : (p % 2 == 0 ? p / 2 : p);
+}
+
+// Whether the pattern comes back often enough (four times) for the periodic form, and its split: workgroups
+// own at least U spans each and, beyond eight workgroups per CU, more of them.
+inline bool periodic_split(int64_t total, int64_t channels, int64_t inner, int u, SpanArgs* g) {
+  const int64_t nvec = total / 4, lv = channel_period(channels, inner);
+  if (channels == 1 || nvec / lv < 4 || lv >= (1ll << 30)) return false;
+  const int64_t span = lv <= kThreads ? lv * (kThreads / lv) : lv;
+  g->total = total;
+  g->span = (int32_t)span;
+  g->spans = (nvec + span - 1) / span;
+  g->nseg = (int32_t)((span + kThreads - 1) / kThreads);
+  g->seg_len = (int32_t)((span + g->nseg - 1) / g->nseg);
+  int64_t rows = g->spans * g->nseg / (256 * 8);
+  rows = (rows + u - 1) / u * u;
+  if (rows < u) rows = u;
+  while (rows > 1 && ((g->spans + rows - 1) / rows) * g->nseg < 256) rows /= 2;  // small tensors: spread over the CUs
+  g->rows = (int32_t)rows;
+  return ((g->spans + rows - 1) / rows) * g->nseg < (1ll << 31);
+}
+
+// Periodic / flat launch of an operator; OpP keeps reciprocals for the periodic kernel, OpF does not.
+template <class OpP, class OpF, class... A>
+void launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStream_t st, A... args) {
+  constexpr int U = kVecPerLane;
+  const ChannelDiv d = channel_div(total, channels, inner);
+  SpanArgs g;
+  if (periodic_split(total, channels, inner, U, &g)) {
+    const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
+    hipLaunchKernelGGL((periodic_kernel<OpP, U>), dim3((unsigned)wgs), dim3(kThreads), 0, st, OpP{args...}, g, d);
+    return;
+  }
+  // one vector per lane while that does not fill the chip, four beyond
+  const int64_t nvec = total / 4 > 0 ? total / 4 : 1;
+  const int64_t w1 = (nvec + kThreads - 1) / kThreads, w4 = (nvec + kThreads * U - 1) / (kThreads * U);
+#define HAGO_FLAT(UU, MULTI, W) \
+  hipLaunchKernelGGL((flat_kernel<OpF, UU, MULTI>), dim3((unsigned)(W)), dim3(kThreads), 0, st, OpF{args...}, total, d)
+  if (w1 <= 1024) {
+    if (inner < 4) HAGO_FLAT(1, true, w1);
+    else HAGO_FLAT(1, false, w1);
+  } else {
+    if (inner < 4) HAGO_FLAT(U, true, w4);
+    else HAGO_FLAT(U, false, w4);
+  }
+#undef HAGO_FLAT
+}
+
+// Batched candidates over such rows: the lane's channels stay, the candidates' parameters are read per
+// candidate (from the cache) and x is kept in registers, as in the row kernel.
+template <int U, bool PERIODIC>
+__global__ __launch_bounds__(kThreads) void simquant_batched_ragged_kernel(
+    const float* __restrict__ x, float* __restrict__ y, SpanArgs g, ChannelDiv d, int32_t nbatch, int32_t nparam,
+    const float* __restrict__ scale, const int32_t* __restrict__ zp, CandidateClips clips) {
+  const int t = threadIdx.x;
+  const int64_t total = g.total, nvec = total >> 2;
+  if (blockIdx.x == 0 && t < (int)(total & 3)) {
+    int64_t k;
+    const int64_t i = 4 * nvec + t;
+    const int64_t c = channel_at(d, i, k);
+    for (int b = 0; b < nbatch; ++b)
+      y[(int64_t)b * total + i] = simquant_one(x[i], scale[(int64_t)b * nparam + c], (float)zp[(int64_t)b * nparam + c],
+                                               clips.lo[b], clips.hi[b]);
+  }
+  int64_t v0, step, end;
+  if constexpr (PERIODIC) {
+    const int32_t rg = (int32_t)(blockIdx.x / (uint32_t)g.nseg);
+    const int32_t j = (int32_t)(blockIdx.x - (uint32_t)rg * (uint32_t)g.nseg) * g.seg_len + t;
+    if (t >= g.seg_len || j >= g.span) return;
+    v0 = (int64_t)rg * g.rows * g.span + j;
+    step = g.span;
+    end = v0 + (int64_t)g.rows * g.span < nvec ? v0 + (int64_t)g.rows * g.span : nvec;
+  } else {
+    v0 = (int64_t)blockIdx.x * (kThreads * U) + t;
+    step = kThreads;
+    end = v0 + kThreads * U < nvec ? v0 + kThreads * U : nvec;
+  }
+  if (v0 >= end) return;
+  int64_t c[4];
+  if constexpr (PERIODIC) channels4(d, 4 * v0, c);
+  for (int64_t v = v0; v < end; v += U * step) {
+    v4f a[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v + u * step < end) a[u] = load4(x, 4 * (v + u * step));
+    auto params = [&](int b, ScaleZero (&p)[4]) {
+      const float* sb = scale + (int64_t)b * nparam;
+      const int32_t* zb = zp + (int64_t)b * nparam;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p[e] = scale_zero<PERIODIC>(sb, zb, c[e]);
+    };
+    auto write = [&](int b, int u, const ScaleZero (&p)[4]) {
+      v4f n;
+      quotients4<PERIODIC>(a[u], p, n);
+      const float lo = clips.lo[b], hi = clips.hi[b];
+      store4(y + (int64_t)b * total, 4 * (v + u * step),
+             v4f{simquant_of(n.x, p[0].s, p[0].zf, lo, hi), simquant_of(n.y, p[1].s, p[1].zf, lo, hi),
+                 simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)});
+    };
+    if constexpr (PERIODIC) {
+      for (int b = 0; b < nbatch; ++b) {
+        ScaleZero p[4];
+        params(b, p);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (v + u * step < end) write(b, u, p);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (v + u * step >= end) break;
+        channels4(d, 4 * (v + u * step), c);
+        for (int b = 0; b < nbatch; ++b) {
+          ScaleZero p[4];
+          params(b, p);
+          write(b, u, p);
+        }
+      }
+    }
+  }
+}
+
+inline void launch_batched_ragged(const float* x, float* y, int64_t total, int64_t channels, int64_t inner,
+                                  int32_t nbatch, const float* scale, const int32_t* zp, const CandidateClips& clips,
+                                  hipStream_t st) {
+  constexpr int U = 2;
+  const ChannelDiv d = channel_div(total, channels, inner);
+  SpanArgs g;
+  if (periodic_split(total, channels, inner, U, &g)) {
+    const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
+    hipLaunchKernelGGL((simquant_batched_ragged_kernel<U, true>), dim3((unsigned)wgs), dim3(kThreads), 0, st, x, y, g, d,
+                       nbatch, (int32_t)channels, scale, zp, clips);
+    return;
+  }
+  g = SpanArgs{};
+  g.total = total;
+  const int64_t nvec = total / 4 > 0 ? total / 4 : 1;
+  if (nvec <= 1024 * kThreads)
+    hipLaunchKernelGGL((simquant_batched_ragged_kernel<1, false>), dim3((unsigned)((nvec + kThreads - 1) / kThreads)),
+                       dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips);
+  else
+    hipLaunchKernelGGL((simquant_batched_ragged_kernel<U, false>),
+                       dim3((unsigned)((nvec + kThreads * U - 1) / (kThreads * U))), dim3(kThreads), 0, st, x, y, g, d,
+                       nbatch, (int32_t)channels, scale, zp, clips);
 }
 
 // ---- max-abs calibration (Eq. 2): thr[c] = max |x[o, c, i]| over o, i.  NaN never wins a
@@ -512,7 +829,8 @@ __device__ __forceinline__ float wave_max(float m) {
   return m;
 }
 
-// thr must hold zeros on entry.
+// SOLE: the workgroup's maximum is the result; otherwise it is merged into *thr_c (zeroed beforehand).
+template <bool SOLE>
 __device__ __forceinline__ void block_merge_max(float m, uint32_t* thr_c) {
   __shared__ float s_m[kThreads / 64];
   m = wave_max(m);
@@ -521,7 +839,8 @@ __device__ __forceinline__ void block_merge_max(float m, uint32_t* thr_c) {
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int w = 1; w < kThreads / 64; ++w) m = s_m[w] > m ? s_m[w] : m;
-    if (m > 0.0f) atomicMax(thr_c, __float_as_uint(m));
+    if constexpr (SOLE) *thr_c = __float_as_uint(m);
+    else if (m > 0.0f) atomicMax(thr_c, __float_as_uint(m));
   }
   __syncthreads();
 }
@@ -532,15 +851,17 @@ __global__ __launch_bounds__(kThreads) void fill_zero_kernel(uint32_t* p, int64_
 }
 
 // rows: as the other row kernels (row = outer * channels index, 128-bit nontemporal loads, U
-// vectors per lane in flight).  A job is (channel, row segment, group of outer indices): the
-// workgroup walks the rows o = og, og + ogroups, ... of its channel and merges once, so the
-// barriers and the atomic are paid once per several rows.
-template <int U>
+// vectors per lane in flight), for rows of any length and alignment.  A job is (channel, row
+// segment, group of outer indices): the workgroup walks the rows o = og, og + ogroups, ... of its
+// channel and merges once, so the barriers and the atomic are paid once per several rows.
+// SOLE: one job per channel, which stores its result (the thresholds need not be zeroed first).
+template <int U, bool SOLE>
 __global__ __launch_bounds__(kThreads) void absmax_rows_kernel(
-    const v4f* __restrict__ x, int64_t outer, int32_t channels, int64_t inner_vec, int32_t nseg,
+    const float* __restrict__ x, int64_t outer, int32_t channels, int64_t inner, int32_t nseg,
     int32_t seg_len, int32_t ogroups, int per_channel, uint32_t* __restrict__ thr) {
   // per tensor the "row" is the whole tensor: outer == 1, channels == 1
   const int64_t jobs = (int64_t)channels * nseg * ogroups;
+  const int64_t inner_vec = inner >> 2;
   for (int64_t job = blockIdx.x; job < jobs; job += gridDim.x) {
     // job = og * (channels * nseg) + c * nseg + seg: neighbouring workgroups, neighbouring rows
     int32_t og, seg, c;
@@ -560,13 +881,13 @@ __global__ __launch_bounds__(kThreads) void absmax_rows_kernel(
     const int64_t v1 = (v0 + seg_len < inner_vec) ? v0 + seg_len : inner_vec;
     float m = 0.0f;
     for (int64_t o = og; o < outer; o += ogroups) {
-      const v4f* xr = x + (o * channels + c) * inner_vec;
+      const float* xr = x + (o * channels + c) * inner;
+      if (seg == 0 && threadIdx.x < (unsigned)(inner & 3)) m = absmax_step(m, xr[4 * inner_vec + threadIdx.x]);
       for (int64_t vb = v0 + threadIdx.x; vb < v1; vb += (int64_t)kThreads * U) {
         v4f a[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-          a[u] = vb + u * kThreads < v1 ? __builtin_nontemporal_load(xr + vb + u * kThreads)
-                                        : v4f{0.f, 0.f, 0.f, 0.f};
+          a[u] = vb + u * kThreads < v1 ? (v4f)load4(xr, 4 * (vb + u * kThreads)) : v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           m = absmax_step(m, a[u].x); m = absmax_step(m, a[u].y);
@@ -574,23 +895,97 @@ __global__ __launch_bounds__(kThreads) void absmax_rows_kernel(
         }
       }
     }
-    block_merge_max(m, thr + (per_channel ? c : 0));
+    block_merge_max<SOLE>(m, thr + (per_channel ? c : 0));
   }
 }
 
-// columns: the tensor as [outer][channels * inner]; a lane owns one column j (channel j / inner)
-// and walks a chunk of `orows` outer rows, so neighbouring lanes read neighbouring addresses.
-// Used for short, unaligned or channel-last rows.  One atomic per lane and chunk.
-__global__ __launch_bounds__(kThreads) void absmax_cols_kernel(
-    const float* __restrict__ x, int64_t outer, int64_t cols, int64_t inner, int64_t orows,
-    int per_channel, uint32_t* __restrict__ thr) {
-  const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (j >= cols) return;
-  const int64_t o0 = (int64_t)blockIdx.y * orows;
-  const int64_t o1 = (o0 + orows < outer) ? o0 + orows : outer;
+// Short rows that come back often (channel-last tensors among them; see SpanArgs): a lane keeps a
+// maximum for each of its four elements over the workgroup's spans, the lanes merge in an LDS table,
+// one integer maximum per channel goes out (more channels than the table holds: straight from the
+// lanes).  SOLE: one workgroup does all, and stores.
+constexpr int kTableChannels = 8192;
+
+template <bool SOLE, bool TABLE = true>
+__global__ __launch_bounds__(kThreads) void absmax_periodic_kernel(const float* __restrict__ x, SpanArgs g, ChannelDiv d,
+                                                                   uint32_t* __restrict__ thr) {
+  extern __shared__ uint32_t s_max[];
+  const int t = threadIdx.x;
+  const int32_t channels = (int32_t)d.channels;
+  if constexpr (TABLE) {
+    for (int32_t c = t; c < channels; c += kThreads) s_max[c] = 0u;
+    __syncthreads();
+  }
+  auto merge = [&](int64_t c, float m) {
+    if (m > 0.0f) atomicMax((TABLE ? s_max : thr) + c, __float_as_uint(m));
+  };
+  const int32_t rg = (int32_t)(blockIdx.x / (uint32_t)g.nseg);
+  const int32_t j = (int32_t)(blockIdx.x - (uint32_t)rg * (uint32_t)g.nseg) * g.seg_len + t;
+  const int64_t nvec = g.total >> 2;
+  if (blockIdx.x == 0 && t < (int)(g.total & 3)) {
+    int64_t k;
+    const int64_t i = 4 * nvec + t;
+    const int64_t c = channel_at(d, i, k);
+    merge(c, absmax_step(0.0f, x[i]));
+  }
+  if (t < g.seg_len && j < g.span) {
+    constexpr int U = kVecPerLane;
+    float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    int64_t v = (int64_t)rg * g.rows * g.span + j;
+    const int64_t end = v + (int64_t)g.rows * g.span < nvec ? v + (int64_t)g.rows * g.span : nvec;
+    for (; v < end; v += (int64_t)U * g.span) {
+      v4f a[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        a[u] = v + (int64_t)u * g.span < end ? (v4f)load4(x, 4 * (v + (int64_t)u * g.span)) : v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m[e] = absmax_step(m[e], a[u][e]);
+    }
+    int64_t c[4];
+    channels4(d, 4ll * j, c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      // (a run of elements of one channel merges in registers first)
+      if (e + 1 < 4 && c[e + 1] == c[e]) m[e + 1] = absmax_step(m[e + 1], m[e]);
+      else merge(c[e], m[e]);
+    }
+  }
+  if constexpr (TABLE) {
+    __syncthreads();
+    for (int32_t c = t; c < channels; c += kThreads) {
+      const uint32_t m = s_max[c];
+      if constexpr (SOLE) thr[c] = m;
+      else if (m) atomicMax(thr + c, m);
+    }
+  }
+}
+
+// Few elements per channel: `lanes` (a power of two up to 64) lanes own a channel and store its result.
+__global__ __launch_bounds__(kThreads) void absmax_lanes_kernel(const float* __restrict__ x, int64_t outer,
+                                                                int64_t channels, int64_t inner, int32_t lanes,
+                                                                float* __restrict__ thr) {
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t c = i / lanes;
+  const int sub = (int)(i - c * lanes);
   float m = 0.0f;
-  for (int64_t o = o0; o < o1; ++o) m = absmax_step(m, x[o * cols + j]);
-  if (m > 0.0f) atomicMax(thr + (per_channel ? j / inner : 0), __float_as_uint(m));
+  if (c < channels) {
+    for (int64_t o = 0; o < outer; ++o) {
+      const float* xr = x + (o * channels + c) * inner;
+      for (int64_t k = sub; k < inner; k += 4 * lanes) {
+        float a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] = k + u * lanes < inner ? xr[k + u * lanes] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m = absmax_step(m, a[u]);
+      }
+    }
+  }
+  for (int s = lanes >> 1; s >= 1; s >>= 1) {
+    const float o = __shfl_xor(m, s);
+    m = o > m ? o : m;
+  }
+  if (c < channels && sub == 0) thr[c] = m;
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -620,9 +1015,8 @@ hipError_t launch_simquant(const float* x, float* y, int64_t outer, int64_t chan
                        (int32_t)(per_channel ? channels : 1), inner_vec, nseg, seg_len, scale, zp,
                        per_channel, JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi, 0, 0);
   } else {
-    hipLaunchKernelGGL(simquant_flat_kernel<false>, dim3(grid_for((total + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, st, x, y, total, inner, channels, scale, zp, per_channel,
-                       lo, hi, 0, 0);
+    launch_ragged<SimquantOp<false, true>, SimquantOp<false, false>>(
+        total, per_channel ? channels : 1, per_channel ? inner : total, st, x, y, scale, zp, lo, hi, 0, 0);
   }
   return hipGetLastError();
 }
@@ -645,9 +1039,8 @@ hipError_t launch_simquant_wrap(const float* x, float* y, int64_t outer, int64_t
                        per_channel, JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi,
                        wrap_bits, wrap_signed);
   } else {
-    hipLaunchKernelGGL(simquant_flat_kernel<true>, dim3(grid_for((total + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, st, x, y, total, inner, channels, scale, zp, per_channel,
-                       lo, hi, wrap_bits, wrap_signed);
+    launch_ragged<SimquantOp<true, true>, SimquantOp<true, false>>(
+        total, per_channel ? channels : 1, per_channel ? inner : total, st, x, y, scale, zp, lo, hi, wrap_bits, wrap_signed);
   }
   return hipGetLastError();
 }
@@ -677,9 +1070,7 @@ hipError_t launch_simquant_batched(const float* x, float* y, int64_t outer, int6
                        nparam, inner_vec, nseg, seg_len, nbatch, nparam, scale, zp, per_channel,
                        JobDiv{reciprocal32(nseg), reciprocal32(nparam)}, clips);
   } else {
-    hipLaunchKernelGGL(simquant_batched_flat_kernel, dim3(grid_for((total + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, st, x, y, total, inner, channels, nbatch, nparam, scale, zp,
-                       per_channel, clips);
+    launch_batched_ragged(x, y, total, nparam, per_channel ? inner : total, nbatch, scale, zp, clips, st);
   }
   return hipGetLastError();
 }
@@ -702,9 +1093,8 @@ static hipError_t launch_quant_t(const void* in, void* out, float* out2, int64_t
                        inner_vec, nseg, seg_len, scale, zp, per_channel,
                        JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi);
   } else {
-    hipLaunchKernelGGL((quant_flat_kernel<Q, OP>), dim3(grid_for((total + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, st, in, out, out2, total, inner, channels, scale, zp, per_channel,
-                       lo, hi);
+    launch_ragged<QuantOp<Q, OP, OP != 1>, QuantOp<Q, OP, false>>(
+        total, per_channel ? channels : 1, per_channel ? inner : total, st, in, out, out2, scale, zp, lo, hi);
   }
   return hipGetLastError();
 }
@@ -737,42 +1127,68 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
   const int64_t nthr = per_channel ? channels : 1;
   if (nthr == 0) return hipSuccess;
   uint32_t* t = reinterpret_cast<uint32_t*>(thr);
-  // (a fill kernel, not hipMemsetAsync: the call may be captured into a graph)
-  hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((nthr + kThreads - 1) / kThreads)),
-                     dim3(kThreads), 0, st, t, nthr);
+  auto zero_first = [&] {
+    // (a fill kernel, not hipMemsetAsync: the call may be captured into a graph)
+    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((nthr + kThreads - 1) / kThreads)),
+                       dim3(kThreads), 0, st, t, nthr);
+  };
   const int64_t total = outer * channels * inner;
-  if (total == 0) return hipGetLastError();
-  const int64_t row_len = per_channel ? inner : total;
-  if (row_len % 4 == 0 && row_len >= 512 && aligned16(x)) {
-    const int64_t inner_vec = row_len / 4;
-    int32_t nseg, seg_len;
-    split_row(inner_vec, kVecPerLane, &nseg, &seg_len);
-    // about four workgroups per CU: rows of one channel beyond that share a workgroup (config 4
-    // tensor: 12.8 us with 8 rows per workgroup, 15.8 us with one)
-    const int64_t nchan = per_channel ? channels : 1, nouter = per_channel ? outer : 1;
-    int64_t rows_per_wg = nouter * nchan * nseg / (256 * 4);
-    if (rows_per_wg < 1) rows_per_wg = 1;
-    const int64_t ogroups = (nouter + rows_per_wg - 1) / rows_per_wg;
-    const int64_t jobs = nchan * nseg * ogroups;
-    const int64_t cap = 256 * 32;
-    hipLaunchKernelGGL(absmax_rows_kernel<kVecPerLane>, dim3((unsigned)(jobs < cap ? jobs : cap)),
-                       dim3(kThreads), 0, st, reinterpret_cast<const v4f*>(x), nouter, (int32_t)nchan,
-                       inner_vec, nseg, seg_len, (int32_t)ogroups, per_channel, t);
-  } else {
-    const int64_t cols = per_channel ? channels * inner : inner * channels;
-    const int64_t col_inner = per_channel ? inner : cols;
-    const int64_t xblocks = (cols + kThreads - 1) / kThreads;
-    if (xblocks >= (1ll << 31)) return hipErrorInvalidValue;
-    // enough row chunks to fill the chip, at most 65535
-    int64_t chunks = (256 * 8 + xblocks - 1) / xblocks;
-    if (chunks > outer) chunks = outer;
-    if (chunks > 65535) chunks = 65535;
-    if (chunks < 1) chunks = 1;
-    const int64_t orows = (outer + chunks - 1) / chunks;
-    chunks = (outer + orows - 1) / orows;
-    hipLaunchKernelGGL(absmax_cols_kernel, dim3((unsigned)xblocks, (unsigned)chunks), dim3(kThreads),
-                       0, st, x, outer, cols, col_inner, orows, per_channel, t);
+  if (total == 0) {
+    zero_first();
+    return hipGetLastError();
   }
+  const int64_t nchan = per_channel ? channels : 1;
+  const int64_t nouter = nchan > 1 ? outer : 1, row_len = nchan > 1 ? inner : total;  // one channel: one row
+  // Rows shorter than a workgroup's 1024 elements: merged in LDS where their channels come back often ...
+  SpanArgs g;
+  if (row_len < 4 * kThreads && periodic_split(total, nchan, row_len, kVecPerLane, &g)) {
+    const bool table = nchan <= kTableChannels;
+    const size_t lds = table ? (size_t)nchan * sizeof(uint32_t) : 0;
+    if (table && total <= 16384 && g.nseg == 1) {  // one workgroup: no second launch to zero the thresholds
+      g.rows = (int32_t)g.spans;
+      hipLaunchKernelGGL((absmax_periodic_kernel<true>), dim3(1), dim3(kThreads), lds, st, x, g, channel_div(total, nchan, row_len), t);
+      return hipGetLastError();
+    }
+    // every workgroup ends with an atomic per channel: twice the CUs' number of workgroups at most
+    int64_t rows = g.spans * g.nseg / (256 * 2);
+    if (rows > g.rows) g.rows = (int32_t)rows;
+    zero_first();
+    const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
+    auto kern = table ? absmax_periodic_kernel<false, true> : absmax_periodic_kernel<false, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(kThreads), lds, st, x, g, channel_div(total, nchan, row_len), t);
+    return hipGetLastError();
+  }
+  // ... a few lanes per channel where they do not.
+  if (row_len < 4 * kThreads && nouter * row_len <= 65536) {
+    int32_t lanes = 1;
+    while (lanes < 64 && lanes * 4 < row_len) lanes *= 2;
+    const int64_t wgs = (nchan * lanes + kThreads - 1) / kThreads;
+    if (wgs < (1ll << 31)) {
+      hipLaunchKernelGGL(absmax_lanes_kernel, dim3((unsigned)wgs), dim3(kThreads), 0, st, x, nouter, nchan, row_len, lanes, thr);
+      return hipGetLastError();
+    }
+  }
+  int32_t nseg, seg_len;
+  split_row(row_len / 4 > 0 ? row_len / 4 : 1, kVecPerLane, &nseg, &seg_len);
+  if (nchan >= (1ll << 31) || row_len / 4 / kThreads >= (1ll << 31)) return hipErrorInvalidValue;
+  // A channel of up to 64 KB, or enough channels to fill the chip: one workgroup each, which stores.
+  if (nouter * row_len <= 16384 || nchan >= 1024) {
+    const int64_t cap = 256 * 32;
+    hipLaunchKernelGGL((absmax_rows_kernel<kVecPerLane, true>), dim3((unsigned)(nchan < cap ? nchan : cap)), dim3(kThreads), 0,
+                       st, x, nouter, (int32_t)nchan, row_len, 1, (int32_t)(row_len / 4), 1, per_channel, t);
+    return hipGetLastError();
+  }
+  // about four workgroups per CU: rows of one channel beyond that share a workgroup (config 4
+  // tensor: 12.8 us with 8 rows per workgroup, 15.8 us with one)
+  int64_t rows_per_wg = nouter * nchan * nseg / (256 * 4);
+  if (rows_per_wg < 1) rows_per_wg = 1;
+  const int64_t ogroups = (nouter + rows_per_wg - 1) / rows_per_wg;
+  const int64_t jobs = nchan * nseg * ogroups;
+  const int64_t cap = 256 * 32;
+  zero_first();
+  hipLaunchKernelGGL((absmax_rows_kernel<kVecPerLane, false>), dim3((unsigned)(jobs < cap ? jobs : cap)),
+                     dim3(kThreads), 0, st, x, nouter, (int32_t)nchan, row_len, nseg, seg_len, (int32_t)ogroups,
+                     per_channel, t);
   return hipGetLastError();
 }
 
@@ -798,20 +1214,12 @@ static hipError_t launch_requantize_t(const AccT* acc, int64_t outer, int64_t ch
                        acc, reinterpret_cast<uint32_t*>(out), rows, (int32_t)(pc ? channels : 1),
                        inner_vec, nseg, seg_len, rq.multiplier, rq.shift, pc,
                        JobDiv{reciprocal32(nseg), reciprocal32(pc ? channels : 1)}, rs);
-  } else if (pc && inner == 1 && channels % 4 == 0 && io_aligned && rq.multiplier && aligned16(rq.multiplier) &&
-             aligned16(rq.shift)) {
-    const int64_t total_vec = total / 4;
-    auto kern = rq.half_away ? requant_lastaxis_kernel<AccT, true> : requant_lastaxis_kernel<AccT, false>;
-    hipLaunchKernelGGL(kern,
-                       dim3(grid_for((total_vec + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
-                       acc, reinterpret_cast<uint32_t*>(out), total_vec, (int32_t)(channels / 4),
-                       reinterpret_cast<const int4*>(rq.multiplier),
-                       reinterpret_cast<const int4*>(rq.shift), rs);
   } else {
-    auto kern = rq.half_away ? requant_flat_kernel<AccT, true> : requant_flat_kernel<AccT, false>;
-    hipLaunchKernelGGL(kern, dim3(grid_for((total + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, st, acc, reinterpret_cast<uint8_t*>(out), total, inner,
-                       channels, rq.multiplier, rq.shift, pc, rs);
+    const int64_t ch = pc ? channels : 1, in = pc ? inner : total;
+    if (rq.half_away)
+      launch_ragged<RequantOp<AccT, true>, RequantOp<AccT, true>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
+    else
+      launch_ragged<RequantOp<AccT, false>, RequantOp<AccT, false>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
   }
   return hipGetLastError();
 }
