@@ -1,8 +1,10 @@
-"""ctypes binding of libhago.so: same names as the C ABI, argument marshalling only.
+"""Binding of libhago.so: same names as the C ABI, argument marshalling only.
 
 Tensors are torch tensors on the GPU; the binding passes their device pointers
 and the current torch stream to the library and allocates the output tensor.
-There is no CPU fallback: if the library is missing, loading fails.
+The operators are marshalled by a native module (csrc/native.cpp), everything
+around them by ctypes.  There is no CPU fallback: if the library is missing,
+loading fails.
 """
 from __future__ import annotations
 
@@ -19,6 +21,7 @@ ROUND_UPWARD, ROUND_HALF_AWAY = 0, 1   # hago_rounding
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libhago.so")
+_NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 EXPORTS = ("hago_simquant", "hago_simquant_batched", "hago_absmax", "hago_simquant_wrap", "hago_quantize", "hago_dequantize", "hago_simquant_codes", "hago_qdense", "hago_qconv2d", "hago_qconv2d_ws", "hago_qconv2d_workspace_bytes", "hago_qconv2d_static", "hago_requantize",
            "hago_status_string", "hago_bit_range", "hago_set_test_hook", "hago_probe_mfma_i8", "hago_probe_copy")
@@ -45,6 +48,7 @@ def library_path() -> str:
 
 
 _lib = None
+_native = None
 
 
 def lib():
@@ -165,184 +169,87 @@ class Requant:
                         self.out.c(), self.clip_lo, self.clip_hi, self.rounding)
 
 
-def _torch():
-    import torch
-    return torch
+def _native_module():
+    """The marshalling module (csrc/native.cpp), bound to the loaded library."""
+    global _native
+    if _native is None:
+        L = lib()
+        import torch  # noqa: F401  (the module links to torch's libraries)
+        if not os.path.exists(_NATIVE_PATH):
+            raise FileNotFoundError(
+                f"{_NATIVE_PATH} is missing: build it with `python -m paper_2103_14949_amd.build` "
+                "(there is no fallback path)")
+        from . import _native as m
+        m.bind({name: C.cast(getattr(L, name), C.c_void_p).value for name in m.entries()}, _check)
+        _native = m
+    return _native
+
+
+def __getattr__(name):
+    # the type of the calls that prepare=True returns
+    if name == "Prepared":
+        return _native_module().Prepared
+    raise AttributeError(name)
 
 
 def _stream():
-    return _torch().cuda.current_stream().cuda_stream
-
-
-def _tdtype(code):
-    t = _torch()
-    return {U8: t.uint8, I8: t.int8, I16: t.int16, I32: t.int32, F32: t.float32, I24: t.int32}[code]
-
-
-def _code(tensor):
-    t = _torch()
-    return {t.uint8: U8, t.int8: I8, t.int16: I16, t.int32: I32, t.float32: F32}[tensor.dtype]
+    import torch
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-class Prepared:
-    """A library call with its arguments already marshalled; calling it re-issues the same
-    launch (same buffers, same stream) with one foreign-function call."""
-
-    __slots__ = ("_fn", "_args", "_keep", "out")
-
-    def __init__(self, fn, args, keep, out):
-        self._fn, self._args, self._keep, self.out = fn, args, keep, out
-
-    def __call__(self):
-        code = self._fn(*self._args)
-        if code != 0:
-            _check(code)
-        return self.out
-
+# Every operator below takes its output tensor as `out` (allocated when None), launches on torch's current
+# stream and returns the output; with prepare=True it returns instead a Prepared object, a call with its
+# arguments already marshalled (`.out` is its output) that re-issues the same launch on the same buffers and stream.
 
 def simquant(x, scale, zero_point, q: QType, clip_lo=None, clip_hi=None, per_channel=None, out=None,
              prepare=False):
     """hago_simquant over x[outer, channels, inner] (fp32, contiguous)."""
-    assert x.dim() == 3 and x.is_contiguous()
-    outer, channels, inner = x.shape
-    lo, hi = bit_range(q.bits, q.is_signed)
-    clip_lo = lo if clip_lo is None else clip_lo
-    clip_hi = hi if clip_hi is None else clip_hi
-    pc = int(scale.numel() > 1) if per_channel is None else int(per_channel)
-    y = _torch().empty_like(x) if out is None else out
-    args = (_ptr(x), _ptr(y), outer, channels, inner, _ptr(scale), _ptr(zero_point), pc, q.c(),
-            int(clip_lo), int(clip_hi), _stream())
-    if prepare:
-        return Prepared(lib().hago_simquant, args, (x, y, scale, zero_point), y)
-    _check(lib().hago_simquant(*args))
-    return y
+    return (_native or _native_module()).simquant(x, scale, zero_point, q, clip_lo, clip_hi, per_channel, out, prepare)
 
 
 def simquant_wrap(x, scale, zero_point, q: QType, clip_lo=None, clip_hi=None, per_channel=None, out=None,
                   prepare=False):
     """hago_simquant_wrap over x[outer, channels, inner]: simulated quantize with the overflow of q's container."""
-    assert x.dim() == 3 and x.is_contiguous()
-    outer, channels, inner = x.shape
-    lo, hi = bit_range(min(q.bits, 25), q.is_signed)
-    clip_lo = lo if clip_lo is None else clip_lo
-    clip_hi = hi if clip_hi is None else clip_hi
-    pc = int(scale.numel() > 1) if per_channel is None else int(per_channel)
-    y = _torch().empty_like(x) if out is None else out
-    args = (_ptr(x), _ptr(y), outer, channels, inner, _ptr(scale), _ptr(zero_point), pc, q.c(),
-            int(clip_lo), int(clip_hi), _stream())
-    if prepare:
-        return Prepared(lib().hago_simquant_wrap, args, (x, y, scale, zero_point), y)
-    _check(lib().hago_simquant_wrap(*args))
-    return y
+    return (_native or _native_module()).simquant_wrap(x, scale, zero_point, q, clip_lo, clip_hi, per_channel, out, prepare)
 
 
 def simquant_batched(x, scales, zero_points, q: QType, clip_lo, clip_hi, per_channel=True, out=None,
                      prepare=False):
     """hago_simquant_batched: candidates b over x[outer, channels, inner]; scales / zero_points are
     device tensors [nbatch, channels] (or [nbatch, 1]); clip_lo / clip_hi are host sequences."""
-    assert x.dim() == 3 and x.is_contiguous() and scales.is_contiguous() and zero_points.is_contiguous()
-    outer, channels, inner = x.shape
-    nb = len(clip_lo)
-    assert len(clip_hi) == nb and scales.shape[0] == nb and zero_points.shape[0] == nb
-    t = _torch()
-    y = t.empty((nb,) + tuple(x.shape), dtype=t.float32, device=x.device) if out is None else out
-    lo = (C.c_int32 * max(nb, 1))(*[int(v) for v in clip_lo])
-    hi = (C.c_int32 * max(nb, 1))(*[int(v) for v in clip_hi])
-    args = (_ptr(x), _ptr(y), outer, channels, inner, nb, _ptr(scales), _ptr(zero_points),
-            int(bool(per_channel)), q.c(), C.cast(lo, C.c_void_p), C.cast(hi, C.c_void_p), _stream())
-    if prepare:
-        return Prepared(lib().hago_simquant_batched, args, (x, y, scales, zero_points, lo, hi), y)
-    _check(lib().hago_simquant_batched(*args))
-    return y
-
-
-_TORCH_OF = {U8: "uint8", I8: "int8", I16: "int16", I32: "int32"}
+    return (_native or _native_module()).simquant_batched(x, scales, zero_points, q, clip_lo, clip_hi, per_channel, out, prepare)
 
 
 def quantize(x, scale, zero_point, q: QType, clip_lo=None, clip_hi=None, per_channel=None, out=None,
              prepare=False):
     """hago_quantize over x[outer, channels, inner] (fp32): integer codes in q's container."""
-    assert x.dim() == 3 and x.is_contiguous()
-    outer, channels, inner = x.shape
-    lo, hi = bit_range(q.bits, q.is_signed)
-    clip_lo = lo if clip_lo is None else clip_lo
-    clip_hi = hi if clip_hi is None else clip_hi
-    pc = int(scale.numel() > 1) if per_channel is None else int(per_channel)
-    t = _torch()
-    codes = t.empty(x.shape, dtype=getattr(t, _TORCH_OF[q.dtype]), device=x.device) if out is None else out
-    args = (_ptr(x), _ptr(codes), outer, channels, inner, _ptr(scale), _ptr(zero_point), pc, q.c(),
-            int(clip_lo), int(clip_hi), _stream())
-    if prepare:
-        return Prepared(lib().hago_quantize, args, (x, codes, scale, zero_point), codes)
-    _check(lib().hago_quantize(*args))
-    return codes
+    return (_native or _native_module()).quantize(x, scale, zero_point, q, clip_lo, clip_hi, per_channel, out, prepare)
 
 
 def simquant_codes(x, scale, zero_point, q: QType, clip_lo=None, clip_hi=None, per_channel=None, out=None,
                    out_codes=None, prepare=False):
     """hago_simquant_codes over x[outer, channels, inner] (fp32): (simulated-quantized fp32, integer codes)."""
-    assert x.dim() == 3 and x.is_contiguous()
-    outer, channels, inner = x.shape
-    lo, hi = bit_range(q.bits, q.is_signed)
-    clip_lo = lo if clip_lo is None else clip_lo
-    clip_hi = hi if clip_hi is None else clip_hi
-    pc = int(scale.numel() > 1) if per_channel is None else int(per_channel)
-    t = _torch()
-    y = t.empty_like(x) if out is None else out
-    codes = (t.empty(x.shape, dtype=getattr(t, _TORCH_OF[q.dtype]), device=x.device)
-             if out_codes is None else out_codes)
-    args = (_ptr(x), _ptr(y), _ptr(codes), outer, channels, inner, _ptr(scale), _ptr(zero_point), pc, q.c(),
-            int(clip_lo), int(clip_hi), _stream())
-    if prepare:
-        return Prepared(lib().hago_simquant_codes, args, (x, y, codes, scale, zero_point), (y, codes))
-    _check(lib().hago_simquant_codes(*args))
-    return y, codes
+    return (_native or _native_module()).simquant_codes(x, scale, zero_point, q, clip_lo, clip_hi, per_channel, out, out_codes,
+                                                        prepare)
 
 
 def dequantize(codes, q: QType, scale, zero_point, per_channel=None, out=None, prepare=False):
     """hago_dequantize over codes[outer, channels, inner] in q's container: fp32."""
-    assert codes.dim() == 3 and codes.is_contiguous()
-    outer, channels, inner = codes.shape
-    pc = int(scale.numel() > 1) if per_channel is None else int(per_channel)
-    t = _torch()
-    y = t.empty(codes.shape, dtype=t.float32, device=codes.device) if out is None else out
-    args = (_ptr(codes), q.c(), _ptr(y), outer, channels, inner, _ptr(scale), _ptr(zero_point), pc,
-            _stream())
-    if prepare:
-        return Prepared(lib().hago_dequantize, args, (codes, y, scale, zero_point), y)
-    _check(lib().hago_dequantize(*args))
-    return y
+    return (_native or _native_module()).dequantize(codes, q, scale, zero_point, per_channel, out, prepare)
 
 
 def absmax(x, per_channel=True, out=None, prepare=False):
     """hago_absmax over x[outer, channels, inner] (fp32, contiguous): thresholds [channels] or [1]."""
-    assert x.dim() == 3 and x.is_contiguous()
-    outer, channels, inner = x.shape
-    n = channels if per_channel else 1
-    thr = _torch().empty(n, dtype=_torch().float32, device=x.device) if out is None else out
-    args = (_ptr(x), outer, channels, inner, int(bool(per_channel)), _ptr(thr), _stream())
-    if prepare:
-        return Prepared(lib().hago_absmax, args, (x, thr), thr)
-    _check(lib().hago_absmax(*args))
-    return thr
+    return (_native or _native_module()).absmax(x, per_channel, out, prepare)
 
 
 def requantize(acc, rq: Requant, out=None, prepare=False):
     """hago_requantize over acc[outer, channels, inner] (int32 / int16)."""
-    assert acc.dim() == 3 and acc.is_contiguous()
-    outer, channels, inner = acc.shape
-    if out is None:
-        out = _torch().empty(acc.shape, dtype=_tdtype(rq.out.dtype), device=acc.device)
-    st = rq.c()
-    args = (_ptr(acc), _code(acc), outer, channels, inner, C.byref(st), _ptr(out), _stream())
-    if prepare:
-        return Prepared(lib().hago_requantize, args, (acc, rq, st, out), out)
-    _check(lib().hago_requantize(*args))
-    return out
+    return (_native or _native_module()).requantize(acc, rq, out, prepare)
 
 
 def qdense(a, a_t: QType, w, w_t: QType, bias=None, acc_dtype=I32, rq: Requant | None = None,
@@ -350,20 +257,7 @@ def qdense(a, a_t: QType, w, w_t: QType, bias=None, acc_dtype=I32, rq: Requant |
     """hago_qdense: a [M,K] (uint8/int8), w [N,K] int8 -> [M,N].
 
     prepare=True returns a Prepared call instead of launching."""
-    assert a.dim() == 2 and w.dim() == 2 and a.is_contiguous() and w.is_contiguous()
-    M, K = a.shape
-    N = w.shape[0]
-    assert w.shape[1] == K
-    if out is None:
-        dt = _tdtype(rq.out.dtype) if rq is not None else _tdtype(acc_dtype)
-        out = _torch().empty((M, N), dtype=dt, device=a.device)
-    st = rq.c() if rq is not None else None
-    args = (_ptr(a), a_t.c(), _ptr(w), w_t.c(), _ptr(bias), M, N, K, acc_dtype,
-            C.byref(st) if st is not None else None, _ptr(out), flags, _stream())
-    if prepare:
-        return Prepared(lib().hago_qdense, args, (a, w, bias, rq, st, out), out)
-    _check(lib().hago_qdense(*args))
-    return out
+    return (_native or _native_module()).qdense(a, a_t, w, w_t, bias, acc_dtype, rq, flags, out, prepare)
 
 
 def _conv_dims(a, w, layout):
@@ -394,26 +288,5 @@ def qconv2d(a, a_t: QType, w, w_t: QType, bias=None, layout=NCHW, stride=(1, 1),
     With `workspace` (a uint8 device tensor of at least qconv2d_workspace_bytes(...) bytes, or an
     empty one when that is 0) the call goes to hago_qconv2d_ws; with static_scratch=True to
     hago_qconv2d_static."""
-    assert a.dim() == 4 and w.dim() == 4 and a.is_contiguous() and w.is_contiguous()
-    B, Cc, H, W, O, KH, KW = _conv_dims(a, w, layout)
-    OH = (H + 2 * pad[0] - KH) // stride[0] + 1
-    OW = (W + 2 * pad[1] - KW) // stride[1] + 1
-    if out is None:
-        dt = _tdtype(rq.out.dtype) if rq is not None else _tdtype(acc_dtype)
-        shape = (B, O, max(OH, 0), max(OW, 0)) if layout == NCHW else (B, max(OH, 0), max(OW, 0), O)
-        out = _torch().empty(shape, dtype=dt, device=a.device)
-    st = rq.c() if rq is not None else None
-    args = (_ptr(a), a_t.c(), _ptr(w), w_t.c(), _ptr(bias), layout, B, Cc, H, W, O,
-            KH, KW, stride[0], stride[1], pad[0], pad[1], groups, acc_dtype,
-            C.byref(st) if st is not None else None, _ptr(out))
-    if workspace is not None:
-        fn = lib().hago_qconv2d_ws
-        args += (_ptr(workspace) if workspace.numel() else None, workspace.numel() * workspace.element_size(),
-                 flags, _stream())
-    else:
-        fn = lib().hago_qconv2d_static if static_scratch else lib().hago_qconv2d
-        args += (flags, _stream())
-    if prepare:
-        return Prepared(fn, args, (a, w, bias, rq, st, out, workspace), out)
-    _check(fn(*args))
-    return out
+    return (_native or _native_module()).qconv2d(a, a_t, w, w_t, bias, layout, stride, pad, groups, acc_dtype, rq, flags, out,
+                                                 prepare, workspace, static_scratch)

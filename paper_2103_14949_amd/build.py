@@ -1,7 +1,8 @@
-"""Build libhago.so (the C-ABI library) from the HIP sources for gfx950.
+"""Build libhago.so (the C-ABI library) from the HIP sources for gfx950, and the binding's native
+marshalling module (_native.so, host code against torch's headers).
 
-hipcc cross-compiles without a GPU.  The library is written next to this file
-so that it travels with the source tree.
+hipcc cross-compiles without a GPU.  The libraries are written next to this file
+so that they travel with the source tree.
 """
 from __future__ import annotations
 
@@ -26,8 +27,30 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+NATIVE_LIB = os.path.join(HERE, "_native.so")
+
+
+def build_native(verbose: bool = False) -> str:
+    """Compile the binding's native module; always recompiles."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    include = [*cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           *[f"-isystem{d}" for d in include], os.path.join(CSRC, "native.cpp"), "-o", NATIVE_LIB, f"-L{torch_lib}",
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python", f"-Wl,-rpath,{torch_lib}"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return NATIVE_LIB
+
+
 def build(verbose: bool = False, jobs: int = 4) -> str:
-    """Compile every .hip file and link the shared library; always recompiles."""
+    """Compile every .hip file and link the shared library, and the native module; always recompiles."""
+    build_native(verbose)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
