@@ -172,7 +172,7 @@ hago_status hago_simquant(const float* x, float* y, int64_t outer,
  * a: device [M,K], HAGO_U8 or HAGO_I8.  w: device [N,K] HAGO_I8, symmetric
  * (w_t.zero_point must be 0).  bias: device [N] int32 or NULL.
  * Or both operands HAGO_I16 (int16 data, acc_dtype HAGO_I32 or HAGO_I24): there
- * is no 16-bit matrix instruction, so this triple runs on the vector ALUs.
+ * is no 16-bit matrix instruction, so this triple runs as four byte products.
  * Errors: NULL, SHAPE (negative dims, > 2^31-1), DTYPE, BITS, PARAM,
  * ACC_BOUND (flags & HAGO_STRICT_ACC16 and acc_dtype I16 / I24 and
  * K * max|a - z_a| * max|w| over the declared bit ranges > 2^15 - 1 /
@@ -430,7 +430,8 @@ hago_status hago_probe_copy(const void* src, void* dst, int64_t bytes,
  *                           2 the streaming kernel, skipping the kernels
  *                           specialised for 1x1 and 3x3 convolutions
  *   HAGO_HOOK_STREAM_TILE   -1 automatic; 0..4 a tile of the streaming dense kernel
- *   HAGO_HOOK_GENERAL_TILE  -1 automatic; 0..6 a tile of the general kernel
+ *   HAGO_HOOK_GENERAL_TILE  -1 automatic; 0..6 a tile of the general convolution
+ *                           kernel (modulo 5: a form of the general dense kernel)
  * Unknown keys are ignored.
  */
 #define HAGO_HOOK_GEMM_PATH 0

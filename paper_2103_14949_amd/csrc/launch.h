@@ -85,8 +85,8 @@ struct GemmArgs {
   RequantArgs rq;
 };
 
-// int16 x int16 operands (dense, or a groups == 1 convolution when cg != nullptr) on the vector ALUs.
-hipError_t launch_qgemm16(const GemmArgs& g, const ConvGeom* cg, hipStream_t st);
+// int16 x int16 operands, groups == 1 convolution, on the vector ALUs.
+hipError_t launch_qconv16(const GemmArgs& g, const ConvGeom& cg, hipStream_t st);
 // C[M,N] = act[M,K] x wgt[N,K]^T on int8 MFMA; out row-major [M,N].
 hipError_t launch_qdense(const GemmArgs& g, hipStream_t st);
 

@@ -1,5 +1,6 @@
 // Quantized GEMM on the gfx950 int8 matrix cores (v_mfma_i32_32x32x32_i8):
-// dense layers and non-depthwise convolutions (implicit GEMM), int32
+// dispatch of dense layers and convolutions, and the general kernel for
+// non-depthwise convolutions (implicit GEMM from the caller's layout), int32
 // accumulation (optionally reduced modulo 2^16), fused requantize epilogue.
 //
 // A workgroup of WP x WQ wavefronts computes a BP x BQ tile of
@@ -10,7 +11,7 @@
 // accumulator registers, four CONSECUTIVE rows i.  P is therefore chosen as
 // the operand whose index is contiguous in the output tensor, so that four
 // results pack into one 32-bit store:
-//   dense, NHWC conv : P = weights (i = output channel),  Q = activations
+//   NHWC conv        : P = weights (i = output channel),  Q = activations
 //   NCHW conv        : P = activations (i = output pixel), Q = weights
 //
 // What bounds the kernel.  A CU multiplies 4096 byte pairs per clock but its
@@ -46,7 +47,7 @@ namespace {
 constexpr int kBK = 128;           // k-bytes per LDS stage
 constexpr int kChunks = kBK / 16;  // 16-byte chunks per LDS row
 
-enum { MODE_DENSE = 0, MODE_CONV_NCHW = 1, MODE_CONV_NHWC = 2 };
+enum { MODE_CONV_NCHW = 1, MODE_CONV_NHWC = 2 };
 
 __device__ __forceinline__ int lds_off(int row, int chunk) {
   return row * kBK + ((chunk ^ row ^ (row >> 3)) & (kChunks - 1)) * 16;
@@ -177,11 +178,7 @@ __device__ __forceinline__ v4i load_im2col_nhwc(const QgemmParams& p, const Pixe
   return v4i{(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
 }
 
-// VEC: every operand row can be read as aligned 16-byte chunks (dense: K % 16 == 0; NHWC: C % 16
-// == 0).  Then staging loads are unconditional (addresses clamped into the tensor, the value
-// replaced afterwards where it lies outside), so that a whole stage of loads is in flight while
-// the previous stage is multiplied.  Without VEC the loads are assembled bytewise (any shape).
-template <int WP, int WQ, int TP, int TQ, int MODE, bool VEC>
+template <int WP, int WQ, int TP, int TQ, int MODE>
 __global__ __launch_bounds__(64 * WP * WQ) void qgemm_kernel(QgemmParams p) {
   constexpr int NT = 64 * WP * WQ;
   constexpr int BP = WP * TP * 32;
@@ -195,7 +192,7 @@ __global__ __launch_bounds__(64 * WP * WQ) void qgemm_kernel(QgemmParams p) {
   constexpr int NW = ACT_ON_P ? NQ : NP;
   constexpr int RW = ACT_ON_P ? BQ : BP;  // rows of the weight tile
   constexpr int STAGE = (BP + BQ) * kBK;  // bytes of one LDS stage
-  static_assert(MODE == MODE_DENSE || (RA % 64 == 0 && (NT % RA == 0 || RA % NT == 0)),
+  static_assert(RA % 64 == 0 && (NT % RA == 0 || RA % NT == 0),
                 "im2col staging needs a fixed tile row per lane and a uniform chunk per wavefront");
 
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -223,92 +220,44 @@ __global__ __launch_bounds__(64 * WP * WQ) void qgemm_kernel(QgemmParams p) {
   const int w_lds = ACT_ON_P ? BP * kBK : 0;
 
   // im2col: the lane's tile row is the same in every stage
-  PixelPos pp{};
-  if constexpr (MODE != MODE_DENSE) pp = pixel_pos(p.g, a0 + (t % RA), p.M, MODE == MODE_CONV_NHWC);
+  const PixelPos pp = pixel_pos(p.g, a0 + (t % RA), p.M, MODE == MODE_CONV_NHWC);
 
   v4i st_a[NA], st_w[NW];
   int32_t wsum[NW];
 #pragma unroll
   for (int s = 0; s < NW; ++s) wsum[s] = 0;
 
-  // fast path: clamped row pointers, computed once
-  const uint8_t* wrow[NW];
-  const uint8_t* arow[NA];
-  bool wrow_ok[NW], arow_ok[NA];
-  if constexpr (VEC) {
+  auto fetch = [&](int k0) {
 #pragma unroll
     for (int s = 0; s < NW; ++s) {
       const int q = t + NT * s;
-      const int row = w0 + q / kChunks;
-      wrow_ok[s] = (q < RW * kChunks) && row < p.N;
-      wrow[s] = reinterpret_cast<const uint8_t*>(p.wgt) + (size_t)(wrow_ok[s] ? row : 0) * p.K +
-                (q % kChunks) * 16;
-    }
-    if constexpr (MODE == MODE_DENSE) {
-#pragma unroll
-      for (int s = 0; s < NA; ++s) {
-        const int q = t + NT * s;
-        const int row = a0 + q / kChunks;
-        arow_ok[s] = (q < RA * kChunks) && row < p.M;
-        arow[s] = p.act + (size_t)(arow_ok[s] ? row : 0) * p.K + (q % kChunks) * 16;
-      }
-    }
-  }
-  const int kmax = p.K - 16;  // last chunk start that is inside a row (VEC: K % 16 == 0, K >= 16)
-
-  auto fetch = [&](int k0) {
-    if constexpr (VEC) {
-#pragma unroll
-      for (int s = 0; s < NW; ++s) {
-        const int kc = k0 + ((t + NT * s) % kChunks) * 16;
-        const int back = kc > kmax ? kc - kmax : 0;  // pull a chunk beyond K back inside the row
-        st_w[s] = *reinterpret_cast<const v4i*>(wrow[s] + k0 - back);
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < NW; ++s) {
-        const int q = t + NT * s;
-        st_w[s] = v4i{0, 0, 0, 0};
-        if (q < RW * kChunks)
-          st_w[s] = load_rowmajor(reinterpret_cast<const uint8_t*>(p.wgt), w0 + q / kChunks, p.N,
-                                  p.K, k0 + (q % kChunks) * 16, p.vec_k);
-      }
+      st_w[s] = v4i{0, 0, 0, 0};
+      if (q < RW * kChunks)
+        st_w[s] = load_rowmajor(reinterpret_cast<const uint8_t*>(p.wgt), w0 + q / kChunks, p.N,
+                                p.K, k0 + (q % kChunks) * 16, p.vec_k);
     }
 #pragma unroll
     for (int s = 0; s < NA; ++s) {
       const int q = t + NT * s;
-      if constexpr (MODE == MODE_DENSE && VEC) {
-        const int kc = k0 + (q % kChunks) * 16;
-        const int back = kc > kmax ? kc - kmax : 0;
-        st_a[s] = *reinterpret_cast<const v4i*>(arow[s] + k0 - back);
-      } else {
-        st_a[s] = v4i{0, 0, 0, 0};
-        if (q < RA * kChunks) {
-          if constexpr (MODE == MODE_DENSE) {
-            st_a[s] = load_rowmajor(p.act, a0 + q / kChunks, p.M, p.K, k0 + (q % kChunks) * 16, p.vec_k);
-          } else {
-            const int ch = __builtin_amdgcn_readfirstlane(q / RA);
-            if constexpr (MODE == MODE_CONV_NCHW)
-              st_a[s] = load_im2col_nchw(p, pp, k0 + ch * 16);
-            else
-              st_a[s] = load_im2col_nhwc(p, pp, k0 + ch * 16);
-          }
-        }
+      st_a[s] = v4i{0, 0, 0, 0};
+      if (q < RA * kChunks) {
+        const int ch = __builtin_amdgcn_readfirstlane(q / RA);
+        if constexpr (MODE == MODE_CONV_NCHW)
+          st_a[s] = load_im2col_nchw(p, pp, k0 + ch * 16);
+        else
+          st_a[s] = load_im2col_nhwc(p, pp, k0 + ch * 16);
       }
     }
   };
 
-  // registers -> LDS; the weight row sums and the uint8 -> int8 flip happen here, once per byte
-  auto stash = [&](int buf, int k0) {
+  // registers -> LDS; the weight row sums are taken here, once per byte
+  auto stash = [&](int buf) {
     uint8_t* base = s_tile + buf * STAGE;
 #pragma unroll
     for (int s = 0; s < NW; ++s) {
       const int q = t + NT * s;
       if (q < RW * kChunks) {
-        v4i v = st_w[s];
-        if constexpr (VEC) {
-          if (!(wrow_ok[s] && k0 + (q % kChunks) * 16 < p.K)) v = v4i{0, 0, 0, 0};
-        }
+        const v4i v = st_w[s];
         wsum[s] += bytesum(v);
         *reinterpret_cast<v4i*>(base + w_lds + lds_off(q / kChunks, q % kChunks)) = v;
       }
@@ -316,19 +265,7 @@ __global__ __launch_bounds__(64 * WP * WQ) void qgemm_kernel(QgemmParams p) {
 #pragma unroll
     for (int s = 0; s < NA; ++s) {
       const int q = t + NT * s;
-      if (q < RA * kChunks) {
-        if constexpr (MODE == MODE_DENSE) {
-          const int x4 = (int)p.act_xor4;
-          v4i v = st_a[s];
-          if constexpr (VEC) {
-            if (!(arow_ok[s] && k0 + (q % kChunks) * 16 < p.K)) v = v4i{0, 0, 0, 0};
-          }
-          *reinterpret_cast<v4i*>(base + a_lds + lds_off(q / kChunks, q % kChunks)) =
-              v4i{v.x ^ x4, v.y ^ x4, v.z ^ x4, v.w ^ x4};
-        } else {
-          *reinterpret_cast<v4i*>(base + a_lds + lds_off(q % RA, q / RA)) = st_a[s];
-        }
-      }
+      if (q < RA * kChunks) *reinterpret_cast<v4i*>(base + a_lds + lds_off(q % RA, q / RA)) = st_a[s];
     }
   };
 
@@ -343,7 +280,7 @@ __global__ __launch_bounds__(64 * WP * WQ) void qgemm_kernel(QgemmParams p) {
   const int KT = (p.K + kBK - 1) / kBK;
   if (KT > 0) {
     fetch(0);
-    stash(0, 0);
+    stash(0);
   }
   __syncthreads();
 
@@ -372,7 +309,7 @@ __global__ __launch_bounds__(64 * WP * WQ) void qgemm_kernel(QgemmParams p) {
         for (int j = 0; j < TQ; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(pf[i], qf[j], acc[i][j], 0, 0, 0);
     }
-    if (kt + 1 < KT) stash(buf ^ 1, (kt + 1) * kBK);
+    if (kt + 1 < KT) stash(buf ^ 1);
     __syncthreads();
   }
 
@@ -405,7 +342,7 @@ constexpr TileShape kShapes[] = {
 };
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
 
-template <int WP, int WQ, int TP, int TQ, int MODE, bool VEC>
+template <int WP, int WQ, int TP, int TQ, int MODE>
 hipError_t launch_cfg(const QgemmParams& p, hipStream_t st) {
   constexpr int BP = WP * TP * 32, BQ = WQ * TQ * 32;
   constexpr int CH = (MODE == MODE_CONV_NCHW) ? BQ : BP;
@@ -413,7 +350,7 @@ hipError_t launch_cfg(const QgemmParams& p, hipStream_t st) {
   const int P_ext = (MODE == MODE_CONV_NCHW) ? p.M : p.N;
   const int Q_ext = (MODE == MODE_CONV_NCHW) ? p.N : p.M;
   const int64_t tiles = (int64_t)((P_ext + BP - 1) / BP) * ((Q_ext + BQ - 1) / BQ);
-  auto kern = qgemm_kernel<WP, WQ, TP, TQ, MODE, VEC>;
+  auto kern = qgemm_kernel<WP, WQ, TP, TQ, MODE>;
   static std::atomic<uint64_t> attr_set{0};  // per kernel: the devices whose dynamic-LDS limit is raised
   hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), (int)lds, attr_set);
   if (e != hipSuccess) return e;
@@ -424,7 +361,6 @@ hipError_t launch_cfg(const QgemmParams& p, hipStream_t st) {
 // Whether a shape can be instantiated for a mode (im2col staging wants a fixed tile row per
 // lane and a wavefront-uniform chunk).
 constexpr bool shape_ok(int mode, int wp, int wq, int tp, int tq) {
-  if (mode == MODE_DENSE) return true;
   const int nt = 64 * wp * wq;
   const int ra = (mode == MODE_CONV_NCHW) ? wp * tp * 32 : wq * tq * 32;
   return ra % 64 == 0 && (nt % ra == 0 || ra % nt == 0);
@@ -433,11 +369,11 @@ constexpr bool shape_ok(int mode, int wp, int wq, int tp, int tq) {
 template <int MODE, int I>
 hipError_t launch_shape_rec(int shape, const QgemmParams& p, hipStream_t st) {
   if constexpr (I >= kNumShapes) {
-    return launch_cfg<2, 2, 2, 2, MODE, false>(p, st);
+    return launch_cfg<2, 2, 2, 2, MODE>(p, st);
   } else {
     constexpr TileShape s = kShapes[I];
     if constexpr (shape_ok(MODE, s.wp, s.wq, s.tp, s.tq)) {
-      if (shape == I) return launch_cfg<s.wp, s.wq, s.tp, s.tq, MODE, MODE == MODE_DENSE>(p, st);
+      if (shape == I) return launch_cfg<s.wp, s.wq, s.tp, s.tq, MODE>(p, st);
     }
     return launch_shape_rec<MODE, I + 1>(shape, p, st);
   }
@@ -497,32 +433,37 @@ void set_test_hook(int key, int value) {
   if (key >= 0 && key < kNumHooks) g_hook[key].store(value, std::memory_order_relaxed);
 }
 
+hipError_t launch_qgemm_any(const QgemmParams& p, bool i16, int form, hipStream_t st);
+
 hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
-  if (a.operand16) return launch_qgemm16(a, nullptr, st);
   QgemmParams p = make_qgemm_params(a, nullptr);
-  p.vec_k = (a.K % 16 == 0) && ptr_aligned(a.act, 16) && ptr_aligned(a.wgt, 16);
+  const bool vec_k = !a.operand16 && a.K % 16 == 0 && a.K >= 16 && ptr_aligned(a.act, 16) && ptr_aligned(a.wgt, 16);
+  const bool fits32 = (int64_t)a.N * a.K < (1ll << 31) && (int64_t)a.M * a.K < (1ll << 31);
+  if (!vec_k || !fits32 || g_hook[kHookGemmPath].load(std::memory_order_relaxed) == 1) {
+    const int tile = g_hook[kHookGenericTile].load(std::memory_order_relaxed);
+    return launch_qgemm_any(p, a.operand16, tile < 0 ? -1 : tile % 5, st);
+  }
+  const int forced = g_hook[kHookDmaTile].load(std::memory_order_relaxed);
+  // A long reduction over few tiles: the direct form splits it over eight wavefronts (1 x 4096 -> 4096
+  // 8.2 us against 15.5, 37 x 3072 -> 768 8.3 against 9.4; equal at K = 768).
+  if (forced < 0 && a.K >= 1024 && (int64_t)((a.N + 31) / 32) * ((a.M + 31) / 32) <= 256)
+    return launch_qgemm_any(p, false, 0, st);
+  p.vec_k = 1;
   p.vec_out = (a.N % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
   p.vec16_out = (a.N % 16 == 0) && ptr_aligned(a.out, 16);
-  if (!p.vec_k || a.K < 16) return launch_cfg<2, 2, 2, 2, MODE_DENSE, false>(p, st);
-  const bool generic = g_hook[kHookGemmPath].load(std::memory_order_relaxed) == 1;
-  const bool fits32 = (int64_t)a.N * a.K < (1ll << 31) && (int64_t)a.M * a.K < (1ll << 31);
-  if (fits32 && !generic) {
-    const int forced = g_hook[kHookDmaTile].load(std::memory_order_relaxed);
-    // Tile shape: the one whose busiest CU has the least to do (rounds of tiles over the 256
-    // CUs x tile area), with larger tiles discounted for their better operand reuse.
-    struct Cand { int id, bp, bq; double eff; };
-    static const Cand cands[] = {{0, 256, 256, 1.0}, {1, 192, 256, 0.95}, {2, 128, 128, 0.75}, {4, 64, 64, 0.5}};
-    int best = 0;
-    double best_cost = 0;
-    for (const Cand& c : cands) {
-      const int64_t tiles = (int64_t)((a.N + c.bp - 1) / c.bp) * ((a.M + c.bq - 1) / c.bq);
-      const double cost = (double)((tiles + 255) / 256) * c.bp * c.bq / c.eff;
-      if (c.id == 0 || cost < best_cost) { best = c.id; best_cost = cost; }
-    }
-    return launch_qdense_dma(p, forced >= 0 ? forced : best, st);
+  // Tile shape: the one whose busiest CU has the least to do (rounds of tiles over the 256
+  // CUs x tile area), with larger tiles discounted for their better operand reuse.
+  struct Cand { int id, bp, bq; double eff; };
+  static const Cand cands[] = {{0, 256, 256, 1.0}, {1, 192, 256, 0.95}, {2, 128, 128, 0.75}, {4, 64, 64, 0.5}};
+  int best = 0;
+  double best_cost = 0;
+  for (const Cand& c : cands) {
+    const int64_t tiles = (int64_t)((a.N + c.bp - 1) / c.bp) * ((a.M + c.bq - 1) / c.bq);
+    const double cost = (double)((tiles + 255) / 256) * c.bp * c.bq / c.eff;
+    if (c.id == 0 || cost < best_cost) { best = c.id; best_cost = cost; }
   }
-  return launch_shape<MODE_DENSE>(pick_shape(MODE_DENSE, a.N, a.M, a.K), p, st);
+  return launch_qdense_dma(p, forced >= 0 ? forced : best, st);
 }
 
 hipError_t launch_qconv_dma(const QgemmParams& p, bool nchw_out, hipStream_t st);
@@ -584,7 +525,7 @@ static hipError_t conv_dma(const GemmArgs& a, const ConvGeom& cg, void* ws, bool
 hipError_t launch_qconv_gemm(const GemmArgs& a, const ConvGeom& cg, void* ws, bool weights_ready,
                              hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
-  if (a.operand16) return launch_qgemm16(a, &cg, st);
+  if (a.operand16) return launch_qconv16(a, cg, st);
   hipError_t err = hipSuccess;
   const int path = g_hook[kHookGemmPath].load(std::memory_order_relaxed);  // 1 / 2: skip the special cases
   if (path == 0) {

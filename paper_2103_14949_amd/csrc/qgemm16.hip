@@ -1,10 +1,10 @@
-// int16 x int16 operands with 32-bit (or 24-bit) accumulation: the second operand triple the
+// int16 x int16 convolution with 32-bit (or 24-bit) accumulation: the second operand triple the
 // paper names (Introduction; Sec. 4.1 hardware specification: "conv2d operator with int16 x int16
 // inputs with int32 accumulation").  gfx950 has no int16 matrix instruction, so this runs on the
 // vector ALUs with v_dot2_i32_i16 (two multiply-adds per lane and instruction): a plain LDS-tiled
 // GEMM, 64 x 64 outputs per workgroup, 32 reduction elements per stage, 4 x 4 outputs per
-// thread.  Dense layers and groups == 1 convolutions (both layouts, as an implicit GEMM whose
-// loader gathers the taps) share the kernel.
+// thread; groups == 1 convolutions in both layouts, as an implicit GEMM whose loader gathers the taps (dense
+// layers: qgemm_any.hip).
 //
 // The activation zero point is not subtracted from the operands (a - z need not fit int16):
 // sum (a - z) w = sum a w - z sum w, with the weight row sums accumulated by the same threads.
@@ -31,8 +31,8 @@ struct G16Params {
   int32_t M, N, K;
   int32_t per_channel, has_rq, acc_wrap_shift;
   int32_t z_a;
-  int32_t mode;      // 0 dense, 1 conv NCHW, 2 conv NHWC
-  int32_t vec_k;     // dense rows are aligned 16-byte chunks
+  int32_t mode;      // 1 conv NCHW, 2 conv NHWC
+  int32_t vec_k;     // weight rows are aligned 16-byte chunks
   RequantScalars rs;
   ConvGeom g;
 };
@@ -46,7 +46,6 @@ __device__ __forceinline__ int32_t dot2(uint32_t a, uint32_t b, int32_t c) {
 // taps outside the image as the zero point.
 __device__ __forceinline__ int32_t act_elem(const G16Params& p, int m, int k) {
   if (m >= p.M || k >= p.K) return 0;
-  if (p.mode == 0) return p.act[(int64_t)m * p.K + k];
   const ConvGeom& g = p.g;
   const int ohw = g.OH * g.OW;
   const int b = m / ohw;
@@ -93,14 +92,9 @@ __global__ __launch_bounds__(256) void qgemm16_kernel(G16Params p) {
   for (int k0 = 0; k0 < p.K; k0 += kStage) {
     uint32_t va[4], vw[4];
     const int m = m0 + lrow, n = n0 + lrow, k = k0 + lchunk;
-    if (p.vec_k && p.mode == 0 && m < p.M && k + 8 <= p.K) {
-      const uint4 q = *reinterpret_cast<const uint4*>(p.act + (int64_t)m * p.K + k);
-      va[0] = q.x; va[1] = q.y; va[2] = q.z; va[3] = q.w;
-    } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        va[e] = ((uint32_t)act_elem(p, m, k + 2 * e) & 0xffffu) | ((uint32_t)act_elem(p, m, k + 2 * e + 1) << 16);
-    }
+    for (int e = 0; e < 4; ++e)
+      va[e] = ((uint32_t)act_elem(p, m, k + 2 * e) & 0xffffu) | ((uint32_t)act_elem(p, m, k + 2 * e + 1) << 16);
     if (p.vec_k && n < p.N && k + 8 <= p.K) {
       const uint4 q = *reinterpret_cast<const uint4*>(p.wgt + (int64_t)n * p.K + k);
       vw[0] = q.x; vw[1] = q.y; vw[2] = q.z; vw[3] = q.w;
@@ -170,7 +164,7 @@ __global__ __launch_bounds__(256) void qgemm16_kernel(G16Params p) {
 
 }  // namespace
 
-hipError_t launch_qgemm16(const GemmArgs& a, const ConvGeom* cg, hipStream_t st) {
+hipError_t launch_qconv16(const GemmArgs& a, const ConvGeom& cg, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
   G16Params p{};
   p.act = static_cast<const int16_t*>(a.act);
@@ -184,11 +178,10 @@ hipError_t launch_qgemm16(const GemmArgs& a, const ConvGeom* cg, hipStream_t st)
   p.has_rq = a.has_rq;
   p.acc_wrap_shift = a.acc_wrap_shift;
   p.z_a = a.act_zero_point;
-  p.mode = cg ? (cg->nhwc ? 2 : 1) : 0;
-  p.vec_k = (a.K % 8 == 0) && ((reinterpret_cast<uintptr_t>(a.act) & 15u) == 0) &&
-            ((reinterpret_cast<uintptr_t>(a.wgt) & 15u) == 0);
+  p.mode = cg.nhwc ? 2 : 1;
+  p.vec_k = (a.K % 8 == 0) && ((reinterpret_cast<uintptr_t>(a.wgt) & 15u) == 0);
   p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
-  if (cg) p.g = *cg;
+  p.g = cg;
   const int64_t tiles = (int64_t)((a.M + kTile - 1) / kTile) * ((a.N + kTile - 1) / kTile);
   if (tiles >= (1ll << 31)) return hipErrorInvalidValue;
   if (a.act_zero_point != 0)
