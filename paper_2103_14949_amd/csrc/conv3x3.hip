@@ -35,6 +35,8 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));  // results go out at any alignment
+typedef uint32_t u32_any __attribute__((aligned(1)));
 
 struct C3Params {
   const uint8_t* act;
@@ -327,12 +329,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
 
     // ---- epilogue: the lane's 16 consecutive pixels of channel o0 + 32 tn + j, per row block
     const int npix = rows * W;                           // valid pixels of this tile
-    const bool tile16 = (npix & 15) == 0 && ((y0 * W) & 15) == 0 && (HW & 15) == 0;
 #pragma unroll
     for (int f = 0; f < AF; ++f) {
       const int pix0 = 32 * (AF * wave + f) + 16 * h;    // first of the 16 pixels inside the tile
       const int64_t obase = (int64_t)b * O * HW + (int64_t)y0 * W + pix0;
-      const bool full16 = tile16 && pix0 + 16 <= npix;
+      const int left = npix - pix0;                      // (image sizes off a multiple of 16: unaligned stores, fours at the end)
 #pragma unroll
       for (int tn = 0; tn < 2; ++tn) {
         const int o = o0 + 32 * tn + j;
@@ -366,12 +367,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
               dw[g] = pack4(v[0], v[1], v[2], v[3]);
             }
           }
-          if (full16 && (reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
-            *reinterpret_cast<uint4*>(dst) = make_uint4(dw[0], dw[1], dw[2], dw[3]);
-          } else {
+          if (left >= 16) {
+            *reinterpret_cast<v4i_any*>(dst) = v4i{(int)dw[0], (int)dw[1], (int)dw[2], (int)dw[3]};
+          } else {  // (W is a multiple of 4, so are the tile's pixels)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-              if (pix0 + r < npix) dst[r] = (uint8_t)(dw[r >> 2] >> (8 * (r & 3)));
+            for (int g = 0; g < 4; ++g)
+              if (4 * g < left) reinterpret_cast<u32_any*>(dst)[g] = dw[g];
           }
         } else {
           int32_t v[16];
@@ -382,30 +383,22 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
           }
           if (p.out_mode == 1) {
             int32_t* dst = static_cast<int32_t*>(p.out) + oo;
-            if (full16 && (reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
 #pragma unroll
-              for (int g = 0; g < 4; ++g)
-                reinterpret_cast<int4*>(dst)[g] = make_int4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
-            } else {
-#pragma unroll
-              for (int r = 0; r < 16; ++r)
-                if (pix0 + r < npix) dst[r] = v[r];
-            }
+            for (int g = 0; g < 4; ++g)
+              if (4 * g < left) reinterpret_cast<v4i_any*>(dst)[g] = v4i{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
           } else {
             int16_t* dst = static_cast<int16_t*>(p.out) + oo;
-            if (full16 && (reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
+            uint32_t dq[8];
 #pragma unroll
-              for (int g = 0; g < 2; ++g) {
-                uint32_t dq[4];
+            for (int x = 0; x < 8; ++x) dq[x] = ((uint32_t)v[2 * x] & 0xffffu) | ((uint32_t)v[2 * x + 1] << 16);
+            if (left >= 16) {
 #pragma unroll
-                for (int x = 0; x < 4; ++x)
-                  dq[x] = ((uint32_t)v[8 * g + 2 * x] & 0xffffu) | ((uint32_t)v[8 * g + 2 * x + 1] << 16);
-                reinterpret_cast<uint4*>(dst)[g] = make_uint4(dq[0], dq[1], dq[2], dq[3]);
-              }
+              for (int g = 0; g < 2; ++g)
+                reinterpret_cast<v4i_any*>(dst)[g] = v4i{(int)dq[4 * g], (int)dq[4 * g + 1], (int)dq[4 * g + 2], (int)dq[4 * g + 3]};
             } else {
 #pragma unroll
-              for (int r = 0; r < 16; ++r)
-                if (pix0 + r < npix) dst[r] = (int16_t)v[r];
+              for (int x = 0; x < 8; ++x)
+                if (2 * x < left) reinterpret_cast<u32_any*>(dst)[x] = dq[x];
             }
           }
         }
