@@ -354,11 +354,17 @@ __global__ __launch_bounds__(64) void pw_nchw_quad_kernel(PwArgs p) {
     store_all.template operator()<false>();
 }
 
+// Whether the 128-pixel form serves C -> N channels: it re-reads the input per 32 output channels, from the cache, and
+// has four times the pixels in flight per load (us of this form, of the 32-pixel one or the general kernel: 88 -> 528 at
+// 56 x 56 13, 85; 128 -> 128 at 28 x 28 6.5, 8.5; 96 -> 40 5.2, 4.5; 528 -> 88 11.4, 10.7).
+inline bool quad_form(int64_t C, int64_t N) {
+  return N <= 32 || ((C <= 64 || (N > 64 && C <= 128) || (N > 128 && C <= 256)) && (N + 31) / 32 <= 65535);
+}
+
 template <int MODE, bool ACC16>
 hipError_t launch_nt(const PwArgs& p, hipStream_t st) {
-  // 128 pixels per wavefront, one wavefront per workgroup, 32 output channels per workgroup row:
-  // for up to 32 output channels, and for few input channels (the input is then cheap to re-read)
-  if (p.N <= 32 || (p.C <= 64 && (p.N + 31) / 32 <= 65535)) {
+  // 128 pixels per wavefront, one wavefront per workgroup, 32 output channels per workgroup row
+  if (quad_form(p.C, p.N)) {
     PwArgs q = p;
     q.tiles_per_img = (p.HW + 127) / 128;
     q.tiles = (int64_t)p.B * q.tiles_per_img;  // < 2^31: B and H*W are 32-bit and B * H*W fits the tensor
@@ -378,7 +384,7 @@ hipError_t launch_nt(const PwArgs& p, hipStream_t st) {
 bool try_qconv_pointwise_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hipError_t* err) {
   const int64_t HW = (int64_t)cg.H * cg.W;
   const size_t esz = a.has_rq ? 1 : (a.acc16 ? 2 : 4);
-  const bool quad = cg.O <= 32 || cg.C <= 64;  // the 128-pixel kernel (any O when C is small)
+  const bool quad = quad_form(cg.C, cg.O);  // the 128-pixel kernel
   if (a.acc_wrap_shift != 0 && a.acc_wrap_shift != 16) return false;  // 24-bit accumulators: the general path
   if (a.has_rq && a.rq.half_away && !quad) return false;  // the wider kernel: ties toward +infinity only
   if (cg.nhwc || cg.KH != 1 || cg.KW != 1 || cg.stride_h != 1 || cg.stride_w != 1 || cg.pad_h != 0 ||
