@@ -201,9 +201,9 @@ hago_status hago_qdense(const void* a, hago_qtype a_t, const void* w,
  * NCHW 3x3 stride-1 pad-1 convolutions with C a multiple of 32 up to 128 and
  * W a multiple of 4 up to 128 (configs 2 and 3) run one kernel that reads
  * the caller's tensors directly, as fast as or faster than hago_qconv2d_ws;
- * every other groups == 1 geometry runs a general kernel that gathers its
- * operands from the caller's layout and is several times slower than
- * hago_qconv2d_ws.
+ * every other groups == 1 geometry runs a general one-launch kernel, which
+ * hago_qconv2d_ws only beats on long reductions (3x3 beyond 128 channels, 5x5
+ * and larger).
  */
 hago_status hago_qconv2d(const void* a, hago_qtype a_t, const void* w,
                          hago_qtype w_t, const int32_t* bias,
@@ -427,8 +427,9 @@ hago_status hago_probe_copy(const void* src, void* dst, int64_t bytes,
  * this process, so that tests can compare every variant with the oracle on
  * one shape.  Results never depend on it.  Keys:
  *   HAGO_HOOK_GEMM_PATH     0 automatic; 1 the general register-staged kernel;
- *                           2 the streaming kernel, skipping the kernels
- *                           specialised for 1x1 and 3x3 convolutions
+ *                           2 the streaming kernel, skipping the one-launch
+ *                           convolution kernels; 3 the general one-launch
+ *                           convolution kernel
  *   HAGO_HOOK_STREAM_TILE   -1 automatic; 0..4 a tile of the streaming dense kernel
  *   HAGO_HOOK_GENERAL_TILE  -1 automatic; 0..6 a tile of the general convolution
  *                           kernel (modulo 5: a form of the general dense kernel)

@@ -114,6 +114,9 @@ void set_test_hook(int key, int value);
 // 3x3 stride-1 pad-1 NCHW convolution in one launch, no scratch; false when the geometry is not
 // that kernel's (nothing is launched then).
 bool try_qconv3x3_nchw(const GemmArgs& g, const ConvGeom& cg, hipStream_t st, hipError_t* err);
+// Convolution of any geometry in one launch, no scratch; forced_shape >= 0: that wavefront shape (tests).  False when the
+// geometry is not that kernel's (nothing is launched then).
+bool try_qconv_direct(const GemmArgs& g, const ConvGeom& cg, int forced_shape, hipStream_t st, hipError_t* err);
 // 1x1 stride-1 unpadded NCHW convolution straight from the caller's buffers; false when the
 // geometry is not that kernel's (nothing is launched then).
 bool try_qconv_pointwise_nchw(const GemmArgs& g, const ConvGeom& cg, hipStream_t st, hipError_t* err);

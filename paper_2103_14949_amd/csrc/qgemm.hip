@@ -538,7 +538,22 @@ hipError_t launch_qconv_gemm(const GemmArgs& a, const ConvGeom& cg, void* ws, bo
     // (faster than rewriting it through the workspace first, and it needs none)
     if (try_qconv3x3_nchw(a, cg, st, &err)) return err;
   }
-  if (ws && path != 1 && qconv_workspace_bytes(cg) >= 0) return conv_dma(a, cg, ws, weights_ready, st);
+  const int tile = g_hook[kHookGenericTile].load(std::memory_order_relaxed);
+  if (path == 3 && try_qconv_direct(a, cg, tile, st, &err)) return err;
+  if (ws && path != 1 && qconv_workspace_bytes(cg) >= 0) {
+    // The rewrite through the workspace costs a launch and the copy's traffic; staging the weights in every
+    // workgroup costs the one-launch kernel more the longer the reduction is (us with workspace, one launch):
+    //   few channels, 1x1               3 -> 64 7x7 at 224 x 224: 26, 14;  64 -> 128 1x1 stride 2: 12, 7.4
+    //   3x3 up to 128 channels, NCHW    64 -> 128 stride 2: 14.2, 10.5;  40 -> 45 at 42 x 41: 15, 10.6;  256 -> 256: 17, 20
+    //   3x3, NHWC, 16 channels a chunk  the rewrite is a plain copy: 64 -> 64 at 28 x 28 8.6, 9.8;  at 56 x 56, batch 32 18, 15.5
+    //   5x5 and larger                  30 -> 43 5x5: 15, 20
+    const int taps = cg.KH * cg.KW;
+    const bool one_launch = cg.C <= 16 || taps == 1 ||
+                            (taps <= 9 && cg.C <= 128 && (!cg.nhwc || cg.C % 16 != 0 || (int64_t)cg.B * cg.C * cg.H * cg.W >= (3 << 20)));
+    if (path == 0 && one_launch && try_qconv_direct(a, cg, -1, st, &err)) return err;
+    return conv_dma(a, cg, ws, weights_ready, st);
+  }
+  if (path == 0 && try_qconv_direct(a, cg, -1, st, &err)) return err;
   QgemmParams p = make_qgemm_params(a, &cg);
   if (cg.nhwc) {
     p.vec_k = (cg.C % 16 == 0) && ptr_aligned(a.act, 16) && ptr_aligned(a.wgt, 16);
