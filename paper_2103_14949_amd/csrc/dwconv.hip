@@ -3,8 +3,8 @@
 // so there is no MFMA here; the work is 9 multiply-adds per output on the
 // vector ALUs (4 at a time with v_dot4).
 //
-//   rows3x3  : NCHW, 3x3, stride 1, pad 1, W % 4 == 0, aligned.  One WAVEFRONT per (image,
-//              channel, band of rows, segment of 64 columns) and no LDS: a lane loads one
+//   rows3x3  : NCHW, 3x3, stride 1, pad 1, W >= 4.  One WAVEFRONT per (image,
+//              channel, band of rows, segment of up to 64 columns) and no LDS: a lane loads one
 //              dword per input row and gets its neighbours' by DPP; see the kernel.
 //   rows3x3s2: the same for stride 2 (two outputs per lane and row).
 //   small3x3 : stride 1, W <= 16, H <= 64, any alignment: several planes per wavefront.
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kThreads) void dw_wave3x3_kernel(DwArgs p, int32_t 
 }
 
 
-// NCHW 3x3 stride 1 pad 1, W % 4 == 0, 4-byte aligned tensors and weights, planes
+// NCHW 3x3 stride 1 pad 1, W >= 4, 4-byte aligned weights, planes
 // below 2 GB: no LDS.  One wavefront per (plane, band of 4 * rpc rows), rpc <= 16.  Lane (q, rc):
 // strip of four output columns q, quarter rc of the band's rows.  A lane loads ONE dword per
 // input row (its own strip) and takes the left and right neighbours' dwords by DPP row shifts
@@ -356,11 +356,14 @@ __global__ __launch_bounds__(kThreads) void dw_wave3x3_kernel(DwArgs p, int32_t 
 // weights, bias and multiplier -- comes through scalar loads and scalar arithmetic, and the
 // per-output work is three dot products, one 64-bit multiply-add, one shift and one clamp.
 // MODE 0: requantized 8-bit, 1: raw int32, 2: raw int16; ACC16: accumulator wraps to 16 bits.
-// WIDE: images wider than 64 columns are cut into segments of 64 (grid z = band * nsegs + segment);
+// WIDE: images wider than 64 columns are cut into segments of segw <= 64 (grid z = band * nsegs + segment);
 // the lanes at the ends of a segment fetch the neighbouring segment's dword with one more load
 // per row, which replaces what the DPP shift cannot deliver.
-template <int MODE, bool ACC16, bool WIDE>
-__global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t rpc, int32_t nsegs) {
+// RAGGED: rows that are not whole dwords (or tensors at any byte).  Loads and stores are unaligned; the last strip of a
+// row is loaded from the row's last four bytes and shifted into place, and stored as those four bytes together with the
+// end of its left neighbour's results (16 x 288 planes of 41 x 41: 24.8 us through LDS, 8.6 here).
+template <int MODE, bool ACC16, bool WIDE, bool RAGGED>
+__global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t rpc, int32_t nsegs, int32_t segw) {
   // grid: x = groups of four channels, y = image, z = band (and column segment)
   const ConvGeom& g = p.g;
   const int H = g.H, W = g.W;
@@ -370,7 +373,7 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t 
   const int64_t plane = (int64_t)blockIdx.y * g.C + c;
   const int seg = WIDE ? (int)blockIdx.z % nsegs : 0;
   const int band = WIDE ? (int)blockIdx.z / nsegs : (int)blockIdx.z;
-  const int cb = seg * 64;  // first column of the segment
+  const int cb = WIDE ? seg * segw : 0;  // first column of the segment
   constexpr uint32_t kOob = 0x80000000u;
   constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
   constexpr int kPass = 16;  // most output rows per lane
@@ -378,12 +381,18 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t 
   const int q = lane & 15;
   const int rc = lane >> 4;
   const int y0 = (band * 4 + rc) * rpc;  // first output row of the lane
-  const bool has_strip = cb + (q << 2) < W;
-  const uint32_t lane_off = has_strip ? (uint32_t)(cb + (q << 2)) : kOob;  // byte column of the strip
+  const int x0 = cb + (q << 2);          // first column of the strip
+  const bool has_strip = x0 < W && (!WIDE || (q << 2) < segw);
+  // RAGGED: columns by which the row's last strip is pulled back to end with the row
+  const int pull = RAGGED && has_strip && x0 + 4 > W ? x0 + 4 - W : 0;
+  const uint32_t lane_off = has_strip ? (uint32_t)(x0 - pull) : kOob;  // byte column of the strip's dword
+  const uint32_t pull_bits = (uint32_t)(8 * pull), col_mask = 0xffffffffu >> pull_bits;
   // the dword beyond the segment's end that this lane stands in for (first lane: left, last: right)
   const bool left_edge = WIDE && q == 0 && seg > 0;
-  const bool right_edge = WIDE && q == 15 && cb + 64 < W;
-  const uint32_t edge_off = left_edge ? (uint32_t)(cb - 4) : (right_edge ? (uint32_t)(cb + 64) : kOob);
+  const bool right_edge = WIDE && (q << 2) + 4 == segw && cb + segw < W;
+  const int right_x = RAGGED && cb + segw + 4 > W ? W - 4 : cb + segw;  // (only its first column is used)
+  const uint32_t edge_off = left_edge ? (uint32_t)(cb - 4) : (right_edge ? (uint32_t)right_x : kOob);
+  const uint32_t edge_bits = RAGGED && right_edge ? (uint32_t)(8 * (cb + segw - right_x)) : 0u;
   const uint32_t x4 = p.act_xor * 0x01010101u;
   const uint32_t pad4 = (((uint32_t)p.z_a ^ p.act_xor) & 0xffu) * 0x01010101u;
   const int64_t pbytes = (int64_t)H * W;
@@ -425,6 +434,8 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t 
   auto row = [&](int i) {
     uint32_t flip = (i == 0 ? y0 > 0 : i < rows_in) ? flip_lane : pad4;
     asm volatile("" : "+v"(flip));
+    if constexpr (RAGGED)
+      return Row{(((d[i] >> pull_bits) ^ flip) & col_mask) | (pad4 & ~col_mask), WIDE ? (de[i] >> edge_bits) ^ flip : 0u};
     return Row{d[i] ^ flip, WIDE ? de[i] ^ flip : 0u};
   };
 
@@ -500,7 +511,7 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t 
   };
   // A store beyond the image lies beyond the plane, and a strip-less lane's offset starts at
   // 2^31: both are out of the descriptor's range and dropped.
-  const uint32_t so0 = has_strip ? (uint32_t)(cb + (q << 2) + y0 * W) * kEsz : kOob;
+  const uint32_t so0 = has_strip ? (uint32_t)(x0 - (MODE == 0 ? pull : 0) + y0 * W) * kEsz : kOob;
 
   // FOLD (requantized, 32-bit accumulator, and the channel's constants small enough): the
   // correction term, the rounding term and the output zero point all go into one 64-bit
@@ -511,7 +522,8 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t 
   // PLAIN: int8 activations with zero point 0 need no flip at all (the mask is zero everywhere)
   auto rows = [&]<bool FOLD, bool PLAIN>() {
     auto rowp = [&](int i) {
-      if constexpr (PLAIN) return Row{d[i], WIDE ? de[i] : 0u};
+      if constexpr (PLAIN && RAGGED) return Row{d[i] >> pull_bits, WIDE ? de[i] >> edge_bits : 0u};
+      else if constexpr (PLAIN) return Row{d[i], WIDE ? de[i] : 0u};
       else return row(i);
     };
     int32_t lo = p.rs.lo_rel + (FOLD ? z : 0), hi = p.rs.hi_rel + (FOLD ? z : 0);
@@ -543,15 +555,31 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t 
             const int64_t pr = (int64_t)acc[e] * (int64_t)m + k64 + (FOLD ? 0 : (int64_t)((acc[e] >> 31) & away));
             r[e] = med3((int32_t)(pr >> (31 + sh)), lo, hi) + (FOLD ? 0 : z);
           }
-          __builtin_amdgcn_raw_buffer_store_b32(pack4_perm(r[0], r[1], r[2], r[3]), rout, so, 0, 0);
+          uint32_t dw = pack4_perm(r[0], r[1], r[2], r[3]);
+          if constexpr (RAGGED) {
+            const uint32_t lw = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)dw, 0x111, 0xf, 0xf, true);  // row_shr:1
+            dw = (uint32_t)((((uint64_t)dw << 32) | lw) >> (32 - pull_bits));
+          }
+          __builtin_amdgcn_raw_buffer_store_b32(dw, rout, so, 0, 0);
         } else if constexpr (MODE == 1) {
           typedef int32_t v4i32 __attribute__((ext_vector_type(4)));
-          __builtin_amdgcn_raw_buffer_store_b128(v4i32{acc[0], acc[1], acc[2], acc[3]}, rout, so, 0, 0);
+          if constexpr (RAGGED) {
+            __builtin_amdgcn_raw_buffer_store_b128(v4i32{acc[0], acc[1], acc[2], acc[3]}, rout, pull ? kOob : so, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 3; ++e) __builtin_amdgcn_raw_buffer_store_b32((uint32_t)acc[e], rout, pull && e < 4 - pull ? so + 4 * e : kOob, 0, 0);
+          } else {
+            __builtin_amdgcn_raw_buffer_store_b128(v4i32{acc[0], acc[1], acc[2], acc[3]}, rout, so, 0, 0);
+          }
         } else {
           typedef uint32_t v2u32 __attribute__((ext_vector_type(2)));
-          __builtin_amdgcn_raw_buffer_store_b64(
-              v2u32{(uint32_t)(acc[0] & 0xffff) | ((uint32_t)acc[1] << 16),
-                    (uint32_t)(acc[2] & 0xffff) | ((uint32_t)acc[3] << 16)}, rout, so, 0, 0);
+          const v2u32 v = {(uint32_t)(acc[0] & 0xffff) | ((uint32_t)acc[1] << 16), (uint32_t)(acc[2] & 0xffff) | ((uint32_t)acc[3] << 16)};
+          if constexpr (RAGGED) {
+            __builtin_amdgcn_raw_buffer_store_b64(v, rout, pull ? kOob : so, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 3; ++e) __builtin_amdgcn_raw_buffer_store_b16((short)acc[e], rout, pull && e < 4 - pull ? so + 2 * e : kOob, 0, 0);
+          } else {
+            __builtin_amdgcn_raw_buffer_store_b64(v, rout, so, 0, 0);
+          }
         }
       }
     }
@@ -574,9 +602,9 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t 
 // lane with rpc output rows loads 2 * rpc + 1 input rows.  The two 8-bit results of a lane are
 // merged with its neighbour's into one dword store when output rows are dword-aligned
 // (W % 8 == 0), else stored as 16 bits.
-// MODE / ACC16 as above.
-template <int MODE, bool ACC16, bool WIDE>
-__global__ __launch_bounds__(kThreads) void dw_rows3x3s2_kernel(DwArgs p, int32_t rpc, int32_t nsegs) {
+// MODE / ACC16 / WIDE / RAGGED as above.
+template <int MODE, bool ACC16, bool WIDE, bool RAGGED>
+__global__ __launch_bounds__(kThreads) void dw_rows3x3s2_kernel(DwArgs p, int32_t rpc, int32_t nsegs, int32_t segw) {
   // grid: x = groups of four channels, y = image, z = band of 4 * rpc output rows (and column segment)
   const ConvGeom& g = p.g;
   const int H = g.H, W = g.W, OH = g.OH, OW = g.OW;
@@ -586,7 +614,7 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3s2_kernel(DwArgs p, int32_
   const int64_t plane = (int64_t)blockIdx.y * g.C + c;
   const int seg = WIDE ? (int)blockIdx.z % nsegs : 0;
   const int band = WIDE ? (int)blockIdx.z / nsegs : (int)blockIdx.z;
-  const int cb = seg * 64;  // first input column of the segment
+  const int cb = WIDE ? seg * segw : 0;  // first input column of the segment
   constexpr uint32_t kOob = 0x80000000u;
   constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
   constexpr int kPass = 16;  // most output rows per lane
@@ -595,8 +623,11 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3s2_kernel(DwArgs p, int32_
   const int rc = lane >> 4;
   const int oy0 = (band * 4 + rc) * rpc;  // first output row of the lane
   const int y0 = 2 * oy0 - 1;             // its first input row
-  const bool has_strip = cb + (q << 2) < W;
-  const uint32_t lane_off = has_strip ? (uint32_t)(cb + (q << 2)) : kOob;
+  const int x0 = cb + (q << 2);
+  const bool has_strip = x0 < W && (!WIDE || (q << 2) < segw);
+  const int pull = RAGGED && has_strip && x0 + 4 > W ? x0 + 4 - W : 0;
+  const uint32_t lane_off = has_strip ? (uint32_t)(x0 - pull) : kOob;
+  const uint32_t pull_bits = (uint32_t)(8 * pull), col_mask = 0xffffffffu >> pull_bits;
   const bool left_edge = WIDE && q == 0 && seg > 0;  // this lane's left neighbour is in the previous segment
   const uint32_t edge_off = left_edge ? (uint32_t)(cb - 4) : kOob;
   const uint32_t x4 = p.act_xor * 0x01010101u;
@@ -636,6 +667,8 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3s2_kernel(DwArgs p, int32_
   auto row = [&](int j) {
     uint32_t flip = (j == 0 ? y0 >= 0 : j < rows_in) ? flip_lane : pad4;
     asm volatile("" : "+v"(flip));
+    if constexpr (RAGGED)
+      return Row{(((d[j] >> pull_bits) ^ flip) & col_mask) | (pad4 & ~col_mask), WIDE ? de[j] ^ flip : 0u};
     return Row{d[j] ^ flip, WIDE ? de[j] ^ flip : 0u};
   };
 
@@ -693,15 +726,17 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3s2_kernel(DwArgs p, int32_
   auto dot4 = [](uint32_t a, int32_t b, int32_t c) {
     return __builtin_amdgcn_sdot4((int)a, b, c, false);
   };
-  const bool merge = (OW & 3) == 0;  // output rows start on dwords: even lanes store four results
+  const bool merge = !RAGGED && (OW & 3) == 0;  // output rows start on dwords: even lanes store four results
   // outputs 2q, 2q+1 of row oy0 + i; out-of-range rows lie beyond the plane (dropped)
   const uint32_t so0 = has_strip ? (uint32_t)(cb / 2 + 2 * q + oy0 * OW) * kEsz : kOob;
+  const bool single = RAGGED && has_strip && cb / 2 + 2 * q + 1 >= OW;  // the row's last output, on its own
   const uint32_t so0_even = (has_strip && (q & 1) == 0) ? so0 : kOob;
 
   // PLAIN: int8 activations with zero point 0 need no flip at all (the mask is zero everywhere)
   auto rows = [&]<bool FOLD, bool PLAIN>() {
     auto rowp = [&](int i) {
-      if constexpr (PLAIN) return Row{d[i], WIDE ? de[i] : 0u};
+      if constexpr (PLAIN && RAGGED) return Row{d[i] >> pull_bits, WIDE ? de[i] : 0u};
+      else if constexpr (PLAIN) return Row{d[i], WIDE ? de[i] : 0u};
       else return row(i);
     };
     int32_t lo = p.rs.lo_rel + (FOLD ? z : 0), hi = p.rs.hi_rel + (FOLD ? z : 0);
@@ -739,14 +774,19 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3s2_kernel(DwArgs p, int32_
             const uint32_t nb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h16, 0x101, 0xf, 0xf, true);  // row_shl:1
             __builtin_amdgcn_raw_buffer_store_b32(h16 | (nb << 16), rout, so0_even + (so0_even != kOob ? step : 0u), 0, 0);
           } else {
-            __builtin_amdgcn_raw_buffer_store_b16((short)h16, rout, so0 + (so0 != kOob ? step : 0u), 0, 0);
+            const uint32_t so = so0 + (so0 != kOob ? step : 0u);
+            __builtin_amdgcn_raw_buffer_store_b16((short)h16, rout, single ? kOob : so, 0, 0);
+            if constexpr (RAGGED) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)r[0], rout, single ? so : kOob, 0, 0);
           }
         } else if constexpr (MODE == 1) {
           typedef int32_t v2i32 __attribute__((ext_vector_type(2)));
-          __builtin_amdgcn_raw_buffer_store_b64(v2i32{acc[0], acc[1]}, rout, so0 + (so0 != kOob ? step : 0u), 0, 0);
+          const uint32_t so = so0 + (so0 != kOob ? step : 0u);
+          __builtin_amdgcn_raw_buffer_store_b64(v2i32{acc[0], acc[1]}, rout, single ? kOob : so, 0, 0);
+          if constexpr (RAGGED) __builtin_amdgcn_raw_buffer_store_b32((uint32_t)acc[0], rout, single ? so : kOob, 0, 0);
         } else {
-          __builtin_amdgcn_raw_buffer_store_b32(((uint32_t)acc[0] & 0xffffu) | ((uint32_t)acc[1] << 16), rout,
-                                                so0 + (so0 != kOob ? step : 0u), 0, 0);
+          const uint32_t so = so0 + (so0 != kOob ? step : 0u);
+          __builtin_amdgcn_raw_buffer_store_b32(((uint32_t)acc[0] & 0xffffu) | ((uint32_t)acc[1] << 16), rout, single ? kOob : so, 0, 0);
+          if constexpr (RAGGED) __builtin_amdgcn_raw_buffer_store_b16((short)acc[0], rout, single ? so : kOob, 0, 0);
         }
       }
     }
@@ -1052,16 +1092,16 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
   const size_t esz = a.has_rq ? 1 : (a.acc16 ? 2 : 4);
   const bool vec_io = (cg.W % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.act) & 3u) == 0) &&
                       ((reinterpret_cast<uintptr_t>(a.out) & (4 * esz - 1)) == 0);
-  // the register kernel: bands of 4 * rpc rows, one wavefront each
-  const int32_t rpc = (cg.H + 3) / 4 < 16 ? (cg.H + 3) / 4 : 16;
-  const int64_t nband_r = (cg.H + 4 * rpc - 1) / (4 * rpc);
+  // the register kernel: bands of 4 * rpc <= 64 rows, as even as they come, one wavefront each
+  const int64_t nband_r = (cg.H + 63) / 64;
+  const int32_t rpc = (int32_t)((cg.H + 4 * nband_r - 1) / (4 * nband_r));
   // (the wavefront-per-plane kernel rounds ties toward +infinity only)
   const bool upward = !(a.has_rq && a.rq.half_away);
   // stride 2: the register kernel for the downsampling layers
   const bool s2_ok = !cg.nhwc && cg.KH == 3 && cg.KW == 3 && cg.stride_h == 2 && cg.stride_w == 2 &&
                      cg.pad_h == 1 && cg.pad_w == 1;
-  const int32_t rpc2 = (cg.OH + 3) / 4 < 16 ? (cg.OH + 3) / 4 : 16;
-  const int64_t nband2 = (cg.OH + 4 * rpc2 - 1) / (4 * rpc2);
+  const int64_t nband2 = (cg.OH + 63) / 64;
+  const int32_t rpc2 = (int32_t)((cg.OH + 4 * nband2 - 1) / (4 * nband2));
   // (the register kernels are compiled for 32- and 16-bit accumulators; 24-bit ones take the
   // kernels that wrap by a run-time width)
   const bool regs_ok = a.acc_wrap_shift == 0 || a.acc_wrap_shift == 16;
@@ -1097,32 +1137,36 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
       return hipGetLastError();
     }
   }
-  const int32_t nsegs = (cg.W + 63) / 64;  // column segments of the register kernels
-  if (regs_ok && s2_ok && cg.W % 4 == 0 && (reinterpret_cast<uintptr_t>(a.act) & 3u) == 0 &&
-      (reinterpret_cast<uintptr_t>(a.out) & 7u) == 0 && (reinterpret_cast<uintptr_t>(a.wgt) & 3u) == 0 &&
-      cg.B <= 65535 && nband2 * nsegs <= 65535 && (int64_t)cg.H * cg.W * 4 < (1ll << 31) &&
-      (int64_t)cg.C * 9 < (1ll << 30)) {
-    auto kern = nsegs > 1 ? (p.out_mode == 1 ? dw_rows3x3s2_kernel<1, false, true>
-                             : p.out_mode == 2 ? dw_rows3x3s2_kernel<2, true, true>
-                             : p.acc16 ? dw_rows3x3s2_kernel<0, true, true> : dw_rows3x3s2_kernel<0, false, true>)
-                          : (p.out_mode == 1 ? dw_rows3x3s2_kernel<1, false, false>
-                             : p.out_mode == 2 ? dw_rows3x3s2_kernel<2, true, false>
-                             : p.acc16 ? dw_rows3x3s2_kernel<0, true, false> : dw_rows3x3s2_kernel<0, false, false>);
+  // Column segments of the register kernels: 64 columns each where rows are whole dwords; else as even as whole strips
+  // allow, and never with a last one of fewer than four columns (its strip is loaded and stored as the row's last four).
+  const bool whole = cg.W % 4 == 0 && (reinterpret_cast<uintptr_t>(a.act) & 3u) == 0;
+  int32_t nsegs = (cg.W + 63) / 64;
+  int32_t segw = whole ? 64 : ((cg.W + nsegs - 1) / nsegs + 3) / 4 * 4;
+  while (cg.W > 64 && segw > 12 && cg.W % segw != 0 && cg.W % segw < 4) segw -= 4;
+  nsegs = segw > 12 || cg.W <= 64 ? (cg.W + segw - 1) / segw : 65536;  // (65536: no such width, one segment too many for the grid)
+#define HAGO_DW_ROWS(KERN, WIDE_, RAG_)                                                                              \
+  (p.out_mode == 1 ? KERN<1, false, WIDE_, RAG_>                                                                     \
+   : p.out_mode == 2 ? KERN<2, true, WIDE_, RAG_> : p.acc16 ? KERN<0, true, WIDE_, RAG_> : KERN<0, false, WIDE_, RAG_>)
+#define HAGO_DW_PICK(KERN, RAG_)                                                                                     \
+  (nsegs > 1 ? (RAG_ ? HAGO_DW_ROWS(KERN, true, true) : HAGO_DW_ROWS(KERN, true, false))                             \
+             : (RAG_ ? HAGO_DW_ROWS(KERN, false, true) : HAGO_DW_ROWS(KERN, false, false)))
+  if (regs_ok && s2_ok && cg.W >= 4 && (reinterpret_cast<uintptr_t>(a.wgt) & 3u) == 0 && cg.B <= 65535 &&
+      nband2 * nsegs <= 65535 && (int64_t)cg.H * cg.W * 4 < (1ll << 31) && (int64_t)cg.C * 9 < (1ll << 30)) {
+    const bool ragged = !whole || (reinterpret_cast<uintptr_t>(a.out) & 7u) != 0;
+    auto kern = HAGO_DW_PICK(dw_rows3x3s2_kernel, ragged);
     hipLaunchKernelGGL(kern, dim3((unsigned)((cg.C + 3) / 4), (unsigned)cg.B, (unsigned)(nband2 * nsegs)),
-                       dim3(kThreads), 0, st, p, rpc2, nsegs);
+                       dim3(kThreads), 0, st, p, rpc2, nsegs, segw);
     return hipGetLastError();
   }
-  if (regs_ok && plane_ok && vec_io && (reinterpret_cast<uintptr_t>(a.wgt) & 3u) == 0 &&
+  if (regs_ok && plane_ok && cg.W >= 4 && (reinterpret_cast<uintptr_t>(a.wgt) & 3u) == 0 &&
       cg.B <= 65535 && nband_r * nsegs <= 65535 && (int64_t)cg.H * cg.W * 4 < (1ll << 31) &&
       (int64_t)cg.C * 9 < (1ll << 30)) {
-    auto kern = nsegs > 1 ? (p.out_mode == 1 ? dw_rows3x3_kernel<1, false, true>
-                             : p.out_mode == 2 ? dw_rows3x3_kernel<2, true, true>
-                             : p.acc16 ? dw_rows3x3_kernel<0, true, true> : dw_rows3x3_kernel<0, false, true>)
-                          : (p.out_mode == 1 ? dw_rows3x3_kernel<1, false, false>
-                             : p.out_mode == 2 ? dw_rows3x3_kernel<2, true, false>
-                             : p.acc16 ? dw_rows3x3_kernel<0, true, false> : dw_rows3x3_kernel<0, false, false>);
+    const bool ragged = !vec_io;
+    auto kern = HAGO_DW_PICK(dw_rows3x3_kernel, ragged);
     hipLaunchKernelGGL(kern, dim3((unsigned)((cg.C + 3) / 4), (unsigned)cg.B, (unsigned)(nband_r * nsegs)),
-                       dim3(kThreads), 0, st, p, rpc, nsegs);
+                       dim3(kThreads), 0, st, p, rpc, nsegs, segw);
+#undef HAGO_DW_PICK
+#undef HAGO_DW_ROWS
   } else if (upward && plane_ok && cg.W <= 64 && wave_lds <= (size_t)kMaxLdsBytes && planes < (1ll << 32)) {
     const uint32_t w4 = vec_io ? (uint32_t)cg.W / 4 : 1u;
     const uint32_t inv_w4 = w4 > 1 ? (uint32_t)(((1ull << 32) + w4 - 1) / w4) : 0u;  // unused for w4 == 1
