@@ -4,18 +4,15 @@
 // In NCHW the reduction index c is the slow one, while the MFMA wants, per lane, 16
 // consecutive k-bytes of one row.  The general convolution path therefore rewrites the input
 // into a channel-last copy first, which for this operator (few output channels, so hardly any
-// reuse of the input) costs more memory traffic than the convolution itself.  Here a
-// wavefront owns 32 consecutive pixels of one image.  A lane loads dwords (four consecutive
-// pixels of one channel); the four lanes of a quad load four consecutive channels of the same
-// four pixels and transpose that 4x4 byte block among themselves (two DPP quad permutes and two
-// byte permutes), after which each lane holds four consecutive channels of ITS pixel: one dword
-// of its MFMA operand.  Each input byte is fetched once, 256 bytes per load instruction.
-// The MFMA runs with the pixels as its P operand: a lane then owns one output channel and, per
-// group of four accumulator registers, four consecutive pixels, which are packed and stored
-// together.  The work is bound by memory, not by the matrix pipe (an output channel tile does
-// 1/32 of an MFMA per pixel and k-step).
+// reuse of the input) costs more memory traffic than the convolution itself.  Here lanes load dwords (four consecutive
+// pixels of one channel) and transpose 4x4 byte blocks in registers.  The MFMA runs with the pixels as its P operand: a
+// lane then owns one output channel and, per group of accumulator registers, consecutive pixels, which are packed and
+// stored together.  Every block of 32 output channels reads the input again, from the cache; against the forms that read
+// it once (conv_direct.hip, or a channel-last copy in the workspace and qgemm_dma.hip) that is the faster one up to the
+// largest layers (us here, there without and with a workspace: 64 -> 384 on 8 x 56 x 56 7.9, 12.7; 512 -> 128 on
+// 4 x 28 x 28 5.3, 10.6; 256 -> 256 on 32 x 28 x 28 9.8, 11.8, 15.4; 512 -> 512 29.9, 28.2, 28.1; 1024 -> 1024 on
+// 32 x 14 x 14 26, 38, 27.5), so it serves every layer of its kind.
 //
-// All loads of a few k-steps (32 channels each) are issued before the first is used.
 // Out-of-range channels and pixels are fetched through buffer descriptors with out-of-range
 // offsets (they read as 0; the weights of padded channels are 0 as well).
 #include "hago_device.h"
@@ -40,341 +37,330 @@ struct PwArgs {
   int32_t B, C, HW, N;
   int32_t tiles_per_img;
   int64_t tiles;
+  int32_t per_wave;            // blocks of 32 output channels of a wavefront
+  int32_t nblocks;             // such groups of blocks
+  uint32_t inv_tpi, inv_nb;    // ceil(2^32 / tiles_per_img) and of nblocks where that divides exactly, else 0
   uint32_t act_xor4;   // 0x80808080 for uint8 activations
   int32_t corr_coef;   // off - z_a
   int32_t per_channel;
   RequantScalars rs;
 };
 
-// MODE 0: requantized 8-bit, 1: raw int32, 2: raw int16; ACC16: accumulator wraps to 16 bits;
-// NT: 32-channel tiles per wavefront (N <= 32 * NT).
-template <int MODE, bool ACC16, int NT>
-__global__ __launch_bounds__(256) void pw_nchw_kernel(PwArgs p) {
+// MODE 0: requantized 8-bit, 1: raw int32, 2: raw int16; ACC16: accumulator wraps to 16 bits.
+// A wavefront owns 128 consecutive pixels of one image and a block (or several) of 32 output channels, as four MFMA row
+// tiles.  Lane (i, h) loads, for each of its 16 channels (k-half h), the dword of pixels 4i .. 4i+3:
+// consecutive lanes read consecutive dwords, so a load instruction covers 128 contiguous bytes
+// of a channel (two channels per instruction).  Four 4x4 byte transposes inside the lane (eight byte permutes each, no
+// lane exchange) turn the 16 dwords into the 16 k-bytes of each of the lane's four pixels, and pixel 4i + j becomes row i
+// of row tile j: four MFMAs share one weight operand.  On the way out lane (n, h) then holds, for its output channel,
+// registers (g, e) of tile j = pixel 4 * (8g + 4h + e) + j: the four tiles pack into one dword and the four e into 16
+// contiguous bytes.  (Passing the results through LDS, so that eight lanes write the 128 bytes of a channel, was slower:
+// 24 -> 144 channels on 32 x 56 x 56 11.2 us, 8.9 as they are.)
+// Rows start at any byte (the loads and stores are unaligned ones).  The last tile of an image is moved back to end with
+// it, so that tiles are whole and pixels covered twice get the same value; of an image of less than 128 pixels the last
+// four are.
+//   CH = 1, 2, 3 (C <= 96): all input channels of a tile are transposed once and stay in registers for several blocks of
+//     output channels (88 -> 528 on 8 x 56 x 56: 11.2 us with a wavefront for every block, 9.4 so).
+//   CH = 5: five steps of 32 channels are in flight at a time.
+//   KS = 4: four wavefronts share a tile and block, a quarter of the steps each, and add up through LDS (576 -> 96
+//     channels of one 14 x 14 image are six tiles, 18 steps in a row each, else: 8.6 us, 5.8 so).
+typedef uint32_t u32_u __attribute__((aligned(1)));
+typedef v4i v4i_u __attribute__((aligned(1)));
+typedef int v2i_u __attribute__((ext_vector_type(2), aligned(1)));
+
+template <int MODE, bool ACC16, int KS, int CH>
+__global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
+  constexpr int kPart = 65;  // dwords of a lane's partial sums: 64 accumulators and the row sum (odd: no bank conflicts)
+  __shared__ int32_t lds[KS == 1 ? 1 : KS * 64 * kPart];
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t tile = (int64_t)blockIdx.x * 4 + wave;
-  if (tile >= p.tiles) return;  // wavefront-uniform; the kernel has no barrier
-  const int b = (int)(tile / p.tiles_per_img);
-  const int pix0 = (int)(tile - (int64_t)b * p.tiles_per_img) * 32;
-  const int i = lane & 31, h = lane >> 5;
+  const int wave = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Workgroups go to the eight XCDs round-robin.  A channel plane is not a multiple of the
+  // 128-byte line in general, so neighbouring tiles share lines, and the blocks of output channels of a tile share its
+  // input; numbering them so that an XCD gets a run of consecutive ones lets that XCD's L2 serve the shared lines (with
+  // the plain order every such line was fetched from memory by two XCDs: 1.5 times the bytes).
+  uint32_t id;
+  {
+    const uint32_t nt = gridDim.x, x = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const uint32_t qn = nt >> 3, rn = nt & 7;
+    id = x * qn + (x < rn ? x : rn) + slot;
+  }
+  const uint32_t tile = p.inv_nb ? __umulhi(id, p.inv_nb) : id / (uint32_t)p.nblocks;
+  const int blk0 = (int)(id - tile * (uint32_t)p.nblocks) * p.per_wave;
+  const int b = (int)(p.inv_tpi ? __umulhi(tile, p.inv_tpi) : tile / (uint32_t)p.tiles_per_img);
   const int C = p.C, HW = p.HW, N = p.N;
+  int pix0 = ((int)tile - b * p.tiles_per_img) * 128;
+  if (HW >= 128 && pix0 > HW - 128) pix0 = HW - 128;
+  const int i = lane & 31, h = lane >> 5;
 
   const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(p.act) + (int64_t)b * C * HW, 0, C * HW, 0x00020000);
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<int8_t*>(p.wgt), 0, N * C, 0x00020000);
-  // the quad's four pixels (H * W % 4 == 0: all inside the image or all outside); + channel * HW
-  const int q = lane & 3;
-  const uint32_t a_lane = (pix0 + (i & ~3) < HW) ? (uint32_t)(pix0 + (i & ~3)) : kOob;
-  // byte selectors of the two transpose steps (own dword in S1: bytes 0-3, partner's in S0: 4-7)
-  const uint32_t sel1 = (q & 2) ? 0x03020706u : 0x05040100u;  // halves swapped with lane q ^ 2
-  const uint32_t sel2 = (q & 1) ? 0x03070105u : 0x06020400u;  // bytes swapped with lane q ^ 1
-  uint32_t w_lane[NT];                                                    // + k
-#pragma unroll
-  for (int t = 0; t < NT; ++t) w_lane[t] = (t * 32 + i < N) ? (uint32_t)((t * 32 + i) * C) : kOob;
+  // the lane's four pixels, and its 16 channels of a step
+  int px = pix0 + 4 * i;
+  const bool px_ok = px < HW;
+  if (px > HW - 4) px = HW - 4;
+  const uint32_t a_lane = px_ok ? (uint32_t)(px + 16 * h * HW) : kOob;
 
-  // the lane's output channels: requantize parameters (used at the very end)
-  int32_t bias_r[NT], mult_r[NT], shift_r[NT];
+  const int ksteps = (C + 31) >> 5, whole = C >> 5;
+  const uint32_t k_left = (uint32_t)(C - 32 * whole);  // channels of the last, partial step
+  // channels 4m .. 4m+3 of the lane's 16 exist or not as a whole (C % 4 == 0): the ones that do not must be exactly
+  // zero on both sides (the flip would make them -128, and the 16-byte weight load runs into the next row)
+  auto live = [&](int s, int m) { return s < whole || 16u * h + 4u * m < k_left ? 0xffffffffu : 0u; };
+  auto load_a = [&](int s, uint32_t (&ab)[16]) {
+    const uint32_t so = (uint32_t)(32 * s) * (uint32_t)HW;
+    if (s < whole) {  // uniform
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int n = t * 32 + i;
-    bias_r[t] = 0; mult_r[t] = 0; shift_r[t] = 0;
+      for (int d = 0; d < 16; ++d) ab[d] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rin, a_lane, so + (uint32_t)(d * HW), 0);
+    } else {  // channels beyond C are not fetched
+#pragma unroll
+      for (int d = 0; d < 16; ++d)
+        ab[d] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
+            rin, a_lane != kOob && 16u * h + d < k_left ? a_lane + so + (uint32_t)(d * HW) : kOob, 0, 0);
+    }
+  };
+  auto load_w = [&](int s, int n) {
+    return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
+        rw, n < N && 32 * s + 16 * h < C ? (uint32_t)(n * C + 16 * h) + (uint32_t)(32 * s) : kOob, 0, 0));
+  };
+  auto operand = [&](int s, const uint32_t (&ab)[16], v4i (&af)[4]) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      // rows a..d = channels 4m .. 4m+3, bytes = pixels 0..3  ->  rows = pixels, bytes = channels
+      const uint32_t a = ab[4 * m], bq = ab[4 * m + 1], c = ab[4 * m + 2], d = ab[4 * m + 3];
+      const uint32_t t0 = __builtin_amdgcn_perm(bq, a, 0x05010400u);  // a0 b0 a1 b1
+      const uint32_t t1 = __builtin_amdgcn_perm(bq, a, 0x07030602u);  // a2 b2 a3 b3
+      const uint32_t t2 = __builtin_amdgcn_perm(d, c, 0x05010400u);   // c0 d0 c1 d1
+      const uint32_t t3 = __builtin_amdgcn_perm(d, c, 0x07030602u);   // c2 d2 c3 d3
+      const uint32_t x4 = p.act_xor4 & live(s, m);  // (bytes that were not fetched are 0 and stay it)
+      af[0][m] = (int)(__builtin_amdgcn_perm(t2, t0, 0x05040100u) ^ x4);
+      af[1][m] = (int)(__builtin_amdgcn_perm(t2, t0, 0x07060302u) ^ x4);
+      af[2][m] = (int)(__builtin_amdgcn_perm(t3, t1, 0x05040100u) ^ x4);
+      af[3][m] = (int)(__builtin_amdgcn_perm(t3, t1, 0x07060302u) ^ x4);
+    }
+  };
+  v16i acc[4];
+  int32_t wsum;
+  auto clear = [&]() {
+    wsum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[j][r] = 0;
+  };
+  auto multiply = [&](int s, v4i wb, const v4i (&af)[4]) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      wb[m] &= (int)live(s, m);
+      wsum = __builtin_amdgcn_sdot4(wb[m], 0x01010101, wsum, false);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[j], wb, acc[j], 0, 0, 0);
+  };
+  struct Rq { int32_t bias, m, sh; };  // of the lane's output channel
+  auto load_rq = [&](int n) {
+    Rq r{0, 0, 0};
     if (n < N) {
-      if (p.bias) bias_r[t] = p.bias[n];
+      if (p.bias) r.bias = p.bias[n];
       if (MODE == 0) {
-        mult_r[t] = rq_mult(p.mult, p.per_channel ? n : 0);
-        shift_r[t] = rq_shift(p.mult, p.shift, p.per_channel ? n : 0);
+        r.m = rq_mult(p.mult, p.per_channel ? n : 0);
+        r.sh = rq_shift(p.mult, p.shift, p.per_channel ? n : 0);
       }
     }
-  }
+    return r;
+  };
 
-  v16i acc[NT];
-  int32_t wsum[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    wsum[t] = 0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[t][r] = 0;
-  }
-  // k-steps whose loads are in flight together (fewer with more accumulators, for registers)
-  constexpr int kChunk = NT == 4 ? 4 : 6;
-  const int ksteps = (C + 31) >> 5;
-  for (int s0 = 0; s0 < ksteps; s0 += kChunk) {
-    uint32_t ab[kChunk][4];
-    v4i wb[kChunk][NT];
-#pragma unroll
-    for (int u = 0; u < kChunk; ++u) {
-      if (s0 + u < ksteps) {  // uniform
-        const int k = (s0 + u) * 32 + 16 * h;  // first channel of this lane's 16 (C % 16 == 0)
-        const bool kok = k < C;
-#pragma unroll
-        for (int d = 0; d < 4; ++d)  // channel k + 4d + q, four pixels
-          ab[u][d] = __builtin_amdgcn_raw_buffer_load_b32(
-              rin, (kok && a_lane != kOob) ? a_lane + (uint32_t)((k + 4 * d + q) * HW) : kOob, 0, 0);
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-          wb[u][t] = __builtin_amdgcn_raw_buffer_load_b128(
-              rw, (kok && w_lane[t] != kOob) ? w_lane[t] + (uint32_t)k : kOob, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kChunk; ++u) {
-      if (s0 + u < ksteps) {  // uniform
-        v4i af;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          const uint32_t x = ab[u][d];  // pixels 0..3 of channel q  ->  channels 0..3 of pixel q
-          const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, true);  // quad_perm [2,3,0,1]
-          const uint32_t a2 = __builtin_amdgcn_perm(t, x, sel1);
-          const uint32_t v = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a2, 0xB1, 0xf, 0xf, true);  // quad_perm [1,0,3,2]
-          af[d] = (int)(__builtin_amdgcn_perm(v, a2, sel2) ^ p.act_xor4);
-        }
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-#pragma unroll
-          for (int d = 0; d < 4; ++d)
-            wsum[t] = __builtin_amdgcn_sdot4(wb[u][t][d], 0x01010101, wsum[t], false);
-          acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af, wb[u][t], acc[t], 0, 0, 0);
-        }
-      }
-    }
-  }
-
-  // Lane l owns channel t * 32 + l % 32; registers 4g .. 4g+3 are pixels 8g + 4 * (l / 32) + 0..3.
   const RequantScalars rs = p.rs;
   constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
+  // results of output channel n from the accumulators (KS = 4: of register group `wave` only, in the first four registers)
+  auto finish = [&](int n, Rq rq) {
+    const int32_t corr = rq.bias + p.corr_coef * wsum;
+    const int64_t rnd = (int64_t)1 << (30 + rq.sh);
+    uint8_t* const orow = static_cast<uint8_t*>(p.out) + ((int64_t)b * N + n) * HW * kEsz;
+    // FOLD (requantized, 32-bit accumulator, every lane's constants small enough): the correction
+    // term, the rounding term and the output zero point go into one 64-bit constant per lane, so
+    // an output is clamp((acc * m + k64) >> (31 + sh)) against the absolute bounds:
+    // ((acc + corr) * m + rnd) >> s + z == (acc * m + corr * m + rnd + z * 2^s) >> s exactly, and
+    // acc + corr cannot wrap when |corr| <= 2^30 and |acc| <= 2^30 (|acc| <= C * 2^15 < 2^30 for
+    // C < 2^15).  With sh <= 19 and an 8-bit z nothing leaves 63 bits.
+    const int32_t away = rs.half_away ? -1 : 0;  // mask of the sign-bit correction
+    auto store_all = [&]<bool FOLD>() {
+      const int32_t lo = rs.lo_rel + (FOLD ? rs.z_out : 0), hi = rs.hi_rel + (FOLD ? rs.z_out : 0);
+      const int64_t k64 = FOLD ? (int64_t)corr * rq.m + rnd + ((int64_t)rs.z_out << (31 + rq.sh)) : rnd;
+      const int32_t add = FOLD ? 0 : corr;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int n = t * 32 + i;
-    const int32_t ws = wsum[t] + __shfl_xor(wsum[t], 32);  // the two k-halves of the row sums
-    const int32_t corr = bias_r[t] + p.corr_coef * ws;
-    const int64_t rnd = (int64_t)1 << (30 + shift_r[t]);
-    uint8_t* orow = static_cast<uint8_t*>(p.out) + ((int64_t)b * N + n) * HW * kEsz;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int pg = pix0 + 8 * g + 4 * h;  // HW % 4 == 0: the group is inside the image or outside
-      if (n < N && pg < HW) {
-        int32_t v[4];
+      for (int gi = 0; gi < 4 / KS; ++gi) {
+        const int g = KS == 1 ? gi : wave;
+        uint32_t dw[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          v[e] = acc[t][4 * g + e] + corr;
-          if (ACC16) v[e] = (int32_t)(int16_t)v[e];
-        }
-        if constexpr (MODE == 0) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int64_t pr = (int64_t)v[e] * (int64_t)mult_r[t] + rnd;
-            v[e] = med3((int32_t)(pr >> (31 + shift_r[t])), rs.lo_rel, rs.hi_rel) + rs.z_out;
-          }
-          *reinterpret_cast<uint32_t*>(orow + pg) = pack4_perm(v[0], v[1], v[2], v[3]);
-        } else if constexpr (MODE == 1) {
-          *reinterpret_cast<int4*>(orow + (int64_t)pg * 4) = make_int4(v[0], v[1], v[2], v[3]);
-        } else {
-          *reinterpret_cast<short4*>(orow + (int64_t)pg * 2) =
-              make_short4((short)v[0], (short)v[1], (short)v[2], (short)v[3]);
-        }
-      }
-    }
-  }
-}
-
-// N <= 32: a wavefront owns 128 consecutive pixels of one image, as four MFMA row tiles.
-// Lane (i, h) loads, for each of its 16 channels (k-half h), the dword of pixels 4i .. 4i+3:
-// consecutive lanes read consecutive dwords, so a load instruction covers 128 contiguous bytes
-// of a channel (two channels per instruction) and every byte is fetched once.  Four 4x4 byte
-// transposes inside the lane (eight byte permutes each, no lane exchange) turn the 16 dwords
-// into the 16 k-bytes of each of the lane's four pixels, and pixel 4i + j becomes row i of row
-// tile j: four MFMAs share one weight operand.  On the way out lane (n, h) then holds, for its
-// output channel, registers (g, e) of tile j = pixel 4 * (8g + 4h + e) + j: the four tiles pack
-// into one dword and the four e into 16 contiguous bytes, so a store instruction writes 32
-// contiguous bytes of each channel.
-template <int MODE, bool ACC16>
-__global__ __launch_bounds__(64) void pw_nchw_quad_kernel(PwArgs p) {
-  const int lane = threadIdx.x;
-  // Workgroups go to the eight XCDs round-robin.  A channel plane is not a multiple of the
-  // 128-byte line in general, so neighbouring tiles share lines; numbering the tiles so that
-  // an XCD gets a run of consecutive ones lets that XCD's L2 serve the shared lines (with the
-  // plain order every such line was fetched from memory by two XCDs: 1.5 times the bytes).
-  int64_t tile = blockIdx.x;
-  if (gridDim.y == 1) {
-    const int64_t nt = gridDim.x, x = tile & 7, slot = tile >> 3;
-    const int64_t qn = nt >> 3, rn = nt & 7;
-    tile = x * qn + (x < rn ? x : rn) + slot;
-  }
-  const int b = (int)(tile / p.tiles_per_img);
-  const int pix0 = (int)(tile - (int64_t)b * p.tiles_per_img) * 128;
-  const int i = lane & 31, h = lane >> 5;
-  const int C = p.C, HW = p.HW, N = p.N;
-  // grid y: block of 32 output channels (few input channels, many output channels: the input is
-  // re-read per block, from the cache)
-  const int n = (int)blockIdx.y * 32 + i;  // the lane's output channel
-
-  const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(p.act) + (int64_t)b * C * HW, 0, C * HW, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<int8_t*>(p.wgt), 0, N * C, 0x00020000);
-  // the lane's four pixels (H * W % 4 == 0: all inside the image or all outside); + channel * HW
-  const uint32_t a_lane = (pix0 + 4 * i < HW) ? (uint32_t)(pix0 + 4 * i) : kOob;
-  const uint32_t w_lane = (n < N) ? (uint32_t)(n * C) : kOob;  // + k
-
-  // the lane's output channel: requantize parameters (used at the very end)
-  int32_t bias_r = 0, mult_r = 0, shift_r = 0;
-  if (n < N) {
-    if (p.bias) bias_r = p.bias[n];
-    if (MODE == 0) {
-      mult_r = rq_mult(p.mult, p.per_channel ? n : 0);
-      shift_r = rq_shift(p.mult, p.shift, p.per_channel ? n : 0);
-    }
-  }
-
-  v16i acc[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0;
-  int32_t wsum = 0;
-  constexpr int kChunk = 5;  // k-steps (32 channels each) whose loads are in flight together
-  const int ksteps = (C + 31) >> 5;
-  // FULL: all kChunk steps exist, so the code has no branches and the compiler waits for each
-  // step's loads separately (the first MFMAs run while later steps are still arriving)
-  auto chunk = [&]<bool FULL>(int s0) {
-    uint32_t ab[kChunk][16];
-    v4i wb[kChunk];
-#pragma unroll
-    for (int u = 0; u < kChunk; ++u) {
-      if (FULL || s0 + u < ksteps) {  // uniform
-        const int k = (s0 + u) * 32 + 16 * h;  // first channel of this lane's 16 (C % 4 == 0)
-        const bool kok = k < C;
-        const uint32_t a0 = (kok && a_lane != kOob) ? a_lane + (uint32_t)(k * HW) : kOob;
-#pragma unroll
-        for (int d = 0; d < 16; ++d)  // channel k + d, four pixels; channels beyond C are not fetched
-          ab[u][d] = __builtin_amdgcn_raw_buffer_load_b32(
-              rin, (a0 != kOob && k + d < C) ? a0 + (uint32_t)(d * HW) : kOob, 0, 0);
-        wb[u] = __builtin_amdgcn_raw_buffer_load_b128(
-            rw, (kok && w_lane != kOob) ? w_lane + (uint32_t)k : kOob, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kChunk; ++u) {
-      if (FULL || s0 + u < ksteps) {  // uniform
-        v4i af[4];
-        const int kc = (s0 + u) * 32 + 16 * h;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          // channels 4m .. 4m+3 of this group exist or not as a whole (C % 4 == 0): the ones that
-          // do not must be exactly zero on both sides (the flip would make them -128, and the
-          // 16-byte weight load runs into the next row)
-          const uint32_t live = kc + 4 * m < C ? 0xffffffffu : 0u;
-          wb[u][m] &= (int)live;
-          // rows a..d = channels 4m .. 4m+3, bytes = pixels 0..3  ->  rows = pixels, bytes = channels
-          const uint32_t a = ab[u][4 * m], bq = ab[u][4 * m + 1], c = ab[u][4 * m + 2], d = ab[u][4 * m + 3];
-          const uint32_t t0 = __builtin_amdgcn_perm(bq, a, 0x05010400u);  // a0 b0 a1 b1
-          const uint32_t t1 = __builtin_amdgcn_perm(bq, a, 0x07030602u);  // a2 b2 a3 b3
-          const uint32_t t2 = __builtin_amdgcn_perm(d, c, 0x05010400u);   // c0 d0 c1 d1
-          const uint32_t t3 = __builtin_amdgcn_perm(d, c, 0x07030602u);   // c2 d2 c3 d3
-          af[0][m] = (int)((__builtin_amdgcn_perm(t2, t0, 0x05040100u) ^ p.act_xor4) & live);
-          af[1][m] = (int)((__builtin_amdgcn_perm(t2, t0, 0x07060302u) ^ p.act_xor4) & live);
-          af[2][m] = (int)((__builtin_amdgcn_perm(t3, t1, 0x05040100u) ^ p.act_xor4) & live);
-          af[3][m] = (int)((__builtin_amdgcn_perm(t3, t1, 0x07060302u) ^ p.act_xor4) & live);
-        }
-#pragma unroll
-        for (int d = 0; d < 4; ++d) wsum = __builtin_amdgcn_sdot4(wb[u][d], 0x01010101, wsum, false);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[j], wb[u], acc[j], 0, 0, 0);
-      }
-    }
-  };
-  for (int s0 = 0; s0 < ksteps; s0 += kChunk) {
-    if (s0 + kChunk <= ksteps)
-      chunk.template operator()<true>(s0);
-    else
-      chunk.template operator()<false>(s0);
-  }
-
-  const RequantScalars rs = p.rs;
-  constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
-  const int32_t ws = wsum + __shfl_xor(wsum, 32);  // the two k-halves of the row sums
-  const int32_t corr = bias_r + p.corr_coef * ws;
-  const int64_t rnd = (int64_t)1 << (30 + shift_r);
-  uint8_t* orow = static_cast<uint8_t*>(p.out) + ((int64_t)b * N + n) * HW * kEsz;
-  const bool vec16 = (HW & 15) == 0 && (reinterpret_cast<uintptr_t>(p.out) & 15u) == 0;
-  // FOLD (requantized, 32-bit accumulator, every lane's constants small enough): the correction
-  // term, the rounding term and the output zero point go into one 64-bit constant per lane, so
-  // an output is clamp((acc * m + k64) >> (31 + sh)) against the absolute bounds:
-  // ((acc + corr) * m + rnd) >> s + z == (acc * m + corr * m + rnd + z * 2^s) >> s exactly, and
-  // acc + corr cannot wrap when |corr| <= 2^30 and |acc| <= 2^30 (|acc| <= C * 2^15 < 2^30 for
-  // C < 2^15).  With sh <= 19 and an 8-bit z nothing leaves 63 bits.
-  const int32_t away = rs.half_away ? -1 : 0;  // mask of the sign-bit correction
-  auto store_all = [&]<bool FOLD>() {
-    const int32_t lo = rs.lo_rel + (FOLD ? rs.z_out : 0), hi = rs.hi_rel + (FOLD ? rs.z_out : 0);
-    const int64_t k64 = FOLD ? (int64_t)corr * mult_r + rnd + ((int64_t)rs.z_out << (31 + shift_r)) : rnd;
-    const int32_t add = FOLD ? 0 : corr;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      uint32_t dw[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int pq = pix0 + 4 * (8 * g + 4 * h + e);  // first of the four pixels; HW % 4 == 0
-        int32_t v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          v[j] = acc[j][4 * g + e] + add;
-          if (ACC16) v[j] = (int32_t)(int16_t)v[j];
-        }
-        if constexpr (MODE == 0) {
+          int32_t v[4];
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            // (general form only: halves away from zero add the accumulator's sign bit)
-            const int64_t pr = (int64_t)v[j] * (int64_t)mult_r + k64 + (FOLD ? 0 : (int64_t)((v[j] >> 31) & away));
-            v[j] = med3((int32_t)(pr >> (31 + shift_r)), lo, hi) + (FOLD ? 0 : rs.z_out);
+            v[j] = acc[j][4 * gi + e] + add;
+            if (ACC16) v[j] = (int32_t)(int16_t)v[j];
           }
-          dw[e] = pack4_perm(v[0], v[1], v[2], v[3]);
-          if (!vec16 && n < N && pq < HW) *reinterpret_cast<uint32_t*>(orow + pq) = dw[e];
-        } else if constexpr (MODE == 1) {
-          if (n < N && pq < HW) *reinterpret_cast<int4*>(orow + (int64_t)pq * 4) = make_int4(v[0], v[1], v[2], v[3]);
-        } else {
-          if (n < N && pq < HW)
-            *reinterpret_cast<short4*>(orow + (int64_t)pq * 2) =
-                make_short4((short)v[0], (short)v[1], (short)v[2], (short)v[3]);
+          if constexpr (MODE == 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              // (general form only: halves away from zero add the accumulator's sign bit)
+              const int64_t pr = (int64_t)v[j] * (int64_t)rq.m + k64 + (FOLD ? 0 : (int64_t)((v[j] >> 31) & away));
+              v[j] = med3((int32_t)(pr >> (31 + rq.sh)), lo, hi) + (FOLD ? 0 : rs.z_out);
+            }
+            dw[e] = pack4_perm(v[0], v[1], v[2], v[3]);
+          } else {
+            int pq = pix0 + 4 * (8 * g + 4 * h + e);  // first of the four pixels
+            const bool ok = n < N && pq < HW;
+            if (pq > HW - 4) pq = HW - 4;
+            if constexpr (MODE == 1) {
+              if (ok) *reinterpret_cast<v4i_u*>(orow + (int64_t)pq * kEsz) = v4i{v[0], v[1], v[2], v[3]};
+            } else {
+              if (ok) *reinterpret_cast<v2i_u*>(orow + (int64_t)pq * kEsz) =
+                  v2i_u{(v[0] & 0xffff) | (int)((uint32_t)v[1] << 16), (v[2] & 0xffff) | (int)((uint32_t)v[3] << 16)};
+            }
+          }
+        }
+        if constexpr (MODE == 0) {
+          const int pg = pix0 + 32 * g + 16 * h;
+          if (n < N && pg + 16 <= HW) {
+            *reinterpret_cast<v4i_u*>(orow + pg) = v4i{(int)dw[0], (int)dw[1], (int)dw[2], (int)dw[3]};
+          } else if (n < N) {  // (an image of less than 128 pixels)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (pg + 4 * e < HW) *reinterpret_cast<u32_u*>(orow + (pg + 4 * e > HW - 4 ? HW - 4 : pg + 4 * e)) = dw[e];
+          }
         }
       }
-      if constexpr (MODE == 0) {
-        const int pg = pix0 + 32 * g + 16 * h;  // HW % 16 == 0: the 16 pixels are inside the image or outside
-        if (vec16 && n < N && pg < HW)
-          *reinterpret_cast<uint4*>(orow + pg) = make_uint4(dw[0], dw[1], dw[2], dw[3]);
+    };
+    const bool lane_ok = rq.sh >= 0 && rq.sh <= 19 && corr >= -(1 << 30) && corr <= (1 << 30);
+    const bool fold = MODE == 0 && !ACC16 && C < (1 << 15) && rs.z_out >= -256 && rs.z_out <= 255 &&
+                      !rs.half_away && __builtin_amdgcn_ballot_w64(!lane_ok) == 0;  // wavefront-uniform
+    if (fold)
+      store_all.template operator()<true>();
+    else
+      store_all.template operator()<false>();
+  };
+
+  if constexpr (KS == 1 && CH <= 3) {
+    uint32_t ab[CH][16];
+#pragma unroll
+    for (int s = 0; s < CH; ++s) load_a(s, ab[s]);
+    v4i wb[CH], wn[CH];
+    auto load_block = [&](int blk, v4i (&w)[CH]) {
+#pragma unroll
+      for (int s = 0; s < CH; ++s) w[s] = load_w(s, blk * 32 + i);
+      return load_rq(blk * 32 + i);
+    };
+    Rq rq = load_block(blk0, wb);
+    v4i af[CH][4];
+#pragma unroll
+    for (int s = 0; s < CH; ++s) operand(s, ab[s], af[s]);
+    const int blocks = (N + 31) >> 5, last = blk0 + p.per_wave < blocks ? blk0 + p.per_wave : blocks;
+    for (int blk = blk0; blk < last; ++blk) {
+      clear();
+#pragma unroll
+      for (int s = 0; s < CH; ++s) multiply(s, wb[s], af[s]);
+      Rq rn{0, 0, 0};
+      if (blk + 1 < last) rn = load_block(blk + 1, wn);  // under way during this block's results
+      wsum += __shfl_xor(wsum, 32);                      // the two k-halves of the row sums
+      finish(blk * 32 + i, rq);
+      rq = rn;
+#pragma unroll
+      for (int s = 0; s < CH; ++s) wb[s] = wn[s];
+    }
+  } else {
+    const int n = blk0 * 32 + i;
+    clear();
+    // FULL: all CH steps exist and are whole, so the code has no branches and the compiler waits for each
+    // step's loads separately (the first MFMAs run while later steps are still arriving)
+    auto chunk = [&]<bool FULL>(int s0) {
+      uint32_t ab[CH][16];
+      v4i wb[CH];
+      if constexpr (FULL) __builtin_assume(s0 + (CH - 1) * KS < whole);
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const int s = s0 + u * KS;
+        if (FULL || s < ksteps) {  // uniform
+          if constexpr (FULL) {
+            const uint32_t so = (uint32_t)(32 * s) * (uint32_t)HW;
+#pragma unroll
+            for (int d = 0; d < 16; ++d) ab[u][d] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rin, a_lane, so + (uint32_t)(d * HW), 0);
+          } else {
+            load_a(s, ab[u]);
+          }
+          wb[u] = load_w(s, n);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const int s = FULL ? 0 : s0 + u * KS;  // (step 0 is a whole one wherever FULL is)
+        if (FULL || s < ksteps) {  // uniform
+          v4i af[4];
+          operand(s, ab[u], af);
+          multiply(s, wb[u], af);
+        }
+      }
+    };
+    const Rq rq = load_rq(n);
+    for (int s0 = wave; s0 < ksteps; s0 += CH * KS) {
+      if (s0 + (CH - 1) * KS < whole)
+        chunk.template operator()<true>(s0);
+      else
+        chunk.template operator()<false>(s0);
+    }
+    wsum += __shfl_xor(wsum, 32);  // the two k-halves of the row sums
+    if constexpr (KS > 1) {
+      // each wavefront takes one group g of registers of all four tiles
+      int32_t* part = lds + (wave * 64 + lane) * kPart;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[(r >> 2) * 16 + j * 4 + (r & 3)] = acc[j][r];
+      part[64] = wsum;
+      __syncthreads();
+      const int32_t* mine = lds + lane * kPart;
+      wsum = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[j][e] = 0;
+#pragma unroll
+      for (int w = 0; w < KS; ++w) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[j][e] += mine[w * 64 * kPart + wave * 16 + j * 4 + e];
+        wsum += mine[w * 64 * kPart + 64];
       }
     }
-  };
-  const bool lane_ok = shift_r >= 0 && shift_r <= 19 && corr >= -(1 << 30) && corr <= (1 << 30);
-  const bool fold = MODE == 0 && !ACC16 && C < (1 << 15) && rs.z_out >= -256 && rs.z_out <= 255 &&
-                    !rs.half_away && __builtin_amdgcn_ballot_w64(!lane_ok) == 0;  // wavefront-uniform
-  if (fold)
-    store_all.template operator()<true>();
-  else
-    store_all.template operator()<false>();
-}
-
-// Whether the 128-pixel form serves C -> N channels: it re-reads the input per 32 output channels, from the cache, and
-// has four times the pixels in flight per load (us of this form, of the 32-pixel one or the general kernel: 88 -> 528 at
-// 56 x 56 13, 85; 128 -> 128 at 28 x 28 6.5, 8.5; 96 -> 40 5.2, 4.5; 528 -> 88 11.4, 10.7).
-inline bool quad_form(int64_t C, int64_t N) {
-  return N <= 32 || ((C <= 64 || (N > 64 && C <= 128) || (N > 128 && C <= 256)) && (N + 31) / 32 <= 65535);
+    finish(n, rq);
+  }
 }
 
 template <int MODE, bool ACC16>
-hipError_t launch_nt(const PwArgs& p, hipStream_t st) {
-  // 128 pixels per wavefront, one wavefront per workgroup, 32 output channels per workgroup row
-  if (quad_form(p.C, p.N)) {
-    PwArgs q = p;
-    q.tiles_per_img = (p.HW + 127) / 128;
-    q.tiles = (int64_t)p.B * q.tiles_per_img;  // < 2^31: B and H*W are 32-bit and B * H*W fits the tensor
-    hipLaunchKernelGGL((pw_nchw_quad_kernel<MODE, ACC16>), dim3((unsigned)q.tiles, (unsigned)((p.N + 31) / 32)),
-                       dim3(64), 0, st, q);
-    return hipGetLastError();
-  }
-  const unsigned grid = (unsigned)((p.tiles + 3) / 4);
-  if (p.N <= 64) hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 2>), dim3(grid), dim3(256), 0, st, p);
-  else hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 4>), dim3(grid), dim3(256), 0, st, p);
+hipError_t launch(PwArgs q, hipStream_t st) {
+  const int32_t blocks = (q.N + 31) / 32;
+  // C <= 96: several blocks per wavefront as long as that leaves 1.5 wavefronts per SIMD
+  const int64_t per = q.C <= 96 ? q.tiles * blocks / 1536 : 1;
+  q.per_wave = (int32_t)(per < 1 ? 1 : per < blocks ? per : blocks);
+  q.nblocks = (blocks + q.per_wave - 1) / q.per_wave;
+  q.per_wave = (blocks + q.nblocks - 1) / q.nblocks;
+  const int64_t ids = q.tiles * q.nblocks;
+  auto inverse = [&](int32_t d, int64_t n) { return d > 1 && n * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; };
+  q.inv_tpi = inverse(q.tiles_per_img, q.tiles);
+  q.inv_nb = inverse(q.nblocks, ids);
+  // Four wavefronts per tile and block up to where one each fills half of the SIMDs (us with four and with one: 384 -> 64
+  // on 8 x 56 x 56, 400 of them, 6.0, 7.9; 480 -> 80 on 2 x 112 x 112, 588, 10.5, 8.3).
+  if (q.C > 64 && ids <= 512)
+    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 4, 5>), dim3((unsigned)ids), dim3(256), 0, st, q);
+  else if (q.C <= 32)
+    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 1, 1>), dim3((unsigned)ids), dim3(64), 0, st, q);
+  else if (q.C <= 64)
+    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 1, 2>), dim3((unsigned)ids), dim3(64), 0, st, q);
+  else if (q.C <= 96)
+    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 1, 3>), dim3((unsigned)ids), dim3(64), 0, st, q);
+  else
+    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 1, 5>), dim3((unsigned)ids), dim3(64), 0, st, q);
   return hipGetLastError();
 }
 
@@ -383,16 +369,10 @@ hipError_t launch_nt(const PwArgs& p, hipStream_t st) {
 // Returns false (and launches nothing) when the geometry is not this kernel's.
 bool try_qconv_pointwise_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hipError_t* err) {
   const int64_t HW = (int64_t)cg.H * cg.W;
-  const size_t esz = a.has_rq ? 1 : (a.acc16 ? 2 : 4);
-  const bool quad = quad_form(cg.C, cg.O);  // the 128-pixel kernel
   if (a.acc_wrap_shift != 0 && a.acc_wrap_shift != 16) return false;  // 24-bit accumulators: the general path
-  if (a.has_rq && a.rq.half_away && !quad) return false;  // the wider kernel: ties toward +infinity only
-  if (cg.nhwc || cg.KH != 1 || cg.KW != 1 || cg.stride_h != 1 || cg.stride_w != 1 || cg.pad_h != 0 ||
-      cg.pad_w != 0 || (quad ? cg.C % 4 != 0 : cg.C % 16 != 0) || HW % 4 != 0 || (!quad && cg.O > 128) ||
-      (int64_t)cg.C * HW >= (1ll << 31) ||
-      (int64_t)cg.O * cg.C >= (1ll << 31) || (reinterpret_cast<uintptr_t>(a.wgt) & 15u) != 0 ||
-      (reinterpret_cast<uintptr_t>(a.act) & 3u) != 0 ||
-      (reinterpret_cast<uintptr_t>(a.out) & (4 * esz - 1)) != 0)
+  if (cg.nhwc || cg.KH != 1 || cg.KW != 1 || cg.stride_h != 1 || cg.stride_w != 1 || cg.pad_h != 0 || cg.pad_w != 0 ||
+      cg.C % 4 != 0 || HW < 4 || (int64_t)cg.C * HW >= (1ll << 31) || (int64_t)cg.O * cg.C >= (1ll << 31) ||
+      cg.B * ((HW + 127) / 128) * ((cg.O + 31) / 32) >= (1ll << 31))
     return false;
   PwArgs p{};
   p.act = static_cast<const uint8_t*>(a.act);
@@ -402,15 +382,15 @@ bool try_qconv_pointwise_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t
   p.mult = a.rq.multiplier;
   p.shift = a.rq.shift;
   p.B = cg.B; p.C = cg.C; p.HW = (int32_t)HW; p.N = cg.O;
-  p.tiles_per_img = (int32_t)((HW + 31) / 32);
+  p.tiles_per_img = (int32_t)((HW + 127) / 128);
   p.tiles = (int64_t)cg.B * p.tiles_per_img;
   p.act_xor4 = a.act_unsigned ? 0x80808080u : 0u;
   p.corr_coef = (a.act_unsigned ? 128 : 0) - a.act_zero_point;
   p.per_channel = a.rq.per_channel;
   p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
-  if (p.tiles == 0 || p.tiles / 4 >= (1ll << 31)) return false;
-  if (a.has_rq) *err = a.acc16 ? launch_nt<0, true>(p, st) : launch_nt<0, false>(p, st);
-  else *err = a.acc16 ? launch_nt<2, true>(p, st) : launch_nt<1, false>(p, st);
+  if (p.tiles == 0) return false;
+  if (a.has_rq) *err = a.acc16 ? launch<0, true>(p, st) : launch<0, false>(p, st);
+  else *err = a.acc16 ? launch<2, true>(p, st) : launch<1, false>(p, st);
   return true;
 }
 
