@@ -117,6 +117,8 @@ bool try_qconv3x3_nchw(const GemmArgs& g, const ConvGeom& cg, hipStream_t st, hi
 // Convolution of any geometry in one launch, no scratch; forced_shape >= 0: that wavefront shape (tests).  False when the
 // geometry is not that kernel's (nothing is launched then).
 bool try_qconv_direct(const GemmArgs& g, const ConvGeom& cg, int forced_shape, hipStream_t st, hipError_t* err);
+// Channel-last convolution of 16 or more channels, operands straight from memory to registers; false: not its geometry.
+bool try_qconv_gather(const GemmArgs& g, const ConvGeom& cg, int forced_shape, hipStream_t st, hipError_t* err);
 // 1x1 stride-1 unpadded NCHW convolution straight from the caller's buffers; false when the
 // geometry is not that kernel's (nothing is launched then).
 bool try_qconv_pointwise_nchw(const GemmArgs& g, const ConvGeom& cg, hipStream_t st, hipError_t* err);

@@ -540,6 +540,8 @@ hipError_t launch_qconv_gemm(const GemmArgs& a, const ConvGeom& cg, void* ws, bo
   }
   const int tile = g_hook[kHookGenericTile].load(std::memory_order_relaxed);
   if (path == 3 && try_qconv_direct(a, cg, tile, st, &err)) return err;
+  if (path == 4 && try_qconv_gather(a, cg, tile < 0 ? 0 : tile, st, &err)) return err;
+  if (path == 0 && try_qconv_gather(a, cg, -1, st, &err)) return err;
   if (ws && path != 1 && qconv_workspace_bytes(cg) >= 0) {
     // The rewrite through the workspace costs a launch and the copy's traffic; staging the weights in every
     // workgroup costs the one-launch kernel more the longer the reduction is (us with workspace, one launch):

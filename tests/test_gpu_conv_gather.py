@@ -1,0 +1,53 @@
+"""GPU parity of the channel-last convolution that loads both operands straight from memory, every tile shape and output
+mode, against the oracle: channel counts off the 16-byte chunk, odd numbers of chunks, fewer steps than wavefronts, filters
+that hang over every edge, channel and pixel counts off the tile."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import *  # noqa: E402,F401,F403
+from paper_2103_14949_amd import datagen
+
+CASES = [
+    # B C H W O KH KW stride pad
+    (1, 16, 4, 5, 3, 1, 1, (1, 1), (0, 0)),        # one chunk
+    (2, 17, 7, 9, 33, 3, 3, (1, 1), (1, 1)),       # the second chunk repeats 15 channels
+    (3, 31, 6, 5, 64, 1, 1, (2, 2), (0, 0)),
+    (2, 48, 9, 9, 70, 3, 3, (2, 2), (1, 1)),       # three chunks a tap: pairs straddle taps
+    (1, 64, 13, 11, 65, 5, 5, (1, 1), (2, 2)),
+    (5, 40, 7, 7, 45, 3, 3, (1, 1), (1, 1)),
+    (2, 18, 6, 8, 5, 3, 3, (1, 1), (4, 4)),        # filters outside the image altogether
+    (1, 20, 5, 4, 12, 3, 2, (1, 2), (0, 1)),
+    (1, 32, 40, 41, 130, 1, 3, (1, 1), (0, 1)),
+    (4, 200, 3, 3, 20, 3, 3, (1, 1), (1, 1)),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("shape", [0, 1, 2])
+def test_gathered_convolution(case, shape, gemm_path):
+    B, C, H, W, O, KH, KW, stride, pad = case
+    rng = np.random.default_rng(abs(hash(case)) % 2 ** 31)
+    w = rng.integers(-127, 128, (O, C, KH, KW)).astype(np.int8)
+    bias = rng.integers(-10 ** 5, 10 ** 5, O).astype(np.int32)
+    mult, shift = datagen.requant_params(rng, np.full(O, 74.0 * 73.0 * np.sqrt(C * KH * KW)), 40.0)
+    to = lambda x: np.ascontiguousarray(x.transpose(0, 2, 3, 1))  # noqa: E731
+    w_t, wl = hago.QType(hago.I8), to(w)
+    args, rargs = (hago.NHWC, stride, pad, 1), (ref.NHWC, stride, pad, 1)
+    gemm_path(4)
+    hago.set_test_hook(hago.HOOK_GENERAL_TILE, shape)
+    try:
+        for adt, za in ((np.uint8, 131), (np.int8, 0), (np.int8, -5)):
+            a = to((rng.integers(0, 256, (B, C, H, W)) if adt == np.uint8 else rng.integers(-128, 128, (B, C, H, W))).astype(adt))
+            a_t, da, dw = act_qtype(a, za), dev(a), dev(wl)
+            assert_same(host(hago.qconv2d(da, a_t, dw, w_t, dev(bias), *args)), ref.qconv2d(a, za, wl, bias, *rargs), f"raw {case}")
+            if za == 0:
+                assert_same(host(hago.qconv2d(da, a_t, dw, w_t, None, *args, hago.I16)), ref.qconv2d(a, za, wl, None, *rargs, ref.I16), "raw 16")
+                continue
+            for out_u8, z, clip, rounding in ((False, -3, (-128, 127), 0), (True, 10, (10, 255), 1)):
+                want = ref.qconv2d(a, za, wl, bias, *rargs, ref.I32, ref_requant(mult, shift, out_u8, z, clip, rounding))
+                got = hago.qconv2d(da, a_t, dw, w_t, dev(bias), *args, hago.I32, gpu_requant(mult, shift, out_u8, z, clip, rounding=rounding))
+                assert_same(host(got), want, f"requantized {case} u8={out_u8}")
+    finally:
+        hago.set_test_hook(hago.HOOK_GENERAL_TILE, -1)
