@@ -429,7 +429,7 @@ hago_status hago_probe_copy(const void* src, void* dst, int64_t bytes,
  *   HAGO_HOOK_GEMM_PATH     0 automatic; 1 the general register-staged kernel;
  *                           2 the streaming kernel, skipping the one-launch
  *                           convolution kernels; 3 the general one-launch
- *                           convolution kernel; 4 the channel-last kernel
+ *                           convolution kernel; 4 the convolution kernels
  *                           without staging
  *   HAGO_HOOK_STREAM_TILE   -1 automatic; 0..4 a tile of the streaming dense kernel
  *   HAGO_HOOK_GENERAL_TILE  -1 automatic; 0..6 a tile of the general convolution

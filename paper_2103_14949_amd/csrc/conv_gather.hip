@@ -1,4 +1,4 @@
-// Channel-last convolution of 16 or more channels in one launch, without LDS staging: out[b][oy][ox][n] =
+// Convolution in one launch, without LDS staging.  Channel-last first, of 16 or more channels (NCHW: below): out[b][oy][ox][n] =
 // sum_{ky,kx,c} (a[b][oy sh + ky - ph][ox sw + kx - pw][c] - z_a) * w[n][ky][kx][c] + bias[n].
 //
 // In channel-last tensors the 16 reduction bytes that a lane gives to a matrix instruction lie together in memory, for the
@@ -277,6 +277,320 @@ hipError_t launch_shape(const CgParams& p, int mode, hipStream_t st) {
   return hipGetLastError();
 }
 
+// ---- NCHW.  The 16 reduction elements of a lane (k = (c, ky, kx), in the order of the weights) are 16 bytes at 16 places,
+// loaded one by one: neighbouring lanes are neighbouring pixels, so a byte load of a wavefront touches two or three lines.
+// What an element adds to the address of a pixel's window is the same for every lane of a half, and comes with its tap's
+// number from a table in LDS (26 and 6 bits) that the workgroup builds once; whether the tap is inside the image is bit 63 of a mask of
+// the pixel's missing taps, shifted by that number, and goes into the offset's sign bit (out of the descriptor's range).
+// The weights of a wavefront's steps stay in registers while the workgroup goes from tile to tile, if they are at most
+// five steps.
+//   KS = 4: four wavefronts share a tile as above; KS = 1: each has one of its own (short reductions).
+constexpr int kResident = 5;
+struct CnParams {
+  const uint8_t* act;
+  const int8_t* wgt;
+  const int32_t* bias;
+  void* out;
+  const int32_t* mult;
+  const int32_t* shift;
+  int32_t B, C, H, W, N, OW, OHW, KH, KW, sh, sw, ph, pw;
+  int32_t K, taps, steps;
+  int32_t tiles_per_img, tiles, nblocks;        // pixel tiles; blocks of output channels
+  uint32_t inv_tpi, inv_ow, inv_taps, inv_kw;   // as above
+  uint32_t x4, zbyte;                           // sign flip of uint8 bytes; the zero point's byte as stored
+  int32_t corr_coef, per_channel, acc_wrap_shift;
+  RequantScalars rs;
+};
+
+template <int MODE, int TC, int KS, bool ZP>
+__global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_gather_nchw_kernel(CnParams p) {
+  constexpr int NW = KS == 8 ? 8 : 4;                          // wavefronts
+  constexpr int UPW = KS == 1 ? 4 : (4 * TC < KS ? 1 : 4 * TC / KS);  // groups of four registers a wavefront finishes at a time
+  constexpr int NFIN = KS == 1 ? 0 : 4 * TC / UPW;             // wavefronts that finish (KS > 1)
+  extern __shared__ __align__(16) int32_t smem[];
+  uint32_t* const s_tab = reinterpret_cast<uint32_t*>(smem);                          // steps * 32
+  int32_t* const s_wsum = smem + p.steps * 32;                                        // NW x 32 TC (KS > 1)
+  v4i* const s_part = reinterpret_cast<v4i*>(s_wsum + (KS == 1 ? 0 : NW * 32 * TC));   // NW TC 4 64 (KS > 1)
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int blk = (int)(blockIdx.x % (unsigned)p.nblocks), first = (int)(blockIdx.x / (unsigned)p.nblocks);
+  const int stride = (int)(gridDim.x / (unsigned)p.nblocks);
+  const int n0 = blk * 32 * TC;
+  const int K = p.K;
+
+  // the table
+  for (int k = threadIdx.x; k < p.steps * 32; k += 64 * NW) {
+    const uint32_t c = div_by((uint32_t)k, (uint32_t)p.taps, p.inv_taps), tap = (uint32_t)k - c * (uint32_t)p.taps;
+    const uint32_t ky = div_by(tap, (uint32_t)p.KW, p.inv_kw), kx = tap - ky * (uint32_t)p.KW;
+    s_tab[k] = k < K ? ((c * (uint32_t)p.H + ky) * (uint32_t)p.W + kx) << 6 | (63 - tap) : 0u;
+  }
+
+  // this wavefront's steps and their weights
+  const int s_first = KS == 1 ? 0 : p.steps * wave / KS, s_last = KS == 1 ? p.steps : p.steps * (wave + 1) / KS;
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(p.wgt), 0, p.N * K, 0x00020000);
+  // (the last, incomplete step byte by byte: none of the next channel)
+  v4i wtail[TC];
+  const int whole = K >> 5;
+  if (s_last > whole) {
+#pragma unroll
+    for (int t = 0; t < TC; ++t)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const int ch = n0 + 32 * t + n, k0 = 32 * whole + 16 * h + 4 * d;
+        uint32_t v = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          v |= (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rw, ch < p.N && k0 + e < K ? (uint32_t)(ch * K + k0 + e) : kOob, 0, 0) << (8 * e);
+        wtail[t][d] = (int)v;
+      }
+  }
+  auto load_w = [&](int s, int t) -> v4i {
+    const int ch = n0 + 32 * t + n;
+    if (s >= whole) return wtail[t];  // uniform
+    return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, ch < p.N ? (uint32_t)(ch * K + 32 * s + 16 * h) : kOob, 0, 0));
+  };
+  const bool resident = s_last - s_first <= kResident;
+  v4i wres[kResident][TC];
+  int32_t wsum[TC];
+#pragma unroll
+  for (int t = 0; t < TC; ++t) wsum[t] = 0;
+  auto sum_w = [&](const v4i& w, int t) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) wsum[t] = __builtin_amdgcn_sdot4(w[d], 0x01010101, wsum[t], false);
+  };
+  if (resident) {
+#pragma unroll
+    for (int u = 0; u < kResident; ++u)
+      if (s_first + u < s_last)
+#pragma unroll
+        for (int t = 0; t < TC; ++t) wres[u][t] = load_w(s_first + u, t);
+#pragma unroll
+    for (int u = 0; u < kResident; ++u)
+      if (s_first + u < s_last)
+#pragma unroll
+        for (int t = 0; t < TC; ++t) sum_w(wres[u][t], t);
+  } else {
+    for (int s = s_first; s < s_last; ++s)
+#pragma unroll
+      for (int t = 0; t < TC; ++t) sum_w(load_w(s, t), t);
+  }
+  // the lane's output channels
+  int32_t mult[TC], shift[TC], corr[TC];
+#pragma unroll
+  for (int t = 0; t < TC; ++t) {
+    const int ch = n0 + 32 * t + n < p.N ? n0 + 32 * t + n : p.N - 1;
+    corr[t] = p.bias ? p.bias[ch] : 0;
+    mult[t] = MODE == 0 ? rq_mult(p.mult, p.per_channel ? ch : 0) : 0;
+    shift[t] = MODE == 0 ? rq_shift(p.mult, p.shift, p.per_channel ? ch : 0) : 0;
+  }
+#pragma unroll
+  for (int t = 0; t < TC; ++t) {
+    wsum[t] += __shfl_xor(wsum[t], 32);
+    if constexpr (KS > 1) {
+      if (h == 0) s_wsum[wave * 32 * TC + 32 * t + n] = wsum[t];
+    }
+  }
+  __syncthreads();  // the table (and the sums) are there
+  const RequantScalars rs = p.rs;
+  bool fold = MODE == 0 && K < (1 << 15) && rs.z_out >= -256 && rs.z_out <= 255 && !rs.half_away && p.acc_wrap_shift == 0;
+  int64_t k64[TC];
+#pragma unroll
+  for (int t = 0; t < TC; ++t) {
+    if constexpr (KS > 1) {
+      wsum[t] = 0;
+#pragma unroll
+      for (int w = 0; w < KS; ++w) wsum[t] += s_wsum[w * 32 * TC + 32 * t + n];
+    }
+    corr[t] += p.corr_coef * wsum[t];
+    k64[t] = (int64_t)corr[t] * mult[t] + ((int64_t)1 << (30 + shift[t])) + ((int64_t)rs.z_out << (31 + shift[t]));
+    fold = fold && __builtin_amdgcn_ballot_w64(!(shift[t] >= 0 && shift[t] <= 19 && corr[t] >= -(1 << 30) && corr[t] <= (1 << 30))) == 0;
+  }
+
+  const int64_t img_in = (int64_t)p.C * p.H * p.W;
+  constexpr int AT = KS == 1 ? NW : 1;  // tiles of a workgroup at a time
+  for (int tl0 = first * AT; tl0 < p.tiles; tl0 += stride * AT) {
+    const int tl = KS == 1 ? tl0 + wave : tl0;
+    if (KS == 1 && tl >= p.tiles) break;  // (no barrier in this form's loop)
+    const int b = (int)div_by((uint32_t)tl, (uint32_t)p.tiles_per_img, p.inv_tpi);
+    int pix0 = (tl - b * p.tiles_per_img) * 32;
+    if (p.OHW >= 32 && pix0 > p.OHW - 32) pix0 = p.OHW - 32;  // (the last tile ends with the image)
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.act) + b * img_in, 0, (int)img_in, 0x00020000);
+    const int m = pix0 + channel_of_row(n);  // (registers are 16 consecutive pixels)
+    const uint32_t oy = div_by((uint32_t)m, (uint32_t)p.OW, p.inv_ow);
+    const int iy = (int)oy * p.sh - p.ph, ix = (m - (int)oy * p.OW) * p.sw - p.pw;
+    const uint32_t base = (uint32_t)(iy * p.W + ix);
+    const int xl = ix < 0 ? -ix : 0, xr = p.W - ix < p.KW ? p.W - ix : p.KW;  // columns xl .. xr - 1 of the filter are inside
+    const uint64_t cols = xl < xr ? ((1ull << xr) - 1) & ~((1ull << xl) - 1) : 0;
+    uint64_t missing = 0;  // bit: tap outside the image; bit 63: elements beyond K
+    for (int ky = 0; ky < p.KH; ++ky)
+      if ((uint32_t)(iy + ky) < (uint32_t)p.H) missing |= cols << (ky * p.KW);
+    missing = m < p.OHW ? ~missing : ~0ull;
+
+    v16i acc[TC];
+#pragma unroll
+    for (int t = 0; t < TC; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[t][r] = 0;
+    struct Step { uint32_t byte[16], out; };  // out: bit 15 - e, element e is missing (ZP)
+    auto gather = [&](int s, Step& q) {
+      q.out = 0;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const uint32_t at = s_tab[32 * s + 16 * h + e];
+        const uint32_t miss = (uint32_t)((missing << (at & 63u)) >> 32);
+        if constexpr (ZP) q.out = __builtin_amdgcn_alignbit(q.out, miss, 31);
+        q.byte[e] = (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(ra, (miss & kOob) | ((base + (at >> 6)) & 0x7fffffffu), 0, 0);
+      }
+    };
+    auto operand = [&](const Step& q) {
+      v4i a;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        uint32_t v = q.byte[4 * d] | q.byte[4 * d + 1] << 8 | q.byte[4 * d + 2] << 16 | q.byte[4 * d + 3] << 24;
+        if constexpr (ZP) {  // missing taps read 0
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v |= ((uint32_t)__builtin_amdgcn_sbfe((int)q.out, 15 - 4 * d - e, 1) & p.zbyte) << (8 * e);
+        }
+        a[d] = (int)(v ^ p.x4);
+      }
+      return a;
+    };
+    if (resident) {
+#pragma unroll
+      for (int u = 0; u < kResident; ++u) {
+        if (s_first + u < s_last) {
+          Step q;
+          gather(s_first + u, q);
+          const v4i a = operand(q);
+#pragma unroll
+          for (int t = 0; t < TC; ++t) acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, wres[u][t], acc[t], 0, 0, 0);
+        }
+      }
+    } else {
+      Step q[2];
+      v4i w[2][TC];
+      auto fetch = [&](int s, Step& q_, v4i (&w_)[TC]) {
+#pragma unroll
+        for (int t = 0; t < TC; ++t) w_[t] = load_w(s, t);
+        gather(s, q_);
+      };
+      auto use = [&](const Step& q_, const v4i (&w_)[TC]) {
+        const v4i a = operand(q_);
+#pragma unroll
+        for (int t = 0; t < TC; ++t) acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, w_[t], acc[t], 0, 0, 0);
+      };
+      fetch(s_first, q[0], w[0]);
+      for (int s = s_first; s < s_last; s += 2) {
+        if (s + 1 < s_last) fetch(s + 1, q[1], w[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        use(q[0], w[0]);
+        if (s + 1 < s_last) {
+          if (s + 2 < s_last) fetch(s + 2, q[0], w[0]);
+          __builtin_amdgcn_sched_barrier(0);
+          use(q[1], w[1]);
+        }
+      }
+    }
+
+    // results: lane n has channel n0 + 32 t + n, registers 4 g + e pixel 16 h + 4 g + e of the tile
+    constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
+    auto finish = [&](int g0, int t, int32_t mu, int32_t sf, int32_t co, int64_t kk, auto&& sums) {
+      const int ch = n0 + 32 * t + n, px = pix0 + 16 * h + 4 * g0;
+      int32_t v[UPW][4];
+#pragma unroll
+      for (int u = 0; u < UPW; ++u) {
+        const v4i s = sums(u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (MODE == 0 && fold) v[u][e] = med3((int32_t)(((int64_t)s[e] * (int64_t)mu + kk) >> (31 + sf)), rs.lo_rel + rs.z_out, rs.hi_rel + rs.z_out);
+          else {
+            v[u][e] = wrap_acc_bits(s[e] + co, p.acc_wrap_shift);
+            if constexpr (MODE == 0) v[u][e] = requant_general(v[u][e], mu, sf, rs);
+          }
+        }
+      }
+      if (ch >= p.N || px >= p.OHW) return;
+      uint8_t* o = static_cast<uint8_t*>(p.out) + (((int64_t)b * p.N + ch) * p.OHW + px) * kEsz;
+      if (px + 4 * UPW <= p.OHW) {
+        if constexpr (MODE == 0) {
+          uint32_t dw[UPW];
+#pragma unroll
+          for (int u = 0; u < UPW; ++u) dw[u] = pack4_perm(v[u][0], v[u][1], v[u][2], v[u][3]);
+          if constexpr (UPW == 4) *reinterpret_cast<v4i_u*>(o) = v4i{(int)dw[0], (int)dw[1], (int)dw[2], (int)dw[3]};
+          else if constexpr (UPW == 2) *reinterpret_cast<v2i_u*>(o) = v2i_u{(int)dw[0], (int)dw[1]};
+          else *reinterpret_cast<u32_u*>(o) = dw[0];
+        } else {
+#pragma unroll
+          for (int u = 0; u < UPW; ++u) {
+            if constexpr (MODE == 1) *reinterpret_cast<v4i_u*>(o + 16 * u) = v4i{v[u][0], v[u][1], v[u][2], v[u][3]};
+            else *reinterpret_cast<v2i_u*>(o + 8 * u) = v2i_u{(v[u][0] & 0xffff) | (int)((uint32_t)v[u][1] << 16), (v[u][2] & 0xffff) | (int)((uint32_t)v[u][3] << 16)};
+          }
+        }
+        return;
+      }
+#pragma unroll
+      for (int u = 0; u < UPW; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (px + 4 * u + e >= p.OHW) continue;
+          if constexpr (MODE == 0) o[4 * u + e] = (uint8_t)v[u][e];
+          else if constexpr (MODE == 1) reinterpret_cast<int32_t*>(o)[4 * u + e] = v[u][e];
+          else reinterpret_cast<int16_t*>(o)[4 * u + e] = (int16_t)v[u][e];
+        }
+    };
+    if constexpr (KS == 1) {
+#pragma unroll
+      for (int t = 0; t < TC; ++t)
+        finish(0, t, mult[t], shift[t], corr[t], k64[t],
+               [&](int u) { return v4i{acc[t][4 * u], acc[t][4 * u + 1], acc[t][4 * u + 2], acc[t][4 * u + 3]}; });
+    } else {
+#pragma unroll
+      for (int t = 0; t < TC; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          s_part[((wave * TC + t) * 4 + g) * 64 + lane] = v4i{acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]};
+      __syncthreads();
+      if (wave < NFIN) {
+        const int unit0 = wave * UPW, tc = unit0 >> 2, g0 = unit0 & 3;
+        int32_t mu = mult[0], sf = shift[0], co = corr[0];
+        int64_t kk = k64[0];
+#pragma unroll
+        for (int t = 1; t < TC; ++t)
+          if (tc == t) { mu = mult[t]; sf = shift[t]; co = corr[t]; kk = k64[t]; }
+        finish(g0, tc, mu, sf, co, kk, [&](int u) {
+          v4i s = {0, 0, 0, 0};
+#pragma unroll
+          for (int w = 0; w < KS; ++w) s += s_part[((w * TC + tc) * 4 + g0 + u) * 64 + lane];
+          return s;
+        });
+      }
+      __syncthreads();  // the partial sums have been read
+    }
+  }
+}
+
+template <int TC, int KS, bool ZP>
+hipError_t launch_nchw_zp(const CnParams& p, int mode, hipStream_t st) {
+  constexpr int NW = KS == 8 ? 8 : 4, AT = KS == 1 ? NW : 1;
+  CnParams q = p;
+  q.nblocks = (q.N + 32 * TC - 1) / (32 * TC);
+  const size_t lds = (size_t)q.steps * 128 + (KS == 1 ? 0 : NW * 32 * TC * 4 + (size_t)NW * TC * 4 * 64 * 16);
+  auto kern = mode == 0 ? conv_gather_nchw_kernel<0, TC, KS, ZP> : mode == 1 ? conv_gather_nchw_kernel<1, TC, KS, ZP> : conv_gather_nchw_kernel<2, TC, KS, ZP>;
+  static std::atomic<uint64_t> attr_set[3];
+  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set[mode]);
+  if (e != hipSuccess) return e;
+  const int64_t groups = ((int64_t)q.tiles + AT - 1) / AT;
+  int64_t per_blk = (lds <= 80 * 1024 && NW == 4 ? 512 : 256) / q.nblocks;
+  per_blk = per_blk < 1 ? 1 : (per_blk > groups ? groups : per_blk);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(per_blk * q.nblocks)), dim3(64 * NW), lds, st, q);
+  return hipGetLastError();
+}
+
+template <int TC, int KS>
+hipError_t launch_nchw(const CnParams& p, int mode, hipStream_t st) {
+  return p.zbyte ? launch_nchw_zp<TC, KS, true>(p, mode, st) : launch_nchw_zp<TC, KS, false>(p, mode, st);
+}
+
 }  // namespace
 
 // Returns false (and launches nothing) when the geometry is not this kernel's, or another kernel is the better one.
@@ -329,6 +643,65 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, int forced_shape, h
     case 0: *err = launch_shape<2, 2, 4>(p, mode, st); break;
     case 1: *err = launch_shape<2, 2, 8>(p, mode, st); break;
     default: *err = launch_shape<1, 1, 4>(p, mode, st); break;
+  }
+  return true;
+}
+
+// The same for NCHW, any channel count.  forced_shape, pixels x output channels: 0 32 x 32 by eight wavefronts, 1 32 x 64 by
+// four, 2 32 x 32 by four, 3 32 x 64 by one; -1 by size.
+bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err) {
+  const int64_t img = (int64_t)cg.C * cg.H * cg.W;
+  const int64_t ohw = (int64_t)cg.OH * cg.OW;
+  if (cg.nhwc || cg.KH * cg.KW > 63 || a.K > 28000 || img >= (1ll << 26) || (int64_t)cg.O * a.K >= (1ll << 31) ||
+      (int64_t)cg.B * ((ohw + 31) / 32) >= (1ll << 30))
+    return false;
+  CnParams p{};
+  p.act = static_cast<const uint8_t*>(a.act);
+  p.wgt = a.wgt;
+  p.bias = a.bias;
+  p.out = a.out;
+  p.mult = a.rq.multiplier;
+  p.shift = a.rq.shift;
+  p.B = cg.B; p.C = cg.C; p.H = cg.H; p.W = cg.W; p.N = cg.O; p.OW = cg.OW; p.OHW = (int32_t)ohw;
+  p.KH = cg.KH; p.KW = cg.KW; p.sh = cg.stride_h; p.sw = cg.stride_w; p.ph = cg.pad_h; p.pw = cg.pad_w;
+  p.K = a.K;
+  p.taps = cg.KH * cg.KW;
+  p.steps = (a.K + 31) / 32;
+  auto inverse = [](int64_t d, int64_t n) { return d > 1 && n * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d) : 0u; };
+  p.inv_ow = inverse(cg.OW, ohw + 64);
+  p.inv_taps = inverse(p.taps, a.K + 32);
+  p.inv_kw = inverse(cg.KW, p.taps);
+  p.x4 = a.act_unsigned ? 0x80808080u : 0u;
+  p.zbyte = (uint32_t)a.act_zero_point & 0xffu;
+  p.corr_coef = (a.act_unsigned ? 128 : 0) - a.act_zero_point;
+  p.per_channel = a.rq.per_channel;
+  p.acc_wrap_shift = a.acc_wrap_shift;
+  p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
+  const int mode = a.has_rq ? 0 : (a.acc16 ? 2 : 1);
+  p.tiles_per_img = (int32_t)((ohw + 31) / 32);
+  p.tiles = cg.B * p.tiles_per_img;
+  p.inv_tpi = inverse(p.tiles_per_img, p.tiles);
+  // Microseconds: 3.8 and, per CU, 0.4 for every tile and 0.11 (32 channels) or 0.13 (64) for every step, nearly twice that
+  // where neighbouring pixels are not neighbouring bytes; long reductions lose more, as a wavefront has two steps' loads
+  // under way.  The other kernels: 8.5 and their rate and the length of the reduction (which costs the one-launch
+  // kernel more for filters other than 3x3, and is its only cost without a workspace).  Measured (here, other): 5 x 38 x 38 13 -> 42 5x5 6.7, 14.2; 16 x 25 x 26 132 -> 137 1x1 stride 2 5.9,
+  // 9.8; 2 x 18 x 16 63 -> 147 5x5 14.1, 10.7 with and 39.5 without a workspace; 8 x 224 x 224 3 -> 64 7x7 stride 2 24.8, 14.3;
+  // 64 x 32 x 32 3 -> 16 6.6, 8.6.
+  const double step = cg.stride_w > 1 ? 1.8 * p.steps : (double)p.steps;
+  const double r32 = (double)p.tiles * ((a.N + 31) / 32) / 256, r64 = (double)p.tiles * ((a.N + 63) / 64) / 256;
+  const double t32 = (r32 > 1 ? r32 : 1.0) * (0.4 + 0.11 * step), t64 = (r64 > 1 ? r64 : 1.0) * (0.4 + 0.13 * step);
+  const bool alone = p.steps <= 2 && r64 >= 4;
+  int shape = forced_shape;
+  if (shape < 0) {
+    const double t = 3.8 + (alone ? 0.35 * r64 : t32 < t64 ? t32 : t64) + (p.steps > 18 ? 0.1 * (p.steps - 18) : 0.0);
+    if (t >= 8.5 + (double)a.M * a.N * a.K / 0.41e9 + (double)a.K / (has_workspace || p.taps == 9 || p.taps == 1 ? 450 : 70)) return false;
+    shape = alone ? 3 : t64 < t32 ? 1 : p.steps >= 24 && r32 <= 1 ? 0 : 2;
+  }
+  switch (shape) {
+    case 0: *err = launch_nchw<1, 8>(p, mode, st); break;
+    case 1: *err = launch_nchw<2, 4>(p, mode, st); break;
+    case 2: *err = launch_nchw<1, 4>(p, mode, st); break;
+    default: *err = launch_nchw<2, 1>(p, mode, st); break;
   }
   return true;
 }

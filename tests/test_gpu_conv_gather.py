@@ -1,6 +1,6 @@
-"""GPU parity of the channel-last convolution that loads both operands straight from memory, every tile shape and output
-mode, against the oracle: channel counts off the 16-byte chunk, odd numbers of chunks, fewer steps than wavefronts, filters
-that hang over every edge, channel and pixel counts off the tile."""
+"""GPU parity of the convolution that loads both operands straight from memory, both layouts, every tile shape and output
+mode, against the oracle: channel counts off the 16-byte chunk, odd numbers of chunks, fewer steps than wavefronts, weights
+that stay in registers and that do not, filters that hang over every edge, channel and pixel counts off the tile."""
 import numpy as np
 import pytest
 
@@ -21,20 +21,29 @@ CASES = [
     (1, 20, 5, 4, 12, 3, 2, (1, 2), (0, 1)),
     (1, 32, 40, 41, 130, 1, 3, (1, 1), (0, 1)),
     (4, 200, 3, 3, 20, 3, 3, (1, 1), (1, 1)),
+    (2, 3, 31, 37, 20, 7, 7, (2, 2), (3, 3)),      # NCHW only from here: few channels
+    (3, 1, 4, 7, 70, 1, 1, (1, 1), (0, 0)),
+    (3, 6, 11, 14, 33, 5, 5, (1, 1), (2, 2)),
+    (9, 9, 17, 16, 65, 3, 3, (1, 1), (1, 1)),
+    (1, 180, 5, 6, 3, 7, 7, (2, 2), (3, 3)),       # a long table
 ]
 
 
 @pytest.mark.parametrize("case", CASES)
-@pytest.mark.parametrize("shape", [0, 1, 2])
-def test_gathered_convolution(case, shape, gemm_path):
+@pytest.mark.parametrize("shape", [0, 1, 2, 3])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+def test_gathered_convolution(case, shape, layout, gemm_path):
     B, C, H, W, O, KH, KW, stride, pad = case
+    if layout == "nhwc" and (C < 16 or shape == 3 or KH == 7):
+        return
     rng = np.random.default_rng(abs(hash(case)) % 2 ** 31)
     w = rng.integers(-127, 128, (O, C, KH, KW)).astype(np.int8)
     bias = rng.integers(-10 ** 5, 10 ** 5, O).astype(np.int32)
     mult, shift = datagen.requant_params(rng, np.full(O, 74.0 * 73.0 * np.sqrt(C * KH * KW)), 40.0)
-    to = lambda x: np.ascontiguousarray(x.transpose(0, 2, 3, 1))  # noqa: E731
+    lay_g, lay_r = (hago.NCHW, ref.NCHW) if layout == "nchw" else (hago.NHWC, ref.NHWC)
+    to = (lambda x: x) if layout == "nchw" else (lambda x: np.ascontiguousarray(x.transpose(0, 2, 3, 1)))
     w_t, wl = hago.QType(hago.I8), to(w)
-    args, rargs = (hago.NHWC, stride, pad, 1), (ref.NHWC, stride, pad, 1)
+    args, rargs = (lay_g, stride, pad, 1), (lay_r, stride, pad, 1)
     gemm_path(4)
     hago.set_test_hook(hago.HOOK_GENERAL_TILE, shape)
     try:
