@@ -4,7 +4,7 @@
 // The int8 matrix instruction wants 16 consecutive reduction bytes per lane, and in NCHW the
 // reduction index (input channel) is the slow one.  The transposition therefore happens on the
 // way into LDS: a workgroup owns TR whole output rows of one image (TR * W <= 32 * NW * AF pixels) and
-// a block of up to 64 output channels.  It stages
+// a block of 32 or 64 output channels.  It stages
 //   - the input rows it needs, with their one-pixel halo, channel-last: [TR + 2][W + 2][C + 16]
 //     bytes (uint8 inputs flipped to int8, everything outside the image filled with the zero
 //     point, so padded taps contribute 0 under the zero-point identity of the GEMM kernels).  The
@@ -49,7 +49,7 @@ struct C3Params {
   int32_t TR;            // output rows per tile
   int32_t tiles_per_img; // ceil(H / TR)
   int32_t ntiles;        // B * tiles_per_img
-  int32_t nblk;          // blocks of 64 output channels
+  int32_t nblk;          // blocks of 32 TN output channels
   int32_t per_channel, has_rq, acc_wrap_shift;
   int32_t out_mode;      // 0: requantized 8-bit, 1: raw int32, 2: raw int16
   uint32_t act_xor4;     // 0x80808080 for uint8 activations
@@ -79,7 +79,7 @@ __device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, u
 
 // NW: wavefronts per workgroup; AF: 32-pixel MFMA row blocks per wavefront (tiles of 32 * NW * AF
 // pixels); NU: staging units per thread; CK: input channels / 32.
-template <int NW, int AF, int NU, int CK>
+template <int NW, int AF, int NU, int CK, int TN>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(C3Params p) {
   constexpr int NT = 64 * NW;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -111,11 +111,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
     tile_end = p.ntiles;
     tile_step = nwg;
   }
-  const int o0 = blk * 64;                             // this workgroup's block of output channels
+  constexpr int OB = 32 * TN;
+  const int o0 = blk * OB;                             // this workgroup's block of output channels
 
-  uint8_t* s_w = smem;                                 // [64][wstride]
-  uint8_t* s_in = smem + 64 * wstride;                 // [(TR + 2)][Wp][Cp]
-  int32_t* s_sum = reinterpret_cast<int32_t*>(s_in + (p.TR + 2) * Wp * Cp);  // [64] weight sums
+  uint8_t* s_w = smem;                                 // [OB][wstride]
+  uint8_t* s_in = smem + OB * wstride;                 // [(TR + 2)][Wp][Cp]
+  int32_t* s_sum = reinterpret_cast<int32_t*>(s_in + (p.TR + 2) * Wp * Cp);  // [OB] weight sums
 
   // ---- staging units of a tile: (16-channel group, dword of the channel's run of TR + 2 rows)
   const int w4 = W >> 2;
@@ -176,16 +177,16 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   // weight sums per output channel (only the zero-point term needs them): every thread that
   // stages weights adds its four channels' nine taps
   const bool need_sum = p.corr_coef != 0;
-  if (t < 64) s_sum[t] = 0;
+  if (t < OB) s_sum[t] = 0;
   __syncthreads();
 
   if (tile < tile_end) load_tile(tile);   // in flight while the weights are staged
 
-  // ---- per-lane constants: output channels o0 + j and o0 + 32 + j (their loads go out now too)
+  // ---- per-lane constants: output channels o0 + 32 tn + j (their loads go out now too)
   const int j = lane & 31, h = lane >> 5;
-  int32_t corr[2], mu[2], sh[2];
+  int32_t corr[TN], mu[TN], sh[TN];
 #pragma unroll
-  for (int tn = 0; tn < 2; ++tn) {
+  for (int tn = 0; tn < TN; ++tn) {
     const int o = o0 + 32 * tn + j;
     corr[tn] = 0; mu[tn] = 0; sh[tn] = 1;
     if (o < O) {
@@ -198,47 +199,54 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   }
 
   // ---- weights of the block: OIHW (per o: [C][9]) -> [o][tap][C]; channels beyond O are zero.
-  // A unit is four channels of one output channel: 36 contiguous bytes in memory (nine dwords when
-  // the tensor is 4-byte aligned), byte 9 j + k = channel j, tap k; tap k's dword is bytes
+  // A unit is four channels of one output channel: 36 contiguous bytes in memory (nine dwords), byte 9 j + k = channel j, tap k; tap k's dword is bytes
   // (k, 9 + k, 18 + k, 27 + k), picked with three byte permutes.
-  const bool w_aligned = (reinterpret_cast<uintptr_t>(p.wgt) & 3u) == 0;
-  for (int i = t; i < 64 * (C / 4); i += NT) {
-    const int o = i / (C / 4), c4 = (i - o * (C / 4)) * 4;
-    uint32_t tap[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    if (o0 + o < O) {
-      const int8_t* src = p.wgt + ((int64_t)(o0 + o) * C + c4) * 9;
-      if (w_aligned) {
-        uint32_t dw[9];
+  // Two units per thread at a time: their loads go out together (with one, a layer of 128 channels waited for memory
+  // four times in a row before its first tile).  The sums of eight neighbouring lanes, always of one output channel, are
+  // added up before they go to LDS.
+  constexpr int kUnits = OB * (C / 4);
+  for (int i0 = 0; i0 < kUnits; i0 += 2 * NT) {
+    uint32_t dw[2][9];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) dw[k] = reinterpret_cast<const uint32_t*>(src)[k];
+    for (int u = 0; u < 2; ++u) {
+      const int i = i0 + u * NT + t;
+      const int o = i / (C / 4), c4 = (i - o * (C / 4)) * 4;
+      const bool ok = i < kUnits && o0 + o < O;
+      const int8_t* src = p.wgt + ((int64_t)(ok ? o0 + o : 0) * C + (ok ? c4 : 0)) * 9;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-          // selector bytes: 0-3 pick from the second operand, 4-7 from the first
-          constexpr uint32_t kKeep = 0x0c0c0000u;  // upper half zero
-          const int i0 = k, i1 = 9 + k, i2 = 18 + k, i3 = 27 + k;
-          const uint32_t lo = __builtin_amdgcn_perm(dw[i1 >> 2], dw[i0 >> 2], kKeep | (uint32_t)(i0 & 3) | ((uint32_t)(4 + (i1 & 3)) << 8));
-          const uint32_t hi = __builtin_amdgcn_perm(dw[i3 >> 2], dw[i2 >> 2], kKeep | (uint32_t)(i2 & 3) | ((uint32_t)(4 + (i3 & 3)) << 8));
-          tap[k] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-        }
-      } else {
+      for (int k = 0; k < 9; ++k) dw[u][k] = *reinterpret_cast<const u32_any*>(src + 4 * k);
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
+      for (int k = 0; k < 9; ++k) dw[u][k] = ok ? dw[u][k] : 0u;
+    }
 #pragma unroll
-          for (int k = 0; k < 9; ++k) tap[k] |= (uint32_t)(uint8_t)src[jj * 9 + k] << (8 * jj);
+    for (int u = 0; u < 2; ++u) {
+      const int i = i0 + u * NT + t;
+      if (i >= kUnits) continue;  // (kUnits is a multiple of 64: whole wavefronts)
+      const int o = i / (C / 4), c4 = (i - o * (C / 4)) * 4;
+      int32_t part = 0;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        // selector bytes: 0-3 pick from the second operand, 4-7 from the first
+        constexpr uint32_t kKeep = 0x0c0c0000u;  // upper half zero
+        const int i0_ = k, i1 = 9 + k, i2 = 18 + k, i3 = 27 + k;
+        const uint32_t lo = __builtin_amdgcn_perm(dw[u][i1 >> 2], dw[u][i0_ >> 2], kKeep | (uint32_t)(i0_ & 3) | ((uint32_t)(4 + (i1 & 3)) << 8));
+        const uint32_t hi = __builtin_amdgcn_perm(dw[u][i3 >> 2], dw[u][i2 >> 2], kKeep | (uint32_t)(i2 & 3) | ((uint32_t)(4 + (i3 & 3)) << 8));
+        const uint32_t tap = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+        *reinterpret_cast<uint32_t*>(s_w + o * wstride + k * C + c4) = tap;
+        part = __builtin_amdgcn_sdot4((int)tap, 0x01010101, part, false);
+      }
+      if (need_sum) {
+        part += __builtin_amdgcn_update_dpp(0, part, 0xB1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
+        part += __builtin_amdgcn_update_dpp(0, part, 0x4E, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
+        part += __builtin_amdgcn_update_dpp(0, part, 0x141, 0xf, 0xf, true);  // row_half_mirror
+        if ((lane & 7) == 0) atomicAdd(&s_sum[o], part);
       }
     }
-    int32_t part = 0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      *reinterpret_cast<uint32_t*>(s_w + o * wstride + k * C + c4) = tap[k];
-      part = __builtin_amdgcn_sdot4((int)tap[k], 0x01010101, part, false);
-    }
-    if (need_sum) atomicAdd(&s_sum[o], part);
   }
   __syncthreads();
   bool lane_ok = true;   // the folded requantize arithmetic is exact for this lane's channels
 #pragma unroll
-  for (int tn = 0; tn < 2; ++tn) {
+  for (int tn = 0; tn < TN; ++tn) {
     if (o0 + 32 * tn + j < O) corr[tn] += p.corr_coef * s_sum[32 * tn + j];
     lane_ok = lane_ok && sh[tn] >= 1 && sh[tn] <= 19 && corr[tn] >= -(1 << 30) && corr[tn] <= (1 << 30);
   }
@@ -250,10 +258,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   // |corr| <= 2^30, so acc + corr cannot wrap; with sh <= 19 and an 8-bit z nothing leaves 63 bits.
   const bool fold = p.out_mode == 0 && p.acc_wrap_shift == 0 && !p.rs.half_away && p.rs.z_out >= -256 &&
                     p.rs.z_out <= 255 && __builtin_amdgcn_ballot_w64(!lane_ok) == 0;   // wavefront-uniform
-  int64_t k64[2];
-  int32_t lo_s[2], hi_s[2], s1[2];
+  int64_t k64[TN];
+  int32_t lo_s[TN], hi_s[TN], s1[TN];
 #pragma unroll
-  for (int tn = 0; tn < 2; ++tn) {
+  for (int tn = 0; tn < TN; ++tn) {
     s1[tn] = sh[tn] - 1;
     k64[tn] = (int64_t)corr[tn] * mu[tn] + ((int64_t)1 << (30 + (sh[tn] & 31))) + ((int64_t)p.rs.z_out << (31 + (sh[tn] & 31)));
     lo_s[tn] = clip_lo_before_shift(p.rs.lo_rel + p.rs.z_out, s1[tn] & 31);
@@ -281,23 +289,23 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
     __syncthreads();
     if (tile + tile_step < tile_end) load_tile(tile + tile_step);   // the next tile's loads go out now
 
-    // ---- implicit GEMM: 9 taps x C / 32 steps, 2 AF MFMAs (64 output channels) per step
-    v16i acc[AF][2];
+    // ---- implicit GEMM: 9 taps x C / 32 steps, TN AF MFMAs (32 TN output channels) per step
+    v16i acc[AF][TN];
 #pragma unroll
     for (int f = 0; f < AF; ++f)
 #pragma unroll
-      for (int tn = 0; tn < 2; ++tn)
+      for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[f][tn][r] = 0;
     // Fully unrolled, the fragments of step s + 1 are requested before the matrix instructions of
     // step s are issued, so the LDS latency hides behind them; all offsets of the weight
     // fragments are immediates, a tap costs one address addition per row block.
     {
-      v4i bq[2][2], aq[2][AF];
+      v4i bq[2][TN], aq[2][AF];
       uint32_t a_addr[AF];
       auto fetch = [&](int buf, int tap, int c) {
-        bq[buf][0] = *reinterpret_cast<const v4i*>(s_w + b_base + tap * C + 32 * c);
-        bq[buf][1] = *reinterpret_cast<const v4i*>(s_w + b_base + 32 * wstride + tap * C + 32 * c);
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) bq[buf][tn] = *reinterpret_cast<const v4i*>(s_w + b_base + 32 * tn * wstride + tap * C + 32 * c);
 #pragma unroll
         for (int f = 0; f < AF; ++f) aq[buf][f] = *reinterpret_cast<const v4i*>(s_in + a_addr[f] + 32 * c);
       };
@@ -319,10 +327,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
         }
         __builtin_amdgcn_sched_barrier(0);   // keep the requests ahead of this step's matrix instructions
 #pragma unroll
-        for (int f = 0; f < AF; ++f) {
-          acc[f][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(aq[cur][f], bq[cur][0], acc[f][0], 0, 0, 0);
-          acc[f][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(aq[cur][f], bq[cur][1], acc[f][1], 0, 0, 0);
-        }
+        for (int f = 0; f < AF; ++f)
+#pragma unroll
+          for (int tn = 0; tn < TN; ++tn) acc[f][tn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(aq[cur][f], bq[cur][tn], acc[f][tn], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -335,7 +342,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
       const int64_t obase = (int64_t)b * O * HW + (int64_t)y0 * W + pix0;
       const int left = npix - pix0;                      // (image sizes off a multiple of 16: unaligned stores, fours at the end)
 #pragma unroll
-      for (int tn = 0; tn < 2; ++tn) {
+      for (int tn = 0; tn < TN; ++tn) {
         const int o = o0 + 32 * tn + j;
         if (o >= O || pix0 >= npix) continue;
         const int64_t oo = obase + (int64_t)o * HW;
@@ -407,24 +414,25 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   }
 }
 
-template <int NW, int AF, int NU, int CK>
+template <int NW, int AF, int NU, int CK, int TN>
 hipError_t launch_c3_ck(const C3Params& p, size_t lds, int64_t grid, hipStream_t st) {
   static std::atomic<uint64_t> attr_set{0};
   // the LDS size depends on the geometry, not only on the template arguments: raise the kernel's
   // limit to the CU's 160 KB once, whatever this call needs
-  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(conv3x3_nchw_kernel<NW, AF, NU, CK>), 160 * 1024, attr_set);
+  auto kern = conv3x3_nchw_kernel<NW, AF, NU, CK, TN>;
+  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((conv3x3_nchw_kernel<NW, AF, NU, CK>), dim3((unsigned)grid), dim3(64 * NW), lds, st, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), lds, st, p);
   return hipGetLastError();
 }
 
-template <int NW, int AF, int NU>
+template <int NW, int AF, int NU, int TN>
 hipError_t launch_c3(const C3Params& p, size_t lds, int64_t grid, hipStream_t st) {
   switch (p.C / 32) {
-    case 1: return launch_c3_ck<NW, AF, NU, 1>(p, lds, grid, st);
-    case 2: return launch_c3_ck<NW, AF, NU, 2>(p, lds, grid, st);
-    case 3: return launch_c3_ck<NW, AF, NU, 3>(p, lds, grid, st);
-    default: return launch_c3_ck<NW, AF, NU, 4>(p, lds, grid, st);
+    case 1: return launch_c3_ck<NW, AF, NU, 1, TN>(p, lds, grid, st);
+    case 2: return launch_c3_ck<NW, AF, NU, 2, TN>(p, lds, grid, st);
+    case 3: return launch_c3_ck<NW, AF, NU, 3, TN>(p, lds, grid, st);
+    default: return launch_c3_ck<NW, AF, NU, 4, TN>(p, lds, grid, st);
   }
 }
 
@@ -446,7 +454,6 @@ bool try_qconv3x3_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hi
   p.mult = a.rq.multiplier;
   p.shift = a.rq.shift;
   p.B = cg.B; p.C = cg.C; p.H = cg.H; p.W = cg.W; p.O = cg.O;
-  p.nblk = (cg.O + 63) / 64;
   p.per_channel = a.rq.per_channel;
   p.has_rq = a.has_rq;
   p.acc_wrap_shift = a.acc_wrap_shift;
@@ -455,40 +462,57 @@ bool try_qconv3x3_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hi
   p.pad4 = ((((uint32_t)a.act_zero_point) ^ (a.act_unsigned ? 0x80u : 0u)) & 0xffu) * 0x01010101u;
   p.corr_coef = (a.act_unsigned ? 128 : 0) - a.act_zero_point;
   p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
-  // Tile shapes (wavefronts x 32-pixel row blocks per wavefront).  512 pixels cost the fewest LDS
-  // bytes per matrix instruction (each wavefront owns 64 pixels x 64 channels) and are taken when
-  // they still leave every CU a tile; 256 pixels on eight wavefronts otherwise; 128 pixels on four
-  // where the wider tiles' rows do not fit the LDS.
+  // Tile shapes (wavefronts x 32-pixel row blocks per wavefront) and blocks of 32 or 64 output channels: those with the
+  // least time on the busiest CU, in microseconds: the weights once; per tile the matrix instructions, and staging and
+  // epilogue, which two workgroups on a CU do in each other's shadow.  Blocks of 32 leave less of a last block empty, make
+  // twice the workgroups and need half the weights, 64 and wide tiles read fewer LDS bytes per matrix instruction (us with
+  // 32 and 64: 64 -> 64 on one 56 x 56 image 5.1, 6.9; 32 -> 72 on 28 x 49 x 48 7.9, 13.6; 128 -> 184 on 6 x 74 x 72 17.5,
+  // 21.9; 128 -> 256 on 16 x 56 x 56 26.9, 23.9).
   struct Shape { int nw, af; };
   static const Shape shapes[] = {{8, 2}, {8, 1}, {4, 1}};
   size_t lds = 0;
-  int nu = 0, pick = -1;
+  int nu = 0, pick = -1, tn = 0, per_cu = 1;
   int64_t ntiles = 0;
-  for (int i = 0; i < 3 && pick < 0; ++i) {
-    const int pixels = 32 * shapes[i].nw * shapes[i].af, threads = 64 * shapes[i].nw;
-    p.TR = pixels / cg.W < cg.H ? pixels / cg.W : cg.H;
-    // whole 16-pixel groups per tile where that is possible: 16-byte stores
-    int gran = 16;
-    for (int wv = cg.W; (wv & 1) == 0 && gran > 1; wv >>= 1) gran >>= 1;   // 16 / gcd(W, 16)
-    if (p.TR >= gran) p.TR -= p.TR % gran;
-    p.tiles_per_img = (cg.H + p.TR - 1) / p.TR;
-    ntiles = (int64_t)cg.B * p.tiles_per_img;
-    lds = (size_t)64 * (9 * cg.C + 16) + (size_t)(p.TR + 2) * (cg.W + 2) * (cg.C + 16) + 64 * sizeof(int32_t);
-    nu = ((cg.C / 16) * (p.TR + 2) * (cg.W / 4) + threads - 1) / threads;
-    const bool fits = lds <= 160 * 1024 && nu <= 3 && ntiles < (1ll << 31);
-    if (fits && (i > 0 || ntiles * p.nblk >= 256)) pick = i;
-  }
+  double best = 1e300;
+  for (int i = 0; i < 3; ++i)
+    for (int n = 1; n <= 2; ++n) {
+      const int pixels = 32 * shapes[i].nw * shapes[i].af, threads = 64 * shapes[i].nw, ob = 32 * n;
+      if (i == 2 && pick >= 0) continue;  // (four wavefronts: where the wider tiles' rows do not fit the LDS)
+      int tr = pixels / cg.W < cg.H ? pixels / cg.W : cg.H;
+      // whole 16-pixel groups per tile where that is possible: 16-byte stores
+      int gran = 16;
+      for (int wv = cg.W; (wv & 1) == 0 && gran > 1; wv >>= 1) gran >>= 1;   // 16 / gcd(W, 16)
+      if (tr >= gran) tr -= tr % gran;
+      if (tr < 1) continue;
+      const int tiles_per_img = (cg.H + tr - 1) / tr, nblk = (cg.O + ob - 1) / ob;
+      const int64_t nt = (int64_t)cg.B * tiles_per_img;
+      const size_t need = (size_t)ob * (9 * cg.C + 16) + (size_t)(tr + 2) * (cg.W + 2) * (cg.C + 16) + ob * sizeof(int32_t);
+      const int units = ((cg.C / 16) * (tr + 2) * (cg.W / 4) + threads - 1) / threads;
+      if (need > 160 * 1024 || units > 3 || nt >= (1ll << 31)) continue;
+      // two workgroups on a CU, if the LDS and the registers (as compiled) of both fit it
+      const int regs = 66 + 20 * units + (shapes[i].af == 2 ? (n == 2 ? 68 : 20) : (n == 2 ? 32 : 0));
+      const int together = 2 * need <= 160 * 1024 && (shapes[i].nw == 4 || regs <= 128) ? 2 : 1;
+      const double per = (double)((nt * nblk + 255) / 256);
+      // (fewer row blocks or channels share a fragment: the LDS reads take longer than the matrix instructions)
+      const int mine = shapes[i].af * n;
+      const double lds_bound = mine >= 4 ? 1.0 : mine == 2 ? 1.5 : 2.0;
+      const double matrix = shapes[i].nw * mine * lds_bound * 9.0 * (cg.C / 32) * 8.0 / 2100;
+      const double other = 0.6 + 0.5 * units + 0.2 * mine;
+      const double cost = ob * 9.0 * cg.C / 51200 + per * matrix + (per > together ? per / together : 1.0) * other;
+      if (cost < best) {
+        best = cost;
+        pick = i; tn = n; lds = need; nu = units; ntiles = nt; per_cu = together;
+        p.TR = tr; p.tiles_per_img = tiles_per_img; p.nblk = nblk;
+      }
+    }
   if (pick < 0) return false;
   p.ntiles = (int32_t)ntiles;
-  // persistent workgroups: as many as fit the chip at this LDS size (two per CU at most), shared
-  // out evenly among the blocks of output channels
-  const int fit = (int)((160 * 1024) / lds);
-  const int per_cu = fit > 2 ? 2 : fit;
+  // persistent workgroups, as many as fit the chip, shared out evenly among the blocks of output channels
   int64_t per_blk = (256ll * per_cu) / p.nblk;
   if (per_blk < 1) per_blk = 1;
   if (per_blk > ntiles) per_blk = ntiles;
   const int64_t grid = per_blk * p.nblk;
-#define HAGO_C3(I, NWV, AFV, NUV) if (pick == I && nu == NUV) { *err = launch_c3<NWV, AFV, NUV>(p, lds, grid, st); return true; }
+#define HAGO_C3(I, NWV, AFV, NUV) if (pick == I && nu == NUV) { *err = tn == 1 ? launch_c3<NWV, AFV, NUV, 1>(p, lds, grid, st) : launch_c3<NWV, AFV, NUV, 2>(p, lds, grid, st); return true; }
   HAGO_C3(0, 8, 2, 1) HAGO_C3(0, 8, 2, 2) HAGO_C3(0, 8, 2, 3)
   HAGO_C3(1, 8, 1, 1) HAGO_C3(1, 8, 1, 2) HAGO_C3(1, 8, 1, 3)
   HAGO_C3(2, 4, 1, 1) HAGO_C3(2, 4, 1, 2) HAGO_C3(2, 4, 1, 3)
