@@ -277,7 +277,8 @@ hipError_t launch_shape(const CgParams& p, int mode, hipStream_t st) {
   return hipGetLastError();
 }
 
-// ---- NCHW.  The 16 reduction elements of a lane (k = (c, ky, kx), in the order of the weights) are 16 bytes at 16 places,
+// ---- NCHW, and channel-last of fewer than 16 channels.  The 16 reduction elements of a lane (k = (c, ky, kx), or
+// (ky, kx, c): the order of the weights) are 16 bytes at 16 places,
 // loaded one by one: neighbouring lanes are neighbouring pixels, so a byte load of a wavefront touches two or three lines.
 // What an element adds to the address of a pixel's window is the same for every lane of a half, and comes with its tap's
 // number from a table in LDS (26 and 6 bits) that the workgroup builds once; whether the tap is inside the image is bit 63 of a mask of
@@ -294,9 +295,10 @@ struct CnParams {
   const int32_t* mult;
   const int32_t* shift;
   int32_t B, C, H, W, N, OW, OHW, KH, KW, sh, sw, ph, pw;
-  int32_t K, taps, steps;
+  int32_t K, steps, nhwc;
+  uint32_t minor;                               // inner extent of the reduction: taps (NCHW) or C
   int32_t tiles_per_img, tiles, nblocks;        // pixel tiles; blocks of output channels
-  uint32_t inv_tpi, inv_ow, inv_taps, inv_kw;   // as above
+  uint32_t inv_tpi, inv_ow, inv_minor, inv_kw;   // as above
   uint32_t x4, zbyte;                           // sign flip of uint8 bytes; the zero point's byte as stored
   int32_t corr_coef, per_channel, acc_wrap_shift;
   RequantScalars rs;
@@ -320,9 +322,11 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_gather_nchw_kerne
 
   // the table
   for (int k = threadIdx.x; k < p.steps * 32; k += 64 * NW) {
-    const uint32_t c = div_by((uint32_t)k, (uint32_t)p.taps, p.inv_taps), tap = (uint32_t)k - c * (uint32_t)p.taps;
+    const uint32_t major = div_by((uint32_t)k, p.minor, p.inv_minor), minor = (uint32_t)k - major * p.minor;
+    const uint32_t c = p.nhwc ? minor : major, tap = p.nhwc ? major : minor;
     const uint32_t ky = div_by(tap, (uint32_t)p.KW, p.inv_kw), kx = tap - ky * (uint32_t)p.KW;
-    s_tab[k] = k < K ? ((c * (uint32_t)p.H + ky) * (uint32_t)p.W + kx) << 6 | (63 - tap) : 0u;
+    const uint32_t at = p.nhwc ? (ky * (uint32_t)p.W + kx) * (uint32_t)p.C + c : (c * (uint32_t)p.H + ky) * (uint32_t)p.W + kx;
+    s_tab[k] = k < K ? at << 6 | (63 - tap) : 0u;
   }
 
   // this wavefront's steps and their weights
@@ -418,7 +422,7 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_gather_nchw_kerne
     const int m = pix0 + channel_of_row(n);  // (registers are 16 consecutive pixels)
     const uint32_t oy = div_by((uint32_t)m, (uint32_t)p.OW, p.inv_ow);
     const int iy = (int)oy * p.sh - p.ph, ix = (m - (int)oy * p.OW) * p.sw - p.pw;
-    const uint32_t base = (uint32_t)(iy * p.W + ix);
+    const uint32_t base = (uint32_t)(iy * p.W + ix) * (p.nhwc ? (uint32_t)p.C : 1u);
     const int xl = ix < 0 ? -ix : 0, xr = p.W - ix < p.KW ? p.W - ix : p.KW;  // columns xl .. xr - 1 of the filter are inside
     const uint64_t cols = xl < xr ? ((1ull << xr) - 1) & ~((1ull << xl) - 1) : 0;
     uint64_t missing = 0;  // bit: tap outside the image; bit 63: elements beyond K
@@ -510,6 +514,20 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_gather_nchw_kerne
         }
       }
       if (ch >= p.N || px >= p.OHW) return;
+      if (p.nhwc) {  // uniform; a pixel's channels lie across the lanes
+        uint8_t* o = static_cast<uint8_t*>(p.out) + (((int64_t)b * p.OHW + px) * p.N + ch) * kEsz;
+#pragma unroll
+        for (int u = 0; u < UPW; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (px + 4 * u + e >= p.OHW) continue;
+            uint8_t* at = o + (int64_t)(4 * u + e) * p.N * kEsz;
+            if constexpr (MODE == 0) *at = (uint8_t)v[u][e];
+            else if constexpr (MODE == 1) *reinterpret_cast<int32_t*>(at) = v[u][e];
+            else *reinterpret_cast<int16_t*>(at) = (int16_t)v[u][e];
+          }
+        return;
+      }
       uint8_t* o = static_cast<uint8_t*>(p.out) + (((int64_t)b * p.N + ch) * p.OHW + px) * kEsz;
       if (px + 4 * UPW <= p.OHW) {
         if constexpr (MODE == 0) {
@@ -595,7 +613,7 @@ hipError_t launch_nchw(const CnParams& p, int mode, hipStream_t st) {
 
 // Returns false (and launches nothing) when the geometry is not this kernel's, or another kernel is the better one.
 // forced_shape: 0 64 pixels x 64 output channels by four wavefronts, 1 the same by eight, 2 32 x 32 by four; -1 by size.
-bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, int forced_shape, hipStream_t st, hipError_t* err) {
+bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err) {
   const int64_t act_bytes = (int64_t)cg.B * cg.C * cg.H * cg.W, wgt_bytes = (int64_t)cg.O * a.K;
   if (!cg.nhwc || cg.C < 16 || cg.KH > 32 || cg.KW > 32 || act_bytes >= (1ll << 31) || wgt_bytes >= (1ll << 31)) return false;
   CgParams p{};
@@ -625,7 +643,7 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, int forced_shape, h
   p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
   const int mode = a.has_rq ? 0 : (a.acc16 ? 2 : 1);
   // Microseconds.  Here: 3 and, per CU, 0.042 (about 100 cycles of the memory pipe) for every operand load of a tile, nearly
-  // twice that where they are unaligned (the other kernels lose 1.6 there); a step of 64 x 64 is four loads, of 32 x 32 two.  The other kernels: 6 and their
+  // twice that where they are unaligned (the one-launch kernel loses 1.6 there); a step of 64 x 64 is four loads, of 32 x 32 two.  The other kernels: 6 and their
   // rate, or the length of the reduction where there are few tiles.  Measured (here, other): 16 x 28 x 28 64 -> 64 3x3 5.4,
   // 8.4; one image 3.9, 7.1; 32 x 14 x 14 128 -> 128 8.4, 12.0; 8 x 56 x 56 64 -> 128 stride 2 5.8, 10.4; 57 x 56
   // 224 -> 224 7x7 stride 2 31, 66; 4 x 40 x 40 100 -> 200 1x1 stride 2 3.9, 7.8; but 32 x 28 x 28 128 -> 128 22.7, 15.1.
@@ -636,7 +654,7 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, int forced_shape, h
   int shape = forced_shape;
   if (shape < 0) {
     const double rate = (double)a.M * a.N * a.K / 0.41e9, length = (double)a.K / 256;
-    if ((t64 < t32 ? t64 : t32) >= (6.0 + (rate > length ? rate : length)) * (cg.C % 4 ? 1.6 : 1.0)) return false;
+    if ((t64 < t32 ? t64 : t32) >= (6.0 + (rate > length ? rate : length)) * (cg.C % 4 && !has_workspace ? 1.6 : 1.0)) return false;
     shape = t32 < t64 ? 2 : tiles(64) <= 256;  // (eight wavefronts fill a CU's LDS)
   }
   switch (shape) {
@@ -647,12 +665,12 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, int forced_shape, h
   return true;
 }
 
-// The same for NCHW, any channel count.  forced_shape, pixels x output channels: 0 32 x 32 by eight wavefronts, 1 32 x 64 by
+// The same for NCHW, any channel count, and for channel-last of fewer than 16 channels.  forced_shape, pixels x output channels: 0 32 x 32 by eight wavefronts, 1 32 x 64 by
 // four, 2 32 x 32 by four, 3 32 x 64 by one; -1 by size.
 bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err) {
   const int64_t img = (int64_t)cg.C * cg.H * cg.W;
   const int64_t ohw = (int64_t)cg.OH * cg.OW;
-  if (cg.nhwc || cg.KH * cg.KW > 63 || a.K > 28000 || img >= (1ll << 26) || (int64_t)cg.O * a.K >= (1ll << 31) ||
+  if ((cg.nhwc && cg.C >= 16) || cg.KH * cg.KW > 63 || a.K > 28000 || img >= (1ll << 26) || (int64_t)cg.O * a.K >= (1ll << 31) ||
       (int64_t)cg.B * ((ohw + 31) / 32) >= (1ll << 30))
     return false;
   CnParams p{};
@@ -665,12 +683,14 @@ bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_works
   p.B = cg.B; p.C = cg.C; p.H = cg.H; p.W = cg.W; p.N = cg.O; p.OW = cg.OW; p.OHW = (int32_t)ohw;
   p.KH = cg.KH; p.KW = cg.KW; p.sh = cg.stride_h; p.sw = cg.stride_w; p.ph = cg.pad_h; p.pw = cg.pad_w;
   p.K = a.K;
-  p.taps = cg.KH * cg.KW;
+  const int taps = cg.KH * cg.KW;
+  p.nhwc = cg.nhwc;
+  p.minor = (uint32_t)(cg.nhwc ? cg.C : taps);
   p.steps = (a.K + 31) / 32;
   auto inverse = [](int64_t d, int64_t n) { return d > 1 && n * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d) : 0u; };
   p.inv_ow = inverse(cg.OW, ohw + 64);
-  p.inv_taps = inverse(p.taps, a.K + 32);
-  p.inv_kw = inverse(cg.KW, p.taps);
+  p.inv_minor = inverse(p.minor, a.K + 32);
+  p.inv_kw = inverse(cg.KW, taps + 32);
   p.x4 = a.act_unsigned ? 0x80808080u : 0u;
   p.zbyte = (uint32_t)a.act_zero_point & 0xffu;
   p.corr_coef = (a.act_unsigned ? 128 : 0) - a.act_zero_point;
@@ -681,7 +701,7 @@ bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_works
   p.tiles_per_img = (int32_t)((ohw + 31) / 32);
   p.tiles = cg.B * p.tiles_per_img;
   p.inv_tpi = inverse(p.tiles_per_img, p.tiles);
-  // Microseconds: 3.8 and, per CU, 0.4 for every tile and 0.11 (32 channels) or 0.13 (64) for every step, nearly twice that
+  // Microseconds: 3.8 and, per CU, 0.4 for every tile and 0.12 (32 channels) or 0.15 (64) for every step, nearly twice that
   // where neighbouring pixels are not neighbouring bytes; long reductions lose more, as a wavefront has two steps' loads
   // under way.  The other kernels: 8.5 and their rate and the length of the reduction (which costs the one-launch
   // kernel more for filters other than 3x3, and is its only cost without a workspace).  Measured (here, other): 5 x 38 x 38 13 -> 42 5x5 6.7, 14.2; 16 x 25 x 26 132 -> 137 1x1 stride 2 5.9,
@@ -689,12 +709,14 @@ bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_works
   // 64 x 32 x 32 3 -> 16 6.6, 8.6.
   const double step = cg.stride_w > 1 ? 1.8 * p.steps : (double)p.steps;
   const double r32 = (double)p.tiles * ((a.N + 31) / 32) / 256, r64 = (double)p.tiles * ((a.N + 63) / 64) / 256;
-  const double t32 = (r32 > 1 ? r32 : 1.0) * (0.4 + 0.11 * step), t64 = (r64 > 1 ? r64 : 1.0) * (0.4 + 0.13 * step);
+  const double t32 = (r32 > 1 ? r32 : 1.0) * (0.4 + 0.12 * step), t64 = (r64 > 1 ? r64 : 1.0) * (0.4 + 0.15 * step);
   const bool alone = p.steps <= 2 && r64 >= 4;
   int shape = forced_shape;
   if (shape < 0) {
-    const double t = 3.8 + (alone ? 0.35 * r64 : t32 < t64 ? t32 : t64) + (p.steps > 18 ? 0.1 * (p.steps - 18) : 0.0);
-    if (t >= 8.5 + (double)a.M * a.N * a.K / 0.41e9 + (double)a.K / (has_workspace || p.taps == 9 || p.taps == 1 ? 450 : 70)) return false;
+    // (results leave in 16-byte pieces of different channels' planes; channel-last one element per lane and store)
+    const double t = 3.8 + (double)a.M * a.N * (cg.nhwc ? 2.4 : mode == 0 ? 1 : mode == 1 ? 4 : 2) / 1.2e6 + (alone ? 0.35 * r64 : t32 < t64 ? t32 : t64) + (p.steps > 18 ? 0.1 * (p.steps - 18) : 0.0);
+    const double base = has_workspace && (cg.nhwc || cg.W % 4 == 0) ? 7.5 : 8.5;  // (the rewrite is fast there)
+    if (t >= base + (double)a.M * a.N * a.K / 0.41e9 + (double)a.K / (has_workspace || taps == 9 || taps == 1 ? 450 : 70)) return false;
     shape = alone ? 3 : t64 < t32 ? 1 : p.steps >= 24 && r32 <= 1 ? 0 : 2;
   }
   switch (shape) {
