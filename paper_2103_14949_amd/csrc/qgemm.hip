@@ -550,6 +550,7 @@ hipError_t launch_qconv_gemm(const GemmArgs& a, const ConvGeom& cg, void* ws, bo
     //   few channels, 1x1               3 -> 64 7x7 at 224 x 224: 26, 14;  64 -> 128 1x1 stride 2: 12, 7.4
     //   3x3 up to 128 channels, NCHW    64 -> 128 stride 2: 14.2, 10.5;  40 -> 45 at 42 x 41: 15, 10.6;  256 -> 256: 17, 20
     //   the same, whole dwords a row    the rewrite is faster there: 114 -> 31 stride 2 at 44 x 44 15.2, 16.5;  64 -> 31 11, 8.7
+    //   (and on small maps: 90 -> 65 stride 2 at 13 x 14 11.7, 13.6)
     //   few channels, NCHW, whole dwords a row, more than one block of output channels: 6 -> 232 5x5 at 76 x 76 19.6, 28
     //   few channels, NHWC              10 -> 200 stride 2 at 50 x 50 12.0, 16.1;  12 -> 48 5x5 10.0, 12.5;  but 6 -> 94 7x7
     //                                   stride 2 at 109 x 106 23, 14.7: long filters, or a copy that is large padded to 16
@@ -560,7 +561,7 @@ hipError_t launch_qconv_gemm(const GemmArgs& a, const ConvGeom& cg, void* ws, bo
     const bool one_launch =
         cg.C <= 16 ? taps == 1 || pixels * 16 >= (3 << 20) || (cg.nhwc ? cg.C <= 8 && taps >= 25 && a.M >= 20000 : cg.W % 4 != 0 || cg.O <= 64)
         : taps == 1 || (taps <= 9 && (cg.nhwc ? cg.C <= 128 && (cg.C % 16 != 0 || pixels * cg.C >= (3 << 20))
-                                              : cg.C <= (cg.W % 4 == 0 ? 96 : 128)));
+                                              : cg.C <= 64 || (cg.W % 4 == 0 ? cg.C <= 96 : cg.C <= 128 && pixels * cg.C >= (3 << 19))));
     if (path == 0 && one_launch && try_qconv_direct(a, cg, -1, st, &err)) return err;
     return conv_dma(a, cg, ws, weights_ready, st);
   }
