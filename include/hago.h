@@ -96,7 +96,9 @@ typedef enum {
 #define HAGO_WS_WEIGHTS_READY 2u /* hago_qconv2d_ws only: the workspace still
                                 holds this layer's rewritten weights from an
                                 earlier call with the same w, geometry and
-                                workspace; only the activations are rewritten */
+                                workspace; only the activations are rewritten.
+                                B, the output, the accumulator, bias, rq and
+                                the activations may differ between the two */
 
 /* A quantized tensor type: container, effective bit count, signedness of the
  * effective range, zero point.  `bits` is a CONTRACT on the value range
@@ -220,9 +222,11 @@ hago_status hago_qconv2d(const void* a, hago_qtype a_t, const void* w,
  * elements per lane, so a groups == 1 convolution first rewrites, in one
  * launch, the activations into a padded channel-last int8 copy and the
  * weights into [O][KH*KW][C rounded up to 16] inside `workspace`, then runs
- * the implicit GEMM over the copies.  (Geometries for which hago_qconv2d has
- * a kernel of its own that is at least as fast run that kernel here too and
- * leave the workspace untouched.)
+ * the implicit GEMM over the copies.  (Calls for which hago_qconv2d has a
+ * kernel that is at least as fast run that kernel here too.  Without
+ * HAGO_WS_WEIGHTS_READY they still write the weight part, except in 1x1 and
+ * NCHW 3x3 layers that have a kernel of their own: those leave the workspace
+ * untouched and never read weights that an earlier call left there.)
  *   hago_qconv2d_workspace_bytes  (host only, launches nothing): bytes this
  *     geometry wants; 0 when it runs without scratch (depthwise, or shapes
  *     only the general kernel indexes); -1 for arguments hago_qconv2d would
@@ -234,8 +238,9 @@ hago_status hago_qconv2d(const void* a, hago_qtype a_t, const void* w,
  *     keeps no pointer to it after the call's work has run.  Calls that share
  *     one workspace must be ordered on one stream; calls with distinct
  *     workspaces may overlap freely.  With HAGO_WS_WEIGHTS_READY the weight
- *     part is taken as written by an earlier call (weights are constants of a
- *     layer) and only the activations are rewritten.
+ *     part is taken as written by an earlier call without the flag (weights
+ *     are constants of a layer) and only the activations are rewritten; a call
+ *     whose count is 0 (B == 0 among them) writes none.
  * Results are identical to hago_qconv2d's.  Errors as for hago_qconv2d;
  * additionally NULL (workspace needed but NULL) and PARAM (workspace too
  * small, misaligned, or negative size).

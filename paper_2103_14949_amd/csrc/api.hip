@@ -436,7 +436,10 @@ hago_status qconv2d_impl(const void* a, hago_qtype a_t, const void* w, hago_qtyp
       if (hago::static_scratch(&ws, &cap) != hipSuccess) return HAGO_ERR_DEVICE;
     }
   }
-  return from_hip(hago::launch_qconv_gemm(g, cg, ws, (flags & HAGO_WS_WEIGHTS_READY) != 0, st));
+  // (a static scratch array serves every layer: no call may count on another's weights)
+  const hago::WsWeights weights = mode != Scratch::kCaller ? hago::WsWeights::kScratch
+                                  : (flags & HAGO_WS_WEIGHTS_READY) ? hago::WsWeights::kReady : hago::WsWeights::kKeep;
+  return from_hip(hago::launch_qconv_gemm(g, cg, ws, weights, st));
 }
 
 }  // namespace

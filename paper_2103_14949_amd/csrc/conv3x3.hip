@@ -438,12 +438,15 @@ hipError_t launch_c3(const C3Params& p, size_t lds, int64_t grid, hipStream_t st
 
 }  // namespace
 
+bool is_qconv3x3_nchw(const ConvGeom& cg) {
+  return !cg.nhwc && cg.KH == 3 && cg.KW == 3 && cg.stride_h == 1 && cg.stride_w == 1 && cg.pad_h == 1 && cg.pad_w == 1 &&
+         cg.C % 32 == 0 && cg.C <= 128 && cg.W % 4 == 0 && cg.W <= 128;
+}
+
 // Takes NCHW 3x3 stride-1 pad-1 convolutions with C a multiple of 32 up to 128, W a multiple of 4
 // up to 128 and 4-byte aligned activations; returns false (nothing launched) for anything else.
 bool try_qconv3x3_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hipError_t* err) {
-  if (cg.nhwc || cg.KH != 3 || cg.KW != 3 || cg.stride_h != 1 || cg.stride_w != 1 || cg.pad_h != 1 ||
-      cg.pad_w != 1 || cg.C % 32 != 0 || cg.C > 128 || cg.W % 4 != 0 || cg.W > 128 ||
-      (reinterpret_cast<uintptr_t>(a.act) & 3u) != 0 || (int64_t)cg.B * cg.C * cg.H * cg.W >= (1ll << 31) ||
+  if (!is_qconv3x3_nchw(cg) || (reinterpret_cast<uintptr_t>(a.act) & 3u) != 0 || (int64_t)cg.B * cg.C * cg.H * cg.W >= (1ll << 31) ||
       (int64_t)cg.B * cg.O * cg.H * cg.W >= (1ll << 31))
     return false;
   C3Params p{};

@@ -254,4 +254,15 @@ hipError_t launch_conv_prepack(const GemmArgs& a, const ConvGeom& cg, int32_t Cp
   return hipGetLastError();
 }
 
+hipError_t launch_conv_prepack_weights(const GemmArgs& a, const ConvGeom& cg, int32_t Cp, int8_t* wgt_out, hipStream_t st) {
+  PrepackArgs p{};
+  p.wgt = a.wgt;
+  p.wgt_out = wgt_out;
+  p.C = cg.C; p.O = cg.O; p.KH = cg.KH; p.KW = cg.KW; p.Cp = Cp;
+  p.nhwc = cg.nhwc;
+  p.wgt_chunks = (int64_t)p.O * p.KH * p.KW * (Cp / 16);
+  hipLaunchKernelGGL(conv_prepack_kernel, dim3((unsigned)((p.wgt_chunks + 255) / 256)), dim3(256), 0, st, p);
+  return hipGetLastError();
+}
+
 }  // namespace hago

@@ -99,21 +99,29 @@ int64_t qconv_workspace_bytes(const ConvGeom& cg);
 // Implicit-GEMM convolution, groups == 1.  ws: device scratch of at least
 // qconv_workspace_bytes(cg) bytes, 256-byte aligned, or nullptr (then, unless one of the
 // scratch-free special kernels takes the geometry, the generic register-staged kernel runs).
-// weights_ready: the weight part of ws already holds this call's weights (same tensor, same
-// geometry), so only the activations are rewritten.
-hipError_t launch_qconv_gemm(const GemmArgs& g, const ConvGeom& cg, void* ws, bool weights_ready,
-                             hipStream_t st);
+// weights: what becomes of the weight part of ws (HAGO_WS_WEIGHTS_READY).
+enum class WsWeights {
+  kScratch,  // no later call reads it
+  kKeep,     // a later call may say kReady: it holds this call's weights afterwards, whichever kernel ran
+  kReady     // an earlier call with the same weights and geometry (the batch aside) said kKeep
+};
+hipError_t launch_qconv_gemm(const GemmArgs& g, const ConvGeom& cg, void* ws, WsWeights weights, hipStream_t st);
 // The library's fixed scratch array on the current device (static device memory: nothing is
 // allocated or freed, the address never changes) and its capacity in bytes.
 hipError_t static_scratch(void** ptr, int64_t* capacity);
 hipError_t launch_conv_prepack(const GemmArgs& g, const ConvGeom& cg, int32_t Cp, uint8_t* act_out,
                                int8_t* wgt_out, bool skip_weights, hipStream_t st);
+// The weight part alone.
+hipError_t launch_conv_prepack_weights(const GemmArgs& g, const ConvGeom& cg, int32_t Cp, int8_t* wgt_out, hipStream_t st);
 // Test hooks (see hago_set_test_hook): which GEMM kernel family and tile serve the next calls.
 enum { kHookGemmPath = 0, kHookDmaTile = 1, kHookGenericTile = 2, kNumHooks = 3 };
 void set_test_hook(int key, int value);
 // 3x3 stride-1 pad-1 NCHW convolution in one launch, no scratch; false when the geometry is not
 // that kernel's (nothing is launched then).
 bool try_qconv3x3_nchw(const GemmArgs& g, const ConvGeom& cg, hipStream_t st, hipError_t* err);
+// Whether a layer is of that kernel's kind, from its geometry without the batch: its calls run there unless their
+// activations are misaligned.
+bool is_qconv3x3_nchw(const ConvGeom& cg);
 // Convolution of any geometry in one launch, no scratch; forced_shape >= 0: that wavefront shape (tests).  False when the
 // geometry is not that kernel's (nothing is launched then).
 bool try_qconv_direct(const GemmArgs& g, const ConvGeom& cg, int forced_shape, hipStream_t st, hipError_t* err);
@@ -124,6 +132,8 @@ bool try_qconv_gather_nchw(const GemmArgs& g, const ConvGeom& cg, bool has_works
 // 1x1 stride-1 unpadded NCHW convolution straight from the caller's buffers; false when the
 // geometry is not that kernel's (nothing is launched then).
 bool try_qconv_pointwise_nchw(const GemmArgs& g, const ConvGeom& cg, hipStream_t st, hipError_t* err);
+// The same question as is_qconv3x3_nchw: here all calls but those with 24-bit accumulators.
+bool is_qconv_pointwise_nchw(const ConvGeom& cg);
 // depthwise convolution (groups == C == O), no MFMA.
 hipError_t launch_qconv_depthwise(const GemmArgs& g, const ConvGeom& cg, hipStream_t st);
 

@@ -366,12 +366,16 @@ hipError_t launch(PwArgs q, hipStream_t st) {
 
 }  // namespace
 
+bool is_qconv_pointwise_nchw(const ConvGeom& cg) {
+  return !cg.nhwc && cg.KH == 1 && cg.KW == 1 && cg.stride_h == 1 && cg.stride_w == 1 && cg.pad_h == 0 && cg.pad_w == 0 &&
+         cg.C % 4 == 0 && (int64_t)cg.H * cg.W >= 4;
+}
+
 // Returns false (and launches nothing) when the geometry is not this kernel's.
 bool try_qconv_pointwise_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hipError_t* err) {
   const int64_t HW = (int64_t)cg.H * cg.W;
   if (a.acc_wrap_shift != 0 && a.acc_wrap_shift != 16) return false;  // 24-bit accumulators: the general path
-  if (cg.nhwc || cg.KH != 1 || cg.KW != 1 || cg.stride_h != 1 || cg.stride_w != 1 || cg.pad_h != 0 || cg.pad_w != 0 ||
-      cg.C % 4 != 0 || HW < 4 || (int64_t)cg.C * HW >= (1ll << 31) || (int64_t)cg.O * cg.C >= (1ll << 31) ||
+  if (!is_qconv_pointwise_nchw(cg) || (int64_t)cg.C * HW >= (1ll << 31) || (int64_t)cg.O * cg.C >= (1ll << 31) ||
       cg.B * ((HW + 127) / 128) * ((cg.O + 31) / 32) >= (1ll << 31))
     return false;
   PwArgs p{};

@@ -522,18 +522,18 @@ static hipError_t conv_dma(const GemmArgs& a, const ConvGeom& cg, void* ws, bool
   return launch_qconv_dma(p, !cg.nhwc, st);
 }
 
-hipError_t launch_qconv_gemm(const GemmArgs& a, const ConvGeom& cg, void* ws, bool weights_ready,
-                             hipStream_t st) {
-  if (a.M == 0 || a.N == 0) return hipSuccess;
-  if (a.operand16) return launch_qconv16(a, cg, st);
+// A channel-last 1x1 stride-1 unpadded convolution is a dense layer over the pixels.
+static bool is_dense_nhwc(const ConvGeom& cg) {
+  return cg.nhwc && cg.KH == 1 && cg.KW == 1 && cg.stride_h == 1 && cg.stride_w == 1 && cg.pad_h == 0 && cg.pad_w == 0;
+}
+
+// The kernel for the call; *in_workspace: it reads the operands' copies, which ws holds afterwards.
+static hipError_t launch_qconv_chosen(const GemmArgs& a, const ConvGeom& cg, void* ws, bool weights_ready, int path,
+                                      bool* in_workspace, hipStream_t st) {
   hipError_t err = hipSuccess;
-  const int path = g_hook[kHookGemmPath].load(std::memory_order_relaxed);  // 1 / 2: skip the special cases
   if (path == 0) {
     if (try_qconv_pointwise_nchw(a, cg, st, &err)) return err;
-    // channel-last 1x1 stride-1 unpadded convolution is a dense layer over the pixels
-    if (cg.nhwc && cg.KH == 1 && cg.KW == 1 && cg.stride_h == 1 && cg.stride_w == 1 && cg.pad_h == 0 &&
-        cg.pad_w == 0)
-      return launch_qdense(a, st);
+    if (is_dense_nhwc(cg)) return launch_qdense(a, st);
     // 3x3 stride 1 over NCHW: one launch that transposes the tensor on its way into the LDS
     // (faster than rewriting it through the workspace first, and it needs none)
     if (try_qconv3x3_nchw(a, cg, st, &err)) return err;
@@ -563,6 +563,7 @@ hipError_t launch_qconv_gemm(const GemmArgs& a, const ConvGeom& cg, void* ws, bo
         : taps == 1 || (taps <= 9 && (cg.nhwc ? cg.C <= 128 && (cg.C % 16 != 0 || pixels * cg.C >= (3 << 20))
                                               : cg.C <= 64 || (cg.W % 4 == 0 ? cg.C <= 96 : cg.C <= 128 && pixels * cg.C >= (3 << 19))));
     if (path == 0 && one_launch && try_qconv_direct(a, cg, -1, st, &err)) return err;
+    *in_workspace = true;
     return conv_dma(a, cg, ws, weights_ready, st);
   }
   if (path == 0 && try_qconv_direct(a, cg, -1, st, &err)) return err;
@@ -575,6 +576,25 @@ hipError_t launch_qconv_gemm(const GemmArgs& a, const ConvGeom& cg, void* ws, bo
   p.vec_k = (a.K % 16 == 0) && ptr_aligned(a.wgt, 16);
   p.vec_out = ((cg.OH * cg.OW) % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
   return launch_shape<MODE_CONV_NCHW>(pick_shape(MODE_CONV_NCHW, a.M, a.N, a.K), p, st);
+}
+
+// Which kernel serves a call depends on its batch, output type, accumulator and alignment; what a later kReady call may
+// find in ws must not.  So the layers fall in two classes by their geometry without the batch.  Those with a kernel of
+// their own never read kept weights: a call of theirs that has to go through ws (misaligned, 24-bit accumulators) rewrites
+// them with its activations, in the same launch.  For every other layer a kKeep call leaves the weights in ws, with a
+// launch of their own (2.8 us; 5 us for the 2.4 MB of 512 -> 512 3x3) where the kernel that served it reads the caller's
+// tensors; the calls with the flag pay nothing for it.
+hipError_t launch_qconv_gemm(const GemmArgs& a, const ConvGeom& cg, void* ws, WsWeights weights, hipStream_t st) {
+  if (a.M == 0 || a.N == 0) return hipSuccess;
+  if (a.operand16) return launch_qconv16(a, cg, st);
+  const int path = g_hook[kHookGemmPath].load(std::memory_order_relaxed);  // 1 / 2: skip the special cases
+  const bool own_kernel = is_qconv_pointwise_nchw(cg) || is_dense_nhwc(cg) || is_qconv3x3_nchw(cg);
+  bool in_workspace = false;
+  const hipError_t err =
+      launch_qconv_chosen(a, cg, ws, weights == WsWeights::kReady && !own_kernel, path, &in_workspace, st);
+  // (path 1 is the kernel without a workspace)
+  if (err != hipSuccess || weights != WsWeights::kKeep || !ws || in_workspace || own_kernel || path == 1) return err;
+  return launch_conv_prepack_weights(a, cg, (cg.C + 15) / 16 * 16, static_cast<int8_t*>(ws), st);
 }
 
 }  // namespace hago

@@ -1,0 +1,62 @@
+"""HAGO_WS_WEIGHTS_READY: after one call without the flag, a call with it may differ in batch, output, accumulator and
+alignment, and so run another kernel than the first one did."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import *  # noqa: E402,F401,F403
+from paper_2103_14949_amd import datagen
+
+OUT = {"rq": (hago.I32, True), "raw": (hago.I32, False), "i16": (hago.I16, False), "i24": (hago.I24, False)}
+REF_ACC = {hago.I32: ref.I32, hago.I16: ref.I16, hago.I24: ref.I24}
+
+# layout C H W O k stride; then (batch, output, byte offset of the activations) of the first and of the flagged call
+CASES = [
+    ("nchw", 128, 13, 13, 200, 3, 1, (8, "rq", 0), (8, "raw", 0)),      # the output type decides the kernel
+    ("nhwc", 256, 14, 14, 256, 3, 1, (8, "rq", 0), (16, "rq", 0)),      # the batch decides it
+    ("nhwc", 128, 28, 28, 128, 3, 1, (8, "rq", 0), (16, "rq", 0)),
+    ("nchw", 128, 28, 28, 128, 3, 1, (1, "rq", 0), (16, "raw", 1)),     # the alignment
+    ("nchw", 64, 20, 20, 96, 1, 1, (2, "rq", 0), (2, "i24", 0)),        # the accumulator
+    ("nhwc", 64, 28, 28, 64, 3, 1, (16, "raw", 0), (1, "rq", 0)),
+    ("nchw", 40, 21, 20, 45, 5, 2, (2, "i16", 0), (3, "rq", 3)),
+    ("nhwc", 3, 19, 23, 24, 7, 2, (1, "rq", 0), (4, "raw", 0)),
+    ("nhwc", 48, 9, 8, 40, 1, 1, (3, "rq", 0), (5, "i16", 1)),
+]
+
+
+def _at(a, offset):
+    """A device copy of `a` that starts `offset` bytes into an allocation."""
+    raw = torch.empty(a.size + offset, dtype=torch.uint8, device=DEV)
+    raw[offset:].copy_(torch.from_numpy(a.view(np.uint8).reshape(-1)))
+    t = raw[offset:].view(torch.uint8 if a.dtype == np.uint8 else torch.int8).view(a.shape)
+    assert t.data_ptr() % 4 == offset % 4
+    return t
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("path", [0, 2, 4])   # the flagged call: as chosen, through the workspace, gathered
+def test_weights_kept_across_kernels(case, path, gemm_path):
+    layout, C, H, W, O, k, stride, first, second = case
+    rng = np.random.default_rng(C * 1000 + O)
+    to = (lambda x: x) if layout == "nchw" else (lambda x: np.ascontiguousarray(x.transpose(0, 2, 3, 1)))
+    lay_g, lay_r = (hago.NCHW, ref.NCHW) if layout == "nchw" else (hago.NHWC, ref.NHWC)
+    w = to(rng.integers(-127, 128, (O, C, k, k)).astype(np.int8))
+    bias = rng.integers(-10 ** 5, 10 ** 5, O).astype(np.int32)
+    mult, shift = datagen.requant_params(rng, np.full(O, 74.0 * 73.0 * k * np.sqrt(C)), 40.0)
+    st, pad = (stride, stride), (k // 2, k // 2)
+    dw, db = dev(w), dev(bias)
+    shapes = [to(np.zeros((b, C, H, W), np.uint8)).shape for b, _, _ in (first, second)]
+    need = max(hago.qconv2d_workspace_bytes(s, w.shape, lay_g, st, pad) for s in shapes)
+    ws = torch.full((need,), 0xA5, dtype=torch.uint8, device=DEV)
+    for (B, out, offset), flags in ((first, 0), (second, hago.WS_WEIGHTS_READY)):
+        a = to(rng.integers(0, 256, (B, C, H, W)).astype(np.uint8))
+        acc, requantized = OUT[out]
+        if flags:
+            gemm_path(path)
+        got = host(hago.qconv2d(_at(a, offset), act_qtype(a, 131), dw, hago.QType(hago.I8), db, lay_g, st, pad, 1, acc,
+                                gpu_requant(mult, shift) if requantized else None, flags=flags, workspace=ws))
+        pick = sorted({0, B - 1})   # images are independent: the oracle does the first and the last
+        want = ref.qconv2d(a[pick], 131, w, bias, lay_r, st, pad, 1, REF_ACC[acc],
+                           ref_requant(mult, shift) if requantized else None)
+        assert_same(got[pick], want, f"{'flagged' if flags else 'first'} call, path {path}")
