@@ -120,7 +120,13 @@ MaybeRequant requant(PyObject* o) {
   auto ptr_of = [&](PyObject* name) {
     PyObject* v = PyObject_GetAttr(o, name);
     if (!v) throw Raised{};
-    void* p = v == Py_None ? nullptr : (THPVariable_Check(v) ? THPVariable_Unpack(v).data_ptr() : nullptr);
+    void* p;
+    try {
+      p = pointer(v);  // (only None is NULL, the shift-only form)
+    } catch (...) {
+      Py_DECREF(v);
+      throw;
+    }
     Py_DECREF(v);
     return static_cast<const int32_t*>(p);
   };
