@@ -670,7 +670,11 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace,
 bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err) {
   const int64_t img = (int64_t)cg.C * cg.H * cg.W;
   const int64_t ohw = (int64_t)cg.OH * cg.OW;
-  if ((cg.nhwc && cg.C >= 16) || cg.KH * cg.KW > 63 || a.K > 28000 || img >= (1ll << 26) || (int64_t)cg.O * a.K >= (1ll << 31) ||
+  // The table's offsets have 26 bits.  The filter's far corner may lie beyond the image, whose offsets count from the
+  // pixel's own corner: a filter taller than the image reaches further than the image is large.
+  const int64_t far = cg.nhwc ? ((cg.KH - 1) * (int64_t)cg.W + cg.KW - 1) * cg.C + cg.C - 1
+                              : ((cg.C - 1) * (int64_t)cg.H + cg.KH - 1) * cg.W + cg.KW - 1;
+  if ((cg.nhwc && cg.C >= 16) || cg.KH * cg.KW > 63 || a.K > 28000 || img >= (1ll << 26) || far >= (1ll << 26) || (int64_t)cg.O * a.K >= (1ll << 31) ||
       (int64_t)cg.B * ((ohw + 31) / 32) >= (1ll << 30))
     return false;
   CnParams p{};

@@ -60,3 +60,23 @@ def test_gathered_convolution(case, shape, layout, gemm_path):
                 assert_same(host(got), want, f"requantized {case} u8={out_u8}")
     finally:
         hago.set_test_hook(hago.HOOK_GENERAL_TILE, -1)
+
+
+@pytest.mark.parametrize("layout,C,H,W,KH,stride", [
+    ("nchw", 31, 2, 1070000, 5, (1, 4096)),    # image below 2^26 elements, the filter's last tap beyond
+    ("nchw", 30, 2, 1070000, 3, (1, 4096)),    # both below
+    ("nhwc", 5, 2, 6500003, 5, (1, 4096)),
+    ("nhwc", 3, 2, 4000003, 5, (1, 4096)),
+])
+@pytest.mark.parametrize("path", [0, 4])
+def test_filter_taller_than_a_large_image(layout, C, H, W, KH, stride, path, gemm_path):
+    """Offsets from a pixel's corner to a filter's last tap, around the 2^26 that the kernel's table holds."""
+    to = (lambda x: x) if layout == "nchw" else (lambda x: np.ascontiguousarray(x.transpose(0, 2, 3, 1)))
+    lay_g, lay_r = (hago.NCHW, ref.NCHW) if layout == "nchw" else (hago.NHWC, ref.NHWC)
+    rng = np.random.default_rng(C * KH)
+    a = to(rng.integers(0, 256, (1, C, H, W), dtype=np.uint8))
+    w = to(rng.integers(-127, 128, (8, C, KH, 5)).astype(np.int8))
+    pad = (KH // 2, 2)
+    gemm_path(path)
+    got = host(hago.qconv2d(dev(a), act_qtype(a, 131), dev(w), hago.QType(hago.I8), None, lay_g, stride, pad))
+    assert_same(got, ref.qconv2d(a, 131, w, None, lay_r, stride, pad), f"{layout} {C} x {H} x {W}")
