@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int frow = lane & 31, fhalf = lane >> 5;
   const int tiles_m = (p.M + 31) / 32;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);  // consecutive tiles share weight rows, on one XCD
+  const int tile = p.tile0 + xcd_remap(blockIdx.x, gridDim.x);  // consecutive tiles share weight rows, on one XCD
   const int tile_n = tile / tiles_m;
   const int n0 = tile_n * 32, m0 = (tile - tile_n * tiles_m) * 32;
 
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
   const int wp = wave % WP, wq = wave / WP % WQ, kset = wave / (WP * WQ);
   const int frow = lane & 31, fhalf = lane >> 5;
   const int tiles_p = (p.N + BP - 1) / BP;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = p.tile0 + xcd_remap(blockIdx.x, gridDim.x);
   const int tile_q = tile / tiles_p;
   const int p0 = (tile - tile_q * tiles_p) * BP, q0 = tile_q * BQ;
 
@@ -556,11 +556,24 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
   }
 }
 
+// A launch holds fewer than 2^32 threads, which 128 x 128 tiles of 512 threads reach at 2^30 rows: in as many launches
+// as that takes.
+hipError_t launch_tiles(void (*kern)(QgemmParams), QgemmParams p, int64_t tiles, int threads, int lds, hipStream_t st) {
+  if (tiles >= (1ll << 31)) return hipErrorInvalidValue;
+  const int64_t most = (1ll << 32) / threads - 8;  // (a multiple of the eight XCDs)
+  for (int64_t first = 0; first < tiles; first += most) {
+    p.tile0 = (int32_t)first;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles - first < most ? tiles - first : most)), dim3(threads), lds, st, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 template <bool I16, int NW, int U>
 hipError_t launch_direct(const QgemmParams& p, hipStream_t st) {
   const int64_t tiles = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32);
-  hipLaunchKernelGGL((qgemm_direct_kernel<I16, NW, U>), dim3((unsigned)tiles), dim3(64 * NW), 0, st, p);
-  return hipGetLastError();
+  return launch_tiles(qgemm_direct_kernel<I16, NW, U>, p, tiles, 64 * NW, 0, st);
 }
 
 template <bool I16, int WP, int WQ, int TP, int TQ, int KS>
@@ -573,8 +586,7 @@ hipError_t launch_staged(const QgemmParams& p, hipStream_t st) {
   static std::atomic<uint64_t> attr_set{0};
   hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds, attr_set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ * KS), lds, st, p);
-  return hipGetLastError();
+  return launch_tiles(kern, p, tiles, 64 * WP * WQ * KS, lds, st);
 }
 
 }  // namespace

@@ -49,6 +49,7 @@ struct QgemmParams {
   int32_t vec16_out;   // dense: output rows can be written as aligned 16-byte pieces
   RequantScalars rs;
   ConvGeom g;
+  int32_t tile0;       // first tile of this launch (a problem of many tiles takes several)
   // implicit GEMM over a prepacked copy: its byte size and ceil(2^32 / C), ceil(2^32 / KW)
   uint32_t act_bytes, inv_c, inv_kw;
 #ifdef HAGO_PHASE_TIMING

@@ -106,6 +106,35 @@ def test_qdense_more_than_2_31_outputs(N, K):
     assert bool((out8[(reps - 1) * rows_block:reps * rows_block] == out8[:rows_block]).all())
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (2 ** 30 + 300, 5, 3),      # 128 x 128 tiles of 512 threads: more than 2^32 threads
+    (3, 2 ** 30 + 300, 1),      # the same along the output channels
+    (2 ** 29 + 70, 2, 0),       # 32 x 32 tiles of 256 threads, no reduction: the bias
+])
+@pytest.mark.parametrize("i16", [False, True])
+def test_qdense_more_threads_than_a_launch_holds(M, N, K, i16):
+    """Dense problems of more tiles than one launch holds threads for: every row and channel gets its results."""
+    _need_memory(M * N * 2 + (M + N) * K * 2 + N * 4 + (1 << 30))
+    dt, hd = (torch.int16, hago.I16) if i16 else (torch.int8, hago.I8)
+    g = torch.Generator(device=DEV).manual_seed(M % 1000 + K)
+    a = torch.randint(-100, 100, (M, K), generator=g, device=DEV, dtype=dt)
+    w = torch.randint(-100, 100, (N, K), generator=g, device=DEV, dtype=dt)
+    bias = torch.randint(-20000, 20000, (N,), generator=g, device=DEV, dtype=torch.int32)
+    bits = 16 if i16 else 8
+    mult, shift = np.array([2 ** 30], np.int32), np.array([8], np.int32)   # rounds sums / 2^9
+    out = hago.qdense(a, hago.QType(hd, bits, True, 7), w, hago.QType(hd, bits, True, 0), bias, hago.I32, gpu_requant(mult, shift))
+    torch.cuda.synchronize()
+    step = 1 << 24
+    for m0 in range(0, M, step if N < 100 else M):
+        for n0 in range(0, N, N if N < 100 else step):
+            am, wn = a[m0:m0 + step].int() - 7, w[n0:n0 + step].int()
+            acc = bias[None, n0:n0 + step].expand(am.shape[0], wn.shape[0]).clone()
+            for k in range(K):
+                acc += am[:, k:k + 1] * wn[None, :, k]
+            want = ((acc + 256) >> 9).clamp_(-128, 127).to(torch.int8)
+            assert torch.equal(out[m0:m0 + step, n0:n0 + step], want), (m0, n0)
+
+
 def _rep_images(block_imgs, reps):
     """[reps * nb, C, H, W] device tensor that repeats a seeded block of nb images."""
     t = torch.from_numpy(block_imgs).to(DEV)
