@@ -320,6 +320,8 @@ __global__ __launch_bounds__(KS == 8 ? 512 : 256, 2) void conv_gather_nchw_kerne
   const int n0 = blk * 32 * TC;
   const int K = p.K;
 
+  if constexpr (MODE == 0 && TC == 2 && KS == 4 && !ZP) HAGO_SPARE_REGISTER("v223");  // (216 needed; two wavefronts on a SIMD either way)
+
   // the table
   for (int k = threadIdx.x; k < p.steps * 32; k += 64 * NW) {
     const uint32_t major = div_by((uint32_t)k, p.minor, p.inv_minor), minor = (uint32_t)k - major * p.minor;

@@ -637,6 +637,7 @@ __global__ __launch_bounds__(kThreads) void flat_kernel(Op op, int64_t total, Ch
     const int64_t i = 4 * nvec + v0;
     op.one(i, op.par(channel_at(d, i, k)));
   }
+  HAGO_SPARE_REGISTER("v47");  // (48 registers: still eight wavefronts on a SIMD)
   typename Op::Vec a[U];
 #pragma unroll
   for (int u = 0; u < U; ++u)

@@ -1,0 +1,44 @@
+"""The build's look through the kernels' assembly."""
+import glob
+import os
+
+import pytest
+
+from paper_2103_14949_amd import build
+
+KERNEL = """
+_Zkern: ; @_Zkern
+\tv_lshl_add_u64 v[2:3], v[30:31], 3, s[12:13]
+.LBB0_2:
+\t{shift}
+\ts_endpgm
+\t.amdhsa_kernel _Zkern
+\t\t.amdhsa_next_free_vgpr {registers}
+\t.end_amdhsa_kernel
+"""
+
+
+@pytest.mark.parametrize("shift,registers,refused", [
+    ("v_ashrrev_i64 v[16:17], v31, v[16:17]", 32, True),
+    ("v_lshlrev_b64 v[4:5], v215, v[132:133]", 209, True),      # registers come in blocks of eight
+    ("v_lshrrev_b64_e64 v[4:5], v31, s[2:3]", 25, True),
+    ("v_ashrrev_i64 v[16:17], v31, v[16:17]", 33, False),       # another block follows
+    ("v_ashrrev_i64 v[16:17], v30, v[30:31]", 32, False),
+    ("v_ashrrev_i64 v[30:31], s31, v[30:31]", 32, False),
+    ("v_lshlrev_b32_e32 v16, v31, v16", 32, False),
+])
+def test_shift_amounts_in_the_last_register_are_found(shift, registers, refused):
+    found = build.check_shift_amounts(KERNEL.format(shift=shift, registers=registers))
+    assert bool(found) == refused
+    if refused:
+        assert "_Zkern" in found[0] and shift in found[0]
+
+
+def test_no_kernel_as_built_has_one():
+    directory = os.path.join(os.path.dirname(build.LIB), "_build")
+    paths = glob.glob(os.path.join(directory, "**", "*gfx950.s"), recursive=True)
+    if not paths:
+        pytest.skip("no assembly here: the libraries were built elsewhere")
+    for path in paths:
+        with open(path) as f:
+            assert build.check_shift_amounts(f.read()) == [], path

@@ -64,3 +64,13 @@ def test_every_operator_on_ragged_rows(shape, offset):
     a16 = (acc >> 6).astype(np.int16)
     assert_same(host(hago.requantize(_view(a16, offset), gpu_requant(mult, shift))), ref.requantize(a16, ref_requant(mult, shift)),
                 f"requantize int16 {shape}")
+
+
+def test_requantize_int16_many_wavefronts():
+    """A chip full of wavefronts, a few times: each lane's shift is its own wherever its registers lie."""
+    n = 2 ** 25 + 5
+    a = np.random.default_rng(5).integers(-30000, 30000, (1, 1, n)).astype(np.int16)
+    want = ref.requantize(a, ref_requant([2 ** 30], [7]))
+    da, rq = dev(a), gpu_requant([2 ** 30], [7])
+    for _ in range(4):
+        assert_same(host(hago.requantize(da, rq)), want, "int16, flat")
