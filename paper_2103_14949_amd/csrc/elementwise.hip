@@ -629,9 +629,9 @@ __global__ __launch_bounds__(kThreads) void periodic_kernel(Op op, SpanArgs g, C
 
 // MULTI: inner < 4, every element of a vector may have its own channel; else at most two.
 template <class Op, int U, bool MULTI>
-__global__ __launch_bounds__(kThreads) void flat_kernel(Op op, int64_t total, ChannelDiv d) {
+__global__ __launch_bounds__(kThreads) void flat_kernel(Op op, int64_t total, ChannelDiv d, int64_t block0) {
   const int64_t nvec = total >> 2;
-  const int64_t v0 = (int64_t)blockIdx.x * (kThreads * U) + threadIdx.x;
+  const int64_t v0 = (block0 + blockIdx.x) * (kThreads * U) + threadIdx.x;
   if (v0 < (total & 3)) {  // the last, incomplete vector (v0 < 4: threads of the first workgroup)
     int64_t k;
     const int64_t i = 4 * nvec + v0;
@@ -702,14 +702,22 @@ void launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStream_t s
   // one vector per lane while that does not fill the chip, four beyond
   const int64_t nvec = total / 4 > 0 ? total / 4 : 1;
   const int64_t w1 = (nvec + kThreads - 1) / kThreads, w4 = (nvec + kThreads * U - 1) / (kThreads * U);
-#define HAGO_FLAT(UU, MULTI, W) \
-  hipLaunchKernelGGL((flat_kernel<OpF, UU, MULTI>), dim3((unsigned)(W)), dim3(kThreads), 0, st, OpF{args...}, total, d)
+  // (more than one launch from 2^36 elements on)
+  constexpr int64_t most = max_blocks(kThreads);
+#define HAGO_FLAT(UU, MULTI, W)                                                                                       \
+  for (int64_t b0 = 0; b0 < W; b0 += most)                                                                            \
+  hipLaunchKernelGGL((flat_kernel<OpF, UU, MULTI>), dim3((unsigned)(W - b0 < most ? W - b0 : most)), dim3(kThreads), 0, st, \
+                     OpF{args...}, total, d, b0)
   if (w1 <= 1024) {
-    if (inner < 4) HAGO_FLAT(1, true, w1);
-    else HAGO_FLAT(1, false, w1);
+    if (inner < 4) {
+      HAGO_FLAT(1, true, w1);
+    } else {
+      HAGO_FLAT(1, false, w1);
+    }
+  } else if (inner < 4) {
+    HAGO_FLAT(U, true, w4);
   } else {
-    if (inner < 4) HAGO_FLAT(U, true, w4);
-    else HAGO_FLAT(U, false, w4);
+    HAGO_FLAT(U, false, w4);
   }
 #undef HAGO_FLAT
 }
@@ -719,10 +727,10 @@ void launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStream_t s
 template <int U, bool PERIODIC>
 __global__ __launch_bounds__(kThreads) void simquant_batched_ragged_kernel(
     const float* __restrict__ x, float* __restrict__ y, SpanArgs g, ChannelDiv d, int32_t nbatch, int32_t nparam,
-    const float* __restrict__ scale, const int32_t* __restrict__ zp, CandidateClips clips) {
+    const float* __restrict__ scale, const int32_t* __restrict__ zp, CandidateClips clips, int64_t block0) {
   const int t = threadIdx.x;
   const int64_t total = g.total, nvec = total >> 2;
-  if (blockIdx.x == 0 && t < (int)(total & 3)) {
+  if (block0 + blockIdx.x == 0 && t < (int)(total & 3)) {
     int64_t k;
     const int64_t i = 4 * nvec + t;
     const int64_t c = channel_at(d, i, k);
@@ -739,7 +747,7 @@ __global__ __launch_bounds__(kThreads) void simquant_batched_ragged_kernel(
     step = g.span;
     end = v0 + (int64_t)g.rows * g.span < nvec ? v0 + (int64_t)g.rows * g.span : nvec;
   } else {
-    v0 = (int64_t)blockIdx.x * (kThreads * U) + t;
+    v0 = (block0 + blockIdx.x) * (kThreads * U) + t;
     step = kThreads;
     end = v0 + kThreads * U < nvec ? v0 + kThreads * U : nvec;
   }
@@ -797,7 +805,7 @@ inline void launch_batched_ragged(const float* x, float* y, int64_t total, int64
   if (periodic_split(total, channels, inner, U, &g)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
     hipLaunchKernelGGL((simquant_batched_ragged_kernel<U, true>), dim3((unsigned)wgs), dim3(kThreads), 0, st, x, y, g, d,
-                       nbatch, (int32_t)channels, scale, zp, clips);
+                       nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);
     return;
   }
   g = SpanArgs{};
@@ -805,11 +813,14 @@ inline void launch_batched_ragged(const float* x, float* y, int64_t total, int64
   const int64_t nvec = total / 4 > 0 ? total / 4 : 1;
   if (nvec <= 1024 * kThreads)
     hipLaunchKernelGGL((simquant_batched_ragged_kernel<1, false>), dim3((unsigned)((nvec + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips);
-  else
-    hipLaunchKernelGGL((simquant_batched_ragged_kernel<U, false>),
-                       dim3((unsigned)((nvec + kThreads * U - 1) / (kThreads * U))), dim3(kThreads), 0, st, x, y, g, d,
-                       nbatch, (int32_t)channels, scale, zp, clips);
+                       dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);
+  else {
+    constexpr int64_t most = max_blocks(kThreads);
+    const int64_t wgs = (nvec + kThreads * U - 1) / (kThreads * U);
+    for (int64_t b0 = 0; b0 < wgs; b0 += most)  // (more than one launch from 2^35 elements on)
+      hipLaunchKernelGGL((simquant_batched_ragged_kernel<U, false>), dim3((unsigned)(wgs - b0 < most ? wgs - b0 : most)),
+                         dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips, b0);
+  }
 }
 
 // ---- max-abs calibration (Eq. 2): thr[c] = max |x[o, c, i]| over o, i.  NaN never wins a
@@ -847,8 +858,7 @@ __device__ __forceinline__ void block_merge_max(float m, uint32_t* thr_c) {
 }
 
 __global__ __launch_bounds__(kThreads) void fill_zero_kernel(uint32_t* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i < n) p[i] = 0u;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) p[i] = 0u;
 }
 
 // rows: as the other row kernels (row = outer * channels index, 128-bit nontemporal loads, U
@@ -992,7 +1002,7 @@ __global__ __launch_bounds__(kThreads) void absmax_lanes_kernel(const float* __r
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 inline int grid_for(int64_t jobs) {
-  const int64_t cap = 1ll << 30;  // one job per workgroup; the kernels loop beyond this
+  const int64_t cap = max_blocks(kThreads);  // one job per workgroup; the kernels loop beyond this
   return (int)(jobs < cap ? (jobs > 0 ? jobs : 1) : cap);
 }
 
@@ -1130,8 +1140,7 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
   uint32_t* t = reinterpret_cast<uint32_t*>(thr);
   auto zero_first = [&] {
     // (a fill kernel, not hipMemsetAsync: the call may be captured into a graph)
-    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((nthr + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, st, t, nthr);
+    hipLaunchKernelGGL(fill_zero_kernel, dim3(grid_for((nthr + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, t, nthr);
   };
   const int64_t total = outer * channels * inner;
   if (total == 0) {
@@ -1164,7 +1173,7 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
     int32_t lanes = 1;
     while (lanes < 64 && lanes * 4 < row_len) lanes *= 2;
     const int64_t wgs = (nchan * lanes + kThreads - 1) / kThreads;
-    if (wgs < (1ll << 31)) {
+    if (wgs <= max_blocks(kThreads)) {
       hipLaunchKernelGGL(absmax_lanes_kernel, dim3((unsigned)wgs), dim3(kThreads), 0, st, x, nouter, nchan, row_len, lanes, thr);
       return hipGetLastError();
     }

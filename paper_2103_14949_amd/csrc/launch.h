@@ -23,6 +23,8 @@ inline hipError_t raise_lds_limit(const void* kern, int lds_bytes, std::atomic<u
   return e;
 }
 
+// A launch holds fewer than 2^32 threads; of a larger grid the runtime starts a part, without an error.
+constexpr int64_t max_blocks(int threads) { return ((1ll << 32) - 1) / threads; }
 
 struct RequantArgs {
   const int32_t* multiplier;  // device

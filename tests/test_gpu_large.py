@@ -135,6 +135,62 @@ def test_qdense_more_threads_than_a_launch_holds(M, N, K, i16):
             assert torch.equal(out[m0:m0 + step, n0:n0 + step], want), (m0, n0)
 
 
+def test_requantize_more_rows_than_a_launch_holds():
+    """One workgroup per row: 2^24 of them are 2^32 threads."""
+    rows, inner = 2 ** 24 + 5, 512
+    torch.cuda.empty_cache()
+    _need_memory(rows * inner * 3 + rows * 8 + (4 << 30))
+    acc = torch.empty(1, rows, inner, dtype=torch.int16, device=DEV).random_(-30000, 30000)
+    shift = torch.randint(6, 10, (rows,), device=DEV, dtype=torch.int32)
+    mult = torch.full((rows,), 2 ** 30, dtype=torch.int32, device=DEV)
+    out = hago.requantize(acc, hago.Requant(mult, shift, hago.QType(hago.I8)))
+    for c0 in range(0, rows, 1 << 20):
+        s = shift[c0:c0 + (1 << 20), None]
+        want = ((acc[0, c0:c0 + (1 << 20)].int() + (1 << s)) >> (s + 1)).clamp_(-128, 127).to(torch.int8)
+        assert torch.equal(out[0, c0:c0 + (1 << 20)], want), c0
+
+
+def test_requantize_more_vectors_than_a_launch_holds():
+    """Flat over one tensor of no whole vectors: 2^24 workgroups of 4096 elements are 2^36 elements."""
+    total, block = 2 ** 36 + 5, 2 ** 26
+    torch.cuda.empty_cache()
+    _need_memory(total * 3 + (4 << 30))
+    one = torch.empty(block, dtype=torch.int16, device=DEV).random_(-30000, 30000)
+    acc = torch.empty(total, dtype=torch.int16, device=DEV)
+    for k in range(0, total, block):
+        acc[k:k + block] = one[:min(block, total - k)]
+    out = hago.requantize(acc.view(1, 1, total), gpu_requant([2 ** 30], [7])).view(-1)
+    want = ((one.int() + 128) >> 8).clamp_(-128, 127).to(torch.int8)
+    for k in range(0, total, block):
+        assert torch.equal(out[k:k + block], want[:min(block, total - k)]), k
+    del acc, out
+    torch.cuda.empty_cache()
+
+
+def test_absmax_more_lanes_than_a_launch_holds():
+    """64 lanes per channel of 129 elements: 2^26 channels are 2^32 threads."""
+    channels, inner = 2 ** 26 + 3, 129
+    torch.cuda.empty_cache()
+    _need_memory(channels * inner * 4 + (12 << 30))
+    x = torch.empty(1, channels, inner, device=DEV)
+    x.view(-1)[:2 ** 30].normal_()
+    for k in range(2 ** 30, x.numel(), 2 ** 30):
+        x.view(-1)[k:k + 2 ** 30] = x.view(-1)[:min(2 ** 30, x.numel() - k)]
+    thr = hago.absmax(x)
+    for c0 in range(0, channels, 1 << 22):
+        assert torch.equal(thr[c0:c0 + (1 << 22)], x[0, c0:c0 + (1 << 22)].abs().amax(1)), c0
+
+
+def test_absmax_of_nothing_more_channels_than_a_launch_holds():
+    channels = 2 ** 32 + 9
+    torch.cuda.empty_cache()
+    _need_memory(channels * 5)
+    thr = torch.ones(channels, device=DEV)
+    hago.absmax(torch.empty(0, channels, 1, device=DEV), out=thr)
+    for c0 in range(0, channels, 1 << 30):
+        assert not thr[c0:c0 + (1 << 30)].any(), c0
+
+
 def _rep_images(block_imgs, reps):
     """[reps * nb, C, H, W] device tensor that repeats a seeded block of nb images."""
     t = torch.from_numpy(block_imgs).to(DEV)
