@@ -243,7 +243,7 @@ hipError_t launch_conv_prepack(const GemmArgs& a, const ConvGeom& cg, int32_t Cp
     const int64_t act_blocks = (int64_t)cg.B * ctiles * ptiles;
     const int64_t ring_chunks = (int64_t)p.B * ((int64_t)p.Hp * p.Wp - hw) * (Cp / 16);
     const int64_t blocks = act_blocks + (ring_chunks + p.wgt_chunks + 255) / 256;
-    if (blocks < (1ll << 31)) {
+    if (blocks <= max_blocks(256)) {
       hipLaunchKernelGGL(conv_prepack_nchw_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p,
                          (int32_t)ptiles, (int32_t)ctiles, (int32_t)act_blocks, ring_chunks);
       return hipGetLastError();

@@ -903,7 +903,7 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
     q.tiles = (int32_t)tiles;
     q.per_wave = (int32_t)per;
     const int64_t gy = (tiles + per - 1) / per;
-    if (tiles < (1ll << 26) && gy <= 65535 && waves_x * q.nt < (1ll << 32) && waves_x < (1ll << 31) &&
+    if (tiles < (1ll << 26) && gy <= 65535 && waves_x * q.nt < (1ll << 32) && (waves_x + 3) / 4 <= max_blocks(kThreads) &&
         (flat || ((int64_t)cg.H * cg.W * 2 < (1ll << 31) && (int64_t)cg.OH * cg.OW * 2 * (int64_t)esz < (1ll << 31)))) {
 #define HAGO_DW_MODE(S_, CPK_, NJ_) \
   (p.out_mode == 1 ? dw_mfma_kernel<1, S_, CPK_, NJ_> : p.out_mode == 2 ? dw_mfma_kernel<2, S_, CPK_, NJ_> : dw_mfma_kernel<0, S_, CPK_, NJ_>)

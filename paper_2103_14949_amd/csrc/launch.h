@@ -134,7 +134,8 @@ bool try_qconv_gather_nchw(const GemmArgs& g, const ConvGeom& cg, bool has_works
 // 1x1 stride-1 unpadded NCHW convolution straight from the caller's buffers; false when the
 // geometry is not that kernel's (nothing is launched then).
 bool try_qconv_pointwise_nchw(const GemmArgs& g, const ConvGeom& cg, hipStream_t st, hipError_t* err);
-// The same question as is_qconv3x3_nchw: here all calls but those with 24-bit accumulators.
+// The same question as is_qconv3x3_nchw: here all calls but those with 24-bit accumulators, or with more wavefronts than a
+// launch holds.
 bool is_qconv_pointwise_nchw(const ConvGeom& cg);
 // depthwise convolution (groups == C == O), no MFMA.
 hipError_t launch_qconv_depthwise(const GemmArgs& g, const ConvGeom& cg, hipStream_t st);

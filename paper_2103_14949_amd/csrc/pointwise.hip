@@ -376,7 +376,7 @@ bool try_qconv_pointwise_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t
   const int64_t HW = (int64_t)cg.H * cg.W;
   if (a.acc_wrap_shift != 0 && a.acc_wrap_shift != 16) return false;  // 24-bit accumulators: the general path
   if (!is_qconv_pointwise_nchw(cg) || (int64_t)cg.C * HW >= (1ll << 31) || (int64_t)cg.O * cg.C >= (1ll << 31) ||
-      cg.B * ((HW + 127) / 128) * ((cg.O + 31) / 32) >= (1ll << 31))
+      cg.B * ((HW + 127) / 128) * ((cg.O + 31) / 32) > max_blocks(64))
     return false;
   PwArgs p{};
   p.act = static_cast<const uint8_t*>(a.act);

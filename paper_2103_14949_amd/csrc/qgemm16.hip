@@ -35,6 +35,7 @@ struct G16Params {
   int32_t vec_k;     // weight rows are aligned 16-byte chunks
   RequantScalars rs;
   ConvGeom g;
+  uint32_t tile0;    // first tile of this launch
 };
 
 __device__ __forceinline__ int32_t dot2(uint32_t a, uint32_t b, int32_t c) {
@@ -77,7 +78,8 @@ __global__ __launch_bounds__(256) void qgemm16_kernel(G16Params p) {
   const int t = threadIdx.x;
   const int tx = t & 15, ty = t >> 4;
   const int tiles_n = (p.N + kTile - 1) / kTile;
-  const int tile_m = (int)(blockIdx.x / tiles_n), tile_n = (int)(blockIdx.x % tiles_n);
+  const uint32_t tile = p.tile0 + blockIdx.x;
+  const int tile_m = (int)(tile / tiles_n), tile_n = (int)(tile % tiles_n);
   const int m0 = tile_m * kTile, n0 = tile_n * kTile;
 
   int32_t acc[4][4];
@@ -184,11 +186,18 @@ hipError_t launch_qconv16(const GemmArgs& a, const ConvGeom& cg, hipStream_t st)
   p.g = cg;
   const int64_t tiles = (int64_t)((a.M + kTile - 1) / kTile) * ((a.N + kTile - 1) / kTile);
   if (tiles >= (1ll << 31)) return hipErrorInvalidValue;
-  if (a.act_zero_point != 0)
-    hipLaunchKernelGGL(qgemm16_kernel<true>, dim3((unsigned)tiles), dim3(256), 0, st, p);
-  else
-    hipLaunchKernelGGL(qgemm16_kernel<false>, dim3((unsigned)tiles), dim3(256), 0, st, p);
-  return hipGetLastError();
+  constexpr int64_t most = max_blocks(256);
+  for (int64_t first = 0; first < tiles; first += most) {
+    p.tile0 = (uint32_t)first;
+    const unsigned grid = (unsigned)(tiles - first < most ? tiles - first : most);
+    if (a.act_zero_point != 0)
+      hipLaunchKernelGGL(qgemm16_kernel<true>, dim3(grid), dim3(256), 0, st, p);
+    else
+      hipLaunchKernelGGL(qgemm16_kernel<false>, dim3(grid), dim3(256), 0, st, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace hago

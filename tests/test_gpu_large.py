@@ -191,6 +191,44 @@ def test_absmax_of_nothing_more_channels_than_a_launch_holds():
         assert not thr[c0:c0 + (1 << 30)].any(), c0
 
 
+@pytest.mark.parametrize("layout,B,C,H,W,O,k,i16,path", [
+    ("nchw", 2 ** 26 + 3, 4, 2, 2, 1, 1, False, 0),     # 1x1, a wavefront per image
+    ("nchw", 2 ** 24 + 3, 1, 1, 4, 2, 1, False, 2),     # the rewrite into the workspace, a workgroup per image
+    ("nchw", 1, 2 ** 27 + 5, 1, 1, 0, 3, False, 0),     # depthwise, half a wavefront per channel
+    ("nhwc", 1, 1, 1, 2 ** 30 + 100, 1, 1, True, 0),    # int16, 64 pixels per workgroup
+])
+def test_convolutions_of_more_threads_than_a_launch_holds(layout, B, C, H, W, O, k, i16, path, gemm_path):
+    """Tiny images, channels or pixels in numbers; 1x1 filters, or 3x3 ones of which only the centre meets the image."""
+    dw = O == 0
+    torch.cuda.empty_cache()
+    _need_memory(B * C * H * W * 16 + (C * 9 * 2 if dw else 0) + (4 << 30))
+    dt, hd, bits = (torch.int16, hago.I16, 16) if i16 else (torch.int8, hago.I8, 8)
+    g = torch.Generator(device=DEV).manual_seed(B % 100 + C % 100)
+    a = torch.randint(-100, 100, (B, C, H, W) if layout == "nchw" else (B, H, W, C), generator=g, device=DEV, dtype=dt)
+    wshape = (C, 1, k, k) if dw else ((O, C, k, k) if layout == "nchw" else (O, k, k, C))
+    w = torch.randint(-100, 100, wshape, generator=g, device=DEV, dtype=dt)
+    lay, pad, groups = hago.NCHW if layout == "nchw" else hago.NHWC, (k // 2, k // 2), C if dw else 1
+    a_t, w_t = hago.QType(hd, bits, True, 5), hago.QType(hd, bits, True, 0)
+    gemm_path(path)
+    ws = None
+    if path == 2:
+        ws = torch.empty(hago.qconv2d_workspace_bytes(a.shape, w.shape, lay, (1, 1), pad), dtype=torch.uint8, device=DEV)
+    out = hago.qconv2d(a, a_t, w, w_t, None, lay, (1, 1), pad, groups, hago.I32, gpu_requant([2 ** 30], [6]), workspace=ws)
+    torch.cuda.synchronize()
+    rows, centre = (a.view(C, 1), w[:, 0, 1, 1].reshape(C, 1)) if dw else (None, None)
+    if dw:      # every channel its own factor
+        acc = (rows.int() - 5) * centre.int()
+        assert torch.equal(out.view(C, 1), ((acc + 64) >> 7).clamp_(-128, 127).to(torch.int8))
+        return
+    a3, o3 = (a.view(B, C, H * W), out.view(B, O, H * W)) if layout == "nchw" else (a.view(-1, 1, 1), out.view(-1, 1, 1))
+    w2, step = w.view(O, C).int(), 1 << 24
+    for b0 in range(0, a3.shape[0], step):
+        part = a3[b0:b0 + step].int() - 5
+        for o in range(O):
+            acc = sum(part[:, c] * w2[o, c] for c in range(C))
+            assert torch.equal(o3[b0:b0 + step, o], ((acc + 64) >> 7).clamp_(-128, 127).to(torch.int8)), (b0, o)
+
+
 def _rep_images(block_imgs, reps):
     """[reps * nb, C, H, W] device tensor that repeats a seeded block of nb images."""
     t = torch.from_numpy(block_imgs).to(DEV)
