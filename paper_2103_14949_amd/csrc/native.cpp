@@ -40,6 +40,15 @@ int64_t as_int(PyObject* o) {
   if (v == -1 && PyErr_Occurred()) throw Raised{};
   return v;
 }
+// int(o): floats, numpy scalars and one-element tensors too
+int64_t as_converted_int(PyObject* o) {
+  PyObject* k = PyNumber_Long(o);
+  if (!k) throw Raised{};
+  const long long v = PyLong_AsLongLong(k);
+  Py_DECREF(k);
+  if (v == -1 && PyErr_Occurred()) throw Raised{};
+  return v;
+}
 bool as_bool(PyObject* o) {
   const int v = PyObject_IsTrue(o);
   if (v < 0) throw Raised{};
@@ -52,6 +61,18 @@ int64_t attr_int(PyObject* o, PyObject* name) {
   Py_DECREF(v);
   if (r == -1 && PyErr_Occurred()) throw Raised{};
   return r;
+}
+int64_t attr_converted_int(PyObject* o, PyObject* name) {
+  PyObject* v = PyObject_GetAttr(o, name);
+  if (!v) throw Raised{};
+  try {
+    const int64_t r = as_converted_int(v);
+    Py_DECREF(v);
+    return r;
+  } catch (...) {
+    Py_DECREF(v);
+    throw;
+  }
 }
 void require(bool ok) {
   if (!ok) {
@@ -103,7 +124,7 @@ PyObject* output(PyObject* given, at::IntArrayRef shape, at::ScalarType type, co
 
 hago_qtype qtype(PyObject* q) {
   static PyObject *dtype = intern("dtype"), *bits = intern("bits"), *sgn = intern("is_signed"), *zp = intern("zero_point");
-  return hago_qtype{(hago_dtype)attr_int(q, dtype), (int32_t)attr_int(q, bits), (int32_t)attr_int(q, sgn), (int32_t)attr_int(q, zp)};
+  return hago_qtype{(hago_dtype)attr_int(q, dtype), (int32_t)attr_int(q, bits), (int32_t)attr_converted_int(q, sgn), (int32_t)attr_int(q, zp)};
 }
 
 struct MaybeRequant {  // a copy of the caller's parameters; the tensors are kept by the Prepared object
@@ -272,7 +293,7 @@ Tensor3 tensor3(PyObject* o) {
 }
 
 int32_t per_channel_of(PyObject* o, PyObject* scale) {
-  return o == Py_None ? (tensor(scale).numel() > 1 ? 1 : 0) : (int32_t)as_int(o);
+  return o == Py_None ? (tensor(scale).numel() > 1 ? 1 : 0) : (int32_t)as_converted_int(o);
 }
 
 struct Clip {
@@ -281,8 +302,8 @@ struct Clip {
 Clip clip_of(PyObject* lo, PyObject* hi, const hago_qtype& q, int32_t most_bits) {
   Clip c;
   check(L.hago_bit_range(q.bits < most_bits ? q.bits : most_bits, q.is_signed ? 1 : 0, &c.lo, &c.hi));
-  if (lo != Py_None) c.lo = (int32_t)as_int(lo);
-  if (hi != Py_None) c.hi = (int32_t)as_int(hi);
+  if (lo != Py_None) c.lo = (int32_t)as_converted_int(lo);
+  if (hi != Py_None) c.hi = (int32_t)as_converted_int(hi);
   return c;
 }
 
@@ -318,14 +339,12 @@ PyObject* f_simquant_batched(PyObject* const* a, Py_ssize_t n) {
     PyObject* f = PySequence_Fast(seq, "clip limits are sequences");
     if (!f) throw Raised{};
     for (Py_ssize_t i = 0; i < PySequence_Fast_GET_SIZE(f); ++i) {
-      PyObject* k = PyNumber_Long(PySequence_Fast_GET_ITEM(f, i));
-      const long long r = k ? PyLong_AsLongLong(k) : -1;
-      Py_XDECREF(k);
-      if (r == -1 && PyErr_Occurred()) {
+      try {
+        v.push_back((int32_t)as_converted_int(PySequence_Fast_GET_ITEM(f, i)));
+      } catch (...) {
         Py_DECREF(f);
-        throw Raised{};
+        throw;
       }
-      v.push_back((int32_t)r);
     }
     Py_DECREF(f);
     return v;

@@ -34,3 +34,30 @@ def test_requant_parameters_that_are_not_tensors_are_refused(mult, shift):
                  lambda: hago.qconv2d(a.view(1, 2, 4, 4), I8, w.view(4, 2, 2, 4), I8, rq=rq)):
         with pytest.raises(TypeError):
             call()
+
+
+@pytest.mark.parametrize("lo,hi,per_channel", [
+    (-128.0, 127.0, None), (np.float32(-128), np.int64(127), np.bool_(True)), (torch.tensor(-128), torch.tensor(127.0), 1.0),
+    (-128, 127, np.bool_(False)), (True, 5.9, False)])
+def test_clip_limits_and_per_channel_are_converted_with_int(lo, hi, per_channel):
+    """The operators take whatever int() takes; without a device such a call gets as far as its output's allocation."""
+    x = torch.zeros(1, 4, 2)
+    scale, zp = torch.ones(4), torch.zeros(4, dtype=torch.int32)
+    I8 = hago.QType(hago.I8)
+    I8.is_signed = np.bool_(True)
+    for call in (lambda: hago.simquant(x, scale, zp, I8, lo, hi, per_channel),
+                 lambda: hago.simquant_wrap(x, scale, zp, I8, lo, hi, per_channel),
+                 lambda: hago.quantize(x, scale, zp, I8, lo, hi, per_channel),
+                 lambda: hago.simquant_codes(x, scale, zp, I8, lo, hi, per_channel),
+                 lambda: hago.dequantize(x.to(torch.int8), I8, scale, zp, per_channel)):
+        with pytest.raises(RuntimeError) as e:   # no TypeError: the arguments were taken
+            call()
+        assert not isinstance(e.value, hago.HagoError)
+
+
+@pytest.mark.parametrize("lo", ["x", [1], 1j, float("nan"), float("inf")])
+def test_clip_limits_that_int_refuses_are_refused(lo):
+    x, scale, zp = torch.zeros(1, 4, 2), torch.ones(4), torch.zeros(4, dtype=torch.int32)
+    for call in (lambda: hago.simquant(x, scale, zp, I8, lo), lambda: hago.quantize(x, scale, zp, I8, None, lo)):
+        with pytest.raises((TypeError, ValueError, OverflowError)):
+            call()
