@@ -223,7 +223,17 @@ PyObject* prepared_out(PyObject* self, void*) {
   Py_INCREF(o);
   return o;
 }
-PyGetSetDef prepared_getset[] = {{"out", prepared_out, nullptr, "the call's output tensor(s)", nullptr}, {}};
+int set_prepared_out(PyObject* self, PyObject* value, void*) {
+  if (!value) {
+    PyErr_SetString(PyExc_AttributeError, "out");
+    return -1;
+  }
+  Py_INCREF(value);
+  Py_XSETREF(reinterpret_cast<Prepared*>(self)->out, value);
+  return 0;
+}
+PyGetSetDef prepared_getset[] = {
+    {"out", prepared_out, set_prepared_out, "what a call returns: the output tensor(s) (another value does not change where the launch writes)", nullptr}, {}};
 
 PyTypeObject PreparedType = [] {
   PyTypeObject t = {PyVarObject_HEAD_INIT(nullptr, 0)};
@@ -241,7 +251,7 @@ PyTypeObject PreparedType = [] {
   return t;
 }();
 
-// Issues f now, or wraps it.  Takes over the reference to `out`; `keep`: the other arguments, borrowed.
+// Issues f now, or wraps it.  Takes over the reference to `out`; `keep`: the other arguments, borrowed (or NULL).
 template <class F>
 PyObject* issue(const F& f, PyObject* out, bool prepare, std::initializer_list<PyObject*> keep) {
   if (!prepare) {
@@ -255,7 +265,7 @@ PyObject* issue(const F& f, PyObject* out, bool prepare, std::initializer_list<P
     }
     return out;
   }
-  PyObject* k = PyTuple_New((Py_ssize_t)keep.size());
+  PyObject* k = PyTuple_New((Py_ssize_t)keep.size() + 1);
   Prepared* p = k ? PyObject_GC_New(Prepared, &PreparedType) : nullptr;
   if (!p) {
     Py_XDECREF(k);
@@ -263,10 +273,12 @@ PyObject* issue(const F& f, PyObject* out, bool prepare, std::initializer_list<P
     throw Raised{};
   }
   Py_ssize_t i = 0;
-  for (PyObject* o : keep) {
+  auto hold = [&](PyObject* o) {
     Py_INCREF(o);
     PyTuple_SET_ITEM(k, i++, o);
-  }
+  };
+  for (PyObject* o : keep) hold(o ? o : Py_None);
+  hold(out);  // (p->out may be set to something else)
   p->vectorcall = prepared_call;
   p->fn = new std::function<hago_status()>(f);
   p->keep = k;

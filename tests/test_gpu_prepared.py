@@ -1,0 +1,35 @@
+"""The call objects that prepare=True returns: their attribute and what they keep alive."""
+import gc
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from gpu_util import *  # noqa: E402,F401,F403
+
+
+def _layer(rng):
+    a, w = rng.integers(-128, 128, (5, 40)).astype(np.int8), rng.integers(-127, 128, (24, 40)).astype(np.int8)
+    mult, shift = rng.integers(2 ** 30, 2 ** 31, 24).astype(np.int32), np.full(24, 9, np.int32)
+    return a, w, mult, shift
+
+
+def test_out_can_be_set_and_the_launch_keeps_its_buffer():
+    a, w, mult, shift = _layer(np.random.default_rng(1))
+    want = ref.qdense(a, 0, w, None, ref.I32, ref_requant(mult, shift))
+    call = hago.qdense(dev(a), hago.QType(hago.I8), dev(w), hago.QType(hago.I8), None, hago.I32, gpu_requant(mult, shift), prepare=True)
+    written = call.out.data_ptr()
+    call.out = "elsewhere"
+    gc.collect()
+    taken = [torch.full((5, 24), 77, dtype=torch.int8, device=DEV) for _ in range(64)]   # would reuse a freed buffer
+    assert call() == "elsewhere" and call.out == "elsewhere"
+    torch.cuda.synchronize()
+    assert all(t.data_ptr() != written and bool((t == 77).all()) for t in taken)
+    with pytest.raises(AttributeError):
+        del call.out
+    again = hago.qdense(dev(a), hago.QType(hago.I8), dev(w), hago.QType(hago.I8), None, hago.I32, gpu_requant(mult, shift), prepare=True)
+    mine = again.out
+    assert again() is mine
+    assert_same(host(mine), want)
+
