@@ -179,9 +179,9 @@ struct Prepared {
   PyObject* out;
 };
 
-PyObject* prepared_call(PyObject* self, PyObject* const*, size_t nargs, PyObject*) {
+PyObject* prepared_call(PyObject* self, PyObject* const*, size_t nargs, PyObject* names) {
   Prepared* p = reinterpret_cast<Prepared*>(self);
-  if (PyVectorcall_NARGS(nargs) != 0) {
+  if (PyVectorcall_NARGS(nargs) != 0 || (names && PyTuple_GET_SIZE(names) != 0)) {
     PyErr_SetString(PyExc_TypeError, "a prepared call takes no arguments");
     return nullptr;
   }

@@ -1,4 +1,4 @@
-"""The call objects that prepare=True returns: their attribute and what they keep alive."""
+"""The call objects that prepare=True returns: their attribute, what they refuse and what they keep alive."""
 import gc
 
 import numpy as np
@@ -33,3 +33,10 @@ def test_out_can_be_set_and_the_launch_keeps_its_buffer():
     assert again() is mine
     assert_same(host(mine), want)
 
+
+def test_calls_take_no_arguments():
+    call = hago.absmax(dev(np.ones((1, 4, 8), np.float32)), prepare=True)
+    for bad in (lambda: call(1), lambda: call(out=None)):
+        with pytest.raises(TypeError):
+            bad()
+    assert_same(host(call()), np.ones(4, np.float32))
