@@ -127,33 +127,35 @@ hago_qtype qtype(PyObject* q) {
   return hago_qtype{(hago_dtype)attr_int(q, dtype), (int32_t)attr_int(q, bits), (int32_t)attr_converted_int(q, sgn), (int32_t)attr_int(q, zp)};
 }
 
-struct MaybeRequant {  // a copy of the caller's parameters; the tensors are kept by the Prepared object
+struct Ref {  // a reference of our own
+  PyObject* o = nullptr;
+  Ref() = default;
+  Ref(const Ref&) = delete;
+  ~Ref() { Py_XDECREF(o); }
+};
+struct RequantTensors {  // kept by the Prepared object: the attributes they come from may be set to others
+  Ref mult, shift;
+};
+
+struct MaybeRequant {  // a copy of the caller's parameters
   bool present = false;
   hago_requant rq{};
   const hago_requant* ptr() const { return present ? &rq : nullptr; }
 };
 
-MaybeRequant requant(PyObject* o) {
+MaybeRequant requant(PyObject* o, RequantTensors& tensors) {
   MaybeRequant r;
   if (o == Py_None) return r;
   static PyObject *mult = intern("multiplier"), *shift = intern("shift"), *pc = intern("per_channel"), *out = intern("out"),
                   *lo = intern("clip_lo"), *hi = intern("clip_hi"), *rounding = intern("rounding");
-  auto ptr_of = [&](PyObject* name) {
-    PyObject* v = PyObject_GetAttr(o, name);
-    if (!v) throw Raised{};
-    void* p;
-    try {
-      p = pointer(v);  // (only None is NULL, the shift-only form)
-    } catch (...) {
-      Py_DECREF(v);
-      throw;
-    }
-    Py_DECREF(v);
-    return static_cast<const int32_t*>(p);
+  auto ptr_of = [&](PyObject* name, Ref& t) {
+    t.o = PyObject_GetAttr(o, name);
+    if (!t.o) throw Raised{};
+    return static_cast<const int32_t*>(pointer(t.o));  // (only None is NULL, the shift-only form)
   };
   r.present = true;
-  r.rq.multiplier = ptr_of(mult);
-  r.rq.shift = ptr_of(shift);
+  r.rq.multiplier = ptr_of(mult, tensors.mult);
+  r.rq.shift = ptr_of(shift, tensors.shift);
   r.rq.per_channel = (int32_t)attr_int(o, pc);
   PyObject* q = PyObject_GetAttr(o, out);
   if (!q) throw Raised{};
@@ -465,7 +467,8 @@ PyObject* f_absmax(PyObject* const* a, Py_ssize_t n) {
 PyObject* f_requantize(PyObject* const* a, Py_ssize_t n) {
   need_args(n, 4);
   const Tensor3 x = tensor3(a[0]);
-  const MaybeRequant rq = requant(a[1]);
+  RequantTensors tensors;
+  const MaybeRequant rq = requant(a[1], tensors);
   int code;
   switch (x.t.scalar_type()) {
     case at::kByte: code = HAGO_U8; break;
@@ -480,7 +483,7 @@ PyObject* f_requantize(PyObject* const* a, Py_ssize_t n) {
   const int64_t o = x.outer, ch = x.channels, in = x.inner;
   void* st = stream();
   return issue([=] { return L.hago_requantize(src, (hago_dtype)code, o, ch, in, rq.ptr(), dst, st); }, out, as_bool(a[3]),
-               {a[0], a[1]});
+               {a[0], tensors.mult.o, tensors.shift.o});
 }
 
 // (a, a_t, w, w_t, bias, acc_dtype, rq, flags, out, prepare)
@@ -493,7 +496,8 @@ PyObject* f_qdense(PyObject* const* a, Py_ssize_t n) {
   const hago_qtype at_ = qtype(a[1]), wt = qtype(a[3]);
   const int32_t* bias = static_cast<const int32_t*>(pointer(a[4]));
   const int64_t acc = as_int(a[5]);
-  const MaybeRequant rq = requant(a[6]);
+  RequantTensors tensors;
+  const MaybeRequant rq = requant(a[6], tensors);
   const uint32_t flags = (uint32_t)as_int(a[7]);
   const int64_t shape[2] = {M, N};
   PyObject* out = output(a[8], at::IntArrayRef(shape, 2), scalar_type(rq.present ? rq.rq.out.dtype : acc), act);
@@ -501,7 +505,7 @@ PyObject* f_qdense(PyObject* const* a, Py_ssize_t n) {
   void* dst = pointer(out);
   void* st = stream();
   return issue([=] { return L.hago_qdense(ap, at_, wp, wt, bias, M, N, K, (hago_dtype)acc, rq.ptr(), dst, flags, st); }, out,
-               as_bool(a[9]), {a[0], a[2], a[4], a[6]});
+               as_bool(a[9]), {a[0], a[2], a[4], tensors.mult.o, tensors.shift.o});
 }
 
 void pair(PyObject* o, int32_t (&v)[2]) {
@@ -531,7 +535,8 @@ PyObject* f_qconv2d(PyObject* const* a, Py_ssize_t n) {
   pair(a[7], pad);
   const int32_t groups = (int32_t)as_int(a[8]);
   const int64_t acc = as_int(a[9]);
-  const MaybeRequant rq = requant(a[10]);
+  RequantTensors tensors;
+  const MaybeRequant rq = requant(a[10], tensors);
   const uint32_t flags = (uint32_t)as_int(a[11]);
   auto extent = [&](int64_t size, int64_t k, int i) -> int64_t {
     if (stride[i] == 0) {
@@ -557,12 +562,12 @@ PyObject* f_qconv2d(PyObject* const* a, Py_ssize_t n) {
     void* ws = wst.numel() ? wst.data_ptr() : nullptr;
     return issue([=] { return L.hago_qconv2d_ws(ap, at_, wp, wt, bias, (hago_layout)layout, B, C, H, W, O, kh, kw, sh, sw, ph, pw,
                                                 groups, (hago_dtype)acc, rq.ptr(), dst, ws, bytes, flags, st); },
-                 out, prepare, {a[0], a[2], a[4], a[10], a[14]});
+                 out, prepare, {a[0], a[2], a[4], tensors.mult.o, tensors.shift.o, a[14]});
   }
   auto fn = as_bool(a[15]) ? L.hago_qconv2d_static : L.hago_qconv2d;
   return issue([=] { return fn(ap, at_, wp, wt, bias, (hago_layout)layout, B, C, H, W, O, kh, kw, sh, sw, ph, pw, groups,
                                (hago_dtype)acc, rq.ptr(), dst, flags, st); },
-               out, prepare, {a[0], a[2], a[4], a[10]});
+               out, prepare, {a[0], a[2], a[4], tensors.mult.o, tensors.shift.o});
 }
 
 template <PyObject* (*F)(PyObject* const*, Py_ssize_t)>

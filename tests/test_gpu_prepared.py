@@ -40,3 +40,26 @@ def test_calls_take_no_arguments():
         with pytest.raises(TypeError):
             bad()
     assert_same(host(call()), np.ones(4, np.float32))
+
+
+@pytest.mark.parametrize("kind", ["dense", "conv", "requantize"])
+def test_requant_tensors_outlive_their_attributes(kind):
+    """Parameters that a search sets anew do not pull the tensors from under a call that was marshalled before."""
+    a, w, mult, shift = _layer(np.random.default_rng(2))
+    rq, i8 = gpu_requant(mult, shift), hago.QType(hago.I8)
+    rr = ref_requant(mult, shift)
+    if kind == "dense":
+        call, want = hago.qdense(dev(a), i8, dev(w), i8, rq=rq, prepare=True), ref.qdense(a, 0, w, None, ref.I32, rr)
+    elif kind == "conv":
+        a4, w4 = a.reshape(5, 10, 2, 2), w.reshape(24, 10, 2, 2)
+        call = hago.qconv2d(dev(a4), i8, dev(w4), i8, rq=rq, prepare=True)
+        want = ref.qconv2d(a4, 0, w4, None, ref.NCHW, (1, 1), (0, 0), 1, ref.I32, rr)
+    else:
+        acc = np.random.default_rng(3).integers(-2 ** 17, 2 ** 17, (1, 24, 16)).astype(np.int32)
+        call, want = hago.requantize(dev(acc), rq, prepare=True), ref.requantize(acc, rr)
+    addresses = {rq.multiplier.data_ptr(), rq.shift.data_ptr()}
+    rq.multiplier = rq.shift = None
+    gc.collect()
+    taken = [torch.zeros(24, dtype=torch.int32, device=DEV) for _ in range(64)]   # would reuse freed tensors
+    assert_same(host(call()), want, kind)
+    assert not addresses & {t.data_ptr() for t in taken}
