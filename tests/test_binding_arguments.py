@@ -61,3 +61,46 @@ def test_clip_limits_that_int_refuses_are_refused(lo):
     for call in (lambda: hago.simquant(x, scale, zp, I8, lo), lambda: hago.quantize(x, scale, zp, I8, None, lo)):
         with pytest.raises((TypeError, ValueError, OverflowError)):
             call()
+
+
+def _dense(a=torch.zeros(2, 16, dtype=torch.int8), w=torch.zeros(4, 16, dtype=torch.int8), **k):
+    return hago.qdense(a, k.pop("a_t", I8), w, I8, **k)
+
+
+def _conv(a=torch.zeros(1, 2, 4, 4, dtype=torch.int8), w=torch.zeros(4, 2, 2, 4, dtype=torch.int8), **k):
+    return hago.qconv2d(a, I8, w, I8, **k)
+
+
+@pytest.mark.parametrize("call,error", [
+    (lambda: _dense(a=np.zeros((2, 16), np.int8)), TypeError),
+    (lambda: _dense(a=None), TypeError),
+    (lambda: _dense(w=torch.zeros(4, 15, dtype=torch.int8)), AssertionError),
+    (lambda: _dense(a=torch.zeros(2, 4, 4, dtype=torch.int8)), AssertionError),
+    (lambda: _dense(a=torch.zeros(16, 2, dtype=torch.int8).T), AssertionError),
+    (lambda: _dense(bias=[0, 0, 0, 0]), TypeError),
+    (lambda: _dense(out=np.zeros((2, 4), np.int32)), TypeError),
+    (lambda: _dense(acc_dtype="int32"), TypeError),
+    (lambda: _dense(acc_dtype=77), KeyError),
+    (lambda: _dense(a_t=None), AttributeError),
+    (lambda: _dense(flags=1.0), TypeError),
+    (lambda: _dense(rq=object()), AttributeError),
+    (lambda: _conv(a=torch.zeros(2, 4, 4, dtype=torch.int8)), AssertionError),
+    (lambda: _conv(a=torch.zeros(1, 4, 4, 2, dtype=torch.int8).permute(0, 3, 1, 2)), AssertionError),
+    (lambda: _conv(stride=(0, 1)), ZeroDivisionError),
+    (lambda: _conv(stride=(1,)), IndexError),
+    (lambda: _conv(stride=2), TypeError),
+    (lambda: _conv(pad=(0.5, 0)), TypeError),
+    (lambda: _conv(groups=None), TypeError),
+    (lambda: hago.simquant(torch.zeros(4, 2), torch.ones(4), torch.zeros(4), I8), AssertionError),
+    (lambda: hago.simquant(torch.zeros(1, 4, 2), [1.0], torch.zeros(4), I8), TypeError),
+    (lambda: hago.simquant(torch.zeros(1, 4, 2), torch.ones(4), torch.zeros(4), hago.QType(hago.I8, 99)), hago.HagoError),
+    (lambda: hago.quantize(torch.zeros(2, 4, 2).permute(1, 0, 2), torch.ones(4), torch.zeros(4), I8), AssertionError),
+    (lambda: hago.simquant_batched(torch.zeros(1, 4, 2), torch.ones(2, 4), torch.zeros(2, 4), I8, [-1, -1], [1]), AssertionError),
+    (lambda: hago.simquant_batched(torch.zeros(1, 4, 2), torch.ones(2, 4), torch.zeros(2, 4), I8, -1, 1), TypeError),
+    (lambda: hago.absmax(torch.zeros(4, 2)), AssertionError),
+    (lambda: hago.absmax(torch.zeros(1, 4, 2), out=[0.0] * 4), TypeError),
+    (lambda: hago.requantize(torch.zeros(4, 2, dtype=torch.int32), hago.Requant(MULT, SHIFT, I8)), AssertionError),
+])
+def test_refusals(call, error):
+    with pytest.raises(error):
+        call()

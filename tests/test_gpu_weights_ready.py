@@ -35,7 +35,7 @@ def _at(a, offset):
 
 
 @pytest.mark.parametrize("case", CASES)
-@pytest.mark.parametrize("path", [0, 2, 4])   # the flagged call: as chosen, through the workspace, gathered
+@pytest.mark.parametrize("path", [0, 2, 3, 4])   # the flagged call: as chosen, through the workspace, in one launch, gathered
 def test_weights_kept_across_kernels(case, path, gemm_path):
     layout, C, H, W, O, k, stride, first, second = case
     rng = np.random.default_rng(C * 1000 + O)
