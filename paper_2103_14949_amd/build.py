@@ -21,7 +21,7 @@ HIPCC_FLAGS = [
     "-ffp-contract=off",                       # simquant: no fused multiply-add
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
-    "-save-temps=obj",                         # the assembly, for check_shift_amounts
+    "-save-temps=obj",                         # the assembly, for check_assembly
 ]
 
 
@@ -68,13 +68,27 @@ def check_shift_amounts(assembly: str) -> list[str]:
     return found
 
 
+def check_lds_loads(assembly: str) -> list[str]:
+    """Loads into the LDS that directly follow a write of m0, which they take their address from: one wait state is
+    required between the two, and in inline assembly nobody inserts it."""
+    return [f"{m[1].strip()}; {m[2].strip()}" for m in
+            re.finditer(r"^\s+(s_\w+\s+m0,.*)\n(?:\s*;.*\n)*\s+((?:buffer|global|scratch)_load_\w+.*\blds\b.*|global_load_lds_.*)$",
+                        assembly, re.M)]
+
+
+def check_assembly(assembly: str) -> list[str]:
+    """What the kernels must not hold, and the compiler does not avoid."""
+    return ([f"64-bit shift by the last allocated register (add HAGO_SPARE_REGISTER): {f}" for f in check_shift_amounts(assembly)] +
+            [f"LDS load without a wait state after m0: {f}" for f in check_lds_loads(assembly)])
+
+
 def _check_assembly(directory):
     found = []
     for path in sorted(glob.glob(os.path.join(directory, "*gfx950.s"))):
         with open(path) as f:
-            found += check_shift_amounts(f.read())
+            found += check_assembly(f.read())
     if found:
-        raise RuntimeError("64-bit shifts by the last allocated register (add HAGO_SPARE_REGISTER):\n" + "\n".join(found))
+        raise RuntimeError("\n".join(found))
 
 
 def build(verbose: bool = False, jobs: int = 4) -> str:

@@ -34,6 +34,20 @@ def test_shift_amounts_in_the_last_register_are_found(shift, registers, refused)
         assert "_Zkern" in found[0] and shift in found[0]
 
 
+@pytest.mark.parametrize("lines,refused", [
+    ("s_mov_b32 m0, s4|buffer_load_dwordx4 v1, s[8:11], 0 offen lds", True),
+    ("s_add_u32 m0, m0, s4|; a comment|buffer_load_dword v1, s[8:11], s2 offen offset:16 lds", True),
+    ("s_mov_b32 m0, s4|s_nop 0|buffer_load_dwordx4 v1, s[8:11], 0 offen lds", False),
+    ("s_mov_b32 m0, s4|v_xor_b32 v1, s4, v1|buffer_load_dwordx4 v1, s[8:11], 0 offen lds", False),
+    ("s_mov_b32 m0, s4|buffer_load_dwordx4 v[4:7], v1, s[8:11], 0 offen", False),
+    ("s_mov_b32 s3, s4|buffer_load_dwordx4 v1, s[8:11], 0 offen lds", False),
+])
+def test_lds_loads_directly_after_m0_are_found(lines, refused):
+    assembly = "_Zkern:\n" + "".join(f"\t{x}\n" for x in lines.split("|"))
+    assert bool(build.check_lds_loads(assembly)) == refused
+    assert bool(build.check_assembly(assembly)) == refused
+
+
 def test_no_kernel_as_built_has_one():
     directory = os.path.join(os.path.dirname(build.LIB), "_build")
     paths = glob.glob(os.path.join(directory, "**", "*gfx950.s"), recursive=True)
@@ -41,4 +55,4 @@ def test_no_kernel_as_built_has_one():
         pytest.skip("no assembly here: the libraries were built elsewhere")
     for path in paths:
         with open(path) as f:
-            assert build.check_shift_amounts(f.read()) == [], path
+            assert build.check_assembly(f.read()) == [], path
