@@ -199,13 +199,17 @@ hago_status hago_qdense(const void* a, hago_qtype a_t, const void* w,
  * Errors as for hago_qdense; additionally SHAPE for any other `groups`, a
  * kernel larger than the padded image, stride < 1, pad < 0; DTYPE for int16
  * operands with groups != 1.
- * This entry point uses no scratch memory.  Depthwise, 1x1 (either layout) and
- * NCHW 3x3 stride-1 pad-1 convolutions with C a multiple of 32 up to 128 and
- * W a multiple of 4 up to 128 (configs 2 and 3) run one kernel that reads
- * the caller's tensors directly, as fast as or faster than hago_qconv2d_ws;
- * every other groups == 1 geometry runs a general one-launch kernel, which
- * hago_qconv2d_ws only beats on long reductions (3x3 beyond 128 channels, 5x5
- * and larger).
+ * This entry point uses no scratch memory.  Every geometry runs as one launch
+ * that reads the caller's tensors directly.  Depthwise, 1x1 stride-1 (either
+ * layout) and NCHW 3x3 stride-1 pad-1 convolutions with C a multiple of 32 up
+ * to 128 and W a multiple of 4 up to 128 (configs 2 and 3) have kernels that
+ * hago_qconv2d_ws runs too.  Of the other groups == 1 geometries, where they
+ * have enough output to fill the chip, hago_qconv2d_ws goes through the
+ * workspace for filters beyond 9 taps, for up to 9 taps beyond 64 to 128
+ * channels (by layout, W and size), and on small maps for channel-last layers
+ * of whole 16-channel chunks and for layers of up to 16 channels
+ * (channel-last; NCHW with W a multiple of 4 and more than 64 output
+ * channels).  It runs the others as this entry point does.
  */
 hago_status hago_qconv2d(const void* a, hago_qtype a_t, const void* w,
                          hago_qtype w_t, const int32_t* bias,
