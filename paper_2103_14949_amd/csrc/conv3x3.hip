@@ -258,12 +258,17 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   // |corr| <= 2^30, so acc + corr cannot wrap; with sh <= 19 and an 8-bit z nothing leaves 63 bits.
   const bool fold = p.out_mode == 0 && p.acc_wrap_shift == 0 && !p.rs.half_away && p.rs.z_out >= -256 &&
                     p.rs.z_out <= 255 && __builtin_amdgcn_ballot_w64(!lane_ok) == 0;   // wavefront-uniform
+  // Clipped to the container's whole range: shift, clip and pack of two results are one instruction and no clip in front of
+  // it (9 cycles of a SIMD per output instead of 13.4).
+  const bool sat = fold && sat_range(p.rs);
+  const int32_t zc = p.rs.z_out + (sat ? sat_bias(p.rs) : 0);
+  const uint32_t sflip = sat_flip(p.rs);
   int64_t k64[TN];
   int32_t lo_s[TN], hi_s[TN], s1[TN];
 #pragma unroll
   for (int tn = 0; tn < TN; ++tn) {
     s1[tn] = sh[tn] - 1;
-    k64[tn] = (int64_t)corr[tn] * mu[tn] + ((int64_t)1 << (30 + (sh[tn] & 31))) + ((int64_t)p.rs.z_out << (31 + (sh[tn] & 31)));
+    k64[tn] = (int64_t)corr[tn] * mu[tn] + ((int64_t)1 << (30 + (sh[tn] & 31))) + ((int64_t)zc << (31 + (sh[tn] & 31)));
     lo_s[tn] = clip_lo_before_shift(p.rs.lo_rel + p.rs.z_out, s1[tn] & 31);
     hi_s[tn] = clip_hi_before_shift(p.rs.hi_rel + p.rs.z_out, s1[tn] & 31);
   }
@@ -349,7 +354,17 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
         if (p.out_mode == 0) {
           uint8_t* dst = static_cast<uint8_t*>(p.out) + oo;
           uint32_t dw[4];
-          if (fold) {
+          if (sat) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              int32_t r[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) r[e] = (int32_t)(((int64_t)acc[f][tn][4 * g + e] * (int64_t)mu[tn] + k64[tn]) >> 32);
+              ashr_sat_pair<0>(dw[g], r[0], r[1], s1[tn]);
+              ashr_sat_pair<1>(dw[g], r[2], r[3], s1[tn]);
+              dw[g] ^= sflip;
+            }
+          } else if (fold) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               auto one = [&]<int E>() {

@@ -458,6 +458,11 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   bool first = true;  // the workgroup's first tile
   bool fold = false;
   const int32_t lo_abs = p.rs.lo_rel + p.rs.z_out, hi_abs = p.rs.hi_rel + p.rs.z_out;
+  // results clipped to the container's whole range: shift, clip and pack of two are one instruction (the lane's channels
+  // differ in the channel-last form, so it shifts first)
+  const bool sat = sat_range(p.rs);
+  const int32_t zc = p.rs.z_out + (sat ? sat_bias(p.rs) : 0);
+  const uint32_t sflip = sat_flip(p.rs);
   int ch = 0;         // chunk
   v16i acc[AF][2];
   if constexpr (!MULTI) {  // resident for every tile
@@ -573,7 +578,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
       for (int i = t; i < OB; i += NT) {
         const int32_t corr = s_corr[i] + (need_sum ? p.corr_coef * s_sum[i] : 0), mu = s_mu[i], sh = s_sh[i];
         bad |= sh < 1 || sh > 19 || corr < -(1 << 30) || corr > (1 << 30);
-        const int64_t k64 = (int64_t)corr * mu + ((int64_t)1 << (30 + (sh & 31))) + ((int64_t)p.rs.z_out << (31 + (sh & 31)));
+        const int64_t k64 = (int64_t)corr * mu + ((int64_t)1 << (30 + (sh & 31))) + ((int64_t)zc << (31 + (sh & 31)));
         s_corr[i] = corr;
         s_fold[i] = make_int4((int)(uint32_t)k64, (int)(k64 >> 32), mu, sh - 1);
       }
@@ -610,7 +615,9 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
               for (int e = 0; e < 4; ++e) {
                 const int4 k = s_fold[cl + 4 * g + e];
                 const int64_t pr = (int64_t)acc[f][tn][4 * g + e] * (int64_t)k.z + (int64_t)(((uint64_t)(uint32_t)k.y << 32) | (uint32_t)k.x);
-                v[e] = med3((int32_t)(pr >> 32) >> k.w, lo_abs, hi_abs);
+                v[e] = (int32_t)(pr >> 32) >> k.w;
+                if (!sat) v[e] = med3(v[e], lo_abs, hi_abs);
+                else if (4 * g + 4 > left) v[e] = med3(v[e], -128, 127) ^ (int32_t)(sflip & 0xffu);  // (stored one by one)
               }
             } else {
               const int4 c4 = *reinterpret_cast<const int4*>(s_corr + cl + 4 * g);
@@ -626,7 +633,12 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
             }
             uint8_t* dst = static_cast<uint8_t*>(p.out) + (prow + o + 4 * g) * esz;
             if (4 * g + 4 <= left) {
-              if (p.out_mode == 0) {
+              if (p.out_mode == 0 && fold && sat) {
+                uint32_t dw;
+                ashr_sat_pair<0>(dw, v[0], v[1], 0);
+                ashr_sat_pair<1>(dw, v[2], v[3], 0);
+                *reinterpret_cast<u32_any*>(dst) = dw ^ sflip;
+              } else if (p.out_mode == 0) {
                 *reinterpret_cast<u32_any*>(dst) = pack4_perm(v[0], v[1], v[2], v[3]);
               } else if (p.out_mode == 1) {
                 *reinterpret_cast<v4i_any*>(dst) = v4i{v[0], v[1], v[2], v[3]};
@@ -668,7 +680,18 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
           const uint32_t b = divide(R, (uint32_t)p.OH, p.inv_oh, oy);
           int32_t v[16];
           uint32_t dw[4];
-          if (fold) {
+          if (fold && sat) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              int32_t y[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) y[e] = (int32_t)(((int64_t)acc[f][tn][4 * g + e] * (int64_t)mu + k64) >> 32);
+              ashr_sat_pair<0>(dw[g], y[0], y[1], s1);
+              ashr_sat_pair<1>(dw[g], y[2], y[3], s1);
+              dw[g] ^= sflip;
+              __builtin_amdgcn_sched_barrier(0);  // (four products at a time: all sixteen would spill)
+            }
+          } else if (fold) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               auto one = [&]<int E>() {

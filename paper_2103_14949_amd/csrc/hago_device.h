@@ -106,6 +106,24 @@ __device__ __forceinline__ void ashr_into_byte(uint32_t& dst, int32_t src, int32
         : "+v"(dst) : "v"(sh), "v"(src));
 }
 
+// Bytes 2 HALF and 2 HALF + 1 of dst <- a >> sh and b >> sh, saturated to int8; the other two bytes stay.  Shift, clip to the
+// whole range and pack of two results in one instruction of 8.5 cycles on a SIMD, against 2.7 + 4.3 for the shift and the
+// clip of one and 4.5 for each byte permute that packs them (measured with four wavefronts on every SIMD).
+template <int HALF>
+__device__ __forceinline__ void ashr_sat_pair(uint32_t& dst, int32_t a, int32_t b, int32_t sh) {
+  if constexpr (HALF == 0)
+    asm("v_ashr_pk_i8_i32 %0, %1, %2, %3" : "=v"(dst) : "v"(a), "v"(b), "v"(sh));
+  else
+    asm("v_ashr_pk_i8_i32 %0, %1, %2, %3 op_sel:[0,0,0,1]" : "+v"(dst) : "v"(a), "v"(b), "v"(sh));
+}
+
+// Whether the output's clip limits are its container's whole range, so that this saturation is the clip.  sat_bias is added
+// to the output zero point (inside the 64-bit constant of the folded forms) to centre the range on int8's, and sat_flip
+// undoes it in the packed dword: 0 and 0 for int8, -128 and 0x80 per byte for uint8.
+__device__ __forceinline__ bool sat_range(const RequantScalars& rs) { return rs.hi_rel - rs.lo_rel == 255; }
+__device__ __forceinline__ int32_t sat_bias(const RequantScalars& rs) { return -128 - (rs.lo_rel + rs.z_out); }
+__device__ __forceinline__ uint32_t sat_flip(const RequantScalars& rs) { return rs.lo_rel + rs.z_out == 0 ? 0x80808080u : 0u; }
+
 // Clip limits moved in front of a right shift by s: clip(y >> s, lo, hi) == clip(y, lo * 2^s,
 // (hi + 1) * 2^s - 1) >> s for the flooring shift; a limit that leaves int32 saturates there
 // (no y lies beyond it, so it is inactive, as it should be).

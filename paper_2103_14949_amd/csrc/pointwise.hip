@@ -183,10 +183,16 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
     // ((acc + corr) * m + rnd) >> s + z == (acc * m + corr * m + rnd + z * 2^s) >> s exactly, and
     // acc + corr cannot wrap when |corr| <= 2^30 and |acc| <= 2^30 (|acc| <= C * 2^15 < 2^30 for
     // C < 2^15).  With sh <= 19 and an 8-bit z nothing leaves 63 bits.
+    // SAT (the same, sh >= 1 and a clip to the container's whole range): two results' shift, clip and pack are one
+    // instruction, 9 cycles per output in all instead of 16 (24 -> 144 channels on 32 x 56 x 56: 7.9 us, 8.5 before).
+    enum { kGeneral, kFold, kSat };
     const int32_t away = rs.half_away ? -1 : 0;  // mask of the sign-bit correction
-    auto store_all = [&]<bool FOLD>() {
+    auto store_all = [&]<int FORM>() {
+      constexpr bool FOLD = FORM != kGeneral;
       const int32_t lo = rs.lo_rel + (FOLD ? rs.z_out : 0), hi = rs.hi_rel + (FOLD ? rs.z_out : 0);
-      const int64_t k64 = FOLD ? (int64_t)corr * rq.m + rnd + ((int64_t)rs.z_out << (31 + rq.sh)) : rnd;
+      const int32_t zc = rs.z_out + (FORM == kSat ? sat_bias(rs) : 0);
+      const int64_t k64 = FOLD ? (int64_t)corr * rq.m + rnd + ((int64_t)zc << (31 + rq.sh)) : rnd;
+      const uint32_t flip = sat_flip(rs);
       const int32_t add = FOLD ? 0 : corr;
 #pragma unroll
       for (int gi = 0; gi < 4 / KS; ++gi) {
@@ -200,7 +206,13 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
             v[j] = acc[j][4 * gi + e] + add;
             if (ACC16) v[j] = (int32_t)(int16_t)v[j];
           }
-          if constexpr (MODE == 0) {
+          if constexpr (MODE == 0 && FORM == kSat) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = (int32_t)(((int64_t)v[j] * (int64_t)rq.m + k64) >> 32);
+            ashr_sat_pair<0>(dw[e], v[0], v[1], rq.sh - 1);
+            ashr_sat_pair<1>(dw[e], v[2], v[3], rq.sh - 1);
+            dw[e] ^= flip;
+          } else if constexpr (MODE == 0) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
               // (general form only: halves away from zero add the accumulator's sign bit)
@@ -235,10 +247,12 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
     const bool lane_ok = rq.sh >= 0 && rq.sh <= 19 && corr >= -(1 << 30) && corr <= (1 << 30);
     const bool fold = MODE == 0 && !ACC16 && C < (1 << 15) && rs.z_out >= -256 && rs.z_out <= 255 &&
                       !rs.half_away && __builtin_amdgcn_ballot_w64(!lane_ok) == 0;  // wavefront-uniform
-    if (fold)
-      store_all.template operator()<true>();
+    if (fold && sat_range(rs) && __builtin_amdgcn_ballot_w64(n < N && rq.sh < 1) == 0)
+      store_all.template operator()<kSat>();
+    else if (fold)
+      store_all.template operator()<kFold>();
     else
-      store_all.template operator()<false>();
+      store_all.template operator()<kGeneral>();
   };
 
   if constexpr (KS == 1 && CH <= 3) {

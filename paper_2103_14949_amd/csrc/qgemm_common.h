@@ -146,21 +146,33 @@ __device__ __forceinline__ void load_channel_regs(const QgemmParams& p, int w0, 
   }
 }
 
+// Forms of a staged tile's requantize arithmetic.
+//   kRqGeneral: any shift, any correction.
+//   kRqFolded: (acc + corr) * mult + rounding term is one 64-bit multiply-add with the channel's constant, and the result is
+//     its high dword shifted right.
+//   kRqSat: the same with the output zero point in the constant, for outputs clipped to their container's whole range:
+//     shift, clip and pack of two results are one instruction (ashr_sat_pair).
+enum { kRqGeneral, kRqFolded, kRqSat };
+
 // s_corr holds the weight row sums on entry (s_sum2, if given, a second part to add; it may be
 // s_mult); on exit s_corr/s_mult/s_shift hold the
 // per-channel terms and s_c64 the folded addend corr * mult + 2^(30+shift), with which
 // (acc + corr) * mult + rounding term is one 64-bit multiply-add per element.
-// Returns (block-uniform) whether the tile needs the general arithmetic: some channel has
+// Returns (block-uniform) the arithmetic the tile takes.  It needs the general one if some channel has
 // shift 0 (the result is then not the high dword shifted right), or a correction so large
 // that acc + corr could leave int32 (whose wrap-around the folded form would not reproduce;
-// |acc| <= K * 2^14 < 2^30 for K <= 2^16).
+// |acc| <= K * 2^14 < 2^30 for K <= 2^16).  kRqSat: shifts up to 21 too (products and correction are below 2^61, the zero
+// point's 9 bits shifted by 31 + 21 below 2^61 as well).
 template <int NT, int CH>
-__device__ __forceinline__ bool finish_channel_terms(const QgemmParams& p, const ChannelRegs<NT, CH>& r,
-                                                     int32_t* s_corr, int32_t* s_mult,
-                                                     int32_t* s_shift, int64_t* s_c64,
-                                                     const int32_t* s_sum2 = nullptr,
-                                                     int32_t* s_shm1 = nullptr) {
-  int general = p.K > 65536;
+__device__ __forceinline__ int finish_channel_terms(const QgemmParams& p, const ChannelRegs<NT, CH>& r,
+                                                    int32_t* s_corr, int32_t* s_mult,
+                                                    int32_t* s_shift, int64_t* s_c64,
+                                                    const int32_t* s_sum2 = nullptr,
+                                                    int32_t* s_shm1 = nullptr) {
+  const int32_t z = p.rs.z_out;
+  const bool sat = s_shm1 && p.out_mode == 0 && sat_range(p.rs) && z >= -128 && z <= 255;  // (uniform)
+  const int32_t zc = sat ? z + sat_bias(p.rs) : 0;
+  int general = p.K > 65536, high = 0;
 #pragma unroll
   for (int s = 0; s < ChannelRegs<NT, CH>::kSlots; ++s) {
     const int ci = (int)threadIdx.x + NT * s;
@@ -170,12 +182,22 @@ __device__ __forceinline__ bool finish_channel_terms(const QgemmParams& p, const
       s_corr[ci] = corr;
       s_mult[ci] = r.mult[s];
       s_shift[ci] = r.shift[s];
-      if (s_shm1) s_shm1[ci] = r.shift[s] - 1;  // the folded form shifts the high dword by this
-      s_c64[ci] = (int64_t)corr * (int64_t)r.mult[s] + ((int64_t)1 << (30 + (r.shift[s] & 31)));
+      if (s_shm1) s_shm1[ci] = r.shift[s] - 1;  // the folded forms shift the high dword by this
+      s_c64[ci] = (int64_t)corr * (int64_t)r.mult[s] + ((int64_t)1 << (30 + (r.shift[s] & 31))) +
+                  (sat ? (int64_t)zc << (31 + (r.shift[s] & 31)) : 0);
       general |= (r.shift[s] <= 0) | (corr >= (1 << 30)) | (corr <= -(1 << 30));
+      high |= r.shift[s] > 21;
     }
   }
-  return __syncthreads_or(general) != 0;
+  if (sat) {
+    if (!__syncthreads_or(general | high)) return kRqSat;
+#pragma unroll
+    for (int s = 0; s < ChannelRegs<NT, CH>::kSlots; ++s) {
+      const int ci = (int)threadIdx.x + NT * s;
+      if (ci < CH) s_c64[ci] = (int64_t)s_corr[ci] * (int64_t)r.mult[s] + ((int64_t)1 << (30 + (r.shift[s] & 31)));
+    }
+  }
+  return __syncthreads_or(general) ? kRqGeneral : kRqFolded;
 }
 
 // r = floor((a * m + 2^(30+sh)) / 2^(31+sh)).  With SH_GE1 (sh >= 1) the shift
@@ -192,9 +214,11 @@ __device__ __forceinline__ int32_t mul_shift_fast(int32_t a, int32_t m, int64_t 
 // per dword, write the tile to LDS in output order [row m][channel n], then copy
 // it out with 16-byte stores that cover whole output rows.  LDS rows are BP + 16 bytes
 // apart, so the 32 rows a wavefront writes at once spread over the banks.
-// s_out: BQ * (BP + 16) bytes.  FOLDED: the tile qualifies for the folded arithmetic
-// (see finish_channel_terms); otherwise the general form is used.
-template <int WP, int WQ, int TP, int TQ, bool FOLDED>
+// s_out: BQ * (BP + 16) bytes.  FORM: see finish_channel_terms.
+// Bound by vector-ALU issue.  kRqSat: 4.7 cycles of a SIMD for an output's multiply-add, 4.3 for its half of a saturating
+// shift of two rows of a channel, 1.1 for the permutes that sort the pairs into rows (10.1; 11.6 where a wavefront has one
+// row block, and shifts before it packs), against 14.6 for multiply-add, shift, clip and pack one by one.
+template <int WP, int WQ, int TP, int TQ, int FORM>
 __device__ __forceinline__ void qgemm_epilogue_dense_staged(const QgemmParams& p,
                                                             v16i (&acc)[TP][TQ], int p0, int q0,
                                                             const int32_t* s_corr,
@@ -207,10 +231,12 @@ __device__ __forceinline__ void qgemm_epilogue_dense_staged(const QgemmParams& p
   constexpr int BP = WP * TP * 32, BQ = WQ * TQ * 32;
   constexpr int CPR = BP / 16;   // 16-byte chunks per tile row
   constexpr int RS = BP + 16;    // LDS row stride
+  constexpr bool FOLDED = FORM != kRqGeneral;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int wp = wave % WP, wq = wave / WP;
   const int frow = lane & 31, fhalf = lane >> 5;
+  const uint32_t sflip = sat_flip(p.rs);
   int32_t lo = p.rs.lo_rel, hi = p.rs.hi_rel;
   const int32_t z = p.rs.z_out;
   // v_med3 takes one scalar operand at most: keep the bounds in vector registers once
@@ -250,7 +276,9 @@ __device__ __forceinline__ void qgemm_epilogue_dense_staged(const QgemmParams& p
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int64_t pr = (int64_t)acc[ti][tj][g4 * 4 + e] * (int64_t)mm[e] + c64[e];
-          r[tj][e] = (int32_t)(pr >> 32) >> ss[e];  // ss = shift - 1 here
+          r[tj][e] = (int32_t)(pr >> 32);
+          // (ss = shift - 1 here; kRqSat shifts row blocks two at a time below)
+          if (FORM != kRqSat || (tj == TQ - 1 && TQ % 2 == 1)) r[tj][e] >>= ss[e];
         }
     } else {
       const int32_t cc[4] = {cur.c4.x, cur.c4.y, cur.c4.z, cur.c4.w};
@@ -260,6 +288,28 @@ __device__ __forceinline__ void qgemm_epilogue_dense_staged(const QgemmParams& p
         for (int e = 0; e < 4; ++e)
           r[tj][e] = mul_shift_fast<false>(acc[ti][tj][g4 * 4 + e] + cc[e], mm[e],
                                            (int64_t)1 << (30 + ss[e]), ss[e]);
+    }
+    if constexpr (FORM == kRqSat) {
+      auto put = [&](int tj, uint32_t dw) { *reinterpret_cast<uint32_t*>(my_row + tj * 32 * RS + ti * 32 + g4 * 8) = dw ^ sflip; };
+#pragma unroll
+      for (int tj = 0; tj + 1 < TQ; tj += 2) {
+        uint32_t d01, d23;  // channels 0, 1 and 2, 3: rows tj and tj + 1 of each
+        ashr_sat_pair<0>(d01, r[tj][0], r[tj + 1][0], ss[0]);
+        ashr_sat_pair<0>(d23, r[tj][2], r[tj + 1][2], ss[2]);
+        ashr_sat_pair<1>(d01, r[tj][1], r[tj + 1][1], ss[1]);
+        ashr_sat_pair<1>(d23, r[tj][3], r[tj + 1][3], ss[3]);
+        put(tj, __builtin_amdgcn_perm(d23, d01, 0x06040200u));
+        put(tj + 1, __builtin_amdgcn_perm(d23, d01, 0x07050301u));
+      }
+      if constexpr (TQ % 2 == 1) {
+        uint32_t dw;
+        ashr_sat_pair<0>(dw, r[TQ - 1][0], r[TQ - 1][1], 0);
+        ashr_sat_pair<1>(dw, r[TQ - 1][2], r[TQ - 1][3], 0);
+        put(TQ - 1, dw);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      cur = nxt;
+      continue;
     }
 #pragma unroll
     for (int tj = 0; tj < TQ; ++tj) {

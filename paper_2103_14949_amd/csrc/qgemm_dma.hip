@@ -521,19 +521,22 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
     }
   }
   __syncthreads();
-  const bool general = finish_channel_terms<NT, CH>(p, chregs, s_corr, s_mult, s_shift, s_c64,
-                                                    kSplitSum ? s_mult : nullptr, s_shm1);
+  const int form = finish_channel_terms<NT, CH>(p, chregs, s_corr, s_mult, s_shift, s_c64,
+                                                kSplitSum ? s_mult : nullptr, s_shm1);
   HAGO_STAMP(p, 4);
   if constexpr (!ACT_ON_P) {
     constexpr bool kCanStage = BQ * (BP + 16) <= kStages * STAGE && (BQ * BP / 16) % NT == 0;
     if constexpr (kCanStage) {
       if (p.out_mode == 0 && !p.acc_wrap_shift && p.vec16_out && !p.rs.half_away) {
-        if (general)
-          qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, false>(p, acc, p0, q0, s_corr, s_mult, s_shift,
-                                                             s_c64, s_shm1, smem);
+        if (form == kRqSat)
+          qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqSat>(p, acc, p0, q0, s_corr, s_mult, s_shift,
+                                                              s_c64, s_shm1, smem);
+        else if (form == kRqFolded)
+          qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqFolded>(p, acc, p0, q0, s_corr, s_mult, s_shift,
+                                                                 s_c64, s_shm1, smem);
         else
-          qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, true>(p, acc, p0, q0, s_corr, s_mult, s_shift,
-                                                            s_c64, s_shm1, smem);
+          qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqGeneral>(p, acc, p0, q0, s_corr, s_mult, s_shift,
+                                                                  s_c64, s_shm1, smem);
         return;
       }
     }

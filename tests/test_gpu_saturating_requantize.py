@@ -1,0 +1,60 @@
+"""Requantize whose clip is the container's whole range: kernels shift, saturate and pack two results at a time there.
+Results on both sides of either limit, the zero points at the ends of their range, shifts on both sides of the ones that
+form takes (1 to 19, in the dense layers to 21), and a clip narrower by one, which takes the other form."""
+import numpy as np
+import pytest
+
+from gpu_util import *  # noqa: F401,F403
+
+pytestmark = pytest.mark.gpu
+
+# B C H W O k stride groups layout: one for each kernel with such an epilogue, with remainders of their tiles
+LAYERS = {
+    "dense_64": (1, 96, 1, 70, 80, 1, 1, 1, "nhwc"),
+    "dense_128": (1, 64, 1, 2100, 272, 1, 1, 1, "nhwc"),
+    "dense_192x256": (1, 80, 1, 4100, 2320, 1, 1, 1, "nhwc"),
+    "dense_256": (1, 48, 1, 4100, 4112, 1, 1, 1, "nhwc"),
+    "pointwise": (2, 24, 9, 15, 33, 1, 1, 1, "nchw"),
+    "pointwise_split": (1, 160, 5, 7, 40, 1, 1, 1, "nchw"),
+    "conv3x3": (2, 32, 9, 12, 37, 3, 1, 1, "nchw"),
+    "direct_nchw": (2, 20, 29, 31, 37, 3, 2, 1, "nchw"),
+    "direct_nhwc": (20, 20, 29, 31, 37, 3, 2, 1, "nhwc"),
+    "dw_rows": (2, 5, 9, 44, 5, 3, 1, 5, "nchw"),
+    "dw_ragged": (2, 5, 9, 67, 5, 3, 1, 5, "nchw"),
+    "dw_matrix": (3, 5, 11, 14, 5, 3, 1, 5, "nchw"),
+    "dw_matrix_s2": (3, 5, 11, 30, 5, 3, 2, 5, "nchw"),
+    "dw_nhwc": (2, 10, 9, 11, 10, 3, 1, 10, "nhwc"),
+}
+FORMS = [  # out_u8, z, clip, shifts
+    (False, 0, (-128, 127), (1, 12)), (False, -128, (-128, 127), (6, 9)), (False, 127, (-128, 127), (18, 23)),
+    (True, 0, (0, 255), (5, 9)), (True, 255, (0, 255), (0, 4)), (True, 131, (0, 255), (19, 22)),
+    (False, 3, (-128, 126), (5, 9)), (True, 7, (1, 255), (5, 9)),
+]
+
+
+@pytest.mark.parametrize("name", LAYERS)
+def test_whole_range(name):
+    B, C, H, W, O, k, stride, groups, layout = LAYERS[name]
+    rng = np.random.default_rng(sum(map(ord, name)))
+    nchw = layout == "nchw"
+    for act_u8 in (False, True):
+        a = rng.integers(0, 256, (B, C, H, W)).astype(np.uint8) if act_u8 else rng.integers(-128, 128, (B, C, H, W)).astype(np.int8)
+        za = 117 if act_u8 else 0
+        w = rng.integers(-127, 128, (O, C // groups, k, k)).astype(np.int8)
+        bias = rng.integers(-3000, 3000, O).astype(np.int32)
+        if not nchw:
+            a, w = np.ascontiguousarray(a.transpose(0, 2, 3, 1)), np.ascontiguousarray(w.transpose(0, 2, 3, 1))
+        pad, st = (k // 2, k // 2), (stride, stride)
+        # one accumulation by the oracle; every form requantizes it
+        sums = ref.qconv2d(a, za, w, bias, ref.NCHW if nchw else ref.NHWC, st, pad, groups, ref.I32)
+        da, dw, db = dev(a), dev(w), dev(bias)
+        for out_u8, z, clip, (s0, s1) in FORMS:
+            mult = rng.integers(2 ** 30, 2 ** 31, O, dtype=np.int64).astype(np.int32)
+            shift = rng.integers(s0, s1 + 1, O).astype(np.int32)
+            rows = sums.reshape(B, O, -1) if nchw else sums.reshape(-1, O, 1)
+            want = ref.requantize(np.ascontiguousarray(rows), ref_requant(mult, shift, out_u8, z, clip)).reshape(sums.shape)
+            got = qconv2d(da, act_qtype(a, za), dw, hago.QType(hago.I8), db, hago.NCHW if nchw else hago.NHWC, st, pad, groups,
+                          hago.I32, gpu_requant(mult, shift, out_u8, z, clip))
+            assert_same(host(got), want, f"{name} u8={act_u8} {out_u8, z, clip, s0, s1}")
+            if s0 >= 5 and s1 <= 9 and clip in ((-128, 127), (0, 255)):
+                assert (want == clip[0]).any() and (want == clip[1]).any() and len(np.unique(want)) > 100 or groups > 1
