@@ -136,7 +136,7 @@ def build_phase_timing(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build", "phase")
     os.makedirs(objdir, exist_ok=True)
-    timed = ("qgemm_dma.hip", "qgemm.hip")
+    timed = ("qgemm_dma.hip", "qgemm_line.hip", "qgemm.hip")
     procs, objs = [], []
     for src in sources():
         base = os.path.basename(src)

@@ -452,16 +452,23 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
   p.vec_k = 1;
   p.vec_out = (a.N % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
   p.vec16_out = (a.N % 16 == 0) && ptr_aligned(a.out, 16);
-  // Tile shape: the one whose busiest CU has the least to do (rounds of tiles over the 256
-  // CUs x tile area), with larger tiles discounted for their better operand reuse.
-  struct Cand { int id, bp, bq; double eff; };
-  static const Cand cands[] = {{0, 256, 256, 1.0}, {1, 192, 256, 0.95}, {2, 128, 128, 0.75}, {4, 64, 64, 0.5}};
-  int best = 0;
-  double best_cost = 0;
+  // Tile shape: the least time on the busiest CU, in microseconds: rounds of tiles over the 256 CUs (one workgroup on each,
+  // but of the 64 x 64 tiles, whose loads and matrix instructions overlap each other's), each a constant and a part
+  // proportional to K, as one tile of it takes without and with company.  Fitted to (measured us, best in brackets)
+  //   2048 x 768 -> 3072   256 x 256 14.1, 192 x 256 11.5, [128 x 256 10.1], 128 x 128 16.5, 64 x 64 15.4
+  //   4096 x 768 -> 2304   14.5, [12.6], 19.7, 20.2, 22.5     4096 x 3072 -> 768   33.7, 27.6, 23.7, [15.7], 23.7
+  //   2048 x 768 -> 768    12.8, 10.8, 9.0, 6.9, [6.1]        1024 x 1024 -> 1024  14.9, 12.4, 10.2, 7.5, [5.5]
+  //   5000 x 640 -> 2560   [14.4], 21.9, 18.4, 24.0, 25.3     256 x 4096 -> 4096   41.8, 34.4, 29.6, [16.7], 17.0
+  struct Cand { int id, bp, bq; double fix, per_k; };
+  static const Cand cands[] = {{0, 256, 256, 3.7, 0.0089}, {1, 192, 256, 2.8, 0.0072}, {5, 128, 256, 1.9, 0.0062}, {2, 128, 128, 2.1, 0.0034}};
+  const auto tiles = [&](int bp, int bq) { return (int64_t)((a.N + bp - 1) / bp) * ((a.M + bq - 1) / bq); };
+  const double rounds64 = (double)((tiles(64, 64) + 255) / 256);
+  double best_cost = rounds64 * (0.3 + 0.0023 * a.K);
+  if (best_cost < 0.003 * a.K) best_cost = 0.003 * a.K;  // (one tile's chain of stages)
+  int best = 4;
   for (const Cand& c : cands) {
-    const int64_t tiles = (int64_t)((a.N + c.bp - 1) / c.bp) * ((a.M + c.bq - 1) / c.bq);
-    const double cost = (double)((tiles + 255) / 256) * c.bp * c.bq / c.eff;
-    if (c.id == 0 || cost < best_cost) { best = c.id; best_cost = cost; }
+    const double cost = (double)((tiles(c.bp, c.bq) + 255) / 256) * (c.fix + c.per_k * a.K);
+    if (cost < best_cost) { best = c.id; best_cost = cost; }
   }
   return launch_qdense_dma(p, forced >= 0 ? forced : best, st);
 }

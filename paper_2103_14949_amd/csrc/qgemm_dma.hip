@@ -1,4 +1,4 @@
-// Dense int8 GEMM, fast path: operands stream from global memory straight
+// int8 GEMM for small and middling tiles and for implicit convolutions (large dense tiles: qgemm_line.hip): operands stream from global memory straight
 // into LDS (buffer_load ... lds, 16 bytes per lane) through a ring of 64-byte
 // k-stages, so no vector registers and no LDS-write instructions are spent on
 // staging and two stages of loads are in flight behind the one being read.
@@ -42,57 +42,16 @@
 // it from LDS a second time (two 16-byte reads per lane and stage), independent of the
 // fragments it multiplies; summing the fragments themselves would repeat the work in every
 // wavefront that holds the same weights.
-#include "qgemm_common.h"
-
-#include <type_traits>
-#include <utility>
+#include "qgemm_stream.h"
 
 namespace hago {
 
 namespace {
 
 constexpr int kBK = 64;       // k-bytes per stage (default; small tiles use 128)
-constexpr uint32_t kOob = 0x80000000u;  // offset beyond any tensor (sizes are < 2^31 bytes)
-
-// Chunk permutation of an LDS row of BK bytes.  With these a fragment read (lane -> row lane % 32,
-// chunk 2 h + lane / 32 for 32-k group h) runs at the full LDS rate (measured; other XOR patterns
-// of the row bits run at half rate or less).  It depends on the row inside a 16-row block only.
-template <int BK>
-__device__ __forceinline__ int swz(int row) {
-  return BK == 64 ? (row >> 2) & 3 : (row >> 1) & 7;
-}
-
 // The L DMA instructions of a stage are dealt over its nh 32-k groups: group h issues
 // [dma_first(h), dma_first(h + 1)).
 constexpr int dma_first(int h, int l, int nh) { return (h * l + nh - 1) / nh; }
-
-__device__ __forceinline__ void dma16(v4i rsrc, uint32_t lds_addr, uint32_t voff) {
-  // m0 = LDS byte address of the wavefront's 1 KB window; lane l lands at m0 + 16 * l.  A write of m0 and an LDS load
-  // need a wait state between them, which the compiler does not see to inside inline assembly (the four encoder layers of
-  // 4096 rows take 55.5 us with it, 55.6 without).
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :
-               : "s"(lds_addr), "v"(voff), "s"(rsrc)
-               : "memory", "m0");
-}
-
-// Same with a scalar byte offset added to every lane's address (not range checked).
-__device__ __forceinline__ void dma16s(v4i rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-               : "memory", "m0");
-}
-
-__device__ __forceinline__ v4i make_rsrc(const void* base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  v4i r;
-  r.x = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-  r.y = __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));  // stride 0, no swizzle
-  r.z = __builtin_amdgcn_readfirstlane((int)bytes);
-  r.w = 0x00020000;  // raw buffer, 32-bit data format
-  return r;
-}
 
 // kStages: depth of the LDS ring; OCC: wavefronts per SIMD the register budget must allow
 // (two 4-wavefront workgroups per CU keep the matrix pipe busy across each other's barriers).
@@ -145,28 +104,8 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
   const int Q_ext = ACT_ON_P ? p.N : p.M;
   const int tiles_p = (P_ext + BP - 1) / BP;
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
-  // Tiles are numbered panel by panel (kPanel tiles wide along P, all of Q), row by row inside
-  // a panel: the tiles that run on an XCD at the same time then form a compact block and share
-  // both operands' rows in its L2.
-  constexpr int kPanel = 8;
   int tile_p, tile_q;
-  {
-    const int tiles_q = (Q_ext + BQ - 1) / BQ;
-    const int full = tiles_p / kPanel;
-    const int per_panel = kPanel * tiles_q;
-    int r = tile, w = kPanel, base = 0;
-    if (tile >= full * per_panel) {
-      r = tile - full * per_panel;
-      w = tiles_p - full * kPanel;
-      base = full * kPanel;
-    } else {
-      const int pn = tile / per_panel;
-      r = tile - pn * per_panel;
-      base = pn * kPanel;
-    }
-    tile_q = r / w;
-    tile_p = base + (r - tile_q * w);
-  }
+  panel_tile(tile, tiles_p, (Q_ext + BQ - 1) / BQ, tile_p, tile_q);
   const int p0 = tile_p * BP;  // first P row of the tile
   const int q0 = tile_q * BQ;  // first Q row of the tile
   const int w0 = ACT_ON_P ? q0 : p0;  // first output channel
@@ -579,14 +518,17 @@ hipError_t launch_dma_cfg(const QgemmParams& p, hipStream_t st) {
 
 }  // namespace
 
+hipError_t launch_qdense_line(const QgemmParams& p, int shape, hipStream_t st);
+
 // Requires: K % 16 == 0, K >= 16, 16-byte aligned operands, N*K and M*K below 2^31.
 hipError_t launch_qdense_dma(const QgemmParams& p, int shape, hipStream_t st) {
   switch (shape) {
-    case 1: return launch_dma_cfg<2, 4, 3, 2, 4, 1, false, false>(p, st);   // 192 x 256
+    case 1: return launch_qdense_line(p, 1, st);                                  // 192 x 256
     case 2: return launch_dma_cfg<2, 4, 2, 1, 4, 1, false, false, 128>(p, st);   // 128 x 128, 128-byte stages
     case 3: return launch_dma_cfg<2, 4, 2, 1, 4, 1, false, false>(p, st);   // 128 x 128, 64-byte stages
     case 4: return launch_dma_cfg<2, 2, 1, 1, 4, 2, false, false>(p, st);   // 64 x 64: few rows
-    default: return launch_dma_cfg<2, 4, 4, 2, 4, 1, false, false>(p, st);  // 256 x 256
+    case 5: return launch_qdense_line(p, 5, st);                                  // 128 x 256
+    default: return launch_qdense_line(p, 0, st);                                 // 256 x 256
   }
 }
 
