@@ -445,9 +445,12 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
     return launch_qgemm_any(p, a.operand16, tile < 0 ? -1 : tile % 5, st);
   }
   const int forced = g_hook[kHookDmaTile].load(std::memory_order_relaxed);
-  // A long reduction over few tiles: the direct form splits it over eight wavefronts (1 x 4096 -> 4096
-  // 8.2 us against 15.5, 37 x 3072 -> 768 8.3 against 9.4; equal at K = 768).
-  if (forced < 0 && a.K >= 1024 && (int64_t)((a.N + 31) / 32) * ((a.M + 31) / 32) <= 256)
+  // A long reduction over few tiles: the direct form splits it over eight wavefronts (equal at K = 768).  us, there and as
+  // 64 x 64 tiles with 128-byte stages: 1 x 4096 -> 4096 8.1, 10.9; 1 x 1024 -> 4096 4.6, 5.0; 16 x 2048 -> 2048 6.0, 6.6;
+  // 200 x 4096 -> 1024 10.1, 11.3; 702 x 2112 -> 128, where K ends inside a stage, 5.5, 7.4; but with more rows
+  // 90 x 1280 -> 1280 6.6, 5.4; 627 x 1536 -> 320 6.8, 5.8; 300 x 2048 -> 1024 7.2, 6.5.
+  if (forced < 0 && a.K >= 1024 && (int64_t)((a.N + 31) / 32) * ((a.M + 31) / 32) <= 256 &&
+      (a.M <= 32 || a.K % 128 != 0 || a.K >= 4096))
     return launch_qgemm_any(p, false, 0, st);
   p.vec_k = 1;
   p.vec_out = (a.N % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
@@ -462,10 +465,16 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
   struct Cand { int id, bp, bq; double fix, per_k; };
   static const Cand cands[] = {{0, 256, 256, 3.7, 0.0089}, {1, 192, 256, 2.8, 0.0072}, {5, 128, 256, 1.9, 0.0062}, {2, 128, 128, 2.1, 0.0034}};
   const auto tiles = [&](int bp, int bq) { return (int64_t)((a.N + bp - 1) / bp) * ((a.M + bq - 1) / bq); };
+  // Long reductions on few 64 x 64 tiles are a chain of stages: with 128-byte ones, which two workgroups on a CU have room
+  // for, 1024 x 2048 -> 1024 takes 6.65 (7.5), 1500 x 2688 -> 128 7.4 (8.4), 500 x 4096 -> 1024 11.4 (16.5), 1024 x 768 ->
+  // 768 4.8 (5.0); where K ends inside a stage every lane works out its addresses: 1000 x 1600 -> 512 7.3 (6.5),
+  // 1000 x 4032 -> 512 13.2 (16.2).
   const double rounds64 = (double)((tiles(64, 64) + 255) / 256);
+  const bool wide64 = rounds64 <= 2 && a.K >= 768 && (a.K % 128 == 0 || a.K >= 2816);
   double best_cost = rounds64 * (0.3 + 0.0023 * a.K);
-  if (best_cost < 0.003 * a.K) best_cost = 0.003 * a.K;  // (one tile's chain of stages)
-  int best = 4;
+  if (wide64) best_cost = (rounds64 > 1 ? 0.0034 : 0.0022) * a.K;
+  else if (best_cost < 0.003 * a.K) best_cost = 0.003 * a.K;  // (one tile's chain of stages)
+  int best = wide64 ? 6 : 4;
   for (const Cand& c : cands) {
     const double cost = (double)((tiles(c.bp, c.bq) + 255) / 256) * (c.fix + c.per_k * a.K);
     if (cost < best_cost) { best = c.id; best_cost = cost; }

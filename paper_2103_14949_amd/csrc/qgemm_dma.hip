@@ -1,5 +1,5 @@
-// int8 GEMM for small and middling tiles and for implicit convolutions (large dense tiles: qgemm_line.hip): operands stream from global memory straight
-// into LDS (buffer_load ... lds, 16 bytes per lane) through a ring of 64-byte
+// int8 GEMM for small and middling tiles and for implicit convolutions (large dense tiles:
+// qgemm_line.hip): operands stream from global memory straight into LDS (buffer_load ... lds, 16 bytes per lane) through a ring of 64-byte
 // k-stages, so no vector registers and no LDS-write instructions are spent on
 // staging and two stages of loads are in flight behind the one being read.
 //
@@ -527,6 +527,7 @@ hipError_t launch_qdense_dma(const QgemmParams& p, int shape, hipStream_t st) {
     case 2: return launch_dma_cfg<2, 4, 2, 1, 4, 1, false, false, 128>(p, st);   // 128 x 128, 128-byte stages
     case 3: return launch_dma_cfg<2, 4, 2, 1, 4, 1, false, false>(p, st);   // 128 x 128, 64-byte stages
     case 4: return launch_dma_cfg<2, 2, 1, 1, 4, 2, false, false>(p, st);   // 64 x 64: few rows
+    case 6: return launch_dma_cfg<2, 2, 1, 1, 4, 2, false, false, 128>(p, st);   // 64 x 64, 128-byte stages: long reductions
     case 5: return launch_qdense_line(p, 5, st);                                  // 128 x 256
     default: return launch_qdense_line(p, 0, st);                                 // 256 x 256
   }

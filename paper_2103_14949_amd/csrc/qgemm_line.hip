@@ -4,8 +4,9 @@
 // qgemm_dma.hip, whose ring of four 64-byte stages served these tiles before.
 //
 // What bounds it.  A 192 x 256 tile of K = 768 fetches 344 KB from L2 into one CU's LDS while its SIMDs have 9 216 cycles of
-// matrix instructions (5.8 us at the 1.6 GHz that the board holds under them).  With 64-byte stages a DMA instruction
-// fetches halves of 128-byte lines and the stream delivers about 42 GB/s to a CU, 8.15 us; whole lines run at up to 75 GB/s.
+// matrix instructions (5.8 us at the 1.6 GHz that the board holds under them).  What the L2 holds reaches the LDS at
+// 130 GB/s per CU, but most of a line's first readers wait for it to come from memory: with 64-byte stages, which fetch a
+// line in two halves and have a barrier for each, the main loop took 8.15 us, 42 GB/s per CU.
 // Two slots of 128-byte stages (112 KB of LDS for 192 rows of weights and 256 of activations) leave a stage's loads almost
 // a whole stage of matrix instructions to land in.  For that the wavefronts must be done with a slot early: fragments are
 // double-buffered by 32-k groups, the reads of a group go out behind the matrix instructions of the one before, so that

@@ -8,7 +8,7 @@ from gpu_util import *  # noqa: F401,F403
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("tile", [0, 1, 5])  # 256 x 256, 192 x 256, 128 x 256
+@pytest.mark.parametrize("tile", [0, 1, 5, 6])  # 256 x 256, 192 x 256, 128 x 256; 64 x 64
 @pytest.mark.parametrize("K", [16, 48, 112, 128, 144, 240, 256, 272, 384, 400, 1040])
 def test_stage_edges(tile, K):
     rng = np.random.default_rng(100 * K + tile)
