@@ -27,7 +27,6 @@ namespace hago {
 
 namespace {
 
-typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));
 typedef uint32_t u32_any __attribute__((aligned(1)));
 typedef uint16_t u16_any __attribute__((aligned(1)));
 

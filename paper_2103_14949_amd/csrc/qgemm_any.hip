@@ -28,7 +28,6 @@ namespace hago {
 
 namespace {
 
-typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));
 
 // 16 NV bytes of a row in registers.  MIS: as the aligned dwords that hold them, `at` the first byte's place in the first.
 template <int NV, bool MIS>

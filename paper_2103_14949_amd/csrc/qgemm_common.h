@@ -22,6 +22,7 @@ namespace hago {
 #endif
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v4i_any __attribute__((ext_vector_type(4), aligned(1)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 #ifdef HAGO_PHASE_TIMING
@@ -210,9 +211,10 @@ __device__ __forceinline__ int32_t mul_shift_fast(int32_t a, int32_t m, int64_t 
   return (int32_t)(pr >> (31 + sh));
 }
 
-// Dense epilogue of a tile (interior or ragged, N % 16 == 0) through LDS: requantize, pack four channels
+// Dense epilogue of a tile (interior or ragged) through LDS: requantize, pack four channels
 // per dword, write the tile to LDS in output order [row m][channel n], then copy
-// it out with 16-byte stores that cover whole output rows.  LDS rows are BP + 16 bytes
+// it out with 16-byte stores that cover whole output rows, at whatever byte those start (rows of 1001 results stored one by
+// one from the registers: 64 x 256 -> 129 6.1 us, 3.6 so; 4096 x 768 -> 3070 49, 17).  LDS rows are BP + 16 bytes
 // apart, so the 32 rows a wavefront writes at once spread over the banks.
 // s_out: BQ * (BP + 16) bytes.  FORM: see finish_channel_terms.
 // Bound by vector-ALU issue.  kRqSat: 4.7 cycles of a SIMD for an output's multiply-add, 4.3 for its half of a saturating
@@ -331,27 +333,51 @@ __device__ __forceinline__ void qgemm_epilogue_dense_staged(const QgemmParams& p
     const int q = (int)threadIdx.x + NT * s;
     const int row = q / CPR, c = q % CPR;
     const v4i v = *reinterpret_cast<const v4i*>(s_out + row * RS + c * 16);
-    // ragged tiles: rows beyond M and 16-channel chunks beyond N (N % 16 == 0) stay in LDS
-    if (!ragged || (q0 + row < p.M && p0 + c * 16 < p.N))
+    // ragged tiles: rows beyond M and channels beyond N stay in LDS
+    if (ragged && (q0 + row >= p.M || p0 + c * 16 >= p.N)) continue;
+    uint8_t* dst = out8 + (size_t)(q0 + row) * p.N + p0 + c * 16;
+    if (p.vec16_out) {  // (uniform)
       // streaming store: the tile is complete and nothing in this launch reads it again, so it
       // need not stay in L2 until the end-of-kernel write-back (large outputs: 1 us per launch)
-      __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(out8 + (size_t)(q0 + row) * p.N + p0 + c * 16));
+      __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(dst));
+    } else if (p0 + c * 16 + 16 <= p.N) {
+      *reinterpret_cast<v4i_any*>(dst) = v;  // (pieces of a line meet in L2)
+    } else {  // the row's last channels
+      const int left = p.N - p0 - c * 16;
+      uint32_t w[4] = {(uint32_t)v.x, (uint32_t)v.y, (uint32_t)v.z, (uint32_t)v.w};
+#pragma unroll
+      for (int e = 0; e < 15; ++e)
+        if (e < left) dst[e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
+    }
   }
   HAGO_STAMP(p, 6);
 }
 
-// Straight-line epilogue of a tile (interior or ragged) whose packed stores are aligned.
+// Straight-line epilogue of a tile (interior or ragged): groups of four along the packed axis are one store, in a dense
+// tile at any address and cut where the row ends, else aligned and inside the tensor or outside.
 // OM: 0 requantized 8-bit, 1 raw int32, 2 raw int16.
 template <int OM>
 __device__ __forceinline__ void store_group(void* out, size_t off, int32_t v0, int32_t v1,
                                             int32_t v2, int32_t v3) {
+  typedef uint32_t u32_any __attribute__((aligned(1)));
+  typedef short v4s_any __attribute__((ext_vector_type(4), aligned(1)));
   if constexpr (OM == 0)
-    *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(out) + off) = pack4(v0, v1, v2, v3);
+    *reinterpret_cast<u32_any*>(static_cast<uint8_t*>(out) + off) = pack4(v0, v1, v2, v3);
   else if constexpr (OM == 1)
-    *reinterpret_cast<int4*>(static_cast<int32_t*>(out) + off) = make_int4(v0, v1, v2, v3);
+    *reinterpret_cast<v4i_any*>(static_cast<int32_t*>(out) + off) = v4i{v0, v1, v2, v3};
   else
-    *reinterpret_cast<short4*>(static_cast<int16_t*>(out) + off) =
-        make_short4((short)v0, (short)v1, (short)v2, (short)v3);
+    *reinterpret_cast<v4s_any*>(static_cast<int16_t*>(out) + off) = v4s_any{(short)v0, (short)v1, (short)v2, (short)v3};
+}
+// The first n results of a group.
+template <int OM>
+__device__ __forceinline__ void store_some(void* out, size_t off, const int32_t (&v)[4], int n) {
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    if (e >= n) break;
+    if constexpr (OM == 0) static_cast<uint8_t*>(out)[off + e] = (uint8_t)v[e];
+    else if constexpr (OM == 1) static_cast<int32_t*>(out)[off + e] = v[e];
+    else static_cast<int16_t*>(out)[off + e] = (int16_t)v[e];
+  }
 }
 
 template <int OM, bool AWAY>
@@ -380,8 +406,6 @@ __device__ __forceinline__ void qgemm_epilogue_fast(const QgemmParams& p, v16i (
   const int frow = lane & 31, fhalf = lane >> 5;
   const RequantScalars rs = p.rs;
   const int32_t acc16 = p.acc_wrap_shift;
-  // ragged tiles: a group of four results along the packed axis is inside the tensor or outside
-  // (the packed extent is a multiple of 4, of 16 where 16-byte stores are used)
   const int P_ext = ACT_ON_P ? p.M : p.N;
   const int Q_ext = ACT_ON_P ? p.N : p.M;
   if constexpr (!ACT_ON_P) {
@@ -400,8 +424,11 @@ __device__ __forceinline__ void qgemm_epilogue_fast(const QgemmParams& p, v16i (
           const int32_t r1 = finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 1] + c4.y, m4.y, s4.y, acc16, rs);
           const int32_t r2 = finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 2] + c4.z, m4.z, s4.z, acc16, rs);
           const int32_t r3 = finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 3] + c4.w, m4.w, s4.w, acc16, rs);
-          if (!RAGGED || (j < Q_ext && p0 + i_loc < P_ext))
-            store_group<OM>(p.out, (size_t)j * p.N + (p0 + i_loc), r0, r1, r2, r3);
+          const size_t o = (size_t)j * p.N + (p0 + i_loc);
+          if (!RAGGED || (j < Q_ext && p0 + i_loc + 4 <= P_ext))
+            store_group<OM>(p.out, o, r0, r1, r2, r3);
+          else if (j < Q_ext)
+            store_some<OM>(p.out, o, {r0, r1, r2, r3}, P_ext - p0 - i_loc);
         }
       }
     }
@@ -478,9 +505,8 @@ __device__ __forceinline__ void qgemm_epilogue_fast(const QgemmParams& p, v16i (
 // registers 4g .. 4g+3, rows 8g + 4*(l / 32) + 0..3.
 //   ACT_ON_P == false (dense, NHWC): i = output channel n, j = row m, out[m*N + n]
 //   ACT_ON_P == true  (NCHW)       : i = pixel m, j = channel n, out[(b*N + n)*OHW + pix]
-// Tensors whose groups of four results along the packed axis are aligned stores
-// take a straight-line path (ragged tiles included: a group is inside or outside);
-// everything else goes through the element-wise generic path.
+// Dense tiles, and others whose groups of four results along the packed axis are aligned stores,
+// take a straight-line path; NCHW images off a multiple of four are stored one by one.
 template <int WP, int WQ, int TP, int TQ, bool ACT_ON_P, bool PIXPERM = false>
 __device__ __forceinline__ void qgemm_epilogue(const QgemmParams& p, v16i (&acc)[TP][TQ], int p0,
                                                int q0, const int32_t* s_corr,
@@ -493,7 +519,7 @@ __device__ __forceinline__ void qgemm_epilogue(const QgemmParams& p, v16i (&acc)
   const int P_ext = ACT_ON_P ? p.M : p.N;
   const int Q_ext = ACT_ON_P ? p.N : p.M;
   const int ohw = p.g.OH * p.g.OW;
-  const bool fast = p.vec_out;  // groups of four along the packed axis are aligned stores
+  const bool fast = !ACT_ON_P || p.vec_out;  // (vec_out: groups of four along the packed axis are aligned stores)
 
   if (fast) {
     // interior tiles (block-uniform) run without the per-store bounds checks
@@ -561,67 +587,35 @@ __device__ __forceinline__ void qgemm_epilogue(const QgemmParams& p, v16i (&acc)
     return;
   }
 
-  // ---- generic path: any output mode, partial tiles, unaligned outputs
+  // ---- NCHW pixels in the order of the rows (the general kernel), images off a multiple of four: one by one
+  if constexpr (ACT_ON_P && !PIXPERM) {
 #pragma unroll 1
-  for (int tj = 0; tj < TQ; ++tj) {
-    const int j_loc = (wq * TQ + tj) * 32 + frow;
-    const int j = q0 + j_loc;
+    for (int tj = 0; tj < TQ; ++tj) {
+      const int j_loc = (wq * TQ + tj) * 32 + frow;
+      const int j = q0 + j_loc;
 #pragma unroll
-    for (int ti = 0; ti < TP; ++ti) {
+      for (int ti = 0; ti < TP; ++ti) {
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int i_loc = (wp * TP + ti) * 32 + (PIXPERM ? fhalf * 16 + g4 * 4 : g4 * 8 + fhalf * 4);
-        const int i = p0 + i_loc;
-        int32_t v[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int ci = ACT_ON_P ? j_loc : i_loc + r;
-          // acc[..][tj] with a runtime tj would need dynamic register indexing; select instead
-          int32_t raw = 0;
-#pragma unroll
-          for (int x = 0; x < TQ; ++x) raw = (x == tj) ? acc[ti][x][g4 * 4 + r] : raw;
-          int32_t a = raw + s_corr[ci];
-          if (p.acc_wrap_shift) a = wrap_acc_bits(a, p.acc_wrap_shift);
-          if (p.has_rq) a = requant_general(a, s_mult[ci], s_shift[ci], p.rs);
-          v[r] = a;
-        }
-        if (j >= Q_ext || i >= P_ext) continue;
-        // flat offset of (i, j) in the output tensor
-        int64_t off;
-        int b = 0, pix = 0;
-        if constexpr (ACT_ON_P) {
-          b = i / ohw;
-          pix = i - b * ohw;
-          off = ((int64_t)b * p.N + j) * ohw + pix;
-        } else {
-          off = (int64_t)j * p.N + i;
-        }
-        if (p.vec_out && i + 3 < P_ext) {
-          if (p.out_mode == 0)
-            *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.out) + off) =
-                pack4(v[0], v[1], v[2], v[3]);
-          else if (p.out_mode == 1)
-            *reinterpret_cast<int4*>(static_cast<int32_t*>(p.out) + off) =
-                make_int4(v[0], v[1], v[2], v[3]);
-          else
-            *reinterpret_cast<short4*>(static_cast<int16_t*>(p.out) + off) =
-                make_short4((short)v[0], (short)v[1], (short)v[2], (short)v[3]);
-        } else {
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const int i = p0 + (wp * TP + ti) * 32 + g4 * 8 + fhalf * 4;
+          int b = i / ohw;
+          int pix = i - b * ohw;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            if (i + r >= P_ext) break;
-            int64_t o = off + r;
-            if constexpr (ACT_ON_P) {
-              int pr = pix + r, br = b;
-              while (pr >= ohw) { pr -= ohw; ++br; }
-              o = ((int64_t)br * p.N + j) * ohw + pr;
+            // acc[..][tj] with a runtime tj would need dynamic register indexing; select instead
+            int32_t raw = 0;
+#pragma unroll
+            for (int x = 0; x < TQ; ++x) raw = (x == tj) ? acc[ti][x][g4 * 4 + r] : raw;
+            int32_t a = raw + s_corr[j_loc];
+            if (p.acc_wrap_shift) a = wrap_acc_bits(a, p.acc_wrap_shift);
+            if (p.has_rq) a = requant_general(a, s_mult[j_loc], s_shift[j_loc], p.rs);
+            if (j < Q_ext && i + r < P_ext) {
+              const int64_t o = ((int64_t)b * p.N + j) * ohw + pix;
+              if (p.out_mode == 0) static_cast<uint8_t*>(p.out)[o] = (uint8_t)a;
+              else if (p.out_mode == 1) static_cast<int32_t*>(p.out)[o] = a;
+              else static_cast<int16_t*>(p.out)[o] = (int16_t)a;
             }
-            if (p.out_mode == 0)
-              static_cast<uint8_t*>(p.out)[o] = (uint8_t)v[r];
-            else if (p.out_mode == 1)
-              static_cast<int32_t*>(p.out)[o] = v[r];
-            else
-              static_cast<int16_t*>(p.out)[o] = (int16_t)v[r];
+            if (++pix == ohw) { pix = 0; ++b; }
           }
         }
       }

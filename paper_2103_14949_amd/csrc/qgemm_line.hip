@@ -198,7 +198,7 @@ __global__ __launch_bounds__(64 * WP * WQ, 1) void qgemm_line_kernel(QgemmParams
   const int form = finish_channel_terms<NT, BP>(p, chregs, s_corr, s_mult, s_shift, s_c64, nullptr, s_shm1);
   HAGO_STAMP(p, 4);
   static_assert(BQ * (BP + 16) <= 2 * STAGE && (BQ * BP / 16) % NT == 0, "the results are staged in the ring's place");
-  if (p.out_mode == 0 && !p.acc_wrap_shift && p.vec16_out && !p.rs.half_away) {
+  if (p.out_mode == 0 && !p.acc_wrap_shift && !p.rs.half_away) {
     if (form == kRqSat)
       qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqSat>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
     else if (form == kRqFolded)

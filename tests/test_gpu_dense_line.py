@@ -14,7 +14,7 @@ def test_stage_edges(tile, K):
     rng = np.random.default_rng(100 * K + tile)
     hago.set_test_hook(hago.HOOK_STREAM_TILE, tile)
     try:
-        for M, N, act_u8 in ((300, 208, True), (257, 400, False), (1, 16, True), (512, 37, True)):
+        for M, N, act_u8 in ((300, 208, True), (257, 401, False), (1, 16, True), (512, 37, True), (70, 399, True)):
             a = rng.integers(0, 256, (M, K)).astype(np.uint8) if act_u8 else rng.integers(-128, 128, (M, K)).astype(np.int8)
             za = 131 if act_u8 else -7
             w = rng.integers(-127, 128, (N, K)).astype(np.int8)
