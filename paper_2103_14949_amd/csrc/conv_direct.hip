@@ -148,7 +148,8 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
       }
     }
   }
-  struct TilePos { int R0, x0, V0; };  // first stacked row, first column, first staged row of the stack
+  // first stacked row, first column, first staged row of the stack; the image that row lies in, and its row there
+  struct TilePos { int R0, x0, V0, b0, hv0; };
   auto tile_pos = [&](int tl) {
     uint32_t seg, oy;
     const int rt = (int)divide((uint32_t)tl, (uint32_t)p.nseg, p.inv_nseg, seg);
@@ -157,21 +158,31 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
     q.x0 = (int)seg * p.TW;
     const uint32_t b = divide((uint32_t)q.R0, (uint32_t)p.OH, p.inv_oh, oy);
     q.V0 = (int)(b * (uint32_t)p.HV + oy * (uint32_t)p.sr);
+    q.b0 = (int)b;
+    q.hv0 = (int)oy * p.sr;
     return q;
   };
   // image row of staged row v: whether it exists, and its offset (b * C * H + iy rows for NCHW, (b * H + iy) * W pixels for NHWC)
   auto image_row = [&](const TilePos& q, int v, uint32_t& off) {
-    uint32_t hv;
-    const uint32_t b = divide((uint32_t)(q.V0 + v), (uint32_t)p.HV, p.inv_hv, hv);
+    uint32_t hv = (uint32_t)(q.hv0 + v), b = (uint32_t)q.b0;
+    if (p.rows <= p.HV) {  // uniform: the tile crosses one image boundary at most
+      const bool over = hv >= (uint32_t)p.HV;
+      hv -= over ? (uint32_t)p.HV : 0u;
+      b += over ? 1u : 0u;
+    } else {
+      b = divide((uint32_t)(q.V0 + v), (uint32_t)p.HV, p.inv_hv, hv);
+    }
     int iy = (int)hv - p.ph;
     if (p.sr != p.sh) {  // stride beyond the kernel: only the rows the taps touch are staged
       const int oy = (int)hv / p.KH;
       iy = oy * p.sh + ((int)hv - oy * p.KH) - p.ph;
     }
     const bool ok = v >= 0 && b < (uint32_t)p.B && (unsigned)iy < (unsigned)p.H;
-    off = ok ? (NHWC ? (b * (uint32_t)p.H + (uint32_t)iy) * (uint32_t)p.W : (b * (uint32_t)p.C) * (uint32_t)HW + (uint32_t)(iy * p.W)) : 0u;
+    off = NHWC ? (b * (uint32_t)p.H + (uint32_t)iy) * (uint32_t)p.W : b * (uint32_t)(p.C * HW) + (uint32_t)(iy * p.W);
     return ok;
   };
+  const __amdgpu_buffer_rsrc_t rs_act =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.act), 0, (int)p.act_bytes, 0x00020000);
   uint32_t u_mask[NU];  // bytes of the loaded dwords that lie inside the image (NHWC: all or none)
   int32_t u_shift[NU];  // bits that move them into place (> 0: right)
   auto load_input = [&](const TilePos& q, int c0) {
@@ -195,25 +206,17 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
 #pragma unroll
         for (int i = 0; i < 4; ++i) raw[n][i] = (uint32_t)v[i];
       } else {
-        // the quad's dword, pulled inside the row; channels beyond C repeat the last one (their weights are 0)
+        // the quad's dword, pulled inside the row; channels beyond C read what follows, or nothing beyond the tensor (their
+        // weights are 0).  A quad without a byte in the image is out of the descriptor's range and reads 0.
         const int ixc = ix < 0 ? 0 : (ix > p.W - 4 ? p.W - 4 : ix);
         const int d = ix - ixc;
         u_mask[n] = !row_ok || d >= 4 || d <= -4 ? 0u : (d >= 0 ? 0xffffffffu >> (8 * d) : 0xffffffffu << (-8 * d));
         u_shift[n] = d >= 4 || d <= -4 ? 0 : 8 * d;
-        const int c = c0 + u_c[n] < p.C ? c0 + u_c[n] : p.C - 1;
-        const int left = p.C - 1 - c;
-        uint32_t at = off + (uint32_t)c * (uint32_t)HW + (uint32_t)ixc;
-        if (p.aligned && !u_mask[n]) {  // (the aligned form stores the dwords as they are)
+        const uint32_t at = u_mask[n] ? off + (uint32_t)(c0 + u_c[n]) * (uint32_t)HW + (uint32_t)ixc : 0x80000000u;
 #pragma unroll
-          for (int k = 0; k < 16; ++k) raw[n][k] = p.pad4;
-        }
-        if (u_mask[n]) {
-#pragma unroll
-          for (int k = 0; k < 16; ++k) {
-            if (SMALL && k % 4 == 0 && k >= p.small_c) break;  // uniform
-            raw[n][k] = *reinterpret_cast<const u32_any*>(p.act + at);
-            at += k < left ? (uint32_t)HW : 0u;
-          }
+        for (int k = 0; k < 16; ++k) {
+          if (SMALL && k % 4 == 0 && k >= p.small_c) break;  // uniform
+          raw[n][k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs_act, at + (uint32_t)(k * HW), 0, 0);
         }
       }
     }
@@ -270,8 +273,8 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
 #pragma unroll
           for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(dst + i * PS) = make_uint4(o[0][i], o[1][i], o[2][i], o[3][i]);
         };
-        const uint32_t flip = p.act_xor4 & mask;
-        if (p.aligned) write([&](uint32_t v) { return v ^ flip; });  // uniform
+        const uint32_t flip = p.act_xor4 & mask, whole = mask ? p.act_xor4 : p.pad4;
+        if (p.aligned) write([&](uint32_t v) { return v ^ whole; });  // uniform: a dword lies inside the image or outside
         else write([&](uint32_t v) { return ((((v >> rs_) << ls_) & mask) ^ flip) | pad; });
       }
     }
@@ -281,7 +284,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   // ---- weights of chunk c0, in batches of UB units per thread whose loads are issued together; channels and output
   // channels that do not exist are zero.  A unit: four channels' nine taps (WT 9), 16 channels of a tap (2), one dword (0).
   const int T = p.KH * p.KW;
-  constexpr int UB = WT == 9 ? 2 : (SMALL ? 6 : 4), WD = WT == 9 ? 9 : (WT == 2 ? 4 : 1);
+  constexpr int UB = WT == 9 ? (WCH == 2 && !MULTI ? 4 : 2) : (SMALL ? 6 : 4), WD = WT == 9 ? 9 : (WT == 2 ? 4 : 1);
   uint32_t wraw[UB][WD];
   const int c4n = p.CC >> 2, c16n = p.CC >> 4;
   const int wper = WT == 9 ? c4n : (WT == 2 ? T * c16n : p.groups * 8);  // units per output channel
@@ -382,12 +385,25 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   load_input(pos, 0);
   const bool need_sum = p.corr_coef != 0;
   if (t == 0) *s_flag = 0;
-  for (int i = t; i < OB; i += NT) {
-    const int o = o0 + i;
-    s_sum[i] = 0;
-    s_corr[i] = o < p.O && p.bias ? p.bias[o] : 0;
-    s_mu[i] = o < p.O && p.has_rq ? rq_mult(p.mult, p.per_channel ? o : 0) : 0;
-    s_sh[i] = o < p.O && p.has_rq ? rq_shift(p.mult, p.shift, p.per_channel ? o : 0) : 1;
+  // a channel's constants stay in registers until its terms are formed: storing them here would wait for every load
+  // before them
+  static_assert(OB <= NT, "a thread has one output channel");
+  int32_t c_bias = 0, c_mu = 0, c_sh = 1;
+  if (t < OB) {
+    const int o = o0 + t;
+    s_sum[t] = 0;
+    if (o < p.O) {
+      if (p.bias) c_bias = p.bias[o];
+      if (p.has_rq) {
+        c_mu = rq_mult(p.mult, p.per_channel ? o : 0);
+        c_sh = rq_shift(p.mult, p.shift, p.per_channel ? o : 0);
+      }
+    }
+    if constexpr (NHWC && AF == 2) {  // (that form has no register to spare)
+      s_corr[t] = c_bias;
+      s_mu[t] = c_mu;
+      s_sh[t] = c_sh;
+    }
   }
 
   // MFMA rows and columns: NCHW pixels x channels, row r of a 32-row block is pixel pix_perm(r) of it (a lane's 16
@@ -464,6 +480,31 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   const uint32_t sflip = sat_flip(p.rs);
   int ch = 0;         // chunk
   v16i acc[AF][2];
+  // The block's terms, when its weight sums are complete.  Folded requantize (32-bit accumulator, constants small enough in
+  // every channel of the block): correction, rounding term and output zero point go into one 64-bit constant, the result is
+  // the high dword of acc * m + k64 shifted by sh - 1; |acc| < 2^30 for reductions up to 2^16, so acc + corr cannot wrap.
+  // Without chunks they are formed behind the staging of the weights, and the barrier behind the input's staging serves
+  // them too (64 -> 128 3x3 stride 2 on 32 x 56 x 56: 10.2 us, 10.4 before; 3 -> 64 7x7 on 8 x 224 x 224,
+  // with the input's loads by descriptor, one addition each, 10.6, 12.2 before).
+  auto form_terms = [&]() {
+    int bad = p.out_mode != 0 || p.acc_wrap_shift != 0 || p.rs.half_away || p.rs.z_out < -256 || p.rs.z_out > 255 || p.C * T > 65536;
+    if (t < OB) {
+      if constexpr (NHWC && AF == 2) {
+        c_bias = s_corr[t];
+        c_mu = s_mu[t];
+        c_sh = s_sh[t];
+      }
+      const int32_t corr = c_bias + (need_sum ? p.corr_coef * s_sum[t] : 0), mu = c_mu, sh = c_sh;
+      bad |= sh < 1 || sh > 19 || corr < -(1 << 30) || corr > (1 << 30);
+      const int64_t k64 = (int64_t)corr * mu + ((int64_t)1 << (30 + (sh & 31))) + ((int64_t)zc << (31 + (sh & 31)));
+      s_corr[t] = corr;
+      s_mu[t] = mu;
+      s_sh[t] = sh;
+      s_fold[t] = make_int4((int)(uint32_t)k64, (int)(k64 >> 32), mu, sh - 1);
+    }
+    if (bad) atomicOr(s_flag, 1);
+    if (MULTI) __syncthreads();
+  };
   if constexpr (!MULTI) {  // resident for every tile
     __syncthreads();
     if constexpr (SMALL) stage_weights_small(need_sum);
@@ -472,6 +513,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   for (;;) {
     __syncthreads();   // the previous chunk has been consumed
     if constexpr (MULTI) stage_weights(ch * p.CC, false, first && need_sum);
+    if (!MULTI && first) form_terms();
     store_input();     // registers -> LDS
     __syncthreads();
     // the next chunk's or tile's loads go out now
@@ -568,23 +610,8 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
       continue;
     }
     ch = 0;
-    if (first) {
-      // (the weight sums of every chunk are complete: the barrier above follows the last one's staging)
-      // Folded requantize (32-bit accumulator, constants small enough in every channel of the block): correction,
-      // rounding term and output zero point go into one 64-bit constant, the result is the high dword of
-      // acc * m + k64 shifted by sh - 1; |acc| < 2^30 for reductions up to 2^16, so acc + corr cannot wrap.
-      int bad = p.out_mode != 0 || p.acc_wrap_shift != 0 || p.rs.half_away || p.rs.z_out < -256 || p.rs.z_out > 255 || p.C * T > 65536;
-      for (int i = t; i < OB; i += NT) {
-        const int32_t corr = s_corr[i] + (need_sum ? p.corr_coef * s_sum[i] : 0), mu = s_mu[i], sh = s_sh[i];
-        bad |= sh < 1 || sh > 19 || corr < -(1 << 30) || corr > (1 << 30);
-        const int64_t k64 = (int64_t)corr * mu + ((int64_t)1 << (30 + (sh & 31))) + ((int64_t)zc << (31 + (sh & 31)));
-        s_corr[i] = corr;
-        s_fold[i] = make_int4((int)(uint32_t)k64, (int)(k64 >> 32), mu, sh - 1);
-      }
-      if (bad) atomicOr(s_flag, 1);
-      __syncthreads();
-      fold = *s_flag == 0;
-    }
+    if (first && MULTI) form_terms();  // (the sums of the last chunk are complete)
+    if (first) fold = *s_flag == 0;
     first = false;
 
     // ---- epilogue

@@ -720,7 +720,7 @@ hipError_t launch_qgemm_any(const QgemmParams& p, bool i16, int form, hipStream_
     // 141 x 2145 -> 1327 9.5, 10.6; but 305 tiles of 1937 x 3015 -> 154 24, 13; int16 332 x 131 -> 721 4.5, 5.9; 512 x 768 ->
     // 768 9.2, 8.0), or their reductions are one or two groups (int8 2572 x 25 -> 132 4.1, 5.0; int16 1024 x 64 -> 768 5.0, 4.3).
     if (t32 <= 256) form = 0;
-    else if (!i16 && t32 * groups <= 512) form = 1;
+    else if (!i16 && t32 * groups <= 1024) form = 1;
     // 128 x 128 tiles once four rounds of 64 x 64 ones would run (2000 x 2001 -> 2003 24 against 34)
     else if (t64 >= 1024) form = 3;
     // two sets of wavefronts (1021 x 1283 -> 1001 8.6, 9.9 with one; int16 1024 x 768 -> 768 8.1, 9.3)
