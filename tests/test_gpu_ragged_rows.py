@@ -74,3 +74,16 @@ def test_requantize_int16_many_wavefronts():
     da, rq = dev(a), gpu_requant([2 ** 30], [7])
     for _ in range(4):
         assert_same(host(hago.requantize(da, rq)), want, "int16, flat")
+
+
+@pytest.mark.parametrize("shape", [(70, 200, 1), (5000, 129, 1), (33, 131, 3), (300, 768, 1), (16, 100, 49), (1100, 4001, 1), (20000, 33, 1),
+                                   (64, 43, 3)])
+def test_absmax_by_slabs_of_channels(shape):
+    """Patterns of more than 32 vectors, whole and ragged slabs of 16 vectors, channels that run on over several elements."""
+    rng = np.random.default_rng(sum(shape))
+    x = rng.normal(0, 1, shape).astype(np.float32)
+    x[:, ::5] *= -7.0
+    x[0, 0, 0] = np.nan
+    x[-1, -1, -1] = -np.inf
+    x[:, shape[1] // 2] = 0.0
+    assert_same_bits(host(hago.absmax(dev(x))), ref.absmax(x, True), f"absmax {shape}")

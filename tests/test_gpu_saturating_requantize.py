@@ -58,3 +58,17 @@ def test_whole_range(name):
             assert_same(host(got), want, f"{name} u8={act_u8} {out_u8, z, clip, s0, s1}")
             if s0 >= 5 and s1 <= 9 and clip in ((-128, 127), (0, 255)):
                 assert (want == clip[0]).any() and (want == clip[1]).any() and len(np.unique(want)) > 100 or groups > 1
+
+
+@pytest.mark.parametrize("shape", [(300, 64, 1), (90, 35, 1), (64, 12, 3), (5000, 8, 1)])
+@pytest.mark.parametrize("dtype", [np.int32, np.int16])
+def test_whole_range_standalone(shape, dtype):
+    """The standalone operator on rows whose channels a lane keeps."""
+    rng = np.random.default_rng(sum(shape))
+    acc = rng.integers(np.iinfo(dtype).min, np.iinfo(dtype).max, shape, endpoint=True).astype(dtype)
+    acc[: shape[0] // 2] >>= 9
+    for out_u8, z, clip, (s0, s1) in FORMS:
+        mult = rng.integers(2 ** 30, 2 ** 31, shape[1], dtype=np.int64).astype(np.int32)
+        shift = rng.integers(s0, s1 + 1, shape[1]).astype(np.int32)
+        assert_same(host(hago.requantize(dev(acc), gpu_requant(mult, shift, out_u8, z, clip))),
+                    ref.requantize(acc, ref_requant(mult, shift, out_u8, z, clip)), f"{shape} {out_u8, z, clip, s0, s1}")
