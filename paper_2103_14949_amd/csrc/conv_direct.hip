@@ -633,6 +633,38 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
           const int cl = 64 * wch + 32 * tn + 16 * h, o = o0 + cl;  // 16 consecutive channels
           if (!px_ok || o >= p.O) continue;
           const int left = p.O - o;
+          if (fold && sat) {  // uniform
+            uint32_t dw[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              int32_t y[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const int4 k = s_fold[cl + 4 * g + e];
+                y[e] = (int32_t)(((int64_t)acc[f][tn][4 * g + e] * (int64_t)k.z + (int64_t)(((uint64_t)(uint32_t)k.y << 32) | (uint32_t)k.x)) >> 32) >> k.w;
+              }
+              ashr_sat_pair<0>(dw[g], y[0], y[1], 0);
+              ashr_sat_pair<1>(dw[g], y[2], y[3], 0);
+              dw[g] ^= sflip;
+              __builtin_amdgcn_sched_barrier(0);  // (four products at a time)
+            }
+            uint8_t* dst = static_cast<uint8_t*>(p.out) + prow + o;
+            if (left >= 16) {  // one store of 16 bytes: a store per dword is a pass of the memory pipe per lane each
+              *reinterpret_cast<v4i_any*>(dst) = v4i{(int)dw[0], (int)dw[1], (int)dw[2], (int)dw[3]};
+            } else {
+#pragma unroll
+              for (int g = 0; g < 4; ++g) {
+                if (4 * g + 4 <= left) {
+                  *reinterpret_cast<u32_any*>(dst + 4 * g) = dw[g];
+                } else {
+#pragma unroll
+                  for (int e = 0; e < 3; ++e)
+                    if (4 * g + e < left) dst[4 * g + e] = (uint8_t)(dw[g] >> (8 * e));
+                }
+              }
+            }
+            continue;
+          }
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
             int32_t v[4];
@@ -641,9 +673,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
               for (int e = 0; e < 4; ++e) {
                 const int4 k = s_fold[cl + 4 * g + e];
                 const int64_t pr = (int64_t)acc[f][tn][4 * g + e] * (int64_t)k.z + (int64_t)(((uint64_t)(uint32_t)k.y << 32) | (uint32_t)k.x);
-                v[e] = (int32_t)(pr >> 32) >> k.w;
-                if (!sat) v[e] = med3(v[e], lo_abs, hi_abs);
-                else if (4 * g + 4 > left) v[e] = med3(v[e], -128, 127) ^ (int32_t)(sflip & 0xffu);  // (stored one by one)
+                v[e] = med3((int32_t)(pr >> 32) >> k.w, lo_abs, hi_abs);
               }
             } else {
               const int4 c4 = *reinterpret_cast<const int4*>(s_corr + cl + 4 * g);
@@ -659,12 +689,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
             }
             uint8_t* dst = static_cast<uint8_t*>(p.out) + (prow + o + 4 * g) * esz;
             if (4 * g + 4 <= left) {
-              if (p.out_mode == 0 && fold && sat) {
-                uint32_t dw;
-                ashr_sat_pair<0>(dw, v[0], v[1], 0);
-                ashr_sat_pair<1>(dw, v[2], v[3], 0);
-                *reinterpret_cast<u32_any*>(dst) = dw ^ sflip;
-              } else if (p.out_mode == 0) {
+              if (p.out_mode == 0) {
                 *reinterpret_cast<u32_any*>(dst) = pack4_perm(v[0], v[1], v[2], v[3]);
               } else if (p.out_mode == 1) {
                 *reinterpret_cast<v4i_any*>(dst) = v4i{v[0], v[1], v[2], v[3]};
