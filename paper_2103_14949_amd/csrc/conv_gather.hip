@@ -12,6 +12,10 @@
 //   mask.  C % 16 != 0: the last chunk of a tap is moved back to end with it, and the weights of the channels it repeats
 //   are zeroed.  The rows of the weight operand are permuted so that a lane's 16 results of a 32-channel tile are 16
 //   consecutive channels.
+//   MIS: pixels or weights off multiples of four bytes.  Such a 16-byte load costs four times an aligned one (128 cycles of
+//   the memory pipe for the 32 x 2 pieces of a wavefront, 32 so), so the aligned dwords that hold the bytes are loaded, one
+//   more per piece, and shifted into place (us as loaded directly and so: 61 -> 64 3x3 on 8 x 41 x 41 7.2, 6.3; 201 -> 120 3x3 on one 14 x 14
+//   image 11.0, 8.3; 31 -> 60 5x5 on 3 x 40 x 40 7.8, 6.3).
 #include "hago_device.h"
 #include "launch.h"
 
@@ -26,6 +30,7 @@ typedef uint32_t u32_u __attribute__((aligned(1)));
 typedef int v2i_u __attribute__((ext_vector_type(2), aligned(1)));
 
 constexpr uint32_t kOob = 0x80000000u;
+constexpr uint32_t kBeyond = 0x80000010u;  // the same behind whole dwords of tensors of up to 2^31 bytes, from any byte
 
 struct CgParams {
   const uint8_t* act;
@@ -51,7 +56,7 @@ __device__ __forceinline__ uint32_t div_by(uint32_t n, uint32_t d, uint32_t inv)
 __device__ __forceinline__ int channel_of_row(int r) { return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3); }
 
 // MODE 0: requantized 8-bit, 1: raw int32, 2: raw int16.
-template <int MODE, int TP, int TC, int KS>
+template <int MODE, bool MIS, int TP, int TC, int KS>
 __global__ __launch_bounds__(64 * KS) void conv_gather_kernel(CgParams p) {
   constexpr int NTILE = TP * TC;
   constexpr int UPW = 4 * NTILE / KS;   // groups of four registers that a wavefront finishes (1, 2 or 4 of one tile)
@@ -74,8 +79,29 @@ __global__ __launch_bounds__(64 * KS) void conv_gather_kernel(CgParams p) {
   const uint32_t tile_m = div_by(id, (uint32_t)p.tiles_n, p.inv_tn);
   const int m0 = (int)tile_m * 32 * TP, n0 = (int)(id - tile_m * (uint32_t)p.tiles_n) * 32 * TC;
 
-  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.act), 0, (int)p.act_bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(p.wgt), 0, (int)p.wgt_bytes, 0x00020000);
+  // MIS: descriptors of the whole dwords that hold the tensors (their first and last hold bytes of the tensor)
+  const uint32_t a0 = MIS ? (uint32_t)reinterpret_cast<uintptr_t>(p.act) & 3u : 0u;
+  const uint32_t w0 = MIS ? (uint32_t)reinterpret_cast<uintptr_t>(p.wgt) & 3u : 0u;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(p.act) - a0, 0, (int)(MIS ? (p.act_bytes + a0 + 3u) & ~3u : p.act_bytes), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<int8_t*>(p.wgt) - w0, 0, (int)(MIS ? (p.wgt_bytes + w0 + 3u) & ~3u : p.wgt_bytes), 0x00020000);
+  struct Piece {  // 16 bytes as loaded
+    v4i v;
+    uint32_t more;
+    __device__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+      const uint32_t at = MIS ? off & ~3u : off;
+      v = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, 0));
+      if constexpr (MIS) more = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, at + 16, 0, 0);
+    }
+    __device__ void settle(uint32_t off) {  // the offset, modulo 4
+      if constexpr (MIS) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+          v[d] = (int)__builtin_amdgcn_alignbyte(d < 3 ? (uint32_t)v[d + 1] : more, (uint32_t)v[d], off);
+      }
+    }
+  };
   // the lane's pixels: byte offset of the window's first tap (it may lie before the tensor), and the filter rows and
   // columns that are inside the image
   uint32_t poff[TP], rows_in[TP], cols_in[TP];
@@ -86,7 +112,7 @@ __global__ __launch_bounds__(64 * KS) void conv_gather_kernel(CgParams p) {
     const uint32_t b = div_by((uint32_t)m, ohw, p.inv_ohw), r = (uint32_t)m - b * ohw;
     const uint32_t oy = div_by(r, (uint32_t)p.OW, p.inv_ow);
     const int iy = (int)oy * p.sh - p.ph, ix = (int)(r - oy * (uint32_t)p.OW) * p.sw - p.pw;
-    poff[t] = (uint32_t)((((int)b * p.H + iy) * p.W + ix) * p.C);
+    poff[t] = (uint32_t)((((int)b * p.H + iy) * p.W + ix) * p.C) + a0;
     auto inside = [](int first, int taps, int size) {  // bit k: 0 <= first + k < size
       const int lo = first < 0 ? -first : 0, hi = size - first < taps ? size - first : taps;
       return lo < hi ? (0xffffffffu >> (32 - hi)) & (0xffffffffu << lo) : 0u;
@@ -99,7 +125,7 @@ __global__ __launch_bounds__(64 * KS) void conv_gather_kernel(CgParams p) {
 #pragma unroll
   for (int t = 0; t < TC; ++t) {
     const int ch = n0 + 32 * t + channel_of_row(n);
-    woff[t] = ch < p.N ? (uint32_t)ch * kbytes : kOob;
+    woff[t] = ch < p.N ? (uint32_t)ch * kbytes + w0 : kBeyond;
   }
 
   v16i acc[TP][TC];
@@ -114,8 +140,8 @@ __global__ __launch_bounds__(64 * KS) void conv_gather_kernel(CgParams p) {
   }
   const int s_first = p.steps * wave / KS, s_last = p.steps * (wave + 1) / KS;
   for (int s0 = s_first; s0 < s_last; s0 += U) {
-    v4i pa[U][TP], wa[U][TC];
-    uint32_t flip[U][TP], dup[U];
+    Piece pa[U][TP], wa[U][TC];
+    uint32_t flip[U][TP], dup[U], ptap[U], wtap[U];  // (ptap, wtap: what the step adds to the offsets)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u < s_last) {  // uniform
@@ -124,18 +150,18 @@ __global__ __launch_bounds__(64 * KS) void conv_gather_kernel(CgParams p) {
         const uint32_t ky = div_by(tap, (uint32_t)p.KW, p.inv_kw), kx = tap - ky * (uint32_t)p.KW;
         const uint32_t c0 = 16 * j < (uint32_t)p.C - 16 ? 16 * j : (uint32_t)p.C - 16;
         dup[u] = 16 * j - c0;  // channels of the chunk before it, repeated
-        const uint32_t toff = (ky * (uint32_t)p.W + kx) * (uint32_t)p.C + c0;
+        ptap[u] = (ky * (uint32_t)p.W + kx) * (uint32_t)p.C + c0;
+        wtap[u] = tap * (uint32_t)p.C + c0;
         const bool real = q < (uint32_t)p.chunks;
 #pragma unroll
         for (int t = 0; t < TP; ++t) {
           const bool ok = real && ((rows_in[t] >> ky) & (cols_in[t] >> kx) & 1u);
           flip[u][t] = ok ? p.x4 : p.pad4;
-          pa[u][t] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(ra, ok ? poff[t] + toff : kOob, 0, 0));
+          pa[u][t].load(ra, ok ? poff[t] + ptap[u] : kBeyond);
         }
 #pragma unroll
         for (int t = 0; t < TC; ++t)
-          wa[u][t] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
-              rw, real && woff[t] != kOob ? woff[t] + tap * (uint32_t)p.C + c0 : kOob, 0, 0));
+          wa[u][t].load(rw, real && woff[t] != kBeyond ? woff[t] + wtap[u] : kBeyond);
       }
     }
 #pragma unroll
@@ -143,22 +169,24 @@ __global__ __launch_bounds__(64 * KS) void conv_gather_kernel(CgParams p) {
       if (s0 + u < s_last) {  // uniform
 #pragma unroll
         for (int t = 0; t < TC; ++t) {
+          wa[u][t].settle(woff[t] + wtap[u]);
           if (p.C & 15) {  // uniform
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
               const uint32_t o = dup[u] < 4u * d ? 0u : dup[u] - 4u * d;
-              wa[u][t][d] = o < 4u ? wa[u][t][d] & (int)(0xffffffffu << (8 * o)) : 0;
+              wa[u][t].v[d] = o < 4u ? wa[u][t].v[d] & (int)(0xffffffffu << (8 * o)) : 0;
             }
           }
 #pragma unroll
-          for (int d = 0; d < 4; ++d) wsum[t] = __builtin_amdgcn_sdot4(wa[u][t][d], 0x01010101, wsum[t], false);
+          for (int d = 0; d < 4; ++d) wsum[t] = __builtin_amdgcn_sdot4(wa[u][t].v[d], 0x01010101, wsum[t], false);
         }
 #pragma unroll
         for (int i = 0; i < TP; ++i) {
+          pa[u][i].settle(poff[i] + ptap[u]);
 #pragma unroll
-          for (int d = 0; d < 4; ++d) pa[u][i][d] ^= (int)flip[u][i];
+          for (int d = 0; d < 4; ++d) pa[u][i].v[d] ^= (int)flip[u][i];
 #pragma unroll
-          for (int t = 0; t < TC; ++t) acc[i][t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wa[u][t], pa[u][i], acc[i][t], 0, 0, 0);
+          for (int t = 0; t < TC; ++t) acc[i][t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wa[u][t].v, pa[u][i].v, acc[i][t], 0, 0, 0);
         }
       }
     }
@@ -272,8 +300,12 @@ hipError_t launch_shape(const CgParams& p, int mode, hipStream_t st) {
   q.tiles_n = (q.N + 32 * TC - 1) / (32 * TC);
   const int64_t ids = (int64_t)((q.M + 32 * TP - 1) / (32 * TP)) * q.tiles_n;
   q.inv_tn = q.tiles_n > 1 && ids * q.tiles_n < (1ll << 32) ? (uint32_t)(((1ull << 32) + q.tiles_n - 1) / q.tiles_n) : 0u;
-  auto kern = mode == 0 ? conv_gather_kernel<0, TP, TC, KS> : mode == 1 ? conv_gather_kernel<1, TP, TC, KS> : conv_gather_kernel<2, TP, TC, KS>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
+  auto run = [&]<bool MIS>() {
+    auto kern = mode == 0 ? conv_gather_kernel<0, MIS, TP, TC, KS> : mode == 1 ? conv_gather_kernel<1, MIS, TP, TC, KS> : conv_gather_kernel<2, MIS, TP, TC, KS>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
+  };
+  if (q.C % 4 != 0 || ((reinterpret_cast<uintptr_t>(q.act) | reinterpret_cast<uintptr_t>(q.wgt)) & 3u) != 0) run.template operator()<true>();
+  else run.template operator()<false>();
   return hipGetLastError();
 }
 
@@ -644,15 +676,16 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace,
   p.acc_wrap_shift = a.acc_wrap_shift;
   p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
   const int mode = a.has_rq ? 0 : (a.acc16 ? 2 : 1);
-  // Microseconds.  Here: 3 and, per CU, 0.042 (about 100 cycles of the memory pipe) for every operand load of a tile, nearly
-  // twice that where they are unaligned (the one-launch kernel loses 1.6 there); a step of 64 x 64 is four loads, of 32 x 32 two.  The other kernels: 6 and their
+  // Microseconds, fitted to 36 layers drawn at random (each within 12%).  Here, per tile of a CU: 2.3 and 0.108 a step for 64 x
+  // 64, 0.53 and 0.059 for 32 x 32, a step's part 1.4 times that where the operands' rows are unaligned (the one-launch
+  // kernel loses 1.6 there).  The other kernels: 6 and their
   // rate, or the length of the reduction where there are few tiles.  Measured (here, other): 16 x 28 x 28 64 -> 64 3x3 5.4,
   // 8.4; one image 3.9, 7.1; 32 x 14 x 14 128 -> 128 8.4, 12.0; 8 x 56 x 56 64 -> 128 stride 2 5.8, 10.4; 57 x 56
   // 224 -> 224 7x7 stride 2 31, 66; 4 x 40 x 40 100 -> 200 1x1 stride 2 3.9, 7.8; but 32 x 28 x 28 128 -> 128 22.7, 15.1.
   auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
-  const double step = 0.042 * p.steps * (cg.C % 4 ? 1.8 : 1.0);
-  auto time = [&](int64_t n, int loads) { return 3.0 + step * loads * (n > 256 ? (double)n / 256 : 1.0); };
-  const double t64 = time(tiles(64), 4), t32 = time(tiles(32), 2);
+  const double step = p.steps * (cg.C % 4 ? 1.4 : 1.0);
+  auto time = [&](int64_t n, double tile, double per_step) { return (tile + per_step * step) * (n > 256 ? (double)n / 256 : 1.0); };
+  const double t64 = 1.6 + time(tiles(64), 2.3, 0.108), t32 = 2.5 + time(tiles(32), 0.53, 0.059);
   int shape = forced_shape;
   if (shape < 0) {
     const double rate = (double)a.M * a.N * a.K / 0.41e9, length = (double)a.K / 256;
@@ -715,7 +748,9 @@ bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_works
   // 64 x 32 x 32 3 -> 16 6.6, 8.6.
   const double step = cg.stride_w > 1 ? 1.8 * p.steps : (double)p.steps;
   const double r32 = (double)p.tiles * ((a.N + 31) / 32) / 256, r64 = (double)p.tiles * ((a.N + 63) / 64) / 256;
-  const double t32 = (r32 > 1 ? r32 : 1.0) * (0.4 + 0.12 * step), t64 = (r64 > 1 ? r64 : 1.0) * (0.4 + 0.15 * step);
+  // (long reductions of neighbouring pixels: blocks of 32 by eight wavefronts, 34 -> 140 5x5 on 88 x 87 18.8, with 64 by four 25.6)
+  const bool deep = p.steps >= 24 && cg.stride_w == 1;
+  const double t32 = (r32 > 1 ? r32 : 1.0) * (0.4 + 0.12 * step), t64 = (r64 > 1 ? r64 : 1.0) * (0.4 + 0.15 * step) * (deep ? 1.4 : 1.0);
   const bool alone = p.steps <= 2 && r64 >= 4;
   int shape = forced_shape;
   if (shape < 0) {
@@ -723,7 +758,7 @@ bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_works
     const double t = 3.8 + (double)a.M * a.N * (cg.nhwc ? 2.4 : mode == 0 ? 1 : mode == 1 ? 4 : 2) / 1.2e6 + (alone ? 0.35 * r64 : t32 < t64 ? t32 : t64) + (p.steps > 18 ? 0.1 * (p.steps - 18) : 0.0);
     const double base = has_workspace && (cg.nhwc || cg.W % 4 == 0) ? 7.5 : 8.5;  // (the rewrite is fast there)
     if (t >= base + (double)a.M * a.N * a.K / 0.41e9 + (double)a.K / (has_workspace || taps == 9 || taps == 1 ? 450 : 70)) return false;
-    shape = alone ? 3 : t64 < t32 ? 1 : p.steps >= 24 && r32 <= 1 ? 0 : 2;
+    shape = alone ? 3 : t64 < t32 ? 1 : deep || (p.steps >= 12 && r32 <= 1) ? 0 : 2;
   }
   switch (shape) {
     case 0: *err = launch_nchw<1, 8>(p, mode, st); break;

@@ -62,6 +62,29 @@ def test_gathered_convolution(case, shape, layout, gemm_path):
         hago.set_test_hook(hago.HOOK_GENERAL_TILE, -1)
 
 
+@pytest.mark.parametrize("C", [16, 17, 18, 19, 36])
+@pytest.mark.parametrize("off_a,off_w", [(1, 0), (0, 2), (3, 1), (2, 3)])
+@pytest.mark.parametrize("shape", [0, 1, 2])
+def test_operands_at_any_byte(C, off_a, off_w, shape, gemm_path):
+    """Rows loaded as aligned dwords: tensors that start and end inside a dword, at the very edges of what is theirs."""
+    rng = np.random.default_rng(100 * C + 10 * off_a + off_w)
+    a, za = rng.integers(0, 256, (2, 5, 7, C)).astype(np.uint8), 131
+    w = rng.integers(-127, 128, (35, 3, 3, C)).astype(np.int8)
+    def placed(x, off):
+        whole = torch.full((x.size + 32,), 77, dtype=torch.uint8, device="cuda").view(dev(x).dtype)
+        at = whole[16 + off: 16 + off + x.size].view(x.shape)
+        at.copy_(dev(x))
+        return at
+    want = ref.qconv2d(a, za, w, None, ref.NHWC, (1, 1), (1, 1), 1)
+    gemm_path(4)
+    hago.set_test_hook(hago.HOOK_GENERAL_TILE, shape)
+    try:
+        got = hago.qconv2d(placed(a, off_a), act_qtype(a, za), placed(w, off_w), hago.QType(hago.I8), None, hago.NHWC, (1, 1), (1, 1), 1)
+        assert_same(host(got), want, f"C={C} off {off_a},{off_w}")
+    finally:
+        hago.set_test_hook(hago.HOOK_GENERAL_TILE, -1)
+
+
 @pytest.mark.parametrize("layout,C,H,W,KH,stride", [
     ("nchw", 31, 2, 1070000, 5, (1, 4096)),    # image below 2^26 elements, the filter's last tap beyond
     ("nchw", 30, 2, 1070000, 3, (1, 4096)),    # both below
