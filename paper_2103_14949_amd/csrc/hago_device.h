@@ -117,6 +117,13 @@ __device__ __forceinline__ void ashr_sat_pair(uint32_t& dst, int32_t a, int32_t 
     asm("v_ashr_pk_i8_i32 %0, %1, %2, %3 op_sel:[0,0,0,1]" : "+v"(dst) : "v"(a), "v"(b), "v"(sh));
 }
 
+// v, unknown to the optimizer.  Where several forms of an epilogue follow one another, it widens the factors of their
+// products to 64 bits once, in front of all, and the products then take a full 64 x 64 multiply instead of v_mad_i64_i32.
+__device__ __forceinline__ int32_t opaque(int32_t v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
 // Whether the output's clip limits are its container's whole range, so that this saturation is the clip.  sat_bias is added
 // to the output zero point (inside the 64-bit constant of the folded forms) to centre the range on int8's, and sat_flip
 // undoes it in the packed dword: 0 and 0 for int8, -128 and 0x80 per byte for uint8.

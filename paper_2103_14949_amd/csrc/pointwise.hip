@@ -9,7 +9,7 @@
 // lane then owns one output channel and, per group of accumulator registers, consecutive pixels, which are packed and
 // stored together.  Every block of 32 output channels reads the input again, from the cache; against the forms that read
 // it once (conv_direct.hip, or a channel-last copy in the workspace and qgemm_dma.hip) that is the faster one up to the
-// largest layers (us here, there without and with a workspace: 64 -> 384 on 8 x 56 x 56 7.9, 12.7; 512 -> 128 on
+// largest layers (us here, there without and with a workspace: 64 -> 384 on 8 x 56 x 56 6.5, 12.7; 512 -> 128 on
 // 4 x 28 x 28 5.3, 10.6; 256 -> 256 on 32 x 28 x 28 9.8, 11.8, 15.4; 512 -> 512 29.9, 28.2, 28.1; 1024 -> 1024 on
 // 32 x 14 x 14 26, 38, 27.5), so it serves every layer of its kind.
 //
@@ -54,8 +54,13 @@ struct PwArgs {
 // lane exchange) turn the 16 dwords into the 16 k-bytes of each of the lane's four pixels, and pixel 4i + j becomes row i
 // of row tile j: four MFMAs share one weight operand.  On the way out lane (n, h) then holds, for its output channel,
 // registers (g, e) of tile j = pixel 4 * (8g + 4h + e) + j: the four tiles pack into one dword and the four e into 16
-// contiguous bytes.  (Passing the results through LDS, so that eight lanes write the 128 bytes of a channel, was slower:
-// 24 -> 144 channels on 32 x 56 x 56 11.2 us, 8.9 as they are.)
+// contiguous bytes.  64 lanes that store 16 bytes each to 32 channels take 168 cycles of the memory pipe (256 off 16 bytes),
+// a bound for large images; so pieces of one channel are brought together first, 64 bytes of it in the four lanes of a
+// quad: the two halves of the wavefront swap registers (v_permlane32_swap), the lanes of a quad transpose four by DPP (raw results: a
+// lane's four e are 64 or 32 bytes).  Us with the lanes' own pieces stored and so: 24 -> 144 channels on 32 x 56 x 56 8.1, 7.6, on 16 x 55 x 55 6.0, 5.1;
+// 64 -> 384 on 8 x 56 x 56 7.75, 6.5; raw 32 -> 192 on 16 x 28 x 28 6.6, 4.6.  (Through LDS: slower than either.)
+//   SMALL: images of less than 128 pixels, whose lanes store their own pieces, whole or by fours (64 -> 384 raw on 8 x 9 x
+//     9 3.3 us, 3.7 otherwise).
 // Rows start at any byte (the loads and stores are unaligned ones).  The last tile of an image is moved back to end with
 // it, so that tiles are whole and pixels covered twice get the same value; of an image of less than 128 pixels the last
 // four are.
@@ -68,7 +73,25 @@ typedef uint32_t u32_u __attribute__((aligned(1)));
 typedef v4i v4i_u __attribute__((aligned(1)));
 typedef int v2i_u __attribute__((ext_vector_type(2), aligned(1)));
 
-template <int MODE, bool ACC16, int KS, int CH>
+// d[t] of lane r of a quad <-> d[r] of its lane t.
+template <int D>
+__device__ __forceinline__ void quad_transpose(uint32_t (&d)[4][D], int lane) {
+  auto exchange = [&]<int CTRL>(uint32_t& lower, uint32_t& upper, bool high) {
+    const uint32_t from_upper = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upper, CTRL, 0xf, 0xf, true);
+    const uint32_t from_lower = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lower, CTRL, 0xf, 0xf, true);
+    lower = high ? from_upper : lower;
+    upper = high ? upper : from_lower;
+  };
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    exchange.template operator()<0xB1>(d[0][k], d[1][k], lane & 1);  // quad_perm 1,0,3,2
+    exchange.template operator()<0xB1>(d[2][k], d[3][k], lane & 1);
+    exchange.template operator()<0x4E>(d[0][k], d[2][k], lane & 2);  // quad_perm 2,3,0,1
+    exchange.template operator()<0x4E>(d[1][k], d[3][k], lane & 2);
+  }
+}
+
+template <int MODE, bool ACC16, int KS, int CH, bool SMALL>
 __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
   constexpr int kPart = 65;  // dwords of a lane's partial sums: 64 accumulators and the row sum (odd: no bank conflicts)
   __shared__ int32_t lds[KS == 1 ? 1 : KS * 64 * kPart];
@@ -173,10 +196,10 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
   const RequantScalars rs = p.rs;
   constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
   // results of output channel n from the accumulators (KS = 4: of register group `wave` only, in the first four registers)
-  auto finish = [&](int n, Rq rq) {
+  auto finish = [&](int n0, int n, Rq rq) {
     const int32_t corr = rq.bias + p.corr_coef * wsum;
     const int64_t rnd = (int64_t)1 << (30 + rq.sh);
-    uint8_t* const orow = static_cast<uint8_t*>(p.out) + ((int64_t)b * N + n) * HW * kEsz;
+    uint8_t* const orow = static_cast<uint8_t*>(p.out) + ((int64_t)b * N + n) * HW;  // (8-bit results)
     // FOLD (requantized, 32-bit accumulator, every lane's constants small enough): the correction
     // term, the rounding term and the output zero point go into one 64-bit constant per lane, so
     // an output is clamp((acc * m + k64) >> (31 + sh)) against the absolute bounds:
@@ -184,7 +207,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
     // acc + corr cannot wrap when |corr| <= 2^30 and |acc| <= 2^30 (|acc| <= C * 2^15 < 2^30 for
     // C < 2^15).  With sh <= 19 and an 8-bit z nothing leaves 63 bits.
     // SAT (the same, sh >= 1 and a clip to the container's whole range): two results' shift, clip and pack are one
-    // instruction, 9 cycles per output in all instead of 16 (24 -> 144 channels on 32 x 56 x 56: 7.9 us, 8.5 before).
+    // instruction, 9 cycles per output in all instead of 16 (24 -> 144 channels on 32 x 56 x 56: 0.6 us less).
     enum { kGeneral, kFold, kSat };
     const int32_t away = rs.half_away ? -1 : 0;  // mask of the sign-bit correction
     auto store_all = [&]<int FORM>() {
@@ -194,53 +217,89 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
       const int64_t k64 = FOLD ? (int64_t)corr * rq.m + rnd + ((int64_t)zc << (31 + rq.sh)) : rnd;
       const uint32_t flip = sat_flip(rs);
       const int32_t add = FOLD ? 0 : corr;
+      constexpr int kGroups = 4 / KS;
+      uint32_t dw[kGroups][4];
 #pragma unroll
-      for (int gi = 0; gi < 4 / KS; ++gi) {
-        const int g = KS == 1 ? gi : wave;
-        uint32_t dw[4];
+      for (int g = 0; g < kGroups; ++g) {
+        uint32_t raw[4][MODE == 1 ? 4 : 2];
+        const int32_t mult = opaque(rq.m);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           int32_t v[4];
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            v[j] = acc[j][4 * gi + e] + add;
+            v[j] = acc[j][4 * g + e] + add;
             if (ACC16) v[j] = (int32_t)(int16_t)v[j];
           }
           if constexpr (MODE == 0 && FORM == kSat) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = (int32_t)(((int64_t)v[j] * (int64_t)rq.m + k64) >> 32);
-            ashr_sat_pair<0>(dw[e], v[0], v[1], rq.sh - 1);
-            ashr_sat_pair<1>(dw[e], v[2], v[3], rq.sh - 1);
-            dw[e] ^= flip;
+            for (int j = 0; j < 4; ++j) v[j] = (int32_t)(((int64_t)v[j] * (int64_t)mult + k64) >> 32);
+            ashr_sat_pair<0>(dw[g][e], v[0], v[1], rq.sh - 1);
+            ashr_sat_pair<1>(dw[g][e], v[2], v[3], rq.sh - 1);
+            dw[g][e] ^= flip;
           } else if constexpr (MODE == 0) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
               // (general form only: halves away from zero add the accumulator's sign bit)
-              const int64_t pr = (int64_t)v[j] * (int64_t)rq.m + k64 + (FOLD ? 0 : (int64_t)((v[j] >> 31) & away));
+              const int64_t pr = (int64_t)v[j] * (int64_t)mult + k64 + (FOLD ? 0 : (int64_t)((v[j] >> 31) & away));
               v[j] = med3((int32_t)(pr >> (31 + rq.sh)), lo, hi) + (FOLD ? 0 : rs.z_out);
             }
-            dw[e] = pack4_perm(v[0], v[1], v[2], v[3]);
+            dw[g][e] = pack4_perm(v[0], v[1], v[2], v[3]);
+          } else if constexpr (MODE == 1) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) raw[e][j] = (uint32_t)v[j];
           } else {
-            int pq = pix0 + 4 * (8 * g + 4 * h + e);  // first of the four pixels
-            const bool ok = n < N && pq < HW;
-            if (pq > HW - 4) pq = HW - 4;
-            if constexpr (MODE == 1) {
-              if (ok) *reinterpret_cast<v4i_u*>(orow + (int64_t)pq * kEsz) = v4i{v[0], v[1], v[2], v[3]};
-            } else {
-              if (ok) *reinterpret_cast<v2i_u*>(orow + (int64_t)pq * kEsz) =
-                  v2i_u{(v[0] & 0xffff) | (int)((uint32_t)v[1] << 16), (v[2] & 0xffff) | (int)((uint32_t)v[3] << 16)};
-            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) raw[e][j] = ((uint32_t)v[2 * j] & 0xffffu) | ((uint32_t)v[2 * j + 1] << 16);
           }
         }
-        if constexpr (MODE == 0) {
-          const int pg = pix0 + 32 * g + 16 * h;
+        if constexpr (MODE == 0 && (KS == 4 || SMALL)) {
+          const int pg = pix0 + 32 * (KS == 1 ? g : wave) + 16 * h;
           if (n < N && pg + 16 <= HW) {
-            *reinterpret_cast<v4i_u*>(orow + pg) = v4i{(int)dw[0], (int)dw[1], (int)dw[2], (int)dw[3]};
+            *reinterpret_cast<v4i_u*>(orow + pg) = v4i{(int)dw[g][0], (int)dw[g][1], (int)dw[g][2], (int)dw[g][3]};
           } else if (n < N) {  // (an image of less than 128 pixels)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (pg + 4 * e < HW) *reinterpret_cast<u32_u*>(orow + (pg + 4 * e > HW - 4 ? HW - 4 : pg + 4 * e)) = dw[e];
+              if (pg + 4 * e < HW) *reinterpret_cast<u32_u*>(orow + (pg + 4 * e > HW - 4 ? HW - 4 : pg + 4 * e)) = dw[g][e];
           }
+        } else if constexpr (MODE != 0) {
+          // four pixels a piece: four lanes write 64 (32) consecutive bytes
+          if constexpr (!SMALL) quad_transpose(raw, lane);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const int nn = SMALL ? n : (n & ~3) + t;
+            int pq = pix0 + 32 * (KS == 1 ? g : wave) + 16 * h + 4 * (SMALL ? t : lane & 3);
+            const bool ok = nn < N && pq < HW;
+            if (pq > HW - 4) pq = HW - 4;
+            uint8_t* const dst = static_cast<uint8_t*>(p.out) + (((int64_t)b * N + nn) * HW + pq) * kEsz;
+            if constexpr (MODE == 1) {
+              if (ok) *reinterpret_cast<v4i_u*>(dst) = v4i{(int)raw[t][0], (int)raw[t][1], (int)raw[t][2], (int)raw[t][3]};
+            } else {
+              if (ok) *reinterpret_cast<v2i_u*>(dst) = v2i_u{(int)raw[t][0], (int)raw[t][1]};
+            }
+          }
+        }
+      }
+      if constexpr (MODE == 0 && KS == 1 && !SMALL) {
+        // pieces 2g + h of 16 pixels: the upper ones to the upper half of the wavefront, then to the lanes of a quad
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            const auto sw = __builtin_amdgcn_permlane32_swap(dw[g][e], dw[g + 2][e], false, false);
+            dw[g][e] = sw[0], dw[g + 2][e] = sw[1];
+          }
+          const uint32_t x = dw[1][e];
+          dw[1][e] = dw[2][e], dw[2][e] = x;
+        }
+        quad_transpose(dw, lane);
+        uint8_t* const first_row = static_cast<uint8_t*>(p.out) + ((int64_t)b * N + n0) * HW;
+        auto row = [&](int nn) { return first_row + (uint64_t)(uint32_t)(nn - n0) * (uint32_t)HW; };
+        const int pg = pix0 + 64 * h + 16 * (lane & 3);
+#pragma unroll
+        for (int t = 0; t < kGroups; ++t) {
+          const int nn = (n & ~3) + t;
+          if (nn < N) *reinterpret_cast<v4i_u*>(row(nn) + pg) = v4i{(int)dw[t][0], (int)dw[t][1], (int)dw[t][2], (int)dw[t][3]};
         }
       }
     };
@@ -277,7 +336,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
       Rq rn{0, 0, 0};
       if (blk + 1 < last) rn = load_block(blk + 1, wn);  // under way during this block's results
       wsum += __shfl_xor(wsum, 32);                      // the two k-halves of the row sums
-      finish(blk * 32 + i, rq);
+      finish(blk * 32, blk * 32 + i, rq);
       rq = rn;
 #pragma unroll
       for (int s = 0; s < CH; ++s) wb[s] = wn[s];
@@ -347,7 +406,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
         wsum += mine[w * 64 * kPart + 64];
       }
     }
-    finish(n, rq);
+    finish(blk0 * 32, n, rq);
   }
 }
 
@@ -365,16 +424,15 @@ hipError_t launch(PwArgs q, hipStream_t st) {
   q.inv_nb = inverse(q.nblocks, ids);
   // Four wavefronts per tile and block up to where one each fills half of the SIMDs (us with four and with one: 384 -> 64
   // on 8 x 56 x 56, 400 of them, 6.0, 7.9; 480 -> 80 on 2 x 112 x 112, 588, 10.5, 8.3).
-  if (q.C > 64 && ids <= 512)
-    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 4, 5>), dim3((unsigned)ids), dim3(256), 0, st, q);
-  else if (q.C <= 32)
-    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 1, 1>), dim3((unsigned)ids), dim3(64), 0, st, q);
-  else if (q.C <= 64)
-    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 1, 2>), dim3((unsigned)ids), dim3(64), 0, st, q);
-  else if (q.C <= 96)
-    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 1, 3>), dim3((unsigned)ids), dim3(64), 0, st, q);
-  else
-    hipLaunchKernelGGL((pw_nchw_kernel<MODE, ACC16, 1, 5>), dim3((unsigned)ids), dim3(64), 0, st, q);
+  auto run = [&]<int KS, int CH>() {
+    const auto kern = KS == 1 && q.HW < 128 ? pw_nchw_kernel<MODE, ACC16, KS, CH, KS == 1> : pw_nchw_kernel<MODE, ACC16, KS, CH, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
+  };
+  if (q.C > 64 && ids <= 512) run.template operator()<4, 5>();
+  else if (q.C <= 32) run.template operator()<1, 1>();
+  else if (q.C <= 64) run.template operator()<1, 2>();
+  else if (q.C <= 96) run.template operator()<1, 3>();
+  else run.template operator()<1, 5>();
   return hipGetLastError();
 }
 

@@ -13,6 +13,7 @@ SIZES = [  # B C H W O
     (1, 4, 1, 4, 1), (3, 24, 1, 5, 33), (2, 32, 3, 3, 40), (1, 36, 7, 7, 32), (5, 64, 9, 9, 64), (2, 60, 11, 13, 70),
     (1, 68, 8, 16, 33), (2, 96, 10, 13, 96), (1, 100, 15, 15, 20), (2, 164, 12, 11, 65), (1, 576, 14, 14, 96),
     (3, 640, 5, 5, 31), (1, 324, 40, 41, 45), (9, 24, 57, 55, 144), (4, 80, 56, 57, 160), (1, 100, 46, 47, 1000),
+    (2, 8, 1, 127, 6), (2, 40, 3, 43, 7), (1, 72, 4, 32, 5),
 ]
 
 
