@@ -15,9 +15,12 @@
 //     over pixel tiles with the weights resident.
 // The loads of the NEXT tile are issued before the current one is multiplied and are written to
 // LDS after it, so memory latency hides behind the matrix instructions and the epilogue.  The
-// start-up chain is kept short the same way: the first tile's loads and the per-channel constants
-// go out before the weights are fetched, and the weight sums of the zero-point term are added up
-// (LDS atomics) by the threads that stage the weights, only when that term is not zero.
+// start-up chain is what bounds small layers and half of a layer of one tile per workgroup: all first loads, of the
+// weights, the tile and the per-channel constants, go out by descriptor before any is waited for, divisions are
+// multiplications by inverses (us before and so: 64 -> 64 on one 56 x 56 image 5.06, 4.65, on 16 of uint8 7.5, 6.8; 32 ->
+// 72 on 28 x 48 x 48 7.7, 6.85; 128 -> 128 on 64 x 28 x 28 14.2, 13.6), and the weight sums of the zero-point term are added up
+// (LDS atomics) by the threads that stage the weights, only when that term is not zero.  (Weights loaded as they lie and
+// regrouped through LDS: 0.1 to 0.3 us slower; the tile's loads first: 0.1 to 0.4.)
 // The 16 bytes of padding per pixel / per output channel make the 16-byte fragment reads of 32
 // consecutive pixels (or channels) conflict-free (strides of 20 or 36 dwords).  A filter tap is
 // then just an address offset into the staged tile, so every input byte is fetched once.
@@ -55,8 +58,16 @@ struct C3Params {
   uint32_t act_xor4;     // 0x80808080 for uint8 activations
   uint32_t pad4;         // staged value of a pixel outside the image, in every byte
   int32_t corr_coef;     // off - z_a
+  uint32_t inv_tpi, inv_nblk, inv_run4, inv_w4, inv_w;  // ceil(2^32 / d) of tiles_per_img, nblk, the dwords of a run and of a row, W
   RequantScalars rs;
 };
+
+constexpr uint32_t kOob = 0x80000000u;  // a buffer offset that reads as 0
+
+// n / d for n * d < 2^32 (inv == 0: d is 1, or n too large for that)
+__device__ __forceinline__ uint32_t div_by(uint32_t n, uint32_t d, uint32_t inv) {
+  return inv ? __umulhi(n, inv) : n / d;
+}
 
 // row r of a 32-row block <-> pixel of the block (see the header)
 __device__ __forceinline__ constexpr int pix_of_row(int r) {
@@ -101,13 +112,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   if (nwg % 8 == 0) {
     const int xcd = (int)blockIdx.x & 7, q = (int)blockIdx.x >> 3;
     const int per_xcd = (p.ntiles + 7) / 8;
-    blk = q % p.nblk;
-    tile = xcd * per_xcd + q / p.nblk;
+    const int share = (int)div_by((uint32_t)q, (uint32_t)p.nblk, p.inv_nblk);
+    blk = q - share * p.nblk;
+    tile = xcd * per_xcd + share;
     tile_end = (xcd + 1) * per_xcd < p.ntiles ? (xcd + 1) * per_xcd : p.ntiles;
     tile_step = nwg / 8;
   } else {
-    blk = (int)blockIdx.x % p.nblk;
-    tile = (int)blockIdx.x / p.nblk;
+    tile = (int)div_by(blockIdx.x, (uint32_t)p.nblk, p.inv_nblk);
+    blk = (int)blockIdx.x - tile * p.nblk;
     tile_end = p.ntiles;
     tile_step = nwg;
   }
@@ -130,35 +142,35 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
     const int u = t + NT * n;
     u_row[n] = -1; u_off[n] = 0; u_src[n] = 0;
     if (u < units) {
-      const int c16 = u / run4, d = u - c16 * run4;
-      const int r = d / w4, x4 = d - r * w4;
+      const int c16 = (int)div_by((uint32_t)u, (uint32_t)run4, p.inv_run4), d = u - c16 * run4;
+      const int r = (int)div_by((uint32_t)d, (uint32_t)w4, p.inv_w4), x4 = d - r * w4;
       u_row[n] = r;
       u_off[n] = (r * Wp + 1 + 4 * x4) * Cp + 16 * c16;
       u_src[n] = (uint32_t)(c16 * 16) * (uint32_t)HW + (uint32_t)(4 * x4);   // + (y0 - 1 + r) * W
     }
   }
+  // (by descriptor: one offset register per unit, the channel in a scalar; rows outside the image read as 0)
   auto load_tile = [&](int tile) {
-    const int b = tile / p.tiles_per_img;
+    const int b = (int)div_by((uint32_t)tile, (uint32_t)p.tiles_per_img, p.inv_tpi);
     const int y0 = (tile - b * p.tiles_per_img) * p.TR;
-    const uint8_t* img = p.act + (int64_t)b * C * HW;
+    const __amdgpu_buffer_rsrc_t rin =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.act) + (int64_t)b * C * HW, 0, C * HW, 0x00020000);
 #pragma unroll
     for (int n = 0; n < NU; ++n) {
       const int iy = y0 - 1 + u_row[n];
-      const bool ok = u_row[n] >= 0 && (unsigned)iy < (unsigned)H;
+      const uint32_t at = u_row[n] >= 0 && (unsigned)iy < (unsigned)H ? u_src[n] + (uint32_t)(iy * W) : kOob;
 #pragma unroll
-      for (int k = 0; k < 16; ++k)
-        raw[n][k] = ok ? *reinterpret_cast<const uint32_t*>(img + u_src[n] + (uint32_t)(iy * W) + (uint32_t)k * (uint32_t)HW)
-                       : p.pad4;
+      for (int k = 0; k < 16; ++k) raw[n][k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rin, at, k * HW, 0);
     }
   };
   auto store_tile = [&](int tile) {
-    const int b = tile / p.tiles_per_img;
+    const int b = (int)div_by((uint32_t)tile, (uint32_t)p.tiles_per_img, p.inv_tpi);
     const int y0 = (tile - b * p.tiles_per_img) * p.TR;
 #pragma unroll
     for (int n = 0; n < NU; ++n) {
       if (u_row[n] < 0) continue;
       const int iy = y0 - 1 + u_row[n];
-      const uint32_t flip = (unsigned)iy < (unsigned)H ? p.act_xor4 : 0u;   // padding is staged as it is
+      const uint32_t flip = (unsigned)iy < (unsigned)H ? p.act_xor4 : p.pad4;  // (padding was read as 0)
       uint32_t px[4][4];   // [channel quad][pixel]
 #pragma unroll
       for (int g = 0; g < 4; ++g) transpose4(raw[n][4 * g], raw[n][4 * g + 1], raw[n][4 * g + 2], raw[n][4 * g + 3], flip, px[g]);
@@ -180,46 +192,49 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   if (t < OB) s_sum[t] = 0;
   __syncthreads();
 
-  if (tile < tile_end) load_tile(tile);   // in flight while the weights are staged
+  // ---- weights of the block: OIHW (per o: [C][9]) -> [o][tap][C]; channels beyond O are zero.
+  // A unit is four channels of one output channel: 36 contiguous bytes in memory (nine dwords), unit i at byte 36 i of the block; byte 9 j + k = channel
+  // j, tap k; tap k's dword is bytes (k, 9 + k, 18 + k, 27 + k), picked with three byte permutes.
+  // The loads of up to four units per thread go out together, in front of the tile's (whose latency the regrouping
+  // hides), and the constants' behind both: nothing is waited for before all of them are under way.  The sums of eight
+  // neighbouring lanes, always of one output channel, are added up before they go to LDS.
+  constexpr int kUnits = OB * (C / 4);
+  constexpr int kBatch = (kUnits + NT - 1) / NT < 4 ? (kUnits + NT - 1) / NT : 4;
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<int8_t*>(p.wgt) + (int64_t)o0 * C * 9, 0, (O - o0 < OB ? O - o0 : OB) * C * 9, 0x00020000);
+  uint32_t dw[kBatch][9];
+  auto load_weights = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+      for (int k = 0; k < 9; ++k) dw[u][k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rw, 36 * (i0 + u * NT + t) + 4 * k, 0, 0);
+  };
+  load_weights(0);
+  if (tile < tile_end) load_tile(tile);
 
-  // ---- per-lane constants: output channels o0 + 32 tn + j (their loads go out now too)
+  // ---- per-lane constants: output channels o0 + 32 tn + j
   const int j = lane & 31, h = lane >> 5;
   int32_t corr[TN], mu[TN], sh[TN];
+  {
+    auto table = [&](const int32_t* q, int n) {
+      return __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(q), 0, q ? 4 * n : 0, 0x00020000);
+    };
+    const int rq_n = p.has_rq ? (p.per_channel ? O : 1) : 0;
+    const __amdgpu_buffer_rsrc_t rb = table(p.bias, O), rm = table(p.mult, rq_n), rs_ = table(p.shift, rq_n);
 #pragma unroll
-  for (int tn = 0; tn < TN; ++tn) {
-    const int o = o0 + 32 * tn + j;
-    corr[tn] = 0; mu[tn] = 0; sh[tn] = 1;
-    if (o < O) {
-      corr[tn] = p.bias ? p.bias[o] : 0;
-      if (p.has_rq) {
-        mu[tn] = rq_mult(p.mult, p.per_channel ? o : 0);
-        sh[tn] = rq_shift(p.mult, p.shift, p.per_channel ? o : 0);
-      }
+    for (int tn = 0; tn < TN; ++tn) {
+      const int o = o0 + 32 * tn + j;
+      const uint32_t at = o < O ? 4u * (uint32_t)(p.per_channel ? o : 0) : kOob;
+      corr[tn] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rb, o < O ? 4 * o : kOob, 0, 0);
+      mu[tn] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, at, 0, 0);
+      sh[tn] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rs_, at, 0, 0);
     }
   }
 
-  // ---- weights of the block: OIHW (per o: [C][9]) -> [o][tap][C]; channels beyond O are zero.
-  // A unit is four channels of one output channel: 36 contiguous bytes in memory (nine dwords), byte 9 j + k = channel j, tap k; tap k's dword is bytes
-  // (k, 9 + k, 18 + k, 27 + k), picked with three byte permutes.
-  // Two units per thread at a time: their loads go out together (with one, a layer of 128 channels waited for memory
-  // four times in a row before its first tile).  The sums of eight neighbouring lanes, always of one output channel, are
-  // added up before they go to LDS.
-  constexpr int kUnits = OB * (C / 4);
-  for (int i0 = 0; i0 < kUnits; i0 += 2 * NT) {
-    uint32_t dw[2][9];
+  for (int i0 = 0; i0 < kUnits; i0 += kBatch * NT) {
+    if (i0 > 0) load_weights(i0);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = i0 + u * NT + t;
-      const int o = i / (C / 4), c4 = (i - o * (C / 4)) * 4;
-      const bool ok = i < kUnits && o0 + o < O;
-      const int8_t* src = p.wgt + ((int64_t)(ok ? o0 + o : 0) * C + (ok ? c4 : 0)) * 9;
-#pragma unroll
-      for (int k = 0; k < 9; ++k) dw[u][k] = *reinterpret_cast<const u32_any*>(src + 4 * k);
-#pragma unroll
-      for (int k = 0; k < 9; ++k) dw[u][k] = ok ? dw[u][k] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < kBatch; ++u) {
       const int i = i0 + u * NT + t;
       if (i >= kUnits) continue;  // (kUnits is a multiple of 64: whole wavefronts)
       const int o = i / (C / 4), c4 = (i - o * (C / 4)) * 4;
@@ -247,7 +262,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   bool lane_ok = true;   // the folded requantize arithmetic is exact for this lane's channels
 #pragma unroll
   for (int tn = 0; tn < TN; ++tn) {
-    if (o0 + 32 * tn + j < O) corr[tn] += p.corr_coef * s_sum[32 * tn + j];
+    if (o0 + 32 * tn + j < O) {
+      corr[tn] += p.corr_coef * s_sum[32 * tn + j];
+      if (p.has_rq && !p.mult) mu[tn] = 1 << 30, sh[tn] -= 1;
+    } else {
+      sh[tn] = 1;
+    }
     lane_ok = lane_ok && sh[tn] >= 1 && sh[tn] <= 19 && corr[tn] >= -(1 << 30) && corr[tn] <= (1 << 30);
   }
   // FOLD (requantized, 32-bit accumulator, every lane's constants small enough): correction term,
@@ -256,11 +276,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   // clamped BEFORE that shift against limits scaled by 2^(sh-1), so that the shift can drop each
   // result straight into its byte of the output dword.  |acc| <= 9 C 2^14 < 2^30 and
   // |corr| <= 2^30, so acc + corr cannot wrap; with sh <= 19 and an 8-bit z nothing leaves 63 bits.
-  const bool fold = p.out_mode == 0 && p.acc_wrap_shift == 0 && !p.rs.half_away && p.rs.z_out >= -256 &&
+  const bool exact = p.out_mode == 0 && !p.rs.half_away && p.rs.z_out >= -256 &&
                     p.rs.z_out <= 255 && __builtin_amdgcn_ballot_w64(!lane_ok) == 0;   // wavefront-uniform
+  const bool fold = exact && p.acc_wrap_shift == 0;
   // Clipped to the container's whole range: shift, clip and pack of two results are one instruction and no clip in front of
   // it (9 cycles of a SIMD per output instead of 13.4).
-  const bool sat = fold && sat_range(p.rs);
+  // With a narrow accumulator the correction term is added in front of its wrapping instead (128 -> 128 on 64 x 28 x 28,
+  // 16 bits: the general form's results took 4.6 us of 17.0, these 1.9 of 13.9).
+  const bool sat = exact && sat_range(p.rs);
   const int32_t zc = p.rs.z_out + (sat ? sat_bias(p.rs) : 0);
   const uint32_t sflip = sat_flip(p.rs);
   int64_t k64[TN];
@@ -268,7 +291,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
 #pragma unroll
   for (int tn = 0; tn < TN; ++tn) {
     s1[tn] = sh[tn] - 1;
-    k64[tn] = (int64_t)corr[tn] * mu[tn] + ((int64_t)1 << (30 + (sh[tn] & 31))) + ((int64_t)zc << (31 + (sh[tn] & 31)));
+    k64[tn] = (fold ? (int64_t)corr[tn] * mu[tn] : 0) + ((int64_t)1 << (30 + (sh[tn] & 31))) + ((int64_t)zc << (31 + (sh[tn] & 31)));
     lo_s[tn] = clip_lo_before_shift(p.rs.lo_rel + p.rs.z_out, s1[tn] & 31);
     hi_s[tn] = clip_hi_before_shift(p.rs.hi_rel + p.rs.z_out, s1[tn] & 31);
   }
@@ -280,13 +303,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   for (int f = 0; f < AF; ++f) {
     const int q = 32 * (AF * wave + f) + pix_of_row(j);  // the lane's pixel in row block f
     const int qc = q < pt ? q : 0;                       // rows beyond the tile read pixel 0 (results dropped)
-    const int qr = qc / W, qx = qc - qr * W;
+    const int qr = (int)div_by((uint32_t)qc, (uint32_t)W, p.inv_w), qx = qc - qr * W;
     a_base[f] = (uint32_t)((qr * Wp + qx) * Cp + 16 * h);
   }
   const uint32_t b_base = (uint32_t)(j * wstride + 16 * h);
 
   for (; tile < tile_end; tile += tile_step) {
-    const int b = tile / p.tiles_per_img;
+    const int b = (int)div_by((uint32_t)tile, (uint32_t)p.tiles_per_img, p.inv_tpi);
     const int y0 = (tile - b * p.tiles_per_img) * p.TR;          // first output row
     const int rows = (H - y0 < p.TR) ? H - y0 : p.TR;            // output rows of this tile
     __syncthreads();       // the previous tile has been consumed
@@ -354,7 +377,18 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
         if (p.out_mode == 0) {
           uint8_t* dst = static_cast<uint8_t*>(p.out) + oo;
           uint32_t dw[4];
-          if (sat) {
+          if (sat && !fold) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              int32_t r[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                r[e] = (int32_t)(((int64_t)wrap_acc_bits(acc[f][tn][4 * g + e] + corr[tn], p.acc_wrap_shift) * (int64_t)mu[tn] + k64[tn]) >> 32);
+              ashr_sat_pair<0>(dw[g], r[0], r[1], s1[tn]);
+              ashr_sat_pair<1>(dw[g], r[2], r[3], s1[tn]);
+              dw[g] ^= sflip;
+            }
+          } else if (sat) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               int32_t r[4];
@@ -484,7 +518,7 @@ bool try_qconv3x3_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hi
   // least time on the busiest CU, in microseconds: the weights once; per tile the matrix instructions, and staging and
   // epilogue, which two workgroups on a CU do in each other's shadow.  Blocks of 32 leave less of a last block empty, make
   // twice the workgroups and need half the weights, 64 and wide tiles read fewer LDS bytes per matrix instruction (us with
-  // 32 and 64: 64 -> 64 on one 56 x 56 image 5.1, 6.9; 32 -> 72 on 28 x 49 x 48 7.9, 13.6; 128 -> 184 on 6 x 74 x 72 17.5,
+  // 32 and 64, by loads of 64-bit addresses: 64 -> 64 on one 56 x 56 image 5.1, 6.9; 32 -> 72 on 28 x 49 x 48 7.9, 13.6; 128 -> 184 on 6 x 74 x 72 17.5,
   // 21.9; 128 -> 256 on 16 x 56 x 56 26.9, 23.9).
   struct Shape { int nw, af; };
   static const Shape shapes[] = {{8, 2}, {8, 1}, {4, 1}};
@@ -530,6 +564,12 @@ bool try_qconv3x3_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hi
   if (per_blk < 1) per_blk = 1;
   if (per_blk > ntiles) per_blk = ntiles;
   const int64_t grid = per_blk * p.nblk;
+  auto inverse = [](int64_t d, int64_t n) { return d > 1 && n * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d) : 0u; };
+  p.inv_tpi = inverse(p.tiles_per_img, ntiles);
+  p.inv_nblk = inverse(p.nblk, grid);
+  p.inv_w4 = inverse(cg.W / 4, (p.TR + 2) * (cg.W / 4));
+  p.inv_run4 = inverse((p.TR + 2) * (cg.W / 4), 3 * 512);
+  p.inv_w = inverse(cg.W, 512);
 #define HAGO_C3(I, NWV, AFV, NUV) if (pick == I && nu == NUV) { *err = tn == 1 ? launch_c3<NWV, AFV, NUV, 1>(p, lds, grid, st) : launch_c3<NWV, AFV, NUV, 2>(p, lds, grid, st); return true; }
   HAGO_C3(0, 8, 2, 1) HAGO_C3(0, 8, 2, 2) HAGO_C3(0, 8, 2, 3)
   HAGO_C3(1, 8, 1, 1) HAGO_C3(1, 8, 1, 2) HAGO_C3(1, 8, 1, 3)

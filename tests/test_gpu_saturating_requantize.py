@@ -60,6 +60,27 @@ def test_whole_range(name):
                 assert (want == clip[0]).any() and (want == clip[1]).any() and len(np.unique(want)) > 100 or groups > 1
 
 
+@pytest.mark.parametrize("acc", ["I16", "I24"])
+@pytest.mark.parametrize("act_u8", [False, True])
+def test_whole_range_narrow_accumulator(acc, act_u8):
+    """The 3x3 convolution's form for accumulators that wrap: the correction and bias are inside the wrapped sum."""
+    rng = np.random.default_rng(5 + act_u8)
+    B, C, H, W, O = 2, 64, 9, 12, 37
+    a = rng.integers(0, 256, (B, C, H, W)).astype(np.uint8) if act_u8 else rng.integers(-128, 128, (B, C, H, W)).astype(np.int8)
+    za = 117 if act_u8 else -5
+    w = rng.integers(-127, 128, (O, C, 3, 3)).astype(np.int8)
+    bias = rng.integers(-2 ** 23, 2 ** 23, O).astype(np.int32)
+    da, dw, db = dev(a), dev(w), dev(bias)
+    for out_u8, z, clip, (s0, s1) in FORMS:
+        for use_mult in (True, False):
+            mult = rng.integers(2 ** 30, 2 ** 31, O, dtype=np.int64).astype(np.int32) if use_mult else None
+            shift = rng.integers(s0, s1 + 1, O).astype(np.int32)
+            want = ref.qconv2d(a, za, w, bias, ref.NCHW, (1, 1), (1, 1), 1, getattr(ref, acc), ref_requant(mult, shift, out_u8, z, clip))
+            rq = hago.Requant(dev(mult), dev(shift), hago.QType(hago.U8 if out_u8 else hago.I8, 8, not out_u8, z), *clip)
+            got = hago.qconv2d(da, act_qtype(a, za), dw, hago.QType(hago.I8), db, hago.NCHW, (1, 1), (1, 1), 1, getattr(hago, acc), rq)
+            assert_same(host(got), want, f"{acc} u8={act_u8} {out_u8, z, clip, s0, s1} mult={use_mult}")
+
+
 @pytest.mark.parametrize("shape", [(300, 64, 1), (90, 35, 1), (64, 12, 3), (5000, 8, 1)])
 @pytest.mark.parametrize("dtype", [np.int32, np.int16])
 def test_whole_range_standalone(shape, dtype):
