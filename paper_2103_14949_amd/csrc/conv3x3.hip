@@ -372,7 +372,26 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn) {
         const int o = o0 + 32 * tn + j;
-        if (o >= O || pix0 >= npix) continue;
+        if (pix0 >= npix) continue;  // (whole halves of the wavefront)
+        if (p.out_mode == 1) {
+          // a lane's 64 bytes go out by the quad: its channel t's from all four lanes
+          uint32_t v[4][4];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int32_t a = acc[f][tn][r] + corr[tn];
+            v[r >> 2][r & 3] = (uint32_t)(p.acc_wrap_shift ? wrap_acc_bits(a, p.acc_wrap_shift) : a);
+          }
+          quad_transpose(v, lane);
+#pragma unroll
+          for (int t4 = 0; t4 < 4; ++t4) {
+            const int oq = (o & ~3) + t4, g = lane & 3;
+            if (oq < O && 4 * g < left)
+              *reinterpret_cast<v4i_any*>(static_cast<int32_t*>(p.out) + obase + (int64_t)oq * HW + 4 * g) =
+                  v4i{(int)v[t4][0], (int)v[t4][1], (int)v[t4][2], (int)v[t4][3]};
+          }
+          continue;
+        }
+        if (o >= O) continue;
         const int64_t oo = obase + (int64_t)o * HW;
         if (p.out_mode == 0) {
           uint8_t* dst = static_cast<uint8_t*>(p.out) + oo;
@@ -437,25 +456,18 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
             v[r] = acc[f][tn][r] + corr[tn];
             if (p.acc_wrap_shift) v[r] = wrap_acc_bits(v[r], p.acc_wrap_shift);
           }
-          if (p.out_mode == 1) {
-            int32_t* dst = static_cast<int32_t*>(p.out) + oo;
+          int16_t* dst = static_cast<int16_t*>(p.out) + oo;
+          uint32_t dq[8];
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-              if (4 * g < left) reinterpret_cast<v4i_any*>(dst)[g] = v4i{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+          for (int x = 0; x < 8; ++x) dq[x] = ((uint32_t)v[2 * x] & 0xffffu) | ((uint32_t)v[2 * x + 1] << 16);
+          if (left >= 16) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+              reinterpret_cast<v4i_any*>(dst)[g] = v4i{(int)dq[4 * g], (int)dq[4 * g + 1], (int)dq[4 * g + 2], (int)dq[4 * g + 3]};
           } else {
-            int16_t* dst = static_cast<int16_t*>(p.out) + oo;
-            uint32_t dq[8];
 #pragma unroll
-            for (int x = 0; x < 8; ++x) dq[x] = ((uint32_t)v[2 * x] & 0xffffu) | ((uint32_t)v[2 * x + 1] << 16);
-            if (left >= 16) {
-#pragma unroll
-              for (int g = 0; g < 2; ++g)
-                reinterpret_cast<v4i_any*>(dst)[g] = v4i{(int)dq[4 * g], (int)dq[4 * g + 1], (int)dq[4 * g + 2], (int)dq[4 * g + 3]};
-            } else {
-#pragma unroll
-              for (int x = 0; x < 8; ++x)
-                if (2 * x < left) reinterpret_cast<u32_any*>(dst)[x] = dq[x];
-            }
+            for (int x = 0; x < 8; ++x)
+              if (2 * x < left) reinterpret_cast<u32_any*>(dst)[x] = dq[x];
           }
         }
       }

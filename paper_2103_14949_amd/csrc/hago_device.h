@@ -124,6 +124,26 @@ __device__ __forceinline__ int32_t opaque(int32_t v) {
   return v;
 }
 
+// d[t] of lane r of a quad <-> d[r] of its lane t (every lane of the quad takes part).  Where a lane holds 16 bytes of each of
+// four pieces of a row, the quad's stores then write 64 consecutive bytes: 64 cycles of the memory pipe for a wavefront's 16
+// bytes per lane, against 168 where every lane writes to a line of its own and 256 off four bytes.
+template <int D>
+__device__ __forceinline__ void quad_transpose(uint32_t (&d)[4][D], int lane) {
+  auto exchange = [&]<int CTRL>(uint32_t& lower, uint32_t& upper, bool high) {
+    const uint32_t from_upper = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upper, CTRL, 0xf, 0xf, true);
+    const uint32_t from_lower = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lower, CTRL, 0xf, 0xf, true);
+    lower = high ? from_upper : lower;
+    upper = high ? upper : from_lower;
+  };
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    exchange.template operator()<0xB1>(d[0][k], d[1][k], lane & 1);  // quad_perm 1,0,3,2
+    exchange.template operator()<0xB1>(d[2][k], d[3][k], lane & 1);
+    exchange.template operator()<0x4E>(d[0][k], d[2][k], lane & 2);  // quad_perm 2,3,0,1
+    exchange.template operator()<0x4E>(d[1][k], d[3][k], lane & 2);
+  }
+}
+
 // Whether the output's clip limits are its container's whole range, so that this saturation is the clip.  sat_bias is added
 // to the output zero point (inside the 64-bit constant of the folded forms) to centre the range on int8's, and sat_flip
 // undoes it in the packed dword: 0 and 0 for int8, -128 and 0x80 per byte for uint8.

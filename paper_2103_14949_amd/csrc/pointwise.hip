@@ -73,24 +73,6 @@ typedef uint32_t u32_u __attribute__((aligned(1)));
 typedef v4i v4i_u __attribute__((aligned(1)));
 typedef int v2i_u __attribute__((ext_vector_type(2), aligned(1)));
 
-// d[t] of lane r of a quad <-> d[r] of its lane t.
-template <int D>
-__device__ __forceinline__ void quad_transpose(uint32_t (&d)[4][D], int lane) {
-  auto exchange = [&]<int CTRL>(uint32_t& lower, uint32_t& upper, bool high) {
-    const uint32_t from_upper = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upper, CTRL, 0xf, 0xf, true);
-    const uint32_t from_lower = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lower, CTRL, 0xf, 0xf, true);
-    lower = high ? from_upper : lower;
-    upper = high ? upper : from_lower;
-  };
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    exchange.template operator()<0xB1>(d[0][k], d[1][k], lane & 1);  // quad_perm 1,0,3,2
-    exchange.template operator()<0xB1>(d[2][k], d[3][k], lane & 1);
-    exchange.template operator()<0x4E>(d[0][k], d[2][k], lane & 2);  // quad_perm 2,3,0,1
-    exchange.template operator()<0x4E>(d[1][k], d[3][k], lane & 2);
-  }
-}
-
 template <int MODE, bool ACC16, int KS, int CH, bool SMALL>
 __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
   constexpr int kPart = 65;  // dwords of a lane's partial sums: 64 accumulators and the row sum (odd: no bank conflicts)
