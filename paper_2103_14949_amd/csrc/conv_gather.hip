@@ -754,8 +754,9 @@ bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_works
   const bool alone = p.steps <= 2 && r64 >= 4;
   int shape = forced_shape;
   if (shape < 0) {
-    // (results leave in 16-byte pieces of different channels' planes; channel-last one element per lane and store)
-    const double t = 3.8 + (double)a.M * a.N * (cg.nhwc ? 2.4 : mode == 0 ? 1 : mode == 1 ? 4 : 2) / 1.2e6 + (alone ? 0.35 * r64 : t32 < t64 ? t32 : t64) + (p.steps > 18 ? 0.1 * (p.steps - 18) : 0.0);
+    // (results leave in pieces of 4 to 16 pixels of different channels' planes, as fast whatever their width: 20 -> 64 5x5 on 16 x 40 x 41
+    // 12.5 in 8 and in 32 bits, there 24; channel-last one element per lane and store)
+    const double t = 3.8 + (double)a.M * a.N * (cg.nhwc ? 2.4 : 1.0) / 1.2e6 + (alone ? 0.35 * r64 : t32 < t64 ? t32 : t64) + (p.steps > 18 ? 0.1 * (p.steps - 18) : 0.0);
     const double base = has_workspace && (cg.nhwc || cg.W % 4 == 0) ? 7.5 : 8.5;  // (the rewrite is fast there)
     if (t >= base + (double)a.M * a.N * a.K / 0.41e9 + (double)a.K / (has_workspace || taps == 9 || taps == 1 ? 450 : 70)) return false;
     shape = alone ? 3 : t64 < t32 ? 1 : deep || (p.steps >= 12 && r32 <= 1) ? 0 : 2;
