@@ -289,7 +289,36 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   const int c4n = p.CC >> 2, c16n = p.CC >> 4;
   const int wper = WT == 9 ? c4n : (WT == 2 ? T * c16n : p.groups * 8);  // units per output channel
   const int wunits = OB * wper;
+  // Units that are whole or nothing are loaded by descriptor, the ones beyond the channels out of its range (us with a
+  // 64-bit address and conditions per unit and so: 48 -> 64 3x3 stride 2 on 16 x 56 x 56 9.1, 8.4, channel-last, all in
+  // this kernel, 10.5, 9.1; 64 -> 128 on as many 8.9, 8.6).
+  const int w_left = p.O - o0 < OB ? p.O - o0 : OB;
+  const __amdgpu_buffer_rsrc_t rs_wgt = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<int8_t*>(p.wgt) + (int64_t)o0 * p.C * T, 0, w_left * p.C * T, 0x00020000);
+  const bool w_whole = !SMALL && ((WT == 9 && p.C % 4 == 0) || (WT == 2 && p.C % 16 == 0));
   auto load_weights = [&](int c0, int i0) {
+    if (w_whole) {  // uniform
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int i = i0 + u * NT + t;
+        uint32_t ru;
+        const int o = (int)divide((uint32_t)i, (uint32_t)wper, p.inv_wper, ru);
+        if constexpr (WT == 9) {
+          const int c = c0 + 4 * (int)ru;
+          const uint32_t at = i < wunits && c < p.C ? (uint32_t)((o * p.C + c) * 9) : 0x80000000u;
+#pragma unroll
+          for (int k = 0; k < 9; ++k) wraw[u][k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs_wgt, at + 4 * k, 0, 0);
+        } else if constexpr (WT == 2) {
+          uint32_t cu;
+          const int tap = (int)divide(ru, (uint32_t)c16n, p.inv_c16, cu), c = c0 + 16 * (int)cu;
+          const uint32_t at = i < wunits && c < p.C ? (uint32_t)((o * T + tap) * p.C + c) : 0x80000000u;
+          const v4i v = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs_wgt, at, 0, 0));
+#pragma unroll
+          for (int k = 0; k < 4; ++k) wraw[u][k] = (uint32_t)v[k];
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
       const int i = i0 + u * NT + t;
@@ -484,7 +513,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   // every channel of the block): correction, rounding term and output zero point go into one 64-bit constant, the result is
   // the high dword of acc * m + k64 shifted by sh - 1; |acc| < 2^30 for reductions up to 2^16, so acc + corr cannot wrap.
   // Without chunks they are formed behind the staging of the weights, and the barrier behind the input's staging serves
-  // them too (64 -> 128 3x3 stride 2 on 32 x 56 x 56: 10.2 us, 10.4 before; 3 -> 64 7x7 on 8 x 224 x 224,
+  // them too (64 -> 128 3x3 stride 2 on 32 x 56 x 56: 10.3 us, 10.4 before; 3 -> 64 7x7 on 8 x 224 x 224,
   // with the input's loads by descriptor, one addition each, 10.6, 12.2 before).
   auto form_terms = [&]() {
     int bad = p.out_mode != 0 || p.acc_wrap_shift != 0 || p.rs.half_away || p.rs.z_out < -256 || p.rs.z_out > 255 || p.C * T > 65536;

@@ -58,3 +58,25 @@ def test_direct_convolution(case, shape, layout, gemm_path):
                 assert_same(host(got), want, f"requantized {case} u8={out_u8}")
     finally:
         hago.set_test_hook(hago.HOOK_GENERAL_TILE, -1)
+
+
+@pytest.mark.parametrize("off", [0, 1, 2, 3])
+@pytest.mark.parametrize("layout,C,O,stride", [("nchw", 32, 37, 1), ("nchw", 128, 70, 1), ("nchw", 36, 70, 2), ("nchw", 38, 70, 2), ("nhwc", 48, 70, 2),
+                                               ("nhwc", 40, 70, 2)])
+def test_weights_at_any_byte(layout, C, O, stride, off, gemm_path):
+    """3x3 weights loaded by descriptor (both one-launch kernels): tensors that start inside a dword, between other bytes,
+    channel counts on both sides of the whole units, output channels off the block."""
+    rng = np.random.default_rng(C + off)
+    a, za = rng.integers(0, 256, (2, C, 12, 16)).astype(np.uint8), 131
+    w, bias = rng.integers(-127, 128, (O, C, 3, 3)).astype(np.int8), rng.integers(-10 ** 5, 10 ** 5, O).astype(np.int32)
+    if layout == "nhwc":
+        a, w = (np.ascontiguousarray(x.transpose(0, 2, 3, 1)) for x in (a, w))
+    lay_g, lay_r = (hago.NCHW, ref.NCHW) if layout == "nchw" else (hago.NHWC, ref.NHWC)
+    whole = torch.full((w.size + 32,), 77, dtype=torch.int8, device="cuda:0")
+    dw = whole[16 + off: 16 + off + w.size].view(w.shape)
+    dw.copy_(dev(w))
+    want = ref.qconv2d(a, za, w, bias, lay_r, (stride, stride), (1, 1), 1)
+    if stride == 2:
+        gemm_path(3)
+    got = hago.qconv2d(dev(a), act_qtype(a, za), dw, hago.QType(hago.I8), dev(bias), lay_g, (stride, stride), (1, 1), 1)
+    assert_same(host(got), want, f"{layout} C={C} off {off}")
