@@ -214,7 +214,7 @@ def main():
             traffic = int(meta["traffic_bytes_per_launch"])
             traffic_src = {"file": "profiles/qgemm_dma_config5_hbm_traffic.md (FETCH_SIZE x2 + WRITE_SIZE, KiB)",
                            "kernel": meta.get("kernel"), "commit": meta.get("commit")}
-    roofline = {"bound": "mfma", "traffic_source": traffic_src, "kernel": "qgemm_dma_kernel (int8 MFMA 32x32x32, fused requantize)",
+    roofline = {"bound": "mfma", "traffic_source": traffic_src, "kernel": "qgemm_line_kernel and qgemm_dma_kernel (int8 MFMA 32x32x32, fused requantize)",
                 "achieved": round(achieved, 2), "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
                 "frac": round(achieved / PEAK_INT8_TOPS, 4), "traffic": traffic,
                 "avg_launch_us": round(avg_launch_ms * 1e3, 3), "launches_per_step": len(layers),
