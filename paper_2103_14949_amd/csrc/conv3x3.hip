@@ -69,6 +69,12 @@ __device__ __forceinline__ uint32_t div_by(uint32_t n, uint32_t d, uint32_t inv)
   return inv ? __umulhi(n, inv) : n / d;
 }
 
+// v; what follows from it is computed where it is used, not in front of the loop around
+__device__ __forceinline__ int stay_here(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // row r of a 32-row block <-> pixel of the block (see the header)
 __device__ __forceinline__ constexpr int pix_of_row(int r) {
   return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
@@ -373,6 +379,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
         if (p.out_mode == 1) {
           // a lane's 64 bytes go out by the quad: its channel t's from all four lanes
           uint32_t v[4][4];
+          // (the four channels' addresses, kept through the loop over the tiles, were up to 20 registers, and with them went the second
+          // workgroup on a CU: 32 -> 64 on 64 x 56 x 56 11.1 us, 10.8 so; 128 -> 256 on 16 x 56 x 56 21.5, 21.0)
+          const int at = stay_here(lane), g = at & 3, oq0 = o0 + 32 * tn + (at & 28);
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int32_t a = acc[f][tn][r] + corr[tn];
@@ -381,7 +390,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
           quad_transpose(v, lane);
 #pragma unroll
           for (int t4 = 0; t4 < 4; ++t4) {
-            const int oq = (o & ~3) + t4, g = lane & 3;
+            const int oq = oq0 + t4;
             if (oq < O && 4 * g < left)
               *reinterpret_cast<v4i_any*>(static_cast<int32_t*>(p.out) + obase + (int64_t)oq * HW + 4 * g) =
                   v4i{(int)v[t4][0], (int)v[t4][1], (int)v[t4][2], (int)v[t4][3]};
