@@ -11,6 +11,7 @@
 // a whole stage of matrix instructions to land in.  For that the wavefronts must be done with a slot early: fragments are
 // double-buffered by 32-k groups, the reads of a group go out behind the matrix instructions of the one before, so that
 // before its last group a stage has been read completely.  The one barrier per stage lies there, half as many per k.
+// (Lanes beyond K are masked in both operands, stream_offset.h: 4096 x 784 -> 3072 17.5 us, 17.7 with the weights alone masked.)
 // us, 64-byte stages and here (u8, both with the present epilogue): 4096 x 768 -> 3072 15.5, 14.6; -> 2304 13.4, 12.6;
 // 4096 x 4096 -> 4096 (256 x 256 tiles) 65, 62.  128 x 256 tiles serve layers that fill the chip with neither larger ones nor
 // one round of 128 x 128: 2048 x 768 -> 3072 10.1 (13.6), 2048 x 1024 -> 4096 13.5 (21.6), 3000 x 512 -> 2048 8.2 (11.2).  Now the main loop is 7.6 of 13.0 us of a workgroup at N = 3072, start 1.3,
@@ -65,22 +66,18 @@ __global__ __launch_bounds__(64 * WP * WQ, 1) void qgemm_line_kernel(QgemmParams
   for (int d = 0; d < L; ++d) {
     const bool isq = d >= GP / NW;
     const int row = (isq ? q0 - BP : p0) + (wave + NW * d) * RPI + lrow;
-    voff[d] = row < (isq ? p.M : p.N) ? (uint32_t)row * (uint32_t)p.K + (uint32_t)lck : kOob;
+    voff[d] = stream_row_offset(row, isq ? p.M : p.N, p.K, lck);
   }
   const int KT = (p.K + BK - 1) / BK;
-  // DMA instructions lo .. hi - 1 of a stage.  Stages beyond K have no records and write zeros.  In the stage that K ends
-  // inside, weight lanes beyond K get an offset beyond the tensor and write zeros; what the activations hold there is
-  // multiplied by them.
+  // DMA instructions lo .. hi - 1 of a stage.  Lanes beyond K, in the stage that K ends inside and in the ones behind it, get
+  // an offset beyond the tensor and write zeros.
   auto issue = [&](int stage, auto slot, auto lo, auto hi) {
-    const bool none = stage >= KT;  // uniform
-    const v4i dw = {rs_w.x, rs_w.y, none ? 0 : rs_w.z, rs_w.w}, da = {rs_a.x, rs_a.y, none ? 0 : rs_a.z, rs_a.w};
-    const bool inside = stage * BK + lck < p.K;
+    const int k0 = stage * BK;
     [&]<int... I>(std::integer_sequence<int, I...>) {
       ([&] {
         constexpr int d = decltype(lo)::value + I;
-        constexpr bool isq = d >= GP / NW;
-        dma16s(isq ? da : dw, wave_lds + (uint32_t)(decltype(slot)::value * STAGE + NW * d * 1024),
-               isq || inside ? voff[d] : kOob, (uint32_t)(stage * BK));
+        dma16s(d >= GP / NW ? rs_a : rs_w, wave_lds + (uint32_t)(decltype(slot)::value * STAGE + NW * d * 1024),
+               stream_lane_offset(voff[d], k0, lck, p.K), stream_scalar_offset(k0, p.K));
       }(), ...);
     }(std::make_integer_sequence<int, decltype(hi)::value - decltype(lo)::value>{});
   };

@@ -3,13 +3,12 @@
 #pragma once
 
 #include "qgemm_common.h"
+#include "stream_offset.h"
 
 #include <type_traits>
 #include <utility>
 
 namespace hago {
-
-constexpr uint32_t kOob = 0x80000000u;  // offset beyond any tensor (sizes are < 2^31 bytes)
 
 // Chunk permutation of an LDS row of BK bytes.  With these a fragment read (lane -> row lane % 32,
 // chunk 2 h + lane / 32 for 32-k group h) runs at the full LDS rate (measured; other XOR patterns
@@ -29,7 +28,8 @@ __device__ __forceinline__ void dma16(v4i rsrc, uint32_t lds_addr, uint32_t voff
                : "memory", "m0");
 }
 
-// Same with a scalar byte offset added to every lane's address (not range checked).
+// Same with a scalar byte offset added to every lane's address.  The range check does not see it: what is not to be fetched
+// needs a lane offset beyond the tensor.
 __device__ __forceinline__ void dma16s(v4i rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
