@@ -210,43 +210,27 @@ __global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
   const int g0 = groups * wave / NW, g1 = groups * (wave + 1) / NW;
   const int gf = g1 < (p.K >> 5) ? g1 : (p.K >> 5);  // complete groups end here
 
-  // per-channel constants of the finishing threads: thread (g4, lane) of the first 256.  int8: requested behind the first
-  // operands (in front of them small calls were 0.2 us longer); int16: in front (0.3 us longer behind them).
-  const int fin_n = n0 + 8 * (t >> 6) + 4 * fhalf;  // first of its four channels (t < 256)
-  int32_t bias[4] = {0, 0, 0, 0}, mu[4] = {0, 0, 0, 0}, sh[4] = {0, 0, 0, 0};
+  // per-channel constants of the finishing threads: thread (g4, lane) of the first 256.  By descriptor, three loads in front of
+  // the operands' and no load under a condition of its own (us, so and as loads under conditions behind the first operands,
+  // whose results are copied and therefore waited for one after another: 702 x 2112 -> 128 5.49, 5.67; 300 x 100 -> 500 3.26,
+  // 3.47; 3 x 63 -> 92 3.52, 3.58; int16 128 x 256 -> 512 4.45, 4.62, 100 x 400 -> 300 4.53 both).  What they mean is sorted out
+  // when the tile is finished.  (The kernel arguments that this needs loaded with the first ones: all of these 0.2 longer.)
+  const int fin = 8 * wave + 4 * fhalf, fin_n = n0 + fin;  // first of its four channels (t < 256)
+  v4i bias, mu, sh;
   auto load_constants = [&]() {
-    if (t >= 256) return;  // wavefront-uniform
-    if (fin_n + 4 <= p.N && p.per_channel) {
-      auto four = [&](const int32_t* src, int32_t (&v)[4]) {
-        const v4i q = *reinterpret_cast<const v4i_any*>(src + fin_n);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = q[e];
-      };
-      if (p.bias) four(p.bias, bias);
-      if (p.has_rq) {
-        if (p.mult) four(p.mult, mu);
-        four(p.shift, sh);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int n = fin_n + e < p.N ? fin_n + e : p.N - 1;
-        if (p.bias) bias[e] = p.bias[n];
-        if (p.has_rq) {
-          if (p.mult) mu[e] = p.mult[p.per_channel ? n : 0];
-          sh[e] = p.shift[p.per_channel ? n : 0];
-        }
-      }
-    }
-    const int less = p.mult ? 0 : 1;  // (as rq_mult, rq_shift)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (!p.mult) mu[e] = 1 << 30;
-      sh[e] -= less;
-    }
+    if (wave >= 4) return;
+    auto four = [&](const int32_t* src, bool each) {
+      const int left = p.N - n0 < 32 ? p.N - n0 : 32;
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(src + (src && each ? n0 : 0)), 0,
+                                                                         src ? (each ? 4 * left : 4) : 0, 0x00020000);
+      return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, each ? 4 * fin : 0, 0, 0));
+    };
+    bias = four(p.bias, true);
+    mu = four(p.has_rq ? p.mult : nullptr, p.per_channel);
+    sh = four(p.has_rq ? p.shift : nullptr, p.per_channel);
   };
 
-  if (I16) load_constants();
+  load_constants();
   Tile32<I16> acc;
   acc.clear();
   int32_t wsum = 0, asum = 0;
@@ -311,15 +295,12 @@ __global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
     };
     Batch b0, b1;
     load(g0, b0);
-    if (!I16) load_constants();
     for (int g = g0; g < gf; g += 2 * U) {
       if (g + U < gf) load(g + U, b1);
       use(g, b0);
       if (g + 2 * U < gf) load(g + 2 * U, b0);
       if (g + U < gf) use(g + U, b1);
     }
-  } else if (!I16) {
-    load_constants();
   }
   if (gf < g1) {
     const int k = gf * 32 + 16 * fhalf;
@@ -362,7 +343,8 @@ __global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
   for (int e = 0; e < 4; ++e) {
     v[e] = s[e] + channel_term<I16>(p, bias[e], ws[e], groups * 32) + 128 * as;
     if (p.acc_wrap_shift) v[e] = wrap_acc_bits(v[e], p.acc_wrap_shift);
-    if (p.has_rq) v[e] = requant_general(v[e], mu[e], sh[e], p.rs);
+    const int c = p.per_channel ? e : 0;
+    if (p.has_rq) v[e] = requant_general(v[e], p.mult ? mu[c] : 1 << 30, sh[c] - (p.mult ? 0 : 1), p.rs);  // (as rq_mult, rq_shift)
   }
   store_four(p, m, fin_n, v);
 }
