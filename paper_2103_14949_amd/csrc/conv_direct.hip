@@ -84,6 +84,10 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   constexpr int NU = NHWC ? 8 : (AF == 2 ? 2 : 3);  // staging units per thread
   constexpr int NV = NHWC ? 4 : 16;   // dwords per unit
   constexpr int OB = 64 * WCH;        // output channels per workgroup
+  // 512 pixels channel-last: every register is taken (253 of 256).  Its channel constants wait in LDS, and it finds a row's
+  // image by division: with the form of one comparison it spilled 62 registers (us, so and then: 3 -> 64 7x7 on 8 x 224 x 224
+  // 13.0, 14.5, raw 20.4, 21.5; 64 -> 64 3x3 on 32 x 56 x 56 13.4, 14.6).
+  constexpr bool kTight = NHWC && AF == 2;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -165,7 +169,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   // image row of staged row v: whether it exists, and its offset (b * C * H + iy rows for NCHW, (b * H + iy) * W pixels for NHWC)
   auto image_row = [&](const TilePos& q, int v, uint32_t& off) {
     uint32_t hv = (uint32_t)(q.hv0 + v), b = (uint32_t)q.b0;
-    if (p.rows <= p.HV) {  // uniform: the tile crosses one image boundary at most
+    if (!kTight && p.rows <= p.HV) {  // uniform: the tile crosses one image boundary at most
       const bool over = hv >= (uint32_t)p.HV;
       hv -= over ? (uint32_t)p.HV : 0u;
       b += over ? 1u : 0u;
@@ -183,8 +187,8 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   };
   const __amdgpu_buffer_rsrc_t rs_act =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.act), 0, (int)p.act_bytes, 0x00020000);
-  uint32_t u_mask[NU];  // bytes of the loaded dwords that lie inside the image (NHWC: all or none)
-  int32_t u_shift[NU];  // bits that move them into place (> 0: right)
+  uint32_t u_mask[NHWC ? 1 : NU];  // NCHW: bytes of the loaded dwords that lie inside the image
+  int32_t u_shift[NU];  // NCHW: bits that move them into place (> 0: right); NHWC: bytes, -1: outside the image
   auto load_input = [&](const TilePos& q, int c0) {
 #pragma unroll
     for (int n = 0; n < NU; ++n) {
@@ -194,8 +198,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
       const int ix = q.x0 * p.sw + u_x[n] - p.pw - p.off_x;
       if constexpr (NHWC) {
         const bool ok = row_ok && (unsigned)ix < (unsigned)p.W;
-        u_mask[n] = ok ? 0xffffffffu : 0u;
-        u_shift[n] = 0;
+        u_shift[n] = ok ? 0 : -1;
         v4i v = {0, 0, 0, 0};
         if (ok) {
           // (16 bytes that would run past the tensor's end are read from its last 16 and moved into place later)
@@ -227,7 +230,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
       if (n > 0 && NT * n >= units) break;  // uniform
       __builtin_amdgcn_sched_barrier(0);    // one unit's registers at a time
       if (u_v[n] < 0) continue;
-      const uint32_t mask = u_mask[n], pad = p.pad4 & ~mask;
+      const uint32_t mask = NHWC ? (u_shift[n] < 0 ? 0u : 0xffffffffu) : u_mask[n], pad = p.pad4 & ~mask;
       uint8_t* dst = s_in + u_lds[n];
       if constexpr (NHWC) {
         uint32_t w[4];
@@ -428,7 +431,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
         c_sh = rq_shift(p.mult, p.shift, p.per_channel ? o : 0);
       }
     }
-    if constexpr (NHWC && AF == 2) {  // (that form has no register to spare)
+    if constexpr (kTight) {
       s_corr[t] = c_bias;
       s_mu[t] = c_mu;
       s_sh[t] = c_sh;
@@ -518,7 +521,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   auto form_terms = [&]() {
     int bad = p.out_mode != 0 || p.acc_wrap_shift != 0 || p.rs.half_away || p.rs.z_out < -256 || p.rs.z_out > 255 || p.C * T > 65536;
     if (t < OB) {
-      if constexpr (NHWC && AF == 2) {
+      if constexpr (kTight) {
         c_bias = s_corr[t];
         c_mu = s_mu[t];
         c_sh = s_sh[t];
