@@ -24,8 +24,13 @@ def test_stage_edges(tile, K):
             args = dev(a), act_qtype(a, za), dev(w), hago.QType(hago.I8), dev(bias)
             for acc, racc in ((hago.I32, ref.I32), (hago.I16, ref.I16)):
                 assert_same(host(hago.qdense(*args, acc)), ref.qdense(a, za, w, bias, racc), f"raw {M, N, K, acc}")
-            for clip in ((-128, 127), (-100, 90)):
-                assert_same(host(hago.qdense(*args, hago.I32, gpu_requant(mult, shift, False, 5, clip))),
-                            ref.qdense(a, za, w, bias, ref.I32, ref_requant(mult, shift, False, 5, clip)), f"{M, N, K, clip}")
+            # one channel in its first 32 with a shift that the folded (0) or the saturating form (22) does not take
+            for special in (None, 0, 22):
+                sh = shift.copy()
+                if special is not None:
+                    sh[min(21, N - 1)] = special
+                for out_u8, z, clip in ((False, 5, (-128, 127)), (False, 5, (-100, 90)), (True, 131, (0, 255))):
+                    assert_same(host(hago.qdense(*args, hago.I32, gpu_requant(mult, sh, out_u8, z, clip))),
+                                ref.qdense(a, za, w, bias, ref.I32, ref_requant(mult, sh, out_u8, z, clip)), f"{M, N, K, out_u8, clip, special}")
     finally:
         hago.set_test_hook(hago.HOOK_STREAM_TILE, -1)

@@ -60,7 +60,8 @@ def test_qdense_requant_and_acc16(M, N, K):
     assert_same(host(got), want, "acc16 requant")
 
 
-@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])  # 256 x 256, 192 x 256, 128 x 128 with 128- and with 64-byte stages, 64 x 64
+# 256 x 256, 192 x 256, 128 x 128 with 128- and with 64-byte stages, 64 x 64, 128 x 256, 64 x 64 with 128-byte stages
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 6])
 @pytest.mark.parametrize("K", [448, 400, 64, 16])  # whole 64-byte stages / a 16-byte tail / one stage
 @pytest.mark.parametrize("adt,za", [(np.uint8, 121), (np.uint8, 128), (np.int8, -4)])
 def test_qdense_every_tile_shape(tile, K, adt, za, stream_tile):
@@ -125,7 +126,7 @@ def _extreme_terms(rng, N):
     return bias.astype(np.int32), shift
 
 
-@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 6])
 @pytest.mark.parametrize("out_u8,z_out", [(False, 0), (True, 131), (False, -9)])
 def test_qdense_epilogue_switches_every_tile(tile, out_u8, z_out, stream_tile):
     """The streaming kernel's fused epilogue picks, per tile, between the folded arithmetic and the
