@@ -462,21 +462,32 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
   //   4096 x 768 -> 2304   14.5, [12.6], 19.7, 20.2, 22.5     4096 x 3072 -> 768   33.7, 27.6, 23.7, [15.7], 23.7
   //   2048 x 768 -> 768    12.8, 10.8, 9.0, 6.9, [6.1]        1024 x 1024 -> 1024  14.9, 12.4, 10.2, 7.5, [5.5]
   //   5000 x 640 -> 2560   [14.4], 21.9, 18.4, 24.0, 25.3     256 x 4096 -> 4096   41.8, 34.4, 29.6, [16.7], 17.0
-  struct Cand { int id, bp, bq; double fix, per_k; };
-  static const Cand cands[] = {{0, 256, 256, 3.7, 0.0089}, {1, 192, 256, 2.8, 0.0072}, {5, 128, 256, 1.9, 0.0062}, {2, 128, 128, 2.1, 0.0034}};
+  // Where K ends inside a 128-byte stage, every lane of the 128 x 128 tile works out its addresses (917 x 1344 -> 1216 8.8 as
+  // 128 x 128, 7.1 as 64 x 64; 1561 x 1600 -> 1040 10.7, 9.1).  Raw results take their bytes' time, int32 ones 0.055 us per
+  // 1000 of a tile (1565 x 384 -> 2496 raw: 128 x 256 11.5, 64 x 64 9.8; requantized 7.4, 7.0).  Over 90 shapes drawn at random,
+  // each requantized and raw, the tile so chosen is 0.2 % from the best on average, 5 % at most.
+  struct Cand { int id, bp, bq; double fix, per_k, tail_fix, tail_per_k; };
+  static const Cand cands[] = {{0, 256, 256, 3.7, 0.0089, 0, 0}, {1, 192, 256, 2.8, 0.0072, 0, 0}, {5, 128, 256, 1.9, 0.0062, 0, 0},
+                               {2, 128, 128, 2.1, 0.0034, 0.4, 0.0004}};
   const auto tiles = [&](int bp, int bq) { return (int64_t)((a.N + bp - 1) / bp) * ((a.M + bq - 1) / bq); };
+  const double raw = a.has_rq ? 0 : a.acc16 ? 2.7e-5 : 5.5e-5;  // per result of a tile
   // Long reductions on few 64 x 64 tiles are a chain of stages: with 128-byte ones, which two workgroups on a CU have room
   // for, 1024 x 2048 -> 1024 takes 6.65 (7.5), 1500 x 2688 -> 128 7.4 (8.4), 500 x 4096 -> 1024 11.4 (16.5), 1024 x 768 ->
-  // 768 4.8 (5.0); where K ends inside a stage every lane works out its addresses: 1000 x 1600 -> 512 7.3 (6.5),
-  // 1000 x 4032 -> 512 13.2 (16.2).
+  // 768 4.8 (5.0).  Where K ends inside a stage every lane works out its addresses; K % 128 = 64, which 64-byte stages
+  // do not know as a tail, is theirs: 1000 x 2880 -> 512 10.3 (9.2), 1000 x 4032 -> 512 12.4 (11.3), 300 x 3008 -> 1024 10.4
+  // (9.3); of the other K the longer ones are not: 357 x 3488 -> 720 11.9 (12.5), 3352 x 2272 -> 96 9.0 (9.4), but 768 x 1904 ->
+  // 1088 8.3 (8.4), 463 x 928 -> 1520 6.6 (6.3).
   const double rounds64 = (double)((tiles(64, 64) + 255) / 256);
-  const bool wide64 = rounds64 <= 2 && a.K >= 768 && (a.K % 128 == 0 || a.K >= 2816);
+  const bool wide64 = rounds64 <= 2 && a.K >= 768 && (a.K % 128 == 0 || (a.K % 64 != 0 && a.K >= 2048));
   double best_cost = rounds64 * (0.3 + 0.0023 * a.K);
-  if (wide64) best_cost = (rounds64 > 1 ? 0.0034 : 0.0022) * a.K;
+  if (wide64 && a.K % 128 == 0) best_cost = (rounds64 > 1 ? 0.0034 : 0.0022) * a.K;
   else if (best_cost < 0.003 * a.K) best_cost = 0.003 * a.K;  // (one tile's chain of stages)
+  best_cost += rounds64 * raw * 64 * 64;
   int best = wide64 ? 6 : 4;
   for (const Cand& c : cands) {
-    const double cost = (double)((tiles(c.bp, c.bq) + 255) / 256) * (c.fix + c.per_k * a.K);
+    const bool tail = a.K % 128 != 0;
+    const double one = c.fix + c.per_k * a.K + (tail ? c.tail_fix + c.tail_per_k * a.K : 0) + raw * c.bp * c.bq;
+    const double cost = (double)((tiles(c.bp, c.bq) + 255) / 256) * one;
     if (cost < best_cost) { best = c.id; best_cost = cost; }
   }
   return launch_qdense_dma(p, forced >= 0 ? forced : best, st);
