@@ -395,7 +395,12 @@ __device__ __forceinline__ constexpr int pix_perm(int r) {
   return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
 }
 
-template <int WP, int WQ, int TP, int TQ, bool ACT_ON_P, int OM, bool PIXPERM, bool RAGGED, bool AWAY>
+// Tiles inside the matrix store without a check, tiles that end with it check every group of four, and only where the packed
+// extent is no multiple of four is a group cut (checking for that everywhere: raw results of 2 x 16 -> 16 3.1 us, 2.8 so;
+// 6132 x 640 -> 192 6.1, 5.6).
+enum { kInside, kWholeGroups, kCutGroups };
+
+template <int WP, int WQ, int TP, int TQ, bool ACT_ON_P, int OM, bool PIXPERM, int EDGE, bool AWAY>
 __device__ __forceinline__ void qgemm_epilogue_fast(const QgemmParams& p, v16i (&acc)[TP][TQ],
                                                     int p0, int q0, const int32_t* s_corr,
                                                     const int32_t* s_mult,
@@ -425,9 +430,9 @@ __device__ __forceinline__ void qgemm_epilogue_fast(const QgemmParams& p, v16i (
           const int32_t r2 = finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 2] + c4.z, m4.z, s4.z, acc16, rs);
           const int32_t r3 = finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 3] + c4.w, m4.w, s4.w, acc16, rs);
           const size_t o = (size_t)j * p.N + (p0 + i_loc);
-          if (!RAGGED || (j < Q_ext && p0 + i_loc + 4 <= P_ext))
+          if (EDGE == kInside || (j < Q_ext && p0 + i_loc + (EDGE == kCutGroups ? 4 : 1) <= P_ext))
             store_group<OM>(p.out, o, r0, r1, r2, r3);
-          else if (j < Q_ext)
+          else if (EDGE == kCutGroups && j < Q_ext)
             store_some<OM>(p.out, o, {r0, r1, r2, r3}, P_ext - p0 - i_loc);
         }
       }
@@ -455,7 +460,7 @@ __device__ __forceinline__ void qgemm_epilogue_fast(const QgemmParams& p, v16i (
                              finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 1] + c, m, sh, acc16, rs),
                              finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 2] + c, m, sh, acc16, rs),
                              finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 3] + c, m, sh, acc16, rs));
-            if (!RAGGED || (j < Q_ext && i < P_ext))
+            if (EDGE == kInside || (j < Q_ext && i < P_ext))
               *reinterpret_cast<uint4*>(static_cast<uint8_t*>(p.out) + ((size_t)b * p.N + j) * ohw + pix) =
                   make_uint4(dw[0], dw[1], dw[2], dw[3]);
             continue;
@@ -476,7 +481,7 @@ __device__ __forceinline__ void qgemm_epilogue_fast(const QgemmParams& p, v16i (
                 const int32_t hi16 = finish_one<OM, AWAY>(acc[ti][tj][g2 * 8 + 2 * x + 1] + c, m, sh, acc16, rs);
                 dw[x] = ((uint32_t)lo16 & 0xffffu) | ((uint32_t)hi16 << 16);
               }
-              if (!RAGGED || (j < Q_ext && i < P_ext))
+              if (EDGE == kInside || (j < Q_ext && i < P_ext))
                 *reinterpret_cast<uint4*>(static_cast<int16_t*>(p.out) + ((size_t)b * p.N + j) * ohw + pix) =
                     make_uint4(dw[0], dw[1], dw[2], dw[3]);
             }
@@ -492,7 +497,7 @@ __device__ __forceinline__ void qgemm_epilogue_fast(const QgemmParams& p, v16i (
           const int32_t r1 = finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 1] + c, m, sh, acc16, rs);
           const int32_t r2 = finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 2] + c, m, sh, acc16, rs);
           const int32_t r3 = finish_one<OM, AWAY>(acc[ti][tj][g4 * 4 + 3] + c, m, sh, acc16, rs);
-          if (!RAGGED || (j < Q_ext && i < P_ext))
+          if (EDGE == kInside || (j < Q_ext && i < P_ext))
             store_group<OM>(p.out, ((size_t)b * p.N + j) * ohw + pix, r0, r1, r2, r3);
         }
       }
@@ -524,13 +529,12 @@ __device__ __forceinline__ void qgemm_epilogue(const QgemmParams& p, v16i (&acc)
   if (fast) {
     // interior tiles (block-uniform) run without the per-store bounds checks
     const bool ragged = p0 + BP > P_ext || q0 + BQ > Q_ext;
-#define HAGO_FAST_EPILOGUE_R(OM, AWAY)                                                                  \
-  (ragged ? qgemm_epilogue_fast<WP, WQ, TP, TQ, ACT_ON_P, OM, PIXPERM, true, AWAY>(p, acc, p0, q0,      \
-                                                                                   s_corr, s_mult,      \
-                                                                                   s_shift)             \
-          : qgemm_epilogue_fast<WP, WQ, TP, TQ, ACT_ON_P, OM, PIXPERM, false, AWAY>(p, acc, p0, q0,     \
-                                                                                    s_corr, s_mult,     \
-                                                                                    s_shift))
+#define HAGO_FAST_EPILOGUE_E(OM, EDGE, AWAY) \
+  qgemm_epilogue_fast<WP, WQ, TP, TQ, ACT_ON_P, OM, PIXPERM, EDGE, AWAY>(p, acc, p0, q0, s_corr, s_mult, s_shift)
+#define HAGO_FAST_EPILOGUE_R(OM, AWAY)                                                        \
+  (!ragged ? HAGO_FAST_EPILOGUE_E(OM, kInside, AWAY)                                          \
+           : ACT_ON_P || P_ext % 4 == 0 ? HAGO_FAST_EPILOGUE_E(OM, kWholeGroups, AWAY)        \
+                                        : HAGO_FAST_EPILOGUE_E(OM, (ACT_ON_P ? kWholeGroups : kCutGroups), AWAY))
     // (the tie rule only matters for requantized output)
 #define HAGO_FAST_EPILOGUE(OM) HAGO_FAST_EPILOGUE_R(OM, false)
     if (p.out_mode == 0) {
@@ -544,6 +548,7 @@ __device__ __forceinline__ void qgemm_epilogue(const QgemmParams& p, v16i (&acc)
       HAGO_FAST_EPILOGUE(2);
     }
 #undef HAGO_FAST_EPILOGUE_R
+#undef HAGO_FAST_EPILOGUE_E
 #undef HAGO_FAST_EPILOGUE
     return;
   }
