@@ -93,8 +93,10 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
   int32_t* s_shift = s_mult + CH;
   int64_t* s_c64 = reinterpret_cast<int64_t*>(s_shift + CH);
   int32_t* s_shm1 = reinterpret_cast<int32_t*>(s_c64 + CH);  // shift - 1
+  __shared__ int32_t s_vote;
 
   const int t = threadIdx.x;
+  if (t == 0) s_vote = 0;
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wp = wave % WP;
@@ -460,7 +462,7 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
     }
   }
   __syncthreads();
-  const int form = finish_channel_terms<NT, CH>(p, chregs, s_corr, s_mult, s_shift, s_c64,
+  const int form = finish_channel_terms<NT, CH>(p, chregs, s_corr, s_mult, s_shift, s_c64, &s_vote,
                                                 kSplitSum ? s_mult : nullptr, s_shm1);
   HAGO_STAMP(p, 4);
   if constexpr (!ACT_ON_P) {

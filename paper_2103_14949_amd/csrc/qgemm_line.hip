@@ -43,8 +43,10 @@ __global__ __launch_bounds__(64 * WP * WQ, 1) void qgemm_line_kernel(QgemmParams
   int32_t* s_shift = s_mult + BP;
   int64_t* s_c64 = reinterpret_cast<int64_t*>(s_shift + BP);
   int32_t* s_shm1 = reinterpret_cast<int32_t*>(s_c64 + BP);  // shift - 1
+  __shared__ int32_t s_vote;
 
   const int t = threadIdx.x;
+  if (t == 0) s_vote = 0;
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wp = wave % WP, wq = wave / WP;
@@ -192,7 +194,7 @@ __global__ __launch_bounds__(64 * WP * WQ, 1) void qgemm_line_kernel(QgemmParams
   v += __shfl_xor(v, 32);
   if (wave < WBLK && fhalf == 0) s_corr[wave * 32 + frow] = v;
   __syncthreads();
-  const int form = finish_channel_terms<NT, BP>(p, chregs, s_corr, s_mult, s_shift, s_c64, nullptr, s_shm1);
+  const int form = finish_channel_terms<NT, BP>(p, chregs, s_corr, s_mult, s_shift, s_c64, &s_vote, nullptr, s_shm1);
   HAGO_STAMP(p, 4);
   static_assert(BQ * (BP + 16) <= 2 * STAGE && (BQ * BP / 16) % NT == 0, "the results are staged in the ring's place");
   if (p.out_mode == 0 && !p.acc_wrap_shift && !p.rs.half_away) {
