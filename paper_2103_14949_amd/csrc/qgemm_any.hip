@@ -194,7 +194,7 @@ template <bool I16, bool MIS, int NW, int U>
 __global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
   constexpr int kEsz = I16 ? 2 : 1;
   __shared__ __attribute__((aligned(16))) int32_t s_part[NW][4][64][4];  // [wavefront][register group][lane][4]
-  __shared__ __attribute__((aligned(16))) int32_t s_wsum[NW][32], s_asum[I16 ? NW : 1][32];
+  __shared__ __attribute__((aligned(16))) int32_t s_wsum[NW][32], s_asum[I16 ? NW : 1][32], s_constant[3][32];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int frow = lane & 31, fhalf = lane >> 5;
@@ -210,27 +210,19 @@ __global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
   const int g0 = groups * wave / NW, g1 = groups * (wave + 1) / NW;
   const int gf = g1 < (p.K >> 5) ? g1 : (p.K >> 5);  // complete groups end here
 
-  // per-channel constants of the finishing threads: thread (g4, lane) of the first 256.  By descriptor, three loads in front of
-  // the operands' and no load under a condition of its own (us, so and as loads under conditions behind the first operands,
-  // whose results are copied and therefore waited for one after another: 702 x 2112 -> 128 5.49, 5.67; 300 x 100 -> 500 3.26,
-  // 3.47; 3 x 63 -> 92 3.52, 3.58; int16 128 x 256 -> 512 4.45, 4.62, 100 x 400 -> 300 4.53 both).  What they mean is sorted out
-  // when the tile is finished.  (The kernel arguments that this needs loaded with the first ones: all of these 0.2 longer.)
-  const int fin = 8 * wave + 4 * fhalf, fin_n = n0 + fin;  // first of its four channels (t < 256)
-  v4i bias, mu, sh;
-  auto load_constants = [&]() {
-    if (wave >= 4) return;
-    auto four = [&](const int32_t* src, bool each) {
-      const int left = p.N - n0 < 32 ? p.N - n0 : 32;
-      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(src + (src && each ? n0 : 0)), 0,
-                                                                         src ? (each ? 4 * left : 4) : 0, 0x00020000);
-      return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, each ? 4 * fin : 0, 0, 0));
-    };
-    bias = four(p.bias, true);
-    mu = four(p.has_rq ? p.mult : nullptr, p.per_channel);
-    sh = four(p.has_rq ? p.shift : nullptr, p.per_channel);
-  };
-
-  load_constants();
+  // the tile's per-channel constants: wavefronts 0, 1 and 2 load the bias, the multipliers and the shifts, one dword per lane,
+  // in front of the operands; they meet the finishing threads in LDS.  (Loaded by those themselves, three times 16 bytes per
+  // lane in each of four wavefronts, they kept the memory pipe from the operands: us, so and then, 1280 x 1776 -> 192 6.3, 6.7;
+  // 1128 x 1552 -> 112 5.2, 5.45; 3 x 1680 -> 32 4.1, 4.45; int16 128 x 256 -> 512 4.3, 4.45, 100 x 400 -> 300 4.3, 4.5.)
+  int32_t constant = 0;
+  if (wave < 3) {
+    const int32_t* src = wave == 0 ? p.bias : !p.has_rq ? nullptr : wave == 1 ? p.mult : p.shift;
+    const bool each = wave == 0 || p.per_channel;
+    const int left = p.N - n0 < 32 ? p.N - n0 : 32;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(src + (src && each ? n0 : 0)), 0,
+                                                                       src ? (each ? 4 * left : 4) : 0, 0x00020000);
+    constant = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, each ? 4 * frow : 0, 0, 0);
+  }
   Tile32<I16> acc;
   acc.clear();
   int32_t wsum = 0, asum = 0;
@@ -315,6 +307,7 @@ __global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
   if (fhalf == 0) {
     s_wsum[wave][frow] = wsum;
     if constexpr (I16) s_asum[wave][frow] = asum;
+    if (wave < 3) s_constant[wave][frow] = constant;
   }
 #pragma unroll
   for (int g = 0; g < 4; ++g)
@@ -323,13 +316,13 @@ __global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
   if (t >= 256) return;
 
   // thread (g4 = t / 64, lane): channels fin_n .. fin_n + 3 of row m0 + lane % 32
-  const int g4 = t >> 6, m = m0 + frow;
+  const int g4 = t >> 6, m = m0 + frow, fin = 8 * g4 + 4 * fhalf, fin_n = n0 + fin;
   v4i s = {0, 0, 0, 0};
   int32_t ws[4] = {0, 0, 0, 0}, as = 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
     const v4i q = *reinterpret_cast<const v4i*>(s_part[w][g4][lane]);
-    const v4i qs = *reinterpret_cast<const v4i*>(&s_wsum[w][8 * g4 + 4 * fhalf]);
+    const v4i qs = *reinterpret_cast<const v4i*>(&s_wsum[w][fin]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       s[e] += q[e];
@@ -338,13 +331,14 @@ __global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
     if constexpr (I16) as += s_asum[w][frow];
   }
   if (m >= p.M || fin_n >= p.N) return;
+  const v4i bias = *reinterpret_cast<const v4i*>(&s_constant[0][fin]), mu = *reinterpret_cast<const v4i*>(&s_constant[1][fin]),
+            sh = *reinterpret_cast<const v4i*>(&s_constant[2][fin]);
   int32_t v[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     v[e] = s[e] + channel_term<I16>(p, bias[e], ws[e], groups * 32) + 128 * as;
     if (p.acc_wrap_shift) v[e] = wrap_acc_bits(v[e], p.acc_wrap_shift);
-    const int c = p.per_channel ? e : 0;
-    if (p.has_rq) v[e] = requant_general(v[e], p.mult ? mu[c] : 1 << 30, sh[c] - (p.mult ? 0 : 1), p.rs);  // (as rq_mult, rq_shift)
+    if (p.has_rq) v[e] = requant_general(v[e], p.mult ? mu[e] : 1 << 30, sh[e] - (p.mult ? 0 : 1), p.rs);  // (as rq_mult, rq_shift)
   }
   store_four(p, m, fin_n, v);
 }
