@@ -445,12 +445,17 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
     return launch_qgemm_any(p, a.operand16, tile < 0 ? -1 : tile % 5, st);
   }
   const int forced = g_hook[kHookDmaTile].load(std::memory_order_relaxed);
-  // A long reduction over few tiles: the direct form splits it over eight wavefronts (equal at K = 768).  us, there and as
-  // 64 x 64 tiles with 128-byte stages: 1 x 4096 -> 4096 8.1, 10.9; 1 x 1024 -> 4096 4.6, 5.0; 16 x 2048 -> 2048 6.0, 6.6;
-  // 200 x 4096 -> 1024 10.1, 11.3; 702 x 2112 -> 128, where K ends inside a stage, 5.5, 7.4; but with more rows
-  // 90 x 1280 -> 1280 6.6, 5.4; 627 x 1536 -> 320 6.8, 5.8; 300 x 2048 -> 1024 7.2, 6.5.
-  if (forced < 0 && a.K >= 1024 && (int64_t)((a.N + 31) / 32) * ((a.M + 31) / 32) <= 256 &&
-      (a.M <= 32 || a.K % 128 != 0 || a.K >= 4096))
+  // One round of 32 x 32 tiles over the chip: the direct form, whose wavefronts split the reduction.  It wins wherever K ends
+  // inside a stage of 128 bytes, the more the longer K is (us, direct and the better of the 64 x 64 tiles: 996 x 16 -> 16 2.9,
+  // 3.2; 443 x 144 -> 16 2.8, 3.5; 62 x 448 -> 208 3.5, 4.4; 429 x 560 -> 368 3.8, 5.0; 170 x 1424 -> 208 4.9, 6.6;
+  // 51 x 5232 -> 16 8.1, 14.6; the other way 4 x 64 -> 64 3.0, 2.9: few rows and an odd multiple of 64).  Whole stages are loaded faster there than here: it wins
+  // from K = 768 to 1024 (1245 x 768 -> 32 4.4, 4.4; 56 x 1024 -> 2528 4.3, 4.8; but 258 x 512 -> 32 4.1, 3.8, 34 x 1280 -> 352
+  // 5.95, 4.9), from K = 640 with up to 16 rows, half of whose lanes share their lines (8 x 768 -> 736 4.0, 4.6; 2 x 5120 -> 96
+  // 8.7, 10.9; but 64 x 4096 -> 512 9.8, 9.4), and with very long ones over most of the chip (200 x 8192 -> 1024 17.1, 18.65;
+  // but 100 x 8192 -> 512 16.8, 15.6).
+  const int64_t t32 = (int64_t)((a.N + 31) / 32) * ((a.M + 31) / 32);
+  if (forced < 0 && t32 <= 256 &&
+      (a.K % 128 != 0 ? a.K % 64 != 0 || a.K >= 320 || a.M > 4 : a.M <= 16 ? a.K >= 640 : (a.K >= 768 && a.K <= 1024) || (a.K >= 7168 && t32 > 128)))
     return launch_qgemm_any(p, false, 0, st);
   p.vec_k = 1;
   p.vec_out = (a.N % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
@@ -468,7 +473,7 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
   // each requantized and raw, the tile so chosen is 0.2 % from the best on average, 5 % at most.
   struct Cand { int id, bp, bq; double fix, per_k, tail_fix, tail_per_k; };
   static const Cand cands[] = {{0, 256, 256, 3.7, 0.0089, 0, 0}, {1, 192, 256, 2.8, 0.0072, 0, 0}, {5, 128, 256, 1.9, 0.0062, 0, 0},
-                               {2, 128, 128, 2.1, 0.0034, 0.4, 0.0004}};
+                               {2, 128, 128, 2.1, 0.0034, 0.5, 0.0005}};
   const auto tiles = [&](int bp, int bq) { return (int64_t)((a.N + bp - 1) / bp) * ((a.M + bq - 1) / bq); };
   const double raw = a.has_rq ? 0 : a.acc16 ? 2.7e-5 : 5.5e-5;  // per result of a tile
   // Long reductions on few 64 x 64 tiles are a chain of stages: with 128-byte ones, which two workgroups on a CU have room
