@@ -686,7 +686,7 @@ hipError_t launch_staged(const QgemmParams& p, hipStream_t st) {
 }  // namespace
 
 // Any M, N >= 1, K >= 0 and alignment.  form < 0: by size (us on one MI355X beside each rule); 0 direct with 8
-// wavefronts, 1 direct with 4, 2 staged 64 x 64, 3 staged 128 x 128, 4 staged 64 x 64 with two sets (int8).
+// wavefronts, 1 direct with 4 (int16: with 8 too), 3 staged 128 x 128, 4 and others staged 64 x 64 with two sets of wavefronts.
 hipError_t launch_qgemm_any(const QgemmParams& p, bool i16, int form, hipStream_t st) {
   const int64_t t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32), t64 = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64);
   const int64_t groups = (p.K + 31) / 32;
@@ -708,9 +708,8 @@ hipError_t launch_qgemm_any(const QgemmParams& p, bool i16, int form, hipStream_
   auto run = [&]<bool MIS>() {
     if (i16) {
       switch (form) {
-        case 0: return launch_direct<true, MIS, 8, 2>(p, st);
-        case 1: return launch_direct<true, MIS, 4, 2>(p, st);
-        case 2: return launch_staged<true, 2, 2, 1, 1, 1>(p, st);
+        case 0:
+        case 1: return launch_direct<true, MIS, 8, 2>(p, st);
         case 3: return launch_staged<true, 2, 4, 2, 1, 1>(p, st);
         default: return launch_staged<true, 2, 2, 1, 1, 2>(p, st);
       }
@@ -718,7 +717,6 @@ hipError_t launch_qgemm_any(const QgemmParams& p, bool i16, int form, hipStream_
     switch (form) {
       case 0: return launch_direct<false, MIS, 8, 4>(p, st);
       case 1: return launch_direct<false, MIS, 4, 4>(p, st);
-      case 2: return launch_staged<false, 2, 2, 1, 1, 1>(p, st);
       case 3: return launch_staged<false, 2, 4, 2, 1, 1>(p, st);
       default: return launch_staged<false, 2, 2, 1, 1, 2>(p, st);
     }
