@@ -294,11 +294,12 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   const int wunits = OB * wper;
   // Units that are whole or nothing are loaded by descriptor, the ones beyond the channels out of its range (us with a
   // 64-bit address and conditions per unit and so: 48 -> 64 3x3 stride 2 on 16 x 56 x 56 9.1, 8.4, channel-last, all in
-  // this kernel, 10.5, 9.1; 64 -> 128 on as many 8.9, 8.6).
+  // this kernel, 10.5, 9.1; 64 -> 128 on as many 8.9, 8.6).  Not units of nine dwords where channels come in chunks: 190 -> 132 3x3
+  // stride 2 on 18 x 38 x 40 25.0, 24.3 without; 242 -> 244 on 13 x 27 x 30 22.1, 21.7.
   const int w_left = p.O - o0 < OB ? p.O - o0 : OB;
   const __amdgpu_buffer_rsrc_t rs_wgt = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<int8_t*>(p.wgt) + (int64_t)o0 * p.C * T, 0, w_left * p.C * T, 0x00020000);
-  const bool w_whole = !SMALL && ((WT == 9 && p.C % 4 == 0) || (WT == 2 && p.C % 16 == 0));
+  const bool w_whole = !SMALL && ((WT == 9 && !MULTI && p.C % 4 == 0) || (WT == 2 && p.C % 16 == 0));
   auto load_weights = [&](int c0, int i0) {
     if (w_whole) {  // uniform
 #pragma unroll
