@@ -19,6 +19,8 @@
 #include "hago_device.h"
 #include "launch.h"
 
+#include <cmath>
+
 namespace hago {
 
 namespace {
@@ -304,7 +306,8 @@ hipError_t launch_shape(const CgParams& p, int mode, hipStream_t st) {
     auto kern = mode == 0 ? conv_gather_kernel<0, MIS, TP, TC, KS> : mode == 1 ? conv_gather_kernel<1, MIS, TP, TC, KS> : conv_gather_kernel<2, MIS, TP, TC, KS>;
     hipLaunchKernelGGL(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
   };
-  if (q.C % 4 != 0 || ((reinterpret_cast<uintptr_t>(q.act) | reinterpret_cast<uintptr_t>(q.wgt)) & 3u) != 0) run.template operator()<true>();
+  // (one step is over before the shifts pay: 22 -> 20 1x1 stride 2 on 59 x 27 x 25 3.15 us, 3.25 with them)
+  if (q.steps > 1 && (q.C % 4 != 0 || ((reinterpret_cast<uintptr_t>(q.act) | reinterpret_cast<uintptr_t>(q.wgt)) & 3u) != 0)) run.template operator()<true>();
   else run.template operator()<false>();
   return hipGetLastError();
 }
@@ -676,20 +679,26 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace,
   p.acc_wrap_shift = a.acc_wrap_shift;
   p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
   const int mode = a.has_rq ? 0 : (a.acc16 ? 2 : 1);
-  // Microseconds, fitted to 36 layers drawn at random (each within 12%).  Here, per tile of a CU: 2.3 and 0.108 a step for 64 x
-  // 64, 0.53 and 0.059 for 32 x 32, a step's part 1.4 times that where the operands' rows are unaligned (the one-launch
-  // kernel loses 1.6 there).  The other kernels: 6 and their
-  // rate, or the length of the reduction where there are few tiles.  Measured (here, other): 16 x 28 x 28 64 -> 64 3x3 5.4,
-  // 8.4; one image 3.9, 7.1; 32 x 14 x 14 128 -> 128 8.4, 12.0; 8 x 56 x 56 64 -> 128 stride 2 5.8, 10.4; 57 x 56
-  // 224 -> 224 7x7 stride 2 31, 66; 4 x 40 x 40 100 -> 200 1x1 stride 2 3.9, 7.8; but 32 x 28 x 28 128 -> 128 22.7, 15.1.
+  // Microseconds, fitted to 333 layers drawn at random (over 333 others the kernel so chosen is 2.5 % from the best on average,
+  // half as long again in the worst).  Here: a start, and per tile of a CU 2.2 and 0.075 a step for 64 x 64, of which a CU has whole rounds up to the third and several side by side
+  // beyond, 0.62 and 0.049 for 32 x 32; a step's part is 1.65 times that where the operands' rows are unaligned.  The other
+  // kernels: 5.9, their rate, the length of the reduction and the tensors' bytes, all but the last 1.2 times for unaligned rows
+  // without a workspace.  Measured (here, other): 16 x 28 x 28 64 -> 64 3x3 5.4, 8.4; one image 3.9, 7.1; 32 x 14 x 14 128 -> 128 8.4,
+  // 12.0; 8 x 56 x 56 64 -> 128 stride 2 5.8, 10.4; 57 x 56 224 -> 224 7x7 stride 2 31, 66; 4 x 40 x 40 100 -> 200 1x1 stride 2
+  // 3.9, 7.8; 4 x 82 x 84 27 -> 104 3x3 11.0, 13.5; 5 x 74 x 72 48 -> 39 5x5 10.1, 17.2; but 32 x 28 x 28 128 -> 128 22.7, 15.1;
+  // 20 x 69 x 72 21 -> 33 5x5 28.8, 17.4; 7 x 72 x 72 113 -> 60 3x3 22.7, 17.5.
   auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
-  const double step = p.steps * (cg.C % 4 ? 1.4 : 1.0);
-  auto time = [&](int64_t n, double tile, double per_step) { return (tile + per_step * step) * (n > 256 ? (double)n / 256 : 1.0); };
-  const double t64 = 1.6 + time(tiles(64), 2.3, 0.108), t32 = 2.5 + time(tiles(32), 0.53, 0.059);
+  const double step = p.steps * (cg.C % 4 ? 1.65 : 1.0);
+  const double x64 = (double)tiles(64) / 256, x32 = (double)tiles(32) / 256;
+  const double t64 = 1.9 + (2.2 + 0.075 * step) * (x64 <= 1 ? 1.0 : x64 <= 3 ? 0.95 * std::ceil(x64) : 2.85 + 0.8 * (x64 - 3));
+  const double t32 = 2.5 + (0.62 + 0.049 * step) * (x32 <= 1 ? 1.0 : std::pow(x32, 0.93));
   int shape = forced_shape;
   if (shape < 0) {
-    const double rate = (double)a.M * a.N * a.K / 0.41e9, length = (double)a.K / 256;
-    if ((t64 < t32 ? t64 : t32) >= (6.0 + (rate > length ? rate : length)) * (cg.C % 4 && !has_workspace ? 1.6 : 1.0)) return false;
+    const double bytes = (double)act_bytes + (double)a.M * a.N * (mode == 0 ? 1 : mode == 1 ? 4 : 2);
+    const double rate = (double)a.M * a.N * a.K / 0.41e9, length = (double)a.K / 175;
+    const double steps_and_rate = rate > length ? rate + 0.8 * length : length + 0.8 * rate;
+    const double other = (5.9 + steps_and_rate) * (cg.C % 4 && !has_workspace ? 1.2 : 1.0) + bytes / 4e6;
+    if ((t64 < t32 ? t64 : t32) >= other) return false;
     shape = t32 < t64 ? 2 : tiles(64) <= 256;  // (eight wavefronts fill a CU's LDS)
   }
   switch (shape) {
@@ -748,9 +757,10 @@ bool try_qconv_gather_nchw(const GemmArgs& a, const ConvGeom& cg, bool has_works
   // 64 x 32 x 32 3 -> 16 6.6, 8.6.
   const double step = cg.stride_w > 1 ? 1.8 * p.steps : (double)p.steps;
   const double r32 = (double)p.tiles * ((a.N + 31) / 32) / 256, r64 = (double)p.tiles * ((a.N + 63) / 64) / 256;
-  // (long reductions of neighbouring pixels: blocks of 32 by eight wavefronts, 34 -> 140 5x5 on 88 x 87 18.8, with 64 by four 25.6)
+  // (long reductions of neighbouring pixels: blocks of 32 by eight wavefronts, 34 -> 140 5x5 on 88 x 87 18.8, with 64 by four 25.6,
+  // but with one round of the latter, 128 -> 34 5x5 on 2 x 51 x 52, 25.9 and 20.1)
   const bool deep = p.steps >= 24 && cg.stride_w == 1;
-  const double t32 = (r32 > 1 ? r32 : 1.0) * (0.4 + 0.12 * step), t64 = (r64 > 1 ? r64 : 1.0) * (0.4 + 0.15 * step) * (deep ? 1.4 : 1.0);
+  const double t32 = (r32 > 1 ? r32 : 1.0) * (0.4 + 0.12 * step), t64 = (r64 > 1 ? r64 : 1.0) * (0.4 + 0.15 * step) * (deep && r64 > 1 ? 1.4 : 1.0);
   const bool alone = p.steps <= 2 && r64 >= 4;
   int shape = forced_shape;
   if (shape < 0) {
