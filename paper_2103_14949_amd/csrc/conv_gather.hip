@@ -685,7 +685,7 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace,
   // kernels: 5.9, their rate, the length of the reduction and the tensors' bytes, all but the last 1.2 times for unaligned rows
   // without a workspace.  Measured (here, other): 16 x 28 x 28 64 -> 64 3x3 5.4, 8.4; one image 3.9, 7.1; 32 x 14 x 14 128 -> 128 8.4,
   // 12.0; 8 x 56 x 56 64 -> 128 stride 2 5.8, 10.4; 57 x 56 224 -> 224 7x7 stride 2 31, 66; 4 x 40 x 40 100 -> 200 1x1 stride 2
-  // 3.9, 7.8; 4 x 82 x 84 27 -> 104 3x3 11.0, 13.5; 5 x 74 x 72 48 -> 39 5x5 10.1, 17.2; but 32 x 28 x 28 128 -> 128 22.7, 15.1;
+  // 3.9, 7.8; 22 x 41 x 41 32 -> 32 3x3 6.8, 8.6; 5 x 74 x 72 48 -> 39 5x5 10.1, 17.2; but 32 x 28 x 28 128 -> 128 22.7, 15.1;
   // 20 x 69 x 72 21 -> 33 5x5 28.8, 17.4; 7 x 72 x 72 113 -> 60 3x3 22.7, 17.5.
   auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
   const double step = p.steps * (cg.C % 4 ? 1.65 : 1.0);

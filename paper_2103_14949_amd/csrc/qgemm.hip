@@ -458,7 +458,6 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
       (a.K % 128 != 0 ? a.K % 64 != 0 || a.K >= 320 || a.M > 4 : a.M <= 16 ? a.K >= 640 : (a.K >= 768 && a.K <= 1024) || (a.K >= 7168 && t32 > 128)))
     return launch_qgemm_any(p, false, 0, st);
   p.vec_k = 1;
-  p.vec_out = (a.N % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
   p.vec16_out = (a.N % 16 == 0) && ptr_aligned(a.out, 16);
   // Tile shape: the least time on the busiest CU, in microseconds: rounds of tiles over the 256 CUs (one workgroup on each,
   // but of the 64 x 64 tiles, whose loads and matrix instructions overlap each other's), each a constant and a part
@@ -546,7 +545,6 @@ static hipError_t conv_dma(const GemmArgs& a, const ConvGeom& cg, void* ws, bool
   p.inv_c = (uint32_t)(((1ull << 32) + (uint64_t)Cp - 1) / (uint64_t)Cp);
   p.inv_kw = cg.KW > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)cg.KW - 1) / (uint64_t)cg.KW) : 0u;
   if (cg.nhwc) {
-    p.vec_out = (a.N % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
     p.vec16_out = (a.N % 16 == 0) && ptr_aligned(a.out, 16);
   } else {
     p.vec_out = ((cg.OH * cg.OW) % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
@@ -602,7 +600,6 @@ static hipError_t launch_qconv_chosen(const GemmArgs& a, const ConvGeom& cg, voi
   QgemmParams p = make_qgemm_params(a, &cg);
   if (cg.nhwc) {
     p.vec_k = (cg.C % 16 == 0) && ptr_aligned(a.act, 16) && ptr_aligned(a.wgt, 16);
-    p.vec_out = (a.N % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
     return launch_shape<MODE_CONV_NHWC>(pick_shape(MODE_CONV_NHWC, a.N, a.M, a.K), p, st);
   }
   p.vec_k = (a.K % 16 == 0) && ptr_aligned(a.wgt, 16);

@@ -46,7 +46,7 @@ struct QgemmParams {
   int32_t corr_coef;   // off - z_a
   uint32_t pad_byte;   // staged value of a padded tap: (z_a XOR act_xor) & 0xff
   int32_t vec_k;       // rows of both operands can be read as aligned 16-byte chunks
-  int32_t vec_out;     // four consecutive results along the packed axis form one aligned store
+  int32_t vec_out;     // NCHW: four consecutive pixels lie in one image and form one aligned store
   int32_t vec16_out;   // dense: output rows can be written as aligned 16-byte pieces
   RequantScalars rs;
   ConvGeom g;
@@ -540,7 +540,7 @@ __device__ __forceinline__ void qgemm_epilogue(const QgemmParams& p, v16i (&acc)
   const int P_ext = ACT_ON_P ? p.M : p.N;
   const int Q_ext = ACT_ON_P ? p.N : p.M;
   const int ohw = p.g.OH * p.g.OW;
-  const bool fast = !ACT_ON_P || p.vec_out;  // (vec_out: groups of four along the packed axis are aligned stores)
+  const bool fast = !ACT_ON_P || p.vec_out;
 
   if (fast) {
     // interior tiles (block-uniform) run without the per-store bounds checks
