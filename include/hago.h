@@ -441,6 +441,7 @@ hago_status hago_probe_copy(const void* src, void* dst, int64_t bytes,
  *                           convolution kernel; 4 the convolution kernels
  *                           without staging
  *   HAGO_HOOK_STREAM_TILE   -1 automatic; 0..6 a tile of the streaming dense kernels
+ *                           (3 is 2)
  *   HAGO_HOOK_GENERAL_TILE  -1 automatic; 0..6 a tile of the general convolution
  *                           kernel (modulo 5: a form of the general dense kernel)
  * Unknown keys are ignored.

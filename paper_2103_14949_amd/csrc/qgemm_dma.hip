@@ -526,8 +526,8 @@ hipError_t launch_qdense_line(const QgemmParams& p, int shape, hipStream_t st);
 hipError_t launch_qdense_dma(const QgemmParams& p, int shape, hipStream_t st) {
   switch (shape) {
     case 1: return launch_qdense_line(p, 1, st);                                  // 192 x 256
-    case 2: return launch_dma_cfg<2, 4, 2, 1, 4, 1, false, false, 128>(p, st);   // 128 x 128, 128-byte stages
-    case 3: return launch_dma_cfg<2, 4, 2, 1, 4, 1, false, false>(p, st);   // 128 x 128, 64-byte stages
+    case 2:
+    case 3: return launch_dma_cfg<2, 4, 2, 1, 4, 1, false, false, 128>(p, st);   // 128 x 128, 128-byte stages
     case 4: return launch_dma_cfg<2, 2, 1, 1, 4, 2, false, false>(p, st);   // 64 x 64: few rows
     case 6: return launch_dma_cfg<2, 2, 1, 1, 4, 2, false, false, 128>(p, st);   // 64 x 64, 128-byte stages: long reductions
     case 5: return launch_qdense_line(p, 5, st);                                  // 128 x 256

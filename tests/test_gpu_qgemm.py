@@ -60,7 +60,7 @@ def test_qdense_requant_and_acc16(M, N, K):
     assert_same(host(got), want, "acc16 requant")
 
 
-# 256 x 256, 192 x 256, 128 x 128 with 128- and with 64-byte stages, 64 x 64, 128 x 256, 64 x 64 with 128-byte stages
+# 256 x 256, 192 x 256, 128 x 128 (2 and 3), 64 x 64, 128 x 256, 64 x 64 with 128-byte stages
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5, 6])
 @pytest.mark.parametrize("K", [448, 400, 64, 16])  # whole 64-byte stages / a 16-byte tail / one stage
 @pytest.mark.parametrize("adt,za", [(np.uint8, 121), (np.uint8, 128), (np.int8, -4)])
