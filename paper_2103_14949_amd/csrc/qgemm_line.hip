@@ -15,7 +15,7 @@
 // us, 64-byte stages and here (u8, both with the present epilogue): 4096 x 768 -> 3072 15.5, 14.6; -> 2304 13.4, 12.6;
 // 4096 x 4096 -> 4096 (256 x 256 tiles) 65, 62.  128 x 256 tiles serve layers that fill the chip with neither larger ones nor
 // one round of 128 x 128: 2048 x 768 -> 3072 10.1 (13.6), 2048 x 1024 -> 4096 13.5 (21.6), 3000 x 512 -> 2048 8.2 (11.2).  Now the main loop is 7.6 of 13.0 us of a workgroup at N = 3072, start 1.3,
-// channel terms 0.9, requantize 1.7, copy-out 0.5, and 2.3 lie between two launches.
+// channel terms 0.8, requantize 1.7, copy-out 0.5, and 2.3 lie between two launches.
 #include "qgemm_stream.h"
 
 namespace hago {
