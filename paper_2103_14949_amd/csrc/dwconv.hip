@@ -36,7 +36,30 @@ struct DwArgs {
   const int32_t* shift;
   int32_t per_channel;
   RequantScalars rs;
+  uint32_t inv_x, inv_mid;  // xcd_place's divisors: ceil(2^32 / d), 0 where that is not exact (or d is 1)
 };
+
+// The work of a launch of gridDim.x * mid * outer workgroups, the outermost index first: images, in all three kernels, so
+// that each keeps to the XCD that its neighbours in a network of 1x1 layers use for it.  Us of an expansion, a depthwise
+// layer and a projection, with the workgroups in launch order (an image's channels on all XCDs) and so, buffers kept
+// and three sets of them in turn: 24 -> 144 -> 24 on 8 x 56 x 56 14.0, 11.9 and 15.0, 13.0; on 32 x 56 x 56 29.9, 22.2 and 23.3,
+// 23.3 (14 MB between the layers: rewriting lines that other XCDs still hold is what cost the first).
+struct DwPlace { int32_t x, mid, outer; };
+__device__ __forceinline__ DwPlace xcd_place(const DwArgs& p, uint32_t mid) {
+  auto over = [](uint32_t n, uint32_t d, uint32_t inv) {
+    return d == 1 ? n : (inv ? __umulhi(n, inv) : (uint32_t)__builtin_amdgcn_readfirstlane((int)(n / d)));
+  };
+  const uint32_t gx = gridDim.x, count = gx * gridDim.y * gridDim.z;
+  const uint32_t id = xcd_run(blockIdx.x + gx * (blockIdx.y + gridDim.y * blockIdx.z), count);
+  const uint32_t rest = over(id, gx, p.inv_x), outer = over(rest, mid, p.inv_mid);
+  return DwPlace{(int32_t)(id - rest * gx), (int32_t)(rest - outer * mid), (int32_t)outer};
+}
+DwArgs with_divisors(DwArgs p, int64_t gx, int64_t mid, int64_t outer) {
+  auto inverse = [](int64_t d, int64_t n) { return d > 1 && n * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d) : 0u; };
+  p.inv_x = inverse(gx, gx * mid * outer);
+  p.inv_mid = inverse(mid, mid * outer);
+  return p;
+}
 
 __device__ __forceinline__ int32_t wrap_acc(int32_t acc, int wrap_shift) {
   return wrap_shift ? wrap_acc_bits(acc, wrap_shift) : acc;
@@ -163,15 +186,16 @@ __device__ __forceinline__ DwChannel dw_channel(const DwArgs& p, int c) {
 // end of its left neighbour's results (16 x 288 planes of 41 x 41: 24.8 us through LDS, 8.6 here).
 template <int MODE, bool ACC16, bool WIDE, bool RAGGED>
 __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t rpc, int32_t nsegs, int32_t segw) {
-  // grid: x = groups of four channels, y = image, z = band (and column segment)
+  // grid: x = groups of four channels, y = image, z = band (and column segment); numbered image, band, group
   const ConvGeom& g = p.g;
   const int H = g.H, W = g.W;
   const int lane = threadIdx.x & 63;
-  const int c = (int)(blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const DwPlace at = xcd_place(p, gridDim.z);
+  const int c = at.x * 4 + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (c >= g.C) return;  // wavefront-uniform; the kernel has no barrier
-  const int64_t plane = (int64_t)blockIdx.y * g.C + c;
-  const int seg = WIDE ? (int)blockIdx.z % nsegs : 0;
-  const int band = WIDE ? (int)blockIdx.z / nsegs : (int)blockIdx.z;
+  const int64_t plane = (int64_t)at.outer * g.C + c;
+  const int seg = WIDE ? at.mid % nsegs : 0;
+  const int band = WIDE ? at.mid / nsegs : at.mid;
   const int cb = WIDE ? seg * segw : 0;  // first column of the segment
   constexpr uint32_t kOob = 0x80000000u;
   constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
@@ -409,7 +433,8 @@ __global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(DwArgs p, DwTile q
   constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
   const int C = q.C, H = q.H, W = q.W, OH = q.OH, OW = q.OW;
-  const int wi = (int)(blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  const DwPlace at = xcd_place(p, gridDim.y);  // x = groups of channels and column tiles, mid = row tiles
+  const int wi = at.x * 4 + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = q.nt > 1 ? (int)__umulhi((uint32_t)wi, q.inv_nt) : wi;
   if (grp >= q.groups) return;  // wavefront-uniform; the kernel has no barrier
   const int ct = wi - grp * q.nt;
@@ -438,7 +463,7 @@ __global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(DwArgs p, DwTile q
     uint32_t so;     // byte offset of the lane's output row
     int32_t img;
   };
-  const int tile0 = (int)blockIdx.y * q.per_wave;
+  const int tile0 = at.mid * q.per_wave;
   const int count = q.tiles - tile0 < q.per_wave ? q.tiles - tile0 : q.per_wave;
   int img = tile0 * 32 / q.period, y0 = tile0 * 32 - img * q.period;  // first image and row of the next tile to load
   auto load = [&](Tile& t) {
@@ -667,14 +692,15 @@ __global__ __launch_bounds__(kThreads) void dw_nhwc3x3_kernel(DwArgs p, int32_t 
   const ConvGeom& g = p.g;
   const int H = g.H, W = g.W, C = g.C, OH = g.OH, OW = g.OW;
   // grid: x = (strip, channel quad), y = run of rows, z = image
-  const uint32_t t = blockIdx.x * kThreads + threadIdx.x;
+  const DwPlace at = xcd_place(p, gridDim.y);
+  const uint32_t t = (uint32_t)at.x * kThreads + threadIdx.x;
   const int strip = c4 > 1 ? (int)__umulhi(t, inv_c4) : (int)t;
   if (strip >= strips) return;
   const int cq = (int)t - strip * c4;
   const int c = 4 * cq < C - 4 ? 4 * cq : C - 4;
   const int xl = OW - 4 < 0 ? 0 : OW - 4;
   const int x0 = 4 * strip < xl ? 4 * strip : xl;
-  const int y0 = (int)blockIdx.y * run;
+  const int y0 = at.mid * run;
   const int rows = OH - y0 < run ? OH - y0 : run;
   const uint32_t x4 = p.act_xor * 0x01010101u;
   const uint32_t pad4 = (((uint32_t)p.z_a ^ p.act_xor) & 0xffu) * 0x01010101u;
@@ -693,7 +719,7 @@ __global__ __launch_bounds__(kThreads) void dw_nhwc3x3_kernel(DwArgs p, int32_t 
   uint32_t d[NC];
   auto load = [&](int iy) {
     const bool ok = (uint32_t)iy < (uint32_t)H;  // uniform
-    const int64_t base = ((int64_t)blockIdx.z * H + (ok ? iy : 0)) * W * C;
+    const int64_t base = ((int64_t)at.outer * H + (ok ? iy : 0)) * W * C;
     const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.act) + base, 0, ok ? W * C : 0, 0x00020000);
 #pragma unroll
     for (int i = 0; i < NC; ++i) d[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rin, off[i], 0, 0);
@@ -779,7 +805,7 @@ __global__ __launch_bounds__(kThreads) void dw_nhwc3x3_kernel(DwArgs p, int32_t 
       }
     };
     auto emit = [&](int oy, const uint32_t (&r0)[4][4], const uint32_t (&r1)[4][4], const uint32_t (&r2)[4][4]) {
-      const int64_t base = ((int64_t)blockIdx.z * OH + oy) * OW * C * kEsz;
+      const int64_t base = ((int64_t)at.outer * OH + oy) * OW * C * kEsz;
       const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(static_cast<uint8_t*>(p.out) + base, 0, OW * C * kEsz, 0x00020000);
       if constexpr (FORM == kSat) {
         // two columns of a channel shift by the same amount; two permutes then sort the pairs into pixels
@@ -916,7 +942,8 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
     if (runs <= 65535 && ((int64_t)c4 * strips + kThreads) * c4 < (1ll << 32)) {
       auto kern = s1 ? (p.out_mode == 1 ? dw_nhwc3x3_kernel<1, 1> : p.out_mode == 2 ? dw_nhwc3x3_kernel<2, 1> : dw_nhwc3x3_kernel<0, 1>)
                      : (p.out_mode == 1 ? dw_nhwc3x3_kernel<1, 2> : p.out_mode == 2 ? dw_nhwc3x3_kernel<2, 2> : dw_nhwc3x3_kernel<0, 2>);
-      hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)runs, (unsigned)cg.B), dim3(kThreads), 0, st, p, c4,
+      hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)runs, (unsigned)cg.B), dim3(kThreads), 0, st,
+                         with_divisors(p, blocks, runs, cg.B), c4,
                          c4 > 1 ? (uint32_t)(((1ull << 32) + c4 - 1) / c4) : 0u, strips, (int32_t)run);
       return hipGetLastError();
     }
@@ -945,7 +972,7 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
                             : (ragged ? HAGO_DW_ROWS(false, true) : HAGO_DW_ROWS(false, false));
 #undef HAGO_DW_ROWS
       hipLaunchKernelGGL(kern, dim3((unsigned)((cg.C + 3) / 4), (unsigned)cg.B, (unsigned)(nband * nsegs)),
-                         dim3(kThreads), 0, st, p, rpc, nsegs, segw);
+                         dim3(kThreads), 0, st, with_divisors(p, (cg.C + 3) / 4, nband * nsegs, cg.B), rpc, nsegs, segw);
       return hipGetLastError();
     }
   }
@@ -982,7 +1009,8 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
       auto kern = S == 2 ? (two ? HAGO_DW_MODE(2, 2, 2) : HAGO_DW_MODE(2, 1, 2))
                          : (!two ? HAGO_DW_MODE(1, 1, 4) : cg.OW > 8 ? HAGO_DW_MODE(1, 2, 4) : HAGO_DW_MODE(1, 2, 2));
 #undef HAGO_DW_MODE
-      hipLaunchKernelGGL(kern, dim3((unsigned)((waves_x + 3) / 4), (unsigned)gy), dim3(kThreads), 0, st, p, q);
+      hipLaunchKernelGGL(kern, dim3((unsigned)((waves_x + 3) / 4), (unsigned)gy), dim3(kThreads), 0, st,
+                         with_divisors(p, (waves_x + 3) / 4, gy, 1), q);
       return hipGetLastError();
     }
   }

@@ -56,6 +56,15 @@ __device__ __forceinline__ int32_t wrap_acc_bits(int32_t acc, int32_t wrap_shift
 // this form, and the kernels it names make their allocation one block larger: VGPR is a register of that block.
 #define HAGO_SPARE_REGISTER(VGPR) asm volatile("" ::: VGPR)
 
+// Workgroups go to the eight XCDs round-robin, each with an L2 of its own.  Numbered like this instead, an XCD works on a
+// run of consecutive ones: number `id` of `count` in launch order -> its place.  Every kernel whose places follow the
+// activations (images first, then pixels) so keeps an eighth of them on one XCD from layer to layer: what a layer wrote is
+// in the L2 that the next one reads it through, and no L2 holds lines that another one writes.
+__device__ __forceinline__ uint32_t xcd_run(uint32_t id, uint32_t count) {
+  const uint32_t x = id & 7, each = count >> 3, more = count & 7;
+  return x * each + (x < more ? x : more) + (id >> 3);
+}
+
 // median of three = clamp when lo <= hi; one instruction instead of two compare/select pairs
 __device__ __forceinline__ int32_t med3(int32_t x, int32_t lo, int32_t hi) {
   int32_t r;
