@@ -21,6 +21,7 @@ HIPCC_FLAGS = [
     "-ffp-contract=off",                       # simquant: no fused multiply-add
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-save-temps=obj",                         # the assembly, for check_assembly
 ]
 

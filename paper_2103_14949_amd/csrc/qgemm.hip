@@ -37,7 +37,7 @@
 // stage; the loads of stage s+1 are in flight while stage s is multiplied.
 // The eight 16-byte chunks of an LDS row are XOR-swizzled with the row index
 // so that fragment reads and staging writes spread over all banks.
-#include "qgemm_common.h"
+#include "qgemm_any.h"
 
 
 namespace hago {
@@ -433,8 +433,6 @@ void set_test_hook(int key, int value) {
   if (key >= 0 && key < kNumHooks) g_hook[key].store(value, std::memory_order_relaxed);
 }
 
-hipError_t launch_qgemm_any(const QgemmParams& p, bool i16, int form, hipStream_t st);
-
 hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
   if (a.M == 0 || a.N == 0) return hipSuccess;
   QgemmParams p = make_qgemm_params(a, nullptr);
@@ -445,18 +443,7 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
     return launch_qgemm_any(p, a.operand16, tile < 0 ? -1 : tile % 5, st);
   }
   const int forced = g_hook[kHookDmaTile].load(std::memory_order_relaxed);
-  // One round of 32 x 32 tiles over the chip: the direct form, whose wavefronts split the reduction.  It wins wherever K ends
-  // inside a stage of 128 bytes, the more the longer K is (us, direct and the better of the 64 x 64 tiles: 996 x 16 -> 16 2.9,
-  // 3.2; 443 x 144 -> 16 2.8, 3.5; 62 x 448 -> 208 3.5, 4.4; 429 x 560 -> 368 3.8, 5.0; 170 x 1424 -> 208 4.9, 6.6;
-  // 51 x 5232 -> 16 8.1, 14.6; the other way 4 x 64 -> 64 3.0, 2.9: few rows and an odd multiple of 64).  Whole stages are loaded faster there than here: it wins
-  // from K = 768 to 1024 (1245 x 768 -> 32 4.4, 4.4; 56 x 1024 -> 2528 4.3, 4.8; but 258 x 512 -> 32 4.1, 3.8, 34 x 1280 -> 352
-  // 5.95, 4.9), from K = 640 with up to 16 rows, half of whose lanes share their lines (8 x 768 -> 736 4.0, 4.6; 2 x 5120 -> 96
-  // 8.7, 10.9; but 64 x 4096 -> 512 9.8, 9.4), and with very long ones over most of the chip (200 x 8192 -> 1024 17.1, 18.65;
-  // but 100 x 8192 -> 512 16.8, 15.6).
-  const int64_t t32 = (int64_t)((a.N + 31) / 32) * ((a.M + 31) / 32);
-  if (forced < 0 && t32 <= 256 &&
-      (a.K % 128 != 0 ? a.K % 64 != 0 || a.K >= 320 || a.M > 4 : a.M <= 16 ? a.K >= 640 : (a.K >= 768 && a.K <= 1024) || (a.K >= 7168 && t32 > 128)))
-    return launch_qgemm_any(p, false, 0, st);
+  if (forced < 0 && qgemm_few_wins(p, false)) return launch_qgemm_few(p, false, 0, st);
   p.vec_k = 1;
   p.vec16_out = (a.N % 16 == 0) && ptr_aligned(a.out, 16);
   // Tile shape: the least time on the busiest CU, in microseconds: rounds of tiles over the 256 CUs (one workgroup on each,

@@ -1,78 +1,41 @@
-// Dense GEMM for operands of any size and alignment, on the int8 matrix cores, in two forms:
+// Dense GEMM for operands of any size and alignment, on the int8 matrix cores, where there are more output tiles than
+// qgemm_few.hip is for: tiles of 64 or 128 rows, operands through registers into a double-buffered LDS stage of 128 source
+// bytes per row, two stages of loads in flight.
 //
-//   direct : few output tiles.  A workgroup owns ONE 32 x 32 tile and its wavefronts split the reduction;
-//            fragments go from global memory straight into registers (no LDS, no barrier in the loop),
-//            the partial sums meet in LDS once.  What bounds such a problem is the chain
-//            launch - first load - reduction - store, so the chain is what this form shortens.
-//   staged : many output tiles.  Tiles of 64 or 128 rows, operands through registers into a
-//            double-buffered LDS stage of 128 source bytes per row, two stages of loads in flight.
-//
-// Rows may start at any byte and the reduction may have any length.  A 16-byte load needs no alignment, but off a multiple
-// of four bytes it costs four times as much: 64 cycles of a CU's memory pipe for 64 lanes in a row instead of 16, 256 for
-// 64 lanes in rows of their own instead of 64 (measured).  So rows off it (MIS) are loaded from the aligned dwords that hold
-// them, one dword more per run, and shifted into place in registers; the first and last of these dwords hold bytes of the
-// row, so no page is touched that the row has no part in.  The last, incomplete chunk of a row is read from the 16 elements
-// that END the row and shifted into place.
-//
-// int16 operands (I16).  gfx950 has no 16-bit integer matrix instruction; a 16-bit value is the sum
-// 256 ah + al of a signed high byte and an unsigned low one, and with al' = al - 128 both are signed bytes:
-//   a = a' + 128, a' = 256 ah + al',     w likewise,
-//   sum a w = 65536 sum ah wh + 256 sum (ah wl' + al' wh) + sum al' wl' + 128 sum a + 128 sum w - 16384 K,
-// modulo 2^32 like the sum itself.  Four byte products in three accumulators replace one product (the vector
-// ALUs' two-element dot product, which this replaced, runs at 1/32 of the byte rate); the plain sums of a
-// row are taken by the lanes that load it.  Elements that pad the reduction are zeros in both operands and are
-// counted in K.
-#include "qgemm_common.h"
+// Rows may start at any byte and the reduction may have any length.  A 16-byte load needs no alignment (off a multiple of
+// four bytes it costs four times as much: 64 cycles of a CU's memory pipe for 64 lanes in a row instead of 16).  The last,
+// incomplete chunk of a row is read from the 16 elements that END the row and shifted into place.
+#include "qgemm_any.h"
 
 namespace hago {
 
 namespace {
 
 
-// 16 NV bytes of a row in registers.  MIS: as the aligned dwords that hold them, `at` the first byte's place in the first.
-template <int NV, bool MIS>
+// 16 NV bytes of a row in registers.
+template <int NV>
 struct Run {
   v4i v[NV];
-  uint32_t more;
   __device__ void load(const uint8_t* ptr) {
-    if constexpr (MIS) {
-      typedef int v4i_dword __attribute__((ext_vector_type(4), aligned(4)));
-      const uintptr_t a = reinterpret_cast<uintptr_t>(ptr);
-      const uint8_t* base = reinterpret_cast<const uint8_t*>(a & ~(uintptr_t)3);
 #pragma unroll
-      for (int i = 0; i < NV; ++i) v[i] = *reinterpret_cast<const v4i_dword*>(base + 16 * i);
-      more = *reinterpret_cast<const uint32_t*>(base + 16 * NV - ((a & 3) ? 0 : 4));
-    } else {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) v[i] = *reinterpret_cast<const v4i_any*>(ptr + 16 * i);
-    }
-  }
-  // the bytes themselves; at = address of the first modulo 4
-  __device__ void settle(uint32_t at) {
-    if constexpr (MIS) {
-#pragma unroll
-      for (int i = 0; i < 4 * NV; ++i) {
-        const uint32_t next = i + 1 < 4 * NV ? (uint32_t)v[(i + 1) / 4][(i + 1) % 4] : more;
-        v[i / 4][i % 4] = (int)__builtin_amdgcn_alignbyte(next, (uint32_t)v[i / 4][i % 4], at);
-      }
-    }
+    for (int i = 0; i < NV; ++i) v[i] = *reinterpret_cast<const v4i_any*>(ptr + 16 * i);
   }
 };
 
 // Elements k, k + 1, ... of the row at `row` (K elements), as many as a run has room for; zeros beyond the row's end.  In two
 // halves, so that other work can lie between the loads and their use: request_tail reads the row's last elements (or the
 // run, if the row has all of it), finish_tail moves them into place.
-template <int NV, bool MIS, int kEsz>
+template <int NV, int kEsz>
 __device__ __forceinline__ const uint8_t* tail_start(const uint8_t* row, int k, int K) {
   constexpr int E = 16 * NV / kEsz;
   return row + (size_t)(K - k >= E ? k : K - E) * kEsz;
 }
-template <int NV, bool MIS, int kEsz>
-__device__ __forceinline__ void request_tail(Run<NV, MIS>& c, const uint8_t* row, int k, int K) {
-  if (K >= 16 * NV / kEsz) c.load(tail_start<NV, MIS, kEsz>(row, k, K));  // (uniform)
+template <int NV, int kEsz>
+__device__ __forceinline__ void request_tail(Run<NV>& c, const uint8_t* row, int k, int K) {
+  if (K >= 16 * NV / kEsz) c.load(tail_start<NV, kEsz>(row, k, K));  // (uniform)
 }
-template <int NV, bool MIS, int kEsz>
-__device__ __forceinline__ void finish_tail(Run<NV, MIS>& c, const uint8_t* row, int k, int K) {
+template <int NV, int kEsz>
+__device__ __forceinline__ void finish_tail(Run<NV>& c, const uint8_t* row, int k, int K) {
   constexpr int ND = 4 * NV, E = 16 * NV / kEsz;
   const int left = K - k;
   uint32_t w[ND];
@@ -86,7 +49,6 @@ __device__ __forceinline__ void finish_tail(Run<NV, MIS>& c, const uint8_t* row,
         w[e * kEsz / 4] |= x << (8 * (e * kEsz % 4));
       }
   } else {
-    c.settle((uint32_t)reinterpret_cast<uintptr_t>(tail_start<NV, MIS, kEsz>(row, k, K)) & 3u);
 #pragma unroll
     for (int i = 0; i < ND; ++i) w[i] = (uint32_t)c.v[i / 4][i % 4];
     if (__builtin_amdgcn_ballot_w64(left > 0 && left < E) == 0) {  // whole runs and none
@@ -109,241 +71,6 @@ __device__ __forceinline__ void finish_tail(Run<NV, MIS>& c, const uint8_t* row,
   for (int i = 0; i < NV; ++i) c.v[i] = v4i{(int)w[4 * i], (int)w[4 * i + 1], (int)w[4 * i + 2], (int)w[4 * i + 3]};
 }
 
-// Plain sum of a register's elements, added to s.
-template <bool I16>
-__device__ __forceinline__ int32_t plain_sum(const v4i& v, int32_t s) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int d = v[e];
-    if constexpr (I16)
-      s = __builtin_amdgcn_sdot2(__builtin_bit_cast(__attribute__((ext_vector_type(2))) short, d),
-                                 __builtin_bit_cast(__attribute__((ext_vector_type(2))) short, 0x00010001), s, false);
-    else
-      s = __builtin_amdgcn_sdot4(d, 0x01010101, s, false);
-  }
-  return s;
-}
-
-// High and low bytes of four int16 elements (low ones biased to signed).
-__device__ __forceinline__ void split16(int d0, int d1, int& hi, int& lo) {
-  hi = (int)__builtin_amdgcn_perm((uint32_t)d1, (uint32_t)d0, 0x07050301u);
-  lo = (int)(__builtin_amdgcn_perm((uint32_t)d1, (uint32_t)d0, 0x06040200u) ^ 0x80808080u);
-}
-
-__device__ __forceinline__ v4i xor4(const v4i& a, uint32_t x) {
-  return v4i{(int)((uint32_t)a.x ^ x), (int)((uint32_t)a.y ^ x), (int)((uint32_t)a.z ^ x), (int)((uint32_t)a.w ^ x)};
-}
-
-// The accumulators of a 32 x 32 tile and their sum modulo 2^32.
-template <bool I16>
-struct Tile32 {
-  v16i a[I16 ? 3 : 1];
-  __device__ void clear() {
-#pragma unroll
-    for (int i = 0; i < (I16 ? 3 : 1); ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) a[i][r] = 0;
-  }
-  __device__ int32_t value(int r) const {
-    if constexpr (I16)
-      return (int32_t)(((uint32_t)a[0][r] << 16) + ((uint32_t)a[1][r] << 8) + (uint32_t)a[2][r]);
-    else
-      return a[0][r];
-  }
-};
-
-__device__ __forceinline__ v16i mfma(const v4i& p, const v4i& q, const v16i& a) {
-  return __builtin_amdgcn_mfma_i32_32x32x32_i8(p, q, a, 0, 0, 0);
-}
-
-// Channel term without the activation's row sum: bias - 16384 K (int16) + coefficient * sum w.
-template <bool I16>
-__device__ __forceinline__ int32_t channel_term(const QgemmParams& p, int32_t bias, int32_t wsum, int32_t kpad) {
-  if constexpr (I16) return bias + (int32_t)((uint32_t)(p.corr_coef + 128) * (uint32_t)wsum) - (int32_t)(16384u * (uint32_t)kpad);
-  else return bias + (int32_t)((uint32_t)p.corr_coef * (uint32_t)wsum);
-}
-
-// Four results of one output row, channels n .. n + 3, where they exist.
-__device__ __forceinline__ void store_four(const QgemmParams& p, int m, int n, const int32_t (&v)[4]) {
-  const int64_t o = (int64_t)m * p.N + n;
-  if (n + 4 <= p.N) {
-    if (p.out_mode == 0) {
-      typedef uint32_t u32_any __attribute__((aligned(1)));
-      *reinterpret_cast<u32_any*>(static_cast<uint8_t*>(p.out) + o) = pack4_perm(v[0], v[1], v[2], v[3]);
-    } else if (p.out_mode == 1) {
-      *reinterpret_cast<v4i_any*>(static_cast<int32_t*>(p.out) + o) = v4i{v[0], v[1], v[2], v[3]};
-    } else {
-      typedef int v2i_any __attribute__((ext_vector_type(2), aligned(1)));
-      *reinterpret_cast<v2i_any*>(static_cast<int16_t*>(p.out) + o) =
-          v2i_any{(int)(((uint32_t)v[0] & 0xffffu) | ((uint32_t)v[1] << 16)), (int)(((uint32_t)v[2] & 0xffffu) | ((uint32_t)v[3] << 16))};
-    }
-    return;
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    if (n + e >= p.N) break;
-    if (p.out_mode == 0) static_cast<uint8_t*>(p.out)[o + e] = (uint8_t)v[e];
-    else if (p.out_mode == 1) static_cast<int32_t*>(p.out)[o + e] = v[e];
-    else static_cast<int16_t*>(p.out)[o + e] = (int16_t)v[e];
-  }
-}
-
-// ---- direct form.  NW wavefronts share one tile; U: 32-k groups per wavefront and batch of loads, two
-// batches in flight.  256 threads (four results each) finish the tile.
-template <bool I16, bool MIS, int NW, int U>
-__global__ __launch_bounds__(64 * NW) void qgemm_direct_kernel(QgemmParams p) {
-  constexpr int kEsz = I16 ? 2 : 1;
-  __shared__ __attribute__((aligned(16))) int32_t s_part[NW][4][64][4];  // [wavefront][register group][lane][4]
-  __shared__ __attribute__((aligned(16))) int32_t s_wsum[NW][32], s_asum[I16 ? NW : 1][32], s_constant[3][32];
-  const int t = threadIdx.x, lane = t & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int frow = lane & 31, fhalf = lane >> 5;
-  const int tiles_m = (p.M + 31) / 32;
-  const int tile = p.tile0 + xcd_remap(blockIdx.x, gridDim.x);  // consecutive tiles share weight rows, on one XCD
-  const int tile_n = tile / tiles_m;
-  const int n0 = tile_n * 32, m0 = (tile - tile_n * tiles_m) * 32;
-
-  // rows beyond the matrix read its last row (their results are dropped)
-  const uint8_t* wrow = reinterpret_cast<const uint8_t*>(p.wgt) + (size_t)(n0 + frow < p.N ? n0 + frow : p.N - 1) * p.K * kEsz;
-  const uint8_t* arow = p.act + (size_t)(m0 + frow < p.M ? m0 + frow : p.M - 1) * p.K * kEsz;
-  const int groups = (p.K + 31) >> 5;
-  const int g0 = groups * wave / NW, g1 = groups * (wave + 1) / NW;
-  const int gf = g1 < (p.K >> 5) ? g1 : (p.K >> 5);  // complete groups end here
-
-  // the tile's per-channel constants: wavefronts 0, 1 and 2 load the bias, the multipliers and the shifts, one dword per lane,
-  // in front of the operands; they meet the finishing threads in LDS.  (Loaded by those themselves, three times 16 bytes per
-  // lane in each of four wavefronts, they kept the memory pipe from the operands: us, so and then, 1280 x 1776 -> 192 6.3, 6.7;
-  // 1128 x 1552 -> 112 5.2, 5.45; 3 x 1680 -> 32 4.1, 4.45; int16 128 x 256 -> 512 4.3, 4.45, 100 x 400 -> 300 4.3, 4.5.)
-  int32_t constant = 0;
-  if (wave < 3) {
-    const int32_t* src = wave == 0 ? p.bias : !p.has_rq ? nullptr : wave == 1 ? p.mult : p.shift;
-    const bool each = wave == 0 || p.per_channel;
-    const int left = p.N - n0 < 32 ? p.N - n0 : 32;
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(src + (src && each ? n0 : 0)), 0,
-                                                                       src ? (each ? 4 * left : 4) : 0, 0x00020000);
-    constant = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, each ? 4 * frow : 0, 0, 0);
-  }
-  Tile32<I16> acc;
-  acc.clear();
-  int32_t wsum = 0, asum = 0;
-  const bool need_wsum = I16 || p.corr_coef != 0;
-  constexpr int kVec = I16 ? 2 : 1;  // a lane's 16 elements
-  using Chunk = Run<kVec, MIS>;
-  const uint32_t wat = (uint32_t)reinterpret_cast<uintptr_t>(wrow) & 3u, aat = (uint32_t)reinterpret_cast<uintptr_t>(arow) & 3u;
-  auto multiply = [&](const Chunk& w, const Chunk& a) {
-    if (need_wsum)
-#pragma unroll
-      for (int i = 0; i < kVec; ++i) wsum = plain_sum<I16>(w.v[i], wsum);
-    if constexpr (I16) {
-      v4i wh, wl, ah, al;
-#pragma unroll
-      for (int i = 0; i < kVec; ++i) asum = plain_sum<I16>(a.v[i], asum);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        int h, l;
-        split16(w.v[e / 2 % kVec][2 * (e % 2)], w.v[e / 2 % kVec][2 * (e % 2) + 1], h, l);
-        wh[e] = h;
-        wl[e] = l;
-        split16(a.v[e / 2 % kVec][2 * (e % 2)], a.v[e / 2 % kVec][2 * (e % 2) + 1], h, l);
-        ah[e] = h;
-        al[e] = l;
-      }
-      acc.a[0] = mfma(wh, ah, acc.a[0]);
-      acc.a[1] = mfma(wh, al, acc.a[1]);
-      acc.a[2] = mfma(wl, al, acc.a[2]);
-      acc.a[1] = mfma(wl, ah, acc.a[1]);
-    } else {
-      acc.a[0] = mfma(w.v[0], xor4(a.v[0], p.act_xor4), acc.a[0]);
-    }
-  };
-  Chunk wt, at;  // the reduction's last, incomplete group (where its loads are many, they are under way from the start)
-  auto request_last = [&]() {
-    request_tail<kVec, MIS, kEsz>(wt, wrow, gf * 32 + 16 * fhalf, p.K);
-    request_tail<kVec, MIS, kEsz>(at, arow, gf * 32 + 16 * fhalf, p.K);
-  };
-  if ((MIS || I16) && gf < g1) request_last();  // uniform
-  if (g0 < gf) {
-    struct Batch {
-      Chunk w[U], a[U];
-    };
-    // (a batch beyond the last group reads that group again: the loads stay unconditional)
-    auto load = [&](int g, Batch& b) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int gg = g + u < gf ? g + u : gf - 1;
-        const size_t off = (size_t)(gg * 32 + 16 * fhalf) * kEsz;
-        b.w[u].load(wrow + off);
-        b.a[u].load(arow + off);
-      }
-    };
-    auto use = [&](int g, Batch& b) {
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (g + u < gf) {
-          b.w[u].settle(wat);
-          b.a[u].settle(aat);
-          multiply(b.w[u], b.a[u]);
-        }
-    };
-    Batch b0, b1;
-    load(g0, b0);
-    for (int g = g0; g < gf; g += 2 * U) {
-      if (g + U < gf) load(g + U, b1);
-      use(g, b0);
-      if (g + 2 * U < gf) load(g + 2 * U, b0);
-      if (g + U < gf) use(g + U, b1);
-    }
-  }
-  if (gf < g1) {
-    const int k = gf * 32 + 16 * fhalf;
-    if (!MIS && !I16) request_last();
-    finish_tail<kVec, MIS, kEsz>(wt, wrow, k, p.K);
-    finish_tail<kVec, MIS, kEsz>(at, arow, k, p.K);
-    multiply(wt, at);
-  }
-
-  wsum += __shfl_xor(wsum, 32);
-  if constexpr (I16) asum += __shfl_xor(asum, 32);
-  if (fhalf == 0) {
-    s_wsum[wave][frow] = wsum;
-    if constexpr (I16) s_asum[wave][frow] = asum;
-    if (wave < 3) s_constant[wave][frow] = constant;
-  }
-#pragma unroll
-  for (int g = 0; g < 4; ++g)
-    *reinterpret_cast<v4i*>(s_part[wave][g][lane]) = v4i{acc.value(4 * g), acc.value(4 * g + 1), acc.value(4 * g + 2), acc.value(4 * g + 3)};
-  __syncthreads();
-  if (t >= 256) return;
-
-  // thread (g4 = t / 64, lane): channels fin_n .. fin_n + 3 of row m0 + lane % 32
-  const int g4 = t >> 6, m = m0 + frow, fin = 8 * g4 + 4 * fhalf, fin_n = n0 + fin;
-  v4i s = {0, 0, 0, 0};
-  int32_t ws[4] = {0, 0, 0, 0}, as = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    const v4i q = *reinterpret_cast<const v4i*>(s_part[w][g4][lane]);
-    const v4i qs = *reinterpret_cast<const v4i*>(&s_wsum[w][fin]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      s[e] += q[e];
-      ws[e] += qs[e];
-    }
-    if constexpr (I16) as += s_asum[w][frow];
-  }
-  if (m >= p.M || fin_n >= p.N) return;
-  const v4i bias = *reinterpret_cast<const v4i*>(&s_constant[0][fin]), mu = *reinterpret_cast<const v4i*>(&s_constant[1][fin]),
-            sh = *reinterpret_cast<const v4i*>(&s_constant[2][fin]);
-  int32_t v[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    v[e] = s[e] + channel_term<I16>(p, bias[e], ws[e], groups * 32) + 128 * as;
-    if (p.acc_wrap_shift) v[e] = wrap_acc_bits(v[e], p.acc_wrap_shift);
-    if (p.has_rq) v[e] = requant_general(v[e], p.mult ? mu[e] : 1 << 30, sh[e] - (p.mult ? 0 : 1), p.rs);  // (as rq_mult, rq_shift)
-  }
-  store_four(p, m, fin_n, v);
-}
-
-// ---- staged form
 constexpr int kRow = 128;  // bytes of an LDS row = source bytes of a row per stage (256: 9.7 us for 1021 x 1283 -> 1001, 8.6 so)
 
 __device__ __forceinline__ int lds_off(int row, int chunk) { return row * kRow + ((chunk ^ row ^ (row >> 3)) & 7) * 16; }
@@ -385,7 +112,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
   }
   constexpr int kVec = I16 ? 2 : 1;
   struct Regs {
-    Run<kVec, false> c[NU];  // (shifting rows off a multiple of four bytes costs more here than its loads: 9.0 us, 8.6)
+    Run<kVec> c[NU];  // (shifting rows off a multiple of four bytes costs more here than its loads: 9.0 us, 8.6)
   };
   int32_t sum[NU];
 #pragma unroll
@@ -394,7 +121,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
     const int k = kt * BK + unit * 16;
 #pragma unroll
     for (int n = 0; n < NU; ++n) {
-      if constexpr (TAIL) request_tail<kVec, false, kEsz>(r.c[n], row[n], k, p.K);
+      if constexpr (TAIL) request_tail<kVec, kEsz>(r.c[n], row[n], k, p.K);
       else r.c[n].load(row[n] + (size_t)k * kEsz);
     }
   };
@@ -403,7 +130,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
 #pragma unroll
     for (int n = 0; n < NU; ++n) {
       const int at = row_t + n * RPU;
-      const Run<kVec, false>& c = r.c[n];
+      const Run<kVec>& c = r.c[n];
       if (I16 || is_weight(n))
 #pragma unroll
         for (int i = 0; i < kVec; ++i) sum[n] = plain_sum<I16>(c.v[i], sum[n]);
@@ -486,7 +213,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
   }
   if (tail)
 #pragma unroll
-    for (int n = 0; n < NU; ++n) finish_tail<kVec, false, kEsz>(r0.c[n], row[n], (KT - 1) * BK + unit * 16, p.K);
+    for (int n = 0; n < NU; ++n) finish_tail<kVec, kEsz>(r0.c[n], row[n], (KT - 1) * BK + unit * 16, p.K);
   if (KT > 0) stash(0, r0);
   __syncthreads();
   int s = 0;
@@ -664,12 +391,6 @@ hipError_t launch_tiles(void (*kern)(QgemmParams), QgemmParams p, int64_t tiles,
   return hipSuccess;
 }
 
-template <bool I16, bool MIS, int NW, int U>
-hipError_t launch_direct(const QgemmParams& p, hipStream_t st) {
-  const int64_t tiles = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32);
-  return launch_tiles(qgemm_direct_kernel<I16, MIS, NW, U>, p, tiles, 64 * NW, 0, st);
-}
-
 template <bool I16, int WP, int WQ, int TP, int TQ, int KS>
 hipError_t launch_staged(const QgemmParams& p, hipStream_t st) {
   constexpr int BP = 32 * WP * TP, BQ = 32 * WQ * TQ;
@@ -685,43 +406,18 @@ hipError_t launch_staged(const QgemmParams& p, hipStream_t st) {
 
 }  // namespace
 
-// Any M, N >= 1, K >= 0 and alignment.  form < 0: by size (us on one MI355X beside each rule); 0 direct with 8
-// wavefronts, 1 direct with 4 (int16: with 8 too), 3 staged 128 x 128, 4 and others staged 64 x 64 with two sets of wavefronts.
+// Any M, N >= 1, K >= 0 and alignment.  form < 0: by size (us on one MI355X beside each rule); 0 and 1 few tiles with 8 and 4
+// wavefronts (where qgemm_few.hip indexes the layer), 3 staged 128 x 128, 4 and others staged 64 x 64 with two sets of
+// wavefronts.
 hipError_t launch_qgemm_any(const QgemmParams& p, bool i16, int form, hipStream_t st) {
-  const int64_t t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32), t64 = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64);
-  const int64_t groups = (p.K + 31) / 32;
-  if (form < 0) {
-    // The direct form reads 64 row segments per load, a workgroup per 32 x 32 tile: it wins while those are one round over
-    // the chip (us, direct and staged: 333 x 1251 -> 221 7.5, 8.0; 7 x 3001 -> 1001 9.1, 12.7; 412 x 1111 -> 285 6.1, 7.8;
-    // 141 x 2145 -> 1327 9.5, 10.6; but 305 tiles of 1937 x 3015 -> 154 24, 13; int16 332 x 131 -> 721 4.5, 5.9; 512 x 768 ->
-    // 768 9.2, 8.0), or their reductions are one or two groups (int8 2572 x 25 -> 132 4.1, 5.0; int16 1024 x 64 -> 768 5.0, 4.3).
-    if (t32 <= 256) form = 0;
-    else if (!i16 && t32 * groups <= 1024) form = 1;
-    // 128 x 128 tiles once four rounds of 64 x 64 ones would run (2000 x 2001 -> 2003 24 against 34)
-    else if (t64 >= 1024) form = 3;
-    // two sets of wavefronts (1021 x 1283 -> 1001 8.6, 9.9 with one; int16 1024 x 768 -> 768 8.1, 9.3)
-    else form = 4;
-  }
-  const size_t esz = i16 ? 2 : 1;
-  // (up to two groups are over before the shifts pay: 4 x 43 -> 34 3.2 us, 3.5 with them; 32 x 257 -> 32 9.2, 5.5 with them)
-  const bool mis = groups > 2 && ((size_t)p.K * esz % 4 != 0 || !ptr_aligned(p.act, 4) || !ptr_aligned(p.wgt, 4));
-  auto run = [&]<bool MIS>() {
-    if (i16) {
-      switch (form) {
-        case 0:
-        case 1: return launch_direct<true, MIS, 8, 2>(p, st);
-        case 3: return launch_staged<true, 2, 4, 2, 1, 1>(p, st);
-        default: return launch_staged<true, 2, 2, 1, 1, 2>(p, st);
-      }
-    }
-    switch (form) {
-      case 0: return launch_direct<false, MIS, 8, 4>(p, st);
-      case 1: return launch_direct<false, MIS, 4, 4>(p, st);
-      case 3: return launch_staged<false, 2, 4, 2, 1, 1>(p, st);
-      default: return launch_staged<false, 2, 2, 1, 1, 2>(p, st);
-    }
-  };
-  return mis ? run.template operator()<true>() : run.template operator()<false>();
+  const int64_t t64 = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64);
+  if (form < 0 && qgemm_few_wins(p, i16)) return launch_qgemm_few(p, i16, 0, st);
+  if ((form == 0 || form == 1) && qgemm_few_ok(p, i16)) return launch_qgemm_few(p, i16, form == 0 ? 8 : 4, st);
+  // 128 x 128 tiles once four rounds of 64 x 64 ones would run (2000 x 2001 -> 2003 24 against 34); else 64 x 64 with two sets
+  // of wavefronts (1021 x 1283 -> 1001 8.6, 9.9 with one; int16 1024 x 768 -> 768 8.1, 9.3)
+  const bool large = form < 0 ? t64 >= 1024 : form == 3;
+  if (i16) return large ? launch_staged<true, 2, 4, 2, 1, 1>(p, st) : launch_staged<true, 2, 2, 1, 1, 2>(p, st);
+  return large ? launch_staged<false, 2, 4, 2, 1, 1>(p, st) : launch_staged<false, 2, 2, 1, 1, 2>(p, st);
 }
 
 }  // namespace hago

@@ -369,6 +369,31 @@ __device__ __forceinline__ void qgemm_epilogue_dense_staged(const QgemmParams& p
   HAGO_STAMP(p, 6);
 }
 
+// Four results of one output row, channels n .. n + 3, where they exist.
+__device__ __forceinline__ void store_four(const QgemmParams& p, int m, int n, const int32_t (&v)[4]) {
+  const int64_t o = (int64_t)m * p.N + n;
+  if (n + 4 <= p.N) {
+    if (p.out_mode == 0) {
+      typedef uint32_t u32_any __attribute__((aligned(1)));
+      *reinterpret_cast<u32_any*>(static_cast<uint8_t*>(p.out) + o) = pack4_perm(v[0], v[1], v[2], v[3]);
+    } else if (p.out_mode == 1) {
+      *reinterpret_cast<v4i_any*>(static_cast<int32_t*>(p.out) + o) = v4i{v[0], v[1], v[2], v[3]};
+    } else {
+      typedef int v2i_any __attribute__((ext_vector_type(2), aligned(1)));
+      *reinterpret_cast<v2i_any*>(static_cast<int16_t*>(p.out) + o) =
+          v2i_any{(int)(((uint32_t)v[0] & 0xffffu) | ((uint32_t)v[1] << 16)), (int)(((uint32_t)v[2] & 0xffffu) | ((uint32_t)v[3] << 16))};
+    }
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (n + e >= p.N) break;
+    if (p.out_mode == 0) static_cast<uint8_t*>(p.out)[o + e] = (uint8_t)v[e];
+    else if (p.out_mode == 1) static_cast<int32_t*>(p.out)[o + e] = v[e];
+    else static_cast<int16_t*>(p.out)[o + e] = (int16_t)v[e];
+  }
+}
+
 // Straight-line epilogue of a tile (interior or ragged): groups of four along the packed axis are one store, in a dense
 // tile at any address and cut where the row ends, else aligned and inside the tensor or outside.
 // OM: 0 requantized 8-bit, 1 raw int32, 2 raw int16.

@@ -47,6 +47,9 @@ __device__ __forceinline__ v4i make_rsrc(const void* base, uint32_t bytes) {
   return r;
 }
 
+// The descriptor of a tensor that is loaded in runs (stream_offset.h).
+__device__ __forceinline__ v4i make_run_rsrc(const uint8_t* base, uint32_t bytes) { return make_rsrc(base - kRunBack, bytes + kRunBack); }
+
 template <int N>
 using template_int = std::integral_constant<int, N>;
 

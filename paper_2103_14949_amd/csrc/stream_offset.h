@@ -10,7 +10,15 @@
 
 namespace hago {
 
-constexpr uint32_t kOob = 0x80000000u;  // offset beyond any tensor (sizes are < 2^31 bytes)
+constexpr uint32_t kOob = 0x80002000u;  // offset beyond any tensor (sizes are < 2^31 bytes), and beyond kRunBack more bytes
+
+// Runs of up to four loads of a wavefront fill consecutive KB of LDS from one value of m0, load i with the instruction offset
+// i KB.  That offset counts on both sides, so the lane offsets of load i take it back, from a descriptor that starts kRunBack
+// bytes before the tensor.
+constexpr uint32_t kRunStep = 1024, kRunBack = 3 * kRunStep;
+constexpr uint32_t stream_run_offset(uint32_t lane_offset, int i) {
+  return lane_offset == kOob ? kOob : lane_offset + (kRunBack - kRunStep * (uint32_t)i);
+}
 
 // Of a lane that fetches row `row` (of `rows` rows of K bytes) and byte `chunk` of every stage's piece of it: the part
 // that all stages share, ...
