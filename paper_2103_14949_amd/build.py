@@ -21,7 +21,7 @@ HIPCC_FLAGS = [
     "-ffp-contract=off",                       # simquant: no fused multiply-add
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
-    "-mllvm", "-amdgpu-kernarg-preload-count=14",
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",   # leading scalar arguments are in registers when a wavefront starts
     "-save-temps=obj",                         # the assembly, for check_assembly
 ]
 

@@ -489,8 +489,7 @@ hipError_t launch_c3_ck(const C3Params& p, size_t lds, int64_t grid, hipStream_t
   auto kern = conv3x3_nchw_kernel<NW, AF, NU, CK, TN>;
   hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), lds, st, p);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3((unsigned)grid), dim3(64 * NW), lds, st, p);
 }
 
 template <int NW, int AF, int NU, int TN>

@@ -889,8 +889,7 @@ hipError_t launch_cd(const CdParams& p, size_t lds, int64_t grid, hipStream_t st
   static std::atomic<uint64_t> attr_set{0};
   hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * WPX * WCH), lds, st, p);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3((unsigned)grid), dim3(64 * WPX * WCH), lds, st, p);
 }
 
 template <bool NHWC, bool SMALL, int WT>

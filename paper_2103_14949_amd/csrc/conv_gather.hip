@@ -304,7 +304,7 @@ hipError_t launch_shape(const CgParams& p, int mode, hipStream_t st) {
   q.inv_tn = q.tiles_n > 1 && ids * q.tiles_n < (1ll << 32) ? (uint32_t)(((1ull << 32) + q.tiles_n - 1) / q.tiles_n) : 0u;
   auto run = [&]<bool MIS>() {
     auto kern = mode == 0 ? conv_gather_kernel<0, MIS, TP, TC, KS> : mode == 1 ? conv_gather_kernel<1, MIS, TP, TC, KS> : conv_gather_kernel<2, MIS, TP, TC, KS>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
+    launch_kernel(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
   };
   // (one step is over before the shifts pay: 22 -> 20 1x1 stride 2 on 59 x 27 x 25 3.15 us, 3.25 with them)
   if (q.steps > 1 && (q.C % 4 != 0 || ((reinterpret_cast<uintptr_t>(q.act) | reinterpret_cast<uintptr_t>(q.wgt)) & 3u) != 0)) run.template operator()<true>();
@@ -637,8 +637,7 @@ hipError_t launch_nchw_zp(const CnParams& p, int mode, hipStream_t st) {
   const int64_t groups = ((int64_t)q.tiles + AT - 1) / AT;
   int64_t per_blk = (lds <= 80 * 1024 && NW == 4 ? 512 : 256) / q.nblocks;
   per_blk = per_blk < 1 ? 1 : (per_blk > groups ? groups : per_blk);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(per_blk * q.nblocks)), dim3(64 * NW), lds, st, q);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3((unsigned)(per_blk * q.nblocks)), dim3(64 * NW), lds, st, q);
 }
 
 template <int TC, int KS>

@@ -244,14 +244,12 @@ hipError_t launch_conv_prepack(const GemmArgs& a, const ConvGeom& cg, int32_t Cp
     const int64_t ring_chunks = (int64_t)p.B * ((int64_t)p.Hp * p.Wp - hw) * (Cp / 16);
     const int64_t blocks = act_blocks + (ring_chunks + p.wgt_chunks + 255) / 256;
     if (blocks <= max_blocks(256)) {
-      hipLaunchKernelGGL(conv_prepack_nchw_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p,
+      return launch_kernel(conv_prepack_nchw_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p,
                          (int32_t)ptiles, (int32_t)ctiles, (int32_t)act_blocks, ring_chunks);
-      return hipGetLastError();
     }
   }
   const int64_t blocks = (p.act_chunks + p.wgt_chunks + 255) / 256;
-  hipLaunchKernelGGL(conv_prepack_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p);
-  return hipGetLastError();
+  return launch_kernel(conv_prepack_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p);
 }
 
 hipError_t launch_conv_prepack_weights(const GemmArgs& a, const ConvGeom& cg, int32_t Cp, int8_t* wgt_out, hipStream_t st) {
@@ -261,8 +259,7 @@ hipError_t launch_conv_prepack_weights(const GemmArgs& a, const ConvGeom& cg, in
   p.C = cg.C; p.O = cg.O; p.KH = cg.KH; p.KW = cg.KW; p.Cp = Cp;
   p.nhwc = cg.nhwc;
   p.wgt_chunks = (int64_t)p.O * p.KH * p.KW * (Cp / 16);
-  hipLaunchKernelGGL(conv_prepack_kernel, dim3((unsigned)((p.wgt_chunks + 255) / 256)), dim3(256), 0, st, p);
-  return hipGetLastError();
+  return launch_kernel(conv_prepack_kernel, dim3((unsigned)((p.wgt_chunks + 255) / 256)), dim3(256), 0, st, p);
 }
 
 }  // namespace hago

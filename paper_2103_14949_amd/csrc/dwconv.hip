@@ -942,10 +942,9 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
     if (runs <= 65535 && ((int64_t)c4 * strips + kThreads) * c4 < (1ll << 32)) {
       auto kern = s1 ? (p.out_mode == 1 ? dw_nhwc3x3_kernel<1, 1> : p.out_mode == 2 ? dw_nhwc3x3_kernel<2, 1> : dw_nhwc3x3_kernel<0, 1>)
                      : (p.out_mode == 1 ? dw_nhwc3x3_kernel<1, 2> : p.out_mode == 2 ? dw_nhwc3x3_kernel<2, 2> : dw_nhwc3x3_kernel<0, 2>);
-      hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)runs, (unsigned)cg.B), dim3(kThreads), 0, st,
+      return launch_kernel(kern, dim3((unsigned)blocks, (unsigned)runs, (unsigned)cg.B), dim3(kThreads), 0, st,
                          with_divisors(p, blocks, runs, cg.B), c4,
                          c4 > 1 ? (uint32_t)(((1ull << 32) + c4 - 1) / c4) : 0u, strips, (int32_t)run);
-      return hipGetLastError();
     }
   }
   // NCHW, stride 1, rows of more than 32 bytes: the dot-product form.  (The matrix form reads a row in 16-byte pieces, one
@@ -971,9 +970,8 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
       auto kern = nsegs > 1 ? (ragged ? HAGO_DW_ROWS(true, true) : HAGO_DW_ROWS(true, false))
                             : (ragged ? HAGO_DW_ROWS(false, true) : HAGO_DW_ROWS(false, false));
 #undef HAGO_DW_ROWS
-      hipLaunchKernelGGL(kern, dim3((unsigned)((cg.C + 3) / 4), (unsigned)cg.B, (unsigned)(nband * nsegs)),
+      return launch_kernel(kern, dim3((unsigned)((cg.C + 3) / 4), (unsigned)cg.B, (unsigned)(nband * nsegs)),
                          dim3(kThreads), 0, st, with_divisors(p, (cg.C + 3) / 4, nband * nsegs, cg.B), rpc, nsegs, segw);
-      return hipGetLastError();
     }
   }
   // NCHW on the matrix cores
@@ -1009,15 +1007,13 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
       auto kern = S == 2 ? (two ? HAGO_DW_MODE(2, 2, 2) : HAGO_DW_MODE(2, 1, 2))
                          : (!two ? HAGO_DW_MODE(1, 1, 4) : cg.OW > 8 ? HAGO_DW_MODE(1, 2, 4) : HAGO_DW_MODE(1, 2, 2));
 #undef HAGO_DW_MODE
-      hipLaunchKernelGGL(kern, dim3((unsigned)((waves_x + 3) / 4), (unsigned)gy), dim3(kThreads), 0, st,
+      return launch_kernel(kern, dim3((unsigned)((waves_x + 3) / 4), (unsigned)gy), dim3(kThreads), 0, st,
                          with_divisors(p, (waves_x + 3) / 4, gy, 1), q);
-      return hipGetLastError();
     }
   }
   const int64_t blocks = (total + kThreads - 1) / kThreads;
   const int64_t cap = 256 * 64;
-  hipLaunchKernelGGL(dw_direct_kernel, dim3((unsigned)(blocks < cap ? blocks : cap)), dim3(kThreads), 0, st, p);
-  return hipGetLastError();
+  return launch_kernel(dw_direct_kernel, dim3((unsigned)(blocks < cap ? blocks : cap)), dim3(kThreads), 0, st, p);
 }
 
 }  // namespace hago

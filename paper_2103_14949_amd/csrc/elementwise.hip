@@ -779,7 +779,7 @@ void launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStream_t s
   SpanArgs g;
   if (periodic_split(total, channels, inner, U, &g)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
-    hipLaunchKernelGGL((periodic_kernel<OpP, U>), dim3((unsigned)wgs), dim3(kThreads), 0, st, OpP{args...}, g, d);
+    launch_kernel((periodic_kernel<OpP, U>), dim3((unsigned)wgs), dim3(kThreads), 0, st, OpP{args...}, g, d);
     return;
   }
   // one vector per lane while that does not fill the chip, four beyond
@@ -789,7 +789,7 @@ void launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStream_t s
   constexpr int64_t most = max_blocks(kThreads);
 #define HAGO_FLAT(UU, MULTI, W)                                                                                       \
   for (int64_t b0 = 0; b0 < W; b0 += most)                                                                            \
-  hipLaunchKernelGGL((flat_kernel<OpF, UU, MULTI>), dim3((unsigned)(W - b0 < most ? W - b0 : most)), dim3(kThreads), 0, st, \
+  launch_kernel((flat_kernel<OpF, UU, MULTI>), dim3((unsigned)(W - b0 < most ? W - b0 : most)), dim3(kThreads), 0, st, \
                      OpF{args...}, total, d, b0)
   if (w1 <= 1024) {
     if (inner < 4) {
@@ -887,7 +887,7 @@ inline void launch_batched_ragged(const float* x, float* y, int64_t total, int64
   SpanArgs g;
   if (periodic_split(total, channels, inner, U, &g)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
-    hipLaunchKernelGGL((simquant_batched_ragged_kernel<U, true>), dim3((unsigned)wgs), dim3(kThreads), 0, st, x, y, g, d,
+    launch_kernel((simquant_batched_ragged_kernel<U, true>), dim3((unsigned)wgs), dim3(kThreads), 0, st, x, y, g, d,
                        nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);
     return;
   }
@@ -895,13 +895,13 @@ inline void launch_batched_ragged(const float* x, float* y, int64_t total, int64
   g.total = total;
   const int64_t nvec = total / 4 > 0 ? total / 4 : 1;
   if (nvec <= 1024 * kThreads)
-    hipLaunchKernelGGL((simquant_batched_ragged_kernel<1, false>), dim3((unsigned)((nvec + kThreads - 1) / kThreads)),
+    launch_kernel((simquant_batched_ragged_kernel<1, false>), dim3((unsigned)((nvec + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);
   else {
     constexpr int64_t most = max_blocks(kThreads);
     const int64_t wgs = (nvec + kThreads * U - 1) / (kThreads * U);
     for (int64_t b0 = 0; b0 < wgs; b0 += most)  // (more than one launch from 2^35 elements on)
-      hipLaunchKernelGGL((simquant_batched_ragged_kernel<U, false>), dim3((unsigned)(wgs - b0 < most ? wgs - b0 : most)),
+      launch_kernel((simquant_batched_ragged_kernel<U, false>), dim3((unsigned)(wgs - b0 < most ? wgs - b0 : most)),
                          dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips, b0);
   }
 }
@@ -1163,7 +1163,7 @@ hipError_t launch_simquant(const float* x, float* y, int64_t outer, int64_t chan
     const int64_t inner_vec = row_len / 4;
     int32_t nseg, seg_len;
     split_row(inner_vec, kVecPerLane, &nseg, &seg_len);
-    hipLaunchKernelGGL((simquant_rows_kernel<kVecPerLane, false>), dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
+    launch_kernel((simquant_rows_kernel<kVecPerLane, false>), dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
                        reinterpret_cast<const v4f*>(x), reinterpret_cast<v4f*>(y), rows,
                        (int32_t)(per_channel ? channels : 1), inner_vec, nseg, seg_len, scale, zp,
                        per_channel, JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi, 0, 0);
@@ -1186,7 +1186,7 @@ hipError_t launch_simquant_wrap(const float* x, float* y, int64_t outer, int64_t
     const int64_t inner_vec = row_len / 4;
     int32_t nseg, seg_len;
     split_row(inner_vec, kVecPerLane, &nseg, &seg_len);
-    hipLaunchKernelGGL((simquant_rows_kernel<kVecPerLane, true>), dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
+    launch_kernel((simquant_rows_kernel<kVecPerLane, true>), dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
                        reinterpret_cast<const v4f*>(x), reinterpret_cast<v4f*>(y), rows,
                        (int32_t)(per_channel ? channels : 1), inner_vec, nseg, seg_len, scale, zp,
                        per_channel, JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi,
@@ -1218,7 +1218,7 @@ hipError_t launch_simquant_batched(const float* x, float* y, int64_t outer, int6
     constexpr int kU = 2;  // fewer vectors in flight per lane: every one is stored nbatch times
     int32_t nseg, seg_len;
     split_row(inner_vec, kU, &nseg, &seg_len);
-    hipLaunchKernelGGL(simquant_batched_rows_kernel<kU>, dim3(grid_for(rows * nseg)), dim3(kThreads),
+    launch_kernel(simquant_batched_rows_kernel<kU>, dim3(grid_for(rows * nseg)), dim3(kThreads),
                        0, st, reinterpret_cast<const v4f*>(x), reinterpret_cast<v4f*>(y), rows,
                        nparam, inner_vec, nseg, seg_len, nbatch, nparam, scale, zp, per_channel,
                        JobDiv{reciprocal32(nseg), reciprocal32(nparam)}, clips);
@@ -1241,7 +1241,7 @@ static hipError_t launch_quant_t(const void* in, void* out, float* out2, int64_t
     const int64_t inner_vec = row_len / 4;
     int32_t nseg, seg_len;
     split_row(inner_vec, kVecPerLane, &nseg, &seg_len);
-    hipLaunchKernelGGL((quant_rows_kernel<Q, OP, kVecPerLane>), dim3(grid_for(rows * nseg)),
+    launch_kernel((quant_rows_kernel<Q, OP, kVecPerLane>), dim3(grid_for(rows * nseg)),
                        dim3(kThreads), 0, st, in, out, out2, rows, (int32_t)(per_channel ? channels : 1),
                        inner_vec, nseg, seg_len, scale, zp, per_channel,
                        JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi);
@@ -1282,7 +1282,7 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
   uint32_t* t = reinterpret_cast<uint32_t*>(thr);
   auto zero_first = [&] {
     // (a fill kernel, not hipMemsetAsync: the call may be captured into a graph)
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(grid_for((nthr + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, t, nthr);
+    launch_kernel(fill_zero_kernel, dim3(grid_for((nthr + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, t, nthr);
   };
   const int64_t total = outer * channels * inner;
   if (total == 0) {
@@ -1298,8 +1298,7 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
     const size_t lds = table ? (size_t)nchan * sizeof(uint32_t) : 0;
     if (table && total <= 16384 && g.nseg == 1) {  // one workgroup: no second launch to zero the thresholds
       g.rows = (int32_t)g.spans;
-      hipLaunchKernelGGL((absmax_periodic_kernel<true>), dim3(1), dim3(kThreads), lds, st, x, g, channel_div(total, nchan, row_len), t);
-      return hipGetLastError();
+      return launch_kernel((absmax_periodic_kernel<true>), dim3(1), dim3(kThreads), lds, st, x, g, channel_div(total, nchan, row_len), t);
     }
     const int64_t lv = channel_period(nchan, row_len), nvec = total / 4, nslab = (lv + 15) / 16;
     if (lv > 32 && nchan * row_len >= 128 && nchan < (1ll << 31) && nslab <= 65536) {  // (no channel twice in a slab)
@@ -1308,9 +1307,8 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
       int64_t groups = 384 / nslab, most = (prows + 63) / 64;
       groups = groups < 1 ? 1 : (groups > most ? most : groups);
       zero_first();
-      hipLaunchKernelGGL((absmax_slab_kernel<kVecPerLane>), dim3((unsigned)(nslab * groups)), dim3(kThreads), 0, st, x, total,
+      return launch_kernel((absmax_slab_kernel<kVecPerLane>), dim3((unsigned)(nslab * groups)), dim3(kThreads), 0, st, x, total,
                          (int32_t)lv, (int32_t)nslab, (int32_t)groups, channel_div(total, nchan, row_len), t);
-      return hipGetLastError();
     }
     // every workgroup ends with an atomic per channel: twice the CUs' number of workgroups at most
     int64_t rows = g.spans * g.nseg / (256 * 2);
@@ -1318,8 +1316,7 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
     zero_first();
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
     auto kern = table ? absmax_periodic_kernel<false, true> : absmax_periodic_kernel<false, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(kThreads), lds, st, x, g, channel_div(total, nchan, row_len), t);
-    return hipGetLastError();
+    return launch_kernel(kern, dim3((unsigned)wgs), dim3(kThreads), lds, st, x, g, channel_div(total, nchan, row_len), t);
   }
   // ... a few lanes per channel where they do not.
   if (row_len < 4 * kThreads && nouter * row_len <= 65536) {
@@ -1327,8 +1324,7 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
     while (lanes < 64 && lanes * 4 < row_len) lanes *= 2;
     const int64_t wgs = (nchan * lanes + kThreads - 1) / kThreads;
     if (wgs <= max_blocks(kThreads)) {
-      hipLaunchKernelGGL(absmax_lanes_kernel, dim3((unsigned)wgs), dim3(kThreads), 0, st, x, nouter, nchan, row_len, lanes, thr);
-      return hipGetLastError();
+      return launch_kernel(absmax_lanes_kernel, dim3((unsigned)wgs), dim3(kThreads), 0, st, x, nouter, nchan, row_len, lanes, thr);
     }
   }
   int32_t nseg, seg_len;
@@ -1337,9 +1333,8 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
   // A channel of up to 64 KB, or enough channels to fill the chip: one workgroup each, which stores.
   if (nouter * row_len <= 16384 || nchan >= 1024) {
     const int64_t cap = 256 * 32;
-    hipLaunchKernelGGL((absmax_rows_kernel<kVecPerLane, true>), dim3((unsigned)(nchan < cap ? nchan : cap)), dim3(kThreads), 0,
+    return launch_kernel((absmax_rows_kernel<kVecPerLane, true>), dim3((unsigned)(nchan < cap ? nchan : cap)), dim3(kThreads), 0,
                        st, x, nouter, (int32_t)nchan, row_len, 1, (int32_t)(row_len / 4), 1, per_channel, t);
-    return hipGetLastError();
   }
   // about four workgroups per CU: rows of one channel beyond that share a workgroup (config 4
   // tensor: 12.8 us with 8 rows per workgroup, 15.8 us with one)
@@ -1349,10 +1344,9 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
   const int64_t jobs = nchan * nseg * ogroups;
   const int64_t cap = 256 * 32;
   zero_first();
-  hipLaunchKernelGGL((absmax_rows_kernel<kVecPerLane, false>), dim3((unsigned)(jobs < cap ? jobs : cap)),
+  return launch_kernel((absmax_rows_kernel<kVecPerLane, false>), dim3((unsigned)(jobs < cap ? jobs : cap)),
                      dim3(kThreads), 0, st, x, nouter, (int32_t)nchan, row_len, nseg, seg_len, (int32_t)ogroups,
                      per_channel, t);
-  return hipGetLastError();
 }
 
 template <typename AccT>
@@ -1373,7 +1367,7 @@ static hipError_t launch_requantize_t(const AccT* acc, int64_t outer, int64_t ch
     auto kern = rq.half_away ? requant_rows_kernel<AccT, kVecPerLane, true>
                 : (rq.multiplier ? requant_rows_kernel<AccT, kVecPerLane, false>
                                  : requant_rows_kernel<AccT, kVecPerLane, false, true>);
-    hipLaunchKernelGGL(kern, dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
+    launch_kernel(kern, dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
                        acc, reinterpret_cast<uint32_t*>(out), rows, (int32_t)(pc ? channels : 1),
                        inner_vec, nseg, seg_len, rq.multiplier, rq.shift, pc,
                        JobDiv{reciprocal32(nseg), reciprocal32(pc ? channels : 1)}, rs);

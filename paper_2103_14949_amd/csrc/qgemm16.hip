@@ -191,9 +191,9 @@ hipError_t launch_qconv16(const GemmArgs& a, const ConvGeom& cg, hipStream_t st)
     p.tile0 = (uint32_t)first;
     const unsigned grid = (unsigned)(tiles - first < most ? tiles - first : most);
     if (a.act_zero_point != 0)
-      hipLaunchKernelGGL(qgemm16_kernel<true>, dim3(grid), dim3(256), 0, st, p);
+      launch_kernel(qgemm16_kernel<true>, dim3(grid), dim3(256), 0, st, p);
     else
-      hipLaunchKernelGGL(qgemm16_kernel<false>, dim3(grid), dim3(256), 0, st, p);
+      launch_kernel(qgemm16_kernel<false>, dim3(grid), dim3(256), 0, st, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -498,8 +498,7 @@ hipError_t launch_dma_kernel(const QgemmParams& p, hipStream_t st) {
   static std::atomic<uint64_t> attr_set{0};  // per kernel: the devices whose dynamic-LDS limit is raised
   hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), (int)lds, attr_set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ), lds, st, p);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ), lds, st, p);
 }
 
 // Picks the kernel variant: uint8 dense activations are flipped in the loop; shapes whose

@@ -329,9 +329,8 @@ hipError_t launch_qgemm_few(const QgemmParams& p, bool i16, int waves, hipStream
     static std::atomic<uint64_t> attr_set{0};  // per kernel: the devices whose dynamic-LDS limit is raised
     const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), kDepth * NW * slot_bytes<MIS>(), attr_set);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * NW), slots * slot_bytes<MIS>(), st, p.act, p.wgt, p.M, p.N, (uint32_t)kb, blocks,
+    return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * NW), slots * slot_bytes<MIS>(), st, p.act, p.wgt, p.M, p.N, (uint32_t)kb, blocks,
                        (uint32_t)tiles, (uint32_t)minor | (channels_first ? 0x80000000u : 0u), inv, size(p.wgt, p.N), size(p.act, p.M), p);
-    return hipGetLastError();
   };
   auto by_form = [&]<bool I16, bool MIS>() {
     // eight wavefronts for tiles that are alone on their CU and have blocks for them (128 x 3072 -> 768 4.3 us, 4.7 with

@@ -217,8 +217,7 @@ hipError_t launch_line(const QgemmParams& p, hipStream_t st) {
   auto run = [&](auto kern, std::atomic<uint64_t>& attr_set) {
     const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), (int)lds, attr_set);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ), lds, st, p);
-    return hipGetLastError();
+    return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ), lds, st, p);
   };
   static std::atomic<uint64_t> set_u8{0}, set_i8{0};  // per kernel: the devices whose dynamic-LDS limit is raised
   return p.act_xor4 ? run(qgemm_line_kernel<WP, WQ, TP, TQ, true>, set_u8) : run(qgemm_line_kernel<WP, WQ, TP, TQ, false>, set_i8);
