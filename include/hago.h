@@ -439,7 +439,8 @@ hago_status hago_probe_copy(const void* src, void* dst, int64_t bytes,
  *                           2 the streaming kernel, skipping the one-launch
  *                           convolution kernels; 3 the general one-launch
  *                           convolution kernel; 4 the convolution kernels
- *                           without staging
+ *                           without staging; 5 the streaming kernel on the
+ *                           caller's channel-last tensor
  *   HAGO_HOOK_STREAM_TILE   -1 automatic; 0..6 a tile of the streaming dense kernels
  *                           (3 is 2)
  *   HAGO_HOOK_GENERAL_TILE  -1 automatic; 0..6 a tile of the general convolution

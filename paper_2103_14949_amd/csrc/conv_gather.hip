@@ -647,6 +647,39 @@ hipError_t launch_nchw(const CnParams& p, int mode, hipStream_t st) {
 
 }  // namespace
 
+namespace {
+
+struct Times { double t64, t32, other; int64_t tiles64; };
+
+Times estimate(const GemmArgs& a, const ConvGeom& cg, bool has_workspace) {
+  const int32_t steps = (cg.KH * cg.KW * ((cg.C + 15) / 16) + 1) / 2;
+  // Microseconds, fitted to 333 layers drawn at random (over 333 others the kernel so chosen is 2.5 % from the best on average,
+  // half as long again in the worst).  Here: a start, and per tile of a CU 2.2 and 0.075 a step for 64 x 64, of which a CU has whole rounds up to the third and several side by side
+  // beyond, 0.62 and 0.049 for 32 x 32; a step's part is 1.65 times that where the operands' rows are unaligned.  The other
+  // kernels: 5.9, their rate, the length of the reduction and the tensors' bytes, all but the last 1.2 times for unaligned rows
+  // without a workspace.  Measured (here, other): 16 x 28 x 28 64 -> 64 3x3 5.4, 8.4; one image 3.9, 7.1; 32 x 14 x 14 128 -> 128 8.4,
+  // 12.0; 8 x 56 x 56 64 -> 128 stride 2 5.8, 10.4; 57 x 56 224 -> 224 7x7 stride 2 31, 66; 4 x 40 x 40 100 -> 200 1x1 stride 2
+  // 3.9, 7.8; 22 x 41 x 41 32 -> 32 3x3 6.8, 8.6; 5 x 74 x 72 48 -> 39 5x5 10.1, 17.2; but 32 x 28 x 28 128 -> 128 22.7, 15.1;
+  // 20 x 69 x 72 21 -> 33 5x5 28.8, 17.4; 7 x 72 x 72 113 -> 60 3x3 22.7, 17.5.
+  auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
+  const double step = steps * (cg.C % 4 ? 1.65 : 1.0);
+  const double x64 = (double)tiles(64) / 256, x32 = (double)tiles(32) / 256;
+  const double t64 = 1.9 + (2.2 + 0.075 * step) * (x64 <= 1 ? 1.0 : x64 <= 3 ? 0.95 * std::ceil(x64) : 2.85 + 0.8 * (x64 - 3));
+  const double t32 = 2.5 + (0.62 + 0.049 * step) * (x32 <= 1 ? 1.0 : std::pow(x32, 0.93));
+  const double bytes = (double)cg.B * cg.C * cg.H * cg.W + (double)a.M * a.N * (a.has_rq ? 1 : a.acc16 ? 2 : 4);
+  const double rate = (double)a.M * a.N * a.K / 0.41e9, length = (double)a.K / 175;
+  const double steps_and_rate = rate > length ? rate + 0.8 * length : length + 0.8 * rate;
+  const double other = (5.9 + steps_and_rate) * (cg.C % 4 && !has_workspace ? 1.2 : 1.0) + bytes / 4e6;
+  return {t64, t32, other, tiles(64)};
+}
+
+}  // namespace
+
+double qconv_gather_estimate(const GemmArgs& a, const ConvGeom& cg, bool has_workspace) {
+  const Times e = estimate(a, cg, has_workspace);
+  return std::fmin(std::fmin(e.t64, e.t32), e.other);
+}
+
 // Returns false (and launches nothing) when the geometry is not this kernel's, or another kernel is the better one.
 // forced_shape: 0 64 pixels x 64 output channels by four wavefronts, 1 the same by eight, 2 32 x 32 by four; -1 by size.
 bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err) {
@@ -678,27 +711,11 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace,
   p.acc_wrap_shift = a.acc_wrap_shift;
   p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
   const int mode = a.has_rq ? 0 : (a.acc16 ? 2 : 1);
-  // Microseconds, fitted to 333 layers drawn at random (over 333 others the kernel so chosen is 2.5 % from the best on average,
-  // half as long again in the worst).  Here: a start, and per tile of a CU 2.2 and 0.075 a step for 64 x 64, of which a CU has whole rounds up to the third and several side by side
-  // beyond, 0.62 and 0.049 for 32 x 32; a step's part is 1.65 times that where the operands' rows are unaligned.  The other
-  // kernels: 5.9, their rate, the length of the reduction and the tensors' bytes, all but the last 1.2 times for unaligned rows
-  // without a workspace.  Measured (here, other): 16 x 28 x 28 64 -> 64 3x3 5.4, 8.4; one image 3.9, 7.1; 32 x 14 x 14 128 -> 128 8.4,
-  // 12.0; 8 x 56 x 56 64 -> 128 stride 2 5.8, 10.4; 57 x 56 224 -> 224 7x7 stride 2 31, 66; 4 x 40 x 40 100 -> 200 1x1 stride 2
-  // 3.9, 7.8; 22 x 41 x 41 32 -> 32 3x3 6.8, 8.6; 5 x 74 x 72 48 -> 39 5x5 10.1, 17.2; but 32 x 28 x 28 128 -> 128 22.7, 15.1;
-  // 20 x 69 x 72 21 -> 33 5x5 28.8, 17.4; 7 x 72 x 72 113 -> 60 3x3 22.7, 17.5.
-  auto tiles = [&](int64_t edge) { return ((a.M + edge - 1) / edge) * ((a.N + edge - 1) / edge); };
-  const double step = p.steps * (cg.C % 4 ? 1.65 : 1.0);
-  const double x64 = (double)tiles(64) / 256, x32 = (double)tiles(32) / 256;
-  const double t64 = 1.9 + (2.2 + 0.075 * step) * (x64 <= 1 ? 1.0 : x64 <= 3 ? 0.95 * std::ceil(x64) : 2.85 + 0.8 * (x64 - 3));
-  const double t32 = 2.5 + (0.62 + 0.049 * step) * (x32 <= 1 ? 1.0 : std::pow(x32, 0.93));
   int shape = forced_shape;
   if (shape < 0) {
-    const double bytes = (double)act_bytes + (double)a.M * a.N * (mode == 0 ? 1 : mode == 1 ? 4 : 2);
-    const double rate = (double)a.M * a.N * a.K / 0.41e9, length = (double)a.K / 175;
-    const double steps_and_rate = rate > length ? rate + 0.8 * length : length + 0.8 * rate;
-    const double other = (5.9 + steps_and_rate) * (cg.C % 4 && !has_workspace ? 1.2 : 1.0) + bytes / 4e6;
-    if ((t64 < t32 ? t64 : t32) >= other) return false;
-    shape = t32 < t64 ? 2 : tiles(64) <= 256;  // (eight wavefronts fill a CU's LDS)
+    const Times e = estimate(a, cg, has_workspace);
+    if ((e.t64 < e.t32 ? e.t64 : e.t32) >= e.other) return false;
+    shape = e.t32 < e.t64 ? 2 : e.tiles64 <= 256;  // (eight wavefronts fill a CU's LDS)
   }
   switch (shape) {
     case 0: *err = launch_shape<2, 2, 4>(p, mode, st); break;

@@ -140,6 +140,8 @@ bool is_qconv3x3_nchw(const ConvGeom& cg);
 bool try_qconv_direct(const GemmArgs& g, const ConvGeom& cg, int forced_shape, hipStream_t st, hipError_t* err);
 // Channel-last convolution of 16 or more channels, operands straight from memory to registers; false: not its geometry.
 bool try_qconv_gather(const GemmArgs& g, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err);
+// The least of the times that kernel and those behind it would take, as its own choice sees them (us).
+double qconv_gather_estimate(const GemmArgs& g, const ConvGeom& cg, bool has_workspace);
 // The same for NCHW, any channel count, and channel-last of fewer channels.  has_workspace: the caller has one for the other kernels.
 bool try_qconv_gather_nchw(const GemmArgs& g, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err);
 // 1x1 stride-1 unpadded NCHW convolution straight from the caller's buffers; false when the

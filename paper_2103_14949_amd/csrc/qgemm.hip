@@ -484,6 +484,7 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_qconv_dma(const QgemmParams& p, bool nchw_out, hipStream_t st);
+hipError_t launch_qconv_dma_direct(const QgemmParams& p, int shape, hipStream_t st);
 
 namespace {
 inline int64_t round256(int64_t v) { return (v + 255) & ~(int64_t)255; }
@@ -543,6 +544,45 @@ static bool is_dense_nhwc(const ConvGeom& cg) {
   return cg.nhwc && cg.KH == 1 && cg.KW == 1 && cg.stride_h == 1 && cg.stride_w == 1 && cg.pad_h == 0 && cg.pad_w == 0;
 }
 
+// Channel-last convolution whose taps are whole 16-byte chunks, streamed from the caller's tensors; false: not its geometry, or
+// another kernel is the better one.  shape: 0 tiles of 64 pixels, 1 of 128 (64 output channels each), -1 by size.
+static bool try_qconv_stream(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int shape, hipStream_t st, hipError_t* err) {
+  const int64_t act_bytes = (int64_t)cg.B * cg.H * cg.W * cg.C, taps = (int64_t)cg.KH * cg.KW;
+  // (32-bit offsets, and divisions by multiplication: exact while k C and tap KW stay below 2^32, a stage beyond K included)
+  if (!cg.nhwc || cg.C % 16 != 0 || act_bytes >= (1ll << 31) || (int64_t)a.N * a.K >= (1ll << 31) ||
+      (a.K + 1024ll) * cg.C >= (1ll << 32) || (taps + 64) * cg.KW >= (1ll << 32) || !ptr_aligned(a.act, 16) || !ptr_aligned(a.wgt, 16) ||
+      ((a.M + 63ll) / 64) * ((a.N + 63ll) / 64) > max_blocks(256))
+    return false;
+  QgemmParams p = make_qgemm_params(a, &cg);
+  p.vec_k = 1;
+  p.act_bytes = (uint32_t)act_bytes;
+  auto inverse = [](int64_t d, int64_t n) { return d > 1 && n * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d) : 0u; };
+  p.inv_c = inverse(cg.C, 0);
+  p.inv_kw = inverse(cg.KW, 0);
+  p.inv_ohw = inverse((int64_t)cg.OH * cg.OW, (int64_t)a.M + 128);
+  p.inv_ow = inverse(cg.OW, (int64_t)cg.OH * cg.OW);
+  p.vec16_out = (a.N % 16 == 0) && ptr_aligned(a.out, 16);
+  if (shape < 0) {
+    // Microseconds, fitted to 412 layers drawn at random (7 and 8 % off): a start, K times what a CU's first tile takes, longer
+    // where a stage holds several taps and with a flip, whose masks go by the lane; and per tile of a CU beyond the first.  The
+    // other kernels by their own estimate, which is better met than this one, so that has to win by 5 %, with a flip 12.  Of
+    // the 412 layers' sum of 3785 us the choice so made saves 400, of the 430 there are.  (Here, the others: 49 tiles 64 -> 64 3x3 on 56 x 56 4.9, 4.15; 32 -> 32
+    // on 32 x 14 x 14 4.5, 3.8; uint8 240 -> 71 5x5 on 10 x 23 x 23 33, 19; 208 -> 17 7x7 stride 2 on 4 x 55 x 55 30, 18.5; the other way beside
+    // the kernel.)
+    const bool flip = p.act_xor4 != 0 || p.pad_byte != 0, uniform = cg.C % 64 == 0;
+    auto time = [&](int pixels, double start, const double (&per_k)[2][2], double tile, double tile_k) {
+      const double x = (double)(((a.M + pixels - 1ll) / pixels) * ((a.N + 63ll) / 64)) / 256;
+      return start + per_k[flip][uniform] * a.K + (x > 1 ? (x - 1) * (tile + tile_k * a.K) : 0.0);
+    };
+    const double t64 = time(64, 3.8, {{0.00252, 0.0024}, {0.00515, 0.0049}}, 1.02, 0.00152);
+    const double t128 = time(128, 4.62, {{0.00387, 0.00331}, {0.00624, 0.00575}}, 2.0, 0.00211);
+    if ((t64 < t128 ? t64 : t128) * (flip ? 1.12 : 1.05) >= qconv_gather_estimate(a, cg, has_workspace)) return false;
+    shape = t128 < t64;
+  }
+  *err = launch_qconv_dma_direct(p, shape, st);
+  return true;
+}
+
 // The kernel for the call; *in_workspace: it reads the operands' copies, which ws holds afterwards.
 static hipError_t launch_qconv_chosen(const GemmArgs& a, const ConvGeom& cg, void* ws, bool weights_ready, int path,
                                       bool* in_workspace, hipStream_t st) {
@@ -556,9 +596,11 @@ static hipError_t launch_qconv_chosen(const GemmArgs& a, const ConvGeom& cg, voi
   }
   const int tile = g_hook[kHookGenericTile].load(std::memory_order_relaxed);
   if (path == 3 && try_qconv_direct(a, cg, tile, st, &err)) return err;
+  if (path == 5 && try_qconv_stream(a, cg, ws != nullptr, tile < 0 ? 0 : tile, st, &err)) return err;
   if (path == 4 && try_qconv_gather(a, cg, ws != nullptr, tile < 0 ? 0 : tile, st, &err)) return err;
   if (path == 4 && try_qconv_gather_nchw(a, cg, ws != nullptr, tile < 0 ? 0 : tile, st, &err)) return err;
   if (path == 0 && try_qconv_gather_nchw(a, cg, ws != nullptr, -1, st, &err)) return err;
+  if (path == 0 && try_qconv_stream(a, cg, ws != nullptr, -1, st, &err)) return err;
   if (path == 0 && try_qconv_gather(a, cg, ws != nullptr, -1, st, &err)) return err;
   if (ws && path != 1 && qconv_workspace_bytes(cg) >= 0) {
     // The rewrite through the workspace costs a launch and the copy's traffic; staging the weights in every

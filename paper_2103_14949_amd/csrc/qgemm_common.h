@@ -53,6 +53,8 @@ struct QgemmParams {
   int32_t tile0;       // first tile of this launch (a problem of many tiles takes several)
   // implicit GEMM over a prepacked copy: its byte size and ceil(2^32 / C), ceil(2^32 / KW)
   uint32_t act_bytes, inv_c, inv_kw;
+  // implicit GEMM over the caller's tensor: ceil(2^32 / (OH OW)) and of OW where that divides exactly, else 0
+  uint32_t inv_ohw, inv_ow;
 #ifdef HAGO_PHASE_TIMING
   long long* dbg;  // per-workgroup phase timestamps (development builds only)
   int dbg_skip;    // bit mask of main-loop parts to leave out in timing experiments

@@ -24,6 +24,16 @@
 // sign-flipped bytes: v_dot4 competes with the MFMAs for the matrix pipe,
 // plain vector instructions run in their shadow.
 //
+// Convolution over the caller's channel-last tensor (kConvDirect), every tap of whole 16-byte chunks: a lane works out its
+// chunk's tap in every stage and whether it lies inside the image; outside, its load is out of range and leaves zeros, which
+// the flip of the fragments turns into the zero point where they are not it already.  One launch without a rewritten copy;
+// against the loads of conv_gather.hip, a lane's 16 bytes of its own row each (a pass of the memory pipe for 16 lanes), 16 rows
+// of 64 bytes cost a load about a third.  What bounds it: launch and first loads (3.8 us), then a stage of two matrix instructions
+// behind each barrier, about 0.15 us alone on a CU and 0.1 in company; where a stage holds several taps the lane's divisions, and
+// with a flip the mask's, are most of it.  Us before (by gathered loads) and so: 64 -> 64 3x3 on 16 x 28 x 28 5.9, 5.2; 128 -> 128 on 4 x 55 x
+// 55 13.9, 8.0, on 32 x 28 x 28 23.4, 10.1; 80 -> 80 on 16 x 37 x 35 12.2, 8.0; 176 -> 36 on 5 x 101 x 101 27.0, 14.7.  (Taps counted up from
+// stage to stage instead of divided out: 48 -> 18 7x7 on 38 x 38 9.1, 12.2 so.)
+//
 // Schedule.  The ring is unrolled in the main loop, so LDS addresses are
 // constants.  At the top of iteration kt both fragment sets (one per 32-k half)
 // hold stage kt.  One s_waitcnt vmcnt + s_barrier per stage says that stage
@@ -48,6 +58,8 @@ namespace hago {
 
 namespace {
 
+enum { kDense = 0, kConvCopy = 1, kConvDirect = 2 };
+
 constexpr int kBK = 64;       // k-bytes per stage (default; small tiles use 128)
 // The L DMA instructions of a stage are dealt over its nh 32-k groups: group h issues
 // [dma_first(h), dma_first(h + 1)).
@@ -55,19 +67,21 @@ constexpr int dma_first(int h, int l, int nh) { return (h * l + nh - 1) / nh; }
 
 // kStages: depth of the LDS ring; OCC: wavefronts per SIMD the register budget must allow
 // (two 4-wavefront workgroups per CU keep the matrix pipe busy across each other's barriers).
-// CONV: the activation operand is an implicit im2col view of a padded NHWC copy of the input
-// (see conv_prepack.hip); ACT_ON_P: activations are the P operand (NCHW output).
-// FLIP: uint8 activations (dense only; the convolution's copy is already flipped).
+// CONV: the activation operand is an implicit im2col view, kConvCopy: of a padded NHWC copy of the input
+// (see conv_prepack.hip), kConvDirect: of the caller's channel-last tensor; ACT_ON_P: activations are the P operand (NCHW output).
+// FLIP: uint8 activations (the convolution's copy is already flipped); kConvDirect: activations that differ from what is
+// multiplied, and taps outside the image from zeros.
 // UNIFORM: K (and the channel count of a convolution) is a multiple of 64, so every stage has one
 // k offset for all lanes, which travels in the DMA instruction's scalar offset: the main loop
 // then computes no addresses and has no branches.  Otherwise every DMA instruction gets per-lane
 // offsets (K tail, stages that straddle filter taps).
 // BK: k-bytes per stage, 64 or 128.  With 128 a DMA instruction fetches whole 128-byte lines (8 rows)
 // and a stage has four 32-k groups instead of two, i.e. half as many barriers per k.
-template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, bool CONV, bool ACT_ON_P, bool FLIP,
+template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, int CONV, bool ACT_ON_P, bool FLIP,
           bool UNIFORM, int BK = kBK>
 __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParams p) {
-  static_assert(!FLIP || (!CONV && !ACT_ON_P), "only dense layers flip, and keep activations on Q");
+  constexpr bool kDirect = CONV == kConvDirect;
+  static_assert(!FLIP || (CONV != kConvCopy && !ACT_ON_P), "the copy is flipped; the others keep activations on Q");
   constexpr bool kPixPerm = CONV && ACT_ON_P;
   static_assert(BK == 64 || BK == 128, "stage width");
   constexpr int NH = BK / 32;       // 32-k groups per stage
@@ -123,6 +137,17 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
   // the logical chunk (in bytes) it fetches inside a stage.
   // weights: row * K.  activations: dense row * K; conv: offset of the output pixel's window
   // origin in the padded NHWC copy.
+  // kConvDirect: the window's origin in the image, rows beyond the output far outside it (no tap of theirs is inside)
+  auto origin = [&](int row, int& b, int& y, int& x) {
+    const ConvGeom& g = p.g;
+    const uint32_t ohw = (uint32_t)(g.OH * g.OW), n = (uint32_t)row;
+    const uint32_t img = ohw == 1 ? n : p.inv_ohw ? __umulhi(n, p.inv_ohw) : n / ohw, pix = n - img * ohw;
+    const uint32_t oy = g.OW == 1 ? pix : p.inv_ow ? __umulhi(pix, p.inv_ow) : pix / (uint32_t)g.OW;
+    b = (int)img;
+    y = row < p.M ? (int)oy * g.stride_h - g.pad_h : -(1 << 30);
+    x = (int)(pix - oy * (uint32_t)g.OW) * g.stride_w - g.pad_w;
+  };
+  auto inside = [&](int y, int x) { return (uint32_t)y < (uint32_t)p.g.H && (uint32_t)x < (uint32_t)p.g.W; };
   auto row_offset = [&](int row, bool is_act) -> uint32_t {
     if (!is_act) return row < p.N ? (uint32_t)row * (uint32_t)p.K : kOob;
     if (row >= p.M) return kOob;
@@ -146,6 +171,7 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
   uint32_t voff[L];  // row offset + chunk: the per-lane part of a full stage's address
   bool slot_real[L]; // false: the slot has no group, it fetches zeros into the spare window
   bool slot_q[L];
+  int slot_y[L], slot_x[L];  // kConvDirect: the origin of the row's window
   const int lrow = lane / CPR;  // row inside a group
   const int lslot = lane % CPR;  // physical 16-byte slot
   const uint32_t spare = lds0 + (uint32_t)kStages * STAGE;
@@ -168,9 +194,25 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
     slot_q[d] = isq;
     slot_real[d] = kEven || grp < G;
     uint32_t off = kOob;
+    if constexpr (kDirect) {
+      if (isq) {
+        int b;
+        origin(q0 + rt, b, slot_y[d], slot_x[d]);
+        const int y = slot_y[d] < -(1 << 29) ? 0 : slot_y[d];
+        voff[d] = (uint32_t)(((b * p.g.H + y) * p.g.W + slot_x[d]) * p.g.C + lck);  // (of a tap inside the image the sum is)
+        continue;
+      }
+    }
     if (slot_real[d]) off = row_offset((isq ? q0 : p0) + rt, isq ? !ACT_ON_P : ACT_ON_P);
     voff[d] = off == kOob ? kOob : off + (uint32_t)lck;
   }
+  // kConvDirect: the tap and the channel at position kk of the reduction (a stage beyond it included)
+  auto tap_of = [&](int kk, int& ky, int& kx, int& c) {
+    const int t = (int)__umulhi((uint32_t)kk, p.inv_c);
+    c = kk - t * p.g.C;
+    ky = p.g.KW == 1 ? t : (int)__umulhi((uint32_t)t, p.inv_kw);
+    kx = t - ky * p.g.KW;
+  };
   // k (position along the reduction) -> byte offset relative to the row offset
   auto k_offset = [&](int kk, bool is_act) -> uint32_t {
     if constexpr (CONV) {
@@ -200,6 +242,18 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
     const bool is_act = isq ? !ACT_ON_P : ACT_ON_P;
     const uint32_t dst =
         slot_real[d] ? wave_lds + (uint32_t)(NW * d * 1024 + RS * STAGE) : spare;
+    if constexpr (kDirect) {
+      // (the range check does not see a scalar offset, and origins lie in front of the tensor: every lane adds its own)
+      if (is_act) {
+        const int kk = stage_idx * BK + (UNIFORM ? 0 : lck);
+        int ky, kx, c;
+        tap_of(kk, ky, kx, c);
+        const bool ok = inside(slot_y[d] + ky, slot_x[d] + kx) && (UNIFORM || kk < p.K);
+        const uint32_t o = voff[d] - (uint32_t)(UNIFORM ? 0 : lck) + (uint32_t)((ky * p.g.W + kx) * p.g.C + c);
+        dma16(UNIFORM ? dq : rs_q, dst, ok ? o : kOob);
+        return;
+      }
+    }
     if constexpr (UNIFORM) {
       dma16s(isq ? dq : dp, dst, voff[d], is_act ? soff_a : soff_w);
     } else {
@@ -226,7 +280,7 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
       a.dp = valid ? rs_p : rs_null;
       a.dq = valid ? rs_q : rs_null;
       a.soff_w = (uint32_t)__builtin_amdgcn_readfirstlane((int)k_offset(stage_idx * BK, false));
-      a.soff_a = (uint32_t)__builtin_amdgcn_readfirstlane((int)k_offset(stage_idx * BK, true));
+      if constexpr (!kDirect) a.soff_a = (uint32_t)__builtin_amdgcn_readfirstlane((int)k_offset(stage_idx * BK, true));
     }
     return a;
   };
@@ -308,10 +362,30 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
   // in the odd one after it).
   constexpr int NM = TP * TQ;  // MFMAs per 32-k group
   constexpr int NFL = TQ * 4;  // dwords to flip per group (dense: the activations are on Q)
-  auto flip1 = [&](v4i& f, int u) {
+  // kConvDirect: what makes the bytes in LDS those that are multiplied, by the lane's row and chunk of a group: the flip of
+  // values inside the image, the zero point in place of the zeros outside
+  int fy[TQ], fx[TQ];
+  uint32_t mask[TQ];
+  if constexpr (kDirect && FLIP) {
+#pragma unroll
+    for (int j = 0; j < TQ; ++j) {
+      int b;
+      origin(q0 + (wq * TQ + j) * 32 + frow, b, fy[j], fx[j]);
+    }
+  }
+  auto set_masks = [&](int stage, int h) {
+    if constexpr (kDirect && FLIP) {
+      int ky, kx, c;
+      tap_of(stage * BK + (UNIFORM ? 0 : 32 * h + 16 * fhalf), ky, kx, c);
+#pragma unroll
+      for (int j = 0; j < TQ; ++j) mask[j] = inside(fy[j] + ky, fx[j] + kx) ? p.act_xor4 : p.pad_byte * 0x01010101u;
+    }
+  };
+  auto flip1 = [&](v4i& f, int u, int j) {
     // in place, so that no copy of the fragment is made
     int x = f[u];
-    asm volatile("v_xor_b32 %0, %1, %0" : "+v"(x) : "s"(p.act_xor4));
+    if constexpr (kDirect) asm volatile("v_xor_b32 %0, %1, %0" : "+v"(x) : "v"(mask[j]));
+    else asm volatile("v_xor_b32 %0, %1, %0" : "+v"(x) : "s"(p.act_xor4));
     f[u] = x;
   };
   auto sum1 = [&](uint32_t& a, int f) {
@@ -327,6 +401,7 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
                       auto dma_slot) {
     constexpr int H = decltype(hconst)::value;
     constexpr int HN = (H + 1) % NH;  // the set multiplied next
+    set_masks(dma_stage - (kStages - 1) + (HN == 0), HN);
     [&]<int... Mi>(std::integer_sequence<int, Mi...>) {
       ([&] {
         constexpr int m = Mi;
@@ -353,7 +428,7 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
 #pragma unroll
           for (int e = 0; e < NFL; ++e) {
             const int at = lo + (e * (NM - lo)) / NFL;
-            if (at == m) flip1(qf[HN][e / 4], e % 4);
+            if (at == m) flip1(qf[HN][e / 4], e % 4, e / 4);
           }
         }
         // refills: qf[j] after the last MFMA of column j, pf[i] after its MFMA of the last column
@@ -408,10 +483,11 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
         qf[h][j] = *reinterpret_cast<const v4i*>(smem + qa[h] + kQBase + j * kFrag);
     }
     if constexpr (FLIP) {  // the first group's fragments
+      set_masks(0, 0);
 #pragma unroll
       for (int j = 0; j < TQ; ++j)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) flip1(qf[0][j], u);
+        for (int u = 0; u < 4; ++u) flip1(qf[0][j], u, j);
     }
     // stage 0's rows (the loop sums stage kt + 1)
 #pragma unroll
@@ -485,7 +561,7 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
   qgemm_epilogue<WP, WQ, TP, TQ, ACT_ON_P, kPixPerm>(p, acc, p0, q0, s_corr, s_mult, s_shift);
 }
 
-template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, bool CONV, bool ACT_ON_P, bool FLIP,
+template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, int CONV, bool ACT_ON_P, bool FLIP,
           bool UNIFORM, int BK>
 hipError_t launch_dma_kernel(const QgemmParams& p, hipStream_t st) {
   constexpr int BP = WP * TP * 32, BQ = WQ * TQ * 32;
@@ -503,11 +579,11 @@ hipError_t launch_dma_kernel(const QgemmParams& p, hipStream_t st) {
 
 // Picks the kernel variant: uint8 dense activations are flipped in the loop; shapes whose
 // stages are uniform take the scalar-offset loop.
-template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, bool CONV, bool ACT_ON_P, int BK = kBK>
+template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, int CONV, bool ACT_ON_P, int BK = kBK>
 hipError_t launch_dma_cfg(const QgemmParams& p, hipStream_t st) {
   const bool uniform = p.K % BK == 0 && (!CONV || p.g.C % BK == 0);
-  if constexpr (!CONV) {
-    if (p.act_xor4 != 0)
+  if constexpr (CONV != kConvCopy) {
+    if (p.act_xor4 != 0 || (CONV == kConvDirect && p.pad_byte != 0))
       return uniform
                  ? launch_dma_kernel<WP, WQ, TP, TQ, kStages, OCC, CONV, ACT_ON_P, true, true, BK>(p, st)
                  : launch_dma_kernel<WP, WQ, TP, TQ, kStages, OCC, CONV, ACT_ON_P, true, false, BK>(p, st);
@@ -532,6 +608,13 @@ hipError_t launch_qdense_dma(const QgemmParams& p, int shape, hipStream_t st) {
     case 5: return launch_qdense_line(p, 5, st);                                  // 128 x 256
     default: return launch_qdense_line(p, 0, st);                                 // 256 x 256
   }
+}
+
+// The same over the caller's channel-last operands (C % 16 == 0, 16-byte aligned, tensors below 2^31 bytes).
+hipError_t launch_qconv_dma_direct(const QgemmParams& p, int shape, hipStream_t st) {
+  // 64 channels x 64 or 128 pixels.  (Over 412 layers 128 x 128 and stages of 128 bytes were the best for 3 % of those that come
+  // here, by 5 %.)
+  return shape == 0 ? launch_dma_cfg<2, 2, 1, 1, 4, 2, kConvDirect, false>(p, st) : launch_dma_cfg<1, 4, 2, 1, 4, 2, kConvDirect, false>(p, st);
 }
 
 // Implicit-GEMM convolution over the prepacked operands (p.act: padded NHWC copy, p.wgt:
