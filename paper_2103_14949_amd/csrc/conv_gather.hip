@@ -304,12 +304,11 @@ hipError_t launch_shape(const CgParams& p, int mode, hipStream_t st) {
   q.inv_tn = q.tiles_n > 1 && ids * q.tiles_n < (1ll << 32) ? (uint32_t)(((1ull << 32) + q.tiles_n - 1) / q.tiles_n) : 0u;
   auto run = [&]<bool MIS>() {
     auto kern = mode == 0 ? conv_gather_kernel<0, MIS, TP, TC, KS> : mode == 1 ? conv_gather_kernel<1, MIS, TP, TC, KS> : conv_gather_kernel<2, MIS, TP, TC, KS>;
-    launch_kernel(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
+    return launch_kernel(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
   };
   // (one step is over before the shifts pay: 22 -> 20 1x1 stride 2 on 59 x 27 x 25 3.15 us, 3.25 with them)
-  if (q.steps > 1 && (q.C % 4 != 0 || ((reinterpret_cast<uintptr_t>(q.act) | reinterpret_cast<uintptr_t>(q.wgt)) & 3u) != 0)) run.template operator()<true>();
-  else run.template operator()<false>();
-  return hipGetLastError();
+  if (q.steps > 1 && (q.C % 4 != 0 || ((reinterpret_cast<uintptr_t>(q.act) | reinterpret_cast<uintptr_t>(q.wgt)) & 3u) != 0)) return run.template operator()<true>();
+  return run.template operator()<false>();
 }
 
 // ---- NCHW, and channel-last of fewer than 16 channels.  The 16 reduction elements of a lane (k = (c, ky, kx), or

@@ -202,13 +202,13 @@ __global__ __launch_bounds__(256) void conv_prepack_nchw_kernel(PrepackArgs p, i
 hipError_t static_scratch(void** ptr, int64_t* capacity) {
   static std::atomic<void*> addr[64];  // per device; zero-initialised
   int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  hipError_t e = reported(hipGetDevice(&dev));
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   void* p = addr[dev].load(std::memory_order_acquire);
   if (!p) {
     // the current device's copy of the array (two threads may both ask; they get the same answer)
-    e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+    e = reported(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
     if (e != hipSuccess) return e;
     if (!p) return hipErrorInvalidSymbol;
     addr[dev].store(p, std::memory_order_release);

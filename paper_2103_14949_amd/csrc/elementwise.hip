@@ -773,36 +773,28 @@ inline bool periodic_split(int64_t total, int64_t channels, int64_t inner, int u
 
 // Periodic / flat launch of an operator; OpP keeps reciprocals for the periodic kernel, OpF does not.
 template <class OpP, class OpF, class... A>
-void launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStream_t st, A... args) {
+hipError_t launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStream_t st, A... args) {
   constexpr int U = kVecPerLane;
   const ChannelDiv d = channel_div(total, channels, inner);
   SpanArgs g;
   if (periodic_split(total, channels, inner, U, &g)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
-    launch_kernel((periodic_kernel<OpP, U>), dim3((unsigned)wgs), dim3(kThreads), 0, st, OpP{args...}, g, d);
-    return;
+    return launch_kernel(periodic_kernel<OpP, U>, dim3((unsigned)wgs), dim3(kThreads), 0, st, OpP{args...}, g, d);
   }
   // one vector per lane while that does not fill the chip, four beyond
   const int64_t nvec = total / 4 > 0 ? total / 4 : 1;
   const int64_t w1 = (nvec + kThreads - 1) / kThreads, w4 = (nvec + kThreads * U - 1) / (kThreads * U);
   // (more than one launch from 2^36 elements on)
   constexpr int64_t most = max_blocks(kThreads);
-#define HAGO_FLAT(UU, MULTI, W)                                                                                       \
-  for (int64_t b0 = 0; b0 < W; b0 += most)                                                                            \
-  launch_kernel((flat_kernel<OpF, UU, MULTI>), dim3((unsigned)(W - b0 < most ? W - b0 : most)), dim3(kThreads), 0, st, \
-                     OpF{args...}, total, d, b0)
-  if (w1 <= 1024) {
-    if (inner < 4) {
-      HAGO_FLAT(1, true, w1);
-    } else {
-      HAGO_FLAT(1, false, w1);
+  auto flat = [&](auto kern, int64_t wgs) {
+    for (int64_t b0 = 0; b0 < wgs; b0 += most) {
+      const hipError_t e = launch_kernel(kern, dim3((unsigned)(wgs - b0 < most ? wgs - b0 : most)), dim3(kThreads), 0, st, OpF{args...}, total, d, b0);
+      if (e != hipSuccess) return e;
     }
-  } else if (inner < 4) {
-    HAGO_FLAT(U, true, w4);
-  } else {
-    HAGO_FLAT(U, false, w4);
-  }
-#undef HAGO_FLAT
+    return hipSuccess;
+  };
+  if (w1 <= 1024) return inner < 4 ? flat(flat_kernel<OpF, 1, true>, w1) : flat(flat_kernel<OpF, 1, false>, w1);
+  return inner < 4 ? flat(flat_kernel<OpF, U, true>, w4) : flat(flat_kernel<OpF, U, false>, w4);
 }
 
 // Batched candidates over such rows: the lane's channels stay, the candidates' parameters are read per
@@ -879,31 +871,31 @@ __global__ __launch_bounds__(kThreads) void simquant_batched_ragged_kernel(
   }
 }
 
-inline void launch_batched_ragged(const float* x, float* y, int64_t total, int64_t channels, int64_t inner,
-                                  int32_t nbatch, const float* scale, const int32_t* zp, const CandidateClips& clips,
-                                  hipStream_t st) {
+inline hipError_t launch_batched_ragged(const float* x, float* y, int64_t total, int64_t channels, int64_t inner,
+                                        int32_t nbatch, const float* scale, const int32_t* zp, const CandidateClips& clips,
+                                        hipStream_t st) {
   constexpr int U = 2;
   const ChannelDiv d = channel_div(total, channels, inner);
   SpanArgs g;
   if (periodic_split(total, channels, inner, U, &g)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
-    launch_kernel((simquant_batched_ragged_kernel<U, true>), dim3((unsigned)wgs), dim3(kThreads), 0, st, x, y, g, d,
-                       nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);
-    return;
+    return launch_kernel(simquant_batched_ragged_kernel<U, true>, dim3((unsigned)wgs), dim3(kThreads), 0, st, x, y, g, d,
+                         nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);
   }
   g = SpanArgs{};
   g.total = total;
   const int64_t nvec = total / 4 > 0 ? total / 4 : 1;
   if (nvec <= 1024 * kThreads)
-    launch_kernel((simquant_batched_ragged_kernel<1, false>), dim3((unsigned)((nvec + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);
-  else {
-    constexpr int64_t most = max_blocks(kThreads);
-    const int64_t wgs = (nvec + kThreads * U - 1) / (kThreads * U);
-    for (int64_t b0 = 0; b0 < wgs; b0 += most)  // (more than one launch from 2^35 elements on)
-      launch_kernel((simquant_batched_ragged_kernel<U, false>), dim3((unsigned)(wgs - b0 < most ? wgs - b0 : most)),
-                         dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips, b0);
+    return launch_kernel(simquant_batched_ragged_kernel<1, false>, dim3((unsigned)((nvec + kThreads - 1) / kThreads)),
+                         dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);
+  constexpr int64_t most = max_blocks(kThreads);
+  const int64_t wgs = (nvec + kThreads * U - 1) / (kThreads * U);
+  for (int64_t b0 = 0; b0 < wgs; b0 += most) {  // (more than one launch from 2^35 elements on)
+    const hipError_t e = launch_kernel(simquant_batched_ragged_kernel<U, false>, dim3((unsigned)(wgs - b0 < most ? wgs - b0 : most)),
+                                       dim3(kThreads), 0, st, x, y, g, d, nbatch, (int32_t)channels, scale, zp, clips, b0);
+    if (e != hipSuccess) return e;
   }
+  return hipSuccess;
 }
 
 // ---- max-abs calibration (Eq. 2): thr[c] = max |x[o, c, i]| over o, i.  NaN never wins a
@@ -1163,15 +1155,13 @@ hipError_t launch_simquant(const float* x, float* y, int64_t outer, int64_t chan
     const int64_t inner_vec = row_len / 4;
     int32_t nseg, seg_len;
     split_row(inner_vec, kVecPerLane, &nseg, &seg_len);
-    launch_kernel((simquant_rows_kernel<kVecPerLane, false>), dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
+    return launch_kernel((simquant_rows_kernel<kVecPerLane, false>), dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
                        reinterpret_cast<const v4f*>(x), reinterpret_cast<v4f*>(y), rows,
                        (int32_t)(per_channel ? channels : 1), inner_vec, nseg, seg_len, scale, zp,
                        per_channel, JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi, 0, 0);
-  } else {
-    launch_ragged<SimquantOp<false, true>, SimquantOp<false, false>>(
-        total, per_channel ? channels : 1, per_channel ? inner : total, st, x, y, scale, zp, lo, hi, 0, 0);
   }
-  return hipGetLastError();
+  return launch_ragged<SimquantOp<false, true>, SimquantOp<false, false>>(
+      total, per_channel ? channels : 1, per_channel ? inner : total, st, x, y, scale, zp, lo, hi, 0, 0);
 }
 
 hipError_t launch_simquant_wrap(const float* x, float* y, int64_t outer, int64_t channels, int64_t inner,
@@ -1186,16 +1176,14 @@ hipError_t launch_simquant_wrap(const float* x, float* y, int64_t outer, int64_t
     const int64_t inner_vec = row_len / 4;
     int32_t nseg, seg_len;
     split_row(inner_vec, kVecPerLane, &nseg, &seg_len);
-    launch_kernel((simquant_rows_kernel<kVecPerLane, true>), dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
+    return launch_kernel((simquant_rows_kernel<kVecPerLane, true>), dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
                        reinterpret_cast<const v4f*>(x), reinterpret_cast<v4f*>(y), rows,
                        (int32_t)(per_channel ? channels : 1), inner_vec, nseg, seg_len, scale, zp,
                        per_channel, JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi,
                        wrap_bits, wrap_signed);
-  } else {
-    launch_ragged<SimquantOp<true, true>, SimquantOp<true, false>>(
-        total, per_channel ? channels : 1, per_channel ? inner : total, st, x, y, scale, zp, lo, hi, wrap_bits, wrap_signed);
   }
-  return hipGetLastError();
+  return launch_ragged<SimquantOp<true, true>, SimquantOp<true, false>>(
+      total, per_channel ? channels : 1, per_channel ? inner : total, st, x, y, scale, zp, lo, hi, wrap_bits, wrap_signed);
 }
 
 hipError_t launch_simquant_batched(const float* x, float* y, int64_t outer, int64_t channels,
@@ -1218,14 +1206,12 @@ hipError_t launch_simquant_batched(const float* x, float* y, int64_t outer, int6
     constexpr int kU = 2;  // fewer vectors in flight per lane: every one is stored nbatch times
     int32_t nseg, seg_len;
     split_row(inner_vec, kU, &nseg, &seg_len);
-    launch_kernel(simquant_batched_rows_kernel<kU>, dim3(grid_for(rows * nseg)), dim3(kThreads),
+    return launch_kernel(simquant_batched_rows_kernel<kU>, dim3(grid_for(rows * nseg)), dim3(kThreads),
                        0, st, reinterpret_cast<const v4f*>(x), reinterpret_cast<v4f*>(y), rows,
                        nparam, inner_vec, nseg, seg_len, nbatch, nparam, scale, zp, per_channel,
                        JobDiv{reciprocal32(nseg), reciprocal32(nparam)}, clips);
-  } else {
-    launch_batched_ragged(x, y, total, nparam, per_channel ? inner : total, nbatch, scale, zp, clips, st);
   }
-  return hipGetLastError();
+  return launch_batched_ragged(x, y, total, nparam, per_channel ? inner : total, nbatch, scale, zp, clips, st);
 }
 
 template <typename Q, int OP>
@@ -1241,15 +1227,13 @@ static hipError_t launch_quant_t(const void* in, void* out, float* out2, int64_t
     const int64_t inner_vec = row_len / 4;
     int32_t nseg, seg_len;
     split_row(inner_vec, kVecPerLane, &nseg, &seg_len);
-    launch_kernel((quant_rows_kernel<Q, OP, kVecPerLane>), dim3(grid_for(rows * nseg)),
+    return launch_kernel((quant_rows_kernel<Q, OP, kVecPerLane>), dim3(grid_for(rows * nseg)),
                        dim3(kThreads), 0, st, in, out, out2, rows, (int32_t)(per_channel ? channels : 1),
                        inner_vec, nseg, seg_len, scale, zp, per_channel,
                        JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi);
-  } else {
-    launch_ragged<QuantOp<Q, OP, OP != 1>, QuantOp<Q, OP, false>>(
-        total, per_channel ? channels : 1, per_channel ? inner : total, st, in, out, out2, scale, zp, lo, hi);
   }
-  return hipGetLastError();
+  return launch_ragged<QuantOp<Q, OP, OP != 1>, QuantOp<Q, OP, false>>(
+      total, per_channel ? channels : 1, per_channel ? inner : total, st, in, out, out2, scale, zp, lo, hi);
 }
 
 // container: 0 int8, 1 uint8, 2 int16, 3 int32.  op 0: fp32 -> codes; 1: codes -> fp32;
@@ -1282,13 +1266,10 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
   uint32_t* t = reinterpret_cast<uint32_t*>(thr);
   auto zero_first = [&] {
     // (a fill kernel, not hipMemsetAsync: the call may be captured into a graph)
-    launch_kernel(fill_zero_kernel, dim3(grid_for((nthr + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, t, nthr);
+    return launch_kernel(fill_zero_kernel, dim3(grid_for((nthr + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, t, nthr);
   };
   const int64_t total = outer * channels * inner;
-  if (total == 0) {
-    zero_first();
-    return hipGetLastError();
-  }
+  if (total == 0) return zero_first();
   const int64_t nchan = per_channel ? channels : 1;
   const int64_t nouter = nchan > 1 ? outer : 1, row_len = nchan > 1 ? inner : total;  // one channel: one row
   // Rows shorter than a workgroup's 1024 elements: merged in LDS where their channels come back often ...
@@ -1306,14 +1287,14 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
       const int64_t prows = (nvec + lv - 1) / lv;
       int64_t groups = 384 / nslab, most = (prows + 63) / 64;
       groups = groups < 1 ? 1 : (groups > most ? most : groups);
-      zero_first();
+      if (const hipError_t e = zero_first(); e != hipSuccess) return e;
       return launch_kernel((absmax_slab_kernel<kVecPerLane>), dim3((unsigned)(nslab * groups)), dim3(kThreads), 0, st, x, total,
                          (int32_t)lv, (int32_t)nslab, (int32_t)groups, channel_div(total, nchan, row_len), t);
     }
     // every workgroup ends with an atomic per channel: twice the CUs' number of workgroups at most
     int64_t rows = g.spans * g.nseg / (256 * 2);
     if (rows > g.rows) g.rows = (int32_t)rows;
-    zero_first();
+    if (const hipError_t e = zero_first(); e != hipSuccess) return e;
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
     auto kern = table ? absmax_periodic_kernel<false, true> : absmax_periodic_kernel<false, false>;
     return launch_kernel(kern, dim3((unsigned)wgs), dim3(kThreads), lds, st, x, g, channel_div(total, nchan, row_len), t);
@@ -1343,7 +1324,7 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
   const int64_t ogroups = (nouter + rows_per_wg - 1) / rows_per_wg;
   const int64_t jobs = nchan * nseg * ogroups;
   const int64_t cap = 256 * 32;
-  zero_first();
+  if (const hipError_t e = zero_first(); e != hipSuccess) return e;
   return launch_kernel((absmax_rows_kernel<kVecPerLane, false>), dim3((unsigned)(jobs < cap ? jobs : cap)),
                      dim3(kThreads), 0, st, x, nouter, (int32_t)nchan, row_len, nseg, seg_len, (int32_t)ogroups,
                      per_channel, t);
@@ -1367,18 +1348,15 @@ static hipError_t launch_requantize_t(const AccT* acc, int64_t outer, int64_t ch
     auto kern = rq.half_away ? requant_rows_kernel<AccT, kVecPerLane, true>
                 : (rq.multiplier ? requant_rows_kernel<AccT, kVecPerLane, false>
                                  : requant_rows_kernel<AccT, kVecPerLane, false, true>);
-    launch_kernel(kern, dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
+    return launch_kernel(kern, dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st,
                        acc, reinterpret_cast<uint32_t*>(out), rows, (int32_t)(pc ? channels : 1),
                        inner_vec, nseg, seg_len, rq.multiplier, rq.shift, pc,
                        JobDiv{reciprocal32(nseg), reciprocal32(pc ? channels : 1)}, rs);
-  } else {
-    const int64_t ch = pc ? channels : 1, in = pc ? inner : total;
-    if (rq.half_away)
-      launch_ragged<RequantOp<AccT, true>, RequantOp<AccT, true>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
-    else
-      launch_ragged<RequantOp<AccT, false>, RequantOp<AccT, false>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
   }
-  return hipGetLastError();
+  const int64_t ch = pc ? channels : 1, in = pc ? inner : total;
+  if (rq.half_away)
+    return launch_ragged<RequantOp<AccT, true>, RequantOp<AccT, true>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
+  return launch_ragged<RequantOp<AccT, false>, RequantOp<AccT, false>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
 }
 
 hipError_t launch_requantize(const void* acc, int acc16, int64_t outer, int64_t channels,

@@ -11,27 +11,35 @@
 
 namespace hago {
 
+// The status of a call of the runtime.  A failure also stays behind as the thread's last error, whatever succeeds after it, and
+// would be taken for one of a later call; who is told of it here is told once, so it is cleared.
+[[nodiscard]] inline hipError_t reported(hipError_t e) {
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
 // The dynamic-LDS limit of a kernel is a per-device attribute.  `done` holds one bit per device
 // (ids modulo 64) on which it has been raised; concurrent first calls may both set it, which is
 // harmless.
-inline hipError_t raise_lds_limit(const void* kern, int lds_bytes, std::atomic<uint64_t>& done) {
-  static const bool one_device = [] { int n = 0; return hipGetDeviceCount(&n) == hipSuccess && n == 1; }();
+[[nodiscard]] inline hipError_t raise_lds_limit(const void* kern, int lds_bytes, std::atomic<uint64_t>& done) {
+  static const bool one_device = [] { int n = 0; return reported(hipGetDeviceCount(&n)) == hipSuccess && n == 1; }();
   int dev = 0;
-  hipError_t e = one_device ? hipSuccess : hipGetDevice(&dev);  // (0.05 us)
+  hipError_t e = one_device ? hipSuccess : reported(hipGetDevice(&dev));  // (0.05 us)
   if (e != hipSuccess) return e;
   const uint64_t bit = 1ull << (dev & 63);
   if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
-  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+  e = reported(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
   if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
   return e;
 }
 
 // One kernel launch.  (The launch syntax and hipLaunchKernelGGL hand the configuration over by two more calls: 2.45 us of host
-// time for a kernel with 216 bytes of arguments, 2.25 so; hipGetLastError behind it is another 0.04.)
+// time for a kernel with 216 bytes of arguments, 2.25 so; hipGetLastError behind it is another 0.04.)  Its status is its own: a
+// call of several launches looks at each.
 template <typename... P>
-inline hipError_t launch_kernel(void (*kern)(P...), dim3 grid, dim3 block, size_t lds_bytes, hipStream_t st, std::type_identity_t<P>... args) {
+[[nodiscard]] inline hipError_t launch_kernel(void (*kern)(P...), dim3 grid, dim3 block, size_t lds_bytes, hipStream_t st, std::type_identity_t<P>... args) {
   void* ptrs[] = {const_cast<void*>(static_cast<const void*>(&args))...};
-  return hipLaunchKernel(reinterpret_cast<const void*>(kern), grid, block, ptrs, lds_bytes, st);
+  return reported(hipLaunchKernel(reinterpret_cast<const void*>(kern), grid, block, ptrs, lds_bytes, st));
 }
 
 // A launch holds fewer than 2^32 threads; of a larger grid the runtime starts a part, without an error.

@@ -415,14 +415,13 @@ hipError_t launch(PwArgs q, hipStream_t st) {
   // on 8 x 56 x 56, 400 of them, 6.0, 7.9; 480 -> 80 on 2 x 112 x 112, 588, 10.5, 8.3).
   auto run = [&]<int KS, int CH>() {
     const auto kern = KS == 1 && q.HW < 128 ? pw_nchw_kernel<MODE, ACC16, KS, CH, KS == 1> : pw_nchw_kernel<MODE, ACC16, KS, CH, false>;
-    launch_kernel(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
+    return launch_kernel(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
   };
-  if (q.C > 64 && ids <= 512) run.template operator()<4, 5>();
-  else if (q.C <= 32) run.template operator()<1, 1>();
-  else if (q.C <= 64) run.template operator()<1, 2>();
-  else if (q.C <= 96) run.template operator()<1, 3>();
-  else run.template operator()<1, 5>();
-  return hipGetLastError();
+  if (q.C > 64 && ids <= 512) return run.template operator()<4, 5>();
+  if (q.C <= 32) return run.template operator()<1, 1>();
+  if (q.C <= 64) return run.template operator()<1, 2>();
+  if (q.C <= 96) return run.template operator()<1, 3>();
+  return run.template operator()<1, 5>();
 }
 
 }  // namespace

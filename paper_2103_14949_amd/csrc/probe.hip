@@ -8,7 +8,7 @@
 //                        (128-bit nontemporal loads and stores, four per lane).
 #include "../../include/hago.h"
 
-#include <hip/hip_runtime.h>
+#include "launch.h"
 
 namespace {
 
@@ -56,9 +56,9 @@ extern "C" {
 hago_status hago_probe_mfma_i8(const void* operands, void* sink, int32_t workgroups, int32_t iters, void* stream) {
   if (!operands || !sink) return HAGO_ERR_NULL;
   if (workgroups < 1 || workgroups > (1 << 20) || iters < 0) return HAGO_ERR_SHAPE;
-  hipLaunchKernelGGL(probe_mfma_kernel, dim3((unsigned)workgroups), dim3(256), 0, static_cast<hipStream_t>(stream),
-                     static_cast<const v4i*>(operands), static_cast<int32_t*>(sink), iters);
-  return hipGetLastError() == hipSuccess ? HAGO_OK : HAGO_ERR_DEVICE;
+  const hipError_t e = hago::launch_kernel(probe_mfma_kernel, dim3((unsigned)workgroups), dim3(256), 0, static_cast<hipStream_t>(stream),
+                                           static_cast<const v4i*>(operands), static_cast<int32_t*>(sink), iters);
+  return e == hipSuccess ? HAGO_OK : HAGO_ERR_DEVICE;
 }
 
 hago_status hago_probe_copy(const void* src, void* dst, int64_t bytes, void* stream) {
@@ -68,9 +68,9 @@ hago_status hago_probe_copy(const void* src, void* dst, int64_t bytes, void* str
   if ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15u) return HAGO_ERR_PARAM;
   const int64_t nvec = bytes / 16;
   const int64_t blocks = (nvec + 1023) / 1024;
-  hipLaunchKernelGGL(probe_copy_kernel, dim3((unsigned)(blocks < (1 << 30) ? blocks : (1 << 30))), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const v4i*>(src), static_cast<v4i*>(dst), nvec);
-  return hipGetLastError() == hipSuccess ? HAGO_OK : HAGO_ERR_DEVICE;
+  const hipError_t e = hago::launch_kernel(probe_copy_kernel, dim3((unsigned)(blocks < (1 << 30) ? blocks : (1 << 30))), dim3(256), 0,
+                                           static_cast<hipStream_t>(stream), static_cast<const v4i*>(src), static_cast<v4i*>(dst), nvec);
+  return e == hipSuccess ? HAGO_OK : HAGO_ERR_DEVICE;
 }
 
 }  // extern "C"

@@ -190,11 +190,7 @@ hipError_t launch_qconv16(const GemmArgs& a, const ConvGeom& cg, hipStream_t st)
   for (int64_t first = 0; first < tiles; first += most) {
     p.tile0 = (uint32_t)first;
     const unsigned grid = (unsigned)(tiles - first < most ? tiles - first : most);
-    if (a.act_zero_point != 0)
-      launch_kernel(qgemm16_kernel<true>, dim3(grid), dim3(256), 0, st, p);
-    else
-      launch_kernel(qgemm16_kernel<false>, dim3(grid), dim3(256), 0, st, p);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_kernel(a.act_zero_point != 0 ? qgemm16_kernel<true> : qgemm16_kernel<false>, dim3(grid), dim3(256), 0, st, p);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

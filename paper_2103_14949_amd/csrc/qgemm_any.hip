@@ -384,8 +384,7 @@ hipError_t launch_tiles(void (*kern)(QgemmParams), QgemmParams p, int64_t tiles,
   const int64_t most = (1ll << 32) / threads - 8;  // (a multiple of the eight XCDs)
   for (int64_t first = 0; first < tiles; first += most) {
     p.tile0 = (int32_t)first;
-    launch_kernel(kern, dim3((unsigned)(tiles - first < most ? tiles - first : most)), dim3(threads), lds, st, p);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_kernel(kern, dim3((unsigned)(tiles - first < most ? tiles - first : most)), dim3(threads), lds, st, p);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
