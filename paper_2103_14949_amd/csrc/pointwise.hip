@@ -392,18 +392,28 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
   }
 }
 
+// Wavefronts of the variant for CH = 2 and 3 (33 to 64 and 65 to 96 channels) that a SIMD has registers for, of 512: up to 128
+// registers a wavefront four, up to 168 three, up to 256 two.
+constexpr int waves_per_simd(int mode, bool acc16, int ch, bool small) {
+  const bool wide = mode == 0 && !acc16;  // (64-bit requantize of four values at a time)
+  if (ch == 3) return wide || small ? 2 : 3;
+  return small ? (wide ? 2 : 3) : (mode == 2 ? 4 : 3);
+}
+
 template <int MODE, bool ACC16>
 hipError_t launch(PwArgs q, hipStream_t st) {
   const int32_t blocks = (q.N + 31) / 32;
-  // C <= 96: several blocks per wavefront.  A SIMD has registers for two wavefronts of more than 64 channels and three of more than
-  // 32: as few blocks as bring all wavefronts there in one round (us with 1, 2 and 3: 72 -> 432 on 42 x 28 x 28, 4116 blocks, 13.5, 12.8,
-  // 11.3; 96 -> 576 on 2 x 112 x 112, 3528, 11.1, 9.7, 11.1; 56 -> 336 on 4 x 98 x 98, 3344, 9.2, 8.2, 9.4; 64 -> 384 on 8 x 56 x 56, 2400,
-  // 6.8, 7.4).  Where one round cannot hold them, and up to 32 channels, so many blocks that 1.5 wavefronts per SIMD are left (24 -> 144
+  // C <= 96: several blocks per wavefront.  Above 32 channels as few as bring all wavefronts into one round, by the registers of the
+  // variant (us with 1, 2 and 3 blocks: 72 -> 432 on 42 x 28 x 28, 4116 blocks, two wavefronts per SIMD, 13.5, 12.8,
+  // 11.3; 96 -> 576 on 2 x 112 x 112, 3528, two, 11.1, 9.7, 11.1; 56 -> 336 on 4 x 98 x 98, 3344, three, 9.2, 8.2, 9.4; 64 -> 384 on 8 x
+  // 56 x 56, 2400, three, 6.8, 7.4; with 16-bit accumulators 88 -> 44 on 285 x 20 x 20, 2280, three, 9.8, 10.8).  Over 416 layers of all
+  // variants such a count is 1.5 % from the best of five, with two wavefronts above 64 channels and three below for all of them 2.1.
+  // Where one round cannot hold them, and up to 32 channels, so many blocks that 1.5 wavefronts per SIMD are left (24 -> 144
   // -> 24 with its depthwise layer on 32 x 56 x 56, 4000 blocks of the first, 24.2, 23.3).
-  const int64_t all = q.tiles * blocks, slots = q.C > 64 ? 2048 : 3072;
+  const int64_t all = q.tiles * blocks, slots = 1024 * waves_per_simd(MODE, ACC16, q.C > 64 ? 3 : 2, q.HW < 128);
   int64_t per = 1;
   if (q.C <= 32 || q.tiles > slots) per = q.C <= 96 && all >= 1536 ? all / 1536 : 1;
-  else if (q.C <= 96) while (q.tiles * ((blocks + per - 1) / per) > slots) ++per;
+  else if (q.C <= 96) per = (blocks + slots / q.tiles - 1) / (slots / q.tiles);
   q.per_wave = (int32_t)(per < blocks ? per : blocks);
   q.nblocks = (blocks + q.per_wave - 1) / q.per_wave;
   q.per_wave = (blocks + q.nblocks - 1) / q.nblocks;

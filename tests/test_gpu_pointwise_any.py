@@ -14,6 +14,8 @@ SIZES = [  # B C H W O
     (1, 68, 8, 16, 33), (2, 96, 10, 13, 96), (1, 100, 15, 15, 20), (2, 164, 12, 11, 65), (1, 576, 14, 14, 96),
     (3, 640, 5, 5, 31), (1, 324, 40, 41, 45), (9, 24, 57, 55, 144), (4, 80, 56, 57, 160), (1, 100, 46, 47, 1000),
     (2, 8, 1, 127, 6), (2, 40, 3, 43, 7), (1, 72, 4, 32, 5),
+    # just more blocks than wavefronts of some or all variants run at once, and so two to four blocks each: small images, larger ones
+    (1030, 68, 1, 4, 40), (1100, 68, 1, 5, 100), (1040, 36, 2, 3, 70), (1100, 64, 1, 4, 100), (1030, 68, 8, 16, 33),
 ]
 
 
