@@ -7,6 +7,7 @@
 //   nhwc3x3  : channel-last, stride 1 and 2, pad 1, C >= 4: four channels, four columns and a run of rows per thread.
 //   direct   : every other geometry / layout: one output per lane straight
 //              from global memory (cache-served), same arithmetic.
+#include "dw_split.h"
 #include "hago_device.h"
 #include "launch.h"
 
@@ -36,30 +37,27 @@ struct DwArgs {
   const int32_t* shift;
   int32_t per_channel;
   RequantScalars rs;
-  uint32_t inv_x, inv_mid;  // xcd_place's divisors: ceil(2^32 / d), 0 where that is not exact (or d is 1)
 };
 
-// The work of a launch of gridDim.x * mid * outer workgroups, the outermost index first: images, in all three kernels, so
+// The work of a launch of gx * mid * outer workgroups, the outermost index first: images, in all three kernels, so
 // that each keeps to the XCD that its neighbours in a network of 1x1 layers use for it.  Us of an expansion, a depthwise
 // layer and a projection, with the workgroups in launch order (an image's channels on all XCDs) and so, buffers kept
 // and three sets of them in turn: 24 -> 144 -> 24 on 8 x 56 x 56 14.0, 11.9 and 15.0, 13.0; on 32 x 56 x 56 29.9, 22.2 and 23.3,
 // 23.3 (14 MB between the layers: rewriting lines that other XCDs still hold is what cost the first).
+// What a workgroup finds its place by comes as the kernel's leading arguments, which are in scalar registers when it starts: from
+// behind the others, where the launch's own dimensions are too, it took 0.1 to 0.2 us of a layer.
 struct DwPlace { int32_t x, mid, outer; };
-__device__ __forceinline__ DwPlace xcd_place(const DwArgs& p, uint32_t mid) {
-  auto over = [](uint32_t n, uint32_t d, uint32_t inv) {
-    return d == 1 ? n : (inv ? __umulhi(n, inv) : (uint32_t)__builtin_amdgcn_readfirstlane((int)(n / d)));
-  };
-  const uint32_t gx = gridDim.x, count = gx * gridDim.y * gridDim.z;
-  const uint32_t id = xcd_run(blockIdx.x + gx * (blockIdx.y + gridDim.y * blockIdx.z), count);
-  const uint32_t rest = over(id, gx, p.inv_x), outer = over(rest, mid, p.inv_mid);
+__device__ __forceinline__ uint32_t over(uint32_t n, uint32_t d, uint32_t inv) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)(d == 1 ? n : inv ? __umulhi(n, inv) : n / d));
+}
+// Of workgroups of equal work, launched as gx x mid x outer.
+__device__ __forceinline__ DwPlace xcd_place(uint32_t gx, uint32_t mid, uint32_t count, uint32_t inv_x, uint32_t inv_mid) {
+  const uint32_t id = xcd_run(blockIdx.x + gx * (blockIdx.y + mid * blockIdx.z), count);
+  const uint32_t rest = over(id, gx, inv_x), outer = over(rest, mid, inv_mid);
   return DwPlace{(int32_t)(id - rest * gx), (int32_t)(rest - outer * mid), (int32_t)outer};
 }
-DwArgs with_divisors(DwArgs p, int64_t gx, int64_t mid, int64_t outer) {
-  auto inverse = [](int64_t d, int64_t n) { return d > 1 && n * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d) : 0u; };
-  p.inv_x = inverse(gx, gx * mid * outer);
-  p.inv_mid = inverse(mid, mid * outer);
-  return p;
-}
+// ceil(2^32 / d) for quotients of numbers below n; 0: not exact (or d is 1).
+uint32_t inverse(int64_t d, int64_t n) { return d > 1 && n * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d) : 0u; }
 
 __device__ __forceinline__ int32_t wrap_acc(int32_t acc, int wrap_shift) {
   return wrap_shift ? wrap_acc_bits(acc, wrap_shift) : acc;
@@ -178,24 +176,27 @@ __device__ __forceinline__ DwChannel dw_channel(const DwArgs& p, int c) {
 // weights, bias and multiplier -- comes through scalar loads and scalar arithmetic, and the
 // per-output work is three dot products, one 64-bit multiply-add, one shift and one clamp.
 // MODE 0: requantized 8-bit, 1: raw int32, 2: raw int16; ACC16: accumulator wraps to 16 bits.
-// WIDE: images wider than 64 columns are cut into segments of segw <= 64 (grid z = band * nsegs + segment);
+// WIDE: images wider than 64 columns are cut into segments of segw <= 64;
 // the lanes at the ends of a segment fetch the neighbouring segment's dword with one more load
 // per row, which replaces what the DPP shift cannot deliver.
 // RAGGED: rows that are not whole dwords (or tensors at any byte).  Loads and stores are unaligned; the last strip of a
 // row is loaded from the row's last four bytes and shifted into place, and stored as those four bytes together with the
 // end of its left neighbour's results (16 x 288 planes of 41 x 41: 24.8 us through LDS, 8.6 here).
 template <int MODE, bool ACC16, bool WIDE, bool RAGGED>
-__global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(DwArgs p, int32_t rpc, int32_t nsegs, int32_t segw) {
-  // grid: x = groups of four channels, y = image, z = band (and column segment); numbered image, band, group
+__global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(uint32_t gx, uint32_t mid, uint32_t count, uint32_t inv_x, uint32_t inv_mid,
+                                                               DwArgs p, int32_t rpc, int32_t nsegs, int32_t segw) {
+  // grid: x = groups of four channels, of each its column segments (which are not equally wide: next to each other, every XCD has as
+  // many of both; 96 -> 576 -> depthwise -> 96 on one 112 x 112 image, segments of 64 and 48 columns, 25.6 us with a segment's groups of
+  // all channels in a row, 22.5 so), y = band, z = image
   const ConvGeom& g = p.g;
   const int H = g.H, W = g.W;
   const int lane = threadIdx.x & 63;
-  const DwPlace at = xcd_place(p, gridDim.z);
-  const int c = at.x * 4 + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const DwPlace at = xcd_place(gx, mid, count, inv_x, inv_mid);
+  const int cgrp = WIDE ? (int)((uint32_t)at.x / (uint32_t)nsegs) : at.x;
+  const int seg = WIDE ? at.x - cgrp * nsegs : 0, band = at.mid;
+  const int c = __builtin_amdgcn_readfirstlane(cgrp * 4 + (int)(threadIdx.x >> 6));
   if (c >= g.C) return;  // wavefront-uniform; the kernel has no barrier
   const int64_t plane = (int64_t)at.outer * g.C + c;
-  const int seg = WIDE ? at.mid % nsegs : 0;
-  const int band = WIDE ? at.mid / nsegs : at.mid;
   const int cb = WIDE ? seg * segw : 0;  // first column of the segment
   constexpr uint32_t kOob = 0x80000000u;
   constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
@@ -420,12 +421,12 @@ struct DwTile {
   int32_t groups, nt, cw;     // channel groups, column tiles, columns of a tile
   uint32_t inv_nt, inv_oh;    // ceil(2^32 / nt); ceil(2^32 / OH), 0: tiles do not run through images
   int32_t period;             // rows of the tile index per image: OH, or whole tiles if those do not run through images
-  int32_t tiles, per_wave;    // row tiles in all and per wavefront
+  int32_t per_wave, longer;   // row tiles of a wavefront (dw_split.h)
 };
 
 // NJ: groups of four columns per lane (2 or 4).
 template <int MODE, int S, int CPK, int NJ>
-__global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(DwArgs p, DwTile q) {
+__global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(uint32_t gx, uint32_t ids, uint32_t inv_x, DwArgs p, DwTile q) {
   typedef int32_t v2i __attribute__((ext_vector_type(2)));
   typedef int32_t v4i __attribute__((ext_vector_type(4)));
   typedef int32_t v16i __attribute__((ext_vector_type(16)));
@@ -433,8 +434,11 @@ __global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(DwArgs p, DwTile q
   constexpr int kEsz = MODE == 0 ? 1 : (MODE == 1 ? 4 : 2);
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
   const int C = q.C, H = q.H, W = q.W, OH = q.OH, OW = q.OW;
-  const DwPlace at = xcd_place(p, gridDim.y);  // x = groups of channels and column tiles, mid = row tiles
-  const int wi = at.x * 4 + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // runs of row tiles, in each the groups of channels and column tiles; by XCD, or, ids = 0, in launch order
+  const uint32_t launched = blockIdx.x + gx * blockIdx.y;
+  const uint32_t id = ids ? xcd_run(launched, ids) : launched;
+  const uint32_t tile_run = over(id, gx, inv_x);
+  const int wi = (int)(id - tile_run * gx) * 4 + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = q.nt > 1 ? (int)__umulhi((uint32_t)wi, q.inv_nt) : wi;
   if (grp >= q.groups) return;  // wavefront-uniform; the kernel has no barrier
   const int ct = wi - grp * q.nt;
@@ -463,8 +467,8 @@ __global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(DwArgs p, DwTile q
     uint32_t so;     // byte offset of the lane's output row
     int32_t img;
   };
-  const int tile0 = at.mid * q.per_wave;
-  const int count = q.tiles - tile0 < q.per_wave ? q.tiles - tile0 : q.per_wave;
+  const int tile0 = (int)tile_run * q.per_wave + ((int)tile_run < q.longer ? (int)tile_run : q.longer);
+  const int count = q.per_wave + ((int)tile_run < q.longer ? 1 : 0);
   int img = tile0 * 32 / q.period, y0 = tile0 * 32 - img * q.period;  // first image and row of the next tile to load
   auto load = [&](Tile& t) {
     const int64_t ibase = (int64_t)img * img_in + (int64_t)c0 * H * W;
@@ -682,7 +686,8 @@ __global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(DwArgs p, DwTile q
 // took 30.7 us; stride 2 had no kernel of its own and took 43.)  The last quad of channels and the last strip are moved
 // back to end with the pixel or row: bytes written twice get the same value.
 template <int MODE, int S>
-__global__ __launch_bounds__(kThreads) void dw_nhwc3x3_kernel(DwArgs p, int32_t c4, uint32_t inv_c4, int32_t strips, int32_t run) {
+__global__ __launch_bounds__(kThreads) void dw_nhwc3x3_kernel(uint32_t gx, uint32_t mid, uint32_t count, uint32_t inv_x, uint32_t inv_mid,
+                                                               DwArgs p, int32_t c4, uint32_t inv_c4, int32_t strips, int32_t run) {
   typedef int32_t v2i __attribute__((ext_vector_type(2)));
   typedef int32_t v4i __attribute__((ext_vector_type(4)));
   typedef uint32_t u32_u __attribute__((aligned(1)));
@@ -692,7 +697,7 @@ __global__ __launch_bounds__(kThreads) void dw_nhwc3x3_kernel(DwArgs p, int32_t 
   const ConvGeom& g = p.g;
   const int H = g.H, W = g.W, C = g.C, OH = g.OH, OW = g.OW;
   // grid: x = (strip, channel quad), y = run of rows, z = image
-  const DwPlace at = xcd_place(p, gridDim.y);
+  const DwPlace at = xcd_place(gx, mid, count, inv_x, inv_mid);
   const uint32_t t = (uint32_t)at.x * kThreads + threadIdx.x;
   const int strip = c4 > 1 ? (int)__umulhi(t, inv_c4) : (int)t;
   if (strip >= strips) return;
@@ -943,7 +948,8 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
       auto kern = s1 ? (p.out_mode == 1 ? dw_nhwc3x3_kernel<1, 1> : p.out_mode == 2 ? dw_nhwc3x3_kernel<2, 1> : dw_nhwc3x3_kernel<0, 1>)
                      : (p.out_mode == 1 ? dw_nhwc3x3_kernel<1, 2> : p.out_mode == 2 ? dw_nhwc3x3_kernel<2, 2> : dw_nhwc3x3_kernel<0, 2>);
       return launch_kernel(kern, dim3((unsigned)blocks, (unsigned)runs, (unsigned)cg.B), dim3(kThreads), 0, st,
-                         with_divisors(p, blocks, runs, cg.B), c4,
+                         (uint32_t)blocks, (uint32_t)runs, (uint32_t)(blocks * runs * cg.B), inverse(blocks, blocks * runs * cg.B),
+                         inverse(runs, runs * cg.B), p, c4,
                          c4 > 1 ? (uint32_t)(((1ull << 32) + c4 - 1) / c4) : 0u, strips, (int32_t)run);
     }
   }
@@ -962,7 +968,7 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
     int32_t segw = whole ? 64 : ((cg.W + nsegs - 1) / nsegs + 3) / 4 * 4;
     while (cg.W > 64 && segw > 12 && cg.W % segw != 0 && cg.W % segw < 4) segw -= 4;
     nsegs = (cg.W + segw - 1) / segw;
-    if (segw > 12 && nband * nsegs <= 65535) {
+    if (segw > 12 && nband * nsegs <= 65535 && (int64_t)(cg.C + 3) / 4 * nsegs <= max_blocks(kThreads)) {
 #define HAGO_DW_ROWS(WIDE_, RAG_)                                                                      \
   (p.out_mode == 1 ? dw_rows3x3_kernel<1, false, WIDE_, RAG_>                                          \
    : p.out_mode == 2 ? dw_rows3x3_kernel<2, true, WIDE_, RAG_>                                         \
@@ -970,8 +976,9 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
       auto kern = nsegs > 1 ? (ragged ? HAGO_DW_ROWS(true, true) : HAGO_DW_ROWS(true, false))
                             : (ragged ? HAGO_DW_ROWS(false, true) : HAGO_DW_ROWS(false, false));
 #undef HAGO_DW_ROWS
-      return launch_kernel(kern, dim3((unsigned)((cg.C + 3) / 4), (unsigned)cg.B, (unsigned)(nband * nsegs)),
-                         dim3(kThreads), 0, st, with_divisors(p, (cg.C + 3) / 4, nband * nsegs, cg.B), rpc, nsegs, segw);
+      const int64_t gx = (int64_t)(cg.C + 3) / 4 * nsegs, mid = nband;
+      return launch_kernel(kern, dim3((unsigned)gx, (unsigned)mid, (unsigned)cg.B), dim3(kThreads), 0, st, (uint32_t)gx, (uint32_t)mid,
+                         (uint32_t)(gx * mid * cg.B), inverse(gx, gx * mid * cg.B), inverse(mid, mid * cg.B), p, rpc, nsegs, segw);
     }
   }
   // NCHW on the matrix cores
@@ -993,22 +1000,20 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
     q.period = flat ? cg.OH : (cg.OH + 31) / 32 * 32;
     q.inv_oh = flat ? (uint32_t)(((1ull << 32) + cg.OH - 1) / cg.OH) : 0u;
     const int64_t tiles = ((int64_t)cg.B * q.period + 31) / 32, waves_x = (int64_t)q.groups * q.nt;
-    // Row tiles per wavefront: as many as leave 2.5 wavefronts per SIMD (a wavefront then has the next tile's loads under
-    // way while it computes; with half as many, or with one tile each, 32 x 288 planes of 28 x 28 took 7.7 and 8.0 us, so 6.4).
-    int64_t per = tiles * waves_x / 2560;
-    per = per < 1 ? 1 : (per > 16 ? 16 : per);
-    q.tiles = (int32_t)tiles;
-    q.per_wave = (int32_t)per;
-    const int64_t gy = (tiles + per - 1) / per;
-    if (tiles < (1ll << 26) && gy <= 65535 && waves_x * q.nt < (1ll << 32) && (waves_x + 3) / 4 <= max_blocks(kThreads) &&
+    const int64_t gx = (waves_x + 3) / 4;
+    const DwSplit split = dw_split(gx, waves_x, tiles);
+    const int64_t gy = split.runs;
+    q.per_wave = split.per;
+    q.longer = split.longer;
+    if (tiles < (1ll << 26) && gy <= 65535 && waves_x * q.nt < (1ll << 32) && gx <= max_blocks(kThreads) &&
         (flat || ((int64_t)cg.H * cg.W * 2 < (1ll << 31) && (int64_t)cg.OH * cg.OW * 2 * (int64_t)esz < (1ll << 31)))) {
 #define HAGO_DW_MODE(S_, CPK_, NJ_) \
   (p.out_mode == 1 ? dw_mfma_kernel<1, S_, CPK_, NJ_> : p.out_mode == 2 ? dw_mfma_kernel<2, S_, CPK_, NJ_> : dw_mfma_kernel<0, S_, CPK_, NJ_>)
       auto kern = S == 2 ? (two ? HAGO_DW_MODE(2, 2, 2) : HAGO_DW_MODE(2, 1, 2))
                          : (!two ? HAGO_DW_MODE(1, 1, 4) : cg.OW > 8 ? HAGO_DW_MODE(1, 2, 4) : HAGO_DW_MODE(1, 2, 2));
 #undef HAGO_DW_MODE
-      return launch_kernel(kern, dim3((unsigned)((waves_x + 3) / 4), (unsigned)gy), dim3(kThreads), 0, st,
-                         with_divisors(p, (waves_x + 3) / 4, gy, 1), q);
+      return launch_kernel(kern, dim3((unsigned)gx, (unsigned)gy), dim3(kThreads), 0, st, (uint32_t)gx, split.by_xcd ? (uint32_t)(gx * gy) : 0u,
+                         inverse(gx, gx * gy), p, q);
     }
   }
   const int64_t blocks = (total + kThreads - 1) / kThreads;
