@@ -1,4 +1,5 @@
 import os
+import re
 import sys
 
 import pytest
@@ -31,6 +32,31 @@ def ref():
     hago_ref.build()
     hago_ref.lib()
     return hago_ref
+
+
+def build_against_fake_runtime(source, exe):
+    """A program that loads the library as built and stands in for the HIP runtime (tests/fake_runtime.h)."""
+    import subprocess
+    from paper_2103_14949_amd import build
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-Wall", "-Werror", "-isystem", os.path.join(rocm, "include"),
+                    "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", source), "-rdynamic", build.LIB,
+                    f"-Wl,-rpath,{os.path.dirname(build.LIB)}", f"-Wl,-rpath-link,{rocm}/lib", f"-Wl,-rpath,{rocm}/lib", "-o", exe], check=True)
+
+
+@pytest.fixture(scope="session")
+def routes(tmp_path_factory):
+    """Calls (lines of tests/routes_driver.cpp) -> the kernels that serve each, on the CPU."""
+    import subprocess
+    exe = str(tmp_path_factory.mktemp("routes") / "routes")
+    build_against_fake_runtime("routes_driver.cpp", exe)
+
+    def kernels(calls):
+        r = subprocess.run([exe], input="".join(c + "\n" for c in calls), capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return [[re.sub(r"^void |hago::|\(anonymous namespace\)::|\(.*$| ", "", k.split("(", 2)[0] + k.split(")::", 1)[1]) for k in line.split("\t")[:-1]]
+                for line in r.stdout.splitlines()]
+    return kernels
 
 
 @pytest.fixture(params=["plain", "ws", "ws_stream"])

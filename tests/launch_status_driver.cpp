@@ -1,51 +1,17 @@
-// What every entry point says of a runtime that refuses.  This program stands in for the calls of the HIP runtime that the
-// library makes (its own definitions come first in the symbol lookup), counts them, and refuses the one it is told to, as the
-// runtime does: the status is returned and stays behind as the thread's last error until somebody asks for it, whatever
-// succeeds in between.  Nothing runs and no GPU is needed.
-//
-// Of each call of the library: with nothing refused it is fine, also where an earlier error of somebody else's is pending,
-// which stays theirs; with any one of its calls refused it reports the device, makes no further launch, and leaves no error
-// behind for the next caller.
-#define __HIP_PLATFORM_AMD__
-#include <hip/hip_runtime_api.h>
+// What every entry point says of a runtime that refuses.  Of each call of the library: with nothing refused it is fine, also where an
+// earlier error of somebody else's is pending, which stays theirs; with any one of its calls refused it reports the device, makes no
+// further launch, and leaves no error behind for the next caller.
+#include "fake_runtime.h"
 
 #include <cstdio>
-#include <cstdlib>
 #include <functional>
 #include <string>
 
 #include "hago.h"
 
-namespace {
-int calls = 0, refused = -1, launches_after = 0;
-hipError_t pending = hipSuccess;
-alignas(256) char scratch[256];
-
-hipError_t answer(bool launch) {
-  if (refused >= 0 && calls > refused && launch) ++launches_after;
-  if (calls++ != refused) return hipSuccess;
-  return pending = hipErrorLaunchFailure;
-}
-}  // namespace
-
-extern "C" {
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return answer(true); }
-hipError_t hipGetLastError() {
-  const hipError_t e = pending;
-  pending = hipSuccess;
-  return e;
-}
-hipError_t hipPeekAtLastError() { return pending; }
-hipError_t hipGetDevice(int* device) { *device = 0; return answer(false); }
-hipError_t hipGetDeviceCount(int* count) { *count = 2; return hipSuccess; }
-hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return answer(false); }
-hipError_t hipGetSymbolAddress(void** at, const void*) { *at = scratch; return answer(false); }
-}
+using namespace fake;
 
 namespace {
-
-template <typename T = void>
-T* at(int n) { return reinterpret_cast<T*>((uintptr_t)(n + 1) << 28); }   // never read
 
 const hago_qtype u8{HAGO_U8, 8, 0, 128}, i8{HAGO_I8, 8, 1, 0}, i16{HAGO_I16, 16, 1, -11};
 const hago_requant rq{at<int32_t>(8), at<int32_t>(9), 1, {HAGO_I8, 8, 1, 0}, -128, 127, HAGO_ROUND_UPWARD};

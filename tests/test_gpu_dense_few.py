@@ -42,13 +42,35 @@ def test_ends_of_blocks(KB, form, gemm_path):
         hago.set_test_hook(hago.HOOK_GENERAL_TILE, -1)
 
 
-@pytest.mark.parametrize("M,K,N", [(512, 65, 1024), (513, 640, 1024), (1000, 64, 1000), (257, 512, 7168), (1025, 1280, 1000), (30, 100, 57350)])
-def test_lines_to_the_larger_tiles(M, K, N):
-    """On both sides of the numbers of tiles at which another kernel takes over; the results of some rows and channels."""
+# Layers on both sides of each line between this kernel and the larger tiles (tests/test_dense_routes.py): type, rows, reduction,
+# channels, bytes into a buffer
+FEW = [
+    ("i8", 512, 768, 1024, 0), ("i8", 544, 80, 992, 0), ("i8", 544, 640, 992, 0), ("i8", 1024, 640, 1024, 0),       # whole chunks
+    ("i8", 544, 640, 992, 4), ("u8", 1024, 511, 2048, 0), ("i8", 1056, 511, 1024, 0), ("u8", 1024, 767, 1024, 0), ("i8", 1024, 768, 1024, 1),
+    ("u8", 7200, 926, 66, 0), ("i8", 20, 1001, 16500, 0), ("u8", 65536, 100, 20, 0),                                  # narrow
+    ("i16", 512, 300, 1024, 0),
+]
+OTHERS = [
+    ("i8", 544, 768, 992, 0), ("i8", 544, 64, 992, 0), ("i8", 544, 656, 992, 0), ("i8", 1025, 640, 1024, 0),
+    ("i8", 1056, 640, 1024, 4), ("u8", 1025, 511, 2048, 0), ("i8", 1056, 513, 1024, 0), ("u8", 1024, 769, 1024, 0), ("i8", 1056, 528, 1024, 1),
+    ("u8", 7200, 926, 98, 0), ("u8", 7200, 1025, 66, 0), ("u8", 65537, 100, 20, 0),
+    ("i16", 544, 300, 992, 0),
+]
+
+
+@pytest.mark.parametrize("act,M,K,N,offset", FEW + OTHERS)
+def test_lines_to_the_larger_tiles(act, M, K, N, offset):
+    """The results of some rows and channels, the last ones among them."""
     rng = np.random.default_rng(M + K)
-    a, w = rng.integers(-128, 128, (M, K)).astype(np.int8), rng.integers(-128, 128, (N, K)).astype(np.int8)
-    for cut_m, cut_n in ((0, 0), (1, 0), (0, 8), (M // 2, 0)):
-        got = host(hago.qdense(dev(a[cut_m:]), hago.QType(hago.I8, 8, True, 3), dev(w[cut_n:]), hago.QType(hago.I8)))
-        rows, cols = rng.integers(0, M - cut_m, 40), rng.integers(0, N - cut_n, 40)
-        rows[0], cols[0] = M - cut_m - 1, N - cut_n - 1
-        assert_same(got[np.ix_(rows, cols)], ref.qdense(a[cut_m:][rows], 3, w[cut_n:][cols], None, ref.I32, None), f"{cut_m, cut_n}")
+    dtype, top = {"u8": (np.uint8, 256), "i8": (np.int8, 128), "i16": (np.int16, 32768)}[act]
+    a = rng.integers(0 if act == "u8" else -top, top, (M, K)).astype(dtype)
+    w = rng.integers(-32768 if act == "i16" else -128, 32768 if act == "i16" else 128, (N, K)).astype(np.int16 if act == "i16" else np.int8)
+    a_t, w_t = (hago.QType(hago.I16, 16, True, 3), hago.QType(hago.I16, 16, True, 0)) if act == "i16" else (act_qtype(a, 3), hago.QType(hago.I8))
+    mult, shift = rng.integers(2 ** 30, 2 ** 31, N, dtype=np.int64).astype(np.int32), rng.integers(8, 15, N).astype(np.int32)
+    rows, cols = rng.integers(0, M, 40), rng.integers(0, N, 40)
+    rows[:2], cols[:2] = (M - 1, M - 2), (N - 1, N - 2)
+    rr = ref_requant(mult[cols], shift[cols])
+    da, dw = inside(a, offset), dev(w)
+    assert_same(host(hago.qdense(da, a_t, dw, w_t))[np.ix_(rows, cols)], ref.qdense(a[rows], 3, w[cols], None, ref.I32, None), "raw")
+    got = host(hago.qdense(da, a_t, dw, w_t, None, hago.I32, gpu_requant(mult, shift)))
+    assert_same(got[np.ix_(rows, cols)], ref.qdense(a[rows], 3, w[cols], None, ref.I32, rr), "requantized")
