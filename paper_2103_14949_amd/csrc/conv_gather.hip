@@ -646,11 +646,8 @@ hipError_t launch_nchw(const CnParams& p, int mode, hipStream_t st) {
 
 }  // namespace
 
-namespace {
-
-struct Times { double t64, t32, other; int64_t tiles64; };
-
-Times estimate(const GemmArgs& a, const ConvGeom& cg, bool has_workspace) {
+const GatherTimes& qconv_gather_times(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, GatherTimes& times) {
+  if (times.t64 >= 0) return times;
   const int32_t steps = (cg.KH * cg.KW * ((cg.C + 15) / 16) + 1) / 2;
   // Microseconds, fitted to 333 layers drawn at random (over 333 others the kernel so chosen is 2.5 % from the best on average,
   // half as long again in the worst).  Here: a start, and per tile of a CU 2.2 and 0.075 a step for 64 x 64, of which a CU has whole rounds up to the third and several side by side
@@ -669,19 +666,13 @@ Times estimate(const GemmArgs& a, const ConvGeom& cg, bool has_workspace) {
   const double rate = (double)a.M * a.N * a.K / 0.41e9, length = (double)a.K / 175;
   const double steps_and_rate = rate > length ? rate + 0.8 * length : length + 0.8 * rate;
   const double other = (5.9 + steps_and_rate) * (cg.C % 4 && !has_workspace ? 1.2 : 1.0) + bytes / 4e6;
-  return {t64, t32, other, tiles(64)};
-}
-
-}  // namespace
-
-double qconv_gather_estimate(const GemmArgs& a, const ConvGeom& cg, bool has_workspace) {
-  const Times e = estimate(a, cg, has_workspace);
-  return std::fmin(std::fmin(e.t64, e.t32), e.other);
+  times = GatherTimes{t64, t32, other, tiles(64)};
+  return times;
 }
 
 // Returns false (and launches nothing) when the geometry is not this kernel's, or another kernel is the better one.
 // forced_shape: 0 64 pixels x 64 output channels by four wavefronts, 1 the same by eight, 2 32 x 32 by four; -1 by size.
-bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err) {
+bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int forced_shape, GatherTimes& times, hipStream_t st, hipError_t* err) {
   const int64_t act_bytes = (int64_t)cg.B * cg.C * cg.H * cg.W, wgt_bytes = (int64_t)cg.O * a.K;
   if (!cg.nhwc || cg.C < 16 || cg.KH > 32 || cg.KW > 32 || act_bytes >= (1ll << 31) || wgt_bytes >= (1ll << 31)) return false;
   CgParams p{};
@@ -712,7 +703,7 @@ bool try_qconv_gather(const GemmArgs& a, const ConvGeom& cg, bool has_workspace,
   const int mode = a.has_rq ? 0 : (a.acc16 ? 2 : 1);
   int shape = forced_shape;
   if (shape < 0) {
-    const Times e = estimate(a, cg, has_workspace);
+    const GatherTimes& e = qconv_gather_times(a, cg, has_workspace, times);
     if ((e.t64 < e.t32 ? e.t64 : e.t32) >= e.other) return false;
     shape = e.t32 < e.t64 ? 2 : e.tiles64 <= 256;  // (eight wavefronts fill a CU's LDS)
   }

@@ -147,9 +147,15 @@ bool is_qconv3x3_nchw(const ConvGeom& cg);
 // geometry is not that kernel's (nothing is launched then).
 bool try_qconv_direct(const GemmArgs& g, const ConvGeom& cg, int forced_shape, hipStream_t st, hipError_t* err);
 // Channel-last convolution of 16 or more channels, operands straight from memory to registers; false: not its geometry.
-bool try_qconv_gather(const GemmArgs& g, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err);
-// The least of the times that kernel and those behind it would take, as its own choice sees them (us).
-double qconv_gather_estimate(const GemmArgs& g, const ConvGeom& cg, bool has_workspace);
+struct GatherTimes;
+bool try_qconv_gather(const GemmArgs& g, const ConvGeom& cg, bool has_workspace, int forced_shape, GatherTimes& times, hipStream_t st, hipError_t* err);
+// What the call would take (us) with that kernel's tiles of 64 x 64 and of 32 x 32, and with the kernels behind it; worked out by
+// the first who asks.
+struct GatherTimes {
+  double t64 = -1, t32, other;
+  int64_t tiles64;
+};
+const GatherTimes& qconv_gather_times(const GemmArgs& g, const ConvGeom& cg, bool has_workspace, GatherTimes& times);
 // The same for NCHW, any channel count, and channel-last of fewer channels.  has_workspace: the caller has one for the other kernels.
 bool try_qconv_gather_nchw(const GemmArgs& g, const ConvGeom& cg, bool has_workspace, int forced_shape, hipStream_t st, hipError_t* err);
 // 1x1 stride-1 unpadded NCHW convolution straight from the caller's buffers; false when the

@@ -39,6 +39,7 @@
 // so that fragment reads and staging writes spread over all banks.
 #include "qgemm_any.h"
 
+#include <algorithm>
 
 namespace hago {
 
@@ -546,7 +547,7 @@ static bool is_dense_nhwc(const ConvGeom& cg) {
 
 // Channel-last convolution whose taps are whole 16-byte chunks, streamed from the caller's tensors; false: not its geometry, or
 // another kernel is the better one.  shape: 0 tiles of 64 pixels, 1 of 128 (64 output channels each), -1 by size.
-static bool try_qconv_stream(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int shape, hipStream_t st, hipError_t* err) {
+static bool try_qconv_stream(const GemmArgs& a, const ConvGeom& cg, bool has_workspace, int shape, GatherTimes& times, hipStream_t st, hipError_t* err) {
   const int64_t act_bytes = (int64_t)cg.B * cg.H * cg.W * cg.C, taps = (int64_t)cg.KH * cg.KW;
   // (32-bit offsets, and divisions by multiplication: exact while k C and tap KW stay below 2^32, a stage beyond K included)
   if (!cg.nhwc || cg.C % 16 != 0 || act_bytes >= (1ll << 31) || (int64_t)a.N * a.K >= (1ll << 31) ||
@@ -576,7 +577,8 @@ static bool try_qconv_stream(const GemmArgs& a, const ConvGeom& cg, bool has_wor
     };
     const double t64 = time(64, 3.8, {{0.00252, 0.0024}, {0.00515, 0.0049}}, 1.02, 0.00152);
     const double t128 = time(128, 4.62, {{0.00387, 0.00331}, {0.00624, 0.00575}}, 2.0, 0.00211);
-    if ((t64 < t128 ? t64 : t128) * (flip ? 1.12 : 1.05) >= qconv_gather_estimate(a, cg, has_workspace)) return false;
+    const GatherTimes& e = qconv_gather_times(a, cg, has_workspace, times);
+    if (std::min(t64, t128) * (flip ? 1.12 : 1.05) >= std::min({e.t64, e.t32, e.other})) return false;
     shape = t128 < t64;
   }
   *err = launch_qconv_dma_direct(p, shape, st);
@@ -596,12 +598,13 @@ static hipError_t launch_qconv_chosen(const GemmArgs& a, const ConvGeom& cg, voi
   }
   const int tile = g_hook[kHookGenericTile].load(std::memory_order_relaxed);
   if (path == 3 && try_qconv_direct(a, cg, tile, st, &err)) return err;
-  if (path == 5 && try_qconv_stream(a, cg, ws != nullptr, tile < 0 ? 0 : tile, st, &err)) return err;
-  if (path == 4 && try_qconv_gather(a, cg, ws != nullptr, tile < 0 ? 0 : tile, st, &err)) return err;
+  GatherTimes times;
+  if (path == 5 && try_qconv_stream(a, cg, ws != nullptr, tile < 0 ? 0 : tile, times, st, &err)) return err;
+  if (path == 4 && try_qconv_gather(a, cg, ws != nullptr, tile < 0 ? 0 : tile, times, st, &err)) return err;
   if (path == 4 && try_qconv_gather_nchw(a, cg, ws != nullptr, tile < 0 ? 0 : tile, st, &err)) return err;
   if (path == 0 && try_qconv_gather_nchw(a, cg, ws != nullptr, -1, st, &err)) return err;
-  if (path == 0 && try_qconv_stream(a, cg, ws != nullptr, -1, st, &err)) return err;
-  if (path == 0 && try_qconv_gather(a, cg, ws != nullptr, -1, st, &err)) return err;
+  if (path == 0 && try_qconv_stream(a, cg, ws != nullptr, -1, times, st, &err)) return err;
+  if (path == 0 && try_qconv_gather(a, cg, ws != nullptr, -1, times, st, &err)) return err;
   if (ws && path != 1 && qconv_workspace_bytes(cg) >= 0) {
     // The rewrite through the workspace costs a launch and the copy's traffic; staging the weights in every
     // workgroup costs the one-launch kernel more the longer the reduction is (us with workspace, one launch):
