@@ -22,7 +22,7 @@ namespace hago {
 
 namespace {
 
-constexpr int kBlock = 128;                      // bytes of a row that a wavefront takes at a time
+constexpr int kBlock = (int)kRunBlock;           // bytes of a row that a wavefront takes at a time
 constexpr int kDepth = 2;                        // such blocks that it has under way
 constexpr int kPitch = 576;                      // LDS bytes of the partial sums of four channels (32 rows): no bank conflicts either way
 
@@ -30,7 +30,7 @@ template <bool MIS>
 constexpr int slot_bytes() { return 64 * kBlock + (MIS ? 512 : 0); }
 
 // Eight rows of a block per load, four loads per value of m0: window i takes the instruction offset i KB, which counts on both
-// sides (the lane offsets take it back, stream_run_offset).
+// sides (the lane offsets take it back, run_offset).
 __device__ __forceinline__ void load_run(const v4i& r, uint32_t lds_addr, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3) {
   asm volatile(
       "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
@@ -74,18 +74,15 @@ __global__ __launch_bounds__(64 * NW, 2) void qgemm_few_kernel(const uint8_t* ac
   // the lane's offsets: rows 8 i + lane / 8 of either operand; MIS: of the dwords behind a block, row lane % 32
   uint32_t off_w[4], off_a[4], more_w = 0, more_a = 0;
   {
-    const uint32_t lrow = (uint32_t)lane >> 3, rows = lrow * KB, base_w = n0 * KB + w_at, base_a = m0 * KB + a_at;
-    const uint32_t chunk = (((uint32_t)lane & 7u) ^ (lrow >> 1)) * 16;  // of even groups of eight rows; of odd ones chunk ^ 64
+    const uint32_t base_w = n0 * KB + w_at, base_a = m0 * KB + a_at;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t c = i & 1 ? chunk ^ 64u : chunk, k = kRunBack - kRunStep * (uint32_t)i, r8 = (uint32_t)(8 * i) * KB;
-      off_w[i] = MIS ? ((rows + (base_w + r8)) & ~3u) + c + k : rows + c + (base_w + r8 + k);
-      off_a[i] = MIS ? ((rows + (base_a + r8)) & ~3u) + c + k : rows + c + (base_a + r8 + k);
+      off_w[i] = run_offset(base_w, KB, (uint32_t)lane, i, MIS);
+      off_a[i] = run_offset(base_a, KB, (uint32_t)lane, i, MIS);
     }
     if constexpr (MIS) {
-      const uint32_t row = ((uint32_t)lane & 31u) * KB;
-      more_w = ((row + base_w) & ~3u) + (kRunBack + kBlock);
-      more_a = ((row + base_a) & ~3u) + (kRunBack + kBlock);
+      more_w = run_behind_offset(base_w, KB, (uint32_t)lane);
+      more_a = run_behind_offset(base_a, KB, (uint32_t)lane);
     }
   }
   auto issue = [&](int b, int slot) {
@@ -327,10 +324,7 @@ hipError_t launch_qgemm_few(const QgemmParams& p, bool i16, int waves, hipStream
   const bool channels_first = p.M >= p.N;  // an XCD's run of tiles keeps the longer operand's rows
   const int64_t minor = channels_first ? tiles_n : tiles_m;
   const uint32_t inv = minor > 1 ? (uint32_t)(((1ull << 32) + minor - 1) / minor) : 0u;
-  auto size = [&](const void* ptr, int64_t rows) {
-    const int64_t at = (int64_t)(reinterpret_cast<uintptr_t>(ptr) & 3);
-    return (uint32_t)((rows * kb + at + 3) & ~(int64_t)3);
-  };
+  auto size = [&](const void* ptr, int64_t rows) { return run_size(rows, kb, (uint32_t)(reinterpret_cast<uintptr_t>(ptr) & 3)); };
   auto run = [&]<bool I16, bool MIS, int NW>() {
     const int slots = blocks < kDepth * NW ? blocks : kDepth * NW;
     const auto kern = qgemm_few_kernel<I16, MIS, NW>;
