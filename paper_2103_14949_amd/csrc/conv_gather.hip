@@ -72,12 +72,7 @@ __global__ __launch_bounds__(64 * KS) void conv_gather_kernel(CgParams p) {
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // consecutive tiles share pixels (and their neighbours' rows): an XCD gets a run of them
-  uint32_t id;
-  {
-    const uint32_t nt = gridDim.x, x = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const uint32_t qn = nt >> 3, rn = nt & 7;
-    id = x * qn + (x < rn ? x : rn) + slot;
-  }
+  const uint32_t id = xcd_run(blockIdx.x, gridDim.x);
   const uint32_t tile_m = div_by(id, (uint32_t)p.tiles_n, p.inv_tn);
   const int m0 = (int)tile_m * 32 * TP, n0 = (int)(id - tile_m * (uint32_t)p.tiles_n) * 32 * TC;
 

@@ -83,12 +83,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
   // 128-byte line in general, so neighbouring tiles share lines, and the blocks of output channels of a tile share its
   // input; numbering them so that an XCD gets a run of consecutive ones lets that XCD's L2 serve the shared lines (with
   // the plain order every such line was fetched from memory by two XCDs: 1.5 times the bytes).
-  uint32_t id;
-  {
-    const uint32_t nt = gridDim.x, x = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const uint32_t qn = nt >> 3, rn = nt & 7;
-    id = x * qn + (x < rn ? x : rn) + slot;
-  }
+  const uint32_t id = xcd_run(blockIdx.x, gridDim.x);
   const uint32_t tile = p.inv_nb ? __umulhi(id, p.inv_nb) : id / (uint32_t)p.nblocks;
   const int blk0 = (int)(id - tile * (uint32_t)p.nblocks) * p.per_wave;
   const int b = (int)(p.inv_tpi ? __umulhi(tile, p.inv_tpi) : tile / (uint32_t)p.tiles_per_img);

@@ -210,7 +210,7 @@ __global__ __launch_bounds__(64 * WP * WQ) void qgemm_kernel(QgemmParams p) {
 
   const int P_ext = ACT_ON_P ? p.M : p.N;
   const int tiles_p = (P_ext + BP - 1) / BP;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = (int)xcd_run(blockIdx.x, gridDim.x);
   const int tile_p = tile % tiles_p;
   const int tile_q = tile / tiles_p;
   const int p0 = tile_p * BP;

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
   const int wp = wave % WP, wq = wave / WP % WQ, kset = wave / (WP * WQ);
   const int frow = lane & 31, fhalf = lane >> 5;
   const int tiles_p = (p.N + BP - 1) / BP;
-  const int tile = p.tile0 + xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = p.tile0 + (int)xcd_run(blockIdx.x, gridDim.x);
   const int tile_q = tile / tiles_p;
   const int p0 = (tile - tile_q * tiles_p) * BP, q0 = tile_q * BQ;
 

@@ -92,14 +92,6 @@ inline bool ptr_aligned(const void* ptr, size_t n) {
 }
 inline size_t qgemm_out_elem_size(const GemmArgs& a) { return a.has_rq ? 1 : (a.acc16 ? 2 : 4); }
 
-// Workgroups are handed to the 8 XCDs round-robin; remap so that the tiles an
-// XCD works on are consecutive (they then share operand panels in its L2).
-__device__ __forceinline__ int xcd_remap(int bid, int ntiles) {
-  const int x = bid & 7, slot = bid >> 3;
-  const int q = ntiles >> 3, r = ntiles & 7;
-  return x * q + (x < r ? x : r) + slot;
-}
-
 // Turn the weight row sums that sit in s_corr[0..CH) into the per-channel
 // terms of the tile: corr = bias + (off - z_a) * sum_k w, multiplier, shift.
 // Channels beyond N get zeros.  Ends with a barrier.

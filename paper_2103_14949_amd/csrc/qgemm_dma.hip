@@ -119,7 +119,7 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
   const int P_ext = ACT_ON_P ? p.M : p.N;
   const int Q_ext = ACT_ON_P ? p.N : p.M;
   const int tiles_p = (P_ext + BP - 1) / BP;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = (int)xcd_run(blockIdx.x, gridDim.x);
   int tile_p, tile_q;
   panel_tile(tile, tiles_p, (Q_ext + BQ - 1) / BQ, tile_p, tile_q);
   const int p0 = tile_p * BP;  // first P row of the tile

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(64 * WP * WQ, 1) void qgemm_line_kernel(QgemmParams
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wp = wave % WP, wq = wave / WP;
   int tile_p, tile_q;
-  panel_tile(xcd_remap(blockIdx.x, gridDim.x), (p.N + BP - 1) / BP, (p.M + BQ - 1) / BQ, tile_p, tile_q);
+  panel_tile((int)xcd_run(blockIdx.x, gridDim.x), (p.N + BP - 1) / BP, (p.M + BQ - 1) / BQ, tile_p, tile_q);
   const int p0 = tile_p * BP, q0 = tile_q * BQ;
 
   const v4i rs_w = make_rsrc(p.wgt, (uint32_t)p.N * (uint32_t)p.K);
