@@ -1,7 +1,8 @@
 """GPU parity of the channel-last convolution that streams the caller's tensors into LDS, in every tile shape, against the
 oracle: reductions that end inside a stage, stages that hold one tap and several, filters that hang over every edge and lie
-outside the image altogether, images of which a tile holds several, channel and pixel counts off the tile, zero points that do
-and do not equal the zeros that loads out of range leave."""
+outside the image altogether, images of which a tile holds several and images too large for a pixel's place in one to be a
+multiplication, channel and pixel counts off the tile, zero points that do and do not equal the zeros that loads out of range
+leave, before the flip and behind it."""
 import numpy as np
 import pytest
 
@@ -24,6 +25,7 @@ CASES = [
     (40, 192, 1, 3, 20, 3, 3, (1, 1), (1, 1)),      # tiles of many images
     (70, 64, 1, 1, 20, 1, 1, (1, 1), (1, 1)),
     (1, 112, 17, 19, 64, 7, 7, (2, 2), (3, 3)),
+    (1, 16, 1, 65540, 5, 1, 3, (1, 1), (0, 1)),     # 2^32 and more: pixels times pixels of an image, and of a row
 ]
 
 
@@ -39,7 +41,7 @@ def test_streamed_convolution(case, shape, gemm_path):
     gemm_path(5)
     hago.set_test_hook(hago.HOOK_GENERAL_TILE, shape)
     try:
-        for adt, za in ((np.uint8, 131), (np.uint8, 0), (np.int8, 0), (np.int8, -5)):
+        for adt, za in ((np.uint8, 131), (np.uint8, 128), (np.uint8, 0), (np.int8, 0), (np.int8, -5)):
             a = (rng.integers(0, 256, (B, H, W, C)) if adt == np.uint8 else rng.integers(-128, 128, (B, H, W, C))).astype(adt)
             a_t, da, dw = act_qtype(a, za), dev(a), dev(w)
             if za == 0:
