@@ -463,11 +463,11 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
   const auto tiles = [&](int bp, int bq) { return (int64_t)((a.N + bp - 1) / bp) * ((a.M + bq - 1) / bq); };
   const double raw = a.has_rq ? 0 : a.acc16 ? 2.7e-5 : 5.5e-5;  // per result of a tile
   // Long reductions on few 64 x 64 tiles are a chain of stages: with 128-byte ones, which two workgroups on a CU have room
-  // for, 1024 x 2048 -> 1024 takes 6.65 (7.5), 1500 x 2688 -> 128 7.4 (8.4), 500 x 4096 -> 1024 11.4 (16.5), 1024 x 768 ->
-  // 768 4.8 (5.0).  Where K ends inside a stage every lane works out its addresses; K % 128 = 64, which 64-byte stages
-  // do not know as a tail, is theirs: 1000 x 2880 -> 512 10.3 (9.2), 1000 x 4032 -> 512 12.4 (11.3), 300 x 3008 -> 1024 10.4
-  // (9.3); of the other K the longer ones are not: 357 x 3488 -> 720 11.9 (12.5), 3352 x 2272 -> 96 9.0 (9.4), but 768 x 1904 ->
-  // 1088 8.3 (8.4), 463 x 928 -> 1520 6.6 (6.3).
+  // for, 1024 x 2048 -> 1024 takes 6.65 (7.5), 1239 x 3072 -> 1451 13.2 (16.2), 1995 x 1664 -> 468 6.4 (7.0), 204 x 3328 -> 3149
+  // raw 9.3 (12.9), 1024 x 768 -> 768 4.8 (5.0).  Where K ends inside a stage every lane works out its addresses; K % 128 = 64,
+  // which 64-byte stages do not know as a tail, is theirs: 722 x 1088 -> 2122 7.5 (6.9), 2599 x 1600 -> 208 7.5 (6.9), 2426 x
+  // 2368 -> 277 9.2 (8.2); of the other K the longer ones are not: 784 x 3344 -> 1044 11.6 (15.1), 1418 x 2448 -> 546 8.9 (10.7),
+  // 3272 x 2464 -> 284 11.0 (10.9), but 768 x 1904 -> 1088 8.3 (8.4), 463 x 928 -> 1520 6.6 (6.3).
   const double rounds64 = (double)((tiles(64, 64) + 255) / 256);
   const bool wide64 = rounds64 <= 2 && a.K >= 768 && (a.K % 128 == 0 || (a.K % 64 != 0 && a.K >= 2048));
   double best_cost = rounds64 * (0.3 + 0.0023 * a.K);
