@@ -42,8 +42,8 @@ struct DwArgs {
 // The work of a launch of gx * mid * outer workgroups, the outermost index first: images, in all three kernels, so
 // that each keeps to the XCD that its neighbours in a network of 1x1 layers use for it.  Us of an expansion, a depthwise
 // layer and a projection, with the workgroups in launch order (an image's channels on all XCDs) and so, buffers kept
-// and three sets of them in turn: 24 -> 144 -> 24 on 8 x 56 x 56 14.0, 11.9 and 15.0, 13.0; on 32 x 56 x 56 29.9, 22.2 and 23.3,
-// 23.3 (14 MB between the layers: rewriting lines that other XCDs still hold is what cost the first).
+// and three sets of them in turn: 24 -> 144 -> 24 on 8 x 56 x 56 14.2, 12.0 and 14.5, 11.9; on 32 x 56 x 56 29.9, 22.5 and 23.8,
+// 23.8 (14 MB between the layers: rewriting lines that other XCDs still hold is what cost the first).
 // What a workgroup finds its place by comes as the kernel's leading arguments, which are in scalar registers when it starts: from
 // behind the others, where the launch's own dimensions are too, it took 0.1 to 0.2 us of a layer.
 struct DwPlace { int32_t x, mid, outer; };

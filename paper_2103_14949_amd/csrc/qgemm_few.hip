@@ -298,10 +298,10 @@ bool qgemm_few_ok(const QgemmParams& p, bool i16) {
 // the loads', are faster here; the lines lie higher for rows of no whole 16 bytes, whose other kernel is the slower one, more so
 // where a quarter or half of its 64 x 64 tiles is empty, and int16 has none (four products for one).  Over 600 layers of other rows and more
 // than 512 tiles the kernel so chosen is 1.2 % from the better one.  Us, here and there:
-//   aligned   256 x 768 -> 768 3.1, 4.5; 128 x 3072 -> 768 4.3, 7.7; 512 x 768 -> 768 3.8, 4.55; 986 x 2880 -> 377 6.8, 8.85;
+//   aligned   256 x 768 -> 768 3.1, 4.5; 128 x 3072 -> 768 4.5, 7.8; 512 x 768 -> 768 3.8, 4.55; 986 x 2880 -> 377 6.8, 8.85;
 //             972 x 640 -> 759 4.55, 4.8; 1097 x 208 -> 859 3.9, 4.3; but 12465 x 64 -> 50 4.0, 3.4, 12754 x 800 -> 61 6.6, 6.1,
 //             1854 x 3072 -> 296 9.2, 8.2, 324 x 64 -> 3208 4.5, 3.8
-//   others    512 x 1283 -> 512 4.5, 8.7; 700 x 333 -> 700 3.65, 5.4; 720 x 2163 -> 366 7.8, 10.9; 373 x 471 -> 2901 6.4, 7.9;
+//   others    512 x 1283 -> 512 4.75, 9.05; 700 x 333 -> 700 3.65, 5.4; 720 x 2163 -> 366 7.8, 10.9; 373 x 471 -> 2901 6.4, 7.9;
 //             52673 x 180 -> 4 5.8, 7.85; 5 x 515 -> 16859 4.5, 7.3; 11 x 2853 -> 21142 13.7, 22.7; 7225 x 926 -> 66 raw 7.0, 8.0; but
 //             118 x 1769 -> 4294 10.2, 9.7, 20680 x 1023 -> 61 12.2, 10.15, 1481 x 740 -> 1272 9.9, 8.5, 1307 x 1272 -> 433 8.35, 7.2
 //   int16     106 x 711 -> 1693 5.4, 6.2; 474 x 2000 -> 659 11.2, 14.2; 119 x 18 -> 2714 3.7, 4.55; but 3591 x 48 -> 192 5.8, 4.3
