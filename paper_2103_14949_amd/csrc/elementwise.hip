@@ -145,8 +145,9 @@ __device__ __forceinline__ float simquant_wrap_of(float u, float s, float zf, fl
 }
 
 // U: 128-bit vectors per lane and job; all of a job's loads are issued before the first
-// result is computed.  Loads and stores carry the nontemporal hint: the tensors are streamed
-// once, and without the hint the copy rate of this chip is about 10 % lower.
+// result is computed.  Loads carry the nontemporal hint (without it the copy rate of this chip is about 10 % lower), stores
+// go through the L2 (`store_through`; us, nontemporal and so: simquant of 8 x 144 x 784 3.95, 3.45, of 32 x 144 x 3136 20.0, 19.2 and with
+// its codes 23.1, 21.2; dequantize of 4096 x 768, per channel, 4.5, 3.95).
 // WRAP: the overflow-simulating form (wrap_bits, wrap_signed).
 template <int U, bool WRAP = false>
 __global__ __launch_bounds__(kThreads) void simquant_rows_kernel(
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(kThreads) void simquant_rows_kernel(
             r = v4f{of(rintf(a[u].x / s), s, zf), of(rintf(a[u].y / s), s, zf), of(rintf(a[u].z / s), s, zf),
                     of(rintf(a[u].w / s), s, zf)};
           }
-          __builtin_nontemporal_store(r, yr + vb + u * kThreads);
+          store_through(yr + vb + u * kThreads, r);
         }
       }
     }
@@ -202,7 +203,7 @@ struct CandidateClips {
   float lo[kMaxCandidates], hi[kMaxCandidates];
 };
 
-template <int U>
+template <int U, bool THROUGH>
 __global__ __launch_bounds__(kThreads) void simquant_batched_rows_kernel(
     const v4f* __restrict__ x, v4f* __restrict__ y, int64_t rows, int32_t channels,
     int64_t inner_vec, int32_t nseg, int32_t seg_len, int32_t nbatch, int32_t nparam,
@@ -239,7 +240,8 @@ __global__ __launch_bounds__(kThreads) void simquant_batched_rows_kernel(
               r = v4f{simquant_one(a[u].x, s, zf, lo, hi), simquant_one(a[u].y, s, zf, lo, hi),
                       simquant_one(a[u].z, s, zf, lo, hi), simquant_one(a[u].w, s, zf, lo, hi)};
             }
-            __builtin_nontemporal_store(r, yr + b * batch_stride + vb + u * kThreads);
+            if constexpr (THROUGH) store_through(yr + b * batch_stride + vb + u * kThreads, r);
+            else __builtin_nontemporal_store(r, yr + b * batch_stride + vb + u * kThreads);
           }
         }
       }
@@ -287,7 +289,7 @@ __global__ __launch_bounds__(kThreads) void requant_rows_kernel(
       for (int u = 0; u < U; ++u) {
         if (vb + u * kThreads < v1) {
           const uint32_t r = pack4(one((int32_t)q[u].x), one((int32_t)q[u].y), one((int32_t)q[u].z), one((int32_t)q[u].w));
-          __builtin_nontemporal_store(r, orow + vb + u * kThreads);
+          store_through(orow + vb + u * kThreads, r);
         }
       }
     }
@@ -370,7 +372,7 @@ __global__ __launch_bounds__(kThreads) void quant_rows_kernel(
             unpack_codes<Q>(a[u], q);
             const v4f r = {dequantize_one(q[0], s, zf), dequantize_one(q[1], s, zf),
                            dequantize_one(q[2], s, zf), dequantize_one(q[3], s, zf)};
-            __builtin_nontemporal_store(r, yr + vb + u * kThreads);
+            store_through(yr + vb + u * kThreads, r);
           }
         }
       } else {
@@ -398,9 +400,9 @@ __global__ __launch_bounds__(kThreads) void quant_rows_kernel(
                 y = v4f{simquant_one(a[u].x, s, zf, lo, hi), simquant_one(a[u].y, s, zf, lo, hi),
                         simquant_one(a[u].z, s, zf, lo, hi), simquant_one(a[u].w, s, zf, lo, hi)};
             }
-            __builtin_nontemporal_store(r, qr + vb + u * kThreads);
+            store_through(qr + vb + u * kThreads, r);
             if constexpr (OP == 2) {
-              __builtin_nontemporal_store(y, reinterpret_cast<v4f*>(out2) + row * inner_vec + vb + u * kThreads);
+              store_through(reinterpret_cast<v4f*>(out2) + row * inner_vec + vb + u * kThreads, y);
             }
           }
         }
@@ -430,8 +432,9 @@ __device__ __forceinline__ auto load4(const T* p, int64_t i) {
   return __builtin_nontemporal_load(reinterpret_cast<const typename AnyVec<T>::T*>(p + i));
 }
 template <typename T, typename V>
-__device__ __forceinline__ void store4(T* p, int64_t i, V v) {
-  __builtin_nontemporal_store((typename AnyVec<T>::T)v, reinterpret_cast<typename AnyVec<T>::T*>(p + i));
+__device__ __forceinline__ void store4(T* p, int64_t i, V v, bool through = true) {
+  if (through) store_through(p + i, v);
+  else __builtin_nontemporal_store((typename AnyVec<T>::T)v, reinterpret_cast<typename AnyVec<T>::T*>(p + i));
 }
 
 // s, z and (RC) the reciprocal of s for fast_quotient4; without it the division is taken at once.
@@ -505,6 +508,7 @@ struct SimquantOp {
   const int32_t* zp;
   float lo, hi;
   int wrap_bits, wrap_signed;
+  bool through = true;
   __device__ Par par(int64_t c) const { return scale_zero<RC>(scale, zp, c); }
   __device__ void keep(Kept& k, const int64_t (&c)[4], bool run) const { k.read(scale, zp, c, run); }
   __device__ void four(int64_t i, Vec v, const Kept& k) const { four(i, v, k.p); }
@@ -516,7 +520,7 @@ struct SimquantOp {
   __device__ void four(int64_t i, Vec v, const Par (&p)[4]) const {
     v4f n;
     quotients4<RC>(v, p, n);
-    store4(y, i, v4f{of(n.x, p[0]), of(n.y, p[1]), of(n.z, p[2]), of(n.w, p[3])});
+    store4(y, i, v4f{of(n.x, p[0]), of(n.y, p[1]), of(n.z, p[2]), of(n.w, p[3])}, through);
   }
   __device__ void one(int64_t i, const Par& p) const { y[i] = of(rintf(x[i] / p.s), p); }
 };
@@ -533,6 +537,7 @@ struct QuantOp {
   const float* scale;
   const int32_t* zp;
   float lo, hi;
+  bool through = true;
   __device__ Par par(int64_t c) const { return scale_zero<RC && OP != 1>(scale, zp, c); }
   __device__ void keep(Kept& k, const int64_t (&c)[4], bool run) const { k.read(scale, zp, c, run); }
   __device__ void four(int64_t i, Vec v, const Kept& k) const { four(i, v, k.p); }
@@ -550,10 +555,10 @@ struct QuantOp {
       v4f n;
       quotients4<RC>(v, p, n);
       store4(static_cast<Q*>(out), i, pack_codes<Q>(quantize_of(n.x, p[0].zf, lo, hi), quantize_of(n.y, p[1].zf, lo, hi),
-                                                    quantize_of(n.z, p[2].zf, lo, hi), quantize_of(n.w, p[3].zf, lo, hi)));
+                                                    quantize_of(n.z, p[2].zf, lo, hi), quantize_of(n.w, p[3].zf, lo, hi)), OP != 2 || through);
       if constexpr (OP == 2)
         store4(out2, i, v4f{simquant_of(n.x, p[0].s, p[0].zf, lo, hi), simquant_of(n.y, p[1].s, p[1].zf, lo, hi),
-                            simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)});
+                            simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)}, through);
     }
   }
   __device__ void one(int64_t i, const Par& p) const {
@@ -757,7 +762,10 @@ inline int64_t channel_period(int64_t channels, int64_t inner) {
 inline bool periodic_split(int64_t total, int64_t channels, int64_t inner, int u, SpanArgs* g) {
   const int64_t nvec = total / 4, lv = channel_period(channels, inner);
   if (channels == 1 || nvec / lv < 4 || lv >= (1ll << 30)) return false;
-  const int64_t span = lv <= kThreads ? lv * (kThreads / lv) : lv;
+  // Spans of whole 64-byte lines (four vectors of fp32) where that keeps five eighths of the lanes: what goes through the L2 is then
+  // whole lines (65536 x 45 channel-last: quantize 5.7 -> 5.3 us, dequantize 4.3 -> 3.9; 20000 x 33, 132 lanes of 231: 3.3 -> 3.6).
+  const int64_t line = lv % 4 == 0 ? 1 : (lv % 2 == 0 ? 2 : 4), most = kThreads / lv, whole = most / line * line;
+  const int64_t span = lv <= kThreads ? lv * (8 * whole >= 5 * most ? whole : most) : lv;
   g->total = total;
   g->span = (int32_t)span;
   g->spans = (nvec + span - 1) / span;
@@ -779,7 +787,11 @@ hipError_t launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStre
   SpanArgs g;
   if (periodic_split(total, channels, inner, U, &g)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
-    return launch_kernel(periodic_kernel<OpP, U>, dim3((unsigned)wgs), dim3(kThreads), 0, st, OpP{args...}, g, d);
+    OpP op{args...};
+    // fp32 to fp32, with codes or without, in spans that end inside lines: such lines cost the write through the L2 more than it gains once 10 MB and more
+    // are read beside it (channel-last 50000 x 65 simquant 7.9 us through it, 7.2 nontemporal; 30000 x 66 4.8, 5.7)
+    if constexpr (requires { op.through; }) op.through = g.seg_len % 4 == 0 || total < 2500000;
+    return launch_kernel(periodic_kernel<OpP, U>, dim3((unsigned)wgs), dim3(kThreads), 0, st, op, g, d);
   }
   // one vector per lane while that does not fill the chip, four beyond
   const int64_t nvec = total / 4 > 0 ? total / 4 : 1;
@@ -846,7 +858,7 @@ __global__ __launch_bounds__(kThreads) void simquant_batched_ragged_kernel(
       const float lo = clips.lo[b], hi = clips.hi[b];
       store4(y + (int64_t)b * total, 4 * (v + u * step),
              v4f{simquant_of(n.x, p[0].s, p[0].zf, lo, hi), simquant_of(n.y, p[1].s, p[1].zf, lo, hi),
-                 simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)});
+                 simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)}, false);
     };
     if constexpr (PERIODIC) {
       for (int b = 0; b < nbatch; ++b) {
@@ -1206,10 +1218,14 @@ hipError_t launch_simquant_batched(const float* x, float* y, int64_t outer, int6
     constexpr int kU = 2;  // fewer vectors in flight per lane: every one is stored nbatch times
     int32_t nseg, seg_len;
     split_row(inner_vec, kU, &nseg, &seg_len);
-    return launch_kernel(simquant_batched_rows_kernel<kU>, dim3(grid_for(rows * nseg)), dim3(kThreads),
-                       0, st, reinterpret_cast<const v4f*>(x), reinterpret_cast<v4f*>(y), rows,
-                       nparam, inner_vec, nseg, seg_len, nbatch, nparam, scale, zp, per_channel,
-                       JobDiv{reciprocal32(nseg), reciprocal32(nparam)}, clips);
+    auto run = [&](auto kern) {
+      return launch_kernel(kern, dim3(grid_for(rows * nseg)), dim3(kThreads), 0, st, reinterpret_cast<const v4f*>(x),
+                           reinterpret_cast<v4f*>(y), rows, nparam, inner_vec, nseg, seg_len, nbatch, nparam, scale, zp, per_channel,
+                           JobDiv{reciprocal32(nseg), reciprocal32(nparam)}, clips);
+    };
+    // Several streams that go through the L2 reach memory less well than lines written back from it once they are too large for
+    // the last-level cache (256 MB): 2 x 58 MB 28.2 us, nontemporal 30.2; 8 x 58 MB 99.0, 95.9.
+    return total * nbatch <= (1 << 26) ? run(simquant_batched_rows_kernel<kU, true>) : run(simquant_batched_rows_kernel<kU, false>);
   }
   return launch_batched_ragged(x, y, total, nparam, per_channel ? inner : total, nbatch, scale, zp, clips, st);
 }

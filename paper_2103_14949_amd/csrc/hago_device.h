@@ -82,6 +82,20 @@ __device__ __forceinline__ void fetch_arguments() {
       : "s"(args), "n"(line(0)), "n"(line(1)), "n"(line(2)), "n"(line(3)), "n"(line(4)), "n"(line(5)));
 }
 
+// A store that goes through the L2 to memory at once (sc1).  An ordinary one, nontemporal or not, leaves a line that the end of the
+// kernel has to write back, since other XCDs may read it next, and the launch behind waits for that: 4.2 MB from 256 workgroups take
+// 1.87 us so and 2.31 with ordinary stores, 16.8 MB 3.43 and 4.64 (nontemporal 3.75), 231 MB 35.4 and 37.3; what the same XCD reads
+// next is in its L2 either way.  Pieces of a line do not meet in the L2 first, so this is for wavefronts that write at least 64
+// aligned consecutive bytes at a time, or 128 at any address (64 bytes per quad of lanes 2.18 us, ordinary 2.34; 32 bytes 4.30,
+// 2.99; 128 bytes off four 2.35, 2.46, nontemporal 2.83).  The asm says nothing of memory: no kernel reads what it writes so.
+template <typename T>
+__device__ __forceinline__ void store_through(void* dst, T v) {
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "one store");
+  if constexpr (sizeof(T) == 4) asm volatile("global_store_dword %0, %1, off sc1" ::"v"(dst), "v"(v));
+  else if constexpr (sizeof(T) == 8) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(dst), "v"(v));
+  else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(dst), "v"(v));  // (data registers: one wait state)
+}
+
 // median of three = clamp when lo <= hi; one instruction instead of two compare/select pairs
 __device__ __forceinline__ int32_t med3(int32_t x, int32_t lo, int32_t hi) {
   int32_t r;
