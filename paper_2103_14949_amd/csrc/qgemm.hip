@@ -445,7 +445,7 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
   const int forced = g_hook[kHookDmaTile].load(std::memory_order_relaxed);
   if (forced < 0 && qgemm_few_wins(p, false)) return launch_qgemm_few(p, false, 0, st);
   p.vec_k = 1;
-  p.vec16_out = (a.N % 16 == 0) && ptr_aligned(a.out, 16);
+  p.line_out = a.N % 64 == 0 && ptr_aligned(a.out, 64);
   // Tile shape: the least time on the busiest CU, in microseconds: rounds of tiles over the 256 CUs (one workgroup on each,
   // but of the 64 x 64 tiles, whose loads and matrix instructions overlap each other's), each a constant and a part
   // proportional to K, as one tile of it takes without and with company.  Fitted to (measured us, best in brackets)
@@ -533,7 +533,7 @@ static hipError_t conv_dma(const GemmArgs& a, const ConvGeom& cg, void* ws, bool
   p.inv_c = (uint32_t)(((1ull << 32) + (uint64_t)Cp - 1) / (uint64_t)Cp);
   p.inv_kw = cg.KW > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)cg.KW - 1) / (uint64_t)cg.KW) : 0u;
   if (cg.nhwc) {
-    p.vec16_out = (a.N % 16 == 0) && ptr_aligned(a.out, 16);
+    p.line_out = a.N % 64 == 0 && ptr_aligned(a.out, 64);
   } else {
     p.vec_out = ((cg.OH * cg.OW) % 4 == 0) && ptr_aligned(a.out, 4 * qgemm_out_elem_size(a));
   }
@@ -562,7 +562,7 @@ static bool try_qconv_stream(const GemmArgs& a, const ConvGeom& cg, bool has_wor
   p.inv_kw = inverse(cg.KW, 0);
   p.inv_ohw = inverse((int64_t)cg.OH * cg.OW, (int64_t)a.M + 128);
   p.inv_ow = inverse(cg.OW, (int64_t)cg.OH * cg.OW);
-  p.vec16_out = (a.N % 16 == 0) && ptr_aligned(a.out, 16);
+  p.line_out = a.N % 64 == 0 && ptr_aligned(a.out, 64);
   if (shape < 0) {
     // Microseconds, fitted to 412 layers drawn at random (7 and 8 % off): a start, K times what a CU's first tile takes, longer
     // where a stage holds several taps and with a flip, whose masks go by the lane; and per tile of a CU beyond the first.  The
