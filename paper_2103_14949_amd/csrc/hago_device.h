@@ -96,6 +96,15 @@ __device__ __forceinline__ void store_through(void* dst, T v) {
   else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(dst), "v"(v));  // (data registers: one wait state)
 }
 
+// 16 bytes at any address, through the L2 or (pieces of a line meet there first) not; `through` is uniform.
+__device__ __forceinline__ void store16(bool through, void* dst, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+  typedef v4u v4u_any __attribute__((aligned(1)));
+  const v4u v = {a, b, c, d};
+  if (through) store_through(dst, v);
+  else *static_cast<v4u_any*>(dst) = v;
+}
+
 // median of three = clamp when lo <= hi; one instruction instead of two compare/select pairs
 __device__ __forceinline__ int32_t med3(int32_t x, int32_t lo, int32_t hi) {
   int32_t r;

@@ -11,6 +11,10 @@
 
 namespace hago {
 
+inline bool ptr_aligned(const void* ptr, size_t n) {
+  return (reinterpret_cast<uintptr_t>(ptr) & (n - 1)) == 0;
+}
+
 // The status of a call of the runtime.  A failure also stays behind as the thread's last error, whatever succeeds after it, and
 // would be taken for one of a later call; who is told of it here is told once, so it is cleared.
 [[nodiscard]] inline hipError_t reported(hipError_t e) {

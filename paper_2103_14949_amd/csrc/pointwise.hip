@@ -43,6 +43,7 @@ struct PwArgs {
   uint32_t act_xor4;   // 0x80808080 for uint8 activations
   int32_t corr_coef;   // off - z_a
   int32_t per_channel;
+  int32_t through;     // results go through the L2
   RequantScalars rs;
 };
 
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
             if (pq > HW - 4) pq = HW - 4;
             uint8_t* const dst = static_cast<uint8_t*>(p.out) + (((int64_t)b * N + nn) * HW + pq) * kEsz;
             if constexpr (MODE == 1) {
-              if (ok) *reinterpret_cast<v4i_u*>(dst) = v4i{(int)raw[t][0], (int)raw[t][1], (int)raw[t][2], (int)raw[t][3]};
+              if (ok) store16(!SMALL && p.through, dst, raw[t][0], raw[t][1], raw[t][2], raw[t][3]);
             } else {
               if (ok) *reinterpret_cast<v2i_u*>(dst) = v2i_u{(int)raw[t][0], (int)raw[t][1]};
             }
@@ -276,7 +277,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
 #pragma unroll
         for (int t = 0; t < kGroups; ++t) {
           const int nn = (n & ~3) + t;
-          if (nn < N) *reinterpret_cast<v4i_u*>(row(nn) + pg) = v4i{(int)dw[t][0], (int)dw[t][1], (int)dw[t][2], (int)dw[t][3]};
+          if (nn < N) store16(p.through, row(nn) + pg, dw[t][0], dw[t][1], dw[t][2], dw[t][3]);
         }
       }
     };
@@ -457,6 +458,10 @@ bool try_qconv_pointwise_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t
   p.corr_coef = (a.act_unsigned ? 128 : 0) - a.act_zero_point;
   p.per_channel = a.rq.per_channel;
   p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
+  // 64 bytes of a row at a time, 128 where they are one-byte results, go through the L2 unless they begin off 16 bytes: one-byte results
+  // of a row of 900 and more do there too (24 -> 144 on 32 x 56 x 56, us through it and not: 6.4, 7.7; 32 -> 192 on 4 x 112 x 112 4.55, 5.69; 12 x 55 x 55 4.83, 5.05; 24 x 35 x 35
+  // 4.53, 4.71; 32 x 23 x 23 4.10, 4.00; 64 x 13 x 13 3.87, 3.72; raw on 16 x 28 x 28 3.82, 4.64; on 8 x 57 x 57 7.35, 7.06).
+  p.through = a.has_rq ? (HW % 16 == 0 && ptr_aligned(a.out, 16)) || HW >= 900 : !a.acc16 && HW % 4 == 0 && ptr_aligned(a.out, 16);
   if (p.tiles == 0) return false;
   if (a.has_rq) *err = a.acc16 ? launch<0, true>(p, st) : launch<0, false>(p, st);
   else *err = a.acc16 ? launch<2, true>(p, st) : launch<1, false>(p, st);

@@ -87,9 +87,6 @@ inline QgemmParams make_qgemm_params(const GemmArgs& a, const ConvGeom* cg) {
   return p;
 }
 
-inline bool ptr_aligned(const void* ptr, size_t n) {
-  return (reinterpret_cast<uintptr_t>(ptr) & (n - 1)) == 0;
-}
 inline size_t qgemm_out_elem_size(const GemmArgs& a) { return a.has_rq ? 1 : (a.acc16 ? 2 : 4); }
 
 // Turn the weight row sums that sit in s_corr[0..CH) into the per-channel

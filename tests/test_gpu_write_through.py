@@ -1,5 +1,6 @@
 """Stores that go through the L2: elementwise spans of whole lines and of broken ones on both sides of their size rule, many
-candidates on both sides of theirs, and dense tiles of every width at rows that begin with a line or anywhere."""
+candidates on both sides of theirs, dense tiles of every width at rows that begin with a line or anywhere, NCHW layers on both
+sides of their lines."""
 import numpy as np
 import pytest
 
@@ -53,3 +54,51 @@ def test_dense_rows(n, m, k, off):
     hago.qdense(dev(a), act_qtype(a, 128), dev(w), hago.QType(hago.I8), None, hago.I32, gpu_requant(mult, shift), out=out)
     assert_same(host(out), ref.qdense(a, 128, w, None, ref.I32, ref_requant(mult, shift)), f"{m}x{k}->{n}")
     assert int((host(guard[:off]) != 77).sum()) == 0 and int((host(guard[off + m * n:]) != 77).sum()) == 0
+
+
+def into_guard(call, shape, dtype, off):
+    """The results of call(out=...) into a tensor that starts `off` elements behind a 256-byte line; what lies around stays."""
+    n = int(np.prod(shape))
+    guard = torch.full((n + off + 256,), 77, dtype=dtype, device=DEV)
+    call(out=guard[off:off + n].view(shape))
+    assert int((guard[:off] != 77).sum()) == 0 and int((guard[off + n:] != 77).sum()) == 0
+    return host(guard[off:off + n].view(shape))
+
+
+# NCHW layers: images that begin with a line, at 16 bytes, at 4 and anywhere; few and many workgroups; a tile's end inside sixteen pixels
+@pytest.mark.parametrize("case", [(2, 32, 33, 36, 40, 3), (3, 64, 15, 16, 72, 3), (64, 64, 19, 20, 40, 3), (24, 32, 56, 56, 33, 3),
+                                  (24, 32, 28, 28, 70, 3), (9, 32, 13, 13, 70, 1), (7, 24, 20, 20, 33, 1), (5, 68, 31, 30, 40, 1),
+                                  (4, 32, 41, 41, 36, 1), (8, 32, 56, 56, 100, 1)])
+def test_nchw_layers(case):
+    B, C, H, W, O, k = case
+    rng = np.random.default_rng(1000 * W + O)
+    w = rng.integers(-127, 128, (O, C, k, k)).astype(np.int8)
+    a = rng.integers(0, 256, (B, C, H, W)).astype(np.uint8)
+    mult, shift = rng.integers(2 ** 30, 2 ** 31, O).astype(np.int32), rng.integers(7, 12, O).astype(np.int32)
+    geo, rgeo = (hago.NCHW, (1, 1), (k // 2, k // 2), 1), (ref.NCHW, (1, 1), (k // 2, k // 2), 1)
+    raw = ref.qconv2d(a, 131, w, None, *rgeo)
+    forms = [(hago.I32, None, torch.int32, raw), (hago.I16, None, torch.int16, raw.astype(np.int16))]
+    for clip, acc, racc in (((-128, 127), hago.I32, ref.I32), ((-100, 90), hago.I32, ref.I32), ((-128, 127), hago.I16, ref.I16)):
+        want = ref.qconv2d(a, 131, w, None, *rgeo, racc, ref_requant(mult, shift, False, -3, clip))
+        forms.append((acc, gpu_requant(mult, shift, False, -3, clip), torch.int8, want))
+    args = (dev(a), act_qtype(a, 131), dev(w), hago.QType(hago.I8), None, *geo)
+    for acc, rq, dtype, want in forms:
+        for off in (0, 1, 16):
+            got = into_guard(lambda out: hago.qconv2d(*args, acc, rq, out=out), raw.shape, dtype, off)
+            assert_same(got, want, f"{case} {dtype} off {off}")
+
+
+# depthwise layers on both sides of 11 MB of results: by the dword, by four rows (every remainder of a quarter's rows, images that end
+# inside sixteen bytes), rows off dwords left in the L2 or not, segments
+@pytest.mark.parametrize("case", [(2, 70, 45, 44), (57, 100, 45, 44), (60, 60, 57, 60), (65, 57, 49, 64), (40, 96, 64, 48), (130, 150, 16, 36),
+                                  (110, 200, 13, 52), (62, 80, 43, 53), (75, 60, 50, 51), (9, 11, 50, 41), (120, 60, 40, 41), (3, 9, 40, 113)])
+def test_depthwise_rows(case):
+    B, C, H, W = case
+    rng = np.random.default_rng(1000 * W + H)
+    w = rng.integers(-127, 128, (C, 1, 3, 3)).astype(np.int8)
+    a = rng.integers(-127, 128, (B, C, H, W)).astype(np.int8)
+    mult, shift = rng.integers(2 ** 30, 2 ** 31, C).astype(np.int32), rng.integers(7, 12, C).astype(np.int32)
+    want = ref.qconv2d(a, 0, w, None, ref.NCHW, (1, 1), (1, 1), C, ref.I32, ref_requant(mult, shift))
+    args = (dev(a), act_qtype(a, 0), dev(w), hago.QType(hago.I8), None, hago.NCHW, (1, 1), (1, 1), C, hago.I32, gpu_requant(mult, shift))
+    for off in (0, 4, 1):
+        assert_same(into_guard(lambda out: hago.qconv2d(*args, out=out), a.shape, torch.int8, off), want, f"{case} off {off}")
