@@ -55,6 +55,7 @@ struct C3Params {
   int32_t nblk;          // blocks of 32 TN output channels
   int32_t per_channel, has_rq, acc_wrap_shift;
   int32_t out_mode;      // 0: requantized 8-bit, 1: raw int32, 2: raw int16
+  int32_t through;       // results go through the L2
   uint32_t act_xor4;     // 0x80808080 for uint8 activations
   uint32_t pad4;         // staged value of a pixel outside the image, in every byte
   int32_t corr_coef;     // off - z_a
@@ -92,6 +93,17 @@ __device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, u
   o[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u) ^ flip;
   o[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u) ^ flip;
   o[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u) ^ flip;
+}
+
+// The upper sixteen lanes of each half of the wavefront give their a to, and take b from, the lower ones: sixteen lanes then hold, of
+// their channel in a and of the one sixteen further on in b, what is a in the lower sixteen and b in the upper ones.  Lanes i, i + 16,
+// i + 32 and i + 48 write 64 consecutive bytes of a channel so.
+__device__ __forceinline__ void swap_sixteens(uint32_t (&a)[4], uint32_t (&b)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const auto s = __builtin_amdgcn_permlane16_swap(a[k], b[k], false, false);
+    a[k] = s[0], b[k] = s[1];
+  }
 }
 
 // NW: wavefronts per workgroup; AF: 32-pixel MFMA row blocks per wavefront (tiles of 32 * NW * AF
@@ -366,114 +378,127 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
     }
 
     // ---- epilogue: the lane's 16 consecutive pixels of channel o0 + 32 tn + j, per row block
-    const int npix = rows * W;                           // valid pixels of this tile
+    const int npix = rows * W;                           // valid pixels of this tile (a multiple of 4, as W is)
+    if (32 * AF * wave >= npix) continue;                // (uniform: a wavefront beyond the tile's pixels)
+    const uint32_t obase = (uint32_t)(b * O) * (uint32_t)HW + (uint32_t)(y0 * W);  // (less than 2^31 results)
+    if (p.out_mode == 0) {
+      auto codes = [&](int f, int tn, uint32_t (&dw)[4]) {
+        // (opaque: the sums and products that forms have in common are formed in front of all of them otherwise)
+        if (sat && !fold) {
+          const int32_t c = opaque(corr[tn]), m = opaque(mu[tn]);
 #pragma unroll
-    for (int f = 0; f < AF; ++f) {
-      const int pix0 = 32 * (AF * wave + f) + 16 * h;    // first of the 16 pixels inside the tile
-      const int64_t obase = (int64_t)b * O * HW + (int64_t)y0 * W + pix0;
-      const int left = npix - pix0;                      // (image sizes off a multiple of 16: unaligned stores, fours at the end)
+          for (int g = 0; g < 4; ++g) {
+            int32_t r[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              r[e] = (int32_t)(((int64_t)wrap_acc_bits(acc[f][tn][4 * g + e] + c, p.acc_wrap_shift) * (int64_t)m + k64[tn]) >> 32);
+            ashr_sat_pair<0>(dw[g], r[0], r[1], s1[tn]);
+            ashr_sat_pair<1>(dw[g], r[2], r[3], s1[tn]);
+            dw[g] ^= sflip;
+          }
+        } else if (sat) {
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            int32_t r[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] = (int32_t)(((int64_t)acc[f][tn][4 * g + e] * (int64_t)mu[tn] + k64[tn]) >> 32);
+            ashr_sat_pair<0>(dw[g], r[0], r[1], s1[tn]);
+            ashr_sat_pair<1>(dw[g], r[2], r[3], s1[tn]);
+            dw[g] ^= sflip;
+          }
+        } else if (fold) {
+          const int32_t m = opaque(mu[tn]);
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            auto one = [&]<int E>() {
+              const int64_t pr = (int64_t)acc[f][tn][4 * g + E] * (int64_t)m + k64[tn];
+              ashr_into_byte<E>(dw[g], med3((int32_t)(pr >> 32), lo_s[tn], hi_s[tn]), s1[tn]);
+            };
+            one.template operator()<0>();
+            one.template operator()<1>();
+            one.template operator()<2>();
+            one.template operator()<3>();
+          }
+        } else {
+          const int32_t c = opaque(corr[tn]), m = opaque(mu[tn]);
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            int32_t v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              v[e] = requant_general(wrap_acc_bits(acc[f][tn][4 * g + e] + c, p.acc_wrap_shift), m, sh[tn], p.rs);
+            }
+            dw[g] = pack4(v[0], v[1], v[2], v[3]);
+          }
+        }
+      };
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn) {
-        const int o = o0 + 32 * tn + j;
-        if (pix0 >= npix) continue;  // (whole halves of the wavefront)
+        uint32_t dw[AF][4];
+#pragma unroll
+        for (int f = 0; f < AF; ++f) codes(f, tn, dw[f]);
+        if constexpr (AF == 2) swap_sixteens(dw[0], dw[1]);
+#pragma unroll
+        for (int f = 0; f < AF; ++f) {
+          const int at = stay_here(lane);
+          const int o = o0 + 32 * tn + (AF == 2 ? 16 * f + (at & 15) : at & 31);
+          const int pix = 32 * (AF * wave + (AF == 2 ? (at >> 4) & 1 : 0)) + 16 * (at >> 5), left = npix - pix;
+          if (o >= O || left <= 0) continue;
+          uint8_t* dst = static_cast<uint8_t*>(p.out) + (obase + (uint32_t)(o * HW + pix));
+          if (left >= 16) {
+            store16(AF == 2 && p.through, dst, dw[f][0], dw[f][1], dw[f][2], dw[f][3]);
+          } else {
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+              if (4 * g < left) reinterpret_cast<u32_any*>(dst)[g] = dw[f][g];
+          }
+        }
+      }
+      continue;
+    }
+#pragma unroll
+    for (int f = 0; f < AF; ++f) {
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) {
         if (p.out_mode == 1) {
           // a lane's 64 bytes go out by the quad: its channel t's from all four lanes
           uint32_t v[4][4];
+          const int32_t c = opaque(corr[tn]);
           // (the four channels' addresses, kept through the loop over the tiles, were up to 20 registers, and with them went the second
           // workgroup on a CU: 32 -> 64 on 64 x 56 x 56 11.1 us, 10.8 so; 128 -> 256 on 16 x 56 x 56 21.5, 21.0)
-          const int at = stay_here(lane), g = at & 3, oq0 = o0 + 32 * tn + (at & 28);
+          const int at = stay_here(lane), pix = 32 * (AF * wave + f) + 16 * (at >> 5) + 4 * (at & 3), oq0 = o0 + 32 * tn + (at & 28);
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int32_t a = acc[f][tn][r] + corr[tn];
-            v[r >> 2][r & 3] = (uint32_t)(p.acc_wrap_shift ? wrap_acc_bits(a, p.acc_wrap_shift) : a);
+            v[r >> 2][r & 3] = (uint32_t)wrap_acc_bits(acc[f][tn][r] + c, p.acc_wrap_shift);
           }
           quad_transpose(v, lane);
 #pragma unroll
           for (int t4 = 0; t4 < 4; ++t4) {
             const int oq = oq0 + t4;
-            if (oq < O && 4 * g < left)
-              *reinterpret_cast<v4i_any*>(static_cast<int32_t*>(p.out) + obase + (int64_t)oq * HW + 4 * g) =
-                  v4i{(int)v[t4][0], (int)v[t4][1], (int)v[t4][2], (int)v[t4][3]};
-          }
-          continue;
-        }
-        if (o >= O) continue;
-        const int64_t oo = obase + (int64_t)o * HW;
-        if (p.out_mode == 0) {
-          uint8_t* dst = static_cast<uint8_t*>(p.out) + oo;
-          uint32_t dw[4];
-          if (sat && !fold) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              int32_t r[4];
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                r[e] = (int32_t)(((int64_t)wrap_acc_bits(acc[f][tn][4 * g + e] + corr[tn], p.acc_wrap_shift) * (int64_t)mu[tn] + k64[tn]) >> 32);
-              ashr_sat_pair<0>(dw[g], r[0], r[1], s1[tn]);
-              ashr_sat_pair<1>(dw[g], r[2], r[3], s1[tn]);
-              dw[g] ^= sflip;
-            }
-          } else if (sat) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              int32_t r[4];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) r[e] = (int32_t)(((int64_t)acc[f][tn][4 * g + e] * (int64_t)mu[tn] + k64[tn]) >> 32);
-              ashr_sat_pair<0>(dw[g], r[0], r[1], s1[tn]);
-              ashr_sat_pair<1>(dw[g], r[2], r[3], s1[tn]);
-              dw[g] ^= sflip;
-            }
-          } else if (fold) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              auto one = [&]<int E>() {
-                const int64_t pr = (int64_t)acc[f][tn][4 * g + E] * (int64_t)mu[tn] + k64[tn];
-                ashr_into_byte<E>(dw[g], med3((int32_t)(pr >> 32), lo_s[tn], hi_s[tn]), s1[tn]);
-              };
-              one.template operator()<0>();
-              one.template operator()<1>();
-              one.template operator()<2>();
-              one.template operator()<3>();
-            }
-          } else {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              int32_t v[4];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                int32_t a = acc[f][tn][4 * g + e] + corr[tn];
-                if (p.acc_wrap_shift) a = wrap_acc_bits(a, p.acc_wrap_shift);
-                v[e] = requant_general(a, mu[tn], sh[tn], p.rs);
-              }
-              dw[g] = pack4(v[0], v[1], v[2], v[3]);
-            }
-          }
-          if (left >= 16) {
-            *reinterpret_cast<v4i_any*>(dst) = v4i{(int)dw[0], (int)dw[1], (int)dw[2], (int)dw[3]};
-          } else {  // (W is a multiple of 4, so are the tile's pixels)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-              if (4 * g < left) reinterpret_cast<u32_any*>(dst)[g] = dw[g];
+            if (oq < O && pix < npix)
+              store16(p.through, static_cast<int32_t*>(p.out) + (obase + (uint32_t)(oq * HW + pix)), v[t4][0], v[t4][1], v[t4][2], v[t4][3]);
           }
         } else {
-          int32_t v[16];
+          uint32_t dq[2][4];
+          const int32_t c = opaque(corr[tn]);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            v[r] = acc[f][tn][r] + corr[tn];
-            if (p.acc_wrap_shift) v[r] = wrap_acc_bits(v[r], p.acc_wrap_shift);
+          for (int x = 0; x < 8; ++x) {
+            // (the low sixteen bits are the wrapped sum's for any accumulator of at least that width)
+            dq[x >> 2][x & 3] = ((uint32_t)(acc[f][tn][2 * x] + c) & 0xffffu) | ((uint32_t)(acc[f][tn][2 * x + 1] + c) << 16);
           }
-          int16_t* dst = static_cast<int16_t*>(p.out) + oo;
-          uint32_t dq[8];
+          swap_sixteens(dq[0], dq[1]);
 #pragma unroll
-          for (int x = 0; x < 8; ++x) dq[x] = ((uint32_t)v[2 * x] & 0xffffu) | ((uint32_t)v[2 * x + 1] << 16);
-          if (left >= 16) {
-#pragma unroll
-            for (int g = 0; g < 2; ++g)
-              reinterpret_cast<v4i_any*>(dst)[g] = v4i{(int)dq[4 * g], (int)dq[4 * g + 1], (int)dq[4 * g + 2], (int)dq[4 * g + 3]};
-          } else {
-#pragma unroll
-            for (int x = 0; x < 8; ++x)
-              if (2 * x < left) reinterpret_cast<u32_any*>(dst)[x] = dq[x];
+          for (int g = 0; g < 2; ++g) {
+            const int at = stay_here(lane), o = o0 + 32 * tn + 16 * g + (at & 15);
+            const int pix = 32 * (AF * wave + f) + 16 * (at >> 5) + 8 * ((at >> 4) & 1), left = npix - pix;
+            if (o >= O || left <= 0) continue;
+            int16_t* dst = static_cast<int16_t*>(p.out) + (obase + (uint32_t)(o * HW + pix));
+            if (left >= 8) {
+              store16(p.through, dst, dq[g][0], dq[g][1], dq[g][2], dq[g][3]);
+            } else {
+              reinterpret_cast<u32_any*>(dst)[0] = dq[g][0];
+              reinterpret_cast<u32_any*>(dst)[1] = dq[g][1];
+            }
           }
         }
       }
@@ -527,6 +552,12 @@ bool try_qconv3x3_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hi
   p.has_rq = a.has_rq;
   p.acc_wrap_shift = a.acc_wrap_shift;
   p.out_mode = a.has_rq ? 0 : (a.acc16 ? 2 : 1);
+  // 64 bytes of a channel at a time go through the L2: 32-bit results always, one-byte results of images that begin at 16 bytes, 16-bit
+  // ones of images that begin with a line.  Us through it and not: raw 64 -> 64 on 16 x 56 x 56 6.7, 8.1; 64 -> 64 on 64 x 56 x 56 14.6, 16.2;
+  // 128 -> 128 on 64 x 28 x 28 13.1, 13.5; 32 -> 200 on 8 x 113 x 100 16.7, 15.7; 16 bits: 128 -> 128 on 64 x 28 x 28 14.45, 14.0; 64 -> 40 on 64
+  // x 19 x 20 6.8, 5.0.
+  const int HW = cg.H * cg.W;
+  p.through = p.out_mode == 0 ? HW % 16 == 0 && ptr_aligned(a.out, 16) : p.out_mode == 1 ? ptr_aligned(a.out, 16) : HW % 32 == 0 && ptr_aligned(a.out, 64);
   p.act_xor4 = a.act_unsigned ? 0x80808080u : 0u;
   p.pad4 = ((((uint32_t)a.act_zero_point) ^ (a.act_unsigned ? 0x80u : 0u)) & 0xffu) * 0x01010101u;
   p.corr_coef = (a.act_unsigned ? 128 : 0) - a.act_zero_point;
