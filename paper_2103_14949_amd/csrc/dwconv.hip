@@ -182,7 +182,11 @@ __device__ __forceinline__ DwChannel dw_channel(const DwArgs& p, int c) {
 // RAGGED: rows that are not whole dwords (or tensors at any byte).  Loads and stores are unaligned; the last strip of a
 // row is loaded from the row's last four bytes and shifted into place, and stored as those four bytes together with the
 // end of its left neighbour's results (16 x 288 planes of 41 x 41: 24.8 us through LDS, 8.6 here).
-template <int MODE, bool ACC16, bool WIDE, bool RAGGED>
+// OUT (MODE 0): how a row's results go out, a dword per lane: kL2 left in the L2, whose lines the kernel's end writes back; kThrough
+//   through it to memory, while other wavefronts work; kFours the same by four rows of a quarter, which are one run of the image: they
+//   meet in LDS and its lanes with a strip write 16 bytes each.
+enum { kL2, kThrough, kFours };
+template <int MODE, bool ACC16, bool WIDE, bool RAGGED, int OUT = kL2>
 __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(uint32_t gx, uint32_t mid, uint32_t count, uint32_t inv_x, uint32_t inv_mid,
                                                                DwArgs p, int32_t rpc, int32_t nsegs, int32_t segw) {
   // grid: x = groups of four channels, of each its column segments (which are not equally wide: next to each other, every XCD has as
@@ -298,6 +302,11 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(uint32_t gx, uint3
   // A store beyond the image lies beyond the plane, and a strip-less lane's offset starts at
   // 2^31: both are out of the descriptor's range and dropped.
   const uint32_t so0 = has_strip ? (uint32_t)(x0 - (MODE == 0 ? pull : 0) + y0 * W) * kEsz : kOob;
+  static_assert(OUT == kL2 || MODE == 0);
+  static_assert(OUT != kFours || (!WIDE && !RAGGED));
+  constexpr int kOutAux = OUT == kL2 ? 0 : 16;  // sc1
+  __shared__ __attribute__((aligned(16))) uint8_t s_fours[OUT == kFours ? kThreads / 16 : 1][256];
+  uint8_t* const fours = s_fours[OUT == kFours ? threadIdx.x >> 4 : 0];
 
   // FOLD (requantized, 32-bit accumulator, and the channel's constants small enough): the
   // correction term, the rounding term and the output zero point all go into one 64-bit
@@ -360,7 +369,28 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(uint32_t gx, uint3
             const uint32_t lw = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)dw, 0x111, 0xf, 0xf, true);  // row_shr:1
             dw = (uint32_t)((((uint64_t)dw << 32) | lw) >> (32 - pull_bits));
           }
-          __builtin_amdgcn_raw_buffer_store_b32(dw, rout, so, 0, 0);
+          if (OUT == kFours && (i | 3) < rpc) {  // (uniform)
+            if (has_strip) *reinterpret_cast<uint32_t*>(fours + 4 * q + (i & 3) * W) = dw;
+            if ((i & 3) == 3) {
+              typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+              const int left = has_strip ? (H - y0 - (i - 3)) * W - 16 * q : 0;  // bytes of the image from the lane's piece on
+              if (left > 0) {
+                const v4u v = *reinterpret_cast<const v4u*>(fours + 16 * q);
+                uint8_t* const dst = static_cast<uint8_t*>(p.out) + plane * pbytes + (uint32_t)((y0 + i - 3) * W + 16 * q);
+                if (left >= 16) {
+                  store_through(dst, v);
+                } else {  // (the image ends with this piece)
+#pragma unroll
+                  for (int e = 0; e < 3; ++e)
+                    if (4 * e < left) reinterpret_cast<uint32_t*>(dst)[e] = v[e];
+                }
+              }
+              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
+          } else {
+            __builtin_amdgcn_raw_buffer_store_b32(dw, rout, so, 0, kOutAux);
+          }
         } else if constexpr (MODE == 1) {
           typedef int32_t v4i32 __attribute__((ext_vector_type(4)));
           if constexpr (RAGGED) {
@@ -969,14 +999,22 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
     while (cg.W > 64 && segw > 12 && cg.W % segw != 0 && cg.W % segw < 4) segw -= 4;
     nsegs = (cg.W + segw - 1) / segw;
     if (segw > 12 && nband * nsegs <= 65535 && (int64_t)(cg.C + 3) / 4 * nsegs <= max_blocks(kThreads)) {
-#define HAGO_DW_ROWS(WIDE_, RAG_)                                                                      \
+      // Rows in pieces slow the way to memory down from 11 MB of results on.  Us of 144 channels with results left in the L2, sent
+      // through it, and by four rows: 8 x 56 x 56 4.72, 4.42, 5.2; 24 x 56 x 56, 10.8 MB, 7.51, 7.05, 6.99; 32 x 56 x 56 8.65, 9.05, 8.15; 32 x 60 x 60
+      // 9.06, 9.96, 8.51; 40 x 48 x 48, 13.3 MB, 9.12, 8.83, 8.17; 26 x 52 x 52, 10.1 MB, 7.13, 6.45, 6.73; rows of 64 bytes on 16 x 64 x 64
+      // 6.53, 5.30, 6.32.  Rows off dwords: 24 x 63 x 63, 13.7 MB, 8.75, 9.35; 24 x 49 x 49 7.13, 6.67; 60 x 41 x 41, 14.5 MB, 0.4 less through it.
+      // Several segments: 8 x 113 x 113 x 96 8.21, 7.31.
+      const int64_t gx = (int64_t)(cg.C + 3) / 4 * nsegs, mid = nband;
+      const bool large = total > 11000000;
+      const int how = !large || nsegs > 1 ? kThrough : ragged ? (cg.W <= 48 ? kThrough : kL2) : cg.W == 64 ? kThrough : kFours;
+#define HAGO_DW_ROWS(WIDE_, RAG_, OUT_)                                                                \
   (p.out_mode == 1 ? dw_rows3x3_kernel<1, false, WIDE_, RAG_>                                          \
    : p.out_mode == 2 ? dw_rows3x3_kernel<2, true, WIDE_, RAG_>                                         \
-   : p.acc16 ? dw_rows3x3_kernel<0, true, WIDE_, RAG_> : dw_rows3x3_kernel<0, false, WIDE_, RAG_>)
-      auto kern = nsegs > 1 ? (ragged ? HAGO_DW_ROWS(true, true) : HAGO_DW_ROWS(true, false))
-                            : (ragged ? HAGO_DW_ROWS(false, true) : HAGO_DW_ROWS(false, false));
+   : p.acc16 ? dw_rows3x3_kernel<0, true, WIDE_, RAG_, OUT_> : dw_rows3x3_kernel<0, false, WIDE_, RAG_, OUT_>)
+      auto kern = nsegs > 1 ? (ragged ? HAGO_DW_ROWS(true, true, kThrough) : HAGO_DW_ROWS(true, false, kThrough))
+                  : ragged ? (how == kL2 ? HAGO_DW_ROWS(false, true, kL2) : HAGO_DW_ROWS(false, true, kThrough))
+                           : (how == kFours ? HAGO_DW_ROWS(false, false, kFours) : HAGO_DW_ROWS(false, false, kThrough));
 #undef HAGO_DW_ROWS
-      const int64_t gx = (int64_t)(cg.C + 3) / 4 * nsegs, mid = nband;
       return launch_kernel(kern, dim3((unsigned)gx, (unsigned)mid, (unsigned)cg.B), dim3(kThreads), 0, st, (uint32_t)gx, (uint32_t)mid,
                          (uint32_t)(gx * mid * cg.B), inverse(gx, gx * mid * cg.B), inverse(mid, mid * cg.B), p, rpc, nsegs, segw);
     }
