@@ -70,12 +70,6 @@ __device__ __forceinline__ uint32_t div_by(uint32_t n, uint32_t d, uint32_t inv)
   return inv ? __umulhi(n, inv) : n / d;
 }
 
-// v; what follows from it is computed where it is used, not in front of the loop around
-__device__ __forceinline__ int stay_here(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 // row r of a 32-row block <-> pixel of the block (see the header)
 __device__ __forceinline__ constexpr int pix_of_row(int r) {
   return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
@@ -93,17 +87,6 @@ __device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, u
   o[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302u) ^ flip;
   o[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100u) ^ flip;
   o[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302u) ^ flip;
-}
-
-// The upper sixteen lanes of each half of the wavefront give their a to, and take b from, the lower ones: sixteen lanes then hold, of
-// their channel in a and of the one sixteen further on in b, what is a in the lower sixteen and b in the upper ones.  Lanes i, i + 16,
-// i + 32 and i + 48 write 64 consecutive bytes of a channel so.
-__device__ __forceinline__ void swap_sixteens(uint32_t (&a)[4], uint32_t (&b)[4]) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const auto s = __builtin_amdgcn_permlane16_swap(a[k], b[k], false, false);
-    a[k] = s[0], b[k] = s[1];
-  }
 }
 
 // NW: wavefronts per workgroup; AF: 32-pixel MFMA row blocks per wavefront (tiles of 32 * NW * AF

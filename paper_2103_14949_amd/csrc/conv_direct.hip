@@ -52,6 +52,7 @@ struct CdParams {
   int32_t per_channel, has_rq, acc_wrap_shift, out_mode;
   uint32_t act_xor4, pad4;
   int32_t corr_coef;
+  int32_t through;            // NCHW, one-byte results: sixteen pixels from a multiple of sixteen on lie in one image (or row) and at 16 bytes
   int64_t act_bytes;
   RequantScalars rs;
 };
@@ -764,6 +765,39 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
 #pragma unroll
       for (int tn = 0; tn < 2; ++tn) {
         const int cl = 64 * wch + 32 * tn + j, o = o0 + cl;
+        if (AF == 2 && fold && sat && p.through) {  // (uniform)
+          // Sixteen pixels of both row blocks: 64 bytes of a channel by four lanes, through the L2 (3 -> 64 7x7 stride 2 on 8 x 224 x 224 10.6 us
+          // with a lane's own sixteen bytes left there, 9.7 so).
+          const int4 k = s_fold[cl];
+          const int64_t k64 = (int64_t)(((uint64_t)(uint32_t)k.y << 32) | (uint32_t)k.x);
+          uint32_t dw[AF][4];
+#pragma unroll
+          for (int f = 0; f < AF; ++f)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              int32_t y[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) y[e] = (int32_t)(((int64_t)acc[f][tn][4 * g + e] * (int64_t)k.z + k64) >> 32);
+              ashr_sat_pair<0>(dw[f][g], y[0], y[1], k.w);
+              ashr_sat_pair<1>(dw[f][g], y[2], y[3], k.w);
+              dw[f][g] ^= sflip;
+              __builtin_amdgcn_sched_barrier(0);  // (four products at a time: all sixteen would spill)
+            }
+          swap_sixteens(dw[0], dw[AF - 1]);
+          const int at = stay_here(lane), q0 = 32 * (AF * wpx + ((at >> 4) & 1)) + 16 * (at >> 5);
+          uint32_t x, oy;
+          const uint32_t r = divide((uint32_t)q0, (uint32_t)p.TW, p.inv_tw, x);
+          const uint32_t R = (uint32_t)pos.R0 + r;
+          const uint32_t b = divide(R, (uint32_t)p.OH, p.inv_oh, oy);
+          const int ox = pos.x0 + (int)x, from = o0 + 64 * wch + 32 * tn + (at & 15);
+          if (q0 < pt && R < Rend && ox < p.OW) {
+            uint8_t* const dst = static_cast<uint8_t*>(p.out) + (((int64_t)b * p.O + from) * OHW + (int)oy * p.OW + ox);
+            typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+            if (from < p.O) store_through(dst, v4u{dw[0][0], dw[0][1], dw[0][2], dw[0][3]});
+            if (from + 16 < p.O) store_through(dst + (int64_t)16 * OHW, v4u{dw[AF - 1][0], dw[AF - 1][1], dw[AF - 1][2], dw[AF - 1][3]});
+          }
+          continue;
+        }
         const int32_t corr = s_corr[cl], mu = s_mu[cl], sh = s_sh[cl], s1 = sh - 1;
         const int4 k = s_fold[cl];
         const int64_t k64 = (int64_t)(((uint64_t)(uint32_t)k.y << 32) | (uint32_t)k.x);
@@ -1023,6 +1057,7 @@ bool try_qconv_direct(const GemmArgs& a, const ConvGeom& cg, int forced_shape, h
     }
   }
   if (best_shape < 0) return false;
+  best.through = ptr_aligned(a.out, 16) && (best.nseg == 1 ? (int64_t)cg.OH * cg.OW % 16 == 0 && (int64_t)best.TR * best.TW % 16 == 0 : cg.OW % 16 == 0);
   const int best_cg = best.small_c ? 1 : best.CC / 16;
   best.inv_unit1 = recip(cg.nhwc ? (int64_t)best.Wq * 4 * best_cg : (int64_t)best.rows * best.Wq);
   best.inv_unit2 = recip(cg.nhwc ? best_cg : best.Wq);

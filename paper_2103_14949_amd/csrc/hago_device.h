@@ -193,6 +193,23 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&d)[4][D], int lane) {
   }
 }
 
+// v; what follows from it is computed where it is used, not in front of the loop around
+__device__ __forceinline__ int stay_here(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// The upper sixteen lanes of each half of the wavefront give their a to, and take b from, the lower ones: sixteen lanes then hold, of
+// their channel in a and of the one sixteen further on in b, what is a in the lower sixteen and b in the upper ones.  Lanes i, i + 16,
+// i + 32 and i + 48 write 64 consecutive bytes of a channel so.
+__device__ __forceinline__ void swap_sixteens(uint32_t (&a)[4], uint32_t (&b)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const auto s = __builtin_amdgcn_permlane16_swap(a[k], b[k], false, false);
+    a[k] = s[0], b[k] = s[1];
+  }
+}
+
 // Whether the output's clip limits are its container's whole range, so that this saturation is the clip.  sat_bias is added
 // to the output zero point (inside the 64-bit constant of the folded forms) to centre the range on int8's, and sat_flip
 // undoes it in the packed dword: 0 and 0 for int8, -128 and 0x80 per byte for uint8.
