@@ -77,9 +77,22 @@ def check_lds_loads(assembly: str) -> list[str]:
                         assembly, re.M)]
 
 
+def check_wide_stores(assembly: str) -> list[str]:
+    """Stores of more than eight bytes in inline assembly that are not followed by two wait states: the registers of their data
+    must not be written before, and nobody inserts them there."""
+    found = []
+    for block in re.findall(r";;?#ASMSTART\n(.*?);;?#ASMEND", assembly, re.S):
+        for m in re.finditer(r"^\s*((?:global|buffer|flat|scratch)_store_dwordx[34]\b.*)\n(.*)", block, re.M):
+            nop = re.match(r"\s*s_nop (\d+)", m[2])
+            if not nop or int(nop[1]) < 1:
+                found.append(m[1].strip())
+    return found
+
+
 def check_assembly(assembly: str) -> list[str]:
     """What the kernels must not hold, and the compiler does not avoid."""
     return ([f"64-bit shift by the last allocated register (add HAGO_SPARE_REGISTER): {f}" for f in check_shift_amounts(assembly)] +
+            [f"wide store without two wait states behind it: {f}" for f in check_wide_stores(assembly)] +
             [f"LDS load without a wait state after m0: {f}" for f in check_lds_loads(assembly)])
 
 

@@ -93,7 +93,7 @@ __device__ __forceinline__ void store_through(void* dst, T v) {
   static_assert(sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "one store");
   if constexpr (sizeof(T) == 4) asm volatile("global_store_dword %0, %1, off sc1" ::"v"(dst), "v"(v));
   else if constexpr (sizeof(T) == 8) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(dst), "v"(v));
-  else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(dst), "v"(v));  // (data registers: one wait state)
+  else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(dst), "v"(v));  // (two wait states before its data registers are written again)
 }
 
 // 16 bytes at any address, through the L2 or (pieces of a line meet there first) not; `through` is uniform.

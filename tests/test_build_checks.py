@@ -48,6 +48,19 @@ def test_lds_loads_directly_after_m0_are_found(lines, refused):
     assert bool(build.check_assembly(assembly)) == refused
 
 
+@pytest.mark.parametrize("lines,refused", [
+    ("global_store_dwordx4 v[4:5], v[0:3], off sc1", True),
+    ("global_store_dwordx4 v[4:5], v[0:3], off sc1|s_nop 0", True),
+    ("buffer_store_dwordx3 v[0:2], v4, s[0:3], 0 offen|v_mov_b32 v0, 0", True),
+    ("global_store_dwordx4 v[4:5], v[0:3], off sc1|s_nop 1", False),
+    ("global_store_dwordx2 v[4:5], v[0:1], off sc1", False),
+])
+def test_wide_stores_without_wait_states_behind_them_are_found(lines, refused):
+    body = "".join(f"\t{x}\n" for x in lines.split("|"))
+    assert bool(build.check_wide_stores(f"_Zkern:\n\t;;#ASMSTART\n{body}\t;;#ASMEND\n\tv_mov_b32 v0, 1\n")) == refused
+    assert not build.check_wide_stores(f"_Zkern:\n{body}")  # (the compiler's own)
+
+
 def test_no_kernel_as_built_has_one():
     directory = os.path.join(os.path.dirname(build.LIB), "_build")
     paths = glob.glob(os.path.join(directory, "**", "*gfx950.s"), recursive=True)
