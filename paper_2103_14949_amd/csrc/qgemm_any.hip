@@ -362,6 +362,9 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
     }
   __syncthreads();
   const int ppr = BP * esz / 16, epp = 16 / esz;  // pieces per row, elements per piece (powers of two)
+  // Rows of 128 bytes and more go through the L2, of 64 where they begin with a line, else pieces of a line meet there (us, left in the L2 and so:
+  // raw 3000 x 101 -> 1984 11.1, 8.9, 3000 x 100 -> 1999 12.75, 11.4, 2000 x 701 -> 1002 10.0, 9.2; 8 bits 3000 x 101 -> 1984 9.4, 8.8).
+  const bool through = ppr >= 8 || p.line_out;
   const int lppr = 31 - __builtin_clz((unsigned)ppr);
   for (int q = t; q < BQ * ppr; q += NT) {
     const int r = q >> lppr, c = q & (ppr - 1);
@@ -370,7 +373,9 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
     const uint8_t* src = smem + r * RS + c * 16;
     uint8_t* dst = static_cast<uint8_t*>(p.out) + ((size_t)m * p.N + n) * esz;
     if (n + epp <= p.N) {
-      *reinterpret_cast<v4i_any*>(dst) = *reinterpret_cast<const v4i*>(src);
+      const v4i v = *reinterpret_cast<const v4i*>(src);
+      if (through) store_through(dst, v);
+      else *reinterpret_cast<v4i_any*>(dst) = v;
     } else {
       for (int b = 0; b < (p.N - n) * esz; ++b) dst[b] = src[b];
     }
@@ -391,11 +396,12 @@ hipError_t launch_tiles(void (*kern)(QgemmParams), QgemmParams p, int64_t tiles,
 }
 
 template <bool I16, int WP, int WQ, int TP, int TQ, int KS>
-hipError_t launch_staged(const QgemmParams& p, hipStream_t st) {
+hipError_t launch_staged(QgemmParams p, hipStream_t st) {
   constexpr int BP = 32 * WP * TP, BQ = 32 * WQ * TQ;
   constexpr int stages = 2 * (BP + BQ) * kRow, out = BQ * (BP * 4 + 16), sums = (KS - 1) * BP * BQ * 4;
   constexpr int most = stages > out ? stages : out, lds = most > sums ? most : sums;
   const int64_t tiles = (int64_t)((p.N + BP - 1) / BP) * ((p.M + BQ - 1) / BQ);
+  p.line_out = p.N % 64 == 0 && ptr_aligned(p.out, 64);
   auto kern = qgemm_staged_kernel<I16, WP, WQ, TP, TQ, KS>;
   static std::atomic<uint64_t> attr_set{0};
   hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds, attr_set);
