@@ -52,7 +52,7 @@ struct CdParams {
   int32_t per_channel, has_rq, acc_wrap_shift, out_mode;
   uint32_t act_xor4, pad4;
   int32_t corr_coef;
-  int32_t through;            // NCHW, one-byte results: sixteen pixels from a multiple of sixteen on lie in one image (or row) and at 16 bytes
+  int32_t through;            // 16 bytes of results, from a multiple of as many pixels (channel-last: channels) on, lie in one image (or row, pixel) and at 16 bytes
   int64_t act_bytes;
   RequantScalars rs;
 };
@@ -78,8 +78,9 @@ __device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, u
 
 // WT: how weights are staged.  9: NCHW 3x3, four channels' nine taps at once; 2: contiguous channels (1x1, NHWC); 0: byte
 // by byte (any kernel; the few-channel form).  MULTI: several chunks of channels.  WPX x WCH wavefronts over pixels and channels, each AF x 32
-// pixels by 64 channels.
-template <bool NHWC, bool SMALL, bool MULTI, int WT, int WPX, int WCH, int AF>
+// pixels by 64 channels.  RAW: sums go out, as 16 or 32 bits (in one kernel with the requantized form every layer of that took 0.3 us more:
+// 64 -> 128 3x3 stride 2 on 32 x 56 x 56 10.7, 10.4 by the requantized form alone before, 10.0 so).
+template <bool NHWC, bool SMALL, bool MULTI, int WT, int WPX, int WCH, int AF, bool RAW>
 __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams p) {
   constexpr int NT = 64 * WPX * WCH;
   constexpr int NU = NHWC ? 8 : (AF == 2 ? 2 : 3);  // staging units per thread
@@ -90,6 +91,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   // 13.0, 14.5, raw 20.4, 21.5; 64 -> 64 3x3 on 32 x 56 x 56 13.4, 14.6).
   constexpr bool kTight = NHWC && AF == 2;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int out_mode = RAW ? (p.out_mode == 1 ? 1 : 2) : 0;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wpx = wave % WPX, wch = wave / WPX;
@@ -445,7 +447,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
     s_sum[t] = 0;
     if (o < p.O) {
       if (p.bias) c_bias = p.bias[o];
-      if (p.has_rq) {
+      if (!RAW) {
         c_mu = rq_mult(p.mult, p.per_channel ? o : 0);
         c_sh = rq_shift(p.mult, p.shift, p.per_channel ? o : 0);
       }
@@ -538,7 +540,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   // them too (64 -> 128 3x3 stride 2 on 32 x 56 x 56: 10.3 us, 10.4 before; 3 -> 64 7x7 on 8 x 224 x 224,
   // with the input's loads by descriptor, one addition each, 10.6, 12.2 before).
   auto form_terms = [&]() {
-    int bad = p.out_mode != 0 || p.acc_wrap_shift != 0 || p.rs.half_away || p.rs.z_out < -256 || p.rs.z_out > 255 || p.C * T > 65536;
+    int bad = RAW || p.acc_wrap_shift != 0 || p.rs.half_away || p.rs.z_out < -256 || p.rs.z_out > 255 || p.C * T > 65536;
     if (t < OB) {
       if constexpr (kTight) {
         c_bias = s_corr[t];
@@ -553,7 +555,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
       s_sh[t] = sh;
       s_fold[t] = make_int4((int)(uint32_t)k64, (int)(k64 >> 32), mu, sh - 1);
     }
-    if (bad) atomicOr(s_flag, 1);
+    if (!RAW && bad) atomicOr(s_flag, 1);
     if (MULTI) __syncthreads();
   };
   if constexpr (!MULTI) {  // resident for every tile
@@ -662,12 +664,12 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
     }
     ch = 0;
     if (first && MULTI) form_terms();  // (the sums of the last chunk are complete)
-    if (first) fold = *s_flag == 0;
+    if (first) fold = !RAW && *s_flag == 0;
     first = false;
 
     // ---- epilogue
     const uint32_t Rend = (uint32_t)(p.B * p.OH);
-    const int esz = p.out_mode == 0 ? 1 : (p.out_mode == 1 ? 4 : 2);
+    const int esz = out_mode == 0 ? 1 : (out_mode == 1 ? 4 : 2);
     if constexpr (NHWC) {
 #pragma unroll
       for (int f = 0; f < AF; ++f) {
@@ -678,6 +680,84 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
         const int ox = pos.x0 + (int)x;
         const bool px_ok = q < pt && R < Rend && ox < p.OW;
         const int64_t prow = ((int64_t)R * p.OW + ox) * p.O;
+        if (p.through && (out_mode != 0 || (fold && sat))) {  // (uniform) four lanes write 64 consecutive bytes of a pixel
+          // through the L2 (3 -> 64 7x7 stride 2 on 8 x 224 x 224: raw 20.5 us with 16 bytes per lane to 32 pixels, 13.3 so, 16 bits 15.7, 11.8, one byte
+          // 12.8, 12.2)
+          // pixel q of the tile, which another lane has the results of
+          auto at_pixel = [&](int q, int64_t& row) {
+            uint32_t x;
+            const uint32_t r = divide((uint32_t)q, (uint32_t)p.TW, p.inv_tw, x);
+            const uint32_t R = (uint32_t)pos.R0 + r;
+            const int ox = pos.x0 + (int)x;
+            row = ((int64_t)R * p.OW + ox) * p.O;
+            return q < pt && R < Rend && ox < p.OW;
+          };
+          const int at = stay_here(lane), q_first = 32 * (AF * wpx + f);
+          if (out_mode == 0) {
+            uint32_t dw[2][4];
+#pragma unroll
+            for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+              for (int g = 0; g < 4; ++g) {
+                int32_t y[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  const int4 k = s_fold[64 * wch + 32 * tn + 16 * h + 4 * g + e];
+                  y[e] = (int32_t)(((int64_t)acc[f][tn][4 * g + e] * (int64_t)k.z + (int64_t)(((uint64_t)(uint32_t)k.y << 32) | (uint32_t)k.x)) >> 32) >> k.w;
+                }
+                ashr_sat_pair<0>(dw[tn][g], y[0], y[1], 0);
+                ashr_sat_pair<1>(dw[tn][g], y[2], y[3], 0);
+                dw[tn][g] ^= sflip;
+                __builtin_amdgcn_sched_barrier(0);  // (four products at a time)
+              }
+            swap_sixteens(dw[0], dw[1]);
+            const int o = o0 + 64 * wch + 32 * ((at >> 4) & 1) + 16 * (at >> 5);
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+              int64_t row;
+              if (at_pixel(q_first + 16 * g + (at & 15), row) && o < p.O)
+                store_through(static_cast<uint8_t*>(p.out) + row + o, v4i{(int)dw[g][0], (int)dw[g][1], (int)dw[g][2], (int)dw[g][3]});
+            }
+            continue;
+          }
+#pragma unroll
+          for (int tn = 0; tn < 2; ++tn) {
+            __builtin_amdgcn_sched_barrier(0);  // one group of results at a time
+            const int32_t* const corr = s_corr + 64 * wch + 32 * tn + 16 * h;
+            if (out_mode == 1) {
+              uint32_t v[4][4];
+#pragma unroll
+              for (int g = 0; g < 4; ++g) {
+                const int4 c4 = *reinterpret_cast<const int4*>(corr + 4 * g);
+                const int32_t cc[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[g][e] = (uint32_t)wrap_acc_bits(acc[f][tn][4 * g + e] + cc[e], p.acc_wrap_shift);
+              }
+              quad_transpose(v, lane);
+              const int o = o0 + 64 * wch + 32 * tn + 16 * (at >> 5) + 4 * (at & 3);
+#pragma unroll
+              for (int t4 = 0; t4 < 4; ++t4) {
+                int64_t row;
+                if (at_pixel(q_first + (at & 28) + t4, row) && o < p.O)
+                  store_through(static_cast<int32_t*>(p.out) + row + o, v4i{(int)v[t4][0], (int)v[t4][1], (int)v[t4][2], (int)v[t4][3]});
+              }
+            } else {
+              uint32_t dq[2][4];
+#pragma unroll
+              for (int y = 0; y < 8; ++y)
+                dq[y >> 2][y & 3] = ((uint32_t)(acc[f][tn][2 * y] + corr[2 * y]) & 0xffffu) | ((uint32_t)(acc[f][tn][2 * y + 1] + corr[2 * y + 1]) << 16);
+              swap_sixteens(dq[0], dq[1]);
+              const int o = o0 + 64 * wch + 32 * tn + 16 * (at >> 5) + 8 * ((at >> 4) & 1);
+#pragma unroll
+              for (int g = 0; g < 2; ++g) {
+                int64_t row;
+                if (at_pixel(q_first + 16 * g + (at & 15), row) && o < p.O)
+                  store_through(static_cast<int16_t*>(p.out) + row + o, v4i{(int)dq[g][0], (int)dq[g][1], (int)dq[g][2], (int)dq[g][3]});
+              }
+            }
+          }
+          continue;
+        }
 #pragma unroll
         for (int tn = 0; tn < 2; ++tn) {
           __builtin_amdgcn_sched_barrier(0);  // one group of results at a time
@@ -735,14 +815,14 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
               for (int e = 0; e < 4; ++e) {
                 v[e] = acc[f][tn][4 * g + e] + cc[e];
                 if (p.acc_wrap_shift) v[e] = wrap_acc_bits(v[e], p.acc_wrap_shift);
-                if (p.out_mode == 0) v[e] = requant_general(v[e], mm[e], hh[e], p.rs);
+                if (out_mode == 0) v[e] = requant_general(v[e], mm[e], hh[e], p.rs);
               }
             }
             uint8_t* dst = static_cast<uint8_t*>(p.out) + (prow + o + 4 * g) * esz;
             if (4 * g + 4 <= left) {
-              if (p.out_mode == 0) {
+              if (out_mode == 0) {
                 *reinterpret_cast<u32_any*>(dst) = pack4_perm(v[0], v[1], v[2], v[3]);
-              } else if (p.out_mode == 1) {
+              } else if (out_mode == 1) {
                 *reinterpret_cast<v4i_any*>(dst) = v4i{v[0], v[1], v[2], v[3]};
               } else {
                 *reinterpret_cast<u32_any*>(dst) = ((uint32_t)v[0] & 0xffffu) | ((uint32_t)v[1] << 16);
@@ -752,8 +832,8 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
 #pragma unroll
               for (int e = 0; e < 4; ++e)
                 if (4 * g + e < left) {
-                  if (p.out_mode == 0) dst[e] = (uint8_t)v[e];
-                  else if (p.out_mode == 1) reinterpret_cast<int32_t*>(dst)[e] = v[e];
+                  if (out_mode == 0) dst[e] = (uint8_t)v[e];
+                  else if (out_mode == 1) reinterpret_cast<int32_t*>(dst)[e] = v[e];
                   else reinterpret_cast<int16_t*>(dst)[e] = (int16_t)v[e];
                 }
             }
@@ -795,6 +875,44 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
             typedef uint32_t v4u __attribute__((ext_vector_type(4)));
             if (from < p.O) store_through(dst, v4u{dw[0][0], dw[0][1], dw[0][2], dw[0][3]});
             if (from + 16 < p.O) store_through(dst + (int64_t)16 * OHW, v4u{dw[AF - 1][0], dw[AF - 1][1], dw[AF - 1][2], dw[AF - 1][3]});
+          }
+          continue;
+        }
+        if (out_mode != 0 && p.through) {  // (uniform) raw: pieces of 16 bytes by lanes that write 64 consecutive ones of a channel
+          // (3 -> 64 7x7 stride 2 on 8 x 224 x 224, 16 bytes per lane to 32 channels and so: 17.8 us, 11.5, 16 bits 12.4, 10.85; 64 -> 128 3x3
+          // stride 2 on 32 x 56 x 56 15.1, 11.65)
+#pragma unroll
+          for (int f = 0; f < AF; ++f) {
+            __builtin_amdgcn_sched_barrier(0);  // one group of results at a time
+            const int32_t corr = s_corr[stay_here(cl)];
+            const int at = stay_here(lane), wide = out_mode == 1;
+            const int q0 = 32 * (AF * wpx + f) + 16 * (at >> 5) + (wide ? 4 * (at & 3) : 8 * ((at >> 4) & 1));
+            const int from = o0 + 64 * wch + 32 * tn + (wide ? at & 28 : at & 15);
+            uint32_t x, oy;
+            const uint32_t r = divide((uint32_t)q0, (uint32_t)p.TW, p.inv_tw, x);
+            const uint32_t R = (uint32_t)pos.R0 + r;
+            const uint32_t b = divide(R, (uint32_t)p.OH, p.inv_oh, oy);
+            const int ox = pos.x0 + (int)x;
+            const bool ok = q0 < pt && R < Rend && ox < p.OW;
+            uint8_t* const dst = static_cast<uint8_t*>(p.out) + (((int64_t)b * p.O + from) * OHW + (int)oy * p.OW + ox) * esz;
+            if (wide) {
+              uint32_t v[4][4];
+#pragma unroll
+              for (int e = 0; e < 16; ++e) v[e >> 2][e & 3] = (uint32_t)wrap_acc_bits(acc[f][tn][e] + corr, p.acc_wrap_shift);
+              quad_transpose(v, lane);
+#pragma unroll
+              for (int t4 = 0; t4 < 4; ++t4)
+                if (ok && from + t4 < p.O) store16(true, dst + (int64_t)t4 * OHW * 4, v[t4][0], v[t4][1], v[t4][2], v[t4][3]);
+            } else {
+              uint32_t dq[2][4];
+#pragma unroll
+              for (int y = 0; y < 8; ++y)  // (the low sixteen bits are the wrapped sum's for any accumulator of at least that width)
+                dq[y >> 2][y & 3] = ((uint32_t)(acc[f][tn][2 * y] + corr) & 0xffffu) | ((uint32_t)(acc[f][tn][2 * y + 1] + corr) << 16);
+              swap_sixteens(dq[0], dq[1]);
+#pragma unroll
+              for (int g = 0; g < 2; ++g)
+                if (ok && from + 16 * g < p.O) store16(true, dst + (int64_t)(16 * g) * OHW * 2, dq[g][0], dq[g][1], dq[g][2], dq[g][3]);
+            }
           }
           continue;
         }
@@ -844,9 +962,9 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
             for (int e = 0; e < 16; ++e) {
               v[e] = acc[f][tn][e] + corr;
               if (p.acc_wrap_shift) v[e] = wrap_acc_bits(v[e], p.acc_wrap_shift);
-              if (p.out_mode == 0) v[e] = requant_general(v[e], mu, sh, p.rs);
+              if (out_mode == 0) v[e] = requant_general(v[e], mu, sh, p.rs);
             }
-            if (p.out_mode == 0)
+            if (out_mode == 0)
 #pragma unroll
               for (int g = 0; g < 4; ++g) dw[g] = pack4_perm(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
           }
@@ -859,9 +977,9 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
           if (p.nseg > 1 && ox >= p.OW) continue;
           uint8_t* dst = static_cast<uint8_t*>(p.out) + (((int64_t)b * p.O + o) * OHW + pix) * esz;
           if (cnt >= 16 && in_img >= 16) {
-            if (p.out_mode == 0) {
+            if (out_mode == 0) {
               *reinterpret_cast<v4i_any*>(dst) = v4i{(int)dw[0], (int)dw[1], (int)dw[2], (int)dw[3]};
-            } else if (p.out_mode == 1) {
+            } else if (out_mode == 1) {
 #pragma unroll
               for (int g = 0; g < 4; ++g) *reinterpret_cast<v4i_any*>(dst + 16 * g) = v4i{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
             } else {
@@ -884,8 +1002,8 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               if (4 * g + 4 <= cnt && until >= 4) {
-                if (p.out_mode == 0) *reinterpret_cast<u32_any*>(d) = dw[g];
-                else if (p.out_mode == 1) *reinterpret_cast<v4i_any*>(d) = v4i{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+                if (out_mode == 0) *reinterpret_cast<u32_any*>(d) = dw[g];
+                else if (out_mode == 1) *reinterpret_cast<v4i_any*>(d) = v4i{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
                 else {
                   *reinterpret_cast<u32_any*>(d) = ((uint32_t)v[4 * g] & 0xffffu) | ((uint32_t)v[4 * g + 1] << 16);
                   *reinterpret_cast<u32_any*>(d + 4) = ((uint32_t)v[4 * g + 2] & 0xffffu) | ((uint32_t)v[4 * g + 3] << 16);
@@ -897,8 +1015,8 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                   if (4 * g + e < cnt) {
-                    if (p.out_mode == 0) *d = (uint8_t)(dw[g] >> (8 * e));
-                    else if (p.out_mode == 1) *reinterpret_cast<int32_t*>(d) = v[4 * g + e];
+                    if (out_mode == 0) *d = (uint8_t)(dw[g] >> (8 * e));
+                    else if (out_mode == 1) *reinterpret_cast<int32_t*>(d) = v[4 * g + e];
                     else *reinterpret_cast<int16_t*>(d) = (int16_t)v[4 * g + e];
                     d += esz;
                     if (--until == 0) { d += jump * esz; until = OHW; }
@@ -919,9 +1037,9 @@ inline uint32_t recip(int64_t d) { return d <= 1 ? 0xffffffffu : (uint32_t)((1ul
 
 template <bool NHWC, bool SMALL, bool MULTI, int WT, int WPX, int WCH, int AF>
 hipError_t launch_cd(const CdParams& p, size_t lds, int64_t grid, hipStream_t st) {
-  auto kern = conv_direct_kernel<NHWC, SMALL, MULTI, WT, WPX, WCH, AF>;
-  static std::atomic<uint64_t> attr_set{0};
-  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set);
+  auto kern = p.has_rq ? conv_direct_kernel<NHWC, SMALL, MULTI, WT, WPX, WCH, AF, false> : conv_direct_kernel<NHWC, SMALL, MULTI, WT, WPX, WCH, AF, true>;
+  static std::atomic<uint64_t> attr_set[2];
+  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set[p.has_rq ? 0 : 1]);
   if (e != hipSuccess) return e;
   return launch_kernel(kern, dim3((unsigned)grid), dim3(64 * WPX * WCH), lds, st, p);
 }
@@ -1057,7 +1175,11 @@ bool try_qconv_direct(const GemmArgs& a, const ConvGeom& cg, int forced_shape, h
     }
   }
   if (best_shape < 0) return false;
-  best.through = ptr_aligned(a.out, 16) && (best.nseg == 1 ? (int64_t)cg.OH * cg.OW % 16 == 0 && (int64_t)best.TR * best.TW % 16 == 0 : cg.OW % 16 == 0);
+  // results that a lane's store takes: of one image (or row) and at 16 bytes; channel-last: of one pixel, one-byte ones a whole line's
+  const int64_t run = a.has_rq ? 16 : (a.acc16 ? 8 : 4);
+  best.through = cg.nhwc ? (a.has_rq ? a.N % 64 == 0 && ptr_aligned(a.out, 64) : a.N % run == 0 && ptr_aligned(a.out, 16))
+                         : ptr_aligned(a.out, 16) && (best.nseg == 1 ? (int64_t)cg.OH * cg.OW % run == 0 && (int64_t)best.TR * best.TW % run == 0
+                                                                     : cg.OW % run == 0);
   const int best_cg = best.small_c ? 1 : best.CC / 16;
   best.inv_unit1 = recip(cg.nhwc ? (int64_t)best.Wq * 4 * best_cg : (int64_t)best.rows * best.Wq);
   best.inv_unit2 = recip(cg.nhwc ? best_cg : best.Wq);
