@@ -91,11 +91,15 @@ __device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, u
 
 // NW: wavefronts per workgroup; AF: 32-pixel MFMA row blocks per wavefront (tiles of 32 * NW * AF
 // pixels); NU: staging units per thread; CK: input channels / 32.
-// OUT: the results, 0 requantized, 1 int32, 2 int16, each in a kernel of its own (us in one kernel for all and so: raw 64 -> 64 on
-// 64 x 56 x 56 17.3, 16.85, 16 bits 14.15, 13.6; 128 -> 128 on 64 x 28 x 28, 16 bits, 14.9, 14.2; 64 -> 64 on 16 x 56 x 56 7.04, 6.83).
+// OUT: the results, each in a kernel of its own (us in one kernel for all and so: raw 64 -> 64 on 64 x 56 x 56 17.3, 16.85, 16 bits 14.15, 13.6;
+// 128 -> 128 on 64 x 28 x 28, 16 bits, 14.9, 14.2; 64 -> 64 on 16 x 56 x 56 7.04, 6.83).  kFull: codes clipped to their container's whole
+// range, of a 32-bit accumulator; kClipped: all others (one kernel for both and so: one image of 64 -> 64 on 56 x 56 4.67 us, 4.52, 32 -> 96 on
+// 8 x 28 x 28 4.29, 4.12, 128 -> 128 on 64 x 28 x 28 13.3, 13.0).
+enum { kFull, kClipped, kWords, kHalves };
 template <int NW, int AF, int NU, int CK, int TN, int OUT>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(C3Params p) {
   constexpr int NT = 64 * NW;
+  constexpr bool kBytes = OUT == kFull || OUT == kClipped;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int t = threadIdx.x;
   const int lane = t & 63;
@@ -221,7 +225,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
     auto table = [&](const int32_t* q, int n) {
       return __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(q), 0, q ? 4 * n : 0, 0x00020000);
     };
-    const int rq_n = OUT == 0 ? (p.per_channel ? O : 1) : 0;
+    const int rq_n = kBytes ? (p.per_channel ? O : 1) : 0;
     const __amdgpu_buffer_rsrc_t rb = table(p.bias, O), rm = table(p.mult, rq_n), rs_ = table(p.shift, rq_n);
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
@@ -264,7 +268,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   for (int tn = 0; tn < TN; ++tn) {
     if (o0 + 32 * tn + j < O) {
       corr[tn] += p.corr_coef * s_sum[32 * tn + j];
-      if (OUT == 0 && !p.mult) mu[tn] = 1 << 30, sh[tn] -= 1;
+      if (kBytes && !p.mult) mu[tn] = 1 << 30, sh[tn] -= 1;
     } else {
       sh[tn] = 1;
     }
@@ -276,14 +280,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
   // clamped BEFORE that shift against limits scaled by 2^(sh-1), so that the shift can drop each
   // result straight into its byte of the output dword.  |acc| <= 9 C 2^14 < 2^30 and
   // |corr| <= 2^30, so acc + corr cannot wrap; with sh <= 19 and an 8-bit z nothing leaves 63 bits.
-  const bool exact = OUT == 0 && !p.rs.half_away && p.rs.z_out >= -256 &&
+  const bool exact = kBytes && !p.rs.half_away && p.rs.z_out >= -256 &&
                     p.rs.z_out <= 255 && __builtin_amdgcn_ballot_w64(!lane_ok) == 0;   // wavefront-uniform
-  const bool fold = exact && p.acc_wrap_shift == 0;
+  const bool fold = exact && (OUT == kFull || p.acc_wrap_shift == 0);
   // Clipped to the container's whole range: shift, clip and pack of two results are one instruction and no clip in front of
   // it (9 cycles of a SIMD per output instead of 13.4).
   // With a narrow accumulator the correction term is added in front of its wrapping instead (128 -> 128 on 64 x 28 x 28,
   // 16 bits: the general form's results took 4.6 us of 17.0, these 1.9 of 13.9).
-  const bool sat = exact && sat_range(p.rs);
+  const bool sat = exact && (OUT == kFull || sat_range(p.rs));
   const int32_t zc = p.rs.z_out + (sat ? sat_bias(p.rs) : 0);
   const uint32_t sflip = sat_flip(p.rs);
   int64_t k64[TN];
@@ -366,10 +370,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
     const int npix = rows * W;                           // valid pixels of this tile (a multiple of 4, as W is)
     if (32 * AF * wave >= npix) continue;                // (uniform: a wavefront beyond the tile's pixels)
     const uint32_t obase = (uint32_t)(b * O) * (uint32_t)HW + (uint32_t)(y0 * W);  // (less than 2^31 results)
-    if constexpr (OUT == 0) {
+    if constexpr (kBytes) {
       auto codes = [&](int f, int tn, uint32_t (&dw)[4]) {
         // (opaque: the sums and products that forms have in common are formed in front of all of them otherwise)
-        if (sat && !fold) {
+        if (OUT != kFull && sat && !fold) {
           const int32_t c = opaque(corr[tn]), m = opaque(mu[tn]);
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
@@ -391,7 +395,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
             ashr_sat_pair<1>(dw[g], r[2], r[3], s1[tn]);
             dw[g] ^= sflip;
           }
-        } else if (fold) {
+        } else if (OUT != kFull && fold) {
           const int32_t m = opaque(mu[tn]);
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
@@ -411,7 +415,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
             int32_t v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              v[e] = requant_general(wrap_acc_bits(acc[f][tn][4 * g + e] + c, p.acc_wrap_shift), m, sh[tn], p.rs);
+              v[e] = requant_general(OUT == kFull ? acc[f][tn][4 * g + e] + c : wrap_acc_bits(acc[f][tn][4 * g + e] + c, p.acc_wrap_shift), m, sh[tn], p.rs);
             }
             dw[g] = pack4(v[0], v[1], v[2], v[3]);
           }
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
     for (int f = 0; f < AF; ++f) {
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn) {
-        if constexpr (OUT == 1) {
+        if constexpr (OUT == kWords) {
           // a lane's 64 bytes go out by the quad: its channel t's from all four lanes
           uint32_t v[4][4];
           const int32_t c = opaque(corr[tn]);
@@ -493,12 +497,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
 
 template <int NW, int AF, int NU, int CK, int TN>
 hipError_t launch_c3_ck(const C3Params& p, size_t lds, int64_t grid, hipStream_t st) {
-  static std::atomic<uint64_t> attr_set[3];
+  static std::atomic<uint64_t> attr_set[4];
   // the LDS size depends on the geometry, not only on the template arguments: raise the kernel's
   // limit to the CU's 160 KB once, whatever this call needs
-  auto kern = p.out_mode == 0   ? conv3x3_nchw_kernel<NW, AF, NU, CK, TN, 0>
-              : p.out_mode == 1 ? conv3x3_nchw_kernel<NW, AF, NU, CK, TN, 1> : conv3x3_nchw_kernel<NW, AF, NU, CK, TN, 2>;
-  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set[p.out_mode]);
+  const int out = p.out_mode == 1 ? kWords : p.out_mode == 2 ? kHalves : sat_range(p.rs) && !p.rs.half_away && p.acc_wrap_shift == 0 ? kFull : kClipped;
+  auto kern = out == kFull      ? conv3x3_nchw_kernel<NW, AF, NU, CK, TN, kFull>
+              : out == kClipped ? conv3x3_nchw_kernel<NW, AF, NU, CK, TN, kClipped>
+              : out == kWords   ? conv3x3_nchw_kernel<NW, AF, NU, CK, TN, kWords> : conv3x3_nchw_kernel<NW, AF, NU, CK, TN, kHalves>;
+  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set[out]);
   if (e != hipSuccess) return e;
   return launch_kernel(kern, dim3((unsigned)grid), dim3(64 * NW), lds, st, p);
 }

@@ -213,7 +213,7 @@ __device__ __forceinline__ void swap_sixteens(uint32_t (&a)[4], uint32_t (&b)[4]
 // Whether the output's clip limits are its container's whole range, so that this saturation is the clip.  sat_bias is added
 // to the output zero point (inside the 64-bit constant of the folded forms) to centre the range on int8's, and sat_flip
 // undoes it in the packed dword: 0 and 0 for int8, -128 and 0x80 per byte for uint8.
-__device__ __forceinline__ bool sat_range(const RequantScalars& rs) { return rs.hi_rel - rs.lo_rel == 255; }
+__host__ __device__ __forceinline__ bool sat_range(const RequantScalars& rs) { return rs.hi_rel - rs.lo_rel == 255; }
 __device__ __forceinline__ int32_t sat_bias(const RequantScalars& rs) { return -128 - (rs.lo_rel + rs.z_out); }
 __device__ __forceinline__ uint32_t sat_flip(const RequantScalars& rs) { return rs.lo_rel + rs.z_out == 0 ? 0x80808080u : 0u; }
 
