@@ -6,6 +6,7 @@ so that they travel with the source tree.
 """
 from __future__ import annotations
 
+import concurrent.futures
 import glob
 import os
 import re
@@ -105,23 +106,23 @@ def _check_assembly(directory):
         raise RuntimeError("\n".join(found))
 
 
-def build(verbose: bool = False, jobs: int = 4) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     """Compile every .hip file and link the shared library, and the native module; always recompiles."""
     build_native(verbose)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    procs, objs = [], []
-    for src in sources():
-        obj = os.path.join(objdir, os.path.basename(src) + ".o")
-        objs.append(obj)
+    objs = [os.path.join(objdir, os.path.basename(src) + ".o") for src in sources()]
+
+    def compile_one(src, obj):
         cmd = [hipcc, *HIPCC_FLAGS, "-c", src, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-        if len(procs) >= jobs:
-            _drain(procs, verbose)
-    _drain(procs, verbose)
+        _drain([(src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))], verbose)
+
+    slow = ("qgemm_dma.hip", "conv3x3.hip", "conv_direct.hip", "dwconv.hip")  # first, so that none of them is waited for alone
+    with concurrent.futures.ThreadPoolExecutor(jobs) as pool:
+        list(pool.map(lambda so: compile_one(*so), sorted(zip(sources(), objs), key=lambda so: not so[0].endswith(slow))))
     _check_assembly(objdir)
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     subprocess.run(cmd, check=True)

@@ -146,6 +146,18 @@ __device__ __forceinline__ void load_channel_regs(const QgemmParams& p, int w0, 
 //     shift, clip and pack of two results are one instruction (ashr_sat_pair).
 enum { kRqGeneral, kRqFolded, kRqSat };
 
+// Results of a kernel, which has the forms for them alone: what other forms need is code that the compiler puts in front of all of them
+// and that a launch of one tile per CU waits for (us in one kernel and so: the four layers of 4096 x 768 51.3, 50.9; 3000 x 128 -> 1001 5.19, 5.07; 8192 x 64 -> 1024 6.42,
+// 6.27; the channel-last bottleneck of 16 x 28 x 28 x 256 12.8, 12.6).
+//   kOutFull: one byte, clipped to its whole range, of a 32-bit accumulator, rounding half up, an output zero point that kRqSat takes;
+//   kOutClipped: the same but for the clip or the zero point; both leave the tile in LDS first.
+//   kOutOther: what the straight-line epilogue writes.
+enum { kOutFull, kOutClipped, kOutOther };
+inline int qgemm_out(const QgemmParams& p) {
+  if (p.out_mode != 0 || p.acc_wrap_shift || p.rs.half_away) return kOutOther;
+  return sat_range(p.rs) && p.rs.z_out >= -128 && p.rs.z_out <= 255 ? kOutFull : kOutClipped;
+}
+
 // s_corr holds the weight row sums on entry (s_sum2, if given, a second part to add; it may be
 // s_mult); on exit s_corr/s_mult/s_shift hold the
 // per-channel terms and s_c64 the folded addend corr * mult + 2^(30+shift), with which
@@ -157,23 +169,26 @@ enum { kRqGeneral, kRqFolded, kRqSat };
 // point's 9 bits shifted by 31 + 21 below 2^61 as well).
 // s_vote: zero on entry.  The workgroup's vote is one word of LDS and one barrier (by __syncthreads_or, which has three, small
 // calls took 0.1 us longer: 170 x 64 -> 128 3.20, 3.09 so).
-template <int NT, int CH>
+template <int NT, int CH, int OUT>
 __device__ __forceinline__ int finish_channel_terms(const QgemmParams& p, const ChannelRegs<NT, CH>& r,
                                                     int32_t* s_corr, int32_t* s_mult,
                                                     int32_t* s_shift, int64_t* s_c64, int32_t* s_vote,
                                                     const int32_t* s_sum2 = nullptr,
                                                     int32_t* s_shm1 = nullptr) {
-  if (p.out_mode != 0) {  // raw results need the correction term alone (6132 x 640 -> 192 6.0 us through the vote below, 5.4 so)
+  if constexpr (OUT == kOutOther) {  // (raw 6132 x 640 -> 192 6.0 us through the vote below, 5.4 so)
 #pragma unroll
     for (int s = 0; s < ChannelRegs<NT, CH>::kSlots; ++s) {
       const int ci = (int)threadIdx.x + NT * s;
-      if (ci < CH) s_corr[ci] = r.bias[s] + p.corr_coef * (s_corr[ci] + (s_sum2 ? s_sum2[ci] : 0));
+      if (ci < CH) {
+        s_corr[ci] = r.bias[s] + p.corr_coef * (s_corr[ci] + (s_sum2 ? s_sum2[ci] : 0));
+        if (p.out_mode == 0) s_mult[ci] = r.mult[s], s_shift[ci] = r.shift[s];
+      }
     }
     __syncthreads();
     return kRqGeneral;
   }
   const int32_t z = p.rs.z_out;
-  const bool sat = s_shm1 && p.out_mode == 0 && sat_range(p.rs) && z >= -128 && z <= 255;  // (uniform)
+  constexpr bool sat = OUT == kOutFull;
   const int32_t zc = sat ? z + sat_bias(p.rs) : 0;
   int general = p.K > 65536, high = 0;
 #pragma unroll

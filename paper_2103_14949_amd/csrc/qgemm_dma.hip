@@ -65,6 +65,13 @@ constexpr int kBK = 64;       // k-bytes per stage (default; small tiles use 128
 // [dma_first(h), dma_first(h + 1)).
 constexpr int dma_first(int h, int l, int nh) { return (h * l + nh - 1) / nh; }
 
+// Whether a tile's results go through LDS where its ring was.
+template <int WP, int WQ, int TP, int TQ, int kStages, bool ACT_ON_P, int BK>
+constexpr bool can_stage() {
+  constexpr int BP = WP * TP * 32, BQ = WQ * TQ * 32;
+  return !ACT_ON_P && BQ * (BP + 16) <= kStages * (BP + BQ) * BK && (BQ * BP / 16) % (64 * WP * WQ) == 0;
+}
+
 // kStages: depth of the LDS ring; OCC: wavefronts per SIMD the register budget must allow
 // (two 4-wavefront workgroups per CU keep the matrix pipe busy across each other's barriers).
 // CONV: the activation operand is an implicit im2col view, kConvCopy: of a padded NHWC copy of the input
@@ -75,10 +82,11 @@ constexpr int dma_first(int h, int l, int nh) { return (h * l + nh - 1) / nh; }
 // k offset for all lanes, which travels in the DMA instruction's scalar offset: the main loop
 // then computes no addresses and has no branches.  Otherwise every DMA instruction gets per-lane
 // offsets (K tail, stages that straddle filter taps).
+// OUT: what results it writes (qgemm_common.h).
 // BK: k-bytes per stage, 64 or 128.  With 128 a DMA instruction fetches whole 128-byte lines (8 rows)
 // and a stage has four 32-k groups instead of two, i.e. half as many barriers per k.
 template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, int CONV, bool ACT_ON_P, bool FLIP,
-          bool UNIFORM, int BK = kBK>
+          bool UNIFORM, int BK, int OUT>
 __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParams p) {
   constexpr bool kDirect = CONV == kConvDirect;
   static_assert(!FLIP || (CONV != kConvCopy && !ACT_ON_P), "the copy is flipped; the others keep activations on Q");
@@ -538,27 +546,19 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
     }
   }
   __syncthreads();
-  const int form = finish_channel_terms<NT, CH>(p, chregs, s_corr, s_mult, s_shift, s_c64, &s_vote,
+  const int form = finish_channel_terms<NT, CH, OUT>(p, chregs, s_corr, s_mult, s_shift, s_c64, &s_vote,
                                                 kSplitSum ? s_mult : nullptr, s_shm1);
   HAGO_STAMP(p, 4);
-  if constexpr (!ACT_ON_P) {
-    constexpr bool kCanStage = BQ * (BP + 16) <= kStages * STAGE && (BQ * BP / 16) % NT == 0;
-    if constexpr (kCanStage) {
-      if (p.out_mode == 0 && !p.acc_wrap_shift && !p.rs.half_away) {
-        if (form == kRqSat)
-          qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqSat>(p, acc, p0, q0, s_corr, s_mult, s_shift,
-                                                              s_c64, s_shm1, smem);
-        else if (form == kRqFolded)
-          qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqFolded>(p, acc, p0, q0, s_corr, s_mult, s_shift,
-                                                                 s_c64, s_shm1, smem);
-        else
-          qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqGeneral>(p, acc, p0, q0, s_corr, s_mult, s_shift,
-                                                                  s_c64, s_shm1, smem);
-        return;
-      }
-    }
+  if constexpr (OUT == kOutOther) {
+    qgemm_epilogue<WP, WQ, TP, TQ, ACT_ON_P, kPixPerm>(p, acc, p0, q0, s_corr, s_mult, s_shift);
+  } else {
+    static_assert(can_stage<WP, WQ, TP, TQ, kStages, ACT_ON_P, BK>(), "the results are staged in the ring's place");
+    constexpr int kFast = OUT == kOutFull ? kRqSat : kRqFolded;
+    if (form == kFast)
+      qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kFast>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
+    else
+      qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqGeneral>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
   }
-  qgemm_epilogue<WP, WQ, TP, TQ, ACT_ON_P, kPixPerm>(p, acc, p0, q0, s_corr, s_mult, s_shift);
 }
 
 template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, int CONV, bool ACT_ON_P, bool FLIP,
@@ -570,11 +570,19 @@ hipError_t launch_dma_kernel(const QgemmParams& p, hipStream_t st) {
   const int P_ext = ACT_ON_P ? p.M : p.N;
   const int Q_ext = ACT_ON_P ? p.N : p.M;
   const int64_t tiles = (int64_t)((P_ext + BP - 1) / BP) * ((Q_ext + BQ - 1) / BQ);
-  auto kern = qgemm_dma_kernel<WP, WQ, TP, TQ, kStages, OCC, CONV, ACT_ON_P, FLIP, UNIFORM, BK>;
-  static std::atomic<uint64_t> attr_set{0};  // per kernel: the devices whose dynamic-LDS limit is raised
-  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), (int)lds, attr_set);
-  if (e != hipSuccess) return e;
-  return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ), lds, st, p);
+  static std::atomic<uint64_t> attr_set[3];  // per kernel: the devices whose dynamic-LDS limit is raised
+  auto run = [&]<int OUT>() {
+    auto kern = qgemm_dma_kernel<WP, WQ, TP, TQ, kStages, OCC, CONV, ACT_ON_P, FLIP, UNIFORM, BK, OUT>;
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), (int)lds, attr_set[OUT]);
+    if (e != hipSuccess) return e;
+    return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ), lds, st, p);
+  };
+  if constexpr (can_stage<WP, WQ, TP, TQ, kStages, ACT_ON_P, BK>()) {
+    const int out = qgemm_out(p);
+    if (out == kOutFull) return run.template operator()<kOutFull>();
+    if (out == kOutClipped) return run.template operator()<kOutClipped>();
+  }
+  return run.template operator()<kOutOther>();
 }
 
 // Picks the kernel variant: uint8 dense activations are flipped in the loop; shapes whose

@@ -22,7 +22,7 @@ namespace hago {
 
 namespace {
 
-template <int WP, int WQ, int TP, int TQ, bool FLIP>
+template <int WP, int WQ, int TP, int TQ, bool FLIP, int OUT>
 __global__ __launch_bounds__(64 * WP * WQ, 1) void qgemm_line_kernel(QgemmParams p) {
   constexpr int BK = 128, NH = 4;   // bytes and 32-k groups of a stage
   constexpr int RPI = 8, CPR = 8;   // rows of a DMA instruction, 16-byte chunks of a row
@@ -194,19 +194,18 @@ __global__ __launch_bounds__(64 * WP * WQ, 1) void qgemm_line_kernel(QgemmParams
   v += __shfl_xor(v, 32);
   if (wave < WBLK && fhalf == 0) s_corr[wave * 32 + frow] = v;
   __syncthreads();
-  const int form = finish_channel_terms<NT, BP>(p, chregs, s_corr, s_mult, s_shift, s_c64, &s_vote, nullptr, s_shm1);
+  const int form = finish_channel_terms<NT, BP, OUT>(p, chregs, s_corr, s_mult, s_shift, s_c64, &s_vote, nullptr, s_shm1);
   HAGO_STAMP(p, 4);
   static_assert(BQ * (BP + 16) <= 2 * STAGE && (BQ * BP / 16) % NT == 0, "the results are staged in the ring's place");
-  if (p.out_mode == 0 && !p.acc_wrap_shift && !p.rs.half_away) {
-    if (form == kRqSat)
-      qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqSat>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
-    else if (form == kRqFolded)
-      qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqFolded>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
+  if constexpr (OUT == kOutOther) {
+    qgemm_epilogue<WP, WQ, TP, TQ, false>(p, acc, p0, q0, s_corr, s_mult, s_shift);
+  } else {
+    constexpr int kFast = OUT == kOutFull ? kRqSat : kRqFolded;
+    if (form == kFast)
+      qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kFast>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
     else
       qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqGeneral>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
-    return;
   }
-  qgemm_epilogue<WP, WQ, TP, TQ, false>(p, acc, p0, q0, s_corr, s_mult, s_shift);
 }
 
 template <int WP, int WQ, int TP, int TQ>
@@ -219,8 +218,14 @@ hipError_t launch_line(const QgemmParams& p, hipStream_t st) {
     if (e != hipSuccess) return e;
     return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ), lds, st, p);
   };
-  static std::atomic<uint64_t> set_u8{0}, set_i8{0};  // per kernel: the devices whose dynamic-LDS limit is raised
-  return p.act_xor4 ? run(qgemm_line_kernel<WP, WQ, TP, TQ, true>, set_u8) : run(qgemm_line_kernel<WP, WQ, TP, TQ, false>, set_i8);
+  static std::atomic<uint64_t> attr_set[2][3];  // per kernel: the devices whose dynamic-LDS limit is raised
+  const int out = qgemm_out(p);
+  auto run_out = [&]<bool FLIP>() {
+    return out == kOutFull      ? run(qgemm_line_kernel<WP, WQ, TP, TQ, FLIP, kOutFull>, attr_set[FLIP][out])
+           : out == kOutClipped ? run(qgemm_line_kernel<WP, WQ, TP, TQ, FLIP, kOutClipped>, attr_set[FLIP][out])
+                                : run(qgemm_line_kernel<WP, WQ, TP, TQ, FLIP, kOutOther>, attr_set[FLIP][out]);
+  };
+  return p.act_xor4 ? run_out.template operator()<true>() : run_out.template operator()<false>();
 }
 
 }  // namespace
