@@ -19,6 +19,10 @@ constexpr int kThreads = 256;
 
 // Forms of the requantize arithmetic: see dw_rows3x3_kernel.
 enum { kGeneral, kFold, kSat };
+// CODES: kernels for codes that are clipped to their container's whole range (of a 32-bit accumulator, rounding half up), of activations
+// that need a flip or none, and for everything else; a wavefront waits for the instructions of the forms that its kernel holds
+// (us in one kernel and so, of a block with its 1x1 layers: 42 x 28 x 28 x 432 29.1, 28.6; 32 x 56 x 56 x 144 at stride 2 17.4, 17.1).
+enum { kOther, kFullPlain, kFullFlipped };
 
 struct DwArgs {
   const uint8_t* act;
@@ -186,7 +190,7 @@ __device__ __forceinline__ DwChannel dw_channel(const DwArgs& p, int c) {
 //   through it to memory, while other wavefronts work; kFours the same by four rows of a quarter, which are one run of the image: they
 //   meet in LDS and its lanes with a strip write 16 bytes each.
 enum { kL2, kThrough, kFours };
-template <int MODE, bool ACC16, bool WIDE, bool RAGGED, int OUT = kL2>
+template <int MODE, bool ACC16, bool WIDE, bool RAGGED, int OUT = kL2, int CODES = kOther>
 __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(uint32_t gx, uint32_t mid, uint32_t count, uint32_t inv_x, uint32_t inv_mid,
                                                                DwArgs p, int32_t rpc, int32_t nsegs, int32_t segw) {
   // grid: x = groups of four channels, of each its column segments (which are not equally wide: next to each other, every XCD has as
@@ -417,16 +421,14 @@ __global__ __launch_bounds__(kThreads) void dw_rows3x3_kernel(uint32_t gx, uint3
   const bool fold = MODE == 0 && !ACC16 && sh >= 0 && sh <= 19 && corr >= -(1 << 30) && corr <= (1 << 30) &&
                     z >= -256 && z <= 255 && !p.rs.half_away;
   const bool sat = fold && sh >= 1 && sat_range(p.rs), no_flip = x4 == 0 && pad4 == 0;
-  if (sat && no_flip)
-    rows.template operator()<kSat, true>();
-  else if (sat)
-    rows.template operator()<kSat, false>();
-  else if (fold && no_flip)
-    rows.template operator()<kFold, true>();
-  else if (fold)
-    rows.template operator()<kFold, false>();
-  else
-    rows.template operator()<kGeneral, false>();
+  if constexpr (CODES != kOther) {
+    if (sat) rows.template operator()<kSat, CODES == kFullPlain>();
+    else rows.template operator()<kGeneral, false>();
+  } else {
+    if (fold && no_flip) rows.template operator()<kFold, true>();
+    else if (fold) rows.template operator()<kFold, false>();
+    else rows.template operator()<kGeneral, false>();
+  }
 }
 
 // NCHW 3x3 pad 1, stride S = 1 or 2, W >= 4 (OW >= 4), on the matrix cores.
@@ -455,7 +457,7 @@ struct DwTile {
 };
 
 // NJ: groups of four columns per lane (2 or 4).
-template <int MODE, int S, int CPK, int NJ>
+template <int MODE, int S, int CPK, int NJ, int CODES>
 __global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(uint32_t gx, uint32_t ids, uint32_t inv_x, DwArgs p, DwTile q) {
   typedef int32_t v2i __attribute__((ext_vector_type(2)));
   typedef int32_t v4i __attribute__((ext_vector_type(4)));
@@ -695,16 +697,14 @@ __global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(uint32_t gx, uint3
                     corr_a >= -(1 << 30) && corr_a <= (1 << 30) && corr_b >= -(1 << 30) && corr_b <= (1 << 30) &&
                     z >= -256 && z <= 255 && !p.rs.half_away;
   const bool sat = fold && ka.sh >= 1 && kb.sh >= 1 && sat_range(p.rs);
-  if (sat && plain)
-    run.template operator()<kSat, true>();
-  else if (sat)
-    run.template operator()<kSat, false>();
-  else if (fold && plain)
-    run.template operator()<kFold, true>();
-  else if (fold)
-    run.template operator()<kFold, false>();
-  else
-    run.template operator()<kGeneral, false>();
+  if constexpr (CODES != kOther) {
+    if (sat) run.template operator()<kSat, CODES == kFullPlain>();
+    else run.template operator()<kGeneral, false>();
+  } else {
+    if (fold && plain) run.template operator()<kFold, true>();
+    else if (fold) run.template operator()<kFold, false>();
+    else run.template operator()<kGeneral, false>();
+  }
 }
 
 // Channel-last 3x3, pad 1, stride S = 1 or 2, C >= 4, any alignment.  A thread owns four consecutive channels (one dword
@@ -715,7 +715,7 @@ __global__ __launch_bounds__(kThreads, 4) void dw_mfma_kernel(uint32_t gx, uint3
 // predecessor multiplied byte by byte, 16 per output, and unpacked the weights of a thread for 8 outputs: 32 x 56 x 56 x 144
 // took 30.7 us; stride 2 had no kernel of its own and took 43.)  The last quad of channels and the last strip are moved
 // back to end with the pixel or row: bytes written twice get the same value.
-template <int MODE, int S>
+template <int MODE, int S, int CODES>
 __global__ __launch_bounds__(kThreads) void dw_nhwc3x3_kernel(uint32_t gx, uint32_t mid, uint32_t count, uint32_t inv_x, uint32_t inv_mid,
                                                                DwArgs p, int32_t c4, uint32_t inv_c4, int32_t strips, int32_t run) {
   typedef int32_t v2i __attribute__((ext_vector_type(2)));
@@ -922,16 +922,14 @@ __global__ __launch_bounds__(kThreads) void dw_nhwc3x3_kernel(uint32_t gx, uint3
       }
     }
   };
-  if (sat && plain)
-    body.template operator()<kSat, true>();
-  else if (sat)
-    body.template operator()<kSat, false>();
-  else if (fold && plain)
-    body.template operator()<kFold, true>();
-  else if (fold)
-    body.template operator()<kFold, false>();
-  else
-    body.template operator()<kGeneral, false>();
+  if constexpr (CODES != kOther) {
+    if (sat) body.template operator()<kSat, CODES == kFullPlain>();
+    else body.template operator()<kGeneral, false>();
+  } else {
+    if (fold && plain) body.template operator()<kFold, true>();
+    else if (fold) body.template operator()<kFold, false>();
+    else body.template operator()<kGeneral, false>();
+  }
 }
 
 }  // namespace
@@ -958,6 +956,9 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
   const int64_t total = (int64_t)cg.B * cg.O * cg.OH * cg.OW;
   if (total == 0) return hipSuccess;
 
+  const bool full = a.has_rq && !a.acc16 && a.acc_wrap_shift == 0 && !p.rs.half_away && p.rs.z_out >= -256 && p.rs.z_out <= 255 && sat_range(p.rs);
+  const int codes = !full ? kOther : p.act_xor == 0 && (p.z_a & 0xff) == 0 ? kFullPlain : kFullFlipped;
+
   const size_t esz = a.has_rq ? 1 : (a.acc16 ? 2 : 4);
   const bool k3 = cg.KH == 3 && cg.KW == 3 && cg.pad_h == 1 && cg.pad_w == 1;
   const bool s1 = k3 && cg.stride_h == 1 && cg.stride_w == 1, s2 = k3 && cg.stride_h == 2 && cg.stride_w == 2;
@@ -975,8 +976,12 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
     const int64_t runs = (cg.OH + run - 1) / run;
     run = (cg.OH + runs - 1) / runs;
     if (runs <= 65535 && ((int64_t)c4 * strips + kThreads) * c4 < (1ll << 32)) {
-      auto kern = s1 ? (p.out_mode == 1 ? dw_nhwc3x3_kernel<1, 1> : p.out_mode == 2 ? dw_nhwc3x3_kernel<2, 1> : dw_nhwc3x3_kernel<0, 1>)
-                     : (p.out_mode == 1 ? dw_nhwc3x3_kernel<1, 2> : p.out_mode == 2 ? dw_nhwc3x3_kernel<2, 2> : dw_nhwc3x3_kernel<0, 2>);
+#define HAGO_DW_NHWC(S_) \
+  (p.out_mode == 1 ? dw_nhwc3x3_kernel<1, S_, kOther> : p.out_mode == 2 ? dw_nhwc3x3_kernel<2, S_, kOther>      \
+   : codes == kFullPlain ? dw_nhwc3x3_kernel<0, S_, kFullPlain>                                        \
+   : codes == kFullFlipped ? dw_nhwc3x3_kernel<0, S_, kFullFlipped> : dw_nhwc3x3_kernel<0, S_, kOther>)
+      auto kern = s1 ? HAGO_DW_NHWC(1) : HAGO_DW_NHWC(2);
+#undef HAGO_DW_NHWC
       return launch_kernel(kern, dim3((unsigned)blocks, (unsigned)runs, (unsigned)cg.B), dim3(kThreads), 0, st,
                          (uint32_t)blocks, (uint32_t)runs, (uint32_t)(blocks * runs * cg.B), inverse(blocks, blocks * runs * cg.B),
                          inverse(runs, runs * cg.B), p, c4,
@@ -1010,7 +1015,10 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
 #define HAGO_DW_ROWS(WIDE_, RAG_, OUT_)                                                                \
   (p.out_mode == 1 ? dw_rows3x3_kernel<1, false, WIDE_, RAG_>                                          \
    : p.out_mode == 2 ? dw_rows3x3_kernel<2, true, WIDE_, RAG_>                                         \
-   : p.acc16 ? dw_rows3x3_kernel<0, true, WIDE_, RAG_, OUT_> : dw_rows3x3_kernel<0, false, WIDE_, RAG_, OUT_>)
+   : p.acc16 ? dw_rows3x3_kernel<0, true, WIDE_, RAG_, OUT_>                                           \
+   : codes == kFullPlain ? dw_rows3x3_kernel<0, false, WIDE_, RAG_, OUT_, kFullPlain>                  \
+   : codes == kFullFlipped ? dw_rows3x3_kernel<0, false, WIDE_, RAG_, OUT_, kFullFlipped>              \
+                           : dw_rows3x3_kernel<0, false, WIDE_, RAG_, OUT_>)
       auto kern = nsegs > 1 ? (ragged ? HAGO_DW_ROWS(true, true, kThrough) : HAGO_DW_ROWS(true, false, kThrough))
                   : ragged ? (how == kL2 ? HAGO_DW_ROWS(false, true, kL2) : HAGO_DW_ROWS(false, true, kThrough))
                            : (how == kFours ? HAGO_DW_ROWS(false, false, kFours) : HAGO_DW_ROWS(false, false, kThrough));
@@ -1046,7 +1054,9 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
     if (tiles < (1ll << 26) && gy <= 65535 && waves_x * q.nt < (1ll << 32) && gx <= max_blocks(kThreads) &&
         (flat || ((int64_t)cg.H * cg.W * 2 < (1ll << 31) && (int64_t)cg.OH * cg.OW * 2 * (int64_t)esz < (1ll << 31)))) {
 #define HAGO_DW_MODE(S_, CPK_, NJ_) \
-  (p.out_mode == 1 ? dw_mfma_kernel<1, S_, CPK_, NJ_> : p.out_mode == 2 ? dw_mfma_kernel<2, S_, CPK_, NJ_> : dw_mfma_kernel<0, S_, CPK_, NJ_>)
+  (p.out_mode == 1 ? dw_mfma_kernel<1, S_, CPK_, NJ_, kOther> : p.out_mode == 2 ? dw_mfma_kernel<2, S_, CPK_, NJ_, kOther> \
+   : codes == kFullPlain ? dw_mfma_kernel<0, S_, CPK_, NJ_, kFullPlain>                                \
+   : codes == kFullFlipped ? dw_mfma_kernel<0, S_, CPK_, NJ_, kFullFlipped> : dw_mfma_kernel<0, S_, CPK_, NJ_, kOther>)
       auto kern = S == 2 ? (two ? HAGO_DW_MODE(2, 2, 2) : HAGO_DW_MODE(2, 1, 2))
                          : (!two ? HAGO_DW_MODE(1, 1, 4) : cg.OW > 8 ? HAGO_DW_MODE(1, 2, 4) : HAGO_DW_MODE(1, 2, 2));
 #undef HAGO_DW_MODE

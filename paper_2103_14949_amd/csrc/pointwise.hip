@@ -68,13 +68,15 @@ struct PwArgs {
 //   CH = 1, 2, 3 (C <= 96): all input channels of a tile are transposed once and stay in registers for several blocks of
 //     output channels (88 -> 528 on 8 x 56 x 56: 11.2 us with a wavefront for every block, 9.4 so).
 //   CH = 5: five steps of 32 channels are in flight at a time.
+//   RANGE: codes clipped to their container's whole range (32-bit accumulator, rounding half up), in a kernel without the other forms (us in
+//     one kernel and so: 24 -> 144 on 32 x 56 x 56 6.6, 6.5; 32 -> 192 on 4 x 112 x 112 4.7, 4.55; 432 -> 72 and 72 -> 432 with their depthwise layer 24.2, 24.0).
 //   KS = 4: four wavefronts share a tile and block, a quarter of the steps each, and add up through LDS (576 -> 96
 //     channels of one 14 x 14 image are six tiles, 18 steps in a row each, else: 8.6 us, 5.8 so).
 typedef uint32_t u32_u __attribute__((aligned(1)));
 typedef v4i v4i_u __attribute__((aligned(1)));
 typedef int v2i_u __attribute__((ext_vector_type(2), aligned(1)));
 
-template <int MODE, bool ACC16, int KS, int CH, bool SMALL>
+template <int MODE, bool ACC16, int KS, int CH, bool SMALL, bool RANGE>
 __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
   constexpr int kPart = 65;  // dwords of a lane's partial sums: 64 accumulators and the row sum (odd: no bank conflicts)
   __shared__ int32_t lds[KS == 1 ? 1 : KS * 64 * kPart];
@@ -284,12 +286,13 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
     const bool lane_ok = rq.sh >= 0 && rq.sh <= 19 && corr >= -(1 << 30) && corr <= (1 << 30);
     const bool fold = MODE == 0 && !ACC16 && C < (1 << 15) && rs.z_out >= -256 && rs.z_out <= 255 &&
                       !rs.half_away && __builtin_amdgcn_ballot_w64(!lane_ok) == 0;  // wavefront-uniform
-    if (fold && sat_range(rs) && __builtin_amdgcn_ballot_w64(n < N && rq.sh < 1) == 0)
-      store_all.template operator()<kSat>();
-    else if (fold)
-      store_all.template operator()<kFold>();
-    else
-      store_all.template operator()<kGeneral>();
+    if constexpr (RANGE) {
+      if (fold && __builtin_amdgcn_ballot_w64(n < N && rq.sh < 1) == 0) store_all.template operator()<kSat>();
+      else store_all.template operator()<kGeneral>();
+    } else {
+      if (fold) store_all.template operator()<kFold>();
+      else store_all.template operator()<kGeneral>();
+    }
   };
 
   if constexpr (KS == 1 && CH <= 3) {
@@ -420,8 +423,14 @@ hipError_t launch(PwArgs q, hipStream_t st) {
   // Four wavefronts per tile and block up to where one each fills half of the SIMDs (us with four and with one: 384 -> 64
   // on 8 x 56 x 56, 400 of them, 6.0, 7.9; 480 -> 80 on 2 x 112 x 112, 588, 10.5, 8.3).
   auto run = [&]<int KS, int CH>() {
-    const auto kern = KS == 1 && q.HW < 128 ? pw_nchw_kernel<MODE, ACC16, KS, CH, KS == 1> : pw_nchw_kernel<MODE, ACC16, KS, CH, false>;
-    return launch_kernel(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
+    auto go = [&]<bool RANGE>() {
+      const auto kern = KS == 1 && q.HW < 128 ? pw_nchw_kernel<MODE, ACC16, KS, CH, KS == 1, RANGE> : pw_nchw_kernel<MODE, ACC16, KS, CH, false, RANGE>;
+      return launch_kernel(kern, dim3((unsigned)ids), dim3(64 * KS), 0, st, q);
+    };
+    if constexpr (MODE == 0 && !ACC16) {
+      if (sat_range(q.rs) && !q.rs.half_away && q.rs.z_out >= -256 && q.rs.z_out <= 255) return go.template operator()<true>();
+    }
+    return go.template operator()<false>();
   };
   if (q.C > 64 && ids <= 512) return run.template operator()<4, 5>();
   if (q.C <= 32) return run.template operator()<1, 1>();
