@@ -78,9 +78,11 @@ __device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, u
 
 // WT: how weights are staged.  9: NCHW 3x3, four channels' nine taps at once; 2: contiguous channels (1x1, NHWC); 0: byte
 // by byte (any kernel; the few-channel form).  MULTI: several chunks of channels.  WPX x WCH wavefronts over pixels and channels, each AF x 32
-// pixels by 64 channels.  RAW: sums go out, as 16 or 32 bits (in one kernel with the requantized form every layer of that took 0.3 us more:
-// 64 -> 128 3x3 stride 2 on 32 x 56 x 56 10.7, 10.4 by the requantized form alone before, 10.0 so).
-template <bool NHWC, bool SMALL, bool MULTI, int WT, int WPX, int WCH, int AF, bool RAW>
+// pixels by 64 channels.  OUT: sums go out, as 16 or 32 bits; or codes clipped to their container's
+// whole range (and terms small enough to fold but for single channels'); or any codes.  (Us in one kernel, with the raw form apart, and so: 64 -> 128
+// 3x3 stride 2 on 32 x 56 x 56 10.7, 10.0, 10.0; 3 -> 64 7x7 on 8 x 224 x 224 9.9, 9.7 with the two kinds of codes apart; 3 -> 72 5x5 on 8 x 112 x 112 11.5, 11.3.)
+enum { kSums, kFullCodes, kAnyCodes };
+template <bool NHWC, bool SMALL, bool MULTI, int WT, int WPX, int WCH, int AF, int OUT>
 __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams p) {
   constexpr int NT = 64 * WPX * WCH;
   constexpr int NU = NHWC ? 8 : (AF == 2 ? 2 : 3);  // staging units per thread
@@ -91,6 +93,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   // 13.0, 14.5, raw 20.4, 21.5; 64 -> 64 3x3 on 32 x 56 x 56 13.4, 14.6).
   constexpr bool kTight = NHWC && AF == 2;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  constexpr bool RAW = OUT == kSums;
   const int out_mode = RAW ? (p.out_mode == 1 ? 1 : 2) : 0;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -528,7 +531,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
   const int32_t lo_abs = p.rs.lo_rel + p.rs.z_out, hi_abs = p.rs.hi_rel + p.rs.z_out;
   // results clipped to the container's whole range: shift, clip and pack of two are one instruction (the lane's channels
   // differ in the channel-last form, so it shifts first)
-  const bool sat = sat_range(p.rs);
+  constexpr bool sat = OUT == kFullCodes;
   const int32_t zc = p.rs.z_out + (sat ? sat_bias(p.rs) : 0);
   const uint32_t sflip = sat_flip(p.rs);
   int ch = 0;         // chunk
@@ -799,7 +802,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
             int32_t v[4];
-            if (fold) {
+            if (!sat && fold) {
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
                 const int4 k = s_fold[cl + 4 * g + e];
@@ -944,7 +947,7 @@ __global__ __launch_bounds__(64 * WPX * WCH, 2) void conv_direct_kernel(CdParams
               dw[g] ^= sflip;
               __builtin_amdgcn_sched_barrier(0);  // (four products at a time: all sixteen would spill)
             }
-          } else if (fold) {
+          } else if (!sat && fold) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               auto one = [&]<int E>() {
@@ -1037,9 +1040,13 @@ inline uint32_t recip(int64_t d) { return d <= 1 ? 0xffffffffu : (uint32_t)((1ul
 
 template <bool NHWC, bool SMALL, bool MULTI, int WT, int WPX, int WCH, int AF>
 hipError_t launch_cd(const CdParams& p, size_t lds, int64_t grid, hipStream_t st) {
-  auto kern = p.has_rq ? conv_direct_kernel<NHWC, SMALL, MULTI, WT, WPX, WCH, AF, false> : conv_direct_kernel<NHWC, SMALL, MULTI, WT, WPX, WCH, AF, true>;
-  static std::atomic<uint64_t> attr_set[2];
-  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set[p.has_rq ? 0 : 1]);
+  const bool full = sat_range(p.rs) && !p.rs.half_away && p.acc_wrap_shift == 0 && p.rs.z_out >= -256 && p.rs.z_out <= 255 && p.C * p.KH * p.KW <= 65536;
+  const int out = !p.has_rq ? kSums : full ? kFullCodes : kAnyCodes;
+  auto kern = out == kSums        ? conv_direct_kernel<NHWC, SMALL, MULTI, WT, WPX, WCH, AF, kSums>
+              : out == kFullCodes ? conv_direct_kernel<NHWC, SMALL, MULTI, WT, WPX, WCH, AF, kFullCodes>
+                                  : conv_direct_kernel<NHWC, SMALL, MULTI, WT, WPX, WCH, AF, kAnyCodes>;
+  static std::atomic<uint64_t> attr_set[3];
+  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 160 * 1024, attr_set[out]);
   if (e != hipSuccess) return e;
   return launch_kernel(kern, dim3((unsigned)grid), dim3(64 * WPX * WCH), lds, st, p);
 }
