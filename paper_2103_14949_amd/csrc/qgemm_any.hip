@@ -77,7 +77,10 @@ __device__ __forceinline__ int lds_off(int row, int chunk) { return row * kRow +
 
 // KS sets of WP x WQ wavefronts take the stage's 32-k groups in turn and meet in LDS at the end: with one tile per
 // CU a second set halves what every wavefront loads, converts and multiplies per stage.
-template <bool I16, int WP, int WQ, int TP, int TQ, int KS>
+// OUT: codes as kOutFull (qgemm_common.h), any other codes, or sums (us in one kernel and so: 2000 x 700 -> 1003 8.1, 7.7, raw 8.0, 7.3; raw 3000 x 101 -> 1984 8.9, 8.1; 1021 x 1283
+// -> 1001 9.0, 8.8; int16 1024 x 768 -> 768 8.3, 8.0).
+enum { kAnyCodes = kOutFull + 1, kSums };
+template <bool I16, int WP, int WQ, int TP, int TQ, int KS, int OUT>
 __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmParams p) {
   constexpr int kEsz = I16 ? 2 : 1;
   constexpr int NT = 64 * WP * WQ * KS, BP = 32 * WP * TP, BQ = 32 * WQ * TQ;
@@ -205,7 +208,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
     bias[n] = 0; mult[n] = 0; shift[n] = 1;
     if (unit == 0 && r < BP && p0 + r < p.N) {
       if (p.bias) bias[n] = p.bias[p0 + r];
-      if (p.has_rq) {
+      if (OUT != kSums) {
         mult[n] = rq_mult(p.mult, p.per_channel ? p0 + r : 0);
         shift[n] = rq_shift(p.mult, p.shift, p.per_channel ? p0 + r : 0);
       }
@@ -247,7 +250,8 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
   // ---- channel terms: the UPR threads of a row hold its sum.  SAT: the output is clipped to its container's whole range
   // and every shift is 1 to 21: the rounding term and the zero point are one constant, and the packing saturates (products
   // are at most 2^62, the constant below 2^61 + 2^51).
-  const bool sat_ok = p.out_mode == 0 && sat_range(p.rs) && !p.rs.half_away && p.rs.z_out >= -128 && p.rs.z_out <= 255;
+  constexpr bool sat_ok = OUT == kOutFull;
+  const int out_mode = OUT != kSums ? 0 : (p.out_mode == 1 ? 1 : 2);
   int no_sat = !sat_ok;
 #pragma unroll
   for (int n = 0; n < NU; ++n) {
@@ -268,7 +272,9 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
       }
     }
   }
-  const bool sat = __syncthreads_or(no_sat) == 0;  // (also: the stages have been consumed)
+  bool sat = false;
+  if constexpr (OUT == kOutFull) sat = __syncthreads_or(no_sat) == 0;  // (also: the stages have been consumed)
+  else __syncthreads();
 
   // ---- the sets' sums meet in LDS: of two, each finishes half of the register groups
   static_assert(KS <= 2, "each set finishes half");
@@ -317,7 +323,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
   }
 
   // ---- requantize into an LDS tile in output order, then rows of 16-byte pieces at any alignment
-  const int esz = p.out_mode == 0 ? 1 : (p.out_mode == 1 ? 4 : 2);
+  const int esz = out_mode == 0 ? 1 : (out_mode == 1 ? 4 : 2);
   const uint32_t sflip = sat_flip(p.rs);
 #pragma unroll
   for (int i = 0; i < TP; ++i)
@@ -338,7 +344,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
         for (int e = 0; e < 4; ++e) {
           v[e] = val[i][j][g][e] + cc[e];
           if constexpr (I16) v[e] += s_asum[r];
-          if (p.acc_wrap_shift) v[e] = wrap_acc_bits(v[e], p.acc_wrap_shift);
+          if (OUT != kOutFull && p.acc_wrap_shift) v[e] = wrap_acc_bits(v[e], p.acc_wrap_shift);
         }
         uint8_t* dst = smem + r * RS + ch * esz;
         if (sat) {
@@ -348,11 +354,11 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
           ashr_sat_pair<0>(dw, v[0], v[1], 0);
           ashr_sat_pair<1>(dw, v[2], v[3], 0);
           *reinterpret_cast<uint32_t*>(dst) = dw ^ sflip;
-        } else if (p.out_mode == 0) {
+        } else if (out_mode == 0) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] = requant_general(v[e], mm[e], hh[e], p.rs);
           *reinterpret_cast<uint32_t*>(dst) = pack4_perm(v[0], v[1], v[2], v[3]);
-        } else if (p.out_mode == 1) {
+        } else if (out_mode == 1) {
           *reinterpret_cast<int4*>(dst) = make_int4(v[0], v[1], v[2], v[3]);
         } else {
           *reinterpret_cast<uint2*>(dst) =
@@ -402,9 +408,11 @@ hipError_t launch_staged(QgemmParams p, hipStream_t st) {
   constexpr int most = stages > out ? stages : out, lds = most > sums ? most : sums;
   const int64_t tiles = (int64_t)((p.N + BP - 1) / BP) * ((p.M + BQ - 1) / BQ);
   p.line_out = p.N % 64 == 0 && ptr_aligned(p.out, 64);
-  auto kern = qgemm_staged_kernel<I16, WP, WQ, TP, TQ, KS>;
-  static std::atomic<uint64_t> attr_set{0};
-  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds, attr_set);
+  const int form = p.out_mode != 0 ? kSums : qgemm_out(p) == kOutFull ? kOutFull : kAnyCodes;
+  auto kern = form == kSums      ? qgemm_staged_kernel<I16, WP, WQ, TP, TQ, KS, kSums>
+              : form == kOutFull ? qgemm_staged_kernel<I16, WP, WQ, TP, TQ, KS, kOutFull> : qgemm_staged_kernel<I16, WP, WQ, TP, TQ, KS, kAnyCodes>;
+  static std::atomic<uint64_t> attr_set[3];
+  hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds, attr_set[form]);
   if (e != hipSuccess) return e;
   return launch_tiles(kern, p, tiles, 64 * WP * WQ * KS, lds, st);
 }
