@@ -377,13 +377,15 @@ __device__ __forceinline__ void qgemm_epilogue_dense_staged(const QgemmParams& p
 
 // Four results of one output row, channels n .. n + 3, where they exist.  Raw int32 ones go through the L2 where they are
 // aligned: eight lanes write 128 bytes of a row.
+template <bool RQ>
 __device__ __forceinline__ void store_four(const QgemmParams& p, int m, int n, const int32_t (&v)[4]) {
+  const int out_mode = RQ ? 0 : (p.out_mode == 1 ? 1 : 2);
   const int64_t o = (int64_t)m * p.N + n;
   if (n + 4 <= p.N) {
-    if (p.out_mode == 0) {
+    if (out_mode == 0) {
       typedef uint32_t u32_any __attribute__((aligned(1)));
       *reinterpret_cast<u32_any*>(static_cast<uint8_t*>(p.out) + o) = pack4_perm(v[0], v[1], v[2], v[3]);
-    } else if (p.out_mode == 1) {
+    } else if (out_mode == 1) {
       const bool through = (p.N & 3) == 0 && (reinterpret_cast<uintptr_t>(p.out) & 15u) == 0;
       store16(through, static_cast<int32_t*>(p.out) + o, (uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
     } else {
@@ -396,8 +398,8 @@ __device__ __forceinline__ void store_four(const QgemmParams& p, int m, int n, c
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     if (n + e >= p.N) break;
-    if (p.out_mode == 0) static_cast<uint8_t*>(p.out)[o + e] = (uint8_t)v[e];
-    else if (p.out_mode == 1) static_cast<int32_t*>(p.out)[o + e] = v[e];
+    if (out_mode == 0) static_cast<uint8_t*>(p.out)[o + e] = (uint8_t)v[e];
+    else if (out_mode == 1) static_cast<int32_t*>(p.out)[o + e] = v[e];
     else static_cast<int16_t*>(p.out)[o + e] = (int16_t)v[e];
   }
 }

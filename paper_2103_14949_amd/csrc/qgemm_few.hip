@@ -47,8 +47,9 @@ __device__ __forceinline__ void load_dword(const v4i& r, uint32_t lds_addr, uint
 }
 
 // The first 14 dwords of the arguments are in scalar registers when a wavefront starts; the others, in `p`, take as long as a
-// load from memory.  KB: bytes of a row.  minor: tiles of the index that runs first, bit 31: that is the channels'.
-template <bool I16, bool MIS, int NW>
+// load from memory.  KB: bytes of a row.  minor: tiles of the index that runs first, bit 31: that is the channels'.  RQ: codes
+// go out, else sums (us in one kernel and so: 8081 x 112 -> 123 4.05, 3.8; 128 x 3072 -> 768 4.45, 4.32; 64 x 256 -> 128 2.77, 2.68, raw 2.60, 2.53).
+template <bool I16, bool MIS, int NW, bool RQ>
 __global__ __launch_bounds__(64 * NW, 2) void qgemm_few_kernel(const uint8_t* act, const int8_t* wgt, int M, int N, uint32_t KB,
                                                                     int blocks, uint32_t count, uint32_t minor, uint32_t inv_minor,
                                                                     uint32_t size_w, uint32_t size_a, QgemmParams p) {
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(64 * NW, 2) void qgemm_few_kernel(const uint8_t* ac
   // bias, are eight loads of a tile for these two, which the operands of the CU's other tiles wait for: 8081 x 112 -> 123 4.6 us, 4.2 so;
   // 5523 x 128 -> 34 3.7, 3.4; 13945 x 42 -> 42 4.5, 4.0; over 1300 layers 0.98 where requantized.  The bias so too: raw layers 3 % slower.)
   int32_t c_mult = 0, c_shift = 0;
-  if (p.has_rq && wave == 0) {
+  if (RQ && wave == 0) {
     const int bytes = p.per_channel ? 4 * N : 4, at = p.per_channel ? 4 * ((int)n0 + frow) : 0;
     const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(p.mult), 0, p.mult ? bytes : 0, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(p.shift), 0, bytes, 0x00020000);
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(64 * NW, 2) void qgemm_few_kernel(const uint8_t* ac
   // partial sums, four channels by four (channels 8 g + 4 fhalf .. of row frow), and the weights' sums behind them
   const int parts = NW < blocks ? NW : blocks;
   constexpr int kScales = 8 * kPitch + 128;
-  if (p.has_rq && wave == 0) *reinterpret_cast<int32_t*>(smem + kScales + 4 * lane) = fhalf ? c_shift : c_mult;
+  if (RQ && wave == 0) *reinterpret_cast<int32_t*>(smem + kScales + 4 * lane) = fhalf ? c_shift : c_mult;
   if (wave < parts) {
     if constexpr (I16) asum += __shfl_xor(asum, 32);
     uint8_t* const s = smem + wave * SLOT + fhalf * kPitch + frow * 16;
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(64 * NW, 2) void qgemm_few_kernel(const uint8_t* ac
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = wrap_acc_bits(v[e], p.acc_wrap_shift);
   }
-  if (p.has_rq) {
+  if constexpr (RQ) {
     const v4i mult = *reinterpret_cast<const v4i*>(smem + kScales + 16 * fc), shift = *reinterpret_cast<const v4i*>(smem + kScales + 128 + 16 * fc);
     const int32_t away = p.rs.half_away ? -1 : 0, lo = p.rs.lo_rel, hi = p.rs.hi_rel, z = p.rs.z_out;
 #pragma unroll
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(64 * NW, 2) void qgemm_few_kernel(const uint8_t* ac
     }
   }
   const int32_t out[4] = {v[0], v[1], v[2], v[3]};
-  store_four(p, m, n, out);
+  store_four<RQ>(p, m, n, out);
 }
 
 }  // namespace
@@ -327,9 +328,9 @@ hipError_t launch_qgemm_few(const QgemmParams& p, bool i16, int waves, hipStream
   auto size = [&](const void* ptr, int64_t rows) { return run_size(rows, kb, (uint32_t)(reinterpret_cast<uintptr_t>(ptr) & 3)); };
   auto run = [&]<bool I16, bool MIS, int NW>() {
     const int slots = blocks < kDepth * NW ? blocks : kDepth * NW;
-    const auto kern = qgemm_few_kernel<I16, MIS, NW>;
-    static std::atomic<uint64_t> attr_set{0};  // per kernel: the devices whose dynamic-LDS limit is raised
-    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), kDepth * NW * slot_bytes<MIS>(), attr_set);
+    const auto kern = p.has_rq ? qgemm_few_kernel<I16, MIS, NW, true> : qgemm_few_kernel<I16, MIS, NW, false>;
+    static std::atomic<uint64_t> attr_set[2];  // per kernel: the devices whose dynamic-LDS limit is raised
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), kDepth * NW * slot_bytes<MIS>(), attr_set[p.has_rq != 0]);
     if (e != hipSuccess) return e;
     return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * NW), slots * slot_bytes<MIS>(), st, p.act, p.wgt, p.M, p.N, (uint32_t)kb, blocks,
                        (uint32_t)tiles, (uint32_t)minor | (channels_first ? 0x80000000u : 0u), inv, size(p.wgt, p.N), size(p.act, p.M), p);
