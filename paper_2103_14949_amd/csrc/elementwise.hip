@@ -431,9 +431,9 @@ template <typename T>
 __device__ __forceinline__ auto load4(const T* p, int64_t i) {
   return __builtin_nontemporal_load(reinterpret_cast<const typename AnyVec<T>::T*>(p + i));
 }
-template <typename T, typename V>
-__device__ __forceinline__ void store4(T* p, int64_t i, V v, bool through = true) {
-  if (through) store_through(p + i, v);
+template <bool THROUGH = true, typename T, typename V>
+__device__ __forceinline__ void store4(T* p, int64_t i, V v) {
+  if constexpr (THROUGH) store_through(p + i, v);
   else __builtin_nontemporal_store((typename AnyVec<T>::T)v, reinterpret_cast<typename AnyVec<T>::T*>(p + i));
 }
 
@@ -497,7 +497,8 @@ __device__ __forceinline__ bool quotients4(v4f x, const ScaleZero (&p)[4], v4f& 
   return false;
 }
 
-template <bool WRAP, bool RC>
+// THROUGH: results go through the L2.
+template <bool WRAP, bool RC, bool THROUGH = true>
 struct SimquantOp {
   typedef v4f Vec;
   typedef ScaleZero Par;
@@ -508,7 +509,6 @@ struct SimquantOp {
   const int32_t* zp;
   float lo, hi;
   int wrap_bits, wrap_signed;
-  bool through = true;
   __device__ Par par(int64_t c) const { return scale_zero<RC>(scale, zp, c); }
   __device__ void keep(Kept& k, const int64_t (&c)[4], bool run) const { k.read(scale, zp, c, run); }
   __device__ void four(int64_t i, Vec v, const Kept& k) const { four(i, v, k.p); }
@@ -520,13 +520,13 @@ struct SimquantOp {
   __device__ void four(int64_t i, Vec v, const Par (&p)[4]) const {
     v4f n;
     quotients4<RC>(v, p, n);
-    store4(y, i, v4f{of(n.x, p[0]), of(n.y, p[1]), of(n.z, p[2]), of(n.w, p[3])}, through);
+    store4<THROUGH>(y, i, v4f{of(n.x, p[0]), of(n.y, p[1]), of(n.z, p[2]), of(n.w, p[3])});
   }
   __device__ void one(int64_t i, const Par& p) const { y[i] = of(rintf(x[i] / p.s), p); }
 };
 
 // OP as in quant_rows_kernel.
-template <typename Q, int OP, bool RC>
+template <typename Q, int OP, bool RC, bool THROUGH = true>
 struct QuantOp {
   typedef typename std::conditional<OP == 1, typename QVec<Q>::T, v4f>::type Vec;
   typedef ScaleZero Par;
@@ -537,7 +537,6 @@ struct QuantOp {
   const float* scale;
   const int32_t* zp;
   float lo, hi;
-  bool through = true;
   __device__ Par par(int64_t c) const { return scale_zero<RC && OP != 1>(scale, zp, c); }
   __device__ void keep(Kept& k, const int64_t (&c)[4], bool run) const { k.read(scale, zp, c, run); }
   __device__ void four(int64_t i, Vec v, const Kept& k) const { four(i, v, k.p); }
@@ -554,11 +553,11 @@ struct QuantOp {
     } else {
       v4f n;
       quotients4<RC>(v, p, n);
-      store4(static_cast<Q*>(out), i, pack_codes<Q>(quantize_of(n.x, p[0].zf, lo, hi), quantize_of(n.y, p[1].zf, lo, hi),
-                                                    quantize_of(n.z, p[2].zf, lo, hi), quantize_of(n.w, p[3].zf, lo, hi)), OP != 2 || through);
+      store4<THROUGH>(static_cast<Q*>(out), i, pack_codes<Q>(quantize_of(n.x, p[0].zf, lo, hi), quantize_of(n.y, p[1].zf, lo, hi),
+                                                             quantize_of(n.z, p[2].zf, lo, hi), quantize_of(n.w, p[3].zf, lo, hi)));
       if constexpr (OP == 2)
-        store4(out2, i, v4f{simquant_of(n.x, p[0].s, p[0].zf, lo, hi), simquant_of(n.y, p[1].s, p[1].zf, lo, hi),
-                            simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)}, through);
+        store4<THROUGH>(out2, i, v4f{simquant_of(n.x, p[0].s, p[0].zf, lo, hi), simquant_of(n.y, p[1].s, p[1].zf, lo, hi),
+                                     simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)});
     }
   }
   __device__ void one(int64_t i, const Par& p) const {
@@ -779,19 +778,21 @@ inline bool periodic_split(int64_t total, int64_t channels, int64_t inner, int u
   return ((g->spans + rows - 1) / rows) * g->nseg < (1ll << 31);
 }
 
-// Periodic / flat launch of an operator; OpP keeps reciprocals for the periodic kernel, OpF does not.
-template <class OpP, class OpF, class... A>
+// Periodic / flat launch of an operator; OpP keeps reciprocals for the periodic kernel, OpF does not; OpN is OpP with results that do not go
+// through the L2, where there is such a form.  (As a member of the operator the choice made its arguments 120 bytes, no multiple of sixteen, and a
+// launch of it cost the host 0.3 us more.)
+template <class OpP, class OpF, class OpN, class... A>
 hipError_t launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStream_t st, A... args) {
   constexpr int U = kVecPerLane;
   const ChannelDiv d = channel_div(total, channels, inner);
   SpanArgs g;
   if (periodic_split(total, channels, inner, U, &g)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
-    OpP op{args...};
     // fp32 to fp32, with codes or without, in spans that end inside lines: such lines cost the write through the L2 more than it gains once 10 MB and more
     // are read beside it (channel-last 50000 x 65 simquant 7.9 us through it, 7.2 nontemporal; 30000 x 66 4.8, 5.7)
-    if constexpr (requires { op.through; }) op.through = g.seg_len % 4 == 0 || total < 2500000;
-    return launch_kernel(periodic_kernel<OpP, U>, dim3((unsigned)wgs), dim3(kThreads), 0, st, op, g, d);
+    if (g.seg_len % 4 == 0 || total < 2500000)
+      return launch_kernel(periodic_kernel<OpP, U>, dim3((unsigned)wgs), dim3(kThreads), 0, st, OpP{args...}, g, d);
+    return launch_kernel(periodic_kernel<OpN, U>, dim3((unsigned)wgs), dim3(kThreads), 0, st, OpN{args...}, g, d);
   }
   // one vector per lane while that does not fill the chip, four beyond
   const int64_t nvec = total / 4 > 0 ? total / 4 : 1;
@@ -856,9 +857,9 @@ __global__ __launch_bounds__(kThreads) void simquant_batched_ragged_kernel(
       v4f n;
       quotients4<PERIODIC>(a[u], p, n);
       const float lo = clips.lo[b], hi = clips.hi[b];
-      store4(y + (int64_t)b * total, 4 * (v + u * step),
+      store4<false>(y + (int64_t)b * total, 4 * (v + u * step),
              v4f{simquant_of(n.x, p[0].s, p[0].zf, lo, hi), simquant_of(n.y, p[1].s, p[1].zf, lo, hi),
-                 simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)}, false);
+                 simquant_of(n.z, p[2].s, p[2].zf, lo, hi), simquant_of(n.w, p[3].s, p[3].zf, lo, hi)});
     };
     if constexpr (PERIODIC) {
       for (int b = 0; b < nbatch; ++b) {
@@ -1172,7 +1173,7 @@ hipError_t launch_simquant(const float* x, float* y, int64_t outer, int64_t chan
                        (int32_t)(per_channel ? channels : 1), inner_vec, nseg, seg_len, scale, zp,
                        per_channel, JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi, 0, 0);
   }
-  return launch_ragged<SimquantOp<false, true>, SimquantOp<false, false>>(
+  return launch_ragged<SimquantOp<false, true>, SimquantOp<false, false>, SimquantOp<false, true, false>>(
       total, per_channel ? channels : 1, per_channel ? inner : total, st, x, y, scale, zp, lo, hi, 0, 0);
 }
 
@@ -1194,7 +1195,7 @@ hipError_t launch_simquant_wrap(const float* x, float* y, int64_t outer, int64_t
                        per_channel, JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi,
                        wrap_bits, wrap_signed);
   }
-  return launch_ragged<SimquantOp<true, true>, SimquantOp<true, false>>(
+  return launch_ragged<SimquantOp<true, true>, SimquantOp<true, false>, SimquantOp<true, true, false>>(
       total, per_channel ? channels : 1, per_channel ? inner : total, st, x, y, scale, zp, lo, hi, wrap_bits, wrap_signed);
 }
 
@@ -1248,7 +1249,7 @@ static hipError_t launch_quant_t(const void* in, void* out, float* out2, int64_t
                        inner_vec, nseg, seg_len, scale, zp, per_channel,
                        JobDiv{reciprocal32(nseg), reciprocal32(per_channel ? channels : 1)}, lo, hi);
   }
-  return launch_ragged<QuantOp<Q, OP, OP != 1>, QuantOp<Q, OP, false>>(
+  return launch_ragged<QuantOp<Q, OP, OP != 1>, QuantOp<Q, OP, false>, QuantOp<Q, OP, OP != 1, OP != 2>>(
       total, per_channel ? channels : 1, per_channel ? inner : total, st, in, out, out2, scale, zp, lo, hi);
 }
 
@@ -1371,8 +1372,8 @@ static hipError_t launch_requantize_t(const AccT* acc, int64_t outer, int64_t ch
   }
   const int64_t ch = pc ? channels : 1, in = pc ? inner : total;
   if (rq.half_away)
-    return launch_ragged<RequantOp<AccT, true>, RequantOp<AccT, true>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
-  return launch_ragged<RequantOp<AccT, false>, RequantOp<AccT, false>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
+    return launch_ragged<RequantOp<AccT, true>, RequantOp<AccT, true>, RequantOp<AccT, true>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
+  return launch_ragged<RequantOp<AccT, false>, RequantOp<AccT, false>, RequantOp<AccT, false>>(total, ch, in, st, acc, out, rq.multiplier, rq.shift, rs);
 }
 
 hipError_t launch_requantize(const void* acc, int acc16, int64_t outer, int64_t channels,
