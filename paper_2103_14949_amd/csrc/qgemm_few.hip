@@ -46,13 +46,34 @@ __device__ __forceinline__ void load_dword(const v4i& r, uint32_t lds_addr, uint
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" : : "s"(lds_addr), "v"(o), "s"(r) : "memory", "m0");
 }
 
-// The first 14 dwords of the arguments are in scalar registers when a wavefront starts; the others, in `p`, take as long as a
-// load from memory.  KB: bytes of a row.  minor: tiles of the index that runs first, bit 31: that is the channels'.  RQ: codes
-// go out, else sums (us in one kernel and so: 8081 x 112 -> 123 4.05, 3.8; 128 x 3072 -> 768 4.45, 4.32; 64 x 256 -> 128 2.77, 2.68, raw 2.60, 2.53).
-template <bool I16, bool MIS, int NW, bool RQ>
+// What the kernel needs of a layer's parameters.  With the scalars in front of them the arguments are 108 bytes: up to 112 a launch costs the
+// host 2.75 us, from 116 on 3.5 (a launch of an empty kernel, of whatever more; the arguments that the runtime adds for the size of
+// the grid count as 256).
+struct FewParams {
+  const int32_t* bias;
+  void* out;
+  const int32_t* mult;
+  const int32_t* shift;
+  int32_t corr_coef, z_out, lo_rel, hi_rel;
+  uint32_t flags;
+};
+enum : uint32_t { kPerChannel = 1, kHalfAway = 2, kFlip = 4, kHalves = 8 };  // and, from bit 8 on, acc_wrap_shift
+
+inline FewParams few_params(const QgemmParams& p) {
+  return FewParams{p.bias, p.out, p.mult, p.shift, p.corr_coef, p.rs.z_out, p.rs.lo_rel, p.rs.hi_rel,
+                   (p.per_channel ? kPerChannel : 0u) | (p.rs.half_away ? kHalfAway : 0u) | (p.act_xor4 ? kFlip : 0u) | (p.out_mode == 2 ? kHalves : 0u) |
+                       (uint32_t)p.acc_wrap_shift << 8};
+}
+
+// The first 14 dwords of the arguments are in scalar registers when a wavefront starts; the others, in `q`, take as long as a
+// load from memory.  KB: bytes of a row.  minor: tiles of the index that runs first, bit 31: that is the channels'.  KIND: bit 0: int16,
+// bit 1: codes go out, else sums (us in one kernel and so: 8081 x 112 -> 123 4.05, 3.8; 128 x 3072 -> 768 4.45, 4.32; 64 x 256 -> 128 2.77, 2.68, raw
+// 2.60, 2.53).
+template <int KIND, bool MIS, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void qgemm_few_kernel(const uint8_t* act, const int8_t* wgt, int M, int N, uint32_t KB,
                                                                     int blocks, uint32_t count, uint32_t minor, uint32_t inv_minor,
-                                                                    uint32_t size_w, uint32_t size_a, QgemmParams p) {
+                                                                    uint32_t size_w, uint32_t size_a, FewParams q) {
+  constexpr bool I16 = KIND & 1, RQ = KIND & 2;
   constexpr int SLOT = slot_bytes<MIS>(), L = MIS ? 10 : 8;  // loads of a block
   constexpr int GB = I16 ? 64 : 32, NG = kBlock / GB;        // bytes of 32 elements; 32-k groups of a block
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -112,7 +133,15 @@ __global__ __launch_bounds__(64 * NW, 2) void qgemm_few_kernel(const uint8_t* ac
 #pragma unroll
   for (v16i& a : acc.a) asm volatile("" : "+v"(a));
   asm volatile("" : "+v"(place), "+v"(sh_w), "+v"(sh_a));
-  fetch_arguments<48 + sizeof(QgemmParams)>();
+  fetch_arguments<56 + sizeof(FewParams)>();
+  QgemmParams p{};
+  p.bias = q.bias, p.out = q.out, p.mult = q.mult, p.shift = q.shift, p.N = N;
+  p.per_channel = q.flags & kPerChannel ? 1 : 0;
+  p.acc_wrap_shift = (int32_t)(q.flags >> 8);
+  p.out_mode = RQ ? 0 : (q.flags & kHalves ? 2 : 1);
+  p.act_xor4 = q.flags & kFlip ? 0x80808080u : 0u;
+  p.corr_coef = q.corr_coef;
+  p.rs = RequantScalars{q.z_out, q.lo_rel, q.hi_rel, q.flags & kHalfAway ? 1 : 0};
   // finishing threads: row t / 8, channels 4 (t % 8) ..
   const int fr = t >> 3, fc = t & 7, m = (int)m0 + fr, n = (int)n0 + 4 * fc;
   v4i c_bias = {0, 0, 0, 0};
@@ -326,14 +355,15 @@ hipError_t launch_qgemm_few(const QgemmParams& p, bool i16, int waves, hipStream
   const int64_t minor = channels_first ? tiles_n : tiles_m;
   const uint32_t inv = minor > 1 ? (uint32_t)(((1ull << 32) + minor - 1) / minor) : 0u;
   auto size = [&](const void* ptr, int64_t rows) { return run_size(rows, kb, (uint32_t)(reinterpret_cast<uintptr_t>(ptr) & 3)); };
+  const FewParams q = few_params(p);
   auto run = [&]<bool I16, bool MIS, int NW>() {
     const int slots = blocks < kDepth * NW ? blocks : kDepth * NW;
-    const auto kern = p.has_rq ? qgemm_few_kernel<I16, MIS, NW, true> : qgemm_few_kernel<I16, MIS, NW, false>;
+    const auto kern = p.has_rq ? qgemm_few_kernel<I16 + 2, MIS, NW> : qgemm_few_kernel<I16, MIS, NW>;
     static std::atomic<uint64_t> attr_set[2];  // per kernel: the devices whose dynamic-LDS limit is raised
     const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), kDepth * NW * slot_bytes<MIS>(), attr_set[p.has_rq != 0]);
     if (e != hipSuccess) return e;
     return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * NW), slots * slot_bytes<MIS>(), st, p.act, p.wgt, p.M, p.N, (uint32_t)kb, blocks,
-                       (uint32_t)tiles, (uint32_t)minor | (channels_first ? 0x80000000u : 0u), inv, size(p.wgt, p.N), size(p.act, p.M), p);
+                       (uint32_t)tiles, (uint32_t)minor | (channels_first ? 0x80000000u : 0u), inv, size(p.wgt, p.N), size(p.act, p.M), q);
   };
   auto by_form = [&]<bool I16, bool MIS>() {
     // eight wavefronts for tiles that are alone on their CU and have blocks for them (128 x 3072 -> 768 4.3 us, 4.7 with
