@@ -87,7 +87,7 @@ constexpr bool can_stage() {
 // and a stage has four 32-k groups instead of two, i.e. half as many barriers per k.
 template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, int CONV, bool ACT_ON_P, bool FLIP,
           bool UNIFORM, int BK, int OUT>
-__global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParams p) {
+__device__ __forceinline__ void qgemm_dma_tile(const QgemmParams& p) {
   constexpr bool kDirect = CONV == kConvDirect;
   static_assert(!FLIP || (CONV != kConvCopy && !ACT_ON_P), "the copy is flipped; the others keep activations on Q");
   constexpr bool kPixPerm = CONV && ACT_ON_P;
@@ -561,6 +561,19 @@ __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(QgemmParam
   }
 }
 
+// One kernel per kind of results, told apart by its argument.
+struct FullParams { QgemmParams p; };
+struct ClippedParams { QgemmParams p; };
+#define HAGO_DMA_KERNEL(PARAMS_, OUT_, P_)                                                                                     \
+  template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, int CONV, bool ACT_ON_P, bool FLIP, bool UNIFORM, int BK>    \
+  __global__ __launch_bounds__(64 * WP * WQ, OCC) void qgemm_dma_kernel(PARAMS_ a) {                                           \
+    qgemm_dma_tile<WP, WQ, TP, TQ, kStages, OCC, CONV, ACT_ON_P, FLIP, UNIFORM, BK, OUT_>(P_);                                 \
+  }
+HAGO_DMA_KERNEL(FullParams, kOutFull, a.p)
+HAGO_DMA_KERNEL(ClippedParams, kOutClipped, a.p)
+HAGO_DMA_KERNEL(QgemmParams, kOutOther, a)
+#undef HAGO_DMA_KERNEL
+
 template <int WP, int WQ, int TP, int TQ, int kStages, int OCC, int CONV, bool ACT_ON_P, bool FLIP,
           bool UNIFORM, int BK>
 hipError_t launch_dma_kernel(const QgemmParams& p, hipStream_t st) {
@@ -571,18 +584,18 @@ hipError_t launch_dma_kernel(const QgemmParams& p, hipStream_t st) {
   const int Q_ext = ACT_ON_P ? p.N : p.M;
   const int64_t tiles = (int64_t)((P_ext + BP - 1) / BP) * ((Q_ext + BQ - 1) / BQ);
   static std::atomic<uint64_t> attr_set[3];  // per kernel: the devices whose dynamic-LDS limit is raised
-  auto run = [&]<int OUT>() {
-    auto kern = qgemm_dma_kernel<WP, WQ, TP, TQ, kStages, OCC, CONV, ACT_ON_P, FLIP, UNIFORM, BK, OUT>;
-    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), (int)lds, attr_set[OUT]);
+  auto run = [&]<typename Params>(const Params& a, int out) {
+    void (*const kern)(Params) = qgemm_dma_kernel<WP, WQ, TP, TQ, kStages, OCC, CONV, ACT_ON_P, FLIP, UNIFORM, BK>;
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), (int)lds, attr_set[out]);
     if (e != hipSuccess) return e;
-    return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ), lds, st, p);
+    return launch_kernel(kern, dim3((unsigned)tiles), dim3(64 * WP * WQ), lds, st, a);
   };
   if constexpr (can_stage<WP, WQ, TP, TQ, kStages, ACT_ON_P, BK>()) {
     const int out = qgemm_out(p);
-    if (out == kOutFull) return run.template operator()<kOutFull>();
-    if (out == kOutClipped) return run.template operator()<kOutClipped>();
+    if (out == kOutFull) return run(FullParams{p}, out);
+    if (out == kOutClipped) return run(ClippedParams{p}, out);
   }
-  return run.template operator()<kOutOther>();
+  return run(p, kOutOther);
 }
 
 // Picks the kernel variant: uint8 dense activations are flipped in the loop; shapes whose
