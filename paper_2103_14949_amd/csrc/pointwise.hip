@@ -34,18 +34,18 @@ struct PwArgs {
   void* out;
   const int32_t* mult;
   const int32_t* shift;
-  int32_t B, C, HW, N;
+  int32_t C, HW, N;
   int32_t tiles_per_img;
-  int64_t tiles;
   int32_t per_wave;            // blocks of 32 output channels of a wavefront
   int32_t nblocks;             // such groups of blocks
   uint32_t inv_tpi, inv_nb;    // ceil(2^32 / tiles_per_img) and of nblocks where that divides exactly, else 0
-  uint32_t act_xor4;   // 0x80808080 for uint8 activations
+  uint32_t ids;        // wavefronts (or four of them) of the launch
   int32_t corr_coef;   // off - z_a
-  int32_t per_channel;
-  int32_t through;     // results go through the L2
+  uint32_t flags;
   RequantScalars rs;
 };
+static_assert(sizeof(PwArgs) <= 112, "a launch with more costs the host 0.7 us more");
+enum : uint32_t { kFlip = 1, kPerChannel = 2, kThrough = 4 };  // uint8 activations; a multiplier per channel; results go through the L2
 
 // MODE 0: requantized 8-bit, 1: raw int32, 2: raw int16; ACC16: accumulator wraps to 16 bits.
 // A wavefront owns 128 consecutive pixels of one image and a block (or several) of 32 output channels, as four MFMA row
@@ -86,11 +86,13 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
   // 128-byte line in general, so neighbouring tiles share lines, and the blocks of output channels of a tile share its
   // input; numbering them so that an XCD gets a run of consecutive ones lets that XCD's L2 serve the shared lines (with
   // the plain order every such line was fetched from memory by two XCDs: 1.5 times the bytes).
-  const uint32_t id = xcd_run(blockIdx.x, gridDim.x);
+  const uint32_t id = xcd_run(blockIdx.x, p.ids);
   const uint32_t tile = p.inv_nb ? __umulhi(id, p.inv_nb) : id / (uint32_t)p.nblocks;
   const int blk0 = (int)(id - tile * (uint32_t)p.nblocks) * p.per_wave;
   const int b = (int)(p.inv_tpi ? __umulhi(tile, p.inv_tpi) : tile / (uint32_t)p.tiles_per_img);
   const int C = p.C, HW = p.HW, N = p.N;
+  const uint32_t act_xor4 = p.flags & kFlip ? 0x80808080u : 0u;
+  const bool per_channel = p.flags & kPerChannel, through = p.flags & kThrough;
   int pix0 = ((int)tile - b * p.tiles_per_img) * 128;
   if (HW >= 128 && pix0 > HW - 128) pix0 = HW - 128;
   const int i = lane & 31, h = lane >> 5;
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
       const uint32_t t1 = __builtin_amdgcn_perm(bq, a, 0x07030602u);  // a2 b2 a3 b3
       const uint32_t t2 = __builtin_amdgcn_perm(d, c, 0x05010400u);   // c0 d0 c1 d1
       const uint32_t t3 = __builtin_amdgcn_perm(d, c, 0x07030602u);   // c2 d2 c3 d3
-      const uint32_t x4 = p.act_xor4 & live(s, m);  // (bytes that were not fetched are 0 and stay it)
+      const uint32_t x4 = act_xor4 & live(s, m);  // (bytes that were not fetched are 0 and stay it)
       af[0][m] = (int)(__builtin_amdgcn_perm(t2, t0, 0x05040100u) ^ x4);
       af[1][m] = (int)(__builtin_amdgcn_perm(t2, t0, 0x07060302u) ^ x4);
       af[2][m] = (int)(__builtin_amdgcn_perm(t3, t1, 0x05040100u) ^ x4);
@@ -166,8 +168,8 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
     if (n < N) {
       if (p.bias) r.bias = p.bias[n];
       if (MODE == 0) {
-        r.m = rq_mult(p.mult, p.per_channel ? n : 0);
-        r.sh = rq_shift(p.mult, p.shift, p.per_channel ? n : 0);
+        r.m = rq_mult(p.mult, per_channel ? n : 0);
+        r.sh = rq_shift(p.mult, p.shift, per_channel ? n : 0);
       }
     }
     return r;
@@ -253,7 +255,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
             if (pq > HW - 4) pq = HW - 4;
             uint8_t* const dst = static_cast<uint8_t*>(p.out) + (((int64_t)b * N + nn) * HW + pq) * kEsz;
             if constexpr (MODE == 1) {
-              if (ok) store16(!SMALL && p.through, dst, raw[t][0], raw[t][1], raw[t][2], raw[t][3]);
+              if (ok) store16(!SMALL && through, dst, raw[t][0], raw[t][1], raw[t][2], raw[t][3]);
             } else {
               if (ok) *reinterpret_cast<v2i_u*>(dst) = v2i_u{(int)raw[t][0], (int)raw[t][1]};
             }
@@ -279,7 +281,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
 #pragma unroll
         for (int t = 0; t < kGroups; ++t) {
           const int nn = (n & ~3) + t;
-          if (nn < N) store16(p.through, row(nn) + pg, dw[t][0], dw[t][1], dw[t][2], dw[t][3]);
+          if (nn < N) store16(through, row(nn) + pg, dw[t][0], dw[t][1], dw[t][2], dw[t][3]);
         }
       }
     };
@@ -400,7 +402,7 @@ constexpr int waves_per_simd(int mode, bool acc16, int ch, bool small) {
 }
 
 template <int MODE, bool ACC16>
-hipError_t launch(PwArgs q, hipStream_t st) {
+hipError_t launch(PwArgs q, int64_t tiles, hipStream_t st) {
   const int32_t blocks = (q.N + 31) / 32;
   // C <= 96: several blocks per wavefront.  Above 32 channels as few as bring all wavefronts into one round, by the registers of the
   // variant (us with 1, 2 and 3 blocks: 72 -> 432 on 42 x 28 x 28, 4116 blocks, two wavefronts per SIMD, 13.5, 12.8,
@@ -409,16 +411,17 @@ hipError_t launch(PwArgs q, hipStream_t st) {
   // variants such a count is 1.5 % from the best of five, with two wavefronts above 64 channels and three below for all of them 2.1.
   // Where one round cannot hold them, and up to 32 channels, so many blocks that 1.5 wavefronts per SIMD are left (24 -> 144
   // -> 24 with its depthwise layer on 32 x 56 x 56, 4000 blocks of the first, 24.2, 23.3).
-  const int64_t all = q.tiles * blocks, slots = 1024 * waves_per_simd(MODE, ACC16, q.C > 64 ? 3 : 2, q.HW < 128);
+  const int64_t all = tiles * blocks, slots = 1024 * waves_per_simd(MODE, ACC16, q.C > 64 ? 3 : 2, q.HW < 128);
   int64_t per = 1;
-  if (q.C <= 32 || q.tiles > slots) per = q.C <= 96 && all >= 1536 ? all / 1536 : 1;
-  else if (q.C <= 96) per = (blocks + slots / q.tiles - 1) / (slots / q.tiles);
+  if (q.C <= 32 || tiles > slots) per = q.C <= 96 && all >= 1536 ? all / 1536 : 1;
+  else if (q.C <= 96) per = (blocks + slots / tiles - 1) / (slots / tiles);
   q.per_wave = (int32_t)(per < blocks ? per : blocks);
   q.nblocks = (blocks + q.per_wave - 1) / q.per_wave;
   q.per_wave = (blocks + q.nblocks - 1) / q.nblocks;
-  const int64_t ids = q.tiles * q.nblocks;
+  const int64_t ids = tiles * q.nblocks;
+  q.ids = (uint32_t)ids;
   auto inverse = [&](int32_t d, int64_t n) { return d > 1 && n * d < (1ll << 32) ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; };
-  q.inv_tpi = inverse(q.tiles_per_img, q.tiles);
+  q.inv_tpi = inverse(q.tiles_per_img, tiles);
   q.inv_nb = inverse(q.nblocks, ids);
   // Four wavefronts per tile and block up to where one each fills half of the SIMDs (us with four and with one: 384 -> 64
   // on 8 x 56 x 56, 400 of them, 6.0, 7.9; 480 -> 80 on 2 x 112 x 112, 588, 10.5, 8.3).
@@ -460,20 +463,19 @@ bool try_qconv_pointwise_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t
   p.out = a.out;
   p.mult = a.rq.multiplier;
   p.shift = a.rq.shift;
-  p.B = cg.B; p.C = cg.C; p.HW = (int32_t)HW; p.N = cg.O;
+  p.C = cg.C; p.HW = (int32_t)HW; p.N = cg.O;
   p.tiles_per_img = (int32_t)((HW + 127) / 128);
-  p.tiles = (int64_t)cg.B * p.tiles_per_img;
-  p.act_xor4 = a.act_unsigned ? 0x80808080u : 0u;
+  const int64_t tiles = (int64_t)cg.B * p.tiles_per_img;
   p.corr_coef = (a.act_unsigned ? 128 : 0) - a.act_zero_point;
-  p.per_channel = a.rq.per_channel;
   p.rs = RequantScalars{a.rq.z_out, a.rq.clip_lo - a.rq.z_out, a.rq.clip_hi - a.rq.z_out, a.rq.half_away};
   // 64 bytes of a row at a time, 128 where they are one-byte results, go through the L2 unless they begin off 16 bytes: one-byte results
   // of a row of 900 and more do there too (24 -> 144 on 32 x 56 x 56, us through it and not: 6.4, 7.7; 32 -> 192 on 4 x 112 x 112 4.55, 5.69; 12 x 55 x 55 4.83, 5.05; 24 x 35 x 35
   // 4.53, 4.71; 32 x 23 x 23 4.10, 4.00; 64 x 13 x 13 3.87, 3.72; raw on 16 x 28 x 28 3.82, 4.64; on 8 x 57 x 57 7.35, 7.06).
-  p.through = a.has_rq ? (HW % 16 == 0 && ptr_aligned(a.out, 16)) || HW >= 900 : !a.acc16 && HW % 4 == 0 && ptr_aligned(a.out, 16);
-  if (p.tiles == 0) return false;
-  if (a.has_rq) *err = a.acc16 ? launch<0, true>(p, st) : launch<0, false>(p, st);
-  else *err = a.acc16 ? launch<2, true>(p, st) : launch<1, false>(p, st);
+  const bool through = a.has_rq ? (HW % 16 == 0 && ptr_aligned(a.out, 16)) || HW >= 900 : !a.acc16 && HW % 4 == 0 && ptr_aligned(a.out, 16);
+  p.flags = (a.act_unsigned ? kFlip : 0u) | (a.rq.per_channel ? kPerChannel : 0u) | (through ? kThrough : 0u);
+  if (tiles == 0) return false;
+  if (a.has_rq) *err = a.acc16 ? launch<0, true>(p, tiles, st) : launch<0, false>(p, tiles, st);
+  else *err = a.acc16 ? launch<2, true>(p, tiles, st) : launch<1, false>(p, tiles, st);
   return true;
 }
 
