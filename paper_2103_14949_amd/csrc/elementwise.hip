@@ -13,6 +13,7 @@
 //              vector, their channels found with one multiply-high division.
 #include "hago_device.h"
 #include "launch.h"
+#include "span_split.h"
 
 #include <type_traits>
 
@@ -20,7 +21,7 @@ namespace hago {
 
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kSpanThreads;
 constexpr int kVecPerLane = 4;  // 128-bit vectors per lane and job of the row kernels
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -666,17 +667,7 @@ __device__ __forceinline__ void channels4(const ChannelDiv& d, int64_t i, int64_
   }
 }
 
-// The channels of consecutive vectors come back every lv vectors (channels * inner elements, taken two
-// or four times where that is not a multiple of four).  `span` is a multiple of lv of about a workgroup's
-// width where lv is small, lv itself where it is large; vector j of every span has the same four channels.  A
-// workgroup owns the vectors [seg * seg_len, ...) of `rows` consecutive spans: the lane's parameters
-// stay in registers, what is left per element is the operator itself.
-struct SpanArgs {
-  int64_t total;  // elements
-  int64_t spans;
-  int32_t span, nseg, seg_len, rows;
-};
-
+// One workgroup of a tensor's division into spans (span_split.h).
 template <class Op, int U>
 __global__ __launch_bounds__(kThreads) void periodic_kernel(Op op, SpanArgs g, ChannelDiv d) {
   const int t = threadIdx.x;
@@ -750,34 +741,6 @@ __global__ __launch_bounds__(kThreads) void flat_kernel(Op op, int64_t total, Ch
   }
 }
 
-// Vectors after which the channels of a vector come back.
-inline int64_t channel_period(int64_t channels, int64_t inner) {
-  const int64_t p = channels * inner;
-  return p % 4 == 0 ? p / 4 : (p % 2 == 0 ? p / 2 : p);
-}
-
-// Whether the pattern comes back often enough (four times) for the periodic form, and its split: workgroups
-// own at least U spans each and, beyond eight workgroups per CU, more of them.
-inline bool periodic_split(int64_t total, int64_t channels, int64_t inner, int u, SpanArgs* g) {
-  const int64_t nvec = total / 4, lv = channel_period(channels, inner);
-  if (channels == 1 || nvec / lv < 4 || lv >= (1ll << 30)) return false;
-  // Spans of whole 64-byte lines (four vectors of fp32) where that keeps five eighths of the lanes: what goes through the L2 is then
-  // whole lines (65536 x 45 channel-last: quantize 5.7 -> 5.3 us, dequantize 4.3 -> 3.9; 20000 x 33, 132 lanes of 231: 3.3 -> 3.6).
-  const int64_t line = lv % 4 == 0 ? 1 : (lv % 2 == 0 ? 2 : 4), most = kThreads / lv, whole = most / line * line;
-  const int64_t span = lv <= kThreads ? lv * (8 * whole >= 5 * most ? whole : most) : lv;
-  g->total = total;
-  g->span = (int32_t)span;
-  g->spans = (nvec + span - 1) / span;
-  g->nseg = (int32_t)((span + kThreads - 1) / kThreads);
-  g->seg_len = (int32_t)((span + g->nseg - 1) / g->nseg);
-  int64_t rows = g->spans * g->nseg / (256 * 8);
-  rows = (rows + u - 1) / u * u;
-  if (rows < u) rows = u;
-  while (rows > 1 && ((g->spans + rows - 1) / rows) * g->nseg < 256) rows /= 2;  // small tensors: spread over the CUs
-  g->rows = (int32_t)rows;
-  return ((g->spans + rows - 1) / rows) * g->nseg < (1ll << 31);
-}
-
 // Periodic / flat launch of an operator; OpP keeps reciprocals for the periodic kernel, OpF does not; OpN is OpP with results that do not go
 // through the L2, where there is such a form.  (As a member of the operator the choice made its arguments 120 bytes, no multiple of sixteen, and a
 // launch of it cost the host 0.3 us more.)
@@ -786,7 +749,7 @@ hipError_t launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStre
   constexpr int U = kVecPerLane;
   const ChannelDiv d = channel_div(total, channels, inner);
   SpanArgs g;
-  if (periodic_split(total, channels, inner, U, &g)) {
+  if (periodic_split(total, channels, inner, U, WholeLines::kAlways, &g)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
     // fp32 to fp32, with codes or without, in spans that end inside lines: such lines cost the write through the L2 more than it gains once 10 MB and more
     // are read beside it (channel-last 50000 x 65 simquant 7.9 us through it, 7.2 nontemporal; 30000 x 66 4.8, 5.7)
@@ -890,7 +853,7 @@ inline hipError_t launch_batched_ragged(const float* x, float* y, int64_t total,
   constexpr int U = 2;
   const ChannelDiv d = channel_div(total, channels, inner);
   SpanArgs g;
-  if (periodic_split(total, channels, inner, U, &g)) {
+  if (periodic_split(total, channels, inner, U, WholeLines::kFewerRounds, &g)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
     return launch_kernel(simquant_batched_ragged_kernel<U, true>, dim3((unsigned)wgs), dim3(kThreads), 0, st, x, y, g, d,
                          nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);
@@ -1291,7 +1254,7 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
   const int64_t nouter = nchan > 1 ? outer : 1, row_len = nchan > 1 ? inner : total;  // one channel: one row
   // Rows shorter than a workgroup's 1024 elements: merged in LDS where their channels come back often ...
   SpanArgs g;
-  if (row_len < 4 * kThreads && periodic_split(total, nchan, row_len, kVecPerLane, &g)) {
+  if (row_len < 4 * kThreads && periodic_split(total, nchan, row_len, kVecPerLane, WholeLines::kNever, &g)) {
     const bool table = nchan <= kTableChannels;
     const size_t lds = table ? (size_t)nchan * sizeof(uint32_t) : 0;
     if (table && total <= 16384 && g.nseg == 1) {  // one workgroup: no second launch to zero the thresholds
@@ -1308,9 +1271,7 @@ hipError_t launch_absmax(const float* x, int64_t outer, int64_t channels, int64_
       return launch_kernel((absmax_slab_kernel<kVecPerLane>), dim3((unsigned)(nslab * groups)), dim3(kThreads), 0, st, x, total,
                          (int32_t)lv, (int32_t)nslab, (int32_t)groups, channel_div(total, nchan, row_len), t);
     }
-    // every workgroup ends with an atomic per channel: twice the CUs' number of workgroups at most
-    int64_t rows = g.spans * g.nseg / (256 * 2);
-    if (rows > g.rows) g.rows = (int32_t)rows;
+    g.rows = absmax_span_rows(g);
     if (const hipError_t e = zero_first(); e != hipSuccess) return e;
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
     auto kern = table ? absmax_periodic_kernel<false, true> : absmax_periodic_kernel<false, false>;
