@@ -70,6 +70,8 @@ enum : uint32_t { kFlip = 1, kPerChannel = 2, kThrough = 4 };  // uint8 activati
 //   CH = 5: five steps of 32 channels are in flight at a time.
 //   RANGE: codes clipped to their container's whole range (32-bit accumulator, rounding half up), in a kernel without the other forms (us in
 //     one kernel and so: 24 -> 144 on 32 x 56 x 56 6.6, 6.5; 32 -> 192 on 4 x 112 x 112 4.7, 4.55; 432 -> 72 and 72 -> 432 with their depthwise layer 24.2, 24.0).
+//     The folded form stays beside the saturating one, for the 32 channels around one of shift 0 (in the general form and so: 24 -> 144 on 32 x 56 x 56
+//     11.1, 7.7; 64 -> 384 on 500 x 8 x 8 13.8, 9.8; without such a channel 6.99, 7.04 and 8.99, 9.00).
 //   KS = 4: four wavefronts share a tile and block, a quarter of the steps each, and add up through LDS (576 -> 96
 //     channels of one 14 x 14 image are six tiles, 18 steps in a row each, else: 8.6 us, 5.8 so).
 typedef uint32_t u32_u __attribute__((aligned(1)));
@@ -290,6 +292,7 @@ __global__ __launch_bounds__(64 * KS, 2) void pw_nchw_kernel(PwArgs p) {
                       !rs.half_away && __builtin_amdgcn_ballot_w64(!lane_ok) == 0;  // wavefront-uniform
     if constexpr (RANGE) {
       if (fold && __builtin_amdgcn_ballot_w64(n < N && rq.sh < 1) == 0) store_all.template operator()<kSat>();
+      else if (fold) store_all.template operator()<kFold>();
       else store_all.template operator()<kGeneral>();
     } else {
       if (fold) store_all.template operator()<kFold>();
