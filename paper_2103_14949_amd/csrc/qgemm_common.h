@@ -149,7 +149,9 @@ enum { kRqGeneral, kRqFolded, kRqSat };
 // Results of a kernel, which has the forms for them alone: what other forms need is code that the compiler puts in front of all of them
 // and that a launch of one tile per CU waits for (us in one kernel and so: the four layers of 4096 x 768 51.3, 50.9; 3000 x 128 -> 1001 5.19, 5.07; 8192 x 64 -> 1024 6.42,
 // 6.27; the channel-last bottleneck of 16 x 28 x 28 x 256 12.8, 12.6).
-//   kOutFull: one byte, clipped to its whole range, of a 32-bit accumulator, rounding half up, an output zero point that kRqSat takes;
+//   kOutFull: one byte, clipped to its whole range, of a 32-bit accumulator, rounding half up, an output zero point that kRqSat takes; kRqFolded
+//     beside it for tiles with a shift above 21 (us in the general form and so: 4096 x 768 -> 2304 13.1, 12.4; 8192 x 64 -> 1024 7.15, 6.75; tiles
+//     without the same);
 //   kOutClipped: the same but for the clip or the zero point; both leave the tile in LDS first.
 //   kOutOther: what the straight-line epilogue writes.
 enum { kOutFull, kOutClipped, kOutOther };

@@ -556,6 +556,8 @@ __device__ __forceinline__ void qgemm_dma_tile(const QgemmParams& p) {
     constexpr int kFast = OUT == kOutFull ? kRqSat : kRqFolded;
     if (form == kFast)
       qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kFast>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
+    else if (OUT == kOutFull && form == kRqFolded)
+      qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqFolded>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
     else
       qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqGeneral>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
   }

@@ -203,6 +203,8 @@ __global__ __launch_bounds__(64 * WP * WQ, 1) void qgemm_line_kernel(QgemmParams
     constexpr int kFast = OUT == kOutFull ? kRqSat : kRqFolded;
     if (form == kFast)
       qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kFast>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
+    else if (OUT == kOutFull && form == kRqFolded)
+      qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqFolded>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
     else
       qgemm_epilogue_dense_staged<WP, WQ, TP, TQ, kRqGeneral>(p, acc, p0, q0, s_corr, s_mult, s_shift, s_c64, s_shm1, smem);
   }
