@@ -77,9 +77,11 @@ __device__ __forceinline__ int lds_off(int row, int chunk) { return row * kRow +
 
 // KS sets of WP x WQ wavefronts take the stage's 32-k groups in turn and meet in LDS at the end: with one tile per
 // CU a second set halves what every wavefront loads, converts and multiplies per stage.
-// OUT: codes as kOutFull (qgemm_common.h), any other codes, or sums (us in one kernel and so: 2000 x 700 -> 1003 8.1, 7.7, raw 8.0, 7.3; raw 3000 x 101 -> 1984 8.9, 8.1; 1021 x 1283
-// -> 1001 9.0, 8.8; int16 1024 x 768 -> 768 8.3, 8.0).
-enum { kAnyCodes = kOutFull + 1, kSums };
+// OUT: codes as kOutFull (qgemm_common.h), the same of a narrow accumulator, any other codes, or sums (us in one kernel and so: 2000 x 700 -> 1003 8.1,
+// 7.7, raw 8.0, 7.3; raw 3000 x 101 -> 1984 8.9, 8.1; 1021 x 1283 -> 1001 9.0, 8.8; int16 1024 x 768 -> 768 8.3, 8.0).  Narrow accumulators have a
+// kernel for the large tiles only (16 bits, us as any other codes and so: 3000 x 101 -> 1984 9.8, 8.8; 2000 x 2001 -> 2003 21.6, 20.8; as a second form of
+// the kernel for other codes: clipped 3000 x 101 -> 1984 9.4, 9.8, and 64 x 64 tiles no faster).
+enum { kAnyCodes = kOutFull + 1, kSums, kNarrowFull };
 template <bool I16, int WP, int WQ, int TP, int TQ, int KS, int OUT>
 __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmParams p) {
   constexpr int kEsz = I16 ? 2 : 1;
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
   // ---- channel terms: the UPR threads of a row hold its sum.  SAT: the output is clipped to its container's whole range
   // and every shift is 1 to 21: the rounding term and the zero point are one constant, and the packing saturates (products
   // are at most 2^62, the constant below 2^61 + 2^51).
-  constexpr bool sat_ok = OUT == kOutFull;
+  constexpr bool sat_ok = OUT == kOutFull || OUT == kNarrowFull;
   const int out_mode = OUT != kSums ? 0 : (p.out_mode == 1 ? 1 : 2);
   int no_sat = !sat_ok;
 #pragma unroll
@@ -273,7 +275,7 @@ __global__ __launch_bounds__(64 * WP * WQ * KS) void qgemm_staged_kernel(QgemmPa
     }
   }
   bool sat = false;
-  if constexpr (OUT == kOutFull) sat = __syncthreads_or(no_sat) == 0;  // (also: the stages have been consumed)
+  if constexpr (sat_ok) sat = __syncthreads_or(no_sat) == 0;  // (also: the stages have been consumed)
   else __syncthreads();
 
   // ---- the sets' sums meet in LDS: of two, each finishes half of the register groups
@@ -408,10 +410,14 @@ hipError_t launch_staged(QgemmParams p, hipStream_t st) {
   constexpr int most = stages > out ? stages : out, lds = most > sums ? most : sums;
   const int64_t tiles = (int64_t)((p.N + BP - 1) / BP) * ((p.M + BQ - 1) / BQ);
   p.line_out = p.N % 64 == 0 && ptr_aligned(p.out, 64);
-  const int form = p.out_mode != 0 ? kSums : qgemm_out(p) == kOutFull ? kOutFull : kAnyCodes;
+  const bool full = qgemm_full_codes(p);
+  int form = p.out_mode != 0 ? kSums : full && !p.acc_wrap_shift ? kOutFull : kAnyCodes;
   auto kern = form == kSums      ? qgemm_staged_kernel<I16, WP, WQ, TP, TQ, KS, kSums>
               : form == kOutFull ? qgemm_staged_kernel<I16, WP, WQ, TP, TQ, KS, kOutFull> : qgemm_staged_kernel<I16, WP, WQ, TP, TQ, KS, kAnyCodes>;
-  static std::atomic<uint64_t> attr_set[3];
+  if constexpr (!I16 && KS == 1) {
+    if (full && p.acc_wrap_shift) form = kNarrowFull, kern = qgemm_staged_kernel<I16, WP, WQ, TP, TQ, KS, kNarrowFull>;
+  }
+  static std::atomic<uint64_t> attr_set[4];
   hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), lds, attr_set[form]);
   if (e != hipSuccess) return e;
   return launch_tiles(kern, p, tiles, 64 * WP * WQ * KS, lds, st);

@@ -155,9 +155,12 @@ enum { kRqGeneral, kRqFolded, kRqSat };
 //   kOutClipped: the same but for the clip or the zero point; both leave the tile in LDS first.
 //   kOutOther: what the straight-line epilogue writes.
 enum { kOutFull, kOutClipped, kOutOther };
+inline bool qgemm_full_codes(const QgemmParams& p) {
+  return p.out_mode == 0 && !p.rs.half_away && sat_range(p.rs) && p.rs.z_out >= -128 && p.rs.z_out <= 255;
+}
 inline int qgemm_out(const QgemmParams& p) {
   if (p.out_mode != 0 || p.acc_wrap_shift || p.rs.half_away) return kOutOther;
-  return sat_range(p.rs) && p.rs.z_out >= -128 && p.rs.z_out <= 255 ? kOutFull : kOutClipped;
+  return qgemm_full_codes(p) ? kOutFull : kOutClipped;
 }
 
 // s_corr holds the weight row sums on entry (s_sum2, if given, a second part to add; it may be

@@ -1,5 +1,5 @@
 // Which kernels serve a call: reads one call a line,
-//   dense <act> <M> <K> <N> <raw> <byte offset of the activations>
+//   dense <act> <M> <K> <N> <raw> <byte offset of the activations> [<accumulator bits>, 32 unless given]
 //   conv <act> <nhwc> <B> <C> <H> <W> <O> <KH> <KW> <stride_h> <stride_w> <pad_h> <pad_w> <raw> <path> <shape>
 // (act: u8, i8 or i16; path and shape: the test hooks) and prints the kernels that it launches on a line, separated by tabs.
 #include "fake_runtime.h"
@@ -22,9 +22,11 @@ int main() {
     fake::launched.clear();
     hago_status s = HAGO_ERR_PARAM;
     if (what == "dense") {
-      int64_t M, K, N, raw, off;
+      int64_t M, K, N, raw, off, bits = 32;
       in >> M >> K >> N >> raw >> off;
-      s = hago_qdense(fake::at<char>(0) + off, a, fake::at(1), w, fake::at<int32_t>(2), M, N, K, HAGO_I32, raw ? nullptr : &rq, fake::at(3), 0, nullptr);
+      if (in && !(in >> bits)) in.clear(), bits = 32;
+      const hago_dtype acc = bits == 16 ? HAGO_I16 : bits == 24 ? HAGO_I24 : HAGO_I32;
+      s = hago_qdense(fake::at<char>(0) + off, a, fake::at(1), w, fake::at<int32_t>(2), M, N, K, acc, raw ? nullptr : &rq, fake::at(3), 0, nullptr);
     } else if (what == "conv") {
       int64_t nhwc, B, C, H, W, O, KH, KW, sh, sw, ph, pw, raw, path, shape;
       in >> nhwc >> B >> C >> H >> W >> O >> KH >> KW >> sh >> sw >> ph >> pw >> raw >> path >> shape;

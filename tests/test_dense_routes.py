@@ -33,3 +33,12 @@ def test_lines_to_the_larger_tiles(routes):
     calls = [dense(*x) for x in few.FEW + few.OTHERS]
     for call, kernel in zip(calls, served(routes, calls)):
         assert kernel.startswith("qgemm_few") == (call in calls[:len(few.FEW)]), (call, kernel)
+
+
+def test_narrow_accumulators_of_any_size(routes):
+    """Whole-range codes of a 16- or 24-bit accumulator: a kernel of their own on the large tiles."""
+    kernels = {(size, bits): served(routes, [f"dense i8 {size} 0 0 {bits}"])[0] for size in ("3000 101 1984", "2000 700 1003") for bits in (32, 24, 16)}
+    large, small = ("qgemm_staged_kernel<false,2,4,2,1,1,", "qgemm_staged_kernel<false,2,2,1,1,2,")
+    assert kernels["3000 101 1984", 16] == kernels["3000 101 1984", 24] != kernels["3000 101 1984", 32]
+    assert all(kernels["3000 101 1984", b].startswith(large) and kernels["2000 700 1003", b].startswith(small) for b in (32, 24, 16))
+    assert kernels["3000 101 1984", 16][len(large):] not in {kernels["2000 700 1003", b][len(small):] for b in (32, 24, 16)}

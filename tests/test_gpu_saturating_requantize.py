@@ -90,6 +90,30 @@ def test_whole_range_narrow_accumulator(acc, act_u8):
             assert_same(host(got), want, f"{acc} u8={act_u8} {out_u8, z, clip, s0, s1} mult={use_mult}")
 
 
+@pytest.mark.parametrize("acc", ["I16", "I24"])
+@pytest.mark.parametrize("tile", [3, 4])   # 128 x 128, which has a form for these, and 64 x 64, which has not
+@pytest.mark.parametrize("M, K, N", [(300, 131, 140), (129, 35, 257), (40, 700, 131)])
+def test_whole_range_narrow_accumulator_dense(M, K, N, tile, acc, gemm_path):
+    """The same in the dense kernel for rows of any size."""
+    rng = np.random.default_rng(M + tile)
+    gemm_path(1)
+    hago.set_test_hook(hago.HOOK_GENERAL_TILE, tile)
+    try:
+        for act_u8 in (False, True):
+            a = rng.integers(0, 256, (M, K)).astype(np.uint8) if act_u8 else rng.integers(-128, 128, (M, K)).astype(np.int8)
+            za, w = 117 if act_u8 else -5, rng.integers(-127, 128, (N, K)).astype(np.int8)
+            bias = rng.integers(-2 ** 23, 2 ** 23, N).astype(np.int32)
+            for out_u8, z, clip, (s0, s1) in FORMS:
+                mult = rng.integers(2 ** 30, 2 ** 31, N, dtype=np.int64).astype(np.int32)
+                shift = rng.integers(s0, s1 + 1, N).astype(np.int32)
+                want = ref.qdense(a, za, w, bias, getattr(ref, acc), ref_requant(mult, shift, out_u8, z, clip))
+                got = hago.qdense(dev(a), act_qtype(a, za), dev(w), hago.QType(hago.I8), dev(bias), getattr(hago, acc),
+                                  gpu_requant(mult, shift, out_u8, z, clip))
+                assert_same(host(got), want, f"{M, K, N} u8={act_u8} {out_u8, z, clip, s0, s1}")
+    finally:
+        hago.set_test_hook(hago.HOOK_GENERAL_TILE, -1)
+
+
 @pytest.mark.parametrize("shape", [(300, 64, 1), (90, 35, 1), (64, 12, 3), (5000, 8, 1)])
 @pytest.mark.parametrize("dtype", [np.int32, np.int16])
 def test_whole_range_standalone(shape, dtype):
