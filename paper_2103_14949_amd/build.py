@@ -90,10 +90,50 @@ def check_wide_stores(assembly: str) -> list[str]:
     return found
 
 
+def check_lane_exchanges(assembly: str) -> list[str]:
+    """Results of vector instructions in inline assembly that lanes exchange (DPP, permlane) fewer than two wait states later, on any
+    way there: those read what stands in the registers before it, and behind inline assembly nobody inserts the wait states."""
+    def registers(text):
+        return {n for first, last in re.findall(r"\bv\[?(\d+)(?::(\d+)\])?", text) for n in range(int(first), int(last or first) + 1)}
+
+    instructions, labels, inside = [], {}, False   # (text, in inline assembly)
+    for line in assembly.splitlines():
+        if "ASMSTART" in line or "ASMEND" in line:
+            inside = "ASMSTART" in line
+        elif m := re.match(r"([\w.$]+):", line):
+            labels[m[1]] = len(instructions)
+        elif m := re.match(r"\s+([a-z]\w+(?: .*?)?)\s*(?:;.*)?$", line):
+            instructions.append((m[1], inside))
+    found = []
+    for at, (text, inside) in enumerate(instructions):
+        if not inside or not text.startswith("v_"):
+            continue
+        written = registers(text.split(",")[0])
+        ways, seen = [(at + 1, 0)], set()
+        while ways:
+            i, states = ways.pop()
+            if states >= 2 or i >= len(instructions) or (i, states) in seen:
+                continue
+            seen.add((i, states))
+            later = instructions[i][0]
+            # (a permlane swap reads both its registers; a DPP instruction all but its first, unless that keeps some of its bits)
+            if later.startswith("v_permlane") and registers(later) & written or (
+                    re.search(r"_dpp\b|\b(?:quad_perm|row_\w+|wave_\w+)\b", later) and registers(later.split(",", 1)[-1]) & written):
+                found.append(f"{text}; {later}")
+            m = re.match(r"s_(c?branch)\w*\s+(\S+)", later)
+            if m and m[2] in labels:
+                ways.append((labels[m[2]], states + 1))
+            if not m or m[1] == "cbranch":
+                nop = re.match(r"s_nop (\w+)", later)
+                ways.append((i + 1, states + (int(nop[1], 0) + 1 if nop else 1)))
+    return found
+
+
 def check_assembly(assembly: str) -> list[str]:
     """What the kernels must not hold, and the compiler does not avoid."""
     return ([f"64-bit shift by the last allocated register (add HAGO_SPARE_REGISTER): {f}" for f in check_shift_amounts(assembly)] +
             [f"wide store without two wait states behind it: {f}" for f in check_wide_stores(assembly)] +
+            [f"lane exchange without two wait states behind inline assembly: {f}" for f in check_lane_exchanges(assembly)] +
             [f"LDS load without a wait state after m0: {f}" for f in check_lds_loads(assembly)])
 
 

@@ -61,6 +61,27 @@ def test_wide_stores_without_wait_states_behind_them_are_found(lines, refused):
     assert not build.check_wide_stores(f"_Zkern:\n{body}")  # (the compiler's own)
 
 
+@pytest.mark.parametrize("lines,refused", [
+    ("v_permlane16_swap_b32 v1, v2", True),
+    ("v_permlane32_swap_b32 v2, v1", True),
+    ("s_nop 0|v_permlane16_swap_b32 v1, v2", True),
+    ("s_nop 1|v_permlane16_swap_b32 v1, v2", False),
+    ("v_xor_b32_e32 v1, v1, v9|v_permlane16_swap_b32 v7, v2|v_permlane16_swap_b32 v1, v2", False),
+    ("v_permlane16_swap_b32 v3, v2", False),
+    ("v_mov_b32_dpp v3, v1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf bound_ctrl:1", True),
+    ("v_add_u32_dpp v3, v[0:1], v4 row_shr:1 row_mask:0xf bank_mask:0xf", True),
+    ("v_mov_b32_dpp v1, v3 row_half_mirror row_mask:0xf bank_mask:0xf", False),
+    ("s_branch .LBB0_9|v_mov_b32_e32 v3, v4|.LBB0_9:|v_permlane16_swap_b32 v1, v2", True),
+    ("s_cbranch_scc1 .LBB0_9|s_nop 3|s_endpgm|.LBB0_9:|v_permlane16_swap_b32 v1, v2", True),
+    ("s_branch .LBB0_9|v_permlane16_swap_b32 v1, v2|.LBB0_9:|v_mov_b32_e32 v3, v4", False),
+])
+def test_lane_exchanges_behind_inline_assembly_are_found(lines, refused):
+    body = "".join(x + "\n" if x.endswith(":") else f"\t{x}\n" for x in lines.split("|"))
+    written = "\tv_ashr_pk_i8_i32 v1, v4, v5, v6 op_sel:[0,0,0,1]\n"
+    assert bool(build.check_lane_exchanges(f"_Zkern:\n\t;;#ASMSTART\n{written}\t;;#ASMEND\n{body}")) == refused
+    assert not build.check_lane_exchanges(f"_Zkern:\n{written}{body}")  # (behind an instruction of the compiler's own it sees to them)
+
+
 def test_no_kernel_as_built_has_one():
     directory = os.path.join(os.path.dirname(build.LIB), "_build")
     paths = glob.glob(os.path.join(directory, "**", "*gfx950.s"), recursive=True)
