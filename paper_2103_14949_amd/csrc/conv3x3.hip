@@ -53,7 +53,7 @@ struct C3Params {
   int32_t tiles_per_img; // ceil(H / TR)
   int32_t ntiles;        // B * tiles_per_img
   int32_t nblk;          // blocks of 32 TN output channels
-  int32_t per_channel, has_rq, acc_wrap_shift;
+  int32_t per_channel, acc_wrap_shift;
   int32_t out_mode;      // 0: requantized 8-bit, 1: raw int32, 2: raw int16
   int32_t through;       // results go through the L2
   uint32_t act_xor4;     // 0x80808080 for uint8 activations
@@ -541,7 +541,6 @@ bool try_qconv3x3_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hi
   p.shift = a.rq.shift;
   p.B = cg.B; p.C = cg.C; p.H = cg.H; p.W = cg.W; p.O = cg.O;
   p.per_channel = a.rq.per_channel;
-  p.has_rq = a.has_rq;
   p.acc_wrap_shift = a.acc_wrap_shift;
   p.out_mode = a.has_rq ? 0 : (a.acc16 ? 2 : 1);
   // 64 bytes of a channel at a time go through the L2: 32-bit results always, one-byte results of images that begin at 16 bytes, 16-bit
