@@ -56,6 +56,15 @@ def assert_same_bits(got, want, what=""):
     assert_same(g, w, what)
 
 
+def into_guard(call, shape, dtype, off):
+    """The results of call(out=...) into a tensor that starts `off` elements behind a 256-byte line; what lies around stays."""
+    n = int(np.prod(shape))
+    guard = torch.full((n + off + 256,), 77, dtype=dtype, device=DEV)
+    call(out=guard[off:off + n].view(shape))
+    assert int((guard[:off] != 77).sum()) == 0 and int((guard[off + n:] != 77).sum()) == 0
+    return host(guard[off:off + n].view(shape))
+
+
 # Which convolution entry point the parity tests call (set by the `conv_entry` fixture):
 #   "plain"  hago_qconv2d (no scratch memory)
 #   "ws"     hago_qconv2d_ws with a workspace of exactly the queried size, filled with garbage

@@ -10,15 +10,6 @@ from gpu_util import *  # noqa: E402,F401,F403
 ACCS = [(hago.I32, ref.I32, torch.int32), (hago.I16, ref.I16, torch.int16)]
 
 
-def into_guard(call, shape, dtype, off):
-    """The results of call(out=...) into a tensor that starts `off` elements behind a 256-byte line; what lies around stays."""
-    n = int(np.prod(shape))
-    guard = torch.full((n + off + 256,), 77, dtype=dtype, device=DEV)
-    call(out=guard[off:off + n].view(shape))
-    assert int((guard[:off] != 77).sum()) == 0 and int((guard[off + n:] != 77).sum()) == 0
-    return host(guard[off:off + n].view(shape))
-
-
 # (few tiles; unaligned rows in 64 and 128 tiles; 64 x 64 tiles; 256-wide ones)
 @pytest.mark.parametrize("m, k", [(70, 64), (45, 131), (1500, 701), (4500, 129), (1100, 768), (4000, 512)])
 @pytest.mark.parametrize("n", [40, 101, 130, 208, 516])

@@ -10,7 +10,7 @@ from gpu_util import *  # noqa: E402,F401,F403
 
 
 # (odd, even and multiple-of-four periods; spans cut to whole lines or not; below and above 2.5 million elements)
-@pytest.mark.parametrize("shape", [(900, 45, 1), (60001, 45, 1), (38500, 65, 1), (39000, 65, 1), (5000, 33, 1), (3000, 39, 1), (2500, 22, 3)])
+@pytest.mark.parametrize("shape", [(900, 45, 1), (60001, 45, 1), (38400, 65, 1), (39000, 65, 1), (5000, 33, 1), (3000, 39, 1), (2500, 22, 3)])
 def test_spans(shape):
     rng = np.random.default_rng(shape[0])
     C = shape[1]
@@ -26,7 +26,7 @@ def test_spans(shape):
     assert_same_bits(host(hago.dequantize(c, q, ds, dz)), ref.dequantize(codes, scale, zp), "dequantize")
 
 
-@pytest.mark.parametrize("outer", [31, 32])   # 8 candidates of 2^21 + 2^16 (outer - 32) elements x 4: 2^26 results and just below
+@pytest.mark.parametrize("outer", [32, 33])   # 8 candidates of 2^18 elements each: 2^26 results, which go through the L2, and more, which do not
 def test_candidates(outer):
     g = torch.Generator(device=DEV)
     g.manual_seed(outer)
@@ -34,13 +34,16 @@ def test_candidates(outer):
     scales = torch.rand((8, 64), generator=g, device=DEV) * 0.04 + 0.01
     zps = torch.randint(-9, 10, (8, 64), generator=g, device=DEV, dtype=torch.int32)
     lo, hi = [-128, -64, -32, -16, -8, -8, -4, -2], [127, 63, 31, 15, 7, 7, 3, 1]
-    for n in (8, 1) if outer == 31 else (8,):
+    assert (x.numel() * 8 <= 1 << 26) == (outer == 32)
+    for n in (8, 1):
         got = hago.simquant_batched(x, scales[:n].contiguous(), zps[:n].contiguous(), hago.QType(hago.I8), lo[:n], hi[:n])
         for b in range(n):
             one = hago.simquant(x, scales[b].contiguous(), zps[b].contiguous(), hago.QType(hago.I8), lo[b], hi[b])
             assert torch.equal(got[b].view(torch.int32), one.view(torch.int32)), (n, b)
-    part = host(x[:1, :2]).copy()
-    assert_same_bits(host(got[0][:1, :2]), ref.simquant(part, host(scales[0][:2]), host(zps[0][:2]), lo[0], hi[0]), "oracle")
+            for o, c in ((0, 0), (outer - 1, 62)):   # the first rows and the last
+                part = host(x[o:o + 1, c:c + 2]).copy()
+                want = ref.simquant(part, host(scales[b][c:c + 2]), host(zps[b][c:c + 2]), lo[b], hi[b])
+                assert_same_bits(host(got[b][o:o + 1, c:c + 2]), want, f"oracle {n, b, o, c}")
 
 
 @pytest.mark.parametrize("n", [64, 72, 128, 129, 192, 200, 1001])
@@ -54,15 +57,6 @@ def test_dense_rows(n, m, k, off):
     hago.qdense(dev(a), act_qtype(a, 128), dev(w), hago.QType(hago.I8), None, hago.I32, gpu_requant(mult, shift), out=out)
     assert_same(host(out), ref.qdense(a, 128, w, None, ref.I32, ref_requant(mult, shift)), f"{m}x{k}->{n}")
     assert int((host(guard[:off]) != 77).sum()) == 0 and int((host(guard[off + m * n:]) != 77).sum()) == 0
-
-
-def into_guard(call, shape, dtype, off):
-    """The results of call(out=...) into a tensor that starts `off` elements behind a 256-byte line; what lies around stays."""
-    n = int(np.prod(shape))
-    guard = torch.full((n + off + 256,), 77, dtype=dtype, device=DEV)
-    call(out=guard[off:off + n].view(shape))
-    assert int((guard[:off] != 77).sum()) == 0 and int((guard[off + n:] != 77).sum()) == 0
-    return host(guard[off:off + n].view(shape))
 
 
 # NCHW layers: images that begin with a line, at 16 bytes, at 4 and anywhere; few and many workgroups; a tile's end inside sixteen pixels
@@ -102,3 +96,32 @@ def test_depthwise_rows(case):
     args = (dev(a), act_qtype(a, 0), dev(w), hago.QType(hago.I8), None, hago.NCHW, (1, 1), (1, 1), C, hago.I32, gpu_requant(mult, shift))
     for off in (0, 4, 1):
         assert_same(into_guard(lambda out: hago.qconv2d(*args, out=out), a.shape, torch.int8, off), want, f"{case} off {off}")
+
+
+# layers of more than 11 MB of results, of whose rows four meet in LDS, in every kind of codes and form of the arithmetic
+@pytest.mark.parametrize("case", [(57, 100, 45, 44), (40, 96, 64, 48)])
+@pytest.mark.parametrize("act_u8", [False, True])
+def test_depthwise_four_rows(case, act_u8):
+    B, C, H, W = case
+    assert B * C * H * W > 11e6
+    rng = np.random.default_rng(1000 * W + H + act_u8)
+    w = rng.integers(-127, 128, (C, 1, 3, 3)).astype(np.int8)
+    a = rng.integers(0, 256, (B, C, H, W)).astype(np.uint8) if act_u8 else rng.integers(-127, 128, (B, C, H, W)).astype(np.int8)
+    za = 131 if act_u8 else 0
+    geo, rgeo = (hago.NCHW, (1, 1), (1, 1), C), (ref.NCHW, (1, 1), (1, 1), C)
+    sums = ref.qconv2d(a, za, w, None, *rgeo, ref.I32).reshape(B, C, H * W)
+    da, dw = dev(a), dev(w)
+    for acc, out_u8, z, clip, rounding, odd in (
+            (hago.I32, False, -3, (-128, 127), 0, True), (hago.I32, True, 7, (0, 255), 0, False), (hago.I32, False, 0, (-100, 90), 0, True),
+            (hago.I32, False, 5, (-128, 127), 1, False), (hago.I16, False, -3, (-128, 127), 0, True), (hago.I24, True, 7, (0, 255), 0, False)):
+        mult, shift = rng.integers(2 ** 30, 2 ** 31, C).astype(np.int32), rng.integers(7, 12, C).astype(np.int32)
+        bias = rng.integers(-3000, 3000, C).astype(np.int32)
+        if odd:   # single channels off the forms of the others
+            shift[3], shift[C - 1], bias[5], bias[C - 2] = 0, 23, 2 ** 30 + 9, -2 ** 30 - 9
+        bits = {hago.I32: 32, hago.I24: 24, hago.I16: 16}[acc]
+        wrapped = ((sums.astype(np.int64) + bias[:, None] + (1 << (bits - 1))) % (1 << bits) - (1 << (bits - 1))).astype(np.int32)
+        want = ref.requantize(wrapped, ref_requant(mult, shift, out_u8, z, clip, rounding)).reshape(a.shape)
+        got = into_guard(lambda out: hago.qconv2d(da, act_qtype(a, za), dw, hago.QType(hago.I8), dev(bias), *geo, acc,
+                                                  gpu_requant(mult, shift, out_u8, z, clip, rounding=rounding), out=out),
+                         a.shape, torch.uint8 if out_u8 else torch.int8, 4)
+        assert_same(got, want, f"{case} u8={act_u8} {acc, out_u8, z, clip, rounding, odd}")
