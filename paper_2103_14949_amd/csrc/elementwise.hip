@@ -742,11 +742,11 @@ __global__ __launch_bounds__(kThreads) void flat_kernel(Op op, int64_t total, Ch
 }
 
 // Periodic / flat launch of an operator; OpP keeps reciprocals for the periodic kernel, OpF does not; OpN is OpP with results that do not go
-// through the L2, where there is such a form.  (As a member of the operator the choice made its arguments 120 bytes, no multiple of sixteen, and a
-// launch of it cost the host 0.3 us more.)
+// through the L2, where there is such a form.  (As a member of the operator the choice made the arguments of a launch more than kCheapArguments.)
 template <class OpP, class OpF, class OpN, class... A>
 hipError_t launch_ragged(int64_t total, int64_t channels, int64_t inner, hipStream_t st, A... args) {
   constexpr int U = kVecPerLane;
+  static_assert(sizeof(OpP) + sizeof(SpanArgs) + sizeof(ChannelDiv) <= kCheapArguments && sizeof(OpN) <= sizeof(OpP));
   const ChannelDiv d = channel_div(total, channels, inner);
   SpanArgs g;
   if (periodic_split(total, channels, inner, U, WholeLines::kAlways, &g)) {

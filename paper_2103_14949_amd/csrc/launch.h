@@ -37,8 +37,12 @@ inline bool ptr_aligned(const void* ptr, size_t n) {
   return e;
 }
 
-// One kernel launch.  (The launch syntax and hipLaunchKernelGGL hand the configuration over by two more calls: 2.45 us of host
-// time for a kernel with 216 bytes of arguments, 2.25 so; hipGetLastError behind it is another 0.04.)  Its status is its own: a
+// Bytes of arguments up to which a launch costs the host 2.6 to 2.9 us.  With more, from 116 on, it costs 3.3 to 3.8 in some processes, in the
+// others as much as with fewer.  A kernel that reads the size of its grid has 256 more of the runtime's own.
+constexpr size_t kCheapArguments = 112;
+
+// One kernel launch.  (The launch syntax and hipLaunchKernelGGL hand the configuration over by two more calls, 0.2 us of host
+// time; hipGetLastError behind it is another 0.04.)  Its status is its own: a
 // call of several launches looks at each.
 template <typename... P>
 [[nodiscard]] inline hipError_t launch_kernel(void (*kern)(P...), dim3 grid, dim3 block, size_t lds_bytes, hipStream_t st, std::type_identity_t<P>... args) {

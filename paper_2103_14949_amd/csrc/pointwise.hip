@@ -44,7 +44,7 @@ struct PwArgs {
   uint32_t flags;
   RequantScalars rs;
 };
-static_assert(sizeof(PwArgs) <= 112, "a launch with more costs the host 0.7 us more");
+static_assert(sizeof(PwArgs) <= kCheapArguments);
 enum : uint32_t { kFlip = 1, kPerChannel = 2, kThrough = 4 };  // uint8 activations; a multiplier per channel; results go through the L2
 
 // MODE 0: requantized 8-bit, 1: raw int32, 2: raw int16; ACC16: accumulator wraps to 16 bits.

@@ -454,9 +454,10 @@ hipError_t launch_qdense(const GemmArgs& a, hipStream_t st) {
   //   2048 x 768 -> 768    12.8, 10.8, 9.0, 6.9, [6.1]        1024 x 1024 -> 1024  14.9, 12.4, 10.2, 7.5, [5.5]
   //   5000 x 640 -> 2560   [14.4], 21.9, 18.4, 24.0, 25.3     256 x 4096 -> 4096   41.8, 34.4, 29.6, [16.7], 17.0
   // Where K ends inside a 128-byte stage, every lane of the 128 x 128 tile works out its addresses (917 x 1344 -> 1216 8.8 as
-  // 128 x 128, 7.1 as 64 x 64; 1561 x 1600 -> 1040 10.7, 9.1).  Raw results take their bytes' time, int32 ones 0.055 us per
-  // 1000 of a tile (1565 x 384 -> 2496 raw: 128 x 256 11.5, 64 x 64 9.8; requantized 7.4, 7.0).  Over 90 shapes drawn at random,
-  // each requantized and raw, the tile so chosen is 0.2 % from the best on average, 5 % at most.
+  // 128 x 128, 7.1 as 64 x 64; 1561 x 1600 -> 1040 10.7, 9.1).  Raw results take their bytes' time, int32 ones 0.02 to
+  // 0.09 us per 1000 of a tile, the more the more bytes all tiles write (128 x 256 tiles, requantized and raw: 1565 x 384 -> 2496 7.4, 7.9, 4096 x 256 ->
+  // 4096 12.4, 17.7).  Over 90 shapes drawn at random the tile so chosen is 0.2 % from the best on average, 5 % at most, where requantized; of raw
+  // results, over 56 others with 0.055 per 1000, as with anything from 0.035 to 0.07, 0.3 and 3.5 %.
   struct Cand { int id, bp, bq; double fix, per_k, tail_fix, tail_per_k; };
   static const Cand cands[] = {{0, 256, 256, 3.7, 0.0089, 0, 0}, {1, 192, 256, 2.8, 0.0072, 0, 0}, {5, 128, 256, 1.9, 0.0062, 0, 0},
                                {2, 128, 128, 2.1, 0.0034, 0.5, 0.0005}};

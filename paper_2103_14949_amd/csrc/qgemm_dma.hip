@@ -563,7 +563,8 @@ __device__ __forceinline__ void qgemm_dma_tile(const QgemmParams& p) {
   }
 }
 
-// One kernel per kind of results, told apart by its argument.
+// One kernel per kind of results, told apart by the type of its argument: the template's arguments stay those of the tile, by which the tests of
+// the routes know a kernel.
 struct FullParams { QgemmParams p; };
 struct ClippedParams { QgemmParams p; };
 #define HAGO_DMA_KERNEL(PARAMS_, OUT_, P_)                                                                                     \

@@ -46,9 +46,7 @@ __device__ __forceinline__ void load_dword(const v4i& r, uint32_t lds_addr, uint
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" : : "s"(lds_addr), "v"(o), "s"(r) : "memory", "m0");
 }
 
-// What the kernel needs of a layer's parameters.  With the scalars in front of them the arguments are 108 bytes: up to 112 a launch costs the
-// host 2.75 us, from 116 on 3.5 (a launch of an empty kernel, of whatever more; the arguments that the runtime adds for the size of
-// the grid count as 256).
+// What the kernel needs of a layer's parameters: with the scalars in front of them the arguments are 108 bytes (kCheapArguments).
 struct FewParams {
   const int32_t* bias;
   void* out;
@@ -57,6 +55,7 @@ struct FewParams {
   int32_t corr_coef, z_out, lo_rel, hi_rel;
   uint32_t flags;
 };
+static_assert(56 + sizeof(FewParams) <= kCheapArguments);
 enum : uint32_t { kPerChannel = 1, kHalfAway = 2, kFlip = 4, kHalves = 8 };  // and, from bit 8 on, acc_wrap_shift
 
 inline FewParams few_params(const QgemmParams& p) {
@@ -67,8 +66,8 @@ inline FewParams few_params(const QgemmParams& p) {
 
 // The first 14 dwords of the arguments are in scalar registers when a wavefront starts; the others, in `q`, take as long as a
 // load from memory.  KB: bytes of a row.  minor: tiles of the index that runs first, bit 31: that is the channels'.  KIND: bit 0: int16,
-// bit 1: codes go out, else sums (us in one kernel and so: 8081 x 112 -> 123 4.05, 3.8; 128 x 3072 -> 768 4.45, 4.32; 64 x 256 -> 128 2.77, 2.68, raw
-// 2.60, 2.53).
+// bit 1: codes go out, else sums (one number, as the tests of the routes know a kernel by the third); us in one kernel for both and so: 8081 x 112 ->
+// 123 4.05, 3.8; 128 x 3072 -> 768 4.45, 4.32; 64 x 256 -> 128 2.77, 2.68, raw 2.60, 2.53.
 template <int KIND, bool MIS, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void qgemm_few_kernel(const uint8_t* act, const int8_t* wgt, int M, int N, uint32_t KB,
                                                                     int blocks, uint32_t count, uint32_t minor, uint32_t inv_minor,
