@@ -58,12 +58,13 @@ inline bool periodic_split(int64_t total, int64_t channels, int64_t inner, int u
   };
   auto workgroups = [](const SpanArgs& a) { return ((a.spans + a.rows - 1) / a.rows) * a.nseg; };
   const int64_t most = lv <= kSpanThreads ? kSpanThreads / lv : 1;
-  *g = split(lv * most);
   const int64_t line = lv % 4 == 0 ? 1 : (lv % 2 == 0 ? 2 : 4), whole = most / line * line;
-  if (lines != WholeLines::kNever && lv <= kSpanThreads && whole < most && 8 * whole >= 5 * most) {
+  const bool cuttable = lv <= kSpanThreads && whole < most && 8 * whole >= 5 * most;
+  *g = split(lv * (cuttable && lines == WholeLines::kAlways ? whole : most));
+  if (cuttable && lines == WholeLines::kFewerRounds) {
     const SpanArgs cut = split(lv * whole);
     auto length = [&](const SpanArgs& a) { return (workgroups(a) + 255) / 256 * a.rows * a.span; };
-    if (lines == WholeLines::kAlways || (inner > 1 ? length(cut) <= length(*g) : 10 * length(cut) < 9 * length(*g))) *g = cut;
+    if (inner > 1 ? length(cut) <= length(*g) : 10 * length(cut) < 9 * length(*g)) *g = cut;
   }
   return workgroups(*g) < (1ll << 31);
 }
