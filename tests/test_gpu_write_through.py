@@ -10,7 +10,7 @@ from gpu_util import *  # noqa: E402,F401,F403
 
 
 # (odd, even and multiple-of-four periods; spans cut to whole lines or not; below and above 2.5 million elements)
-@pytest.mark.parametrize("shape", [(900, 45, 1), (60001, 45, 1), (38400, 65, 1), (39000, 65, 1), (5000, 33, 1), (3000, 39, 1), (2500, 22, 3)])
+@pytest.mark.parametrize("shape", [(900, 45, 1), (60001, 45, 1), (38500, 65, 1), (39000, 65, 1), (5000, 33, 1), (3000, 39, 1), (2500, 22, 3)])
 def test_spans(shape):
     rng = np.random.default_rng(shape[0])
     C = shape[1]
@@ -26,8 +26,30 @@ def test_spans(shape):
     assert_same_bits(host(hago.dequantize(c, q, ds, dz)), ref.dequantize(codes, scale, zp), "dequantize")
 
 
-@pytest.mark.parametrize("outer", [32, 33])   # 8 candidates of 2^18 elements each: 2^26 results, which go through the L2, and more, which do not
+def test_spans_of_65_channels_below_the_rule():
+    assert 38400 * 65 < 2500000 < 38500 * 65
+    test_spans((38400, 65, 1))
+
+
+@pytest.mark.parametrize("outer", [31, 32])   # 8 candidates of 2^21 + 2^16 (outer - 32) elements x 4: 2^26 results and just below
 def test_candidates(outer):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(outer)
+    x = torch.randn((outer, 64, 4096), generator=g, device=DEV)
+    scales = torch.rand((8, 64), generator=g, device=DEV) * 0.04 + 0.01
+    zps = torch.randint(-9, 10, (8, 64), generator=g, device=DEV, dtype=torch.int32)
+    lo, hi = [-128, -64, -32, -16, -8, -8, -4, -2], [127, 63, 31, 15, 7, 7, 3, 1]
+    for n in (8, 1) if outer == 31 else (8,):
+        got = hago.simquant_batched(x, scales[:n].contiguous(), zps[:n].contiguous(), hago.QType(hago.I8), lo[:n], hi[:n])
+        for b in range(n):
+            one = hago.simquant(x, scales[b].contiguous(), zps[b].contiguous(), hago.QType(hago.I8), lo[b], hi[b])
+            assert torch.equal(got[b].view(torch.int32), one.view(torch.int32)), (n, b)
+    part = host(x[:1, :2]).copy()
+    assert_same_bits(host(got[0][:1, :2]), ref.simquant(part, host(scales[0][:2]), host(zps[0][:2]), lo[0], hi[0]), "oracle")
+
+
+@pytest.mark.parametrize("outer", [32, 33])   # 8 candidates of 2^18 elements each: 2^26 results, which go through the L2, and more, which do not
+def test_candidates_of_both_forms(outer):
     g = torch.Generator(device=DEV)
     g.manual_seed(outer)
     x = torch.randn((outer, 64, 4096), generator=g, device=DEV)
