@@ -853,7 +853,7 @@ inline hipError_t launch_batched_ragged(const float* x, float* y, int64_t total,
   constexpr int U = 2;
   const ChannelDiv d = channel_div(total, channels, inner);
   SpanArgs g;
-  if (periodic_split(total, channels, inner, U, WholeLines::kFewerRounds, &g)) {
+  if (periodic_split(total, channels, inner, U, WholeLines::kRounds, &g, nbatch)) {
     const int64_t wgs = ((g.spans + g.rows - 1) / g.rows) * g.nseg;
     return launch_kernel(simquant_batched_ragged_kernel<U, true>, dim3((unsigned)wgs), dim3(kThreads), 0, st, x, y, g, d,
                          nbatch, (int32_t)channels, scale, zp, clips, (int64_t)0);

@@ -17,7 +17,7 @@ void expect(bool ok, const char* what, int64_t outer, int64_t channels, int64_t 
 
 int main() {
   const int64_t inners[] = {1, 2, 3, 9, 20, 49, 255}, outers[] = {1, 7, 64, 900, 3000, 12000, 20000, 65536, 700001};
-  const WholeLines rules[] = {WholeLines::kAlways, WholeLines::kFewerRounds, WholeLines::kNever};
+  const WholeLines rules[] = {WholeLines::kAlways, WholeLines::kRounds, WholeLines::kNever};
   int64_t cut = 0, kept = 0;
   for (int64_t channels = 1; channels <= 600; ++channels)
     for (int64_t inner : inners)
@@ -46,16 +46,22 @@ int main() {
               is(lines != WholeLines::kAlways || g.span % 4 == 0 || 8 * fewer < 5 * lanes, "all lanes");
               ++kept;
             }
-            if (lines == WholeLines::kFewerRounds) {  // no more rounds of a workgroup per CU, by lanes, than with all lanes
-              SpanArgs all;
+            if (lines == WholeLines::kRounds) {  // rounds of a workgroup per CU, by lanes, against those with all lanes
+              SpanArgs all, many;
               periodic_split(total, channels, inner, u, WholeLines::kNever, &all);
+              periodic_split(total, channels, inner, u, lines, &many, 8);
               auto rounds = [](const SpanArgs& a) { return ((a.spans + a.rows - 1) / a.rows * a.nseg + 255) / 256 * a.rows * a.span; };
-              is(rounds(g) <= rounds(all), "rounds");
+              is(g.span == lanes || 10 * rounds(g) <= 9 * rounds(all), "rounds of few candidates");
+              is(many.span == lanes || many.span == fewer || many.span % 4 == 0, "lanes of many candidates");
+              is(many.span == lanes || 100 * rounds(many) <= (inner > 1 ? 107 : 100) * rounds(all), "rounds of many candidates");
+              is(g.span == lanes || many.span == g.span, "what is whole lines for few is for many");
+              is(many.spans * many.span >= nvec && (many.spans - 1) * many.span < nvec, "spans of many candidates");
             }
             if (lines == WholeLines::kNever) {
               g.rows = absmax_span_rows(g);
               const int64_t workgroups = (g.spans + g.rows - 1) / g.rows * g.nseg;
-              is(g.rows >= 1 && workgroups <= 320 && (g.spans < 320 || workgroups >= 160), "workgroups of max-abs");
+              is(g.rows >= 1 && workgroups <= 640 && (g.spans * g.nseg < 128 || workgroups >= 64), "workgroups of max-abs");
+              is(nvec < 1 << 23 || workgroups >= 480, "workgroups of a large max-abs");
             }
           }
       }
