@@ -1013,7 +1013,8 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
       // through it, and by four rows: 8 x 56 x 56 4.72, 4.42, 5.2; 24 x 56 x 56, 10.8 MB, 7.51, 7.05, 6.99; 32 x 56 x 56 8.65, 9.05, 8.15; 32 x 60 x 60
       // 9.06, 9.96, 8.51; 40 x 48 x 48, 13.3 MB, 9.12, 8.83, 8.17; 26 x 52 x 52, 10.1 MB, 7.13, 6.45, 6.73; rows of 64 bytes on 16 x 64 x 64
       // 6.53, 5.30, 6.32.  Rows off dwords: 24 x 63 x 63, 13.7 MB, 8.75, 9.35; 24 x 49 x 49 7.13, 6.67; 60 x 41 x 41, 14.5 MB, 0.4 less through it.
-      // Several segments: 8 x 113 x 113 x 96 8.21, 7.31.
+      // Several segments: 8 x 113 x 113 x 96 8.21, 7.31.  On buffers that the last-level cache does not hold 32 x 56 x 56 takes 11.0 left in the L2, 11.7 by
+      // four rows.
       const int64_t gx = (int64_t)(cg.C + 3) / 4 * nsegs, mid = nband;
       const bool large = total > 11000000;
       const int how = !large || nsegs > 1 ? kThrough : ragged ? (cg.W <= 48 ? kThrough : kL2) : cg.W == 64 ? kThrough : kFours;

@@ -147,8 +147,8 @@ __device__ __forceinline__ float simquant_wrap_of(float u, float s, float zf, fl
 
 // U: 128-bit vectors per lane and job; all of a job's loads are issued before the first
 // result is computed.  Loads carry the nontemporal hint (without it the copy rate of this chip is about 10 % lower), stores
-// go through the L2 (`store_through`; us, nontemporal and so: simquant of 8 x 144 x 784 3.95, 3.45, of 32 x 144 x 3136 20.0, 19.2 and with
-// its codes 23.1, 21.2; dequantize of 4096 x 768, per channel, 4.5, 3.95).
+// go through the L2 (`store_through`; us, nontemporal and so: simquant of 8 x 144 x 784 3.95, 3.45, of 32 x 144 x 3136 19.1, 16.3 and with
+// its codes 22.2, 18.9, but on buffers that the last-level cache does not hold 20.6, 21.3 and 23.4, 24.1; dequantize of 4096 x 768, per channel, 4.5, 3.95).
 // WRAP: the overflow-simulating form (wrap_bits, wrap_signed).
 template <int U, bool WRAP = false>
 __global__ __launch_bounds__(kThreads) void simquant_rows_kernel(
