@@ -160,7 +160,8 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
             print(" ".join(cmd), flush=True)
         _drain([(src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))], verbose)
 
-    slow = ("qgemm_dma.hip", "conv3x3.hip", "conv_direct.hip", "dwconv.hip")  # first, so that none of them is waited for alone
+    # first, so that none of them is waited for alone
+    slow = ("qgemm_dma_other.hip", "qgemm_line_other.hip", "qgemm_dma.hip", "qgemm_dma_clipped.hip", "conv_gather.hip", "dwconv.hip")
     with concurrent.futures.ThreadPoolExecutor(jobs) as pool:
         list(pool.map(lambda so: compile_one(*so), sorted(zip(sources(), objs), key=lambda so: not so[0].endswith(slow))))
     _check_assembly(objdir)
@@ -191,7 +192,7 @@ def build_phase_timing(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build", "phase")
     os.makedirs(objdir, exist_ok=True)
-    timed = ("qgemm_dma.hip", "qgemm_line.hip", "qgemm.hip")
+    timed = [kernel + results for kernel in ("qgemm_dma", "qgemm_line") for results in (".hip", "_clipped.hip", "_other.hip")] + ["qgemm.hip"]
     procs, objs = [], []
     for src in sources():
         base = os.path.basename(src)

@@ -1,0 +1,8 @@
+// Sums of the any-geometry convolution in one launch.
+#include "conv_direct_kernel.h"
+
+namespace hago {
+
+template hipError_t launch_conv_direct<kSums>(const CdParams&, bool, int, int, size_t, int64_t, hipStream_t);
+
+}  // namespace hago
