@@ -32,12 +32,14 @@ bool try_qconv3x3_nchw(const GemmArgs& a, const ConvGeom& cg, hipStream_t st, hi
   p.per_channel = a.rq.per_channel;
   p.acc_wrap_shift = a.acc_wrap_shift;
   p.out_mode = a.has_rq ? 0 : (a.acc16 ? 2 : 1);
-  // 64 bytes of a channel at a time go through the L2: 32-bit results always, one-byte results of images that begin at 16 bytes, 16-bit
+  // 64 bytes of a channel at a time go through the L2: 32-bit results up to 32 MB, one-byte results of images that begin at 16 bytes, 16-bit
   // ones of images that begin with a line.  Us through it and not: raw 64 -> 64 on 16 x 56 x 56 6.7, 8.1; 64 -> 64 on 64 x 56 x 56 14.6, 16.2;
   // 128 -> 128 on 64 x 28 x 28 13.1, 13.5; 32 -> 200 on 8 x 113 x 100 16.7, 15.7; 16 bits: 128 -> 128 on 64 x 28 x 28 14.45, 14.0; 64 -> 40 on 64
-  // x 19 x 20 6.8, 5.0.
+  // x 19 x 20 6.8, 5.0.  32-bit results through it and with the nontemporal hint, from the last-level cache and on buffers beyond it: 64 -> 64 on 64 x 56 x 56,
+  // 51 MB, 17.0, 17.7 and 29.1, 18.1; 128 -> 128 on 64 x 28 x 28, 26 MB, 12.3, 13.3 and 13.8, 12.7.
   const int HW = cg.H * cg.W;
-  p.through = p.out_mode == 0 ? HW % 16 == 0 && ptr_aligned(a.out, 16) : p.out_mode == 1 ? ptr_aligned(a.out, 16) : HW % 32 == 0 && ptr_aligned(a.out, 64);
+  p.through = p.out_mode == 0   ? HW % 16 == 0 && ptr_aligned(a.out, 16)
+              : p.out_mode == 1 ? ptr_aligned(a.out, 16) && (int64_t)cg.B * cg.O * HW <= 8000000 : HW % 32 == 0 && ptr_aligned(a.out, 64);
   p.act_xor4 = a.act_unsigned ? 0x80808080u : 0u;
   p.pad4 = ((((uint32_t)a.act_zero_point) ^ (a.act_unsigned ? 0x80u : 0u)) & 0xffu) * 0x01010101u;
   p.corr_coef = (a.act_unsigned ? 128 : 0) - a.act_zero_point;

@@ -442,8 +442,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void conv3x3_nchw_kernel(
 #pragma unroll
           for (int t4 = 0; t4 < 4; ++t4) {
             const int oq = oq0 + t4;
-            if (oq < O && pix < npix)
-              store16(p.through, static_cast<int32_t*>(p.out) + (obase + (uint32_t)(oq * HW + pix)), v[t4][0], v[t4][1], v[t4][2], v[t4][3]);
+            if (oq < O && pix < npix) {
+              int32_t* const dst = static_cast<int32_t*>(p.out) + (obase + (uint32_t)(oq * HW + pix));
+              const v4i r = {(int)v[t4][0], (int)v[t4][1], (int)v[t4][2], (int)v[t4][3]};
+              if (p.through) store_through(dst, r);
+              else __builtin_nontemporal_store(r, reinterpret_cast<v4i_any*>(dst));
+            }
           }
         } else {
           uint32_t dq[2][4];

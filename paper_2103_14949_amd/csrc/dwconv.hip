@@ -1009,15 +1009,16 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
     while (cg.W > 64 && segw > 12 && cg.W % segw != 0 && cg.W % segw < 4) segw -= 4;
     nsegs = (cg.W + segw - 1) / segw;
     if (segw > 12 && nband * nsegs <= 65535 && (int64_t)(cg.C + 3) / 4 * nsegs <= max_blocks(kThreads)) {
-      // Rows in pieces slow the way to memory down from 11 MB of results on.  Us of 144 channels with results left in the L2, sent
+      // Rows in pieces slow the way to memory down from 9 to 11 MB of results on, on buffers that the last-level cache does not hold from fewer on.  Us of 144 channels with results left in the L2, sent
       // through it, and by four rows: 8 x 56 x 56 4.72, 4.42, 5.2; 24 x 56 x 56, 10.8 MB, 7.51, 7.05, 6.99; 32 x 56 x 56 8.65, 9.05, 8.15; 32 x 60 x 60
       // 9.06, 9.96, 8.51; 40 x 48 x 48, 13.3 MB, 9.12, 8.83, 8.17; 26 x 52 x 52, 10.1 MB, 7.13, 6.45, 6.73; rows of 64 bytes on 16 x 64 x 64
       // 6.53, 5.30, 6.32.  Rows off dwords: 24 x 63 x 63, 13.7 MB, 8.75, 9.35; 24 x 49 x 49 7.13, 6.67; 60 x 41 x 41, 14.5 MB, 0.4 less through it.
-      // Several segments: 8 x 113 x 113 x 96 8.21, 7.31.  On buffers that the last-level cache does not hold 32 x 56 x 56 takes 11.0 left in the L2, 11.7 by
-      // four rows.
+      // Several segments: 8 x 113 x 113 x 96 8.21, 7.31.  Beyond the last-level cache (and from it): 8 x 56 x 56 5.4, 5.9, 5.9; 16 x 56 x 56 7.2, 8.6, 7.6 (6.1,
+      // 5.6, 6.3); 24 x 56 x 56 9.0, 11.2, 9.5 (7.5, 6.9, 7.1); 26 x 52 x 52 8.4, 10.5, 9.0; 32 x 56 x 56 11.0, 14.0, 11.7; 40 x 64 x 64 13.8, 14.9, 13.0 (10.6, 8.0, 9.1);
+      // 60 x 41 x 41 13.3, 16.7 (10.9, 9.7); 16 x 112 x 112 x 96 14.9, 18.5 (10.2, 9.7); 8 x 224 x 224 x 64 20.3, 25.1 (13.4, 14.2): so few pieces of large layers go through.
       const int64_t gx = (int64_t)(cg.C + 3) / 4 * nsegs, mid = nband;
       const bool large = total > 11000000;
-      const int how = !large || nsegs > 1 ? kThrough : ragged ? (cg.W <= 48 ? kThrough : kL2) : cg.W == 64 ? kThrough : kFours;
+      const int how = nsegs > 1 || ragged ? (large ? kL2 : kThrough) : cg.W == 64 || total <= 9000000 ? kThrough : kFours;
 #define HAGO_DW_ROWS(WIDE_, RAG_, OUT_)                                                                \
   (p.out_mode == 1 ? dw_rows3x3_kernel<1, false, WIDE_, RAG_>                                          \
    : p.out_mode == 2 ? dw_rows3x3_kernel<2, true, WIDE_, RAG_>                                         \
@@ -1025,7 +1026,8 @@ hipError_t launch_qconv_depthwise(const GemmArgs& a, const ConvGeom& cg, hipStre
    : codes == kFullPlain ? dw_rows3x3_kernel<0, false, WIDE_, RAG_, OUT_, kFullPlain>                  \
    : codes == kFullFlipped ? dw_rows3x3_kernel<0, false, WIDE_, RAG_, OUT_, kFullFlipped>              \
                            : dw_rows3x3_kernel<0, false, WIDE_, RAG_, OUT_>)
-      auto kern = nsegs > 1 ? (ragged ? HAGO_DW_ROWS(true, true, kThrough) : HAGO_DW_ROWS(true, false, kThrough))
+      auto kern = nsegs > 1 ? (how == kL2 ? (ragged ? HAGO_DW_ROWS(true, true, kL2) : HAGO_DW_ROWS(true, false, kL2))
+                               : (ragged ? HAGO_DW_ROWS(true, true, kThrough) : HAGO_DW_ROWS(true, false, kThrough)))
                   : ragged ? (how == kL2 ? HAGO_DW_ROWS(false, true, kL2) : HAGO_DW_ROWS(false, true, kThrough))
                            : (how == kFours ? HAGO_DW_ROWS(false, false, kFours) : HAGO_DW_ROWS(false, false, kThrough));
 #undef HAGO_DW_ROWS

@@ -87,7 +87,8 @@ __device__ __forceinline__ void fetch_arguments() {
 // 1.87 us so and 2.31 with ordinary stores, 16.8 MB 3.43 and 4.64 (nontemporal 3.75), 231 MB 35.4 and 37.3; what the same XCD reads
 // next is in its L2 either way.  Pieces of a line do not meet in the L2 first, so this is for wavefronts that write at least 64
 // aligned consecutive bytes at a time, or 128 at any address (64 bytes per quad of lanes 2.18 us, ordinary 2.34; 32 bytes 4.30,
-// 2.99; 128 bytes off four 2.35, 2.46, nontemporal 2.83).  The asm says nothing of memory: no kernel reads what it writes so.
+// 2.99; 128 bytes off four 2.35, 2.46, nontemporal 2.83).  Those are buffers that the last-level cache holds: beyond it pieces go to memory one by one, and large
+// results are better left to the L2 or the nontemporal hint (the rules stand where it is called).  The asm says nothing of memory: no kernel reads what it writes so.
 template <typename T>
 __device__ __forceinline__ void store_through(void* dst, T v) {
   static_assert(sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "one store");

@@ -355,9 +355,13 @@ __device__ __forceinline__ void qgemm_epilogue_dense_staged(const QgemmParams& p
   HAGO_STAMP(p, 5);
   uint8_t* out8 = static_cast<uint8_t*>(p.out);
   const bool ragged = q0 + BQ > p.M || p0 + BP > p.N;  // block-uniform
-  // Rows of a tile go straight to memory, so that the kernel's end has nothing to write back (4096 x 768 -> 768, 3.1 MB of results:
-  // 7.5 -> 7.2 us, nontemporal and so; 4096 x 3072 -> 768 14.8 -> 14.5), unless they are narrow and do not begin with a line.
-  const bool through = BP >= 128 || p.line_out;
+  // Up to 4 MB of results of rows of whole lines go through the L2, more and others carry the nontemporal hint, unless they are narrow and do not begin with
+  // a line.  Us through the L2 and with the hint, from the last-level cache and on buffers beyond it: 12544 x 64 -> 256 4.40, 4.60 and 4.67, 4.97; 6000 x
+  // 64 -> 512 4.00, 4.33 and 4.44, 4.74; 4096 x 768 -> 768 6.67, 6.86 and 8.06, 7.96; but 2048 x 768 -> 2304 8.86, 9.03 and 11.4, 9.7; 4096 x 768 -> 2304
+  // 11.9, 11.9 and 13.7, 12.0; 8192 x 512 -> 1536 10.9, 11.0 and 15.6, 11.5; 3000 x 768 -> 2001 10.5, 10.6 and 14.1, 11.2.  (Left in the L2 4096 x 768 -> 2304
+  // 12.7 and 14.9.)
+  const bool through = p.line_out && (uint64_t)(uint32_t)p.M * (uint32_t)p.N <= 4000000u;
+  const bool stream = BP >= 128 || p.line_out;
 #pragma unroll
   for (int s = 0; s < (BQ * CPR) / NT; ++s) {
     const int q = (int)threadIdx.x + NT * s;
@@ -368,6 +372,7 @@ __device__ __forceinline__ void qgemm_epilogue_dense_staged(const QgemmParams& p
     uint8_t* dst = out8 + (size_t)(q0 + row) * p.N + p0 + c * 16;
     if (p0 + c * 16 + 16 <= p.N) {
       if (through) store_through(dst, v);
+      else if (stream) __builtin_nontemporal_store(v, reinterpret_cast<v4i_any*>(dst));
       else *reinterpret_cast<v4i_any*>(dst) = v;  // (pieces of a line meet in L2)
     } else {  // the row's last channels
       const int left = p.N - p0 - c * 16;
